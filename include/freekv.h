@@ -208,11 +208,11 @@ int fkv_sparse_decode_attn(fkv_ctx* ctx, int32_t layer, const void* q_dev, float
 
 /* fkv_sparse_decode_attn for callers that cannot allocate device memory or hand over a workspace
  * sized for it: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same arguments, same kernels and the same result, but the split partials, their (max, sum) pairs and
- * the last-block counters live in a static device array of FKV_STATIC_SCRATCH_BYTES that the library
- * itself holds on every GPU it runs on (until the process ends), not in the caller's arena.  The call
- * allocates nothing (no hipMalloc / hipFree, no allocating library routine) and clears what must
- * start at zero with a small kernel, so it may be captured.  A shape whose partials do not fit
+ * Same arguments, same kernels and the same result, but the split partials and their (max, sum) pairs
+ * (FKV_STATIC_SCRATCH_BYTES of values, each held with a tag) and the launch number live in a static device
+ * array that the library itself holds on every GPU it runs on (until the process ends), not in the caller's
+ * arena.  The call allocates nothing (no hipMalloc / hipFree, no allocating library routine) and counts its
+ * launches on the device with a small kernel, so it may be captured.  A shape whose partials do not fit
  * (heads x splits x G x (d + 2) x 4 bytes, splits as chosen for the shape) is refused with FKV_ENOMEM
  * and a message that names both sizes.  Every call on one GPU shares that GPU's array: calls that
  * overlap in time on one GPU (different streams, different contexts) race; serialise them. */

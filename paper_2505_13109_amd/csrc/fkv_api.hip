@@ -17,12 +17,13 @@ namespace {
 
 std::string g_create_error;
 
-// Scratch of fkv_sparse_decode_attn_static (split partials, their (m, l) pairs, last-block counters):
-// one copy per GPU, held until the process ends.  In host code the array's name is only a handle;
+// Scratch of fkv_sparse_decode_attn_static (the launch number, then split partials and their (m, l) pairs, every value
+// with its tag): one copy per GPU, held until the process ends.  In host code the array's name is only a handle;
 // its device address is looked up once per device (fkv_create) and kept in g_scratch_ptr.
-constexpr size_t kStaticScratchBytes = FKV_STATIC_SCRATCH_BYTES;   // 2 MiB
+constexpr size_t kStaticScratchBytes = FKV_STATIC_SCRATCH_BYTES;   // 2 MiB of values
+constexpr size_t kStaticHead = 256;
 constexpr int kMaxDevices = 64;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticHead + 2 * kStaticScratchBytes];
 void* g_scratch_ptr[kMaxDevices] = {};
 
 struct LayerState {
@@ -39,7 +40,6 @@ struct LayerState {
   bool recall_unsubmitted = false; // its deferred recall is still in the context's list, not on the copy stream yet
   hipEvent_t recall_event = nullptr;   // what "that recall finished" is recorded in (its own ev_recall, or a later layer's)
   int recalled = 0;          // placement HOST: which heads' pending pages have been recalled (bit 0 corrected, bit 1 the others)
-  int epoch = 0;             // decode steps taken through the one-launch path (selection epochs)
   int last_launches = 0;     // kernel launches of the last fkv_decode_step (compute stream)
   int step_launches = 0;     // launches the last run_step made
   int last_grid = 0;         // grid and dynamic LDS of the last one-launch layer-step
@@ -52,9 +52,9 @@ size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 struct Layout {
   // per layer
-  size_t pool, summ, qprev, ids, slots, flags, miss, cosine, counters, tagged, layer_bytes;
+  size_t pool, summ, qprev, ids, slots, flags, miss, cosine, status, tagged, layer_bytes;
   // per context
-  size_t P, score, part_o, part_ml, dbg_page, tstamp, bmax, hmax, zsum, cand_key, cand_id, wide_cnt, ctx_bytes;
+  size_t consts, P, score, part, part_ml, launch_no, step_no, dbg_page, tstamp, exch, keyx, ctx_bytes;
   size_t total;
   size_t host_layer_bytes, host_total;
   int units_per_head, ring_base, n_ring, sel_base, max_splits, k, max_pages;
@@ -70,6 +70,8 @@ Layout make_layout(const fkv_config& c) {
   l.sel_base = l.ring_base + l.n_ring;
   l.units_per_head = c.placement == FKV_PLACE_HBM ? l.max_pages : l.sel_base + 2 * l.k;
   l.max_splits = c.sink_tokens / PG + l.k + c.window_tokens / PG + 1;
+  // most splits a KV head's attention is cut into: 32, or what a limit of 256 pages per block asks for
+  if (l.max_splits > 32) l.max_splits = l.max_splits > 32 * 256 ? (l.max_splits + 255) / 256 : 32;
   size_t o = 0;
   l.pool = o;   o += align_up((size_t)b * n_kv * l.units_per_head * UNIT_BYTES);
   l.summ = o;   o += align_up((size_t)b * n_kv * 2 * l.max_pages * D * 2);
@@ -79,23 +81,22 @@ Layout make_layout(const fkv_config& c) {
   l.flags = o;  o += align_up((size_t)b * n_kv);
   l.miss = o;   o += align_up((size_t)b * n_kv * (1 + 3 * l.k) * 4);   // per head: count, page ids, slots, positions in the picked list
   l.cosine = o; o += align_up((size_t)b * n_q * 8);
-  l.counters = o; o += align_up((size_t)(2 * b * n_kv + 1) * 4);   // last-block counters (selection, attention), then the status word
-  l.tagged = o; o += align_up((size_t)b * n_kv * (l.k > 0 ? l.k : 1) * 8);   // epoch-tagged copies of the picked ids (one-launch layer-step)
+  l.status = o; o += align_up(4);                                    // a kernel gave up a bounded wait
+  l.tagged = o; o += align_up((size_t)b * n_kv * (l.k > 0 ? l.k : 1) * 8);   // tagged copies of the picked ids (one-launch layer-step)
   l.layer_bytes = o;
   size_t p = 0;
-  l.P = p;       p += align_up((size_t)b * n_q * l.max_pages * 4);
+  l.consts = p;  p += align_up(sizeof(LayerConst));
+  l.P = p;       p += align_up((size_t)b * n_q * l.max_pages * 8);   // tagged words (or, in separate launches, fp32)
   l.score = p;   p += align_up((size_t)b * n_kv * l.max_pages * 4);
-  l.part_o = p;  p += align_up((size_t)b * n_kv * l.max_splits * (n_q / n_kv) * D * 4);
-  l.part_ml = p; p += align_up((size_t)b * n_kv * l.max_splits * (n_q / n_kv) * 2 * 4);
+  l.part = p;    p += align_up((size_t)b * n_q * l.max_splits * D * 8);
+  l.part_ml = p; p += align_up((size_t)b * n_q * l.max_splits * 2 * 8);
+  l.launch_no = p; p += align_up((size_t)b * n_kv * 4);
+  l.step_no = p; p += align_up((size_t)b * n_kv * 4);
   l.dbg_page = p; p += align_up((size_t)UNIT_BYTES);
   l.tstamp = p;  p += align_up((size_t)64 * 8);
-  // a selection spread over several blocks per head: per-head maxima and integer softmax sums, the slices' short lists
-  l.bmax = p;     p += align_up((size_t)b * n_kv * (l.max_pages / 32 + 1) * MAX_G * 4);   // one entry per scoring block of a head
-  l.hmax = p;     p += align_up((size_t)b * n_kv * MAX_G * 4);
-  l.zsum = p;     p += align_up((size_t)b * n_kv * MAX_G * 8);
-  l.cand_key = p; p += align_up((size_t)b * n_kv * WIDE_MAX_SLICES * (l.k > 0 ? l.k : 1) * 4);
-  l.cand_id = p;  p += align_up((size_t)b * n_kv * WIDE_MAX_SLICES * (l.k > 0 ? l.k : 1) * 4);
-  l.wide_cnt = p; p += align_up((size_t)b * n_kv * 4);
+  // what a head's selecting blocks exchange, and the candidates' keys
+  l.exch = p;    p += align_up((size_t)b * n_kv * EXCH_WORDS * 8);
+  l.keyx = p;    p += align_up((size_t)b * n_kv * l.max_pages * 8);
   l.ctx_bytes = p;
   l.total = l.layer_bytes * c.n_layers + l.ctx_bytes;
   l.host_layer_bytes = c.placement == FKV_PLACE_HOST ? (size_t)b * n_kv * l.max_pages * UNIT_BYTES : 0;
@@ -126,18 +127,7 @@ const char* check_config(const fkv_config* c) {
 }
 
 Geom make_geom(const fkv_config& c, int L) {
-  Geom g;
-  g.L = L;
-  g.n_full = L / PG;
-  g.r = L % PG;
-  g.n_sink = c.sink_tokens / PG < g.n_full ? c.sink_tokens / PG : g.n_full;
-  const int rest = g.n_full - g.n_sink;
-  g.n_win = c.window_tokens / PG < rest ? c.window_tokens / PG : rest;
-  g.cand_lo = g.n_sink;
-  g.n_cand = g.n_full - g.n_sink - g.n_win;
-  const int k = (c.budget_tokens - c.sink_tokens - c.window_tokens) / PG;
-  g.k_eff = k < g.n_cand ? k : g.n_cand;
-  return g;
+  return geom_of(L, c.sink_tokens / PG, c.window_tokens / PG, (c.budget_tokens - c.sink_tokens - c.window_tokens) / PG);
 }
 
 }  // namespace
@@ -190,14 +180,33 @@ struct fkv_ctx {
   uint8_t* flags(int l) const { return reinterpret_cast<uint8_t*>(layer_base(l) + lay.flags); }
   int32_t* miss(int l) const { return reinterpret_cast<int32_t*>(layer_base(l) + lay.miss); }
   double* cosine(int l) const { return reinterpret_cast<double*>(layer_base(l) + lay.cosine); }
-  int* sel_counters(int l) const { return reinterpret_cast<int*>(layer_base(l) + lay.counters); }
-  int* attn_counters(int l) const { return reinterpret_cast<int*>(layer_base(l) + lay.counters) + cfg.batch * cfg.n_kv_heads; }
   unsigned long long* tagged(int l) const { return reinterpret_cast<unsigned long long*>(layer_base(l) + lay.tagged); }
-  int* status(int l) const { return reinterpret_cast<int*>(layer_base(l) + lay.counters) + 2 * cfg.batch * cfg.n_kv_heads; }
-  float* P() const { return reinterpret_cast<float*>(ctx_base() + lay.P); }
+  int* status(int l) const { return reinterpret_cast<int*>(layer_base(l) + lay.status); }
+  unsigned long long* words(size_t off) const { return reinterpret_cast<unsigned long long*>(ctx_base() + off); }
   float* score() const { return reinterpret_cast<float*>(ctx_base() + lay.score); }
-  float* part_o() const { return reinterpret_cast<float*>(ctx_base() + lay.part_o); }
-  float* part_ml() const { return reinterpret_cast<float*>(ctx_base() + lay.part_ml); }
+  int* step_no() const { return reinterpret_cast<int*>(ctx_base() + lay.step_no); }
+  int* launch_no() const { return reinterpret_cast<int*>(ctx_base() + lay.launch_no); }
+  const LayerConst* consts() const { return reinterpret_cast<const LayerConst*>(ctx_base() + lay.consts); }
+  LayerConst make_consts() const {
+    auto o = [](size_t bytes) { return (uint32_t)(bytes / 256); };
+    LayerConst c{};
+    c.dev_base = dev; c.layer_bytes = lay.layer_bytes;
+    c.o_summ = o(lay.summ); c.o_qprev = o(lay.qprev); c.o_ids = o(lay.ids); c.o_slots = o(lay.slots); c.o_flags = o(lay.flags);
+    c.o_miss = o(lay.miss); c.o_cosine = o(lay.cosine); c.o_status = o(lay.status); c.o_tagged = o(lay.tagged);
+    c.qprev_half = cfg.batch * cfg.n_q_heads * D;
+    c.ids_half = cfg.batch * cfg.n_kv_heads * (lay.k > 0 ? lay.k : 1);
+    c.heads = cfg.batch * cfg.n_kv_heads; c.n_kv = cfg.n_kv_heads; c.k = lay.k; c.max_pages = lay.max_pages; c.max_splits = lay.max_splits;
+    c.n_sink = cfg.sink_tokens / PG; c.n_win = cfg.window_tokens / PG;
+    c.units_per_head = lay.units_per_head; c.ring_base = lay.ring_base; c.n_ring = lay.n_ring; c.sel_base = lay.sel_base;
+    c.corr_pool = cfg.corr_pooling; c.sel_pool = cfg.select_pooling; c.tau = cfg.tau;
+    c.P = words(lay.P); c.part = words(lay.part); c.part_ml = words(lay.part_ml); c.exch = words(lay.exch); c.keyx = words(lay.keyx);
+    c.score = score();
+    c.host_base = host; c.host_layer_bytes = lay.host_layer_bytes;
+    c.tstamp = tstamp();
+    return c;
+  }
+  uint32_t launches = 0;              // launches with tagged exchanges so far (fkv_device.h: host_tag)
+  bool P_tagged = false;              // the format of the page weights the last scoring launch left
   uint16_t* dbg_page() const { return reinterpret_cast<uint16_t*>(ctx_base() + lay.dbg_page); }
   bool lose_selection = false;   // fkv_test_lose_selection: corrected heads' attention waits in vain (tests the bounded wait)
   bool stamp_on = false;   // fkv_instrument_timestamps: kernels record phase timestamps of head 0 (debugging aid)
@@ -250,6 +259,8 @@ static int after_launch(fkv_ctx* ctx, const char* what) {
   return FKV_OK;
 }
 
+static uint32_t next_launch(fkv_ctx* ctx) { return ++ctx->launches & 0x7fffffffu; }
+
 // One launch of the step kernel with the given roles (append / correction test / selection).
 static StepIO make_step_io(fkv_ctx* ctx, int layer, const void* q, const void* k_new, const void* v_new,
                            uint8_t* flags_user, int32_t* ids_user) {
@@ -267,20 +278,16 @@ static StepIO make_step_io(fkv_ctx* ctx, int layer, const void* q, const void* k
   io.flags = ctx->flags(layer);
   io.flags_user = flags_user;
   io.cosine = ctx->cosine(layer);
-  io.P = ctx->P();
+  io.P = ctx->words(ctx->lay.P);
   io.score = ctx->score();
   io.ids = ctx->ids(layer, ls.parity);
   io.ids_user = ids_user;
-  io.counters = ctx->sel_counters(layer);
+  io.exch = ctx->words(ctx->lay.exch);
+  io.keyx = ctx->words(ctx->lay.keyx);
+  io.launch_no = ctx->step_no();
+  io.status = ctx->status(layer);
+  io.P_tagged = &ctx->P_tagged;
   io.tstamp = ctx->tstamp();
-  char* cb = ctx->ctx_base();
-  io.bmax = reinterpret_cast<float*>(cb + ctx->lay.bmax);
-  io.bmax_stride = ctx->lay.max_pages / 32 + 1;
-  io.hmax = reinterpret_cast<float*>(cb + ctx->lay.hmax);
-  io.zsum = reinterpret_cast<unsigned long long*>(cb + ctx->lay.zsum);
-  io.cand_key = reinterpret_cast<uint32_t*>(cb + ctx->lay.cand_key);
-  io.cand_id = reinterpret_cast<int32_t*>(cb + ctx->lay.cand_id);
-  io.wide_counters = reinterpret_cast<int*>(cb + ctx->lay.wide_cnt);
   if (ctx->cfg.placement == FKV_PLACE_HOST) {      // a selection comes with its recall plan
     io.plan_act_ids = ctx->ids(layer, ls.parity ^ 1);
     io.plan_act_slots = ctx->slots(layer, ls.parity ^ 1);
@@ -290,11 +297,34 @@ static StepIO make_step_io(fkv_ctx* ctx, int layer, const void* q, const void* k
   return io;
 }
 
+static AttnIO make_attn_io(fkv_ctx* ctx, int layer, const void* q, float* out, int use) {
+  const LayerState& ls = ctx->layers[layer];
+  AttnIO io{};
+  io.q = static_cast<const uint16_t*>(q);
+  io.act_ids = ctx->ids(layer, ls.parity ^ 1);
+  io.new_ids = ctx->ids(layer, ls.parity);
+  io.act_slots = ctx->slots(layer, ls.parity ^ 1);
+  io.new_slots = ctx->slots(layer, ls.parity);
+  io.flags = ctx->flags(layer);
+  io.use = use;
+  io.part = ctx->words(ctx->lay.part);
+  io.part_ml = ctx->words(ctx->lay.part_ml);
+  io.max_splits = ctx->lay.max_splits;
+  io.launch_no = ctx->launch_no();
+  io.launch_stride = 1;
+  io.status = ctx->status(layer);
+  io.out = out;
+  io.tstamp = ctx->tstamp();
+  return io;
+}
+
 static int run_step(fkv_ctx* ctx, int layer, int roles, const void* q, const void* k_new, const void* v_new,
                     uint8_t* flags_user, int32_t* ids_user, int L_after, hipStream_t st) {
   const StepIO io = make_step_io(ctx, layer, q, k_new, v_new, flags_user, ids_user);
   LayerState& ls = ctx->layers[layer];
-  ls.step_launches = launch_step(ctx->dims, roles, io, make_geom(ctx->cfg, L_after), st);
+  const int n = launch_step(ctx->dims, roles, io, make_geom(ctx->cfg, L_after), st);
+  if (n < 0) return ctx->fail(FKV_EHIP, "the device refused the selection's LDS");
+  ls.step_launches = n;
   if ((roles & ROLE_SELECT) && io.plan_new_slots) ls.recalled = 0;     // a new plan: nothing of it is recalled yet
   return after_launch(ctx, "step kernel");
 }
@@ -455,6 +485,8 @@ int fkv_create(const fkv_config* cfg, void* dev_arena, size_t dev_bytes, void* h
     e = hipMemset(ctx->ids(i, 0), 0xff, n);
     if (e != hipSuccess) break;
   }
+  const LayerConst consts = ctx->make_consts();
+  if (e == hipSuccess) e = hipMemcpy(ctx->ctx_base() + l.consts, &consts, sizeof(consts), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     g_create_error = std::string("HIP failure in fkv_create: ") + hipGetErrorString(e);
@@ -682,10 +714,7 @@ int fkv_sparse_decode_attn(fkv_ctx* ctx, int32_t layer, const void* q_dev, float
     e0 = ctx->prof_ev[ctx->prof_used++];
     e1 = ctx->prof_ev[ctx->prof_used++];
   }
-  launch_attn(ctx->dims, ctx->pool_desc(layer), static_cast<const uint16_t*>(q_dev), ctx->ids(layer, ls.parity ^ 1),
-              ctx->ids(layer, ls.parity), ctx->slots(layer, ls.parity ^ 1), ctx->slots(layer, ls.parity),
-              ctx->flags(layer), use, ctx->part_o(), ctx->part_ml(), ctx->lay.max_splits, ctx->attn_counters(layer),
-              out_dev, g, st, e0, e1, ctx->tstamp());
+  launch_attn(ctx->dims, ctx->pool_desc(layer), make_attn_io(ctx, layer, q_dev, out_dev, use), g, st, e0, e1);
   return after_launch(ctx, "attention kernels");
 }
 
@@ -719,13 +748,17 @@ int fkv_sparse_decode_attn_static(fkv_ctx* ctx, int32_t layer, const void* q_dev
   hipStream_t st = static_cast<hipStream_t>(stream);
   int rcw = wait_recall(ctx, ls, st);
   if (rcw) return rcw;
-  // the array keeps the last call's contents: the counters must start at zero (a fill kernel, not a
-  // memset node, so that the call can be captured into a graph)
-  launch_fill_zero(reinterpret_cast<int*>(base), heads, st);
-  launch_attn(ctx->dims, ctx->pool_desc(layer), static_cast<const uint16_t*>(q_dev), ctx->ids(layer, ls.parity ^ 1),
-              ctx->ids(layer, ls.parity), ctx->slots(layer, ls.parity ^ 1), ctx->slots(layer, ls.parity),
-              ctx->flags(layer), use, reinterpret_cast<float*>(base + b_cnt + b_ml), reinterpret_cast<float*>(base + b_cnt),
-              n_splits, reinterpret_cast<int*>(base), out_dev, g, st, nullptr, nullptr, nullptr);
+  // the array keeps the last call's contents, so this call's words get a tag of their own: the next number, counted on
+  // the device, so that a call captured into a graph has a new one at every replay
+  launch_next_number(reinterpret_cast<int*>(base), st);
+  AttnIO io = make_attn_io(ctx, layer, q_dev, out_dev, use);
+  io.part_ml = reinterpret_cast<unsigned long long*>(base + kStaticHead);
+  io.part = reinterpret_cast<unsigned long long*>(base + kStaticHead + 2 * b_ml);
+  io.max_splits = n_splits;
+  io.launch_no = reinterpret_cast<int*>(base);
+  io.launch_stride = 0;
+  io.tstamp = nullptr;
+  launch_attn(ctx->dims, ctx->pool_desc(layer), io, g, st, nullptr, nullptr);
   return after_launch(ctx, "attention kernels (static scratch)");
 }
 
@@ -819,19 +852,19 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
       FKV_HIP(ctx, hipStreamWaitEvent(st, ls.ev_offload, 0));
       ls.offload_unseen = false;
     }
-    const StepIO io = make_step_io(ctx, layer, q_dev, k_new_dev, v_new_dev, nullptr, nullptr);
     LayerIO lio{};
-    lio.act_ids = ctx->ids(layer, ls.parity ^ 1);
-    lio.part_o = ctx->part_o();
-    lio.part_ml = ctx->part_ml();
-    lio.max_splits = ctx->lay.max_splits;
-    lio.attn_counters = ctx->attn_counters(layer);
+    lio.consts = ctx->consts();
+    lio.layer = layer;
+    lio.parity = ls.parity;
+    lio.have_prev = ls.have_prev_q ? 1 : 0;
+    lio.q = static_cast<const uint16_t*>(q_dev);
+    lio.k_new = static_cast<const uint16_t*>(k_new_dev);
+    lio.v_new = static_cast<const uint16_t*>(v_new_dev);
     lio.out = out_dev;
-    lio.host_pool = host_pool ? ctx->host_pool(layer) : nullptr;
-    lio.tagged = ctx->tagged(layer);
-    lio.epoch = ls.epoch + 1;
-    lio.status = ctx->status(layer);
-    lio.attn_epoch_bias = ctx->lose_selection ? 1 : 0;
+    lio.launch = next_launch(ctx);
+    lio.host_pool = host_pool;
+    lio.max_splits = ctx->lay.max_splits;
+    lio.lose_selection = ctx->lose_selection;
     lio.launch_grid = &ls.last_grid;
     lio.launch_lds = &ls.last_lds;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -840,11 +873,11 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
       e1 = ctx->prof_ev[ctx->prof_used + 1];
       (void)hipEventRecord(e0, st);
     }
-    if (launch_layer(ctx->dims, io, lio, make_geom(ctx->cfg, ls.L + 1), st)) {
+    if (launch_layer(ctx->dims, lio, make_geom(ctx->cfg, ls.L + 1), st)) {
+      ctx->P_tagged = true;
       if (e0) { (void)hipEventRecord(e1, st); ctx->prof_used += 2; }
       rc = after_launch(ctx, "layer kernel");
       if (rc) return rc;
-      ls.epoch += 1;
       ls.last_launches = 1;
       ls.step_launches = 1;
       ls.staged_q = ls.have_flags = ls.have_pending = true;
@@ -926,6 +959,9 @@ int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on) {
 int fkv_instrument_timestamps(fkv_ctx* ctx, int32_t on) {
   if (!ctx) return FKV_EINVAL;
   ctx->stamp_on = on != 0;
+  const LayerConst consts = ctx->make_consts();
+  FKV_HIP(ctx, hipDeviceSynchronize());
+  FKV_HIP(ctx, hipMemcpy(ctx->ctx_base() + ctx->lay.consts, &consts, sizeof(consts), hipMemcpyHostToDevice));
   return FKV_OK;
 }
 
@@ -974,10 +1010,8 @@ int fkv_profile_attn(fkv_ctx* ctx, const void* q_dev, size_t q_layer_stride, flo
   for (int r = 0; r < reps; ++r) {
     for (int l = 0; l < ctx->cfg.n_layers; ++l, ++n) {
       const LayerState& ls = ctx->layers[l];
-      launch_attn(ctx->dims, ctx->pool_desc(l), reinterpret_cast<const uint16_t*>(static_cast<const char*>(q_dev) + q_layer_stride * l),
-                  ctx->ids(l, ls.parity ^ 1), ctx->ids(l, ls.parity), ctx->slots(l, ls.parity ^ 1), ctx->slots(l, ls.parity),
-                  ctx->flags(l), FKV_USE_ACTIVE, ctx->part_o(), ctx->part_ml(), ctx->lay.max_splits, ctx->attn_counters(l),
-                  out_dev, make_geom(ctx->cfg, ls.L), st, nullptr, nullptr, nullptr);
+      launch_attn(ctx->dims, ctx->pool_desc(l), make_attn_io(ctx, l, static_cast<const char*>(q_dev) + q_layer_stride * l, out_dev, FKV_USE_ACTIVE),
+                  make_geom(ctx->cfg, ls.L), st, nullptr, nullptr);
     }
   }
   FKV_HIP(ctx, hipEventRecord(e1, st));
@@ -1009,7 +1043,9 @@ int fkv_profile_select(fkv_ctx* ctx, const void* q_dev, size_t q_layer_stride, i
   for (int r = 0; r < reps; ++r) {
     for (int l = 0; l < ctx->cfg.n_layers; ++l) {
       const StepIO io = make_step_io(ctx, l, static_cast<const char*>(q_dev) + q_layer_stride * l, nullptr, nullptr, nullptr, nullptr);
-      n += launch_step(ctx->dims, ROLE_SELECT, io, make_geom(ctx->cfg, ctx->layers[l].L), st);
+      const int m = launch_step(ctx->dims, ROLE_SELECT, io, make_geom(ctx->cfg, ctx->layers[l].L), st);
+      if (m < 0) return ctx->fail(FKV_EHIP, "the device refused the selection's LDS");
+      n += m;
     }
   }
   FKV_HIP(ctx, hipEventRecord(e1, st));
@@ -1065,7 +1101,16 @@ int fkv_debug_read(fkv_ctx* ctx, int32_t layer, int32_t what, void* host_out, si
   size_t n = 0;
   switch (what) {
     case FKV_DBG_SUMMARIES:   src = ctx->summ(layer); n = (size_t)c.batch * c.n_kv_heads * 2 * ctx->lay.max_pages * D * 2; break;
-    case FKV_DBG_WEIGHTS:     src = ctx->P(); n = (size_t)c.batch * c.n_q_heads * ctx->lay.max_pages * 4; break;
+    case FKV_DBG_WEIGHTS: {
+      n = (size_t)c.batch * c.n_q_heads * ctx->lay.max_pages * 4;
+      if (!ctx->P_tagged) { src = ctx->words(ctx->lay.P); break; }
+      if (bytes < n) return ctx->fail(FKV_EINVAL, "output buffer too small");
+      FKV_HIP(ctx, hipDeviceSynchronize());
+      std::vector<unsigned long long> tmp(n / 4);
+      FKV_HIP(ctx, hipMemcpy(tmp.data(), ctx->words(ctx->lay.P), n * 2, hipMemcpyDeviceToHost));
+      for (size_t i = 0; i < tmp.size(); ++i) static_cast<uint32_t*>(host_out)[i] = (uint32_t)tmp[i];
+      return FKV_OK;
+    }
     case FKV_DBG_SCORES:      src = ctx->score(); n = (size_t)c.batch * c.n_kv_heads * ctx->lay.max_pages * 4; break;
     case FKV_DBG_ACTIVE_IDS:  src = ctx->ids(layer, ls.parity ^ 1); n = (size_t)c.batch * c.n_kv_heads * kk * 4; break;
     case FKV_DBG_PENDING_IDS: src = ctx->ids(layer, ls.parity); n = (size_t)c.batch * c.n_kv_heads * kk * 4; break;

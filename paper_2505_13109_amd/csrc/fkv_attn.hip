@@ -1,31 +1,41 @@
 // Stand-alone launch of sparse decode attention (device code in fkv_attn_dev.h).
 #include "fkv_attn_dev.h"
 
+#include <algorithm>
+
 namespace fkv {
 
-// grid (n_splits, n_kv, batch); NW wavefronts per block
+// grid (n_splits, heads); NW wavefronts per block
 template <int DT, int NW>
-__global__ __launch_bounds__(NW * 64) void attn_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[NW > 1 ? NW * (32 + MAX_G * D) : 1];
-  attn_block<DT, NW>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void attn_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float attn_lds[];
+  touch_args<sizeof(AttnArgs)>();
+  attn_block<DT, NW, false, false>(a, blockIdx.x, blockIdx.y, attn_lds);
 }
 
 // experiment builds only (see knob()): pages per block (0 = choose from the shape)
 static const int g_pps_override = knob("FKV_ATTN_PPS", 0);
 
-// pages per block of NW waves for a head with n_att attended pages
-int attn_pages_per_block(int n_att, int heads, int max_splits, int nw) {
+// pages per block of nw waves for a head with n_att attended pages; max_blocks: most blocks of a launch in which a head has
+// more than one
+int attn_pages_per_block(int n_att, int heads, int max_splits, int nw, int max_blocks) {
   // a page per wave and pass; more pages per block (the page loop is pipelined, the merge gets
   // cheaper) as long as the launch keeps at least ~128 blocks, and never more than 32 splits
-  // per KV head beyond that, so that the merge needs one round trip
+  // per KV head beyond that, so that the merge needs few round trips
+  const int most = 64 * nw;                         // a wave looks up its positions with one load, one per lane
   int pps = nw;
   while (pps < 16 && (long)heads * ((n_att + pps * 2 - 1) / (pps * 2)) >= 128) pps *= 2;
-  while ((n_att + pps - 1) / pps > 32 && (long)heads * ((n_att + pps * 2 - 1) / (pps * 2)) >= 128) pps *= 2;
+  while ((n_att + pps - 1) / pps > 32 && (long)heads * ((n_att + pps * 2 - 1) / (pps * 2)) >= 128 && pps < most) pps *= 2;
   // With many heads the launch is bandwidth-bound and what counts is the fixed cost of a block
-  // (its partial, the counter, the merge): measured best at about one block per compute unit,
+  // (its partial, the exchange, the merge): measured best at about one block per compute unit,
   // down to one block per head.
-  while (pps < n_att && (long)heads * ((n_att + pps * 2 - 1) / (pps * 2)) >= 256) pps *= 2;
-  while ((n_att + pps - 1) / pps > (max_splits < MAX_MERGE_SPLITS ? max_splits : MAX_MERGE_SPLITS)) pps *= 2;
+  while (pps < n_att && pps < most && (long)heads * ((n_att + pps * 2 - 1) / (pps * 2)) >= 256) pps *= 2;
+  // (4-wave blocks fit four to a unit; of long lists, one block to a unit streams better: 248 heads of 129 pages 117.7 us in one
+  // split, 120.6 in two)
+  if (nw == 4 && n_att <= 96) max_blocks *= 2;
+  const int most_splits = std::max(1, std::min(max_splits, max_blocks / heads));
+  if ((n_att + pps - 1) / pps > most_splits) pps = std::min((n_att + most_splits - 1) / most_splits, std::max(pps, most));
+  while ((n_att + pps - 1) / pps > max_splits) pps *= 2;
   if (pps > 16) {                                   // long blocks: split the head evenly
     const int n_splits = (n_att + pps - 1) / pps;
     pps = (n_att + n_splits - 1) / n_splits;
@@ -34,42 +44,27 @@ int attn_pages_per_block(int n_att, int heads, int max_splits, int nw) {
   return pps;
 }
 
-int launch_attn(const Dims& d, const PoolDesc& pd, const uint16_t* q, const int32_t* act_ids,
-                const int32_t* new_ids, const int32_t* act_slots, const int32_t* new_slots,
-                const uint8_t* flags, int use, float* part_o, float* part_ml, int max_splits,
-                int* counters, float* out, Geom g, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end,
-                long long* tstamp) {
-  const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
+void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end) {
+  const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0), heads = d.n_kv * d.batch;
   AttnArgs a{};
-  a.pd = pd; a.q = q; a.act_ids = act_ids; a.new_ids = new_ids; a.act_slots = act_slots; a.new_slots = new_slots;
-  a.flags = flags; a.use = use; a.part_o = part_o; a.part_ml = part_ml; a.max_splits = max_splits;
-  a.pps = attn_pages_per_block(n_att, d.n_kv * d.batch, max_splits, 4);
+  a.pd = pd; a.q = io.q; a.act_ids = io.act_ids; a.new_ids = io.new_ids; a.act_slots = io.act_slots; a.new_slots = io.new_slots;
+  a.flags = io.flags; a.use = io.use; a.part = io.part; a.part_ml = io.part_ml; a.max_splits = io.max_splits;
+  a.launch_no = io.launch_no; a.launch_stride = io.launch_stride;
+  a.pps = attn_pages_per_block(n_att, heads, io.max_splits, 4);
   a.n_splits = (n_att + a.pps - 1) / a.pps;
-  a.counters = counters; a.out = out; a.g = g; a.n_q = d.n_q; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k;
-  a.tstamp = tstamp; a.fused = 0;
-  const int nw = a.pps >= 4 ? 4 : a.pps;
-  dim3 grid(a.n_splits, d.n_kv, d.batch);
+  a.share = (d.G * D + a.n_splits - 1) / a.n_splits;
+  a.out = io.out; a.g = g; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k; a.status = io.status; a.tstamp = io.tstamp;
+  dim3 grid(a.n_splits, heads);
+  constexpr int NW = 4;
+  const size_t lds = attn_lds_floats(NW, d.G) * sizeof(float);
   if (ev_begin) (void)hipEventRecord(ev_begin, st);
-  if (d.dtype == 0) {
-    if (nw == 1)      attn_kernel<0, 1><<<grid, 64, 0, st>>>(a);
-    else if (nw == 2) attn_kernel<0, 2><<<grid, 128, 0, st>>>(a);
-    else              attn_kernel<0, 4><<<grid, 256, 0, st>>>(a);
-  } else {
-    if (nw == 1)      attn_kernel<1, 1><<<grid, 64, 0, st>>>(a);
-    else if (nw == 2) attn_kernel<1, 2><<<grid, 128, 0, st>>>(a);
-    else              attn_kernel<1, 4><<<grid, 256, 0, st>>>(a);
-  }
+  if (d.dtype == 0) attn_kernel<0, NW><<<grid, NW * 64, lds, st>>>(a);
+  else              attn_kernel<1, NW><<<grid, NW * 64, lds, st>>>(a);
   if (ev_end) (void)hipEventRecord(ev_end, st);
-  return a.n_splits;
 }
 
-__global__ __launch_bounds__(256) void fill_zero_kernel(int* __restrict__ p, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-void launch_fill_zero(int* p, int n, hipStream_t st) {
-  if (n > 0) fill_zero_kernel<<<(n + 255) / 256, 256, 0, st>>>(p, n);
-}
+__global__ void next_number_kernel(int* __restrict__ p) { *p += 1; }
+void launch_next_number(int* p, hipStream_t st) { next_number_kernel<<<1, 1, 0, st>>>(p); }
 
 // ---------------------------------------------------------------------------------
 // The pages a head attends, converted to the NHD layout of the paper's hybrid layouts
@@ -93,7 +88,6 @@ __global__ __launch_bounds__(256) void export_nhd_kernel(AttnArgs a, uint16_t* _
   al.ids = (pending ? a.new_ids : a.act_ids) + (size_t)head * k;
   al.slots = a.pd.placement == 0 ? nullptr : (pending ? a.new_slots : a.act_slots) + (size_t)head * k;
   al.n_sink = g.n_sink; al.k = k; al.n_win = g.n_win; al.n_full = g.n_full; al.r = g.r;
-  al.coherent_ids = false;
   const int n_att = g.n_sink + k + g.n_win + (g.r > 0 ? 1 : 0);
   int n_valid = 0, page = -1, unit = -1;
   if (slot < n_att) unit = attend_unit(al, a.pd, slot, n_valid, page);
@@ -140,7 +134,7 @@ void launch_export_nhd(const Dims& d, const PoolDesc& pd, const int32_t* act_ids
                        uint16_t* out, int32_t* slot_pages, int n_slots, Geom g, hipStream_t st, const int32_t* skip_missing) {
   AttnArgs a{};
   a.pd = pd; a.act_ids = act_ids; a.new_ids = new_ids; a.act_slots = act_slots; a.new_slots = new_slots;
-  a.flags = flags; a.use = use; a.g = g; a.n_q = d.n_q; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k;
+  a.flags = flags; a.use = use; a.g = g; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k;
   dim3 grid(n_slots, d.n_kv, d.batch);
   export_nhd_kernel<<<grid, 256, 0, st>>>(a, out, slot_pages, n_slots, skip_missing);
 }

@@ -1,6 +1,6 @@
 // Device code of sparse decode attention over sink + picked pages + window + open page
-// (Sec. 2.1), split over pages with an online softmax; the block that finishes a KV head last
-// does the log-sum-exp merge of its splits.
+// (Sec. 2.1), split over pages with an online softmax; a head's blocks share the
+// log-sum-exp merge of its splits.
 //
 // One wavefront owns one 32-token page at a time and keeps everything in registers:
 //   S^T[32 tok x 16] = K[32 x 128] . Q^T[128 x 16]       8 x v_mfma_f32_16x16x32
@@ -10,14 +10,23 @@
 // product holding the logits of head g for tokens {rb*4+i, 16+rb*4+i}: exactly the 8
 // tokens the same lane must supply as the B operand of the second product (the V page
 // is stored in that token order).  Nothing goes through LDS inside the page loop.
+//
+// What bounds it.  A large launch: the bytes of the pages.  A small one (a request or a few): the chain of dependent
+// steps -- page ids, pages, the block's combine, the exchange between the head's blocks, the merge -- each a round trip.
+// So every step is entered as early as what it depends on allows: a wave looks up all its positions' ids with one load
+// and requests its first page before the correction test is made; the block combines its waves behind one barrier; and
+// the partial results are exchanged as tagged words (st_tag), one trip instead of store, counter and read.
 #pragma once
 #include "fkv_device.h"
 
 namespace fkv {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 template <int DT> struct Mma;
 template <> struct Mma<0> {
@@ -34,30 +43,52 @@ template <> struct Mma<0> {
       lo[e] = (_Float16)(p[e] - (float)h);
     }
   }
+  static __device__ __forceinline__ float add_pair(uint32_t w, float c) {
+    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+    return __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, w), f16x2{(_Float16)1.0f, (_Float16)1.0f}, c, false);
+  }
 };
 template <> struct Mma<1> {
   typedef bf16x8 vec;
   static __device__ __forceinline__ f32x4 mma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ uint16_t rne(float x) {
-    const uint32_t u = __float_as_uint(x);
-    return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+  // pairs, so that the conversions are the packed ones (round to nearest even)
+  static __device__ __forceinline__ uint32_t pack(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
   }
   static __device__ __forceinline__ void split(const float* p, vec& hi, vec& lo) {
+    u32x4 h, l;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint16_t h = rne(p[e]);
-      const float hf = __uint_as_float(((uint32_t)h) << 16);
-      hi[e] = __builtin_bit_cast(__bf16, h);
-      lo[e] = __builtin_bit_cast(__bf16, rne(p[e] - hf));
+    for (int e = 0; e < 4; ++e) {
+      h[e] = pack(p[2 * e], p[2 * e + 1]);
+      l[e] = pack(p[2 * e] - __uint_as_float(h[e] << 16), p[2 * e + 1] - __uint_as_float(h[e] & 0xffff0000u));
     }
+    hi = __builtin_bit_cast(vec, h);
+    lo = __builtin_bit_cast(vec, l);
+  }
+  static __device__ __forceinline__ float add_pair(uint32_t w, float c) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), bf16x2{(__bf16)1.0f, (__bf16)1.0f}, c, false);
   }
 };
 
+// over the four 16-lane rows of a wave: row pairs, then halves, by the row-swapping moves (no LDS traffic)
+__device__ __forceinline__ float max_over_rows(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float sum_over_rows(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-constexpr int MAX_MERGE_SPLITS = 256;   // upper bound on splits per KV head
+constexpr int SELECTION_LOST = -2;      // a page id no list holds: the selection that should have made it gave up a wait
 
 struct AttnArgs {
   PoolDesc pd;
@@ -68,50 +99,46 @@ struct AttnArgs {
   const int32_t* new_slots;
   const uint8_t* flags;
   int use;                   // FKV_USE_*: 0 active, 1 pending, 2 by flag
-  float* part_o;
-  float* part_ml;
+  unsigned long long* part;  // [heads][max_splits][G][D] tagged partial outputs, then [heads][max_splits][G][2] tagged (max, sum)
+  unsigned long long* part_ml;
   int max_splits, pps, n_splits;
-  int* counters;
+  int share;                 // outputs of a head that each of its blocks finishes
+  int* launch_no;            // stand-alone attention: number of the last launch, per head (stride 1: moved on here)
+  int launch_stride;         //   or one for all heads (stride 0: moved on by a kernel of its own)
   float* out;
   Geom g;
-  int n_q, n_kv, G, k;
+  int n_kv, G, k;
+  int* status;               // set to 1 if a wait ran out
   long long* tstamp;
   // --- when attention shares its launch with the step roles ("fused") ---
-  int fused;                 // flags are recomputed here, the new token is taken from k_new/v_new,
-                             // a corrected head waits for its selection
+  // flags are recomputed here, the new token is taken from k_new/v_new, a corrected head waits for its selection
   const uint16_t* q_prev;
   int have_prev;
   float tau;
   int corr_pool;
   const uint16_t* k_new;
   const uint16_t* v_new;
-  const unsigned long long* tagged;   // [heads][k]: this step's picked ids as (epoch << 32 | id), written by the selection
-  int epoch;
-  int* status;               // set to 1 if a wait ran out
+  const unsigned long long* tagged;   // [heads][k]: this step's picked ids, tagged, written by the selection
+  uint32_t tag;              // tag of this launch
+  uint32_t pick_tag;         // tag the picked ids are waited for with: the same (a test of the bounded wait asks for another)
   // fused, KV in a host pool: the tagged words are tagged_pick() values; a corrected head's wave copies a missing page
   // from the host pool into its slot while it attends over it
   const uint16_t* host_pool; // [heads][max_pages] units
   int max_pages;
 };
 
-template <int CH> struct MergeChunk { static constexpr int value = CH; };
-
 // position i of a head's attend list -> HBM unit, page id and number of valid tokens; -1 if empty
 struct AttendList {
   const int32_t* ids;
   const int32_t* slots;
   int n_sink, k, n_win, n_full, r;
-  bool coherent_ids;         // ids written earlier in this very launch: read them at device scope
 };
-// have_id: the page id of position i was fetched earlier (`id`), do not load it again
-__device__ __forceinline__ int attend_unit(const AttendList& al, const PoolDesc& pd, int i, int& n_valid, int& page,
-                                           bool have_id = false, int id_in = -1) {
+__device__ __forceinline__ int attend_unit(const AttendList& al, const PoolDesc& pd, int i, int& n_valid, int& page) {
   n_valid = PG;
   if (i < al.n_sink) { page = i; return i; }
   i -= al.n_sink;
   if (i < al.k) {
-    const int id = have_id ? id_in
-                 : al.coherent_ids ? __hip_atomic_load(al.ids + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : al.ids[i];
+    const int id = al.ids[i];
     page = id;
     if (id < 0) return -1;
     return pd.placement == 0 ? id : pd.sel_base + al.slots[i];
@@ -119,255 +146,284 @@ __device__ __forceinline__ int attend_unit(const AttendList& al, const PoolDesc&
   i -= al.k;
   if (i < al.n_win) page = al.n_full - al.n_win + i;
   else { page = al.n_full; n_valid = al.r; }
-  if (pd.placement == 0) return page;
-  return page < pd.ring_base ? page : pd.ring_base + page % pd.n_ring;
+  return resident_unit(pd, page);
 }
 
-// One block of NW wavefronts: attend-list positions [split*pps, (split+1)*pps) of head (b, m),
-// wave w takes w, w+NW, ...  `lds` is at least NW*(32 + G*128) floats when NW > 1.
-// HOSTFUSED: the variant for a fused launch with the KV in a host pool (a compile-time choice: what it adds to the page
-// loop would cost the other launches registers).
-template <int DT, int NW, bool HOSTFUSED = false>
-__device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int m, int b, float* lds) {
+// floats of LDS that a block of NW waves needs
+__host__ __device__ constexpr int attn_lds_floats(int NW, int G) { return NW * G * (D + 4) + NW * 32 + G * (D / 2 + 4); }
+
+// One block of NW wavefronts: attend-list positions [split*pps, (split+1)*pps) of `head`,
+// wave w takes w, w+NW, ...  `lds`: attn_lds_floats(NW, G) floats, 16-byte aligned.
+// FUSED: in a launch with the step roles; HOSTFUSED: that, with the KV in a host pool (compile-time choices: what they
+// add to the page loop would cost the other launches registers).
+template <int DT, int NW, bool FUSED, bool HOSTFUSED>
+__device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int head, float* lds) {
   typedef typename Mma<DT>::vec vec;
+  static_assert(!FUSED || NW >= MAX_G, "the correction test takes a wave per query head");
   const PoolDesc& pd = a.pd;
   const Geom& g = a.g;
-  const int n_q = a.n_q, n_kv = a.n_kv, G = a.G, k = a.k;
-  const int head = b * n_kv + m;
+  const int G = a.G, k = a.k;
 #define FKV_ASTAMP(i) do { if (a.tstamp && head == 0 && threadIdx.x == 0) a.tstamp[i] = wall_clock64(); } while (0)
   if (split == 0) FKV_ASTAMP(16);
-#ifdef FKV_SEL_STAMPS
-  if (split == 0 && a.tstamp && threadIdx.x == 0) a.tstamp[48 + (head & 7)] = wall_clock64();
-#endif
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int gq = lane & 15, rb = lane >> 4;
+  float* sm_o = lds;                                    // [NW][G][D + 4]
+  float* sm_ml = lds + NW * G * (D + 4);                // [NW][16][2]
+  uint32_t* sm_q = reinterpret_cast<uint32_t*>(sm_ml + NW * 32);        // [G][D / 2 + 4] pairs
   __shared__ double s_cos[MAX_G];
-  __shared__ int s_flag;
+  __shared__ float s_near[MAX_G];
 
-  // Q^T operand: lane (g, kb) holds channels (s*4+kb)*8 .. +8 of head g for k-step s
-  vec qv[4];
-  {
-    const uint16_t* qh = a.q + (size_t)(b * n_q + m * G + (gq < G ? gq : 0)) * D;
+  // the group's queries, for the correction test and (by way of LDS: registers are what this block is short of) as the
+  // Q^T operand
+  const uint16_t* qg = a.q + (size_t)head * G * D;
+  uint32_t cq[MAX_G / NW + 1], cp = 0;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      uint4 w = *reinterpret_cast<const uint4*>(qh + (s * 4 + rb) * 8);
-      if (gq >= G) w = make_uint4(0, 0, 0, 0);
-      qv[s] = __builtin_bit_cast(vec, w);
-    }
-  }
-
-  // In a fused launch the common case is "no correction": fetch the first page id of this wave
-  // from the ACTIVE list now, together with the loads of the correction test, instead of after it.
-  const int pos0 = split * a.pps + wave;
-  const bool spec = a.fused && pos0 >= g.n_sink && pos0 < g.n_sink + k;
-  int spec_id = -1;
-  if (spec) spec_id = a.act_ids[(size_t)head * k + pos0 - g.n_sink];
-
-  bool pending;
-  if (a.fused) {
-    // the correction test again, with the arithmetic of the step role, so that this block does
-    // not have to wait for that role's result
-    if (a.have_prev) {
-      for (int gg = wave; gg < G; gg += NW) {
-        const size_t off = (size_t)(b * n_q + m * G + gg) * D;
-        const double c = head_cosine<DT>(a.q + off, a.q_prev + off, lane, nullptr);
-        if (lane == 0) s_cos[gg] = c;
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) s_flag = pooled_flag(s_cos, G, a.tau, a.corr_pool);
-      __syncthreads();
-      pending = s_flag != 0;
-    } else {
-      pending = true;
-    }
-  } else {
-    pending = a.use == 1 || (a.use == 2 && a.flags[head] != 0);
-  }
-
-  AttendList al;
-  al.ids = (pending ? a.new_ids : a.act_ids) + (size_t)head * k;
-  al.slots = pd.placement == 0 ? nullptr : (pending ? a.new_slots : a.act_slots) + (size_t)head * k;
-  al.n_sink = g.n_sink; al.k = k; al.n_win = g.n_win; al.n_full = g.n_full; al.r = g.r;
-  al.coherent_ids = a.fused && pending;
+  for (int u = 0; u * NW < MAX_G; ++u)
+    if (wave + u * NW < G) cq[u] = *reinterpret_cast<const uint32_t*>(qg + (wave + u * NW) * D + lane * 2);
+  if (FUSED && a.have_prev && wave < G) cp = *reinterpret_cast<const uint32_t*>(a.q_prev + (size_t)head * G * D + wave * D + lane * 2);
+  // ---- what the wave attends: lane l looks up its (l)-th position, one load for all of them ----
   const int n_att = g.n_sink + k + g.n_win + (g.r > 0 ? 1 : 0);
-  const uint16_t* head_pool = pd.pool + (size_t)head * pd.units_per_head * UNIT_ELEMS;
-  // the token appended at this step: in a fused launch its K/V may not be in the pool yet
-  const int new_page = a.fused ? (g.L - 1) / PG : -1, new_tok = (g.L - 1) % PG;
-  const float sl2 = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(d) * log2(e)
+  const int p_end = min(n_att, (split + 1) * a.pps);
+  const int pk_lo = g.n_sink, pk_hi = g.n_sink + k;
+  const int p = split * a.pps + wave + lane * NW;       // (a wave has at most 64 positions: attn_pages_per_block)
+  const bool picked = p >= pk_lo && p < pk_hi && p < p_end;
+  const bool pending = !FUSED && (a.use == 1 || (a.use == 2 && a.flags[head] != 0));
+  const int32_t* ids = (pending ? a.new_ids : a.act_ids) + (size_t)head * k;
+  const int32_t* slots = pd.placement == 0 ? nullptr : (pending ? a.new_slots : a.act_slots) + (size_t)head * k;
+  int page_l, unit_l;
+  page_l = unit_l = -1;
+  if (p < p_end) {
+    if (picked) {
+      page_l = ids[p - pk_lo];
+      if (page_l >= 0) unit_l = pd.placement == 0 ? page_l : pd.sel_base + slots[p - pk_lo];
+    } else {
+      page_l = p < pk_lo ? p : g.n_full - g.n_win + (p - pk_hi);
+      unit_l = resident_unit(pd, page_l);
+    }
+  }
+  const bool dead = __ballot(page_l == SELECTION_LOST) != 0;   // the list was never made: the outputs are poisoned
+  // The token appended at this step: in a fused launch its K/V may not be in the pool yet.  The wave that owns its page
+  // takes it from the step's inputs -- it starts from that token instead of from nothing -- and attends the page without it.
+  const int new_page = FUSED ? (g.L - 1) / PG : -1, new_tok = (g.L - 1) % PG;
+  const bool owns_new = FUSED && __ballot(page_l == new_page && !picked) != 0;
+  if (FUSED && new_tok == 0 && page_l == new_page) unit_l = -1;
 
+  uint32_t tag = a.tag;
+  int launch_no = 0;
+  if (!FUSED) {
+    launch_no = a.launch_no[head * a.launch_stride] + a.launch_stride;
+  }
+
+  const uint16_t* head_pool = pd.pool + (size_t)head * pd.units_per_head * UNIT_ELEMS;
+  const float sl2 = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(d) * log2(e)
   float m_run = -__builtin_inff(), l_run = 0.0f;
   f32x4 acc[8];
-#pragma unroll
-  for (int cb = 0; cb < 8; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 kw[8], vw[8];
+  uint32_t miss_l = 0;                                  // HOSTFUSED: the lane's page has to come from the host pool
 
-  // A corrected head of a fused launch attends with this step's selection, which other blocks of
-  // the same launch are still making.  Only the k picked positions of the attend list depend on it:
-  // the wave first attends its sink, window and open-page positions (phase 0), then waits for the
-  // selection and attends its picked positions (phase 1).  Everything else runs as one phase.
-  const bool two_phase = a.fused && pending && k > 0;
-  const int pk_lo = g.n_sink, pk_hi = g.n_sink + k;
-  const int p_end = min(n_att, (split + 1) * a.pps);
-  bool timed_out = false;
-  for (int phase = 0; phase < (two_phase ? 2 : 1); ++phase) {
-    // first position of this wave, from `from` on, that belongs to the phase and holds a page
-    int n_valid = PG, page = -1;
-    // a position's page: where in the attend list, which unit of the head's pool, where its bytes are read from, and
-    // whether they come from the host pool and have to be put into that unit on the way
-    struct Pick { int pos, unit; const uint16_t* src; bool fill; };
-    auto find = [&](int from, int& nv, int& pg) -> Pick {
-      for (int p2 = from; p2 < p_end; p2 += NW) {
-        if (two_phase && ((p2 >= pk_lo && p2 < pk_hi) != (phase == 1))) continue;
-        bool have_id = spec && !pending && p2 == pos0;
-        int id = spec_id, slot = -1;
-        bool miss = false;
-        if (two_phase && phase == 1) {
-          // Wait for this step's id of the position: the selection writes every picked id as one 64-bit
-          // word tagged with the step's epoch.  The block that makes it is one of the scoring blocks of
-          // this launch, which all have lower block indices than any attention block and never wait for
-          // anything, so it is running or done; the wait is bounded all the same.  The whole wave polls
-          // the same word (one request per poll).
-          if (timed_out) break;
-          const unsigned long long* word = a.tagged + (size_t)head * k + (p2 - pk_lo);
-          unsigned long long w2;
-          int it = 0;
-          while (((w2 = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != (unsigned long long)(uint32_t)a.epoch) {
-            if (++it > (1 << 16)) { timed_out = true; break; }   // ~0.1 s
-            __builtin_amdgcn_s_sleep(4);
-          }
-          if (timed_out) {
-            if (lane == 0) *a.status = 1;
-            break;                                             // the id is not there: read nothing
-          }
-          have_id = true;
-          if constexpr (HOSTFUSED) tagged_unpick((uint32_t)w2, id, slot, miss);
-          else id = (int)(uint32_t)w2;
-        }
-        if (HOSTFUSED && slot >= 0) {
-          // KV in a host pool, this step's selection: the slot came with the id (the slot table in memory is being
-          // written by another block of this launch); a page the cache does not hold is read from the host pool
-          nv = PG;
-          pg = id;
-          const int u = pd.sel_base + slot;
-          const uint16_t* from_pool = head_pool + (size_t)u * UNIT_ELEMS;
-          return Pick{p2, u, miss ? a.host_pool + ((size_t)head * a.max_pages + id) * UNIT_ELEMS : from_pool, miss};
-        }
-        const int u = attend_unit(al, pd, p2, nv, pg, have_id, id);
-        if (u >= 0) return Pick{p2, u, head_pool + (size_t)u * UNIT_ELEMS, false};
-      }
-      return Pick{p_end, -1, nullptr, false};
-    };
-    // Page loop, software-pipelined: the 16 wave-loads of the next page are issued before the
-    // MFMAs of the current one, so a wave that owns several pages keeps 32 KiB in flight.
-    const Pick cur = find(pos0, n_valid, page);
-    int pos = cur.pos, unit = cur.unit;
-    bool fill = cur.fill;
-  uint4 kw[8], vw[8];
-  if (unit >= 0) {
-    const uint4* up = reinterpret_cast<const uint4*>(cur.src) + lane;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) kw[j] = up[j * 64];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) vw[j] = up[(8 + j) * 64];
-  }
-  while (unit >= 0) {
-    // next page of this wave, if any
-    int nn_valid = PG, npage = -1;
-    const Pick nxt = find(pos + NW, nn_valid, npage);
-    const int npos = nxt.pos, nunit = nxt.unit;
-    uint4 kn[8], vn[8];
-    if (nunit >= 0) {
-      const uint4* up = reinterpret_cast<const uint4*>(nxt.src) + lane;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) kn[j] = up[j * 64];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) vn[j] = up[(8 + j) * 64];
+  const uint32_t lane16 = (uint32_t)lane * 16;
+  auto source = [&](int i) -> const char* {             // where position i's bytes are
+    const int u = __builtin_amdgcn_readlane(unit_l, i);
+    const uint16_t* p = head_pool + (size_t)u * UNIT_ELEMS;
+    if constexpr (HOSTFUSED) {
+      if (__builtin_amdgcn_readlane((int)miss_l, i))
+        p = a.host_pool + ((size_t)head * a.max_pages + __builtin_amdgcn_readlane(page_l, i)) * UNIT_ELEMS;
     }
-    if (HOSTFUSED && fill) {
-      // the page came from the host pool: it goes into its page-cache slot as it is (recall, Sec. 3.3: a corrected
-      // head's pages are fetched before it attends; here the wave that attends over the page is the one that fetches it)
-      uint4* dp = reinterpret_cast<uint4*>(pd.pool + ((size_t)head * pd.units_per_head + unit) * UNIT_ELEMS) + lane;
+    return reinterpret_cast<const char*>(p);
+  };
+  // 4 KiB of a page from a scalar base (the opaque copies keep one base register pair per group and the lanes' offset in one)
+  typedef const __attribute__((address_space(1))) char* gptr;
+  auto load4 = [&](u32x4* w, const char* from) {
+    const unsigned long long u = (unsigned long long)from;
+    gptr base = (gptr)(((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u));
+    asm volatile("" : "+s"(base));
 #pragma unroll
-      for (int j = 0; j < 8; ++j) dp[j * 64] = kw[j];
+    for (int j = 0; j < 4; ++j) w[j] = *(const __attribute__((address_space(1))) u32x4*)(base + j * 1024 + lane16);
+  };
+  auto load_k = [&](const char* up) { load4(kw, up); load4(kw + 4, up + 4096); };
+  auto load_v = [&](const char* up) { load4(vw, up + 8192); load4(vw + 4, up + 12288); };
+  // Q^T operand of k-step s: lane (g, kb) holds channels (s*4+kb)*8 .. +8 of head g (the idle columns repeat head 0)
+  const uint32_t* const q_op = sm_q + (gq < G ? gq : 0) * (D / 2 + 4) + rb * 4;
+  auto q_of = [&](int s) { return *reinterpret_cast<const vec*>(q_op + s * 16); };
+  // One page: position i's, whose loads are under way.  Position `next` (-1: none) is requested on the way, its keys once
+  // the products with this page's are made, its values once those are: the registers are free by then.
+  auto attend_page = [&](int i, int next) {
+    const char* const up_next = source(next >= 0 ? next : 0);
+    const int page = __builtin_amdgcn_readlane(FUSED && !HOSTFUSED ? unit_l : page_l, i);   // (KV in HBM: the same)
+    const int n_valid = FUSED ? (page == new_page ? new_tok : PG) : (page == g.n_full ? g.r : PG);
+    if constexpr (HOSTFUSED) {
+      if (__builtin_amdgcn_readlane((int)miss_l, i)) {
+        // the page came from the host pool: it goes into its page-cache slot as it is (recall, Sec. 3.3: a corrected
+        // head's pages are fetched before it attends; here the wave that attends over the page is the one that fetches it)
+        u32x4* dp = reinterpret_cast<u32x4*>(pd.pool + ((size_t)head * pd.units_per_head + __builtin_amdgcn_readlane(unit_l, i)) * UNIT_ELEMS) + lane;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) dp[(8 + j) * 64] = vw[j];
-    }
-    if (page == new_page) {
-      // overwrite the new token's key row and value column with the step's inputs
-      const uint16_t* kn_h = a.k_new + (size_t)head * D;
-      const uint16_t* vn_h = a.v_new + (size_t)head * D;
-      const int mb_new = new_tok >> 4;
-      if (gq == (new_tok & 15)) {
+        for (int j = 0; j < 8; ++j) dp[j * 64] = kw[j];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const uint4 w = *reinterpret_cast<const uint4*>(kn_h + (s * 4 + rb) * 8);
-          if (mb_new == 0) kw[s * 2] = w; else kw[s * 2 + 1] = w;
-        }
-      }
-      const int kb_new = (new_tok & 15) >> 2, e_new = (new_tok & 3) + 4 * (new_tok >> 4);
-      if (rb == kb_new) {
-#pragma unroll
-        for (int cb = 0; cb < 8; ++cb) {
-          const uint32_t v = vn_h[cb * 16 + gq];
-          const uint32_t keep = (e_new & 1) ? 0x0000ffffu : 0xffff0000u;
-          const uint32_t put = (e_new & 1) ? (v << 16) : v;
-          // (no run-time indexing of the register array)
-          if ((e_new >> 1) == 0) vw[cb].x = (vw[cb].x & keep) | put;
-          if ((e_new >> 1) == 1) vw[cb].y = (vw[cb].y & keep) | put;
-          if ((e_new >> 1) == 2) vw[cb].z = (vw[cb].z & keep) | put;
-          if ((e_new >> 1) == 3) vw[cb].w = (vw[cb].w & keep) | put;
-        }
+        for (int j = 0; j < 8; ++j) dp[(8 + j) * 64] = vw[j];
       }
     }
-
     f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
+      const vec qs = q_of(s);
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-        st[mb] = Mma<DT>::mma(__builtin_bit_cast(vec, kw[s * 2 + mb]), qv[s], st[mb]);
+      for (int mb = 0; mb < 2; ++mb) st[mb] = Mma<DT>::mma(__builtin_bit_cast(vec, kw[s * 2 + mb]), qs, st[mb]);
+      if (s < 3) __builtin_amdgcn_sched_barrier(0);     // (not all of the operand at once: registers)
     }
+    if (next >= 0) load_k(up_next);
     // logits (base 2) of head gq for tokens mb*16 + rb*4 + i
     float sc[8];
-    float mx = -__builtin_inff();
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int tok = (e >> 2) * 16 + rb * 4 + (e & 3);
-      sc[e] = tok < n_valid ? st[e >> 2][e & 3] * sl2 : -__builtin_inff();
-      mx = fmaxf(mx, sc[e]);
+    for (int e = 0; e < 8; ++e) sc[e] = st[e >> 2][e & 3] * sl2;
+    if (n_valid < PG) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (rb * 4 >= n_valid - ((e >> 2) * 16 + (e & 3))) sc[e] = -__builtin_inff();
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = fast_exp2(m_run - m_new);
-    float p[8], psum = 0.0f;
+    float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
+    mx = max_over_rows(mx);
+    // The sums are kept relative to the running maximum itself: the tokens that set it, which weigh most, then have the
+    // weight 1, which the split below represents exactly (a reference that lags behind, to save rescaling passes, costs
+    // bf16 outputs a third of their precision).
+    if (__ballot(mx > m_run)) {
+      const float m_new = fmaxf(mx, m_run);
+      const float alpha = m_new == m_run ? 1.0f : fast_exp2(m_run - m_new);
+      l_run *= alpha;
+      m_run = m_new;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      p[e] = fast_exp2(sc[e] - m_new);
-      psum += p[e];
+      for (int cb = 0; cb < 8; ++cb) acc[cb] *= alpha;
     }
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
+    float p[8];
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) acc[cb] *= alpha;
+    for (int e = 0; e < 8; ++e) p[e] = fast_exp2(sc[e] - m_run);
     vec phi, plo;
     Mma<DT>::split(p, phi, plo);
+    // the sum of the weights as they go into the products, so that what the split drops cancels in the quotient
+    float l_lo = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      l_run = Mma<DT>::add_pair(__builtin_bit_cast(u32x4, phi)[e], l_run);
+      l_lo = Mma<DT>::add_pair(__builtin_bit_cast(u32x4, plo)[e], l_lo);
+    }
+    l_run += l_lo;
 #pragma unroll
     for (int cb = 0; cb < 8; ++cb) {
       const vec va = __builtin_bit_cast(vec, vw[cb]);
       acc[cb] = Mma<DT>::mma(va, phi, acc[cb]);
       acc[cb] = Mma<DT>::mma(va, plo, acc[cb]);
     }
-    pos = npos; unit = nunit; n_valid = nn_valid; page = npage; fill = nxt.fill;
-    if (nunit >= 0) {
+    if (next >= 0) load_v(up_next);
+  };
+
+  bool lost = false;                                    // something waited for did not come: the outputs are poisoned
+  bool two_phase = false;
+  // the first page's loads, for the case that the head is not corrected
+  const unsigned long long listed = __ballot(unit_l >= 0);
+  const int i0 = listed ? (int)__builtin_ctzll(listed) : -1;
+  const char* const up0 = source(i0 >= 0 ? i0 : 0);
+  if (i0 >= 0) load_k(up0);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) { kw[j] = kn[j]; vw[j] = vn[j]; }
-    }
+  for (int u = 0; u * NW < MAX_G; ++u)
+    if (wave + u * NW < G) sm_q[(wave + u * NW) * (D / 2 + 4) + lane] = cq[u];
+  // the correction test again, so that this block does not have to wait for that role's result: in fp32 where that
+  // decides it, else with the arithmetic of the step role
+  if (FUSED && a.have_prev && wave < G) {
+    const float c = near_cosine_of<DT>(cq[0], cp);
+    if (lane == 63) s_near[wave] = c;
   }
-  }   // phases
+  lds_barrier();
+  if (FUSED) {
+    int flag = a.have_prev ? __builtin_amdgcn_readfirstlane(near_flag(s_near, G, a.tau, a.corr_pool)) : 1;
+    if (flag < 0) {
+      if (wave < G) {
+        const double c = cosine_of<DT>(cq[0], cp);
+        if (lane == 63) s_cos[wave] = c;
+      }
+      lds_barrier();
+      flag = __builtin_amdgcn_readfirstlane(pooled_flag(s_cos, G, a.tau, a.corr_pool));
+    }
+    two_phase = flag != 0;
+  }
+  if (i0 >= 0) load_v(up0);
+#pragma unroll
+  for (int cb = 0; cb < 8; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (FUSED && owns_new) {
+    uint2 vn[8];
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) vn[cb] = *reinterpret_cast<const uint2*>(a.v_new + (size_t)head * D + cb * 16 + rb * 4);
+    f32x4 st = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)                         // (the key in every row of the tile)
+      st = Mma<DT>::mma(*reinterpret_cast<const vec*>(a.k_new + (size_t)head * D + (s * 4 + rb) * 8), q_of(s), st);
+    m_run = st[0] * sl2;
+    l_run = rb == 0 ? 1.0f : 0.0f;
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb)
+      acc[cb] = f32x4{Unpack<DT>::lo(vn[cb].x), Unpack<DT>::hi(vn[cb].x), Unpack<DT>::lo(vn[cb].y), Unpack<DT>::hi(vn[cb].y)};
+  }
+  // A corrected head of a fused launch attends with this step's selection, which other blocks of
+  // the same launch are still making.  Only the k picked positions of the attend list depend on it:
+  // the wave first attends its sink, window and open-page positions (phase 0), then waits for the selection and
+  // attends its picked positions (phase 1).  Everything else runs as one phase.
+  unsigned long long todo = two_phase ? __ballot(!picked && unit_l >= 0) : listed;
+  bool loaded = todo != 0 && (int)__builtin_ctzll(todo) == i0;
+  for (int phase = 0;; ++phase) {
+    if (todo) {
+      int i = __builtin_ctzll(todo);
+      if (!loaded) {
+        const char* up = source(i);
+        load_k(up);
+        load_v(up);
+      }
+      do {
+        todo &= todo - 1;
+        const int next = todo ? (int)__builtin_ctzll(todo) : -1;
+        attend_page(i, next);
+        i = next;
+      } while (i >= 0);
+    }
+    if (!two_phase || phase == 1) break;
+    todo = __ballot(picked);
+    loaded = false;
+    if (todo == 0) break;
+    // Wait for this step's ids of the positions: the selection writes every picked id as one tagged 64-bit word.
+    // The blocks that make it have lower block indices than any attention block and wait for nothing that has a
+    // higher one, so they are running or done; the wait is bounded all the same.
+    const unsigned long long* word = a.tagged + (size_t)head * k + (picked ? p - pk_lo : 0);
+    unsigned long long w = 0;
+    int it = 0;
+    for (;;) {
+      w = ld_tag(word);
+      if (__ballot(picked && (uint32_t)(w >> 32) != a.pick_tag) == 0 || ++it > MAX_POLLS) break;
+      __builtin_amdgcn_s_sleep(2);
+    }
+    if (it > MAX_POLLS) {                             // the ids are not there: read nothing
+      lost = true;
+      if (lane == 0) *a.status = 1;
+      break;
+    }
+    if (picked) {
+      if constexpr (HOSTFUSED) {
+        // the slot comes with the id (the slot table in memory is being written by another block of this launch);
+        // a page the cache does not hold is read from the host pool
+        int slot;
+        bool miss;
+        tagged_unpick((uint32_t)w, page_l, slot, miss);
+        unit_l = slot >= 0 ? pd.sel_base + slot : -1;
+        miss_l = miss ? 1u : 0u;
+      } else {
+        page_l = (int)(uint32_t)w;
+        unit_l = page_l;
+      }
+    }
+    todo = __ballot(picked && unit_l >= 0);
+  }
+  if (!two_phase && dead) lost = true;
   // A wave whose wait ran out has not read its picked pages: make that visible on the data path.
   // NaN in its sum poisons the block's partial and, through the merge, every output row of the
   // KV head's query group.
-  if (timed_out) l_run = __builtin_nanf("");
+  if (lost) l_run = __builtin_nanf("");
   if constexpr (HOSTFUSED) {
     // With the KV in a host pool the wave that gives up also leaves the page-cache slot it was to fill unfilled, while
     // the recall plan lists the page as cached: the layer's state cannot be trusted from then on.  Every later step of
@@ -375,131 +431,116 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int m, 
     if (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) l_run = __builtin_nanf("");
   }
   if (split == 0) FKV_ASTAMP(17);
-  // per-wave totals of l over the 4 row blocks
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
 
-  float* po = a.part_o + ((size_t)(head * a.max_splits + split) * G) * D;
-  float* pml = a.part_ml + ((size_t)(head * a.max_splits + split) * G) * 2;
-  if (NW == 1) {
-    if (gq < G) {
+  // ---- combine the waves: one barrier ----
+  l_run = sum_over_rows(l_run);                         // per-wave totals of l over the 4 row blocks
+  if (gq < G) {
+    float* o = sm_o + ((size_t)wave * G + gq) * (D + 4);
 #pragma unroll
-      for (int cb = 0; cb < 8; ++cb) {
-        float* dst = po + (size_t)gq * D + cb * 16 + rb * 4;
-        st_dev2(dst, acc[cb][0], acc[cb][1]);
-        st_dev2(dst + 2, acc[cb][2], acc[cb][3]);
+    for (int cb = 0; cb < 8; ++cb) *reinterpret_cast<f32x4*>(o + cb * 16 + rb * 4) = acc[cb];
+    if (rb == 0) *reinterpret_cast<float2*>(sm_ml + (wave * 16 + gq) * 2) = make_float2(m_run, l_run);
+  }
+  // (every wave has read the launch number before anyone can move it on)
+  if (!FUSED) tag = device_tag((uint32_t)__builtin_amdgcn_readfirstlane(launch_no));
+  lds_barrier();
+  // ---- log-sum-exp merge of the head's splits, shared by its blocks ----
+  // Block `split` finishes the split-th `share` of the head's G x D outputs: its threads keep their sums of that part, hand
+  // the others to the blocks that finish them, and fold the other blocks' sums of their own part in as they arrive.  One
+  // trip, and no block reads more than an n_splits-th of the partials (one block merging alone: 6 us of a 20 us launch at
+  // 16 splits of G = 8).  A head's blocks are adjacent in block order and wait for each other only.
+  const int n_splits = a.n_splits, items = G * D;
+  const int own_lo = split * a.share, own_hi = min(items, own_lo + a.share);
+  unsigned long long* const po = a.part + (size_t)head * a.max_splits * items;
+  unsigned long long* const pml = a.part_ml + (size_t)head * a.max_splits * G * 2;
+  constexpr int IT = (MAX_G * D + NW * 64 - 1) / (NW * 64);
+  float o[IT], den[IT], M[IT];
+#pragma unroll
+  for (int t = 0; t < IT; ++t) {
+    const int idx = threadIdx.x + t * NW * 64;
+    if (idx >= items) continue;
+    const int gg = idx / D, c = idx % D;
+    float m[NW], l[NW], v[NW];
+    float Mt = -__builtin_inff();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float2 ml = *reinterpret_cast<const float2*>(sm_ml + (w * 16 + gg) * 2);
+      m[w] = ml.x;
+      l[w] = ml.y;
+      v[w] = sm_o[((size_t)w * G + gg) * (D + 4) + c];
+      Mt = fmaxf(Mt, m[w]);
+    }
+    float ot = 0.0f, dt = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      // a wave that saw no page has m = -inf and zero sums (or a poisoned one)
+      const float wgt = m[w] == -__builtin_inff() ? 0.0f : fast_exp2(m[w] - Mt);
+      ot += v[w] * wgt;
+      dt += m[w] == -__builtin_inff() ? l[w] : l[w] * wgt;
+    }
+    o[t] = ot; den[t] = dt; M[t] = Mt;
+    if (n_splits > 1) {
+      if (idx < own_lo || idx >= own_hi) st_tag(po + (size_t)split * items + idx, __float_as_uint(ot), tag);
+      if (c == 0) {
+        st_tag(pml + (split * G + gg) * 2, __float_as_uint(Mt), tag);
+        st_tag(pml + (split * G + gg) * 2 + 1, __float_as_uint(dt), tag);
       }
-      if (rb == 0) st_dev2(pml + gq * 2, m_run, l_run);
-    }
-  } else {
-    float* sm_m = lds;                    // [NW][16]
-    float* sm_l = lds + NW * 16;          // [NW][16]
-    float* sm_o = lds + NW * 32;          // [NW][G][D]
-    if (rb == 0) sm_m[wave * 16 + gq] = m_run;
-    __syncthreads();
-    if (split == 0) FKV_ASTAMP(22);
-    float M = sm_m[gq];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, sm_m[w * 16 + gq]);
-    // a wave that saw no page has m_run = -inf and zero sums
-    const float wgt = (m_run == -__builtin_inff()) ? 0.0f : fast_exp2(m_run - M);
-    if (gq < G) {
-#pragma unroll
-      for (int cb = 0; cb < 8; ++cb)
-        *reinterpret_cast<f32x4*>(&sm_o[((size_t)wave * G + gq) * D + cb * 16 + rb * 4]) = acc[cb] * wgt;
-      if (rb == 0) sm_l[wave * 16 + gq] = l_run * wgt;
-    }
-    __syncthreads();
-    if (split == 0) FKV_ASTAMP(23);
-    if (a.n_splits == 1) {
-      // the block has the whole head: normalise and write the output, no partial, no merge
-      for (int i = threadIdx.x; i < G * D / 2; i += NW * 64) {
-        const int gg = i / (D / 2), c = (i % (D / 2)) * 2;
-        float s0 = 0.0f, s1 = 0.0f, den = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          s0 += sm_o[((size_t)w * G + gg) * D + c];
-          s1 += sm_o[((size_t)w * G + gg) * D + c + 1];
-          den += sm_l[w * 16 + gg];
-        }
-        const float inv = 1.0f / den;
-        *reinterpret_cast<float2*>(a.out + (size_t)(b * n_q + m * G + gg) * D + c) = make_float2(s0 * inv, s1 * inv);
-      }
-      return;
-    }
-    for (int i = threadIdx.x; i < G * D / 2; i += NW * 64) {
-      const int gg = i / (D / 2), c = (i % (D / 2)) * 2;
-      float s0 = 0.0f, s1 = 0.0f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        s0 += sm_o[((size_t)w * G + gg) * D + c];
-        s1 += sm_o[((size_t)w * G + gg) * D + c + 1];
-      }
-      st_dev2(po + (size_t)gg * D + c, s0, s1);
-    }
-    if (threadIdx.x < G) {
-      float s = 0.0f, MM = sm_m[threadIdx.x];
-#pragma unroll
-      for (int w = 0; w < NW; ++w) { s += sm_l[w * 16 + threadIdx.x]; MM = fmaxf(MM, sm_m[w * 16 + threadIdx.x]); }
-      st_dev2(pml + threadIdx.x * 2, MM, s);
     }
   }
-
-  // ---- log-sum-exp merge of this head's splits, by the block that finishes last ----
   if (split == 0) FKV_ASTAMP(18);
-  if (!last_block_done(a.counters + head, a.n_splits)) return;
-  FKV_ASTAMP(19);
-  // Every thread owns two output channels of one head and folds that head's splits with an
-  // online log-sum-exp.  The (m, l) pairs and the partial outputs of up to CH splits are all
-  // requested before the first one is used: one memory round trip per CH splits, no LDS.  CH is
-  // matched to the number of splits: a trip issues 2 x CH device-scope loads per thread whether
-  // the splits exist or not.
-  const size_t pbase = (size_t)head * a.max_splits;
-  const int nt = NW * 64, items = G * D / 2;
-  auto merge = [&](auto chc) {
-  constexpr int CH = decltype(chc)::value;
-  for (int it = threadIdx.x; it < items; it += nt) {
-    const int gg = it / (D / 2), c2 = it % (D / 2);
-    const float* src_o = a.part_o + (pbase * G + gg) * D + c2 * 2;
-    const float* src_ml = a.part_ml + (pbase * G + gg) * 2;
-    float M = -__builtin_inff(), den = 0.0f, o0 = 0.0f, o1 = 0.0f;
-    for (int s0 = 0; s0 < a.n_splits; s0 += CH) {
-      float2 ml[CH], v[CH];
 #pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        const int sp = min(s0 + u, a.n_splits - 1);
-        ml[u] = ld_dev2(src_ml + (size_t)sp * G * 2);
-        v[u] = ld_dev2(src_o + (size_t)sp * G * D);
+  for (int t = 0; t < IT; ++t) {
+    const int idx = threadIdx.x + t * NW * 64;
+    if (idx < own_lo || idx >= own_hi) continue;
+    const int gg = idx / D;
+    constexpr int CH = 8;
+    // (the others' splits, numbered from 0: the block's own is left out)
+    for (int s0 = 0; s0 < n_splits - 1; s0 += CH) {
+      unsigned long long wm[CH], wl[CH], wo[CH];
+      int it = 0;
+      for (;;) {
+        bool there = true;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+          int sp = min(s0 + u, n_splits - 2);
+          sp += sp >= split ? 1 : 0;
+          wo[u] = ld_tag(po + (size_t)sp * items + idx);
+          wm[u] = ld_tag(pml + (sp * G + gg) * 2);
+          wl[u] = ld_tag(pml + (sp * G + gg) * 2 + 1);
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          there = there & ((uint32_t)(wo[u] >> 32) == tag) & ((uint32_t)(wm[u] >> 32) == tag) & ((uint32_t)(wl[u] >> 32) == tag);
+        if (there) break;
+        if (++it > MAX_POLLS) {
+          *a.status = 1;
+          den[t] = __builtin_nanf("");
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
       }
-      float Mc = M;
+      float Mc = M[t];
 #pragma unroll
-      for (int u = 0; u < CH; ++u)
-        if (s0 + u < a.n_splits) Mc = fmaxf(Mc, ml[u].x);
-      const float resc = (M == -__builtin_inff()) ? 0.0f : fast_exp2(M - Mc);
-      den *= resc; o0 *= resc; o1 *= resc;
-      M = Mc;
+      for (int u = 0; u < CH; ++u) Mc = fmaxf(Mc, __uint_as_float((uint32_t)wm[u]));
+      const bool none = M[t] == -__builtin_inff();
+      const float resc = none ? 0.0f : fast_exp2(M[t] - Mc);
+      den[t] = none ? den[t] : den[t] * resc;
+      o[t] *= resc;
+      M[t] = Mc;
 #pragma unroll
       for (int u = 0; u < CH; ++u) {
-        const float w = (s0 + u < a.n_splits && ml[u].x != -__builtin_inff()) ? fast_exp2(ml[u].x - M) : 0.0f;
-        den += w * ml[u].y;
-        o0 += w * v[u].x;
-        o1 += w * v[u].y;
+        if (s0 + u < n_splits - 1) {
+          const float mu = __uint_as_float((uint32_t)wm[u]), lu = __uint_as_float((uint32_t)wl[u]);
+          const float w = mu == -__builtin_inff() ? 0.0f : fast_exp2(mu - Mc);
+          den[t] += mu == -__builtin_inff() ? lu : w * lu;
+          o[t] += w * __uint_as_float((uint32_t)wo[u]);
+        }
       }
     }
-    const float inv = 1.0f / den;
-    *reinterpret_cast<float2*>(a.out + (size_t)(b * n_q + m * G + gg) * D + c2 * 2) = make_float2(o0 * inv, o1 * inv);
+    a.out[(size_t)head * items + idx] = o[t] / den[t];
+    // (the thread has every other block's sums, so all of them have read the launch number)
+    if (!FUSED && idx == 0 && a.launch_stride) a.launch_no[head] = launch_no;
   }
-  };
-  if (a.n_splits <= 4) merge(MergeChunk<4>{});
-  else if (a.n_splits <= 8) merge(MergeChunk<8>{});
-  else if (a.n_splits <= 12) merge(MergeChunk<12>{});
-  else if (a.n_splits <= 16) merge(MergeChunk<16>{});
-  else if (a.n_splits <= 24) merge(MergeChunk<24>{});
-  else merge(MergeChunk<32>{});
-  FKV_ASTAMP(21);
-#ifdef FKV_SEL_STAMPS
-  if (a.tstamp && threadIdx.x == 0) a.tstamp[32 + (head & 7)] = wall_clock64();
-#endif
+  if (split == 0) FKV_ASTAMP(21);
 #undef FKV_ASTAMP
 }
 

@@ -36,6 +36,20 @@ struct Geom {
   int k_eff;    // pages picked per KV head = min(k, n_cand)
 };
 
+__host__ __device__ inline Geom geom_of(int L, int n_sink, int n_win, int k) {   // sink, window and selectable pages of the budget
+  Geom g;
+  g.L = L;
+  g.n_full = L / PG;
+  g.r = L % PG;
+  g.n_sink = n_sink < g.n_full ? n_sink : g.n_full;
+  const int rest = g.n_full - g.n_sink;
+  g.n_win = n_win < rest ? n_win : rest;
+  g.cand_lo = g.n_sink;
+  g.n_cand = g.n_full - g.n_sink - g.n_win;
+  g.k_eff = k < g.n_cand ? k : g.n_cand;
+  return g;
+}
+
 // Where a KV head's pages live in HBM.  Unit u of head (b, m) starts at
 // pool + ((b * n_kv + m) * units_per_head + u) * UNIT_ELEMS.
 struct PoolDesc {
@@ -66,37 +80,71 @@ __host__ __device__ inline int v_elem_off(int t, int ch) {
 // ---- launch wrappers (defined in the kernel files) ----------------------
 struct Dims { int batch, n_q, n_kv, G, k, max_pages, dtype, max_lds, sel_pool, corr_pool; };
 
+// Launches are numbered (31 bits); the low bit keeps the tags of launches numbered by the host (the layer kernel) apart from
+// those of launches numbered on the device (the step and attention kernels: a program may capture those), which share buffers.
+__host__ __device__ inline uint32_t host_tag(uint32_t launch) { return (launch << 1) | 1u; }
+__host__ __device__ inline uint32_t device_tag(uint32_t launch) { return launch << 1; }
+
 // the fused step kernel: roles are OR-ed
 constexpr int ROLE_APPEND = 1, ROLE_CORR = 2, ROLE_SELECT = 4;
 struct StepIO {
   PoolDesc pd; uint16_t* summ; const uint16_t* k_new; const uint16_t* v_new;      // append
   const uint16_t* q; const uint16_t* q_prev; uint16_t* q_stage; int have_prev; float tau;
   uint8_t* flags; uint8_t* flags_user; double* cosine;                               // correction test
-  float* P; float* score; int32_t* ids; int32_t* ids_user; int* counters;            // selection
+  unsigned long long* P; float* score; int32_t* ids; int32_t* ids_user;              // selection
+  unsigned long long* exch; unsigned long long* keyx;                                // its exchange between blocks
+  int* launch_no; int* status;                                                       // number of the last launch, per head
+  bool* P_tagged;                                                                    // out: the format the launch left P in
   long long* tstamp;                                                                 // debug timestamps or null
-  // scratch of a selection spread over several blocks per head (all may be null: then it is never spread)
-  float* bmax; int bmax_stride; float* hmax; unsigned long long* zsum; uint32_t* cand_key; int32_t* cand_id; int* wide_counters;
   // KV in a host pool (else all null): a launch with ROLE_SELECT also makes the recall plan of the new selection --
   // ACTIVE ids and slots in, PENDING slots and miss lists out
   const int32_t* plan_act_ids; const int32_t* plan_act_slots; int32_t* plan_new_slots; int32_t* plan_miss;
 };
-constexpr int WIDE_MAX_SLICES = 16;       // most blocks that share one head's selection
-bool wide_plan(const Dims& d, const Geom& g, int* B, int* slice);
-void launch_wide_select(const Dims& d, const StepIO& io, Geom g, int B, int slice, int n_score_blocks, hipStream_t st);
+constexpr int EXCH_WORDS = 16 * 3 * MAX_G;   // per head: what the selecting blocks of a head tell each other
 int launch_step(const Dims& d, int roles, const StepIO& io, Geom g, hipStream_t st);   // returns the launches made
+// What the one-launch layer-step needs and no step changes: kept in device memory, one per context, so that a launch hands
+// over 56 bytes -- which the hardware preloads into scalar registers -- and finds the rest in the L2 of every XCD.  (Fresh
+// arguments are a miss of about 0.7 us for every 64 bytes that a block touches, one after the other along its chain.)
+struct LayerConst {
+  // per layer, as offsets from the layer's base in units of 256 bytes; ..._half: from the first to the second of a
+  // ping-pong pair, in elements
+  char* dev_base;
+  unsigned long long layer_bytes;
+  uint32_t o_summ, o_qprev, o_ids, o_slots, o_flags, o_miss, o_cosine, o_status, o_tagged;
+  int32_t qprev_half, ids_half;
+  // per context
+  int32_t heads, n_kv, k, max_pages, max_splits, n_sink, n_win;      // heads: (request, KV head) pairs
+  int32_t units_per_head, ring_base, n_ring, sel_base;
+  int32_t corr_pool, sel_pool;
+  float tau;
+  unsigned long long *P, *part, *part_ml, *exch, *keyx;
+  float* score;
+  const char* host_base;                     // KV in a host pool (else null)
+  unsigned long long host_layer_bytes;
+  long long* tstamp;                         // debug timestamps or null
+};
 // the whole layer-step (step roles + attention) in one launch; false if this shape or placement
 // has to take the separate launches
 struct LayerIO {
-  const int32_t* act_ids; float* part_o; float* part_ml; int max_splits; int* attn_counters; float* out;
-  const uint16_t* host_pool;                 // KV in a host pool: this layer's pool (corrected heads fetch their missing pages from it)
-  unsigned long long* tagged; int epoch; int* status;   // tagged: [heads][k] epoch-tagged copies of the picked ids
-  int attn_epoch_bias;                       // 0; a test of the bounded wait makes attention wait for an epoch that never comes
-  int* launch_grid; size_t* launch_lds;      // out (may be null): shape of the launch that was made
+  const LayerConst* consts;                  // device memory
+  int layer, parity, have_prev;
+  const uint16_t *q, *k_new, *v_new;
+  float* out;
+  uint32_t launch;                           // number of this launch (host_tag)
+  bool host_pool;
+  int max_splits;
+  bool lose_selection;                       // test of the bounded wait: attention waits for a tag that never comes
+  int* launch_grid; size_t* launch_lds;      // out: shape of the launch that was made
 };
 // `reps` launches of a kernel that does nothing, with the given grid, 512 threads and dynamic LDS
 bool launch_floor(int grid, size_t lds, int reps, hipStream_t st);
-bool launch_layer(const Dims& d, const StepIO& io, const LayerIO& lio, Geom g, hipStream_t st);
-int attn_pages_per_block(int n_att, int heads, int max_splits, int nw);
+bool launch_layer(const Dims& d, const LayerIO& lio, Geom g, hipStream_t st);
+constexpr int kComputeUnits = 256;
+// Most blocks of a launch that may wait for each other (a head's selecting blocks, a head's attention blocks).  In block
+// order at most one head's are half there, so a launch by itself always gets on; with two launches on the machine at once
+// there is room for both as long as neither has more of them than half the blocks that fit (two to a compute unit).
+constexpr int kMaxWaiting = kComputeUnits;
+int attn_pages_per_block(int n_att, int heads, int max_splits, int nw, int max_blocks = kMaxWaiting);
 void launch_load_prefix(const Dims& d, const PoolDesc& pd, uint16_t* summ, uint16_t* host_pool,
                         const uint16_t* K, const uint16_t* V, int n_tokens, Geom g, hipStream_t st);
 void launch_summary_recompute(const Dims& d, const PoolDesc& pd, uint16_t* summ, int first_page,
@@ -116,13 +164,15 @@ struct GatherLayers {
   const uint8_t* flags[GATHER_MAX_LAYERS];
 };
 void launch_gather(const Dims& d, const GatherLayers& gl, int heads, hipStream_t st);
-// returns the number of splits written per KV head
-int  launch_attn(const Dims& d, const PoolDesc& pd, const uint16_t* q, const int32_t* act_ids,
-                 const int32_t* new_ids, const int32_t* act_slots, const int32_t* new_slots,
-                 const uint8_t* flags, int use, float* part_o, float* part_ml, int max_splits,
-                 int* counters, float* out, Geom g, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end,
-                 long long* tstamp);
-void launch_fill_zero(int* p, int n, hipStream_t st);       // p[0..n) = 0, by a kernel
+struct AttnIO {
+  const uint16_t* q; const int32_t* act_ids; const int32_t* new_ids; const int32_t* act_slots; const int32_t* new_slots;
+  const uint8_t* flags; int use;
+  unsigned long long* part; unsigned long long* part_ml; int max_splits;
+  int* launch_no; int launch_stride;         // launch numbers: per head, moved on by the kernel (1), or one word (0)
+  int* status; float* out; long long* tstamp;
+};
+void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end);
+void launch_next_number(int* p, hipStream_t st);            // *p += 1, by a kernel
 void launch_read_page(const uint16_t* unit, uint16_t* out_token_major, hipStream_t st);
 void launch_export_nhd(const Dims& d, const PoolDesc& pd, const int32_t* act_ids, const int32_t* new_ids,
                        const int32_t* act_slots, const int32_t* new_slots, const uint8_t* flags, int use,

@@ -42,7 +42,7 @@ __device__ __forceinline__ void plan_head(int32_t* new_ids, const int32_t* act_i
       if (id >= n_full) new_ids[i] = -1;
     }
   }
-  __syncthreads();
+  lds_barrier();
   for (int i = tid; i < k; i += NT)
     if (aid[i] >= 0) used[aslot[i]] = 1;
   if (tid < 64) {
@@ -51,7 +51,7 @@ __device__ __forceinline__ void plan_head(int32_t* new_ids, const int32_t* act_i
     n = (int)wave_sum_u32((uint32_t)n);    // ids are ascending, -1 padded at the end
     if (lane == 0) *n_act_sh = n;
   }
-  __syncthreads();
+  lds_barrier();
   const int n_act = *n_act_sh;
   // hit or miss per picked page (binary search in the ACTIVE ids)
   for (int i = tid; i < k; i += NT) {
@@ -78,7 +78,7 @@ __device__ __forceinline__ void plan_head(int32_t* new_ids, const int32_t* act_i
       base += (int)__builtin_amdgcn_readlane((int)incl, 63);
     }
   }
-  __syncthreads();
+  lds_barrier();
   // the r-th miss (ascending page id) takes the r-th free slot
   if (tid < 64) {
     int n_miss = 0;
@@ -98,7 +98,7 @@ __device__ __forceinline__ void plan_head(int32_t* new_ids, const int32_t* act_i
     }
     if (lane == 0) mh[0] = n_miss;
   }
-  __syncthreads();
+  lds_barrier();
   for (int i = tid; i < k; i += NT) {
     const int s = nslot[i];
     new_slots[i] = s < 0 ? s : (s & ~PLAN_MISS_BIT);

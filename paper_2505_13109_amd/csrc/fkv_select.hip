@@ -1,5 +1,4 @@
-// The "step" kernel (token append, correction test, page weights, and -- in its last scoring
-// block per KV head or in a launch of its own -- the top-k selection), the one-launch layer kernel
+// The "step" kernel (token append, correction test, page weights and the top-k selection), the one-launch layer kernel
 // (the step roles plus the attention blocks), and the host-side rules that size their launches.
 // The roles themselves are in fkv_step_dev.h, attention in fkv_attn_dev.h.
 #include "fkv_step_dev.h"
@@ -10,45 +9,55 @@
 namespace fkv {
 
 // ---------------------------------------------------------------------------------
-// the kernel: 1-D grid, [append blocks][corr blocks][scoring blocks], each set present
-// only if its role bit is set; heads = batch * n_kv.
+// grid (heads, rows): rows as in step_roles
 // ---------------------------------------------------------------------------------
 template <int DT, int G>
-__global__ __launch_bounds__(STEP_THREADS, STEP_THREADS <= 256 ? 2 : 1) void step_kernel(StepArgs a) {
-  extern __shared__ uint32_t dyn_lds[];              // selection: n_cand keys, then G x n_cand weights
-  step_roles<DT, G, false>(a, blockIdx.x, dyn_lds);
+__global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
+  extern __shared__ uint32_t dyn_lds[];              // selection: n_cand keys, then the recall plan
+  touch_args<sizeof(StepArgs)>();
+  step_roles<DT, G>(a, blockIdx.x, blockIdx.y, dyn_lds);
 }
 
-// The scan of the bandwidth-bound regime: append, correction test and page weights only (the selection has
-// a launch of its own there), in 256-thread blocks of one 64-page chunk each.  Measured on the scan alone
-// (256 heads x 992 pages, 130 MB; a plain read of the same bytes takes 22.1 us = 5.9 TB/s on this machine):
-// 23.9 us in this shape against 25.7 us with 512-thread blocks of 128 pages -- the smaller block leaves
-// the unit's slots in finer pieces, so that more blocks are in different phases (loading, computing,
-// draining) at any time; blocks that take several chunks, pipelined or not, are slower than either.
+// The two halves of the bandwidth-bound regime.  The scan: append, correction test and page weights, in 256-thread
+// blocks of one 64-page chunk each; measured on the scan alone (256 heads x 992 pages, 130 MB; a plain read of the same
+// bytes takes 22.1 us = 5.9 TB/s on this machine): 23.9 us in this shape against 25.7 us with 512-thread blocks of 128
+// pages -- the smaller block leaves the unit's slots in finer pieces, so that more blocks are in different phases
+// (loading, computing, draining) at any time; blocks that take several chunks, pipelined or not, are slower than either.
+// A head's chunks are adjacent in block order (blocks that run together read one stretch of memory: 28.2 us with the KV
+// cache between two scans of that size, 30.0 us with the heads next to each other): grid (chunks, heads), below rows of
+// the same width for the other two roles.
 constexpr int SCAN_WAVES = 4, SCAN_PASSES = 4;
 template <int DT, int G>
 __global__ __launch_bounds__(SCAN_WAVES * 64) void scan_kernel(StepArgs a) {
-  const int heads = a.batch * a.n_kv;
-  int bid = blockIdx.x;
-  if (a.roles & ROLE_APPEND) {
-    if (bid < heads) { append_role<DT>(a, bid); return; }
-    bid -= heads;
+  touch_args<sizeof(StepArgs)>();
+  const int y = blockIdx.y;
+  if (y < a.other_rows) {
+    int i = y * a.chunks + blockIdx.x;
+    if (a.roles & ROLE_APPEND) {
+      if (i < a.heads) { append_role<DT>(a, i); return; }
+      i -= a.heads;
+    }
+    if ((a.roles & ROLE_CORR) && i < a.heads) corr_role<DT, G, SCAN_WAVES>(a, i);
+    return;
   }
-  if (a.roles & ROLE_CORR) {
-    if (bid < heads) { corr_role<DT, G, SCAN_WAVES>(a, bid); return; }
-    bid -= heads;
-  }
-  score_role<DT, G, SCAN_WAVES>(a, bid / a.blocks_per_head, bid % a.blocks_per_head);
+  score_role<DT, G, false, SCAN_WAVES>(a, y - a.other_rows, blockIdx.x);
+}
+// The selection after it: one block per slice of a head's candidates, a head's slices adjacent.
+template <int G>
+__global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
+  extern __shared__ uint32_t dyn_lds[];
+  touch_args<sizeof(StepArgs)>();
+  select_role<G, false, SEL_REGS_ALONE>(a, (int)blockIdx.x >> a.slices_log2, (int)blockIdx.x & (a.slices - 1), dyn_lds);
 }
 
-// Dynamic LDS above the default 64 KiB per block has to be granted per kernel function.
-// Returns false if the device refuses (the caller then keeps only the keys in LDS).
-template <int DT, int G>
-static bool raise_lds(size_t lds) {
-  static size_t granted = 0;
+constexpr size_t kLdsPerUnit = 150 * 1024;   // of the 160 KiB of a compute unit
+constexpr int kLayerResident = 2 * kComputeUnits;   // blocks of the layer kernel that the GPU holds at once (by its registers)
+
+// Dynamic LDS above the default 64 KiB per block has to be granted per kernel function; false if the device refuses.
+template <typename F>
+static bool grant_lds(F* fn, size_t lds, size_t& granted) {
   if (lds <= granted) return true;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&step_kernel<DT, G>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
@@ -56,137 +65,68 @@ static bool raise_lds(size_t lds) {
   return true;
 }
 
-// The selection's LDS (keys + staged weights) is allocated for every block of a launch.  When
-// it is small and the launch is at most one round of blocks, the selection rides in the scoring
-// launch (its last block per head runs it); otherwise scoring runs without it and a second
-// launch of one block per head selects.
-constexpr size_t kLdsPerUnit = 150 * 1024;   // of the 160 KiB of a compute unit
-constexpr int kComputeUnits = 256;
-constexpr int kFuseMaxBlocks = kComputeUnits;       // launches up to this size run the selection in their last scoring blocks
-constexpr int kLayerMaxBlocks = 4 * kComputeUnits;  // shapes up to this size take the one-launch layer kernel
-// experiment builds only (see knob()): chunks per scoring block, selection inside the scoring launch
-// (0 never, 1 always), passes a scoring block makes; the defaults choose from the shape
-static const int g_chunks_per_block = knob("FKV_SCORE_CHUNKS", 0);
-static const int g_fuse_mode = knob("FKV_FUSE_SELECT", -1);
-static const int g_min_passes = knob("FKV_LAYER_PASSES", 0);
-static const bool g_scan_kernel = knob("FKV_NO_SCAN_KERNEL", 0) == 0;   // 1: scans stay in 512-thread step_kernel blocks
-// may every block of a `grid`-block launch carry `lds` bytes without starving the scoring blocks?
-static bool lds_fits_launch(size_t lds, int grid) {
-  int per_unit = (grid + kComputeUnits - 1) / kComputeUnits;   // blocks a unit should hold at once
-  if (per_unit < 1) per_unit = 1;
-  if (per_unit > 4) per_unit = 4;
-  return lds * per_unit <= kLdsPerUnit;
+// experiment builds only (see knob())
+static const int g_min_passes = knob("FKV_LAYER_PASSES", 0);      // passes a scoring block makes
+static const int g_slice = knob("FKV_SLICE", 0);                  // candidates per selecting block
+static const int g_one_launch = knob("FKV_ONE_LAUNCH", -1);       // layer-step: 0 separate launches, 1 one launch whenever it can be
+
+static const int g_fuse = knob("FKV_FUSE", -1);
+
+// Selecting blocks of a head, a power of two: each takes at most `most` candidates (its registers), and as few as
+// SEL_REGS per thread as long as the launch stays within kMaxWaiting -- an exchange costs about 2 us in all, a block of
+// 512 candidates more 1.5.
+static int selection_slices(int n_cand, int heads, int most) {
+  const int slice = g_slice > 0 ? g_slice : SEL_REGS * SEL_THREADS;
+  int s = 1;
+  while (s < MAX_SLICES && ((n_cand + s - 1) / s > most || ((n_cand + s - 1) / s > slice && heads * s * 2 <= kMaxWaiting))) s *= 2;
+  return s;
 }
 
-struct WidePlan { const Dims* d; const StepIO* io; bool ok; int B, slice; };
-
-template <int DT, int G>
-static int launch_step_g(StepArgs& a, int grid, int heads, size_t lds_staged, size_t lds_keys, hipStream_t st, const WidePlan& wp) {
-  constexpr size_t kDefaultLimit = 64 * 1024 - 8 * 1024;   // minus this kernel's static LDS, rounded up
-  const bool select = (a.roles & ROLE_SELECT) != 0;
-  size_t lds = lds_staged;
-  a.staged = lds_staged > lds_keys ? 1 : 0;
-  if (select && a.staged && lds > kDefaultLimit && !raise_lds<DT, G>(lds)) {
-    lds = lds_keys;
-    a.staged = 0;
+// Passes of a scoring block: a launch runs in ceil(blocks / resident blocks) rounds, and blocks of a later round (the
+// selection and attention come last) queue behind the scoring blocks.  The passes that give the fewest rounds -- one, the
+// whole launch resident at once, where the shape allows -- and among those the fewest (most blocks).
+static int scoring_passes(const Dims& d, const Geom& g, int slices, int other_rows, int resident) {
+  if (g_min_passes > 0) return g_min_passes;
+  const long heads = (long)d.batch * d.n_kv;
+  int best = 1;
+  long best_rounds = 0;
+  for (int passes = 1; passes <= SCORE_PASSES; passes *= 2) {
+    const long blocks = heads * (2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + other_rows);
+    const long rounds = (blocks + resident - 1) / resident;
+    if (passes == 1 || rounds < best_rounds) { best = passes; best_rounds = rounds; }
   }
-  if (select && !a.staged && lds > kDefaultLimit) (void)raise_lds<DT, G>(lds);
-  // In a launch of many rounds the scoring blocks should end the moment their weights are on the
-  // way: waiting for the stores' acknowledgement and the counter (what the fused selection needs)
-  // would hold the unit's slots for several memory round trips per block.
-  a.fuse_select = (select && lds_fits_launch(lds, grid) && (g_fuse_mode < 0 ? grid <= kFuseMaxBlocks : g_fuse_mode == 1)) ? 1 : 0;
-  a.select_only = 0;
-  // a long candidate list whose selection has its own launch anyway is spread over several blocks per head
-  const bool wide = wp.ok && select && !a.fuse_select;
-  a.bmax = wide ? wp.io->bmax : nullptr;
-  a.bmax_stride = wp.io->bmax_stride;
-  // the recall plan rides at the end of the selecting block's LDS; a spread selection is followed by the plan kernel
-  const bool plan = select && a.plan_new_slots != nullptr;
-  const size_t plan_bytes = plan ? plan_lds_ints(a.k) * sizeof(int32_t) : 0;
-  a.plan_lds_off = (int)((lds - plan_bytes) / sizeof(uint32_t));
-  int32_t* const plan_slots = a.plan_new_slots;
-  auto plan_after_wide = [&]() -> int {
-    if (!plan) return 0;
-    launch_plan(*wp.d, a.ids, a.plan_act_ids, a.plan_act_slots, plan_slots, a.plan_miss, a.g.n_full, st);
-    return 1;
-  };
-  if (wide) a.plan_new_slots = nullptr;
-  if (select && !a.fuse_select && g_scan_kernel) {
-    // the selection does not ride along: the roles go to the scan kernel, one 64-page chunk per 256-thread block
-    StepArgs sa = a;
-    sa.passes = SCAN_PASSES;
-    sa.blocks_per_head = a.g.n_cand > 0 ? (a.g.n_cand + SCAN_WAVES * 4 * SCAN_PASSES - 1) / (SCAN_WAVES * 4 * SCAN_PASSES) : 1;
-    int sgrid = heads * sa.blocks_per_head;
-    if (sa.roles & ROLE_APPEND) sgrid += heads;
-    if (sa.roles & ROLE_CORR) sgrid += heads;
-    const bool fits = !wide || sa.blocks_per_head <= sa.bmax_stride;
-    if (fits) {
-      scan_kernel<DT, G><<<sgrid, SCAN_WAVES * 64, 0, st>>>(sa);
-      if (wide) {
-        launch_wide_select(*wp.d, *wp.io, a.g, wp.B, wp.slice, sa.blocks_per_head, st);
-        return 3 + plan_after_wide();
-      }
-      a.select_only = 1;
-      step_kernel<DT, G><<<heads, STEP_THREADS, lds, st>>>(a);
-      return 2;
-    }
-  }
-  step_kernel<DT, G><<<grid, STEP_THREADS, a.fuse_select ? lds : 0, st>>>(a);
-  if (wide) {
-    launch_wide_select(*wp.d, *wp.io, a.g, wp.B, wp.slice, a.blocks_per_head, st);
-    return 3 + plan_after_wide();
-  }
-  if (select && !a.fuse_select) {
-    a.select_only = 1;
-    step_kernel<DT, G><<<heads, STEP_THREADS, lds, st>>>(a);
-    return 2;
-  }
-  return 1;
+  return best;
 }
 
-template <int DT>
-static int launch_step_dt(StepArgs& a, int G, int grid, int heads, size_t lds_staged, size_t lds_keys, hipStream_t st, const WidePlan& wp) {
-  switch (G) {
-#define FKV_CASE(GG) case GG: return launch_step_g<DT, GG>(a, grid, heads, lds_staged, lds_keys, st, wp);
-    FKV_CASE(1) FKV_CASE(2) FKV_CASE(3) FKV_CASE(4) FKV_CASE(5) FKV_CASE(6) FKV_CASE(7) FKV_CASE(8)
-#undef FKV_CASE
-    default: return 0;
-  }
-}
-
-static void fill_step_args(const Dims& d, int roles, const StepIO& io, Geom g, int passes, bool roomy, StepArgs& a,
-                           int& grid, size_t& lds_staged, size_t& lds_keys, int chunks_per_block = 1) {
+static void fill_step_args(const Dims& d, int roles, const StepIO& io, Geom g, int pages_per_pass, int passes, int slices, StepArgs& a, int& rows, size_t& lds) {
   a = StepArgs{};
   a.roles = roles;
-  a.batch = d.batch; a.n_q = d.n_q; a.n_kv = d.n_kv; a.k = d.k; a.max_pages = d.max_pages;
+  a.heads = d.batch * d.n_kv; a.k = d.k; a.max_pages = d.max_pages;
   a.g = g;
   a.pd = io.pd; a.summ = io.summ; a.k_new = io.k_new; a.v_new = io.v_new;
   a.q = io.q; a.q_prev = io.q_prev; a.q_stage = io.q_stage; a.have_prev = io.have_prev; a.tau = io.tau;
   a.corr_pool = d.corr_pool; a.sel_pool = d.sel_pool;
   a.flags = io.flags; a.flags_user = io.flags_user; a.cosine = io.cosine;
-  a.P = io.P; a.score = io.score; a.ids = io.ids; a.ids_user = io.ids_user; a.counters = io.counters; a.tstamp = io.tstamp;
-  const int heads = d.batch * d.n_kv;
+  a.P = io.P; a.score = io.score; a.ids = io.ids; a.ids_user = io.ids_user; a.exch = io.exch; a.keyx = io.keyx;
+  a.launch_no = io.launch_no; a.status = io.status; a.tstamp = io.tstamp;
   a.passes = passes;
-  const int chunks = g.n_cand > 0 ? (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) : 1;
-  a.blocks_per_head = (chunks + chunks_per_block - 1) / chunks_per_block;
-  grid = 0;
-  lds_staged = lds_keys = 0;
-  if (roles & ROLE_APPEND) grid += heads;
-  if (roles & ROLE_CORR) grid += heads;
+  a.slices = slices;
+  rows = 0;
+  lds = 0;
+  if (roles & ROLE_APPEND) rows += 1;
+  if (roles & ROLE_CORR) rows += 1;
   if (roles & ROLE_SELECT) {
-    grid += heads * a.blocks_per_head;
-    const size_t n = (size_t)(g.n_cand > 0 ? g.n_cand : 1);
-    lds_keys = n * sizeof(uint32_t);
-    lds_staged = n * (1 + d.G) * sizeof(uint32_t);
-    if (io.plan_new_slots) {
+    a.chunks = (g.n_cand + pages_per_pass * passes - 1) / (pages_per_pass * passes);
+    while ((1 << a.slices_log2) < a.slices) a.slices_log2 += 1;
+    a.slice = (g.n_cand + a.slices - 1) / a.slices;
+    rows += a.chunks + a.slices;
+    lds = (size_t)select_key_words(g.n_cand) * sizeof(uint32_t);
+    if (io.plan_new_slots) {                       // the recall plan's LDS follows the keys
       a.plan_act_ids = io.plan_act_ids; a.plan_act_slots = io.plan_act_slots;
       a.plan_new_slots = io.plan_new_slots; a.plan_miss = io.plan_miss;
+      a.plan_lds_off = (int)(lds / sizeof(uint32_t));
+      lds += plan_lds_ints(d.k) * sizeof(int32_t);
     }
-    const size_t plan_bytes = io.plan_new_slots ? plan_lds_ints(d.k) * sizeof(int32_t) : 0;
-    if (lds_staged + plan_bytes + 8192 > (size_t)d.max_lds) lds_staged = lds_keys;   // cannot fit: do not even ask
-    if (n <= (size_t)regs_candidates(d.G, roomy)) lds_staged = lds_keys;   // few enough to stay in registers
-    lds_staged += plan_bytes;                      // the recall plan's LDS follows the selection's
-    lds_keys += plan_bytes;
   }
 }
 
@@ -197,159 +137,199 @@ static bool append_races_selection(int roles, const Geom& g) {
   return (roles & ROLE_APPEND) && (roles & ROLE_SELECT) && g.r == 0 && g.n_win == 0 && g.n_cand > 0;
 }
 
+// Scoring and selection in one launch up to this many pages to score, in units of 32: beyond, the scan is bandwidth-bound
+// and its small blocks, which end the moment their weights are on the way, stream faster.  Whole step, one launch for both
+// against two: 32 KV heads x 992 pages 25.9 us against 27.4, 248 x 320 117 against 119, 192 x 480 equal, 256 x 992 96 against 88.
+constexpr long kFuseMaxChunks = 2560;
+
+template <int DT, int G>
+static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom& g, hipStream_t st) {
+  static size_t granted_step = 48 * 1024, granted_select = 48 * 1024;
+  StepArgs a;
+  int rows;
+  size_t lds;
+  const int heads = d.batch * d.n_kv;
+  if (!(roles & ROLE_SELECT) || (g_fuse >= 0 ? g_fuse == 1 : (long)heads * ((g.n_cand + PAGES_PER_PASS - 1) / PAGES_PER_PASS) <= kFuseMaxChunks)) {
+    const int slices = g.k_eff > 0 ? selection_slices(g.n_cand, heads, SEL_REGS * SEL_THREADS) : 1;
+    fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
+    if (!grant_lds(&step_kernel<DT, G>, lds, granted_step)) return -1;
+    step_kernel<DT, G><<<dim3(heads, rows), STEP_THREADS, lds, st>>>(a);
+    if (roles & ROLE_SELECT) *io.P_tagged = true;
+    return 1;
+  }
+  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCAN_PASSES, g.k_eff > 0 ? selection_slices(g.n_cand, heads, SEL_REGS_ALONE * SEL_THREADS) : 1, a, rows, lds);
+  if (!grant_lds(&select_kernel<G>, lds, granted_select)) return -1;
+  a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
+  scan_kernel<DT, G><<<dim3(a.chunks, a.other_rows + heads), SCAN_WAVES * 64, 0, st>>>(a);
+  select_kernel<G><<<heads * a.slices, SEL_THREADS, lds, st>>>(a);
+  *io.P_tagged = false;
+  return 2;
+}
+
 int launch_step(const Dims& d, int roles, const StepIO& io, Geom g, hipStream_t st) {
   if (d.k == 0) roles &= ~ROLE_SELECT;
   if (roles == 0) return 0;
-  int launches = 0;
   if (append_races_selection(roles, g)) {      // then the append gets a launch of its own first
-    launches += launch_step(d, ROLE_APPEND, io, g, st);
-    roles &= ~ROLE_APPEND;
+    const int n = launch_step(d, ROLE_APPEND, io, g, st);
+    const int m = launch_step(d, roles & ~ROLE_APPEND, io, g, st);
+    return n < 0 || m < 0 ? -1 : n + m;
   }
-  StepArgs a;
-  int grid;
-  size_t lds_staged, lds_keys;
-  // A scoring block lives for one memory round trip whatever it loads, so big scans get fewer
-  // blocks with more pages in flight each, as long as a few blocks per compute unit remain.
-  int passes = g_min_passes > 0 ? g_min_passes : 1;
-  if (g_min_passes <= 0 && (roles & ROLE_SELECT))
-    while (passes < SCORE_PASSES &&
-           (long)d.batch * d.n_kv * ((g.n_cand + PAGES_PER_PASS * passes * 2 - 1) / (PAGES_PER_PASS * passes * 2)) >= 4 * kComputeUnits)
-      passes *= 2;
-  // ... and beyond a few blocks per unit, a block takes several chunks in turn: a block's fixed cost
-  // (dispatch, the query loads, the drain of its stores) is what is left to save once the scan
-  // streams.  (Prefetching the next chunk into a second register set was measured and dropped: the
-  // registers it takes halve the blocks a unit holds, and two blocks that load and compute in turn
-  // stream faster than one that overlaps its own loads.)
-  int chunks_per_block = g_chunks_per_block > 0 ? g_chunks_per_block : 1;
-  if (g_chunks_per_block <= 0 && (roles & ROLE_SELECT)) {
-    const long blocks = (long)d.batch * d.n_kv * ((g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes));
-    while (chunks_per_block < 16 && blocks / chunks_per_block > 4 * kComputeUnits) chunks_per_block *= 2;
+  switch (d.G) {
+#define FKV_CASE(GG) case GG: return d.dtype == 0 ? launch_step_g<0, GG>(d, roles, io, g, st) : launch_step_g<1, GG>(d, roles, io, g, st);
+    FKV_CASE(1) FKV_CASE(2) FKV_CASE(3) FKV_CASE(4) FKV_CASE(5) FKV_CASE(6) FKV_CASE(7) FKV_CASE(8)
+#undef FKV_CASE
+    default: return -1;
   }
-  fill_step_args(d, roles, io, g, passes, false, a, grid, lds_staged, lds_keys, chunks_per_block);
-  WidePlan wp{&d, &io, false, 0, 0};
-  wp.ok = (roles & ROLE_SELECT) && io.bmax && a.blocks_per_head <= io.bmax_stride && knob("FKV_NO_WIDE_SELECT", 0) == 0 && wide_plan(d, g, &wp.B, &wp.slice);
-  if (d.dtype == 0) launches += launch_step_dt<0>(a, d.G, grid, d.batch * d.n_kv, lds_staged, lds_keys, st, wp);
-  else              launches += launch_step_dt<1>(a, d.G, grid, d.batch * d.n_kv, lds_staged, lds_keys, st, wp);
-  return launches;
 }
 
 // ---------------------------------------------------------------------------------
-// The whole layer-step in ONE launch (KV in HBM, small selections): the step roles followed by
-// the attention blocks.  In a step without correction the two chains do not depend on each
-// other -- attention reads the previous step's page ids, takes the new token from the step's
-// inputs and redoes the (tiny) correction test itself -- so they overlap; the attention blocks
+// The whole layer-step in ONE launch: the step roles followed by the attention blocks.  In a step without correction
+// the two chains do not depend on each other -- attention reads the previous step's page ids, takes the new token from
+// the step's inputs and redoes the (tiny) correction test itself -- so they overlap; the attention blocks
 // of a corrected head wait for that head's selection, made by blocks with lower indices.
+// grid (heads, step rows + splits)
 // ---------------------------------------------------------------------------------
-struct LayerArgs {
-  StepArgs s;
-  AttnArgs at;
-  int attn_block0;     // index of the first attention block
-};
+typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // (scalar loads)
+
+// packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), pages per
+// split (9), lose_selection;   split_magic: 2^32 / splits rounded up, 0 for one split
+constexpr int kMaxLayersPacked = 1 << 13, kMaxCtxPacked = 1 << 19;
 
 template <int DT, int G, bool HOSTPOOL>
-__global__ __launch_bounds__(STEP_THREADS, STEP_THREADS <= 256 ? 2 : 1) void layer_kernel(LayerArgs a) {
+__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
+                  uint32_t packed, uint32_t launch, uint32_t plan, uint32_t split_magic) {
   extern __shared__ uint32_t dyn_lds[];
-  if ((int)blockIdx.x < a.attn_block0) {
-    step_roles<DT, G, true>(a.s, blockIdx.x, dyn_lds);
+  LayerConstPtr c = (LayerConstPtr)consts;
+  touch<sizeof(LayerConst)>(c);
+  const int layer = (int)(packed >> 19), parity = (int)(plan >> 1) & 1;
+  char* const base = c->dev_base + c->layer_bytes * (unsigned long long)layer;
+  auto at = [&](uint32_t o) { return base + (unsigned long long)o * 256; };
+  const Geom g = geom_of((int)(packed & 0x7ffffu) + 1, c->n_sink, c->n_win, c->k);
+  const uint32_t tag = host_tag(launch);
+  PoolDesc pd;
+  pd.pool = reinterpret_cast<uint16_t*>(base);
+  pd.units_per_head = c->units_per_head;
+  pd.placement = HOSTPOOL ? 1 : 0;
+  pd.ring_base = c->ring_base; pd.n_ring = c->n_ring; pd.sel_base = c->sel_base;
+  uint16_t* const qprev0 = reinterpret_cast<uint16_t*>(at(c->o_qprev));
+  int32_t* const ids0 = reinterpret_cast<int32_t*>(at(c->o_ids));
+  int32_t* const slots0 = reinterpret_cast<int32_t*>(at(c->o_slots));
+  const int now = parity, before = parity ^ 1;             // halves: PENDING / staged, ACTIVE / previous
+  const int passes_log2 = (int)(plan >> 2) & 3, chunk_log2 = 5 + passes_log2;
+  static_assert(PAGES_PER_PASS == 32, "chunks are a power of two of pages");
+  const int chunks = (g.n_cand + (1 << chunk_log2) - 1) >> chunk_log2;
+  const int slices_log2 = (int)(plan >> 4) & 7, slices = 1 << slices_log2;
+  const int step_rows = 2 + chunks + slices;
+  int* const status = reinterpret_cast<int*>(at(c->o_status));
+  if ((int)blockIdx.y < step_rows) {
+    StepArgs a;
+    a.roles = ROLE_APPEND | ROLE_CORR | ROLE_SELECT;
+    a.heads = c->heads; a.k = c->k; a.max_pages = c->max_pages; a.g = g; a.pd = pd;
+    a.summ = reinterpret_cast<uint16_t*>(at(c->o_summ));
+    a.k_new = k_new; a.v_new = v_new; a.q = q;
+    a.q_prev = qprev0 + (size_t)before * c->qprev_half; a.q_stage = qprev0 + (size_t)now * c->qprev_half;
+    a.have_prev = (int)(plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
+    a.flags = reinterpret_cast<uint8_t*>(at(c->o_flags)); a.flags_user = nullptr;
+    a.cosine = reinterpret_cast<double*>(at(c->o_cosine));
+    a.sel_pool = c->sel_pool; a.P = c->P; a.score = c->score;
+    a.ids = ids0 + (size_t)now * c->ids_half; a.ids_user = nullptr;
+    a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
+    a.slice = (g.n_cand + slices - 1) >> slices_log2;
+    a.exch = c->exch; a.keyx = c->keyx; a.tag = tag; a.launch_no = nullptr; a.status = status; a.tstamp = c->tstamp;
+    a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
+    a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
+    if (HOSTPOOL) {
+      a.plan_act_ids = ids0 + (size_t)before * c->ids_half;
+      a.plan_act_slots = slots0 + (size_t)before * c->ids_half;
+      a.plan_new_slots = slots0 + (size_t)now * c->ids_half;
+      a.plan_miss = reinterpret_cast<int32_t*>(at(c->o_miss));
+      a.plan_lds_off = select_key_words(g.n_cand);
+    }
+    step_roles<DT, G>(a, blockIdx.x, blockIdx.y, dyn_lds);
     return;
   }
-  const int ab = blockIdx.x - a.attn_block0, heads = a.s.batch * a.s.n_kv;
-  const int head = ab % heads, split = ab / heads;
-  attn_block<DT, STEP_WAVES, HOSTPOOL>(a.at, split, head % a.s.n_kv, head / a.s.n_kv, reinterpret_cast<float*>(dyn_lds));
+  AttnArgs a;
+  a.pd = pd; a.q = q;
+  a.act_ids = ids0 + (size_t)before * c->ids_half; a.new_ids = nullptr;
+  a.act_slots = HOSTPOOL ? slots0 + (size_t)before * c->ids_half : nullptr; a.new_slots = nullptr;
+  a.flags = nullptr; a.use = 2; a.part = c->part; a.part_ml = c->part_ml; a.max_splits = c->max_splits;
+  a.n_splits = (int)(plan >> 7) & 63; a.pps = (int)(plan >> 13) & 511;
+  a.share = split_magic ? (int)__umulhi((uint32_t)(G * D + a.n_splits - 1), split_magic) : G * D;
+  a.launch_no = nullptr; a.launch_stride = 0; a.out = out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
+  a.status = status; a.tstamp = c->tstamp;
+  a.q_prev = qprev0 + (size_t)before * c->qprev_half; a.have_prev = (int)(plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
+  a.k_new = k_new; a.v_new = v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
+  a.tag = tag; a.pick_tag = tag + ((plan >> 22) & 1u ? 2u : 0u);
+  a.host_pool = HOSTPOOL ? reinterpret_cast<const uint16_t*>(c->host_base + c->host_layer_bytes * (unsigned long long)layer) : nullptr;
+  a.max_pages = c->max_pages;
+  // numbered through row by row, so that a head's blocks, which wait for each other, are adjacent
+  const uint32_t i = (blockIdx.y - (uint32_t)step_rows) * (uint32_t)c->heads + blockIdx.x;
+  const uint32_t head = split_magic ? __umulhi(i, split_magic) : i;
+  attn_block<DT, STEP_WAVES, true, HOSTPOOL>(a, (int)(i - head * (uint32_t)a.n_splits), (int)head, reinterpret_cast<float*>(dyn_lds));
 }
 
-// experiment builds only: 1 = always separate launches, 0 = one launch whenever it fits
-static const bool g_no_layer_kernel = knob("FKV_NO_LAYER_KERNEL", -1) == 1;
-static const bool g_layer_always = knob("FKV_NO_LAYER_KERNEL", -1) == 0;
+struct LayerLaunch { dim3 grid; size_t lds; uint32_t packed, plan, split_magic; };
 
 template <int DT, int G, bool HOSTPOOL>
-static bool launch_layer_gh(const LayerArgs& a, int grid, size_t lds, hipStream_t st) {
-  static size_t granted = 48 * 1024;      // dynamic LDS beyond the default has to be granted per function
-  if (lds > granted) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&layer_kernel<DT, G, HOSTPOOL>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
-    granted = lds;
-  }
-  layer_kernel<DT, G, HOSTPOOL><<<grid, STEP_THREADS, lds, st>>>(a);
+static bool launch_layer_gh(const LayerIO& io, const LayerLaunch& l, hipStream_t st) {
+  static size_t granted = 48 * 1024;
+  if (!grant_lds(&layer_kernel<DT, G, HOSTPOOL>, l.lds, granted)) return false;
+  layer_kernel<DT, G, HOSTPOOL><<<l.grid, STEP_THREADS, l.lds, st>>>(io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.launch, l.plan, l.split_magic);
   return true;
 }
 template <int DT, int G>
-static bool launch_layer_g(const LayerArgs& a, int grid, size_t lds, hipStream_t st) {
-  return a.at.host_pool ? launch_layer_gh<DT, G, true>(a, grid, lds, st) : launch_layer_gh<DT, G, false>(a, grid, lds, st);
+static bool launch_layer_g(const LayerIO& io, const LayerLaunch& l, hipStream_t st) {
+  return io.host_pool ? launch_layer_gh<DT, G, true>(io, l, st) : launch_layer_gh<DT, G, false>(io, l, st);
 }
 
-bool launch_layer(const Dims& d, const StepIO& io, const LayerIO& lio, Geom g, hipStream_t st) {
+// Which layer-steps take one launch: those that latency bounds.  Measured, one launch against separate ones: 32 KV heads of
+// 8K / 32K / 128K tokens 11 / 16 / 28 us against 19 / 26 / 37, 128 of 2K / 16K / 32K 18 / 27 / 53 against 25 / 31 / 55, and
+// 192 x 65 attended pages 62 against 65.  With 256 KV heads and more, attention by itself has a block for every compute
+// unit and its bytes decide (256 heads of 32K tokens: 103 against 92), as they do beyond kLayerMaxAttended pages (128 x 129:
+// 64 against 70; 248 x 129: 133 against 117).  With the KV in a host pool the link decides early: 64 heads of 16K tokens
+// 241 against 243, 32 of 124K 183 against 183, so the bigger ones take the gather of its own.
+constexpr int kLayerMaxHeads = kComputeUnits - 1;
+constexpr long kLayerMaxAttended = 24576, kLayerMaxBlocks = 2560, kLayerMaxBlocksHost = 1024;
+
+bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const int roles = ROLE_APPEND | ROLE_CORR | ROLE_SELECT;
-  if (g_no_layer_kernel || d.k == 0 || append_races_selection(roles, g)) return false;
-  if (io.pd.placement != 0) {
-    // KV in a host pool: the selecting blocks make the recall plan, the attention blocks of a corrected head fetch its
-    // missing pages themselves; the tagged words have to hold a page id and a slot
-    if (!io.plan_new_slots || !lio.host_pool || d.max_pages > TAGGED_MAX_PAGES || 2 * d.k > TAGGED_MAX_SLOTS) return false;
-  }
-  {   // a candidate list long enough for the selection to be spread over several blocks takes the separate launches
-    int wb, ws;
-    if (io.bmax && knob("FKV_NO_WIDE_SELECT", 0) == 0 && wide_plan(d, g, &wb, &ws)) return false;
-  }
-  LayerArgs a{};
-  int grid = 0;
-  size_t lds = 0;
-  // the launch with scoring blocks that make `passes` passes; does every block's LDS fit?
-  auto plan = [&](int passes) -> bool {
-    size_t lds_staged, lds_keys;
-    fill_step_args(d, roles, io, g, passes, true, a.s, grid, lds_staged, lds_keys);
-    a.s.staged = lds_staged > lds_keys ? 1 : 0;
-    a.s.fuse_select = 1;
-    a.s.select_only = 0;
-    a.s.tagged = lio.tagged;
-    a.s.epoch = lio.epoch;
-    a.s.plan_lds_off = (int)((lds_staged - (a.s.plan_new_slots ? plan_lds_ints(d.k) * sizeof(int32_t) : 0)) / sizeof(uint32_t));
-    const int heads = d.batch * d.n_kv;
-    const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
-    AttnArgs& at = a.at;
-    at.pd = io.pd; at.q = io.q; at.act_ids = lio.act_ids; at.new_ids = io.ids;
-    at.act_slots = io.plan_act_slots; at.new_slots = io.plan_new_slots;       // (null with the KV in HBM)
-    at.host_pool = lio.host_pool; at.max_pages = d.max_pages;
-    at.flags = io.flags; at.use = 2; at.part_o = lio.part_o; at.part_ml = lio.part_ml; at.max_splits = lio.max_splits;
-    at.pps = attn_pages_per_block(n_att, heads, lio.max_splits, STEP_WAVES);
-    at.n_splits = (n_att + at.pps - 1) / at.pps;
-    at.counters = lio.attn_counters; at.out = lio.out; at.g = g;
-    at.n_q = d.n_q; at.n_kv = d.n_kv; at.G = d.G; at.k = d.k; at.tstamp = io.tstamp;
-    at.fused = 1; at.q_prev = io.q_prev; at.have_prev = io.have_prev; at.tau = io.tau; at.corr_pool = d.corr_pool;
-    at.k_new = io.k_new; at.v_new = io.v_new; at.tagged = lio.tagged; at.epoch = lio.epoch + lio.attn_epoch_bias; at.status = lio.status;
-    a.attn_block0 = grid;
-    grid += heads * at.n_splits;
-    const size_t lds_attn = (size_t)STEP_WAVES * (32 + d.G * D) * sizeof(float);
-    lds = lds_staged > lds_attn ? lds_staged : lds_attn;
-    return lds_fits_launch(lds, grid);
-  };
-  // The kernel's registers allow one block per compute unit at a time, so a launch runs in
-  // ceil(blocks / units) rounds, and blocks of a later round (attention comes last) queue behind
-  // the scoring blocks.  Take the passes per scoring block that give the fewest rounds -- one, the
-  // whole launch resident at once, where the shape allows -- and among those the fewest passes
-  // (most blocks); fatter scoring blocks are also what lets a big selection's LDS fit at all.
-  int chosen = 0, best_rounds = 0;
-  for (int passes = g_min_passes > 0 ? g_min_passes : 1; passes <= SCORE_PASSES; passes *= 2) {
-    if (!plan(passes)) continue;
-    const int rounds = (grid + kComputeUnits - 1) / kComputeUnits;
-    if (!chosen || rounds < best_rounds) { chosen = passes; best_rounds = rounds; }
-    if (g_min_passes > 0) break;
-  }
-  // Big shapes are bandwidth-bound, not latency-bound: there the separate kernels, with their
-  // smaller register footprints and blocks that never wait, stream faster than this one.
-  const bool fits = chosen != 0 && plan(chosen) && (grid <= kLayerMaxBlocks || g_layer_always);
-  if (!fits) return false;                                 // big selections keep their own launches
-  if (lio.launch_grid) *lio.launch_grid = grid;
-  if (lio.launch_lds) *lio.launch_lds = lds;
+  if (g_one_launch == 0 || d.k == 0 || append_races_selection(roles, g)) return false;
+  if (io.layer >= kMaxLayersPacked || g.L > kMaxCtxPacked) return false;
+  // KV in a host pool: the selecting blocks make the recall plan, the attention blocks of a corrected head fetch its
+  // missing pages themselves; the tagged words have to hold a page id and a slot
+  if (io.host_pool && (d.max_pages > TAGGED_MAX_PAGES || 2 * d.k > TAGGED_MAX_SLOTS)) return false;
+  const int heads = d.batch * d.n_kv;
+  const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
+  const int slices = g.k_eff > 0 ? selection_slices(g.n_cand, heads, SEL_REGS * SEL_THREADS) : 1;
+  const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, kMaxWaiting - (slices > 1 ? heads * slices : 0));
+  const int n_splits = (n_att + pps - 1) / pps;
+  if (n_splits > 63 || pps > 511) return false;
+  const int passes = scoring_passes(d, g, slices, n_splits, kLayerResident);
+  const int passes_log2 = passes == 4 ? 2 : passes == 2 ? 1 : 0;
+  int slices_log2 = 0;
+  while ((1 << slices_log2) < slices) slices_log2 += 1;
+  const int rows = 2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + n_splits;
+  LayerLaunch l;
+  l.lds = (size_t)select_key_words(g.n_cand) * sizeof(uint32_t) + (io.host_pool ? plan_lds_ints(d.k) * sizeof(int32_t) : 0);
+  const size_t lds_attn = (size_t)attn_lds_floats(STEP_WAVES, d.G) * sizeof(float);
+  if (lds_attn > l.lds) l.lds = lds_attn;
+  const long blocks = (long)heads * rows;
+  if (g_one_launch < 0 && (heads > kLayerMaxHeads || (long)heads * n_att > kLayerMaxAttended ||
+                           blocks > (io.host_pool ? kLayerMaxBlocksHost : kLayerMaxBlocks) || l.lds > kLdsPerUnit / 2)) return false;
+  l.grid = dim3(heads, rows);
+  l.packed = (uint32_t)(g.L - 1) | (uint32_t)io.layer << 19;
+  l.plan = (io.have_prev ? 1u : 0u) | (uint32_t)io.parity << 1 | (uint32_t)passes_log2 << 2 | (uint32_t)slices_log2 << 4 |
+           (uint32_t)n_splits << 7 | (uint32_t)pps << 13 | (io.lose_selection ? 1u << 22 : 0u);
+  l.split_magic = n_splits > 1 ? 0xffffffffu / (uint32_t)n_splits + 1u : 0u;      // exact for the block counts of a layer launch
+  *io.launch_grid = (int)blocks;
+  *io.launch_lds = l.lds;
   switch (d.G) {
-#define FKV_CASE(GG) case GG: return d.dtype == 0 ? launch_layer_g<0, GG>(a, grid, lds, st) : launch_layer_g<1, GG>(a, grid, lds, st);
+#define FKV_CASE(GG) case GG: return d.dtype == 0 ? launch_layer_g<0, GG>(io, l, st) : launch_layer_g<1, GG>(io, l, st);
     FKV_CASE(1) FKV_CASE(2) FKV_CASE(3) FKV_CASE(4) FKV_CASE(5) FKV_CASE(6) FKV_CASE(7) FKV_CASE(8)
 #undef FKV_CASE
     default: return false;
   }
-  return true;
 }
 
 // ---------------------------------------------------------------------------------

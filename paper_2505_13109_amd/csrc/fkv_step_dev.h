@@ -1,5 +1,5 @@
 // Device code of the "step" roles: token append + incremental summaries, correction test, page weights,
-// and (by the last scoring block of each KV head) softmax -> group-mean pooling -> top-k.
+// and softmax -> group-mean pooling -> top-k.
 // One launch; blocks take roles by index, because the three jobs do not depend on each
 // other inside a step: the page being appended to is never a candidate, and a page that
 // becomes a candidate had its summary completed at least a window ago.
@@ -19,11 +19,11 @@
 //            corrections (see div_rn);
 //            (alternatives, App. B.2: fl32(max_g E_g / Z_g); the fp32 sum of the weights in head
 //            order divided by G, or their maximum; the weight of the group's mean or maximum query)
-//   top-k:   radix select on the order-preserving image of the fp32 bit pattern, ties to the
-//            lower page id.
+//   top-k:   on the order-preserving image of the fp32 bit pattern, ties to the lower page id.
 #pragma once
 #include "fkv_device.h"
 #include "fkv_plan_dev.h"
+#include "fkv_attn_dev.h"
 
 #pragma clang fp contract(off)
 
@@ -41,10 +41,11 @@ constexpr int STEP_THREADS = FKV_STEP_THREADS;         // >= 256 (the radix hist
 constexpr int STEP_WAVES = STEP_THREADS / 64;
 constexpr int SCORE_PASSES = FKV_SCORE_PASSES;         // most passes a scoring block can make (StepArgs::passes <= this)
 constexpr int PAGES_PER_PASS = STEP_WAVES * 4;         // a wave scores 4 pages per pass
+constexpr int MAX_SLICES = 16;                         // most blocks that share one head's selection
 
 struct StepArgs {
   int roles;                 // ROLE_* bits
-  int batch, n_q, n_kv, k, max_pages;
+  int heads, k, max_pages;
   Geom g;                    // geometry with the appended token counted
   // append
   PoolDesc pd;
@@ -63,21 +64,25 @@ struct StepArgs {
   double* cosine;
   // selection
   int sel_pool;              // FKV_POOL_*
-  float* P;
+  unsigned long long* P;     // page weights [query heads][max_pages], tagged; in a launch that only scores and one that
+                             // only selects: plain fp32 in the same order
   float* score;
   int32_t* ids;
   int32_t* ids_user;
-  int* counters;
-  int blocks_per_head;       // scoring blocks of a KV head; block i takes chunks i, i + blocks_per_head, ...
-  int passes;                // passes of PAGES_PER_PASS pages a scoring block makes (1 .. SCORE_PASSES)
-  int staged;                // the G x n_cand weights fit in LDS next to the keys
-  int fuse_select;           // the last scoring block of a head runs its selection (else: a second launch does)
-  int select_only;           // this launch: one block per head, selection only
-  float* bmax;               // if not null: [heads][bmax_stride][MAX_G], every scoring block leaves the per-head maxima of
-  int bmax_stride;           // the weights it wrote (for a selection spread over several blocks per head)
+  int chunks;                // scoring blocks of a KV head
+  int other_rows;            // scan: rows of its grid for the other roles
+  int passes;                // passes a scoring block makes (1 .. SCORE_PASSES)
+  int slices, slices_log2;   // selecting blocks of a KV head (1 .. MAX_SLICES, a power of two)
+  int slice;                 // candidates of each (the last may have fewer)
+  unsigned long long* exch;  // [heads][MAX_SLICES][3 * MAX_G] tagged: what a head's selecting blocks tell each other
+  unsigned long long* keyx;  // [heads][max_pages] tagged: the candidates' keys, for the head's last selecting block
+  uint32_t tag;              // tag of this launch; or
+  int* launch_no;            // if not null: [heads] number of the last launch, moved on by a head's last selecting block
+                             // (counted on the device, so that a captured launch has new tags at every replay)
+  int* status;               // set to 1 if a wait ran out
   long long* tstamp;         // debug: 100 MHz timestamps of head 0's phases (may be null)
-  unsigned long long* tagged; // if not null: [heads][k], every picked id once more as (epoch << 32 | id): a block of
-  int epoch;                  // this launch that waits for the selection polls the word it needs
+  unsigned long long* tagged; // if not null: [heads][k], every picked id once more as a tagged word: a block of
+                              // this launch that waits for the selection polls the word it needs
   // KV in a host pool: the selecting block also makes the head's recall plan (fkv_plan_dev.h).  plan_new_slots null:
   // not here.  The tagged words then carry, instead of the bare id, what a waiting attention wave needs to fetch the
   // page: tagged_pick() of (page id, slot, miss).
@@ -96,15 +101,14 @@ template <int DT>
 __device__ __forceinline__ void append_role(const StepArgs& a, int head) {
   const int c = threadIdx.x;
   if (c >= D) return;   // 128 of the block's threads
-  const int b = head / a.n_kv, m = head % a.n_kv;
   const int pos = a.g.L - 1, page = pos / PG, t = pos % PG;
   const uint16_t kb = a.k_new[(size_t)head * D + c];
   const uint16_t vb = a.v_new[(size_t)head * D + c];
-  uint16_t* pmax = a.summ + summ_idx(b, m, a.n_kv, 0, a.max_pages, page) + c;
-  uint16_t* pmin = a.summ + summ_idx(b, m, a.n_kv, 1, a.max_pages, page) + c;
+  uint16_t* pmax = a.summ + summ_idx(0, head, 0, 0, a.max_pages, page) + c;
+  uint16_t* pmin = a.summ + summ_idx(0, head, 0, 1, a.max_pages, page) + c;
   uint16_t omax = kb, omin = kb;
   if (t != 0) { omax = *pmax; omin = *pmin; }
-  uint16_t* unit = a.pd.pool + (head_base(a.pd, b, m, a.n_kv) + resident_unit(a.pd, page)) * UNIT_ELEMS;
+  uint16_t* unit = a.pd.pool + ((size_t)head * a.pd.units_per_head + resident_unit(a.pd, page)) * UNIT_ELEMS;
   unit[k_elem_off(t, c)] = kb;
   unit[v_elem_off(t, c)] = vb;
   const float kf = Unpack<DT>::one(kb);
@@ -118,21 +122,19 @@ __device__ __forceinline__ void append_role(const StepArgs& a, int head) {
 template <int DT, int G, int WAVES = STEP_WAVES>
 __device__ __forceinline__ void corr_role(const StepArgs& a, int head) {
   __shared__ double cg[MAX_G];
-  const int b = head / a.n_kv, m = head % a.n_kv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int gg = wave; gg < G; gg += WAVES) {
-    const size_t off = (size_t)(b * a.n_q + m * G + gg) * D;
+    const size_t off = ((size_t)head * G + gg) * D + lane * 2;
+    const uint32_t qw = *reinterpret_cast<const uint32_t*>(a.q + off);
     double cosv = 0.0;
-    uint32_t qw;
-    if (a.have_prev) cosv = head_cosine<DT>(a.q + off, a.q_prev + off, lane, &qw);
-    else qw = *reinterpret_cast<const uint32_t*>(a.q + off + lane * 2);
-    *reinterpret_cast<uint32_t*>(a.q_stage + off + lane * 2) = qw;
-    if (lane == 0) {
+    if (a.have_prev) cosv = cosine_of<DT>(qw, *reinterpret_cast<const uint32_t*>(a.q_prev + off));
+    *reinterpret_cast<uint32_t*>(a.q_stage + off) = qw;
+    if (lane == 63) {
       cg[gg] = cosv;
-      a.cosine[b * a.n_q + m * G + gg] = cosv;
+      a.cosine[head * G + gg] = cosv;
     }
   }
-  __syncthreads();
+  lds_barrier();
   if (threadIdx.x == 0) {
     uint8_t f = 1;
     if (a.have_prev) f = (uint8_t)pooled_flag(cg, G, a.tau, a.corr_pool);
@@ -155,41 +157,42 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // role: page weights P^h_j from the min-max summaries (Sec. 3.2).
 // A 16-lane group owns one page: lane c8 holds channels 8*c8 .. 8*c8+7 of kmax and
 // kmin (one 16-byte load each, 1 KiB contiguous per wave and array), so a wave
-// scores 4 pages and a block 16 pages.
+// scores 4 pages per pass.  All loads of a block's passes are issued before the first use.
+// Weights that blocks of the same launch wait for (TAGGED) are collected in LDS and go out as whole runs per query head;
+// for a later launch each pass stores its own, which leaves the waves of a bandwidth-bound scan independent of each other
+// (28.2 us against 30.3 us through LDS for 256 heads x 992 pages).
 // ---------------------------------------------------------------------------------
-template <int DT, int G, bool QMODE, int WAVES = STEP_WAVES>
+__device__ __forceinline__ uint32_t launch_tag(const StepArgs& a, int head) {
+  return a.launch_no ? device_tag((uint32_t)a.launch_no[head] + 1u) : a.tag;
+}
+
+template <int DT, int G, bool QMODE, bool TAGGED, int WAVES>
 __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chunk) {
-  constexpr int PAGES_PER_PASS = WAVES * 4;               // (of this block size)
-  const int b = head / a.n_kv, m = head % a.n_kv;
+  constexpr int PASS = WAVES * 4;                         // pages per pass
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane >> 4, c8 = lane & 15;
-  const int pages_per_chunk = PAGES_PER_PASS * a.passes;
-  if (chunk * pages_per_chunk >= a.g.n_cand) return;      // a block that only exists to run the selection
-  // all summary loads of a chunk's passes first, then q: everything is in flight at once
+  const int n = a.g.n_cand, j0 = chunk * PASS * a.passes + wave * 4 + grp;
   uint4 wmax[SCORE_PASSES], wmin[SCORE_PASSES];
-  int page[SCORE_PASSES];
-  auto load_chunk = [&](int ch) {
+  const uint16_t* sm = a.summ + summ_idx(0, head, 0, 0, a.max_pages, a.g.cand_lo) + c8 * 8;
+  const size_t to_min = (size_t)a.max_pages * D;
 #pragma unroll
-    for (int ps = 0; ps < SCORE_PASSES; ++ps) {
-      const int j = ch * pages_per_chunk + ps * PAGES_PER_PASS + wave * 4 + grp;
-      page[ps] = (ps < a.passes && j < a.g.n_cand) ? a.g.cand_lo + j : -1;
-      const int pg = a.g.cand_lo + (j < a.g.n_cand ? j : 0);
-      if (ps < a.passes) {
-        wmax[ps] = *reinterpret_cast<const uint4*>(a.summ + summ_idx(b, m, a.n_kv, 0, a.max_pages, pg) + c8 * 8);
-        wmin[ps] = *reinterpret_cast<const uint4*>(a.summ + summ_idx(b, m, a.n_kv, 1, a.max_pages, pg) + c8 * 8);
-      }
+  for (int ps = 0; ps < SCORE_PASSES; ++ps) {
+    if (ps < a.passes) {
+      const int j = min(j0 + ps * PASS, n - 1);
+      wmax[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D);
+      wmin[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D + to_min);
     }
-  };
-  load_chunk(chunk);
+  }
+  const uint32_t tag = TAGGED ? launch_tag(a, head) : 0u;
   float f[G][8];
 #pragma unroll
   for (int gg = 0; gg < G; ++gg) {
-    const uint4 wq = *reinterpret_cast<const uint4*>(a.q + (size_t)(b * a.n_q + m * G + gg) * D + c8 * 8);
+    const uint4 wq = *reinterpret_cast<const uint4*>(a.q + ((size_t)head * G + gg) * D + c8 * 8);
     unpack8<DT>(wq, f[gg]);
   }
   // Variants that pool the QUERY over the group (App. B.2, MeanQ / MaxQ): one pooled query per KV
-  // head takes the place of head 0 of the group, and only its row of P is written.
-  constexpr int NG = QMODE ? 1 : G;                       // rows of P this launch writes per KV head
+  // head takes the place of head 0 of the group, and only its weight is written.
+  constexpr int NG = QMODE ? 1 : G;                       // weights this launch writes per page
   if (QMODE) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
@@ -202,11 +205,7 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
     }
   }
   const float scale = 0x1.6a09e6p-4f;   // fl32(1/sqrt(128))
-  float* const prow = a.P + (size_t)(b * a.n_q + m * G + (c8 < NG ? c8 : 0)) * a.max_pages;
-  float best = -__builtin_inff();                         // largest weight this lane has written (query head c8)
-  // a block of a big scan takes every blocks_per_head-th chunk of its head, one after the other
-  for (int ch = chunk; ch * pages_per_chunk < a.g.n_cand; ch += a.blocks_per_head) {
-  if (ch != chunk) load_chunk(ch);
+  __shared__ float s_w[NG][TAGGED ? PASS * SCORE_PASSES : 1];
 #pragma unroll
   for (int ps = 0; ps < SCORE_PASSES; ++ps) {
     if (ps >= a.passes) break;
@@ -241,40 +240,30 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
       s = s + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s), 0x140, 0xf, 0xf, false));
       mine = c8 == gg ? s : mine;
     }
-    // one store per pass: lane c8 of a page's 16 lanes writes the weight of query head c8
-    // (device-scope only if a block of this launch is going to read it)
-    if (c8 < NG && page[ps] >= 0) {
-      if (a.fuse_select) st_dev(prow + page[ps], mine * scale);
-      else prow[page[ps]] = mine * scale;
-      best = fmaxf(best, mine * scale);
+    if (TAGGED) {
+      if (c8 < NG) s_w[c8][ps * PASS + wave * 4 + grp] = mine * scale;
+    } else {
+      const int j = j0 + ps * PASS;
+      if (c8 < NG && j < n) reinterpret_cast<float*>(a.P)[((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j] = mine * scale;
     }
   }
-  }
-  if (a.bmax) {
-    // the block's per-head maxima, for whoever needs the head's: over the wave's four 16-lane groups, then
-    // over the waves through LDS; plain stores (the readers are later launches)
-    __shared__ float s_best[WAVES][MAX_G];
-    best = fmaxf(best, __shfl_xor(best, 16, 64));
-    best = fmaxf(best, __shfl_xor(best, 32, 64));
-    if (lane < NG) s_best[wave][lane] = best;
-    __syncthreads();
-    if (threadIdx.x < NG) {
-      float v = s_best[0][threadIdx.x];
-#pragma unroll
-      for (int w = 1; w < WAVES; ++w) v = fmaxf(v, s_best[w][threadIdx.x]);
-      a.bmax[((size_t)head * a.bmax_stride + chunk) * MAX_G + threadIdx.x] = v;
-    }
+  if (!TAGGED) return;
+  lds_barrier();
+  const int pages_log2 = __builtin_ctz(PASS * a.passes), pages = 1 << pages_log2, at0 = chunk * pages;     // (powers of two)
+  for (int i = threadIdx.x; i < NG * pages; i += WAVES * 64) {
+    const int gg = i >> pages_log2, jj = i & (pages - 1);
+    if (at0 + jj < n) st_tag(a.P + ((size_t)head * G + gg) * a.max_pages + a.g.cand_lo + at0 + jj, __float_as_uint(s_w[gg][jj]), tag);
   }
 }
 
-template <int DT, int G, int WAVES = STEP_WAVES>
+template <int DT, int G, bool TAGGED, int WAVES>
 __device__ __forceinline__ void score_role(const StepArgs& a, int head, int chunk) {
-  if (a.sel_pool >= 4) score_pages<DT, G, true, WAVES>(a, head, chunk);
-  else                 score_pages<DT, G, false, WAVES>(a, head, chunk);
+  if (a.sel_pool >= 4) score_pages<DT, G, true, TAGGED, WAVES>(a, head, chunk);
+  else                 score_pages<DT, G, false, TAGGED, WAVES>(a, head, chunk);
 }
 
 // ---------------------------------------------------------------------------------
-// softmax -> group mean -> top-k for one KV head, by one 256-thread block.
+// softmax -> group mean -> top-k of one KV head: the arithmetic.
 // ---------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t softmax_fixed(float p, float mx) {
   const float x = p - mx;
@@ -345,450 +334,454 @@ __device__ __forceinline__ float pooled_score(const uint32_t* e, const double* z
 }
 
 // ---------------------------------------------------------------------------------
-// Block-wide top-kk of n keys held in LDS, ties to the lower index: emit(pos, j) is called for the
-// chosen j in ascending order of j with pos = 0 .. kk-1 (whichever thread owns j calls it).
-// Before the call (and a barrier): hist[3] holds the counts of the keys' top bytes, hist[0..2] zeros.
-// 1 <= kk <= n.
+// role: selection of one KV head by a.slices groups of SEL_THREADS threads with a.slice candidates each.  Each group keeps
+// its candidates' G values in registers from the weights to the key; what needs the whole head is exchanged as tagged
+// words: the per-head maxima, the integer softmax sums (exact, so their order does not matter), and the keys, which the
+// last group turns into the top-k.  A head's groups are adjacent in block order and wait for each other and for scoring
+// blocks (lower indices) only.
+//
+// What bounds it: a chain of short phases, each of them instructions of the waves that share a SIMD one after the other
+// (a wave-instruction takes the SIMD 4 cycles): about 26 per softmax numerator, 8 in fp64 per pooled term, and the
+// reductions, which every wave makes.  A group is 8 waves, two to a SIMD, which fill each other's gaps (4 waves with twice
+// the candidates each: 1 us more of a 10 us layer-step), and waves without a candidate end at once.  A long list is shared
+// (selection_slices); each exchange costs a trip of about 1 us.
+// TAGGED: the weights come from scoring blocks of this launch; else from a launch that has ended.
 // ---------------------------------------------------------------------------------
-template <typename Emit>
-__device__ __forceinline__ void radix_topk(const uint32_t* key, int n, int kk, uint32_t (*hist)[256], uint32_t* s_scan,
-                                           Emit emit) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // radix select: the kk-th largest key, one byte at a time from the top.  Every wave scans
-  // the histogram itself (lane l owns bins 255-4l .. 252-4l), so a pass costs one barrier.
-  // It ends early once every key of the chosen bin is wanted: then "all keys from that bin
-  // upwards" is the answer and the lower bytes need not be resolved (every wave sees the same
-  // histogram, so the whole block takes the exit together).
-  uint32_t prefix = 0, remaining = (uint32_t)kk;
-  uint32_t T = 0, take_eq = 0;                       // take keys > T, and the first take_eq keys == T
-  bool resolved = false;
-#pragma unroll
-  for (int pass = 3; pass >= 0; --pass) {
-    if (resolved) continue;
-    const int shift = pass * 8;
-    if (pass != 3) {
-      for (int j = tid; j < n; j += STEP_THREADS) {
-        const uint32_t kj = key[j];
-        if ((kj >> (shift + 8)) == prefix) atomicAdd(&hist[pass][(kj >> shift) & 255u], 1u);
-      }
-      __syncthreads();
-    }
-    uint32_t c[4], tot = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { c[i] = hist[pass][255 - 4 * lane - i]; tot += c[i]; }
-    const uint32_t incl = wave_scan_u32(tot);
-    uint32_t above = incl - tot;                     // keys in bins above this lane's
-    const bool mine = above < remaining && remaining <= incl;   // exactly one lane
-    uint32_t need = remaining - above;
-    int found = 0;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      if (found == i && c[i] < need) { need -= c[i]; found = i + 1; }
-    }
-    const unsigned long long pick = __ballot(mine);
-    const int src = __builtin_ctzll(pick);
-    const uint32_t cf = found == 0 ? c[0] : found == 1 ? c[1] : found == 2 ? c[2] : c[3];
-    remaining = (uint32_t)__builtin_amdgcn_readlane((int)need, src);          // how many to take inside the bin
-    const uint32_t in_bin = (uint32_t)__builtin_amdgcn_readlane((int)cf, src); // how many it holds
-    const uint32_t bin = (uint32_t)__builtin_amdgcn_readlane(255 - 4 * lane - found, src);
-    prefix = (prefix << 8) | bin;
-    if (pass == 0) {
-      T = prefix;                                    // the kk-th largest key itself;
-      take_eq = remaining;                           // of the keys equal to it, the lowest ids
-      resolved = true;
-    } else if (remaining == in_bin && (prefix << shift) != 0) {
-      T = (prefix << shift) - 1;                     // everything from the bin's lowest key upwards
-      take_eq = 0;
-      resolved = true;
-    }
-  }
-
-  // ordered compaction: thread t owns the contiguous ids [t*per, (t+1)*per)
-  const int per = (n + STEP_THREADS - 1) / STEP_THREADS;
-  const int j0 = tid * per, j1 = min(n, j0 + per);
-  uint32_t cnt = 0;                                  // low 16 bits: keys > T, high 16 bits: keys == T
-  for (int j = j0; j < j1; ++j) {
-    const uint32_t kj = key[j];
-    cnt += (kj > T ? 1u : 0u) + (kj == T ? 0x10000u : 0u);
-  }
-  const uint32_t incl = wave_scan_u32(cnt);
-  if (lane == 63) s_scan[wave] = incl;
-  __syncthreads();
-  uint32_t base = 0;
-  for (int w = 0; w < wave; ++w) base += s_scan[w];
-  const uint32_t excl = base + incl - cnt;
-  uint32_t gt_before = excl & 0xffffu, eq_before = excl >> 16;
-  for (int j = j0; j < j1; ++j) {
-    const uint32_t kj = key[j];
-    if (kj > T || (kj == T && eq_before < take_eq)) {
-      const uint32_t pos = gt_before + min(eq_before, take_eq);
-      emit((int)pos, j);
-    }
-    gt_before += (kj > T);
-    eq_before += (kj == T);
-  }
-}
-
-// Most candidates of a KV head the selection keeps in registers (G values each).  The layer kernel
-// has the registers for 4 per thread anyway (its attention part needs more); the step kernel alone
-// would lose occupancy of its scoring blocks above 2 per thread when G > 4.
-__host__ __device__ constexpr int regs_candidates(int G, bool roomy) { return ((roomy || G <= 4) ? 4 : 2) * STEP_THREADS; }
-
 template <int U> struct UnrollBy { static constexpr int value = U; };
+constexpr int SEL_WAVES = 8, SEL_THREADS = SEL_WAVES * 64;
+constexpr int SEL_REGS = 2, SEL_REGS_ALONE = 8;          // most candidates per thread, in the launches where scoring blocks
+                                                         // share the unit and in the one that only selects
+constexpr int TOPK_BINS = 512;
 
-// phase marks of the selection, kept in registers until its end (investigation builds only)
-#ifdef FKV_SEL_STAMPS
-#define FKV_SEL_MARK(i) sel_t##i = wall_clock64()
-#else
-#define FKV_SEL_MARK(i)
-#endif
+// 32-bit words of dynamic LDS that the keys of n candidates take (whole quads)
+__host__ __device__ constexpr int select_key_words(int n) { return n > 0 ? (n + 3) & ~3 : 4; }
 
-// a page weight: written earlier in this very launch by another block (device-scope read), or by a
-// launch that has ended (plain read)
-__device__ __forceinline__ float ld_weight(const float* p, bool same_launch) {
-  return same_launch ? ld_dev(p) : *p;
+struct alignas(16) SelectLds {
+  uint32_t hist[TOPK_BINS];
+  uint32_t list[64];
+  unsigned long long z[SEL_WAVES][MAX_G];
+  float mx[SEL_WAVES][MAX_G];
+  uint32_t scan[SEL_WAVES];
+  uint32_t n_list;
+  int lost;
+};
+
+// The first histogram of the top-k decides nearly everything: for softmax scores its bins are a sixteenth of an octave
+// wide below 1.0 (down to 2^-32), so the bin of the k-th score holds a handful of keys -- and few keys share a
+// counter, where bins by the top byte put a whole selection on two or three of them.  Other scores: by the top 9 bits.
+constexpr uint32_t kKeyOfOne = 0xBF800000u;               // score_key(1.0f)
+__device__ __forceinline__ uint32_t topk_bin(uint32_t key, bool soft) {     // ascending bins: descending keys
+  return soft ? min((uint32_t)TOPK_BINS - 1, (kKeyOfOne - min(key, kKeyOfOne)) >> 19) : (uint32_t)TOPK_BINS - 1 - (key >> 23);
+}
+// all keys of the bins up to `bin` are above this value, no other key is; bin < TOPK_BINS - 1
+__device__ __forceinline__ uint32_t topk_floor(uint32_t bin, bool soft) {
+  return soft ? kKeyOfOne - ((bin + 1) << 19) : (((uint32_t)TOPK_BINS - 1 - bin) << 23) - 1u;
 }
 
-template <int G, bool STAGED, bool ROOMY>
-__device__ __forceinline__ void select_block(const StepArgs& a, int head, uint32_t* key) {
-  __shared__ float s_redf[STEP_WAVES][G];
-  __shared__ unsigned long long s_redz[STEP_WAVES][G];
-  __shared__ uint32_t hist[4][256];
-  __shared__ uint32_t s_scan[STEP_WAVES];
+// the bin of `hist` (ascending) that holds the `want`-th entry: bin, entries before it, entries in it.  Every wave
+// scans by itself (lane l owns bins 8l .. 8l+7).
+__device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t want, uint32_t& bin, uint32_t& before, uint32_t& in_bin) {
+  const int lane = threadIdx.x & 63;
+  const uint4 c0 = *reinterpret_cast<const uint4*>(hist + 8 * lane), c1 = *reinterpret_cast<const uint4*>(hist + 8 * lane + 4);
+  const uint32_t c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+  const uint32_t tot = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+  const uint32_t incl = wave_scan_u32(tot);
+  uint32_t at = incl - tot, f = 0, cnt = c[0];
+  const int src = __builtin_ctzll(__ballot(at < want && want <= incl));       // exactly one lane
+#pragma unroll
+  for (int i = 1; i < 8; ++i)
+    if (f == i - 1 && at + cnt < want) { at += cnt; cnt = c[i]; f = i; }
+  bin = (uint32_t)__builtin_amdgcn_readlane(8 * lane + (int)f, src);
+  before = (uint32_t)__builtin_amdgcn_readlane((int)at, src);
+  in_bin = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
+}
 
-  const int b = head / a.n_kv, m = head % a.n_kv, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+// Top-kk of n keys held in LDS, ties to the lower index, by nw waves: emit(pos, j) is called for the
+// chosen j in ascending order of j with pos = 0 .. kk-1 (whichever thread owns j calls it).
+// Before the call (and a barrier): sm.hist holds the counts of the keys' bins.  1 <= kk <= n.
+// The keys of the one bin that is only partly wanted are collected and ranked against each other; only if there are
+// more than 64 of them (ties, or scores that are not softmax values) the bytes are resolved one by one.
+template <typename Emit>
+__device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, bool soft, int nw, SelectLds& sm, Emit emit) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = nw * 64;
+  uint32_t T = 0, take_eq = 0;                       // take keys > T, and the first take_eq keys == T
+  if (kk < n) {
+    uint32_t bin, before, in_bin;
+    find_bin(sm.hist, (uint32_t)kk, bin, before, in_bin);
+    const uint32_t need = (uint32_t)kk - before;     // keys of the bin that are wanted
+    if (need == in_bin && bin < TOPK_BINS - 1) {
+      T = topk_floor(bin, soft);
+    } else if (in_bin <= 64) {
+      for (int j = tid; j < n; j += nt) {
+        const uint32_t kj = key[j];
+        if (topk_bin(kj, soft) == bin) sm.list[atomicAdd(&sm.n_list, 1u)] = kj;
+      }
+      lds_barrier();
+      const uint32_t mine = lane < (int)in_bin ? sm.list[lane] : 0u;
+      uint32_t above = 0, same = 0;
+      for (uint32_t i = 0; i < in_bin; ++i) {
+        const uint32_t ki = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)i);
+        above += ki > mine ? 1u : 0u;
+        same += ki == mine ? 1u : 0u;
+      }
+      const int src = __builtin_ctzll(__ballot(lane < (int)in_bin && above < need && need <= above + same));
+      T = (uint32_t)__builtin_amdgcn_readlane((int)mine, src);
+      take_eq = need - (uint32_t)__builtin_amdgcn_readlane((int)above, src);
+    } else {
+      // one byte at a time from the top; ends early once every key of the chosen bin is wanted (every wave sees the same
+      // histogram, so the whole group leaves together)
+      uint32_t prefix = 0, remaining = (uint32_t)kk;
+      for (int shift = 24; shift >= 0; shift -= 8) {
+        lds_barrier();                               // the last histogram has been read
+        for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
+        lds_barrier();
+        for (int j = tid; j < n; j += nt) {
+          const uint32_t kj = key[j];
+          if (shift == 24 || (kj >> ((shift + 8) & 31)) == prefix) atomicAdd(&sm.hist[255u - ((kj >> shift) & 255u)], 1u);
+        }
+        lds_barrier();
+        find_bin(sm.hist, remaining, bin, before, in_bin);
+        remaining -= before;
+        prefix = (prefix << 8) | (255u - bin);
+        if (shift == 0) {
+          T = prefix;                                // the kk-th largest key itself;
+          take_eq = remaining;                       // of the keys equal to it, the lowest ids
+        } else if (remaining == in_bin && (prefix << shift) != 0) {
+          T = (prefix << shift) - 1;                 // everything from the bin's lowest key upwards
+          break;
+        }
+      }
+    }
+  } else {
+    take_eq = (uint32_t)n;
+  }
+
+  // ordered compaction: thread t owns the contiguous ids [4t, 4t + 4), and again nt * 4 further on
+  uint32_t base = 0;                                 // chosen before this round: low 16 bits keys > T, high 16 bits keys == T
+  for (int r0 = 0; r0 < n; r0 += nt * 4) {
+    const int j = r0 + tid * 4;
+    const uint4 k4 = *reinterpret_cast<const uint4*>(key + min(j, (n - 1) & ~3));      // (select_key_words)
+    const uint32_t kj[4] = {k4.x, k4.y, k4.z, k4.w};
+    uint32_t cnt = 0, is[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      is[i] = j + i < n ? (kj[i] > T ? 1u : kj[i] == T ? 0x10000u : 0u) : 0u;
+      cnt += is[i];
+    }
+    const uint32_t incl = wave_scan_u32(cnt);
+    if (r0) lds_barrier();                           // the last round's totals have been read
+    if (lane == 63) sm.scan[wave] = incl;
+    lds_barrier();
+    uint32_t at = base + incl - cnt;
+#pragma unroll
+    for (int w = 0; w < SEL_WAVES; ++w) {
+      const uint32_t v = w < nw ? sm.scan[w] : 0u;
+      if (w < wave) at += v;
+      base += v;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t eq_before = at >> 16;
+      if (is[i] == 1u || (is[i] != 0u && eq_before < take_eq)) emit((int)((at & 0xffffu) + min(eq_before, take_eq)), j + i);
+      at += is[i];
+    }
+  }
+}
+
+template <int G, bool TAGGED, int REGS = SEL_REGS>
+__device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, uint32_t* key) {
+  __shared__ SelectLds sm;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff, k = a.k;
+  const int S = a.slices;
+  const bool last = s == S - 1;
+  const uint32_t tag = launch_tag(a, head);
+  const int j0 = s * a.slice, j1 = min(n, j0 + a.slice);
+  // The waves that take part: as many as there are candidates for; all of them where a plan has to be made or keys of
+  // other slices have to be gathered.  The others of the block end here (a barrier counts the waves that are left).
+  const int nw = (last && S > 1) || a.plan_new_slots || kk == 0 ? SEL_WAVES : min(SEL_WAVES, (j1 - j0 + 63) / 64);
+  if (wave >= nw) return;
+  const int nt = nw * 64;
   int32_t* out = a.ids + (size_t)head * k;
   int32_t* outu = a.ids_user ? a.ids_user + (size_t)head * k : nullptr;
-  // No global store is issued before the last barrier of this function: a barrier waits for
-  // the acknowledgement of every store the wave has in flight, a full trip to memory.
-  // a picked id goes out three ways: the layer's id list, the caller's copy, and (one-launch layer-step) tagged
-  // with the step's epoch in one 64-bit word, so that a waiting attention wave sees "this step's id" in one read
-  unsigned long long* tag = a.tagged ? a.tagged + (size_t)head * k : nullptr;
-  const unsigned long long tag_hi = (unsigned long long)(uint32_t)a.epoch << 32;
+  // a picked id goes out three ways: the layer's id list, the caller's copy, and (one-launch layer-step) as a tagged
+  // word, so that a waiting attention wave sees "this launch's id" in one read
+  unsigned long long* tagw = a.tagged ? a.tagged + (size_t)head * k : nullptr;
   // With a recall plan to make, the ids are only collected in the plan's LDS here and everything goes out after it.
   int32_t* plan_sm = reinterpret_cast<int32_t*>(key) + a.plan_lds_off;
   int32_t* plan_nid = a.plan_new_slots ? plan_sm + 4 * k : nullptr;
   auto put_id = [&](int pos, int id) {
     if (plan_nid) { plan_nid[pos] = id; return; }
-    __hip_atomic_store(out + pos, id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tag) __hip_atomic_store(tag + pos, tag_hi | (uint32_t)id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tagw) st_tag(tagw + pos, (uint32_t)id, tag);
+    out[pos] = id;
     if (outu) outu[pos] = id;
   };
   auto plan_and_publish = [&]() {
     if (!plan_nid) return;
-    __syncthreads();                                   // the ids are all in LDS
-    plan_head<STEP_THREADS>(out, a.plan_act_ids + (size_t)head * k, a.plan_act_slots + (size_t)head * k,
-                            a.plan_new_slots + (size_t)head * k, a.plan_miss + (size_t)head * (1 + 3 * k), k, a.g.n_full,
-                            plan_sm, true);
+    lds_barrier();                                     // the ids are all in LDS
+    plan_head<SEL_THREADS>(out, a.plan_act_ids + (size_t)head * k, a.plan_act_slots + (size_t)head * k,
+                           a.plan_new_slots + (size_t)head * k, a.plan_miss + (size_t)head * (1 + 3 * k), k, a.g.n_full,
+                           plan_sm, true);
     const int32_t* nslot = plan_sm + 5 * k;
-    for (int i = tid; i < k; i += STEP_THREADS) {
-      const int id = plan_nid[i], s = nslot[i];
-      __hip_atomic_store(out + i, id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (tag) __hip_atomic_store(tag + i, tag_hi | tagged_pick(id, s & (TAGGED_MAX_SLOTS - 1), (s & PLAN_MISS_BIT) != 0),
-                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = tid; i < k; i += SEL_THREADS) {
+      const int id = plan_nid[i], sl = nslot[i];
+      if (tagw) st_tag(tagw + i, tagged_pick(id, sl & (TAGGED_MAX_SLOTS - 1), (sl & PLAN_MISS_BIT) != 0), tag);
+      out[i] = id;
       if (outu) outu[i] = id;
     }
   };
   if (kk == 0) {
-    for (int i = tid; i < k; i += STEP_THREADS) put_id(i, -1);
+    for (int i = tid; i < k; i += nt) put_id(i, -1);
     plan_and_publish();
     return;
   }
-#ifdef FKV_SEL_STAMPS
-  long long sel_t0 = 0, sel_t1 = 0, sel_t2 = 0, sel_t3 = 0, sel_t4 = 0;
-#endif
-  FKV_SEL_MARK(0);
-  const float* Pm = a.P + (size_t)(b * a.n_q + m * G) * a.max_pages + lo;
-  uint32_t* pw = key + n;                              // [G][n]: weights, later their fixed-point softmax
-  constexpr bool staged = STAGED;                      // else: re-read the weights from memory in each pass
-  const bool same_launch = a.select_only == 0;         // the weights come from scoring blocks of this launch
   const int mode = a.sel_pool;                         // FKV_POOL_*
   const bool soft = mode <= 1;                         // the variants that pool softmax values
-  const int ng = mode >= 4 ? 1 : G;                    // rows of P in use (pooled query: the group's first)
-#pragma unroll
-  for (int p = 0; p < 4; ++p)
-    if (tid < 256) hist[p][tid] = 0;
-
-  // A few candidates per thread stay in registers from the load to the key: no staging in LDS.
-  const bool in_regs = n <= regs_candidates(G, ROOMY);
-  auto front_in_regs = [&](auto uc) {
-    constexpr int U = decltype(uc)::value;
-    uint32_t e[U][G];                                  // bits of the weights, then softmax numerators
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = min(tid + u * STEP_THREADS, n - 1);
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg)
-        e[u][gg] = gg < ng ? __float_as_uint(ld_weight(Pm + (size_t)gg * a.max_pages + j, same_launch)) : 0u;
-    }
-    double zd[G];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) zd[gg] = 1.0;
-    if (soft) {
-      float mx[G];
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) mx[gg] = -__builtin_inff();
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (tid + u * STEP_THREADS < n) {
-#pragma unroll
-          for (int gg = 0; gg < G; ++gg) mx[gg] = fmaxf(mx[gg], __uint_as_float(e[u][gg]));
-        }
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) {
-        const float w = wave_max_f32(mx[gg]);
-        if (lane == 0) s_redf[wave][gg] = w;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) {
-        float v = s_redf[0][gg];
-#pragma unroll
-        for (int w = 1; w < STEP_WAVES; ++w) v = fmaxf(v, s_redf[w][gg]);
-        mx[gg] = v;
-      }
-      FKV_SEL_MARK(1);
-      unsigned long long z[G];
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) z[gg] = 0;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int gg = 0; gg < G; ++gg) {
-          e[u][gg] = softmax_fixed(__uint_as_float(e[u][gg]), mx[gg]);
-          if (tid + u * STEP_THREADS < n) z[gg] += e[u][gg];
-        }
-      }
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) {
-        const unsigned long long w = wave_sum_u48(z[gg]);
-        if (lane == 0) s_redz[wave][gg] = w;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) {
-        unsigned long long v = 0;
-#pragma unroll
-        for (int w = 0; w < STEP_WAVES; ++w) v += s_redz[w][gg];
-        zd[gg] = (double)v;
-      }
-    } else {
-      FKV_SEL_MARK(1);
-    }
-    double zr[G];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) zr[gg] = reciprocal_near(zd[gg]);
-    FKV_SEL_MARK(2);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = tid + u * STEP_THREADS;
-      const uint32_t kj = score_key(pooled_score<G>(e[u], zd, zr, mode));
-      if (j < n) {
-        key[j] = kj;
-        atomicAdd(&hist[3][kj >> 24], 1u);
-      }
+  const int ng = mode >= 4 ? 1 : G;                    // weights in use per page (pooled query: the group's first)
+  if (last) {
+    for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
+    if (tid == 0) { sm.n_list = 0; sm.lost = 0; }
+  }
+  bool lost = false;                                   // a wait of this wave ran out
+  // load_and_check() again until every lane's words carry the tag
+  auto poll = [&](auto load_and_check) {
+    int it = 0;
+    while (__ballot(!load_and_check()) != 0) {
+      if (++it > MAX_POLLS) { lost = true; break; }
+      __builtin_amdgcn_s_sleep(1);
     }
   };
-  if (in_regs) {
-    if (!soft) __syncthreads();                        // the histograms are clear (else: barriers below)
-    if (n <= STEP_THREADS) front_in_regs(UnrollBy<1>{});
-    else if (n <= 2 * STEP_THREADS) front_in_regs(UnrollBy<2>{});
-    else if constexpr (regs_candidates(G, ROOMY) > 2 * STEP_THREADS) front_in_regs(UnrollBy<4>{});
-  } else {
-  // stage the weights of this head's G query heads in LDS (one device-scope read each, 8 x G
-  // of them in flight per thread) and take the per-head maximum over the candidates
-  float mx[G];
+
+  // ---- this group's weights: thread t has candidates j0 + t + u * nt ----
+  const int U = (j1 - j0 + nt - 1) / nt;               // 1 .. REGS
+  uint32_t e[REGS][G];                             // bits of the weights, then softmax numerators
+  auto ours = [&](int u) { return j0 + tid + u * nt < j1; };
+  // (All of a poll's loads are issued before the first is looked at, and none sits behind a branch of its own: one trip.)
+  auto weights = [&](auto uc) {
+    constexpr int UC = decltype(uc)::value;
+    const size_t base = (size_t)head * G * a.max_pages + lo;
+    size_t at[UC];
 #pragma unroll
-  for (int gg = 0; gg < G; ++gg) mx[gg] = -__builtin_inff();
-  // Each loop over the candidates handles U of them per thread and trip, all loads first, so
-  // that U x G independent chains are in flight; U is matched to n, because a trip works on
-  // U x STEP_THREADS candidates whether they exist or not.
-  auto stage_and_max = [&](auto uc) {
-    constexpr int U = decltype(uc)::value;
-    for (int j0 = tid; j0 < n; j0 += U * STEP_THREADS) {
-      float v[U][G];
+    for (int u = 0; u < UC; ++u) at[u] = base + min(j0 + tid + u * nt, j1 - 1);
+    size_t row[G];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = min(j0 + u * STEP_THREADS, n - 1);
+    for (int gg = 0; gg < G; ++gg) row[gg] = (size_t)min(gg, ng - 1) * a.max_pages;
+    poll([&]() {
+      bool ok = true;
+      if (TAGGED) {
+        unsigned long long w[UC][G];
 #pragma unroll
-        for (int gg = 0; gg < G; ++gg) v[u][gg] = gg < ng ? ld_weight(Pm + (size_t)gg * a.max_pages + j, same_launch) : 0.0f;
-      }
+        for (int u = 0; u < UC; ++u)
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = j0 + u * STEP_THREADS;
-        if (j < n) {
+          for (int gg = 0; gg < G; ++gg) w[u][gg] = ld_tag(a.P + at[u] + row[gg]);
+#pragma unroll
+        for (int u = 0; u < UC; ++u)
 #pragma unroll
           for (int gg = 0; gg < G; ++gg) {
-            if (staged) pw[gg * n + j] = __float_as_uint(v[u][gg]);
-            mx[gg] = fmaxf(mx[gg], v[u][gg]);
+            e[u][gg] = (uint32_t)w[u][gg];
+            ok = ok & ((uint32_t)(w[u][gg] >> 32) == tag);
           }
-        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < UC; ++u)
+#pragma unroll
+          for (int gg = 0; gg < G; ++gg) e[u][gg] = __float_as_uint(reinterpret_cast<const float*>(a.P)[at[u] + row[gg]]);
       }
-    }
+      return ok;
+    });
   };
-  if (soft || staged) {
-    if (n <= 2 * STEP_THREADS) stage_and_max(UnrollBy<2>{});
-    else if (n <= 4 * STEP_THREADS) stage_and_max(UnrollBy<4>{});
-    else stage_and_max(UnrollBy<8>{});
-  }
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) {
-    const float w = wave_max_f32(mx[gg]);
-    if (lane == 0) s_redf[wave][gg] = w;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) {
-    float v = s_redf[0][gg];
-#pragma unroll
-    for (int w = 1; w < STEP_WAVES; ++w) v = fmaxf(v, s_redf[w][gg]);
-    mx[gg] = v;
-  }
-  FKV_SEL_MARK(1);
-  // fixed-point softmax numerators in place, integer denominators (a sum of integers: no order to fix)
-  unsigned long long z[G];
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) z[gg] = 0;
-  auto numerators = [&](auto uc) {
-    constexpr int U = decltype(uc)::value;
-    for (int j0 = tid; j0 < n; j0 += U * STEP_THREADS) {
-      float v[U][G];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = min(j0 + u * STEP_THREADS, n - 1);
-#pragma unroll
-        for (int gg = 0; gg < G; ++gg)
-          v[u][gg] = staged ? __uint_as_float(pw[gg * n + j]) : ld_weight(Pm + (size_t)gg * a.max_pages + j, same_launch);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = j0 + u * STEP_THREADS;
-#pragma unroll
-        for (int gg = 0; gg < G; ++gg) {
-          const uint32_t e = softmax_fixed(v[u][gg], mx[gg]);
-          if (j < n) {
-            if (staged) pw[gg * n + j] = e;
-            z[gg] += e;
-          }
-        }
-      }
-    }
-  };
-  if (soft) {
-    if (n <= 2 * STEP_THREADS) numerators(UnrollBy<2>{});
-    else numerators(UnrollBy<4>{});
-  }
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) {
-    const unsigned long long w = wave_sum_u48(z[gg]);   // z < 2^31 * ceil(n / threads) < 2^48
-    if (lane == 0) s_redz[wave][gg] = w;
-  }
-  __syncthreads();
-  double zd[G];
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) {
-    unsigned long long v = 0;
-#pragma unroll
-    for (int w = 0; w < STEP_WAVES; ++w) v += s_redz[w][gg];
-    zd[gg] = (double)v;
-  }
-  double zr[G];
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) zr[gg] = reciprocal_near(zd[gg]);
-  FKV_SEL_MARK(2);
-  // pooled score of each candidate (each thread reads back only what it wrote); the top
-  // byte of its key goes straight into the first histogram
-  auto pool_and_key = [&](auto uc) {
-    constexpr int U = decltype(uc)::value;
-  for (int j0 = tid; j0 < n; j0 += U * STEP_THREADS) {
-    uint32_t e[U][G];                                // softmax numerators, or the bits of the weights
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = min(j0 + u * STEP_THREADS, n - 1);
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) {
-        if (staged) e[u][gg] = pw[gg * n + j];
-        else if (gg < ng) {
-          const float w = ld_weight(Pm + (size_t)gg * a.max_pages + j, same_launch);
-          e[u][gg] = soft ? softmax_fixed(w, mx[gg]) : __float_as_uint(w);
-        } else e[u][gg] = 0;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = j0 + u * STEP_THREADS;
-      const float sc = pooled_score<G>(e[u], zd, zr, mode);
-      const uint32_t kj = score_key(sc);
-      if (j < n) {
-        key[j] = kj;
-        atomicAdd(&hist[3][kj >> 24], 1u);
-      }
-    }
-  }
-  };
-  if (n <= 2 * STEP_THREADS) pool_and_key(UnrollBy<2>{});
-  else pool_and_key(UnrollBy<4>{});
-  }
-  __syncthreads();
+  if (U == 1) weights(UnrollBy<1>{});
+  else if (REGS == 2 || U == 2) weights(UnrollBy<2>{});
+  else weights(UnrollBy<REGS>{});
+  FKV_STAMP(a, head, 2);
 
-  FKV_SEL_MARK(3);
-  radix_topk(key, n, kk, hist, s_scan, [&](int pos, int j) { put_id(pos, lo + j); });
-  FKV_SEL_MARK(4);
-  for (int i = kk + tid; i < k; i += STEP_THREADS) put_id(i, -1);   // padding
-  plan_and_publish();
-#ifdef FKV_SEL_STAMPS
-  if (a.tstamp && head == 0 && tid == 0) {
-    a.tstamp[40] = sel_t0; a.tstamp[41] = sel_t1; a.tstamp[42] = sel_t2; a.tstamp[43] = sel_t3;
-    a.tstamp[44] = sel_t4; a.tstamp[45] = wall_clock64();
+  // ---- fixed-point softmax: the head's maxima, numerators, integer denominators ----
+  double zd[G], zr[G];
+#pragma unroll
+  for (int gg = 0; gg < G; ++gg) zd[gg] = zr[gg] = 1.0;
+  if (soft) {
+    unsigned long long* const mine = a.exch + ((size_t)head * MAX_SLICES + s) * 3 * MAX_G;
+    const unsigned long long* const all = a.exch + (size_t)head * MAX_SLICES * 3 * MAX_G;
+    const int gl = min(lane & 7, G - 1);               // lane 8r + g works on head g
+    float mx[G];
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      float v = __uint_as_float(e[0][gg]);             // (a thread without a candidate repeats the slice's last one)
+#pragma unroll
+      for (int u = 1; u < REGS; ++u)
+        if (u < U) v = fmaxf(v, __uint_as_float(e[u][gg]));
+      v = wave_max_f32(v);
+      if (lane == 0) sm.mx[wave][gg] = v;
+    }
+    lds_barrier();
+    float v = -__builtin_inff();
+#pragma unroll
+    for (int w = 0; w < SEL_WAVES; ++w) v = fmaxf(v, sm.mx[min(w, nw - 1)][gl]);
+    if (S > 1) {                                       // ... and over the slices: r is a slice
+      if (wave == 0 && lane < G) st_tag(mine + lane, __float_as_uint(v), tag);
+      const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
+      unsigned long long w0 = 0, w1 = 0;
+      poll([&]() {
+        w0 = ld_tag(all + (size_t)r0 * 3 * MAX_G + gl);
+        w1 = ld_tag(all + (size_t)r1 * 3 * MAX_G + gl);
+        return ((uint32_t)(w0 >> 32) == tag) & ((uint32_t)(w1 >> 32) == tag);
+      });
+      v = fmaxf(__uint_as_float((uint32_t)w0), __uint_as_float((uint32_t)w1));
+      v = fmaxf(v, __shfl_xor(v, 8, 64));
+      v = fmaxf(v, __shfl_xor(v, 16, 64));
+      v = fmaxf(v, __shfl_xor(v, 32, 64));
+    }
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), gg));
+    FKV_STAMP(a, head, 3);
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      unsigned long long z = 0;
+#pragma unroll
+      for (int u = 0; u < REGS; ++u) {
+        if (u < U) {
+          e[u][gg] = softmax_fixed(__uint_as_float(e[u][gg]), mx[gg]);
+          if (ours(u)) z += e[u][gg];
+        }
+      }
+      z = wave_sum_u48(z);
+      if (lane == 0) sm.z[wave][gg] = z;
+    }
+    lds_barrier();
+    unsigned long long z = 0;
+#pragma unroll
+    for (int w = 0; w < SEL_WAVES; ++w) z += w < nw ? sm.z[w][gl] : 0ull;
+    if (S > 1) {
+      if (wave == 0 && lane < G) {
+        st_tag(mine + MAX_G + lane, (uint32_t)z, tag);
+        st_tag(mine + 2 * MAX_G + lane, (uint32_t)(z >> 32), tag);
+      }
+      const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
+      unsigned long long w[4];
+      poll([&]() {
+        const unsigned long long* p0 = all + (size_t)r0 * 3 * MAX_G + MAX_G + gl;
+        const unsigned long long* p1 = all + (size_t)r1 * 3 * MAX_G + MAX_G + gl;
+        w[0] = ld_tag(p0); w[1] = ld_tag(p0 + MAX_G); w[2] = ld_tag(p1); w[3] = ld_tag(p1 + MAX_G);
+        return ((uint32_t)(w[0] >> 32) == tag) & ((uint32_t)(w[1] >> 32) == tag) & ((uint32_t)(w[2] >> 32) == tag) & ((uint32_t)(w[3] >> 32) == tag);
+      });
+      z = 0;
+      if ((lane >> 3) < S) z += (w[0] & 0xffffffffull) | (w[1] << 32);
+      if ((lane >> 3) + 8 < S) z += (w[2] & 0xffffffffull) | (w[3] << 32);
+#pragma unroll
+      for (int d = 8; d < 64; d <<= 1) {
+        const uint32_t zl = (uint32_t)__shfl_xor((int)(uint32_t)z, d, 64), zh = (uint32_t)__shfl_xor((int)(uint32_t)(z >> 32), d, 64);
+        z += ((unsigned long long)zh << 32) | zl;
+      }
+    }
+    // one reciprocal per lane, handed to every lane as a scalar
+    const double zv = (double)z, yv = reciprocal_near(zv);
+    const unsigned long long zb = __builtin_bit_cast(unsigned long long, zv), yb = __builtin_bit_cast(unsigned long long, yv);
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      zd[gg] = __builtin_bit_cast(double, ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(zb >> 32), gg) << 32) |
+                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)zb, gg));
+      zr[gg] = __builtin_bit_cast(double, ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(yb >> 32), gg) << 32) |
+                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)yb, gg));
+    }
+  } else {
+    lds_barrier();                                     // the histogram is clear
   }
-#endif
+  FKV_STAMP(a, head, 4);
+
+  // ---- pooled scores -> keys ----
+  uint32_t kreg[REGS];
+#pragma unroll
+  for (int u = 0; u < REGS; ++u) {
+    const int j = j0 + tid + u * nt;
+    if (u < U) {
+      kreg[u] = score_key(pooled_score<G>(e[u], zd, zr, mode));
+      if (ours(u)) {
+        if (last) {
+          key[j] = kreg[u];
+          atomicAdd(&sm.hist[topk_bin(kreg[u], soft)], 1u);
+        } else {
+          st_tag(a.keyx + (size_t)head * a.max_pages + j, kreg[u], tag);
+        }
+      }
+    }
+  }
+  auto keep_scores = [&]() {                           // the pooled scores, kept for inspection
+#pragma unroll
+    for (int u = 0; u < REGS; ++u)
+      if (u < U && ours(u)) a.score[(size_t)head * a.max_pages + lo + j0 + tid + u * nt] = key_score(kreg[u]);
+  };
+  if (!last) {
+    keep_scores();
+    if (lost && lane == 0) *a.status = 1;
+    return;
+  }
+  // the other slices' keys (lower block indices)
+  for (int jj = tid; jj < j0; jj += 4 * nt) {
+    unsigned long long w[4];
+    bool ok = false;
+    for (int it = 0; !ok && it <= MAX_POLLS; ++it) {
+      ok = true;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[u] = ld_tag(a.keyx + (size_t)head * a.max_pages + min(jj + u * nt, j0 - 1));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) ok = ok & ((uint32_t)(w[u] >> 32) == tag);
+    }
+    lost = lost || !ok;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (jj + u * nt < j0) {
+        key[jj + u * nt] = (uint32_t)w[u];
+        atomicAdd(&sm.hist[topk_bin((uint32_t)w[u], soft)], 1u);
+      }
+    }
+  }
+  // a group that gave up a wait has no selection to offer: nothing is published under the tag (waiting attention waves
+  // give up too) and the list names no page
+  if (lost) sm.lost = 1;
+  lds_barrier();
+  if (a.launch_no && tid == 0) a.launch_no[head] += 1;   // (everyone who needs the number has read it: their values are here)
+  if (sm.lost) {
+    if (tid == 0) {
+      *a.status = 1;
+      if (a.plan_new_slots) a.plan_miss[(size_t)head * (1 + 3 * k)] = 0;
+    }
+    for (int i = tid; i < k; i += nt) {
+      out[i] = SELECTION_LOST;
+      if (outu) outu[i] = -1;
+    }
+    return;
+  }
+  FKV_STAMP(a, head, 5);
+  block_topk(key, n, kk, soft, nw, sm, [&](int pos, int j) { put_id(pos, lo + j); });
+  for (int i = kk + tid; i < k; i += nt) put_id(i, -1);   // padding
+  plan_and_publish();
+  FKV_STAMP(a, head, 8);
+  keep_scores();
 }
 
-
 // ---------------------------------------------------------------------------------
-// role dispatch of one block: bid counts [append blocks][corr blocks][scoring blocks], each
-// set present only if its role bit is set; heads = batch * n_kv.
+// role dispatch of one block: row y of the grid counts [append][correction test][scoring ...][selection ...], each
+// present only if its role bit is set; x is the KV head, except that the selection's blocks are numbered through row by
+// row so that a head's are adjacent (they wait for each other: in block order, at most one head's are ever half there).
 // ---------------------------------------------------------------------------------
-template <int DT, int G, bool ROOMY>
-__device__ __forceinline__ void step_roles(const StepArgs& a, int bid, uint32_t* dyn_lds) {
-  const int heads = a.batch * a.n_kv;
-  int head;
-  if (a.select_only) {
-    head = bid;
-  } else {
-    if (a.roles & ROLE_APPEND) {
-      if (bid < heads) { append_role<DT>(a, bid); return; }
-      bid -= heads;
-    }
-    if (a.roles & ROLE_CORR) {
-      if (bid < heads) { corr_role<DT, G>(a, bid); return; }
-      bid -= heads;
-    }
-    head = bid / a.blocks_per_head;
-    const int chunk = bid % a.blocks_per_head;
-    if (chunk == 0) FKV_STAMP(a, head, 0);
-#ifdef FKV_SEL_STAMPS
-    if (chunk == 0 && a.tstamp && threadIdx.x == 0) a.tstamp[56 + (head & 7)] = wall_clock64();
-#endif
-    score_role<DT, G>(a, head, chunk);
-    if (chunk == 0) FKV_STAMP(a, head, 1);
-    if (!a.fuse_select) return;
-    if (a.blocks_per_head == 1) block_release();       // the head's only scoring block: its own weights, once they are out
-    else if (!last_block_done(a.counters + head, a.blocks_per_head)) return;
+template <int DT, int G>
+__device__ __forceinline__ void step_roles(const StepArgs& a, int head, int y, uint32_t* dyn_lds) {
+  if (a.roles & ROLE_APPEND) {
+    if (y == 0) { append_role<DT>(a, head); return; }
+    y -= 1;
   }
-  FKV_STAMP(a, head, 2);
-  if (a.staged) select_block<G, true, ROOMY>(a, head, dyn_lds);
-  else          select_block<G, false, ROOMY>(a, head, dyn_lds);
-  FKV_STAMP(a, head, 8);
-#ifdef FKV_SEL_STAMPS
-  if (a.tstamp && threadIdx.x == 0) a.tstamp[24 + (head & 7)] = wall_clock64();
-#endif
-  // the pooled scores, kept for inspection; after the ids, which nothing here should delay
-  if (a.g.k_eff > 0)
-    for (int j = threadIdx.x; j < a.g.n_cand; j += STEP_THREADS)
-      a.score[(size_t)head * a.max_pages + a.g.cand_lo + j] = key_score(dyn_lds[j]);
+  if (a.roles & ROLE_CORR) {
+    if (y == 0) { corr_role<DT, G>(a, head); return; }
+    y -= 1;
+  }
+  if (y < a.chunks) {
+    if (y == 0) FKV_STAMP(a, head, 0);
+    score_role<DT, G, true, STEP_WAVES>(a, head, y);
+    if (y == 0) FKV_STAMP(a, head, 1);
+    return;
+  }
+  const int i = (y - a.chunks) * a.heads + head;
+  select_role<G, true>(a, i >> a.slices_log2, i & (a.slices - 1), dyn_lds);
 }
 
 }  // namespace fkv
