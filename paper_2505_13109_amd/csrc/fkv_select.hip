@@ -26,7 +26,7 @@ __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
 // A head's chunks are adjacent in block order (blocks that run together read one stretch of memory: 28.2 us with the KV
 // cache between two scans of that size, 30.0 us with the heads next to each other): grid (chunks, heads), below rows of
 // the same width for the other two roles.
-constexpr int SCAN_WAVES = 4, SCAN_PASSES = 4;
+constexpr int SCAN_WAVES = 4;
 template <int DT, int G>
 __global__ __launch_bounds__(SCAN_WAVES * 64) void scan_kernel(StepArgs a) {
   touch_args<sizeof(StepArgs)>();
@@ -157,7 +157,7 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
   }
-  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCAN_PASSES, g.k_eff > 0 ? selection_slices(g.n_cand, heads, SEL_REGS_ALONE * SEL_THREADS) : 1, a, rows, lds);
+  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, g.k_eff > 0 ? selection_slices(g.n_cand, heads, SEL_REGS_ALONE * SEL_THREADS) : 1, a, rows, lds);
   if (!grant_lds(&select_kernel<G>, lds, granted_select)) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
   scan_kernel<DT, G><<<dim3(a.chunks, a.other_rows + heads), SCAN_WAVES * 64, 0, st>>>(a);

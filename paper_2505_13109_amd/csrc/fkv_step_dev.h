@@ -43,6 +43,8 @@ constexpr int SCORE_PASSES = FKV_SCORE_PASSES;         // most passes a scoring 
 constexpr int PAGES_PER_PASS = STEP_WAVES * 4;         // a wave scores 4 pages per pass
 constexpr int MAX_SLICES = 16;                         // most blocks that share one head's selection
 
+template <int U> struct UnrollBy { static constexpr int value = U; };
+
 struct StepArgs {
   int roles;                 // ROLE_* bits
   int heads, k, max_pages;
@@ -171,85 +173,117 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
   constexpr int PASS = WAVES * 4;                         // pages per pass
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane >> 4, c8 = lane & 15;
-  const int n = a.g.n_cand, j0 = chunk * PASS * a.passes + wave * 4 + grp;
+  const int passes = TAGGED ? a.passes : SCORE_PASSES;    // (the scan always makes as many as there are)
+  const int n = a.g.n_cand, j0 = chunk * PASS * passes + wave * 4 + grp;
   uint4 wmax[SCORE_PASSES], wmin[SCORE_PASSES];
   const uint16_t* sm = a.summ + summ_idx(0, head, 0, 0, a.max_pages, a.g.cand_lo) + c8 * 8;
   const size_t to_min = (size_t)a.max_pages * D;
 #pragma unroll
   for (int ps = 0; ps < SCORE_PASSES; ++ps) {
-    if (ps < a.passes) {
+    if (ps < passes) {
       const int j = min(j0 + ps * PASS, n - 1);
       wmax[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D);
       wmin[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D + to_min);
     }
   }
   const uint32_t tag = TAGGED ? launch_tag(a, head) : 0u;
-  float f[G][8];
+  uint4 wq[G];
 #pragma unroll
-  for (int gg = 0; gg < G; ++gg) {
-    const uint4 wq = *reinterpret_cast<const uint4*>(a.q + ((size_t)head * G + gg) * D + c8 * 8);
-    unpack8<DT>(wq, f[gg]);
-  }
+  for (int gg = 0; gg < G; ++gg) wq[gg] = *reinterpret_cast<const uint4*>(a.q + ((size_t)head * G + gg) * D + c8 * 8);
   // Variants that pool the QUERY over the group (App. B.2, MeanQ / MaxQ): one pooled query per KV
   // head takes the place of head 0 of the group, and only its weight is written.
   constexpr int NG = QMODE ? 1 : G;                       // weights this launch writes per page
+  float pooled[8];
   if (QMODE) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      float acc = f[0][c];
+    for (int gg = 0; gg < G; ++gg) {
+      float f[8];
+      unpack8<DT>(wq[gg], f);
 #pragma unroll
-      for (int gg = 1; gg < G; ++gg) acc = a.sel_pool == 4 ? acc + f[gg][c] : fmaxf(acc, f[gg][c]);
-      // fp32 quotient by way of fp64: correctly rounded (53 >= 2 * 24 + 2 bits)
-      if (a.sel_pool == 4) acc = (float)((double)acc / (double)G);
-      f[0][c] = acc;
+      for (int c = 0; c < 8; ++c) {
+        pooled[c] = gg == 0 ? f[c] : a.sel_pool == 4 ? pooled[c] + f[c] : fmaxf(pooled[c], f[c]);
+        asm volatile("" : "+v"(pooled[c]));               // (one head after the other: registers)
+      }
+    }
+    // fp32 quotient by way of fp64: correctly rounded (53 >= 2 * 24 + 2 bits)
+    if (a.sel_pool == 4) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        pooled[c] = (float)((double)pooled[c] / (double)G);
+        asm volatile("" : "+v"(pooled[c]));
+      }
     }
   }
   const float scale = 0x1.6a09e6p-4f;   // fl32(1/sqrt(128))
   __shared__ float s_w[NG][TAGGED ? PASS * SCORE_PASSES : 1];
-#pragma unroll
-  for (int ps = 0; ps < SCORE_PASSES; ++ps) {
-    if (ps >= a.passes) break;
-    float kx[8], kn[8];
-    unpack8<DT>(wmax[ps], kx);
-    unpack8<DT>(wmin[ps], kn);
-    float mine = 0.0f;                                    // the total of query head c8, for lanes c8 < NG
+  // The weights of N passes' pages.  A channel contributes q_c * (q_c >= 0 ? kmax_c : kmin_c): the choice is made on the
+  // packed 16-bit values, by the signs of a query's channel pair as a bit mask (one instruction for two channels, and the
+  // mask serves N passes; as comparisons, 8 G lane masks would have to live in scalar registers, which from G = 5 on there
+  // are not enough of: a layer-step of 8 KV heads x 2016 candidates, G = 8, 21.7 us with those, 18.4 so).
+  auto score = [&](auto nc) {
+    constexpr int N = decltype(nc)::value;
+    float mine[N];                                        // the total of query head c8, for lanes c8 < NG
 #pragma unroll
     for (int gg = 0; gg < NG; ++gg) {
-      // chunk sum, left to right.  The product q_c * (q_c >= 0 ? kmax_c : kmin_c) of two 16-bit
-      // floats is exact in fp32, so the fma rounds once, exactly like "s + product"; a mean
-      // query is a full fp32 number, so there the product is rounded on its own first.
-      float s;
-      if (QMODE) {
-        s = f[0][0] * (f[0][0] >= 0.0f ? kx[0] : kn[0]);
+      uint32_t q2[4] = {wq[gg].x, wq[gg].y, wq[gg].z, wq[gg].w};
+      // (opaque here: else every head's unpacked channels and masks are made ahead of the variants and kept: registers)
 #pragma unroll
-        for (int c = 1; c < 8; ++c) {
-          const float pr = f[0][c] * (f[0][c] >= 0.0f ? kx[c] : kn[c]);
-          s = s + pr;
+      for (int h = 0; h < 4; ++h) asm volatile("" : "+v"(q2[h]));
+      // chunk sum, left to right.  The product of two 16-bit floats is exact in fp32, so the fma rounds once, exactly
+      // like "s + product"; a mean query is a full fp32 number, so there the product is rounded on its own first.
+      float s[N];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        typedef __attribute__((ext_vector_type(2))) short s16x2;
+        uint32_t neg;
+        if (QMODE) neg = (pooled[2 * h] >= 0.0f ? 0u : 0xffffu) | (pooled[2 * h + 1] >= 0.0f ? 0u : 0xffff0000u);
+        else neg = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, q2[h]) >> 15);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const uint32_t kx = h == 0 ? wmax[i].x : h == 1 ? wmax[i].y : h == 2 ? wmax[i].z : wmax[i].w;
+          const uint32_t kn = h == 0 ? wmin[i].x : h == 1 ? wmin[i].y : h == 2 ? wmin[i].z : wmin[i].w;
+          uint32_t k2;                                    // (the compiler takes the expression apart)
+          asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(k2) : "v"(neg), "v"(kn), "v"(kx));
+          if (QMODE) {
+            const float pr = pooled[2 * h] * Unpack<DT>::lo(k2);
+            s[i] = h == 0 ? pr : s[i] + pr;
+            s[i] = s[i] + pooled[2 * h + 1] * Unpack<DT>::hi(k2);
+          } else {
+            s[i] = __builtin_fmaf(Unpack<DT>::lo(q2[h]), Unpack<DT>::lo(k2), h == 0 ? 0.0f : s[i]);
+            s[i] = __builtin_fmaf(Unpack<DT>::hi(q2[h]), Unpack<DT>::hi(k2), s[i]);
+          }
         }
-      } else {
-        s = 0.0f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) s = __builtin_fmaf(f[gg][c], f[gg][c] >= 0.0f ? kx[c] : kn[c], s);
       }
       // adjacent-pair tree over the 16 chunk sums (xor 1, 2 in quads; the mirrors pair lanes
       // that hold equal partial sums' complements, which is the same tree); every lane ends up
       // with the total
-      s = s + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s), 0xB1, 0xf, 0xf, false));
-      s = s + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s), 0x4E, 0xf, 0xf, false));
-      s = s + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s), 0x141, 0xf, 0xf, false));
-      s = s + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s), 0x140, 0xf, 0xf, false));
-      mine = c8 == gg ? s : mine;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        s[i] = s[i] + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s[i]), 0xB1, 0xf, 0xf, false));
+        s[i] = s[i] + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s[i]), 0x4E, 0xf, 0xf, false));
+        s[i] = s[i] + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s[i]), 0x141, 0xf, 0xf, false));
+        s[i] = s[i] + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(s[i]), 0x140, 0xf, 0xf, false));
+        mine[i] = gg == 0 || c8 == gg ? s[i] : mine[i];
+        asm volatile("" : "+v"(mine[i]));                 // (chosen here, not all of them at the store)
+      }
     }
-    if (TAGGED) {
-      if (c8 < NG) s_w[c8][ps * PASS + wave * 4 + grp] = mine * scale;
-    } else {
-      const int j = j0 + ps * PASS;
-      if (c8 < NG && j < n) reinterpret_cast<float*>(a.P)[((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j] = mine * scale;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int j = j0 + i * PASS;
+      if (TAGGED) {
+        if (c8 < NG) s_w[c8][i * PASS + wave * 4 + grp] = mine[i] * scale;
+      } else if (c8 < NG && j < n) {
+        reinterpret_cast<float*>(a.P)[((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j] = mine[i] * scale;
+      }
     }
-  }
+  };
+  static_assert(SCORE_PASSES == 4, "");
+  if (passes == 1) score(UnrollBy<1>{});
+  else if (passes == 2) score(UnrollBy<2>{});
+  else score(UnrollBy<4>{});
   if (!TAGGED) return;
   lds_barrier();
-  const int pages_log2 = __builtin_ctz(PASS * a.passes), pages = 1 << pages_log2, at0 = chunk * pages;     // (powers of two)
+  const int pages_log2 = __builtin_ctz(PASS * passes), pages = 1 << pages_log2, at0 = chunk * pages;     // (powers of two)
   for (int i = threadIdx.x; i < NG * pages; i += WAVES * 64) {
     const int gg = i >> pages_log2, jj = i & (pages - 1);
     if (at0 + jj < n) st_tag(a.P + ((size_t)head * G + gg) * a.max_pages + a.g.cand_lo + at0 + jj, __float_as_uint(s_w[gg][jj]), tag);
@@ -347,7 +381,6 @@ __device__ __forceinline__ float pooled_score(const uint32_t* e, const double* z
 // (selection_slices); each exchange costs a trip of about 1 us.
 // TAGGED: the weights come from scoring blocks of this launch; else from a launch that has ended.
 // ---------------------------------------------------------------------------------
-template <int U> struct UnrollBy { static constexpr int value = U; };
 constexpr int SEL_WAVES = 8, SEL_THREADS = SEL_WAVES * 64;
 constexpr int SEL_REGS = 2, SEL_REGS_ALONE = 8;          // most candidates per thread, in the launches where scoring blocks
                                                          // share the unit and in the one that only selects
