@@ -72,13 +72,19 @@ static const int g_one_launch = knob("FKV_ONE_LAUNCH", -1);       // layer-step:
 
 static const int g_fuse = knob("FKV_FUSE", -1);
 
-// Selecting blocks of a head, a power of two: each takes at most `most` candidates (its registers), and as few as
-// SEL_REGS per thread as long as the launch stays within kMaxWaiting -- an exchange costs about 2 us in all, a block of
-// 512 candidates more 1.5.
-static int selection_slices(int n_cand, int heads, int most) {
-  const int slice = g_slice > 0 ? g_slice : SEL_REGS * SEL_THREADS;
+// Selecting blocks of a head, a power of two: each takes at most `most` candidates (its registers).  One block for short
+// lists and as long as it has at most kSliceWork numerators to make: the exchanges of a shared list cost about 2 us in all
+// (8 heads x 992 candidates, G = 4: 10.1 us in one block, 12.4 in two; G = 5: 13.4 and 12.9; G = 8: 16.3 and 15.1, but
+// with 718 candidates 12.7 and 13.9).  A list that is shared anyway is cut down to
+// a candidate per thread while that leaves the launch small: 8 heads x 2016, G = 8 in two blocks 18.5 us, in four 17.2; but
+// 32 heads x 2016, G = 4, 19.8 and 25.8, the blocks being missed elsewhere.
+constexpr int kSliceAlways = 768, kSliceWork = 4096, kMaxFineSlices = 64;
+static int selection_slices(const Geom& g, int G, int heads, int most) {
+  const int n = g.n_cand;
+  if (g.k_eff == 0 || (n <= most && (n <= kSliceAlways || (long)n * G <= kSliceWork) && g_slice == 0)) return 1;
+  const int fine = g_slice > 0 ? g_slice : SEL_THREADS;
   int s = 1;
-  while (s < MAX_SLICES && ((n_cand + s - 1) / s > most || ((n_cand + s - 1) / s > slice && heads * s * 2 <= kMaxWaiting))) s *= 2;
+  while (s < MAX_SLICES && ((n + s - 1) / s > most || ((n + s - 1) / s > fine && heads * s * 2 <= kMaxFineSlices))) s *= 2;
   return s;
 }
 
@@ -150,14 +156,14 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   size_t lds;
   const int heads = d.batch * d.n_kv;
   if (!(roles & ROLE_SELECT) || (g_fuse >= 0 ? g_fuse == 1 : (long)heads * ((g.n_cand + PAGES_PER_PASS - 1) / PAGES_PER_PASS) <= kFuseMaxChunks)) {
-    const int slices = g.k_eff > 0 ? selection_slices(g.n_cand, heads, SEL_REGS * SEL_THREADS) : 1;
+    const int slices = selection_slices(g, d.G, heads, SEL_REGS * SEL_THREADS);
     fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
     if (!grant_lds(&step_kernel<DT, G>, lds, granted_step)) return -1;
     step_kernel<DT, G><<<dim3(heads, rows), STEP_THREADS, lds, st>>>(a);
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
   }
-  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, g.k_eff > 0 ? selection_slices(g.n_cand, heads, SEL_REGS_ALONE * SEL_THREADS) : 1, a, rows, lds);
+  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, selection_slices(g, d.G, heads, SEL_REGS_ALONE * SEL_THREADS), a, rows, lds);
   if (!grant_lds(&select_kernel<G>, lds, granted_select)) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
   scan_kernel<DT, G><<<dim3(a.chunks, a.other_rows + heads), SCAN_WAVES * 64, 0, st>>>(a);
@@ -301,7 +307,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   if (io.host_pool && (d.max_pages > TAGGED_MAX_PAGES || 2 * d.k > TAGGED_MAX_SLOTS)) return false;
   const int heads = d.batch * d.n_kv;
   const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
-  const int slices = g.k_eff > 0 ? selection_slices(g.n_cand, heads, SEL_REGS * SEL_THREADS) : 1;
+  const int slices = selection_slices(g, d.G, heads, SEL_REGS * SEL_THREADS);
   const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, kMaxWaiting - (slices > 1 ? heads * slices : 0));
   const int n_splits = (n_att + pps - 1) / pps;
   if (n_splits > 63 || pps > 511) return false;

@@ -823,3 +823,27 @@ def test_selection_paths_of_the_separate_step_kernel():
             pr.step(0, t)
         assert pr.stats["misses"] > 0
         pr.close()
+
+
+@pytest.mark.parametrize("G,n_kv,batch,n_cand,k", [
+    (8, 1, 1, 512, 29),      # one block, a candidate per thread
+    (8, 1, 1, 768, 29),      # the longest list that one block takes whatever the group
+    (8, 2, 1, 769, 33),      # shared by two blocks, an odd candidate over
+    (5, 1, 2, 819, 31),      # 4095 numerators: one block
+    (5, 1, 2, 820, 31),      # 4100: two
+    (4, 2, 1, 1024, 61),     # 4096 numerators, every register of one block
+    (4, 2, 1, 1025, 61),     # four blocks, the last one short
+    (1, 1, 1, 2049, 7),      # past one block's registers whatever the group
+    (3, 8, 4, 2100, 61),     # 32 heads: no finer than the registers ask for
+    (7, 1, 1, 8193, 126),    # sixteen blocks, the last one short by many
+    (2, 14, 4, 100, 28),     # 56 heads of 33 pages: attention splits of equal length
+])
+def test_selection_slices_and_attention_splits(G, n_kv, batch, n_cand, k):
+    """List lengths on both sides of each rule that shares a head's selection among blocks, in the one-launch layer-step
+    with the KV in HBM; budgets that do not divide into attention blocks of equal length."""
+    wl = W.Workload("slices", 1, batch, G * n_kv, n_kv, "bf16", (n_cand + 4) * 32 + 1, 128 + 32 * k, 64, 64, 0.8, 3, 0.8, 0.6,
+                    700 + n_cand)
+    pr = _pair(wl, [0])
+    for t in range(wl.steps):
+        pr.step(0, t)
+    pr.close()
