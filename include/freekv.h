@@ -274,7 +274,12 @@ int fkv_commit(fkv_ctx* ctx, int32_t layer);
  * submitted together (one dependency between the two streams instead of one per layer) -- with
  * the last layer of such a group, with the last layer of the context, with the same layer's
  * next step, and by any other call on the context.
- * A caller that wants them on copy_stream now (to synchronise that stream itself) calls fkv_flush. */
+ * A caller that wants them on copy_stream now (to synchronise that stream itself) calls fkv_flush.
+ * Under stream capture (placement HBM; likewise the primitives above): the call changes the context's host-side
+ * state once, and every replay repeats the captured step on what the buffers hold by then -- same position, same
+ * ACTIVE selection, same previous query.  A replay's launches are numbered on the device, by a small kernel
+ * ahead of each, so no replay can take another one's values for its own.  With placement HOST the recall's
+ * events and deferred submissions are host-side state that a replay does not repeat: do not capture there. */
 int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* k_new_dev,
                     const void* v_new_dev, float* out_dev, void* compute_stream, void* copy_stream);
 

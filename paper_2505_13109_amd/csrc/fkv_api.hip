@@ -54,7 +54,7 @@ struct Layout {
   // per layer
   size_t pool, summ, qprev, ids, slots, flags, miss, cosine, status, tagged, layer_bytes;
   // per context
-  size_t consts, P, score, part, part_ml, launch_no, step_no, dbg_page, tstamp, exch, keyx, ctx_bytes;
+  size_t consts, P, score, part, part_ml, launch_no, dbg_page, tstamp, exch, keyx, ctx_bytes;
   size_t total;
   size_t host_layer_bytes, host_total;
   int units_per_head, ring_base, n_ring, sel_base, max_splits, k, max_pages;
@@ -90,8 +90,7 @@ Layout make_layout(const fkv_config& c) {
   l.score = p;   p += align_up((size_t)b * n_kv * l.max_pages * 4);
   l.part = p;    p += align_up((size_t)b * n_q * l.max_splits * D * 8);
   l.part_ml = p; p += align_up((size_t)b * n_q * l.max_splits * 2 * 8);
-  l.launch_no = p; p += align_up((size_t)b * n_kv * 4);
-  l.step_no = p; p += align_up((size_t)b * n_kv * 4);
+  l.launch_no = p; p += align_up(4);                                 // number of the last captured launch
   l.dbg_page = p; p += align_up((size_t)UNIT_BYTES);
   l.tstamp = p;  p += align_up((size_t)64 * 8);
   // what a head's selecting blocks exchange, and the candidates' keys
@@ -184,7 +183,6 @@ struct fkv_ctx {
   int* status(int l) const { return reinterpret_cast<int*>(layer_base(l) + lay.status); }
   unsigned long long* words(size_t off) const { return reinterpret_cast<unsigned long long*>(ctx_base() + off); }
   float* score() const { return reinterpret_cast<float*>(ctx_base() + lay.score); }
-  int* step_no() const { return reinterpret_cast<int*>(ctx_base() + lay.step_no); }
   int* launch_no() const { return reinterpret_cast<int*>(ctx_base() + lay.launch_no); }
   const LayerConst* consts() const { return reinterpret_cast<const LayerConst*>(ctx_base() + lay.consts); }
   LayerConst make_consts() const {
@@ -201,11 +199,12 @@ struct fkv_ctx {
     c.corr_pool = cfg.corr_pooling; c.sel_pool = cfg.select_pooling; c.tau = cfg.tau;
     c.P = words(lay.P); c.part = words(lay.part); c.part_ml = words(lay.part_ml); c.exch = words(lay.exch); c.keyx = words(lay.keyx);
     c.score = score();
+    c.launch_no = launch_no();
     c.host_base = host; c.host_layer_bytes = lay.host_layer_bytes;
     c.tstamp = tstamp();
     return c;
   }
-  uint32_t launches = 0;              // launches with tagged exchanges so far (fkv_device.h: host_tag)
+  uint32_t launches = 0;              // number of the last launch that the host counted
   bool P_tagged = false;              // the format of the page weights the last scoring launch left
   uint16_t* dbg_page() const { return reinterpret_cast<uint16_t*>(ctx_base() + lay.dbg_page); }
   bool lose_selection = false;   // fkv_test_lose_selection: corrected heads' attention waits in vain (tests the bounded wait)
@@ -259,11 +258,22 @@ static int after_launch(fkv_ctx* ctx, const char* what) {
   return FKV_OK;
 }
 
-static uint32_t next_launch(fkv_ctx* ctx) { return ++ctx->launches & 0x7fffffffu; }
+// Numbers the next launch on `st`.
+static LaunchNo next_launch(fkv_ctx* ctx, hipStream_t st) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture == hipStreamCaptureStatusActive) {
+    launch_next_number(ctx->launch_no(), st);
+    return LaunchNo{0, ctx->launch_no()};
+  }
+  ctx->launches = (ctx->launches + 1) & 0x7fffffffu;
+  if (ctx->launches == 0) ctx->launches = 1;
+  return LaunchNo{host_tag(ctx->launches), nullptr};
+}
 
 // One launch of the step kernel with the given roles (append / correction test / selection).
-static StepIO make_step_io(fkv_ctx* ctx, int layer, const void* q, const void* k_new, const void* v_new,
-                           uint8_t* flags_user, int32_t* ids_user) {
+static StepIO make_step_io(fkv_ctx* ctx, int layer, int roles, const void* q, const void* k_new, const void* v_new,
+                           uint8_t* flags_user, int32_t* ids_user, hipStream_t st) {
   LayerState& ls = ctx->layers[layer];
   StepIO io{};
   io.pd = ctx->pool_desc(layer);
@@ -284,7 +294,7 @@ static StepIO make_step_io(fkv_ctx* ctx, int layer, const void* q, const void* k
   io.ids_user = ids_user;
   io.exch = ctx->words(ctx->lay.exch);
   io.keyx = ctx->words(ctx->lay.keyx);
-  io.launch_no = ctx->step_no();
+  if (roles & ROLE_SELECT) io.no = next_launch(ctx, st);      // (the other roles exchange nothing)
   io.status = ctx->status(layer);
   io.P_tagged = &ctx->P_tagged;
   io.tstamp = ctx->tstamp();
@@ -297,7 +307,7 @@ static StepIO make_step_io(fkv_ctx* ctx, int layer, const void* q, const void* k
   return io;
 }
 
-static AttnIO make_attn_io(fkv_ctx* ctx, int layer, const void* q, float* out, int use) {
+static AttnIO make_attn_io(fkv_ctx* ctx, int layer, const void* q, float* out, int use, LaunchNo no) {
   const LayerState& ls = ctx->layers[layer];
   AttnIO io{};
   io.q = static_cast<const uint16_t*>(q);
@@ -310,8 +320,7 @@ static AttnIO make_attn_io(fkv_ctx* ctx, int layer, const void* q, float* out, i
   io.part = ctx->words(ctx->lay.part);
   io.part_ml = ctx->words(ctx->lay.part_ml);
   io.max_splits = ctx->lay.max_splits;
-  io.launch_no = ctx->launch_no();
-  io.launch_stride = 1;
+  io.no = no;
   io.status = ctx->status(layer);
   io.out = out;
   io.tstamp = ctx->tstamp();
@@ -320,7 +329,7 @@ static AttnIO make_attn_io(fkv_ctx* ctx, int layer, const void* q, float* out, i
 
 static int run_step(fkv_ctx* ctx, int layer, int roles, const void* q, const void* k_new, const void* v_new,
                     uint8_t* flags_user, int32_t* ids_user, int L_after, hipStream_t st) {
-  const StepIO io = make_step_io(ctx, layer, q, k_new, v_new, flags_user, ids_user);
+  const StepIO io = make_step_io(ctx, layer, roles, q, k_new, v_new, flags_user, ids_user, st);
   LayerState& ls = ctx->layers[layer];
   const int n = launch_step(ctx->dims, roles, io, make_geom(ctx->cfg, L_after), st);
   if (n < 0) return ctx->fail(FKV_EHIP, "the device refused the selection's LDS");
@@ -714,7 +723,7 @@ int fkv_sparse_decode_attn(fkv_ctx* ctx, int32_t layer, const void* q_dev, float
     e0 = ctx->prof_ev[ctx->prof_used++];
     e1 = ctx->prof_ev[ctx->prof_used++];
   }
-  launch_attn(ctx->dims, ctx->pool_desc(layer), make_attn_io(ctx, layer, q_dev, out_dev, use), g, st, e0, e1);
+  launch_attn(ctx->dims, ctx->pool_desc(layer), make_attn_io(ctx, layer, q_dev, out_dev, use, next_launch(ctx, st)), g, st, e0, e1);
   return after_launch(ctx, "attention kernels");
 }
 
@@ -751,12 +760,10 @@ int fkv_sparse_decode_attn_static(fkv_ctx* ctx, int32_t layer, const void* q_dev
   // the array keeps the last call's contents, so this call's words get a tag of their own: the next number, counted on
   // the device, so that a call captured into a graph has a new one at every replay
   launch_next_number(reinterpret_cast<int*>(base), st);
-  AttnIO io = make_attn_io(ctx, layer, q_dev, out_dev, use);
+  AttnIO io = make_attn_io(ctx, layer, q_dev, out_dev, use, LaunchNo{0, reinterpret_cast<int*>(base)});
   io.part_ml = reinterpret_cast<unsigned long long*>(base + kStaticHead);
   io.part = reinterpret_cast<unsigned long long*>(base + kStaticHead + 2 * b_ml);
   io.max_splits = n_splits;
-  io.launch_no = reinterpret_cast<int*>(base);
-  io.launch_stride = 0;
   io.tstamp = nullptr;
   launch_attn(ctx->dims, ctx->pool_desc(layer), io, g, st, nullptr, nullptr);
   return after_launch(ctx, "attention kernels (static scratch)");
@@ -861,7 +868,7 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
     lio.k_new = static_cast<const uint16_t*>(k_new_dev);
     lio.v_new = static_cast<const uint16_t*>(v_new_dev);
     lio.out = out_dev;
-    lio.launch = next_launch(ctx);
+    lio.tag = next_launch(ctx, st).tag;
     lio.host_pool = host_pool;
     lio.max_splits = ctx->lay.max_splits;
     lio.lose_selection = ctx->lose_selection;
@@ -1010,7 +1017,7 @@ int fkv_profile_attn(fkv_ctx* ctx, const void* q_dev, size_t q_layer_stride, flo
   for (int r = 0; r < reps; ++r) {
     for (int l = 0; l < ctx->cfg.n_layers; ++l, ++n) {
       const LayerState& ls = ctx->layers[l];
-      launch_attn(ctx->dims, ctx->pool_desc(l), make_attn_io(ctx, l, static_cast<const char*>(q_dev) + q_layer_stride * l, out_dev, FKV_USE_ACTIVE),
+      launch_attn(ctx->dims, ctx->pool_desc(l), make_attn_io(ctx, l, static_cast<const char*>(q_dev) + q_layer_stride * l, out_dev, FKV_USE_ACTIVE, next_launch(ctx, st)),
                   make_geom(ctx->cfg, ls.L), st, nullptr, nullptr);
     }
   }
@@ -1042,7 +1049,7 @@ int fkv_profile_select(fkv_ctx* ctx, const void* q_dev, size_t q_layer_stride, i
   int n = 0;
   for (int r = 0; r < reps; ++r) {
     for (int l = 0; l < ctx->cfg.n_layers; ++l) {
-      const StepIO io = make_step_io(ctx, l, static_cast<const char*>(q_dev) + q_layer_stride * l, nullptr, nullptr, nullptr, nullptr);
+      const StepIO io = make_step_io(ctx, l, ROLE_SELECT, static_cast<const char*>(q_dev) + q_layer_stride * l, nullptr, nullptr, nullptr, nullptr, st);
       const int m = launch_step(ctx->dims, ROLE_SELECT, io, make_geom(ctx->cfg, ctx->layers[l].L), st);
       if (m < 0) return ctx->fail(FKV_EHIP, "the device refused the selection's LDS");
       n += m;

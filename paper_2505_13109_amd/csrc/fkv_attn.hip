@@ -47,7 +47,7 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   AttnArgs a{};
   a.pd = pd; a.q = io.q; a.act_ids = io.act_ids; a.new_ids = io.new_ids; a.act_slots = io.act_slots; a.new_slots = io.new_slots;
   a.flags = io.flags; a.use = io.use; a.part = io.part; a.part_ml = io.part_ml; a.max_splits = io.max_splits;
-  a.launch_no = io.launch_no; a.launch_stride = io.launch_stride;
+  a.no = io.no;
   a.pps = attn_pages_per_block(n_att, heads, io.max_splits, 4);
   a.n_splits = (n_att + a.pps - 1) / a.pps;
   a.share = (d.G * D + a.n_splits - 1) / a.n_splits;
@@ -61,7 +61,10 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   if (ev_end) (void)hipEventRecord(ev_end, st);
 }
 
-__global__ void next_number_kernel(int* __restrict__ p) { *p += 1; }
+__global__ void next_number_kernel(int* __restrict__ p) {
+  const int n = (*p + 1) & 0x7fffffff;
+  *p = n ? n : 1;
+}
 void launch_next_number(int* p, hipStream_t st) { next_number_kernel<<<1, 1, 0, st>>>(p); }
 
 // ---------------------------------------------------------------------------------

@@ -103,8 +103,7 @@ struct AttnArgs {
   unsigned long long* part_ml;
   int max_splits, pps, n_splits;
   int share;                 // outputs of a head that each of its blocks finishes
-  int* launch_no;            // stand-alone attention: number of the last launch, per head (stride 1: moved on here)
-  int launch_stride;         //   or one for all heads (stride 0: moved on by a kernel of its own)
+  LaunchNo no;               // stand-alone attention: of this launch
   float* out;
   Geom g;
   int n_kv, G, k;
@@ -119,7 +118,7 @@ struct AttnArgs {
   const uint16_t* k_new;
   const uint16_t* v_new;
   const unsigned long long* tagged;   // [heads][k]: this step's picked ids, tagged, written by the selection
-  uint32_t tag;              // tag of this launch
+  uint32_t tag;              // fused: tag of this launch
   uint32_t pick_tag;         // tag the picked ids are waited for with: the same (a test of the bounded wait asks for another)
   // fused, KV in a host pool: the tagged words are tagged_pick() values; a corrected head's wave copies a missing page
   // from the host pool into its slot while it attends over it
@@ -208,11 +207,8 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
   const bool owns_new = FUSED && __ballot(page_l == new_page && !picked) != 0;
   if (FUSED && new_tok == 0 && page_l == new_page) unit_l = -1;
 
-  uint32_t tag = a.tag;
-  int launch_no = 0;
-  if (!FUSED) {
-    launch_no = a.launch_no[head * a.launch_stride] + a.launch_stride;
-  }
+  int number = 0;                                       // (waited for where the tag is needed)
+  if (!FUSED && a.no.dev) number = *a.no.dev;
 
   const uint16_t* head_pool = pd.pool + (size_t)head * pd.units_per_head * UNIT_ELEMS;
   const float sl2 = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(d) * log2(e)
@@ -440,8 +436,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
     for (int cb = 0; cb < 8; ++cb) *reinterpret_cast<f32x4*>(o + cb * 16 + rb * 4) = acc[cb];
     if (rb == 0) *reinterpret_cast<float2*>(sm_ml + (wave * 16 + gq) * 2) = make_float2(m_run, l_run);
   }
-  // (every wave has read the launch number before anyone can move it on)
-  if (!FUSED) tag = device_tag((uint32_t)__builtin_amdgcn_readfirstlane(launch_no));
+  const uint32_t tag = FUSED ? a.tag : a.no.dev ? device_tag((uint32_t)__builtin_amdgcn_readfirstlane(number)) : a.no.tag;
   lds_barrier();
   // ---- log-sum-exp merge of the head's splits, shared by its blocks ----
   // Block `split` finishes the split-th `share` of the head's G x D outputs: its threads keep their sums of that part, hand
@@ -537,8 +532,6 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
       }
     }
     a.out[(size_t)head * items + idx] = o[t] / den[t];
-    // (the thread has every other block's sums, so all of them have read the launch number)
-    if (!FUSED && idx == 0 && a.launch_stride) a.launch_no[head] = launch_no;
   }
   if (split == 0) FKV_ASTAMP(21);
 #undef FKV_ASTAMP

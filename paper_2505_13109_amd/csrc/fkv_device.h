@@ -210,6 +210,7 @@ __device__ __forceinline__ void st_tag(unsigned long long* p, uint32_t value, ui
 __device__ __forceinline__ unsigned long long ld_tag(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ uint32_t launch_tag(const LaunchNo& n) { return n.dev ? device_tag((uint32_t)*n.dev) : n.tag; }
 // Polls of a waiting wave before it gives up: about 0.1 s.
 constexpr int MAX_POLLS = 1 << 16;
 

@@ -80,8 +80,13 @@ __host__ __device__ inline int v_elem_off(int t, int ch) {
 // ---- launch wrappers (defined in the kernel files) ----------------------
 struct Dims { int batch, n_q, n_kv, G, k, max_pages, dtype, max_lds, sel_pool, corr_pool; };
 
-// Launches are numbered (31 bits); the low bit keeps the tags of launches numbered by the host (the layer kernel) apart from
-// those of launches numbered on the device (the step and attention kernels: a program may capture those), which share buffers.
+// Launches are numbered (31 bits, from 1), and the values that a launch's blocks exchange carry its number as a tag.  The
+// host counts.  A launch that is being captured runs again at every replay with the arguments it was captured with, so its
+// number is counted on the device instead, by a small kernel ahead of it; the low bit keeps the two counts' tags apart.
+struct LaunchNo {
+  uint32_t tag;              // the tag, or
+  const int* dev;            // if not null: where the number is
+};
 __host__ __device__ inline uint32_t host_tag(uint32_t launch) { return (launch << 1) | 1u; }
 __host__ __device__ inline uint32_t device_tag(uint32_t launch) { return launch << 1; }
 
@@ -93,7 +98,7 @@ struct StepIO {
   uint8_t* flags; uint8_t* flags_user; double* cosine;                               // correction test
   unsigned long long* P; float* score; int32_t* ids; int32_t* ids_user;              // selection
   unsigned long long* exch; unsigned long long* keyx;                                // its exchange between blocks
-  int* launch_no; int* status;                                                       // number of the last launch, per head
+  LaunchNo no; int* status;
   bool* P_tagged;                                                                    // out: the format the launch left P in
   long long* tstamp;                                                                 // debug timestamps or null
   // KV in a host pool (else all null): a launch with ROLE_SELECT also makes the recall plan of the new selection --
@@ -119,6 +124,7 @@ struct LayerConst {
   float tau;
   unsigned long long *P, *part, *part_ml, *exch, *keyx;
   float* score;
+  const int* launch_no;                      // number of the last captured launch
   const char* host_base;                     // KV in a host pool (else null)
   unsigned long long host_layer_bytes;
   long long* tstamp;                         // debug timestamps or null
@@ -130,7 +136,7 @@ struct LayerIO {
   int layer, parity, have_prev;
   const uint16_t *q, *k_new, *v_new;
   float* out;
-  uint32_t launch;                           // number of this launch (host_tag)
+  uint32_t tag;                              // of this launch; 0: number it by what is at consts->launch_no
   bool host_pool;
   int max_splits;
   bool lose_selection;                       // test of the bounded wait: attention waits for a tag that never comes
@@ -168,11 +174,11 @@ struct AttnIO {
   const uint16_t* q; const int32_t* act_ids; const int32_t* new_ids; const int32_t* act_slots; const int32_t* new_slots;
   const uint8_t* flags; int use;
   unsigned long long* part; unsigned long long* part_ml; int max_splits;
-  int* launch_no; int launch_stride;         // launch numbers: per head, moved on by the kernel (1), or one word (0)
+  LaunchNo no;
   int* status; float* out; long long* tstamp;
 };
 void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end);
-void launch_next_number(int* p, hipStream_t st);            // *p += 1, by a kernel
+void launch_next_number(int* p, hipStream_t st);            // *p to the next launch number, by a kernel
 void launch_read_page(const uint16_t* unit, uint16_t* out_token_major, hipStream_t st);
 void launch_export_nhd(const Dims& d, const PoolDesc& pd, const int32_t* act_ids, const int32_t* new_ids,
                        const int32_t* act_slots, const int32_t* new_slots, const uint8_t* flags, int use,

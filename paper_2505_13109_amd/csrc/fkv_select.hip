@@ -114,7 +114,7 @@ static void fill_step_args(const Dims& d, int roles, const StepIO& io, Geom g, i
   a.corr_pool = d.corr_pool; a.sel_pool = d.sel_pool;
   a.flags = io.flags; a.flags_user = io.flags_user; a.cosine = io.cosine;
   a.P = io.P; a.score = io.score; a.ids = io.ids; a.ids_user = io.ids_user; a.exch = io.exch; a.keyx = io.keyx;
-  a.launch_no = io.launch_no; a.status = io.status; a.tstamp = io.tstamp;
+  a.no = io.no; a.status = io.status; a.tstamp = io.tstamp;
   a.passes = passes;
   a.slices = slices;
   rows = 0;
@@ -204,7 +204,7 @@ constexpr int kMaxLayersPacked = 1 << 13, kMaxCtxPacked = 1 << 19;
 template <int DT, int G, bool HOSTPOOL>
 __global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
-                  uint32_t packed, uint32_t launch, uint32_t plan, uint32_t split_magic) {
+                  uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
   extern __shared__ uint32_t dyn_lds[];
   LayerConstPtr c = (LayerConstPtr)consts;
   touch<sizeof(LayerConst)>(c);
@@ -212,7 +212,7 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
   char* const base = c->dev_base + c->layer_bytes * (unsigned long long)layer;
   auto at = [&](uint32_t o) { return base + (unsigned long long)o * 256; };
   const Geom g = geom_of((int)(packed & 0x7ffffu) + 1, c->n_sink, c->n_win, c->k);
-  const uint32_t tag = host_tag(launch);
+  const uint32_t tag = host_numbered ? host_numbered : device_tag((uint32_t)*(const __attribute__((address_space(4))) int*)c->launch_no);
   PoolDesc pd;
   pd.pool = reinterpret_cast<uint16_t*>(base);
   pd.units_per_head = c->units_per_head;
@@ -242,7 +242,7 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
     a.ids = ids0 + (size_t)now * c->ids_half; a.ids_user = nullptr;
     a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
     a.slice = (g.n_cand + slices - 1) >> slices_log2;
-    a.exch = c->exch; a.keyx = c->keyx; a.tag = tag; a.launch_no = nullptr; a.status = status; a.tstamp = c->tstamp;
+    a.exch = c->exch; a.keyx = c->keyx; a.no = LaunchNo{tag, nullptr}; a.status = status; a.tstamp = c->tstamp;
     a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
     if (HOSTPOOL) {
@@ -262,7 +262,7 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
   a.flags = nullptr; a.use = 2; a.part = c->part; a.part_ml = c->part_ml; a.max_splits = c->max_splits;
   a.n_splits = (int)(plan >> 7) & 63; a.pps = (int)(plan >> 13) & 511;
   a.share = split_magic ? (int)__umulhi((uint32_t)(G * D + a.n_splits - 1), split_magic) : G * D;
-  a.launch_no = nullptr; a.launch_stride = 0; a.out = out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
+  a.no = LaunchNo{}; a.out = out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
   a.status = status; a.tstamp = c->tstamp;
   a.q_prev = qprev0 + (size_t)before * c->qprev_half; a.have_prev = (int)(plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
   a.k_new = k_new; a.v_new = v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
@@ -281,7 +281,7 @@ template <int DT, int G, bool HOSTPOOL>
 static bool launch_layer_gh(const LayerIO& io, const LayerLaunch& l, hipStream_t st) {
   static size_t granted = 48 * 1024;
   if (!grant_lds(&layer_kernel<DT, G, HOSTPOOL>, l.lds, granted)) return false;
-  layer_kernel<DT, G, HOSTPOOL><<<l.grid, STEP_THREADS, l.lds, st>>>(io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.launch, l.plan, l.split_magic);
+  layer_kernel<DT, G, HOSTPOOL><<<l.grid, STEP_THREADS, l.lds, st>>>(io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
   return true;
 }
 template <int DT, int G>

@@ -78,9 +78,7 @@ struct StepArgs {
   int slice;                 // candidates of each (the last may have fewer)
   unsigned long long* exch;  // [heads][MAX_SLICES][3 * MAX_G] tagged: what a head's selecting blocks tell each other
   unsigned long long* keyx;  // [heads][max_pages] tagged: the candidates' keys, for the head's last selecting block
-  uint32_t tag;              // tag of this launch; or
-  int* launch_no;            // if not null: [heads] number of the last launch, moved on by a head's last selecting block
-                             // (counted on the device, so that a captured launch has new tags at every replay)
+  LaunchNo no;               // of this launch
   int* status;               // set to 1 if a wait ran out
   long long* tstamp;         // debug: 100 MHz timestamps of head 0's phases (may be null)
   unsigned long long* tagged; // if not null: [heads][k], every picked id once more as a tagged word: a block of
@@ -164,10 +162,6 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // for a later launch each pass stores its own, which leaves the waves of a bandwidth-bound scan independent of each other
 // (28.2 us against 30.3 us through LDS for 256 heads x 992 pages).
 // ---------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t launch_tag(const StepArgs& a, int head) {
-  return a.launch_no ? device_tag((uint32_t)a.launch_no[head] + 1u) : a.tag;
-}
-
 template <int DT, int G, bool QMODE, bool TAGGED, int WAVES>
 __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chunk) {
   constexpr int PASS = WAVES * 4;                         // pages per pass
@@ -186,7 +180,7 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
       wmin[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D + to_min);
     }
   }
-  const uint32_t tag = TAGGED ? launch_tag(a, head) : 0u;
+  const uint32_t tag = TAGGED ? launch_tag(a.no) : 0u;
   uint4 wq[G];
 #pragma unroll
   for (int gg = 0; gg < G; ++gg) wq[gg] = *reinterpret_cast<const uint4*>(a.q + ((size_t)head * G + gg) * D + c8 * 8);
@@ -528,7 +522,7 @@ __device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, 
   const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff, k = a.k;
   const int S = a.slices;
   const bool last = s == S - 1;
-  const uint32_t tag = launch_tag(a, head);
+  const uint32_t tag = launch_tag(a.no);
   const int j0 = s * a.slice, j1 = min(n, j0 + a.slice);
   // The waves that take part: as many as there are candidates for; all of them where a plan has to be made or keys of
   // other slices have to be gathered.  The others of the block end here (a barrier counts the waves that are left).
@@ -772,7 +766,6 @@ __device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, 
   // give up too) and the list names no page
   if (lost) sm.lost = 1;
   lds_barrier();
-  if (a.launch_no && tid == 0) a.launch_no[head] += 1;   // (everyone who needs the number has read it: their values are here)
   if (sm.lost) {
     if (tid == 0) {
       *a.status = 1;
