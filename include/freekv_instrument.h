@@ -1,8 +1,8 @@
 /* freekv_instrument.h -- measurement and test hooks of libfreekv.so.
  *
  * Not part of the retrieval-decode interface (freekv.h): these entry points exist for the benchmark
- * (kernel timers on the launch stream, the cost of an empty launch) and for one test of failure
- * handling (a bounded in-kernel wait that the host makes run out).  A serving loop needs none of them.
+ * (kernel timers on the launch stream, the cost of an empty launch) and for tests of what the blocks of a
+ * launch exchange.  A serving loop needs none of them.
  * Same conventions as freekv.h: 0 or a negative FKV_E* code, nothing throws.
  */
 #ifndef FREEKV_INSTRUMENT_H
@@ -47,6 +47,10 @@ int fkv_profile_launch_floor(fkv_ctx* ctx, int32_t layer, int32_t reps, void* st
  * wait for the wrong one).  Every kernel still ends; the wait runs out after about 0.1 s, the head's
  * output rows are NaN and fkv_health reports FKV_ETIMEOUT.  Host-side switch, no GPU work. */
 int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on);
+
+/* Test hook for the numbers that tell one launch's exchanged values from another's (31 bits, one per launch): the
+ * context's next launch gets the number after `last`.  Host-side, no GPU work. */
+int fkv_test_launch_number(fkv_ctx* ctx, int32_t last);
 
 /* While on, kernels record 100 MHz phase timestamps of head 0 (read with FKV_DBG_TSTAMP). */
 int fkv_instrument_timestamps(fkv_ctx* ctx, int32_t on);

@@ -23,7 +23,7 @@ EXPORTED_SYMBOLS = (
     "fkv_load_prefix", "fkv_kv_append", "fkv_page_summary_update", "fkv_corr_check",
     "fkv_page_select", "fkv_recall_pages", "fkv_sparse_decode_attn", "fkv_commit",
     "fkv_decode_step", "fkv_flush", "fkv_debug_read", "fkv_debug_read_page", "fkv_profile_enable", "fkv_profile_read", "fkv_profile_attn", "fkv_profile_select", "fkv_profile_launch_floor", "fkv_step_launches", "fkv_export_nhd",
-    "fkv_sparse_decode_attn_static", "fkv_recall_pending", "fkv_attach_nhd_pool", "fkv_test_lose_selection", "fkv_instrument_timestamps",
+    "fkv_sparse_decode_attn_static", "fkv_recall_pending", "fkv_attach_nhd_pool", "fkv_test_lose_selection", "fkv_test_launch_number", "fkv_instrument_timestamps",
 )
 
 
@@ -83,6 +83,7 @@ def lib() -> C.CDLL:
         "fkv_recall_pending": (C.c_int, [vp, i32, i32, vp]),
         "fkv_attach_nhd_pool": (C.c_int, [vp, vp, vp, i32]),
         "fkv_test_lose_selection": (C.c_int, [vp, i32]),
+        "fkv_test_launch_number": (C.c_int, [vp, i32]),
         "fkv_instrument_timestamps": (C.c_int, [vp, i32]),
         "fkv_sparse_decode_attn": (C.c_int, [vp, i32, vp, vp, i32, vp]),
         "fkv_sparse_decode_attn_static": (C.c_int, [vp, i32, vp, vp, i32, vp]),
@@ -201,6 +202,9 @@ class FreeKV:
 
     def test_lose_selection(self, on):
         self._check(self.L.fkv_test_lose_selection(self._h, int(on)), "fkv_test_lose_selection")
+
+    def test_launch_number(self, last):
+        self._check(self.L.fkv_test_launch_number(self._h, last), "fkv_test_launch_number")
 
     def instrument_timestamps(self, on):
         self._check(self.L.fkv_instrument_timestamps(self._h, int(on)), "fkv_instrument_timestamps")

@@ -54,7 +54,7 @@ struct Layout {
   // per layer
   size_t pool, summ, qprev, ids, slots, flags, miss, cosine, status, tagged, layer_bytes;
   // per context
-  size_t consts, P, score, part, part_ml, launch_no, dbg_page, tstamp, exch, keyx, ctx_bytes;
+  size_t consts, P, part, part_ml, exch, keyx, words_end, P_plain, score, launch_no, dbg_page, tstamp, ctx_bytes;
   size_t total;
   size_t host_layer_bytes, host_total;
   int units_per_head, ring_base, n_ring, sel_base, max_splits, k, max_pages;
@@ -86,16 +86,18 @@ Layout make_layout(const fkv_config& c) {
   l.layer_bytes = o;
   size_t p = 0;
   l.consts = p;  p += align_up(sizeof(LayerConst));
-  l.P = p;       p += align_up((size_t)b * n_q * l.max_pages * 8);   // tagged words (or, in separate launches, fp32)
-  l.score = p;   p += align_up((size_t)b * n_kv * l.max_pages * 4);
+  // tagged words (fkv_device.h: st_tag), and nothing else, from here to words_end
+  l.P = p;       p += align_up((size_t)b * n_q * l.max_pages * 8);
   l.part = p;    p += align_up((size_t)b * n_q * l.max_splits * D * 8);
   l.part_ml = p; p += align_up((size_t)b * n_q * l.max_splits * 2 * 8);
+  l.exch = p;    p += align_up((size_t)b * n_kv * EXCH_WORDS * 8);   // what a head's selecting blocks exchange,
+  l.keyx = p;    p += align_up((size_t)b * n_kv * l.max_pages * 8);  // and the candidates' keys
+  l.words_end = p;
+  l.P_plain = p; p += align_up((size_t)b * n_q * l.max_pages * 4);   // page weights between separate launches
+  l.score = p;   p += align_up((size_t)b * n_kv * l.max_pages * 4);
   l.launch_no = p; p += align_up(4);                                 // number of the last captured launch
   l.dbg_page = p; p += align_up((size_t)UNIT_BYTES);
   l.tstamp = p;  p += align_up((size_t)64 * 8);
-  // what a head's selecting blocks exchange, and the candidates' keys
-  l.exch = p;    p += align_up((size_t)b * n_kv * EXCH_WORDS * 8);
-  l.keyx = p;    p += align_up((size_t)b * n_kv * l.max_pages * 8);
   l.ctx_bytes = p;
   l.total = l.layer_bytes * c.n_layers + l.ctx_bytes;
   l.host_layer_bytes = c.placement == FKV_PLACE_HOST ? (size_t)b * n_kv * l.max_pages * UNIT_BYTES : 0;
@@ -182,6 +184,7 @@ struct fkv_ctx {
   unsigned long long* tagged(int l) const { return reinterpret_cast<unsigned long long*>(layer_base(l) + lay.tagged); }
   int* status(int l) const { return reinterpret_cast<int*>(layer_base(l) + lay.status); }
   unsigned long long* words(size_t off) const { return reinterpret_cast<unsigned long long*>(ctx_base() + off); }
+  float* P_plain() const { return reinterpret_cast<float*>(ctx_base() + lay.P_plain); }
   float* score() const { return reinterpret_cast<float*>(ctx_base() + lay.score); }
   int* launch_no() const { return reinterpret_cast<int*>(ctx_base() + lay.launch_no); }
   const LayerConst* consts() const { return reinterpret_cast<const LayerConst*>(ctx_base() + lay.consts); }
@@ -205,7 +208,7 @@ struct fkv_ctx {
     return c;
   }
   uint32_t launches = 0;              // number of the last launch that the host counted
-  bool P_tagged = false;              // the format of the page weights the last scoring launch left
+  bool P_tagged = false;              // whether the last scoring launch left its page weights in P or in P_plain
   uint16_t* dbg_page() const { return reinterpret_cast<uint16_t*>(ctx_base() + lay.dbg_page); }
   bool lose_selection = false;   // fkv_test_lose_selection: corrected heads' attention waits in vain (tests the bounded wait)
   bool stamp_on = false;   // fkv_instrument_timestamps: kernels record phase timestamps of head 0 (debugging aid)
@@ -267,7 +270,12 @@ static LaunchNo next_launch(fkv_ctx* ctx, hipStream_t st) {
     return LaunchNo{0, ctx->launch_no()};
   }
   ctx->launches = (ctx->launches + 1) & 0x7fffffffu;
-  if (ctx->launches == 0) ctx->launches = 1;
+  if (ctx->launches == 0) {           // the numbers start over: no word may still carry one from the time before
+    ctx->launches = 1;
+    (void)hipMemsetAsync(ctx->ctx_base() + ctx->lay.P, 0, ctx->lay.words_end - ctx->lay.P, st);
+    for (int l = 0; l < ctx->cfg.n_layers; ++l)
+      (void)hipMemsetAsync(ctx->tagged(l), 0, (size_t)ctx->cfg.batch * ctx->cfg.n_kv_heads * (ctx->lay.k > 0 ? ctx->lay.k : 1) * 8, st);
+  }
   return LaunchNo{host_tag(ctx->launches), nullptr};
 }
 
@@ -289,6 +297,7 @@ static StepIO make_step_io(fkv_ctx* ctx, int layer, int roles, const void* q, co
   io.flags_user = flags_user;
   io.cosine = ctx->cosine(layer);
   io.P = ctx->words(ctx->lay.P);
+  io.P_plain = ctx->P_plain();
   io.score = ctx->score();
   io.ids = ctx->ids(layer, ls.parity);
   io.ids_user = ids_user;
@@ -963,6 +972,13 @@ int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on) {
   return FKV_OK;
 }
 
+int fkv_test_launch_number(fkv_ctx* ctx, int32_t last) {
+  if (!ctx) return FKV_EINVAL;
+  if (last < 0) return ctx->fail(FKV_ERANGE, "launch numbers have 31 bits");
+  ctx->launches = (uint32_t)last;
+  return FKV_OK;
+}
+
 int fkv_instrument_timestamps(fkv_ctx* ctx, int32_t on) {
   if (!ctx) return FKV_EINVAL;
   ctx->stamp_on = on != 0;
@@ -1110,7 +1126,7 @@ int fkv_debug_read(fkv_ctx* ctx, int32_t layer, int32_t what, void* host_out, si
     case FKV_DBG_SUMMARIES:   src = ctx->summ(layer); n = (size_t)c.batch * c.n_kv_heads * 2 * ctx->lay.max_pages * D * 2; break;
     case FKV_DBG_WEIGHTS: {
       n = (size_t)c.batch * c.n_q_heads * ctx->lay.max_pages * 4;
-      if (!ctx->P_tagged) { src = ctx->words(ctx->lay.P); break; }
+      if (!ctx->P_tagged) { src = ctx->P_plain(); break; }
       if (bytes < n) return ctx->fail(FKV_EINVAL, "output buffer too small");
       FKV_HIP(ctx, hipDeviceSynchronize());
       std::vector<unsigned long long> tmp(n / 4);

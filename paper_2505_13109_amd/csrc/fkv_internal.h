@@ -96,10 +96,10 @@ struct StepIO {
   PoolDesc pd; uint16_t* summ; const uint16_t* k_new; const uint16_t* v_new;      // append
   const uint16_t* q; const uint16_t* q_prev; uint16_t* q_stage; int have_prev; float tau;
   uint8_t* flags; uint8_t* flags_user; double* cosine;                               // correction test
-  unsigned long long* P; float* score; int32_t* ids; int32_t* ids_user;              // selection
+  unsigned long long* P; float* P_plain; float* score; int32_t* ids; int32_t* ids_user;              // selection
   unsigned long long* exch; unsigned long long* keyx;                                // its exchange between blocks
   LaunchNo no; int* status;
-  bool* P_tagged;                                                                    // out: the format the launch left P in
+  bool* P_tagged;                                                                    // out: whether the launch wrote P or P_plain
   long long* tstamp;                                                                 // debug timestamps or null
   // KV in a host pool (else all null): a launch with ROLE_SELECT also makes the recall plan of the new selection --
   // ACTIVE ids and slots in, PENDING slots and miss lists out

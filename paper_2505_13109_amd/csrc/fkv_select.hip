@@ -164,6 +164,7 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
     return 1;
   }
   fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, selection_slices(g, d.G, heads, SEL_REGS_ALONE * SEL_THREADS), a, rows, lds);
+  a.P = reinterpret_cast<unsigned long long*>(io.P_plain);
   if (!grant_lds(&select_kernel<G>, lds, granted_select)) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
   scan_kernel<DT, G><<<dim3(a.chunks, a.other_rows + heads), SCAN_WAVES * 64, 0, st>>>(a);

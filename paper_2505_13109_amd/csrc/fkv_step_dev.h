@@ -67,7 +67,8 @@ struct StepArgs {
   // selection
   int sel_pool;              // FKV_POOL_*
   unsigned long long* P;     // page weights [query heads][max_pages], tagged; in a launch that only scores and one that
-                             // only selects: plain fp32 in the same order
+                             // only selects: plain fp32 in the same order (in memory of their own: the bits of a plain
+                             // weight could be some launch's tag)
   float* score;
   int32_t* ids;
   int32_t* ids_user;

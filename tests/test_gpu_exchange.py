@@ -89,3 +89,53 @@ def test_a_captured_step_is_right_at_every_replay(call, batch, n_q, n_kv, ctx, l
     g.health(0)
     g.close()
     e.close()
+
+
+def _same_as_a_fresh_context(g, x, tokens):
+    """`g` decodes `tokens` of x (its prompt just loaded) exactly as a context that did nothing before."""
+    e = x.context()
+    out, ref = x.out(), x.out()
+    e.load_prefix(0, x.K, x.V)
+    for t in range(tokens):
+        _step(g, x.q[t], x.k[t], x.v[t], out)
+        _step(e, x.q[t], x.k[t], x.v[t], ref)
+        assert np.array_equal(g.debug_read(0, B.DBG_ACTIVE_IDS), e.debug_read(0, B.DBG_ACTIVE_IDS)), t
+        assert torch.equal(out, ref), t
+    e.close()
+
+
+def test_weights_of_separate_launches_are_no_tags():
+    """A long prompt is scored in a launch of its own, as plain fp32; the short prompt that follows in the same context
+    takes one launch, whose blocks know each other's weights by a launch number.  With every plain weight the same odd bit
+    pattern and the launch numbered to match, no plain weight may be taken for one of the new prompt's."""
+    x = _Inputs(5, 30, 8, 8, 3000, 3)                                     # 240 KV heads
+    long_ctx = (800 + 4) * 32                                             # 7 blocks of 128 pages to score per head
+    g = x.context(max_ctx=long_ctx + 32)
+    ones = torch.ones((30, long_ctx, 8, 128), dtype=DT, device="cuda")
+    g.load_prefix(0, ones, ones)
+    q = torch.zeros((30, 8, 128), dtype=DT, device="cuda")
+    q[..., 0] = 7.0                                                       # 7 * fl32(1 / sqrt(128)): an odd bit pattern
+    _step(g, q, x.k[0], x.v[0], x.out())
+    assert g.step_launches(0) == 3
+    bits = int(g.debug_read(0, B.DBG_WEIGHTS)[0, 0, 2:300].view(np.uint32).min())
+    assert bits & 1 and (g.debug_read(0, B.DBG_WEIGHTS)[:, :, 2:300].view(np.uint32) == bits).all()
+    g.load_prefix(0, x.K, x.V)
+    g.test_launch_number((bits >> 1) - 1)                                 # tag of the next launch: 2 * number + 1 = bits
+    _same_as_a_fresh_context(g, x, 2)
+    assert g.step_launches(0) == 1
+    g.health(0)
+    g.close()
+
+
+def test_launch_numbers_starting_over():
+    """After 2^31 launches the numbers repeat.  Words left by the launches of the first time round carry the same numbers:
+    none of them may be taken for a new one's."""
+    x, y = _Inputs(7, 1, 32, 8, 20000, 4), _Inputs(8, 1, 32, 8, 20000, 4)
+    g = x.context()
+    g.load_prefix(0, y.K, y.V)
+    _step(g, y.q[0], y.k[0], y.v[0], y.out())                             # number 1
+    g.load_prefix(0, x.K, x.V)
+    g.test_launch_number(0x7fffffff)
+    _same_as_a_fresh_context(g, x, 4)
+    g.health(0)
+    g.close()
