@@ -48,6 +48,16 @@ int fkv_profile_launch_floor(fkv_ctx* ctx, int32_t layer, int32_t reps, void* st
  * output rows are NaN and fkv_health reports FKV_ETIMEOUT.  Host-side switch, no GPU work. */
 int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on);
 
+/* Test hook for what a block does when another block of its launch keeps it waiting too long: waits of these kinds
+ * run out at the first look.  Nothing is lost by that -- the waiting block makes what it waits for itself -- so ids and
+ * outputs stay what they are, bit for bit.  Host-side switch, no GPU work. */
+#define FKV_WAIT_WEIGHTS  1  /* the selection's, for page weights from scoring blocks of the launch       */
+#define FKV_WAIT_MAXIMA   2  /* a slice's, for the other slices' maxima                                   */
+#define FKV_WAIT_SUMS     4  /*                ... softmax sums                                           */
+#define FKV_WAIT_KEYS     8  /* the last slice's, for the other slices' keys                              */
+#define FKV_WAIT_ALL     15
+int fkv_test_impatience(fkv_ctx* ctx, int32_t kinds);
+
 /* Test hook for the numbers that tell one launch's exchanged values from another's (31 bits, one per launch): the
  * context's next launch gets the number after `last`.  Host-side, no GPU work. */
 int fkv_test_launch_number(fkv_ctx* ctx, int32_t last);

@@ -16,6 +16,7 @@ FKV_PLACE_HBM, FKV_PLACE_HOST = 0, 1
 FKV_USE_ACTIVE, FKV_USE_PENDING, FKV_USE_BY_FLAG = 0, 1, 2
 FKV_HEADS_ALL, FKV_HEADS_FLAGGED, FKV_HEADS_UNFLAGGED = 0, 1, 2
 FKV_RECALL_GATHER, FKV_RECALL_MEMCPY = 0, 1
+FKV_WAIT_WEIGHTS, FKV_WAIT_MAXIMA, FKV_WAIT_SUMS, FKV_WAIT_KEYS = 1, 2, 4, 8
 DBG_SUMMARIES, DBG_WEIGHTS, DBG_SCORES, DBG_ACTIVE_IDS, DBG_PENDING_IDS, DBG_FLAGS, DBG_MISS, DBG_COSINE, DBG_TSTAMP = range(9)
 
 EXPORTED_SYMBOLS = (
@@ -23,7 +24,7 @@ EXPORTED_SYMBOLS = (
     "fkv_load_prefix", "fkv_kv_append", "fkv_page_summary_update", "fkv_corr_check",
     "fkv_page_select", "fkv_recall_pages", "fkv_sparse_decode_attn", "fkv_commit",
     "fkv_decode_step", "fkv_flush", "fkv_debug_read", "fkv_debug_read_page", "fkv_profile_enable", "fkv_profile_read", "fkv_profile_attn", "fkv_profile_select", "fkv_profile_launch_floor", "fkv_step_launches", "fkv_export_nhd",
-    "fkv_sparse_decode_attn_static", "fkv_recall_pending", "fkv_attach_nhd_pool", "fkv_test_lose_selection", "fkv_test_launch_number", "fkv_instrument_timestamps",
+    "fkv_sparse_decode_attn_static", "fkv_recall_pending", "fkv_attach_nhd_pool", "fkv_test_lose_selection", "fkv_test_launch_number", "fkv_test_impatience", "fkv_instrument_timestamps",
 )
 
 
@@ -84,6 +85,7 @@ def lib() -> C.CDLL:
         "fkv_attach_nhd_pool": (C.c_int, [vp, vp, vp, i32]),
         "fkv_test_lose_selection": (C.c_int, [vp, i32]),
         "fkv_test_launch_number": (C.c_int, [vp, i32]),
+        "fkv_test_impatience": (C.c_int, [vp, i32]),
         "fkv_instrument_timestamps": (C.c_int, [vp, i32]),
         "fkv_sparse_decode_attn": (C.c_int, [vp, i32, vp, vp, i32, vp]),
         "fkv_sparse_decode_attn_static": (C.c_int, [vp, i32, vp, vp, i32, vp]),
@@ -202,6 +204,9 @@ class FreeKV:
 
     def test_lose_selection(self, on):
         self._check(self.L.fkv_test_lose_selection(self._h, int(on)), "fkv_test_lose_selection")
+
+    def test_impatience(self, kinds):
+        self._check(self.L.fkv_test_impatience(self._h, kinds), "fkv_test_impatience")
 
     def test_launch_number(self, last):
         self._check(self.L.fkv_test_launch_number(self._h, last), "fkv_test_launch_number")

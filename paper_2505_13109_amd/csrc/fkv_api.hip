@@ -210,6 +210,7 @@ struct fkv_ctx {
   uint32_t launches = 0;              // number of the last launch that the host counted
   bool P_tagged = false;              // whether the last scoring launch left its page weights in P or in P_plain
   uint16_t* dbg_page() const { return reinterpret_cast<uint16_t*>(ctx_base() + lay.dbg_page); }
+  uint32_t impatient = 0;        // fkv_test_impatience
   bool lose_selection = false;   // fkv_test_lose_selection: corrected heads' attention waits in vain (tests the bounded wait)
   bool stamp_on = false;   // fkv_instrument_timestamps: kernels record phase timestamps of head 0 (debugging aid)
   long long* tstamp() const { return stamp_on ? reinterpret_cast<long long*>(ctx_base() + lay.tstamp) : nullptr; }
@@ -304,7 +305,7 @@ static StepIO make_step_io(fkv_ctx* ctx, int layer, int roles, const void* q, co
   io.exch = ctx->words(ctx->lay.exch);
   io.keyx = ctx->words(ctx->lay.keyx);
   if (roles & ROLE_SELECT) io.no = next_launch(ctx, st);      // (the other roles exchange nothing)
-  io.status = ctx->status(layer);
+  io.impatient = ctx->impatient;
   io.P_tagged = &ctx->P_tagged;
   io.tstamp = ctx->tstamp();
   if (ctx->cfg.placement == FKV_PLACE_HOST) {      // a selection comes with its recall plan
@@ -880,6 +881,7 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
     lio.tag = next_launch(ctx, st).tag;
     lio.host_pool = host_pool;
     lio.max_splits = ctx->lay.max_splits;
+    lio.impatient = ctx->impatient;
     lio.lose_selection = ctx->lose_selection;
     lio.launch_grid = &ls.last_grid;
     lio.launch_lds = &ls.last_lds;
@@ -969,6 +971,14 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
 int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on) {
   if (!ctx) return FKV_EINVAL;
   ctx->lose_selection = on != 0;
+  return FKV_OK;
+}
+
+static_assert(WAIT_WEIGHTS == FKV_WAIT_WEIGHTS && WAIT_MAXIMA == FKV_WAIT_MAXIMA && WAIT_SUMS == FKV_WAIT_SUMS && WAIT_KEYS == FKV_WAIT_KEYS, "");
+int fkv_test_impatience(fkv_ctx* ctx, int32_t kinds) {
+  if (!ctx) return FKV_EINVAL;
+  if (kinds & ~FKV_WAIT_ALL) return ctx->fail(FKV_EINVAL, "unknown kind of wait");
+  ctx->impatient = (uint32_t)kinds;
   return FKV_OK;
 }
 

@@ -88,8 +88,6 @@ __device__ __forceinline__ float sum_over_rows(float v) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-constexpr int SELECTION_LOST = -2;      // a page id no list holds: the selection that should have made it gave up a wait
-
 struct AttnArgs {
   PoolDesc pd;
   const uint16_t* q;
@@ -200,7 +198,6 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
       unit_l = resident_unit(pd, page_l);
     }
   }
-  const bool dead = __ballot(page_l == SELECTION_LOST) != 0;   // the list was never made: the outputs are poisoned
   // The token appended at this step: in a fused launch its K/V may not be in the pool yet.  The wave that owns its page
   // takes it from the step's inputs -- it starts from that token instead of from nothing -- and attends the page without it.
   const int new_page = FUSED ? (g.L - 1) / PG : -1, new_tok = (g.L - 1) % PG;
@@ -415,7 +412,6 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
     }
     todo = __ballot(picked && unit_l >= 0);
   }
-  if (!two_phase && dead) lost = true;
   // A wave whose wait ran out has not read its picked pages: make that visible on the data path.
   // NaN in its sum poisons the block's partial and, through the merge, every output row of the
   // KV head's query group.

@@ -211,7 +211,12 @@ __device__ __forceinline__ unsigned long long ld_tag(const unsigned long long* p
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint32_t launch_tag(const LaunchNo& n) { return n.dev ? device_tag((uint32_t)*n.dev) : n.tag; }
-// Polls of a waiting wave before it gives up: about 0.1 s.
+// A wait between blocks of a launch ends by itself only if the block waited for gets to run, and whether it does is not this
+// launch's to decide: other launches may hold the compute units, with waits of their own.  So nothing depends on it: a block
+// whose patience ends makes what it waits for itself, from what was in memory before the launch, bit for bit what the other
+// block would have made, and goes on (and its compute unit is free again soon).
+constexpr int PATIENCE = 1 << 12;       // polls: a few milliseconds (a launch by itself: microseconds)
+// Polls before a wave gives up on values that are its own by then: never, unless a test sees to it.
 constexpr int MAX_POLLS = 1 << 16;
 
 // A barrier that orders the block's LDS accesses and nothing else: global loads stay in flight across it, and no store's

@@ -90,6 +90,9 @@ struct LaunchNo {
 __host__ __device__ inline uint32_t host_tag(uint32_t launch) { return (launch << 1) | 1u; }
 __host__ __device__ inline uint32_t device_tag(uint32_t launch) { return launch << 1; }
 
+// what blocks of a launch wait for, as bits (a test makes waits of these kinds run out at once)
+constexpr uint32_t WAIT_WEIGHTS = 1, WAIT_MAXIMA = 2, WAIT_SUMS = 4, WAIT_KEYS = 8;
+
 // the fused step kernel: roles are OR-ed
 constexpr int ROLE_APPEND = 1, ROLE_CORR = 2, ROLE_SELECT = 4;
 struct StepIO {
@@ -98,7 +101,7 @@ struct StepIO {
   uint8_t* flags; uint8_t* flags_user; double* cosine;                               // correction test
   unsigned long long* P; float* P_plain; float* score; int32_t* ids; int32_t* ids_user;              // selection
   unsigned long long* exch; unsigned long long* keyx;                                // its exchange between blocks
-  LaunchNo no; int* status;
+  LaunchNo no; uint32_t impatient;
   bool* P_tagged;                                                                    // out: whether the launch wrote P or P_plain
   long long* tstamp;                                                                 // debug timestamps or null
   // KV in a host pool (else all null): a launch with ROLE_SELECT also makes the recall plan of the new selection --
@@ -139,6 +142,7 @@ struct LayerIO {
   uint32_t tag;                              // of this launch; 0: number it by what is at consts->launch_no
   bool host_pool;
   int max_splits;
+  uint32_t impatient;                        // WAIT_* bits
   bool lose_selection;                       // test of the bounded wait: attention waits for a tag that never comes
   int* launch_grid; size_t* launch_lds;      // out: shape of the launch that was made
 };

@@ -40,14 +40,14 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) void scan_kernel(StepArgs a) {
     if ((a.roles & ROLE_CORR) && i < a.heads) corr_role<DT, G, SCAN_WAVES>(a, i);
     return;
   }
-  score_role<DT, G, false, SCAN_WAVES>(a, y - a.other_rows, blockIdx.x);
+  score_role<DT, G, SCORE_PLAIN, SCAN_WAVES>(a, y - a.other_rows, blockIdx.x);
 }
 // The selection after it: one block per slice of a head's candidates, a head's slices adjacent.
 template <int G>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
   extern __shared__ uint32_t dyn_lds[];
   touch_args<sizeof(StepArgs)>();
-  select_role<G, false, SEL_REGS_ALONE>(a, (int)blockIdx.x >> a.slices_log2, (int)blockIdx.x & (a.slices - 1), dyn_lds);
+  select_role<0, G, false, SEL_REGS_ALONE>(a, (int)blockIdx.x >> a.slices_log2, (int)blockIdx.x & (a.slices - 1), dyn_lds);
 }
 
 constexpr size_t kLdsPerUnit = 150 * 1024;   // of the 160 KiB of a compute unit
@@ -114,7 +114,7 @@ static void fill_step_args(const Dims& d, int roles, const StepIO& io, Geom g, i
   a.corr_pool = d.corr_pool; a.sel_pool = d.sel_pool;
   a.flags = io.flags; a.flags_user = io.flags_user; a.cosine = io.cosine;
   a.P = io.P; a.score = io.score; a.ids = io.ids; a.ids_user = io.ids_user; a.exch = io.exch; a.keyx = io.keyx;
-  a.no = io.no; a.status = io.status; a.tstamp = io.tstamp;
+  a.no = io.no; a.impatient = io.impatient; a.tstamp = io.tstamp;
   a.passes = passes;
   a.slices = slices;
   rows = 0;
@@ -199,7 +199,7 @@ int launch_step(const Dims& d, int roles, const StepIO& io, Geom g, hipStream_t 
 typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // (scalar loads)
 
 // packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), pages per
-// split (9), lose_selection;   split_magic: 2^32 / splits rounded up, 0 for one split
+// split (9), lose_selection, WAIT_* bits;   split_magic: 2^32 / splits rounded up, 0 for one split
 constexpr int kMaxLayersPacked = 1 << 13, kMaxCtxPacked = 1 << 19;
 
 template <int DT, int G, bool HOSTPOOL>
@@ -243,7 +243,7 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
     a.ids = ids0 + (size_t)now * c->ids_half; a.ids_user = nullptr;
     a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
     a.slice = (g.n_cand + slices - 1) >> slices_log2;
-    a.exch = c->exch; a.keyx = c->keyx; a.no = LaunchNo{tag, nullptr}; a.status = status; a.tstamp = c->tstamp;
+    a.exch = c->exch; a.keyx = c->keyx; a.no = LaunchNo{tag, nullptr}; a.impatient = plan >> 23; a.tstamp = c->tstamp;
     a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
     if (HOSTPOOL) {
@@ -327,7 +327,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   l.grid = dim3(heads, rows);
   l.packed = (uint32_t)(g.L - 1) | (uint32_t)io.layer << 19;
   l.plan = (io.have_prev ? 1u : 0u) | (uint32_t)io.parity << 1 | (uint32_t)passes_log2 << 2 | (uint32_t)slices_log2 << 4 |
-           (uint32_t)n_splits << 7 | (uint32_t)pps << 13 | (io.lose_selection ? 1u << 22 : 0u);
+           (uint32_t)n_splits << 7 | (uint32_t)pps << 13 | (io.lose_selection ? 1u << 22 : 0u) | io.impatient << 23;
   l.split_magic = n_splits > 1 ? 0xffffffffu / (uint32_t)n_splits + 1u : 0u;      // exact for the block counts of a layer launch
   *io.launch_grid = (int)blocks;
   *io.launch_lds = l.lds;

@@ -80,7 +80,7 @@ struct StepArgs {
   unsigned long long* exch;  // [heads][MAX_SLICES][3 * MAX_G] tagged: what a head's selecting blocks tell each other
   unsigned long long* keyx;  // [heads][max_pages] tagged: the candidates' keys, for the head's last selecting block
   LaunchNo no;               // of this launch
-  int* status;               // set to 1 if a wait ran out
+  uint32_t impatient;        // WAIT_* bits: waits that run out at once (tests)
   long long* tstamp;         // debug: 100 MHz timestamps of head 0's phases (may be null)
   unsigned long long* tagged; // if not null: [heads][k], every picked id once more as a tagged word: a block of
                               // this launch that waits for the selection polls the word it needs
@@ -163,25 +163,28 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // for a later launch each pass stores its own, which leaves the waves of a bandwidth-bound scan independent of each other
 // (28.2 us against 30.3 us through LDS for 256 heads x 992 pages).
 // ---------------------------------------------------------------------------------
-template <int DT, int G, bool QMODE, bool TAGGED, int WAVES>
-__device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chunk) {
+constexpr int SCORE_PLAIN = 0, SCORE_TAGGED = 1, SCORE_FOUR = 2;     // (SCORE_FOUR: a wave by itself, 4 pages from `at` on)
+template <int DT, int G, bool QMODE, int HOW, int WAVES>
+__device__ __forceinline__ void score_pages(const StepArgs& a, int head, int at) {
+  constexpr bool TAGGED = HOW == SCORE_TAGGED;
   constexpr int PASS = WAVES * 4;                         // pages per pass
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane >> 4, c8 = lane & 15;
-  const int passes = TAGGED ? a.passes : SCORE_PASSES;    // (the scan always makes as many as there are)
-  const int n = a.g.n_cand, j0 = chunk * PASS * passes + wave * 4 + grp;
-  uint4 wmax[SCORE_PASSES], wmin[SCORE_PASSES];
+  constexpr int MOST = HOW == SCORE_FOUR ? 1 : SCORE_PASSES;
+  const int passes = TAGGED ? a.passes : MOST;            // (the scan always makes as many as there are)
+  const int n = a.g.n_cand, j0 = HOW == SCORE_FOUR ? at + grp : at * PASS * passes + wave * 4 + grp;
+  uint4 wmax[MOST], wmin[MOST];
   const uint16_t* sm = a.summ + summ_idx(0, head, 0, 0, a.max_pages, a.g.cand_lo) + c8 * 8;
   const size_t to_min = (size_t)a.max_pages * D;
 #pragma unroll
-  for (int ps = 0; ps < SCORE_PASSES; ++ps) {
+  for (int ps = 0; ps < MOST; ++ps) {
     if (ps < passes) {
       const int j = min(j0 + ps * PASS, n - 1);
       wmax[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D);
       wmin[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D + to_min);
     }
   }
-  const uint32_t tag = TAGGED ? launch_tag(a.no) : 0u;
+  const uint32_t tag = HOW != SCORE_PLAIN ? launch_tag(a.no) : 0u;
   uint4 wq[G];
 #pragma unroll
   for (int gg = 0; gg < G; ++gg) wq[gg] = *reinterpret_cast<const uint4*>(a.q + ((size_t)head * G + gg) * D + c8 * 8);
@@ -267,28 +270,30 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
       const int j = j0 + i * PASS;
       if (TAGGED) {
         if (c8 < NG) s_w[c8][i * PASS + wave * 4 + grp] = mine[i] * scale;
+      } else if (HOW == SCORE_FOUR) {
+        if (c8 < NG && j < n) st_tag(a.P + ((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j, __float_as_uint(mine[i] * scale), tag);
       } else if (c8 < NG && j < n) {
         reinterpret_cast<float*>(a.P)[((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j] = mine[i] * scale;
       }
     }
   };
   static_assert(SCORE_PASSES == 4, "");
-  if (passes == 1) score(UnrollBy<1>{});
-  else if (passes == 2) score(UnrollBy<2>{});
-  else score(UnrollBy<4>{});
+  if (HOW == SCORE_FOUR || passes == 1) score(UnrollBy<1>{});
+  else if (passes == 2) score(UnrollBy<(MOST >= 2 ? 2 : 1)>{});
+  else score(UnrollBy<MOST>{});
   if (!TAGGED) return;
   lds_barrier();
-  const int pages_log2 = __builtin_ctz(PASS * passes), pages = 1 << pages_log2, at0 = chunk * pages;     // (powers of two)
+  const int pages_log2 = __builtin_ctz(PASS * passes), pages = 1 << pages_log2, at0 = at * pages;     // (powers of two)
   for (int i = threadIdx.x; i < NG * pages; i += WAVES * 64) {
     const int gg = i >> pages_log2, jj = i & (pages - 1);
     if (at0 + jj < n) st_tag(a.P + ((size_t)head * G + gg) * a.max_pages + a.g.cand_lo + at0 + jj, __float_as_uint(s_w[gg][jj]), tag);
   }
 }
 
-template <int DT, int G, bool TAGGED, int WAVES>
-__device__ __forceinline__ void score_role(const StepArgs& a, int head, int chunk) {
-  if (a.sel_pool >= 4) score_pages<DT, G, true, TAGGED, WAVES>(a, head, chunk);
-  else                 score_pages<DT, G, false, TAGGED, WAVES>(a, head, chunk);
+template <int DT, int G, int HOW, int WAVES>
+__device__ __forceinline__ void score_role(const StepArgs& a, int head, int at) {
+  if (a.sel_pool >= 4) score_pages<DT, G, true, HOW, WAVES>(a, head, at);
+  else                 score_pages<DT, G, false, HOW, WAVES>(a, head, at);
 }
 
 // ---------------------------------------------------------------------------------
@@ -367,7 +372,7 @@ __device__ __forceinline__ float pooled_score(const uint32_t* e, const double* z
 // its candidates' G values in registers from the weights to the key; what needs the whole head is exchanged as tagged
 // words: the per-head maxima, the integer softmax sums (exact, so their order does not matter), and the keys, which the
 // last group turns into the top-k.  A head's groups are adjacent in block order and wait for each other and for scoring
-// blocks (lower indices) only.
+// blocks (lower indices) only, and for neither of them for long (PATIENCE).
 //
 // What bounds it: a chain of short phases, each of them instructions of the waves that share a SIMD one after the other
 // (a wave-instruction takes the SIMD 4 cycles): about 26 per softmax numerator, 8 in fp64 per pooled term, and the
@@ -391,7 +396,7 @@ struct alignas(16) SelectLds {
   float mx[SEL_WAVES][MAX_G];
   uint32_t scan[SEL_WAVES];
   uint32_t n_list;
-  int lost;
+  int failed[3][SEL_WAVES];
 };
 
 // The first histogram of the top-k decides nearly everything: for softmax scores its bins are a sixteenth of an octave
@@ -516,10 +521,295 @@ __device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, b
   }
 }
 
-template <int G, bool TAGGED, int REGS = SEL_REGS>
+// The keys of one head's candidates into `key`, and the counts of their bins into sm.hist, by the groups that share the head.
+// A wave whose patience ends has nothing to say, and what it would have had to is never put into words under the tag: its
+// group learns of it at the next barrier and leaves.  Of the groups only the last one has to end with all the keys, and it
+// can make them alone (alone_keys).  Returns whether this wave's keys (the last group: every key) are made.
+template <int G, bool TAGGED, int REGS>
+__device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, int nw, uint32_t* key, SelectLds& sm, uint32_t (&kreg)[REGS]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
+  const int n = a.g.n_cand, lo = a.g.cand_lo;
+  const int S = a.slices, j0 = s * a.slice, j1 = min(n, j0 + a.slice);
+  const bool last = s == S - 1;
+  const uint32_t tag = launch_tag(a.no);
+  const int mode = a.sel_pool;                         // FKV_POOL_*
+  const bool soft = mode <= 1;                         // the variants that pool softmax values
+  const int ng = mode >= 4 ? 1 : G;                    // weights in use per page (pooled query: the group's first)
+  if (last) {
+    for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
+    if (tid == 0) sm.n_list = 0;
+  }
+  // load_and_check() until every lane's words carry the tag; false: patience ended
+  auto poll = [&](uint32_t kind, auto load_and_check) {
+    for (int it = a.impatient & kind ? PATIENCE : 0;; ++it) {
+      const bool there = __ballot(!load_and_check()) == 0;
+      if (it >= PATIENCE) return false;
+      if (there) return true;
+      __builtin_amdgcn_s_sleep(1);
+    }
+  };
+  bool failed = false;                                 // this wave's patience ended
+  auto tell = [&](int at) { if (lane == 0) sm.failed[at][wave] = failed ? 1 : 0; };
+  auto any_failed = [&](int at) { return __ballot(sm.failed[at][min(lane, nw - 1)] != 0) != 0; };
+
+  // ---- this group's weights: thread t has candidates j0 + t + u * nt ----
+  const int U = (j1 - j0 + nt - 1) / nt;               // 1 .. REGS
+  uint32_t e[REGS][G];                             // bits of the weights, then softmax numerators
+  auto ours = [&](int u) { return j0 + tid + u * nt < j1; };
+  // (All of a poll's loads are issued before the first is looked at, and none sits behind a branch of its own: one trip.)
+  auto weights = [&](auto uc) {
+    constexpr int UC = decltype(uc)::value;
+    const size_t base = (size_t)head * G * a.max_pages + lo;
+    size_t at[UC];
+#pragma unroll
+    for (int u = 0; u < UC; ++u) at[u] = base + min(j0 + tid + u * nt, j1 - 1);
+    size_t row[G];
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) row[gg] = (size_t)min(gg, ng - 1) * a.max_pages;
+    if (TAGGED) {
+      failed = !poll(WAIT_WEIGHTS, [&]() {
+        bool ok = true;
+        unsigned long long w[UC][G];
+#pragma unroll
+        for (int u = 0; u < UC; ++u)
+#pragma unroll
+          for (int gg = 0; gg < G; ++gg) w[u][gg] = ld_tag(a.P + at[u] + row[gg]);
+#pragma unroll
+        for (int u = 0; u < UC; ++u)
+#pragma unroll
+          for (int gg = 0; gg < G; ++gg) {
+            e[u][gg] = (uint32_t)w[u][gg];
+            ok = ok & ((uint32_t)(w[u][gg] >> 32) == tag);
+          }
+        return ok;
+      });
+    } else {
+#pragma unroll
+      for (int u = 0; u < UC; ++u)
+#pragma unroll
+        for (int gg = 0; gg < G; ++gg) e[u][gg] = __float_as_uint(reinterpret_cast<const float*>(a.P)[at[u] + row[gg]]);
+    }
+  };
+  if (U == 1) weights(UnrollBy<1>{});
+  else if (REGS == 2 || U == 2) weights(UnrollBy<2>{});
+  else weights(UnrollBy<REGS>{});
+  FKV_STAMP(a, head, 2);
+  if (TAGGED) tell(0);
+
+  // ---- fixed-point softmax: the head's maxima, numerators, integer denominators ----
+  double zd[G], zr[G];
+#pragma unroll
+  for (int gg = 0; gg < G; ++gg) zd[gg] = zr[gg] = 1.0;
+  if (soft) {
+    unsigned long long* const mine = a.exch + ((size_t)head * MAX_SLICES + s) * 3 * MAX_G;
+    const unsigned long long* const all = a.exch + (size_t)head * MAX_SLICES * 3 * MAX_G;
+    const int gl = min(lane & 7, G - 1);               // lane 8r + g works on head g
+    float mx[G];
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      float v = __uint_as_float(e[0][gg]);             // (a thread without a candidate repeats the slice's last one)
+#pragma unroll
+      for (int u = 1; u < REGS; ++u)
+        if (u < U) v = fmaxf(v, __uint_as_float(e[u][gg]));
+      v = wave_max_f32(v);
+      if (lane == 0) sm.mx[wave][gg] = v;
+    }
+    lds_barrier();
+    if (TAGGED && any_failed(0)) return false;
+    float v = -__builtin_inff();
+#pragma unroll
+    for (int w = 0; w < SEL_WAVES; ++w) v = fmaxf(v, sm.mx[min(w, nw - 1)][gl]);
+    if (S > 1) {                                       // ... and over the slices: r is a slice
+      if (wave == 0 && lane < G) st_tag(mine + lane, __float_as_uint(v), tag);
+      const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
+      unsigned long long w0 = 0, w1 = 0;
+      failed = !poll(WAIT_MAXIMA, [&]() {
+        w0 = ld_tag(all + (size_t)r0 * 3 * MAX_G + gl);
+        w1 = ld_tag(all + (size_t)r1 * 3 * MAX_G + gl);
+        return ((uint32_t)(w0 >> 32) == tag) & ((uint32_t)(w1 >> 32) == tag);
+      });
+      v = fmaxf(__uint_as_float((uint32_t)w0), __uint_as_float((uint32_t)w1));
+      v = fmaxf(v, __shfl_xor(v, 8, 64));
+      v = fmaxf(v, __shfl_xor(v, 16, 64));
+      v = fmaxf(v, __shfl_xor(v, 32, 64));
+      tell(1);
+    }
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), gg));
+    FKV_STAMP(a, head, 3);
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      unsigned long long z = 0;
+#pragma unroll
+      for (int u = 0; u < REGS; ++u) {
+        if (u < U) {
+          e[u][gg] = softmax_fixed(__uint_as_float(e[u][gg]), mx[gg]);
+          if (ours(u)) z += e[u][gg];
+        }
+      }
+      z = wave_sum_u48(z);
+      if (lane == 0) sm.z[wave][gg] = z;
+    }
+    lds_barrier();
+    unsigned long long z = 0;
+#pragma unroll
+    for (int w = 0; w < SEL_WAVES; ++w) z += w < nw ? sm.z[w][gl] : 0ull;
+    if (S > 1) {
+      if (any_failed(1)) return false;
+      if (wave == 0 && lane < G) {
+        st_tag(mine + MAX_G + lane, (uint32_t)z, tag);
+        st_tag(mine + 2 * MAX_G + lane, (uint32_t)(z >> 32), tag);
+      }
+      const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
+      unsigned long long w[4];
+      failed = !poll(WAIT_SUMS, [&]() {
+        const unsigned long long* p0 = all + (size_t)r0 * 3 * MAX_G + MAX_G + gl;
+        const unsigned long long* p1 = all + (size_t)r1 * 3 * MAX_G + MAX_G + gl;
+        w[0] = ld_tag(p0); w[1] = ld_tag(p0 + MAX_G); w[2] = ld_tag(p1); w[3] = ld_tag(p1 + MAX_G);
+        return ((uint32_t)(w[0] >> 32) == tag) & ((uint32_t)(w[1] >> 32) == tag) & ((uint32_t)(w[2] >> 32) == tag) & ((uint32_t)(w[3] >> 32) == tag);
+      });
+      z = 0;
+      if ((lane >> 3) < S) z += (w[0] & 0xffffffffull) | (w[1] << 32);
+      if ((lane >> 3) + 8 < S) z += (w[2] & 0xffffffffull) | (w[3] << 32);
+#pragma unroll
+      for (int d = 8; d < 64; d <<= 1) {
+        const uint32_t zl = (uint32_t)__shfl_xor((int)(uint32_t)z, d, 64), zh = (uint32_t)__shfl_xor((int)(uint32_t)(z >> 32), d, 64);
+        z += ((unsigned long long)zh << 32) | zl;
+      }
+    }
+    // one reciprocal per lane, handed to every lane as a scalar
+    const double zv = (double)z, yv = reciprocal_near(zv);
+    const unsigned long long zb = __builtin_bit_cast(unsigned long long, zv), yb = __builtin_bit_cast(unsigned long long, yv);
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      zd[gg] = __builtin_bit_cast(double, ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(zb >> 32), gg) << 32) |
+                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)zb, gg));
+      zr[gg] = __builtin_bit_cast(double, ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(yb >> 32), gg) << 32) |
+                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)yb, gg));
+    }
+  } else {
+    lds_barrier();                                     // the histogram is clear
+    if (TAGGED && any_failed(0)) return false;
+  }
+  FKV_STAMP(a, head, 4);
+
+  // ---- pooled scores -> keys ----
+#pragma unroll
+  for (int u = 0; u < REGS; ++u) {
+    const int j = j0 + tid + u * nt;
+    if (u < U) {
+      kreg[u] = score_key(pooled_score<G>(e[u], zd, zr, mode));
+      if (ours(u)) {
+        if (last) {
+          key[j] = kreg[u];
+          atomicAdd(&sm.hist[topk_bin(kreg[u], soft)], 1u);
+        } else if (!failed) {
+          st_tag(a.keyx + (size_t)head * a.max_pages + j, kreg[u], tag);
+        }
+      }
+    }
+  }
+  if (!last) return !failed;
+  // the other slices' keys (lower block indices)
+  for (int jj = tid; jj - lane < j0 && !failed; jj += 4 * nt) {
+    unsigned long long w[4];
+    failed = !poll(WAIT_KEYS, [&]() {
+      bool ok = true;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[u] = ld_tag(a.keyx + (size_t)head * a.max_pages + min(jj + u * nt, j0 - 1));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) ok = ok & ((uint32_t)(w[u] >> 32) == tag);
+      return ok;
+    });
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (jj + u * nt < j0) {
+        key[jj + u * nt] = (uint32_t)w[u];
+        atomicAdd(&sm.hist[topk_bin((uint32_t)w[u], soft)], 1u);
+      }
+    }
+  }
+  if (S > 1) tell(2);
+  lds_barrier();
+  return S == 1 || !any_failed(2);
+}
+
+// The same by one group alone, which waits for nobody: page weights (TAGGED: made here once more), maxima, sums, keys, in
+// passes over the whole list.  The same numbers, bit for bit; the pooled scores are kept for inspection on the way.
+template <int DT, int G, bool TAGGED>
+__device__ __forceinline__ void alone_keys(const StepArgs& a, int head, int nw, uint32_t* key, SelectLds& sm) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
+  const int n = a.g.n_cand, lo = a.g.cand_lo;
+  const int mode = a.sel_pool, ng = mode >= 4 ? 1 : G;
+  const bool soft = mode <= 1;
+  lds_barrier();                                       // (every wave is done with the LDS of what it did before)
+  for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
+  if (tid == 0) sm.n_list = 0;
+  if (TAGGED) {
+    for (int j = wave * 4; j < n; j += nw * 4) score_role<DT, G, SCORE_FOUR, SEL_WAVES>(a, head, j);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // they are where the group's waves read them
+  }
+  lds_barrier();
+  auto weight = [&](int j, int gg) -> uint32_t {
+    const size_t at = ((size_t)head * G + min(gg, ng - 1)) * a.max_pages + lo + j;
+    return TAGGED ? (uint32_t)ld_tag(a.P + at) : reinterpret_cast<const uint32_t*>(a.P)[at];
+  };
+  double zd[G], zr[G];
+  float mx[G];
+#pragma unroll
+  for (int gg = 0; gg < G; ++gg) { zd[gg] = zr[gg] = 1.0; mx[gg] = -__builtin_inff(); }
+  if (soft) {
+    for (int j = tid; j < n; j += nt)
+#pragma unroll
+      for (int gg = 0; gg < G; ++gg) mx[gg] = fmaxf(mx[gg], __uint_as_float(weight(j, gg)));
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      const float v = wave_max_f32(mx[gg]);
+      if (lane == 0) sm.mx[wave][gg] = v;
+    }
+    lds_barrier();
+    unsigned long long z[G];
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      for (int w = 0; w < nw; ++w) mx[gg] = fmaxf(mx[gg], sm.mx[w][gg]);
+      z[gg] = 0;
+    }
+    for (int j = tid; j < n; j += nt)
+#pragma unroll
+      for (int gg = 0; gg < G; ++gg) z[gg] += softmax_fixed(__uint_as_float(weight(j, gg)), mx[gg]);
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      const unsigned long long v = wave_sum_u48(z[gg]);
+      if (lane == 0) sm.z[wave][gg] = v;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      unsigned long long v = 0;
+      for (int w = 0; w < nw; ++w) v += sm.z[w][gg];
+      zd[gg] = (double)v;
+      zr[gg] = reciprocal_near(zd[gg]);
+    }
+  }
+  for (int j = tid; j < n; j += nt) {
+    uint32_t x[G];
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      x[gg] = weight(j, gg);
+      if (soft) x[gg] = softmax_fixed(__uint_as_float(x[gg]), mx[gg]);
+    }
+    const uint32_t kj = score_key(pooled_score<G>(x, zd, zr, mode));
+    key[j] = kj;
+    atomicAdd(&sm.hist[topk_bin(kj, soft)], 1u);
+    a.score[(size_t)head * a.max_pages + lo + j] = key_score(kj);
+  }
+  lds_barrier();
+}
+
+template <int DT, int G, bool TAGGED, int REGS = SEL_REGS>
 __device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, uint32_t* key) {
   __shared__ SelectLds sm;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff, k = a.k;
   const int S = a.slices;
   const bool last = s == S - 1;
@@ -563,227 +853,26 @@ __device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, 
     plan_and_publish();
     return;
   }
-  const int mode = a.sel_pool;                         // FKV_POOL_*
-  const bool soft = mode <= 1;                         // the variants that pool softmax values
-  const int ng = mode >= 4 ? 1 : G;                    // weights in use per page (pooled query: the group's first)
-  if (last) {
-    for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
-    if (tid == 0) { sm.n_list = 0; sm.lost = 0; }
-  }
-  bool lost = false;                                   // a wait of this wave ran out
-  // load_and_check() again until every lane's words carry the tag
-  auto poll = [&](auto load_and_check) {
-    int it = 0;
-    while (__ballot(!load_and_check()) != 0) {
-      if (++it > MAX_POLLS) { lost = true; break; }
-      __builtin_amdgcn_s_sleep(1);
-    }
-  };
-
-  // ---- this group's weights: thread t has candidates j0 + t + u * nt ----
-  const int U = (j1 - j0 + nt - 1) / nt;               // 1 .. REGS
-  uint32_t e[REGS][G];                             // bits of the weights, then softmax numerators
-  auto ours = [&](int u) { return j0 + tid + u * nt < j1; };
-  // (All of a poll's loads are issued before the first is looked at, and none sits behind a branch of its own: one trip.)
-  auto weights = [&](auto uc) {
-    constexpr int UC = decltype(uc)::value;
-    const size_t base = (size_t)head * G * a.max_pages + lo;
-    size_t at[UC];
-#pragma unroll
-    for (int u = 0; u < UC; ++u) at[u] = base + min(j0 + tid + u * nt, j1 - 1);
-    size_t row[G];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) row[gg] = (size_t)min(gg, ng - 1) * a.max_pages;
-    poll([&]() {
-      bool ok = true;
-      if (TAGGED) {
-        unsigned long long w[UC][G];
-#pragma unroll
-        for (int u = 0; u < UC; ++u)
-#pragma unroll
-          for (int gg = 0; gg < G; ++gg) w[u][gg] = ld_tag(a.P + at[u] + row[gg]);
-#pragma unroll
-        for (int u = 0; u < UC; ++u)
-#pragma unroll
-          for (int gg = 0; gg < G; ++gg) {
-            e[u][gg] = (uint32_t)w[u][gg];
-            ok = ok & ((uint32_t)(w[u][gg] >> 32) == tag);
-          }
-      } else {
-#pragma unroll
-        for (int u = 0; u < UC; ++u)
-#pragma unroll
-          for (int gg = 0; gg < G; ++gg) e[u][gg] = __float_as_uint(reinterpret_cast<const float*>(a.P)[at[u] + row[gg]]);
-      }
-      return ok;
-    });
-  };
-  if (U == 1) weights(UnrollBy<1>{});
-  else if (REGS == 2 || U == 2) weights(UnrollBy<2>{});
-  else weights(UnrollBy<REGS>{});
-  FKV_STAMP(a, head, 2);
-
-  // ---- fixed-point softmax: the head's maxima, numerators, integer denominators ----
-  double zd[G], zr[G];
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) zd[gg] = zr[gg] = 1.0;
-  if (soft) {
-    unsigned long long* const mine = a.exch + ((size_t)head * MAX_SLICES + s) * 3 * MAX_G;
-    const unsigned long long* const all = a.exch + (size_t)head * MAX_SLICES * 3 * MAX_G;
-    const int gl = min(lane & 7, G - 1);               // lane 8r + g works on head g
-    float mx[G];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      float v = __uint_as_float(e[0][gg]);             // (a thread without a candidate repeats the slice's last one)
-#pragma unroll
-      for (int u = 1; u < REGS; ++u)
-        if (u < U) v = fmaxf(v, __uint_as_float(e[u][gg]));
-      v = wave_max_f32(v);
-      if (lane == 0) sm.mx[wave][gg] = v;
-    }
-    lds_barrier();
-    float v = -__builtin_inff();
-#pragma unroll
-    for (int w = 0; w < SEL_WAVES; ++w) v = fmaxf(v, sm.mx[min(w, nw - 1)][gl]);
-    if (S > 1) {                                       // ... and over the slices: r is a slice
-      if (wave == 0 && lane < G) st_tag(mine + lane, __float_as_uint(v), tag);
-      const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
-      unsigned long long w0 = 0, w1 = 0;
-      poll([&]() {
-        w0 = ld_tag(all + (size_t)r0 * 3 * MAX_G + gl);
-        w1 = ld_tag(all + (size_t)r1 * 3 * MAX_G + gl);
-        return ((uint32_t)(w0 >> 32) == tag) & ((uint32_t)(w1 >> 32) == tag);
-      });
-      v = fmaxf(__uint_as_float((uint32_t)w0), __uint_as_float((uint32_t)w1));
-      v = fmaxf(v, __shfl_xor(v, 8, 64));
-      v = fmaxf(v, __shfl_xor(v, 16, 64));
-      v = fmaxf(v, __shfl_xor(v, 32, 64));
-    }
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), gg));
-    FKV_STAMP(a, head, 3);
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      unsigned long long z = 0;
-#pragma unroll
-      for (int u = 0; u < REGS; ++u) {
-        if (u < U) {
-          e[u][gg] = softmax_fixed(__uint_as_float(e[u][gg]), mx[gg]);
-          if (ours(u)) z += e[u][gg];
-        }
-      }
-      z = wave_sum_u48(z);
-      if (lane == 0) sm.z[wave][gg] = z;
-    }
-    lds_barrier();
-    unsigned long long z = 0;
-#pragma unroll
-    for (int w = 0; w < SEL_WAVES; ++w) z += w < nw ? sm.z[w][gl] : 0ull;
-    if (S > 1) {
-      if (wave == 0 && lane < G) {
-        st_tag(mine + MAX_G + lane, (uint32_t)z, tag);
-        st_tag(mine + 2 * MAX_G + lane, (uint32_t)(z >> 32), tag);
-      }
-      const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
-      unsigned long long w[4];
-      poll([&]() {
-        const unsigned long long* p0 = all + (size_t)r0 * 3 * MAX_G + MAX_G + gl;
-        const unsigned long long* p1 = all + (size_t)r1 * 3 * MAX_G + MAX_G + gl;
-        w[0] = ld_tag(p0); w[1] = ld_tag(p0 + MAX_G); w[2] = ld_tag(p1); w[3] = ld_tag(p1 + MAX_G);
-        return ((uint32_t)(w[0] >> 32) == tag) & ((uint32_t)(w[1] >> 32) == tag) & ((uint32_t)(w[2] >> 32) == tag) & ((uint32_t)(w[3] >> 32) == tag);
-      });
-      z = 0;
-      if ((lane >> 3) < S) z += (w[0] & 0xffffffffull) | (w[1] << 32);
-      if ((lane >> 3) + 8 < S) z += (w[2] & 0xffffffffull) | (w[3] << 32);
-#pragma unroll
-      for (int d = 8; d < 64; d <<= 1) {
-        const uint32_t zl = (uint32_t)__shfl_xor((int)(uint32_t)z, d, 64), zh = (uint32_t)__shfl_xor((int)(uint32_t)(z >> 32), d, 64);
-        z += ((unsigned long long)zh << 32) | zl;
-      }
-    }
-    // one reciprocal per lane, handed to every lane as a scalar
-    const double zv = (double)z, yv = reciprocal_near(zv);
-    const unsigned long long zb = __builtin_bit_cast(unsigned long long, zv), yb = __builtin_bit_cast(unsigned long long, yv);
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      zd[gg] = __builtin_bit_cast(double, ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(zb >> 32), gg) << 32) |
-                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)zb, gg));
-      zr[gg] = __builtin_bit_cast(double, ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(yb >> 32), gg) << 32) |
-                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)yb, gg));
-    }
-  } else {
-    lds_barrier();                                     // the histogram is clear
-  }
-  FKV_STAMP(a, head, 4);
-
-  // ---- pooled scores -> keys ----
   uint32_t kreg[REGS];
-#pragma unroll
-  for (int u = 0; u < REGS; ++u) {
-    const int j = j0 + tid + u * nt;
-    if (u < U) {
-      kreg[u] = score_key(pooled_score<G>(e[u], zd, zr, mode));
-      if (ours(u)) {
-        if (last) {
-          key[j] = kreg[u];
-          atomicAdd(&sm.hist[topk_bin(kreg[u], soft)], 1u);
-        } else {
-          st_tag(a.keyx + (size_t)head * a.max_pages + j, kreg[u], tag);
-        }
-      }
-    }
-  }
+  const bool made = shared_keys<G, TAGGED, REGS>(a, head, s, nw, key, sm, kreg);
   auto keep_scores = [&]() {                           // the pooled scores, kept for inspection
 #pragma unroll
-    for (int u = 0; u < REGS; ++u)
-      if (u < U && ours(u)) a.score[(size_t)head * a.max_pages + lo + j0 + tid + u * nt] = key_score(kreg[u]);
+    for (int u = 0; u < REGS; ++u) {
+      const int j = j0 + tid + u * nt;
+      if (j < j1) a.score[(size_t)head * a.max_pages + lo + j] = key_score(kreg[u]);
+    }
   };
   if (!last) {
-    keep_scores();
-    if (lost && lane == 0) *a.status = 1;
+    if (made) keep_scores();
     return;
   }
-  // the other slices' keys (lower block indices)
-  for (int jj = tid; jj < j0; jj += 4 * nt) {
-    unsigned long long w[4];
-    bool ok = false;
-    for (int it = 0; !ok && it <= MAX_POLLS; ++it) {
-      ok = true;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) w[u] = ld_tag(a.keyx + (size_t)head * a.max_pages + min(jj + u * nt, j0 - 1));
-#pragma unroll
-      for (int u = 0; u < 4; ++u) ok = ok & ((uint32_t)(w[u] >> 32) == tag);
-    }
-    lost = lost || !ok;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (jj + u * nt < j0) {
-        key[jj + u * nt] = (uint32_t)w[u];
-        atomicAdd(&sm.hist[topk_bin((uint32_t)w[u], soft)], 1u);
-      }
-    }
-  }
-  // a group that gave up a wait has no selection to offer: nothing is published under the tag (waiting attention waves
-  // give up too) and the list names no page
-  if (lost) sm.lost = 1;
-  lds_barrier();
-  if (sm.lost) {
-    if (tid == 0) {
-      *a.status = 1;
-      if (a.plan_new_slots) a.plan_miss[(size_t)head * (1 + 3 * k)] = 0;
-    }
-    for (int i = tid; i < k; i += nt) {
-      out[i] = SELECTION_LOST;
-      if (outu) outu[i] = -1;
-    }
-    return;
-  }
+  if (__builtin_expect(!made, 0)) alone_keys<DT, G, TAGGED>(a, head, nw, key, sm);
   FKV_STAMP(a, head, 5);
-  block_topk(key, n, kk, soft, nw, sm, [&](int pos, int j) { put_id(pos, lo + j); });
+  block_topk(key, n, kk, a.sel_pool <= 1, nw, sm, [&](int pos, int j) { put_id(pos, lo + j); });
   for (int i = kk + tid; i < k; i += nt) put_id(i, -1);   // padding
   plan_and_publish();
   FKV_STAMP(a, head, 8);
-  keep_scores();
+  if (made) keep_scores();
 }
 
 // ---------------------------------------------------------------------------------
@@ -803,12 +892,12 @@ __device__ __forceinline__ void step_roles(const StepArgs& a, int head, int y, u
   }
   if (y < a.chunks) {
     if (y == 0) FKV_STAMP(a, head, 0);
-    score_role<DT, G, true, STEP_WAVES>(a, head, y);
+    score_role<DT, G, SCORE_TAGGED, STEP_WAVES>(a, head, y);
     if (y == 0) FKV_STAMP(a, head, 1);
     return;
   }
   const int i = (y - a.chunks) * a.heads + head;
-  select_role<G, true>(a, i >> a.slices_log2, i & (a.slices - 1), dyn_lds);
+  select_role<DT, G, true>(a, i >> a.slices_log2, i & (a.slices - 1), dyn_lds);
 }
 
 }  // namespace fkv

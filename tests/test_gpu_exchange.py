@@ -139,3 +139,46 @@ def test_launch_numbers_starting_over():
     _same_as_a_fresh_context(g, x, 4)
     g.health(0)
     g.close()
+
+
+def _everything(g):
+    return {what: g.debug_read(0, what) for what in (B.DBG_ACTIVE_IDS, B.DBG_FLAGS, B.DBG_WEIGHTS, B.DBG_SCORES)}
+
+
+@pytest.mark.parametrize("call,batch,n_q,n_kv,ctx,kw,launches", [
+    (_step, 1, 32, 8, 20000, {}, 1),                                      # one selecting block per head
+    (_step, 1, 16, 2, 40000, {}, 1),                                      # four slices
+    (_step, 1, 7, 1, 290000, {}, 1),                                      # sixteen, the last one short
+    (_step, 1, 16, 2, 40000, dict(select_pooling="MaxQK"), 1),            # no softmax: keys are all that is exchanged
+    (_step, 1, 10, 2, 40000, dict(select_pooling="MeanQ"), 1),
+    (_step, 1, 16, 2, 40000, dict(placement=1), 1),                       # with a recall plan
+    (_step, 64, 32, 4, 2500, {}, 2),                                      # separate launches, scoring and selection in one
+    (_primitives, 1, 16, 2, 40000, {}, None),                             # the same, four slices
+    (_primitives, 4, 4, 4, 170000, {}, None),                             # selection in a launch of its own, two slices
+])
+@pytest.mark.parametrize("kinds", [B.FKV_WAIT_WEIGHTS, B.FKV_WAIT_MAXIMA, B.FKV_WAIT_SUMS,
+                                   B.FKV_WAIT_KEYS, 15])
+def test_a_selecting_block_that_waits_in_vain(call, batch, n_q, n_kv, ctx, kw, launches, kinds):
+    """Every wait of the given kinds inside the selection runs out at once.  No block may hand on what it did not get: ids,
+    scores and outputs are, bit for bit, those of a context whose waits end."""
+    x = _Inputs(31 + ctx, batch, n_q, n_kv, ctx, 3)
+    g, e = x.context(**kw), x.context(**kw)
+    out, ref = x.out(), x.out()
+    g.load_prefix(0, x.K, x.V)
+    e.load_prefix(0, x.K, x.V)
+    g.test_impatience(kinds)
+    for t in range(3):
+        call(g, x.q[t], x.k[t], x.v[t], out)
+        call(e, x.q[t], x.k[t], x.v[t], ref)
+        assert launches is None or g.step_launches(0) == launches
+        got, want = _everything(g), _everything(e)
+        lo, hi = 2, g.context_len(0) // 32 - 2                            # candidate pages
+        for what in got:
+            a, b = (z[what][..., lo:hi] if what in (B.DBG_WEIGHTS, B.DBG_SCORES) else z[what] for z in (got, want))
+            assert np.array_equal(a, b), (t, what)
+        if kw.get("placement"):
+            assert np.array_equal(g.debug_read(0, B.DBG_MISS)[..., 0], e.debug_read(0, B.DBG_MISS)[..., 0])
+        assert torch.equal(out, ref), t
+    g.health(0)
+    g.close()
+    e.close()
