@@ -396,7 +396,8 @@ struct alignas(16) SelectLds {
   float mx[SEL_WAVES][MAX_G];
   uint32_t scan[SEL_WAVES];
   uint32_t n_list;
-  int failed[3][SEL_WAVES];
+  int alone;
+  int failed[SEL_WAVES];
 };
 
 // The first histogram of the top-k decides nearly everything: for softmax scores its bins are a sixteenth of an octave
@@ -523,7 +524,7 @@ __device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, b
 
 // The keys of one head's candidates into `key`, and the counts of their bins into sm.hist, by the groups that share the head.
 // A wave whose patience ends has nothing to say, and what it would have had to is never put into words under the tag: its
-// group learns of it at the next barrier and leaves.  Of the groups only the last one has to end with all the keys, and it
+// group learns of it at the next barrier, from a value no maximum or sum has, and leaves.  Of the groups only the last one has to end with all the keys, and it
 // can make them alone (alone_keys).  Returns whether this wave's keys (the last group: every key) are made.
 template <int G, bool TAGGED, int REGS>
 __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, int nw, uint32_t* key, SelectLds& sm, uint32_t (&kreg)[REGS]) {
@@ -537,20 +538,23 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
   const int ng = mode >= 4 ? 1 : G;                    // weights in use per page (pooled query: the group's first)
   if (last) {
     for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
-    if (tid == 0) sm.n_list = 0;
+    if (tid == 0) { sm.n_list = 0; sm.alone = 0; }
   }
   // load_and_check() until every lane's words carry the tag; false: patience ended
   auto poll = [&](uint32_t kind, auto load_and_check) {
-    for (int it = a.impatient & kind ? PATIENCE : 0;; ++it) {
-      const bool there = __ballot(!load_and_check()) == 0;
-      if (it >= PATIENCE) return false;
-      if (there) return true;
+    int it = 0;
+    while (__ballot(!load_and_check()) != 0) {
+      if (++it > PATIENCE) return false;
       __builtin_amdgcn_s_sleep(1);
     }
+    return (a.impatient & kind) == 0;
   };
   bool failed = false;                                 // this wave's patience ended
-  auto tell = [&](int at) { if (lane == 0) sm.failed[at][wave] = failed ? 1 : 0; };
-  auto any_failed = [&](int at) { return __ballot(sm.failed[at][min(lane, nw - 1)] != 0) != 0; };
+  auto any_failed = [&]() {                            // (by way of a barrier)
+    if (lane == 0) sm.failed[wave] = failed ? 1 : 0;
+    lds_barrier();
+    return __ballot(sm.failed[min(lane, nw - 1)] != 0) != 0;
+  };
 
   // ---- this group's weights: thread t has candidates j0 + t + u * nt ----
   const int U = (j1 - j0 + nt - 1) / nt;               // 1 .. REGS
@@ -594,7 +598,6 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
   else if (REGS == 2 || U == 2) weights(UnrollBy<2>{});
   else weights(UnrollBy<REGS>{});
   FKV_STAMP(a, head, 2);
-  if (TAGGED) tell(0);
 
   // ---- fixed-point softmax: the head's maxima, numerators, integer denominators ----
   double zd[G], zr[G];
@@ -612,13 +615,14 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
       for (int u = 1; u < REGS; ++u)
         if (u < U) v = fmaxf(v, __uint_as_float(e[u][gg]));
       v = wave_max_f32(v);
+      if (TAGGED && failed) v = __builtin_inff();
       if (lane == 0) sm.mx[wave][gg] = v;
     }
     lds_barrier();
-    if (TAGGED && any_failed(0)) return false;
     float v = -__builtin_inff();
 #pragma unroll
     for (int w = 0; w < SEL_WAVES; ++w) v = fmaxf(v, sm.mx[min(w, nw - 1)][gl]);
+    if (TAGGED && __ballot(v == __builtin_inff()) != 0 && any_failed()) return false;    // (a weight may be infinite)
     if (S > 1) {                                       // ... and over the slices: r is a slice
       if (wave == 0 && lane < G) st_tag(mine + lane, __float_as_uint(v), tag);
       const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
@@ -632,7 +636,6 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
       v = fmaxf(v, __shfl_xor(v, 8, 64));
       v = fmaxf(v, __shfl_xor(v, 16, 64));
       v = fmaxf(v, __shfl_xor(v, 32, 64));
-      tell(1);
     }
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), gg));
@@ -648,6 +651,7 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
         }
       }
       z = wave_sum_u48(z);
+      if (failed) z = 1ull << 56;                      // (sums are below 2^46)
       if (lane == 0) sm.z[wave][gg] = z;
     }
     lds_barrier();
@@ -655,7 +659,7 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
 #pragma unroll
     for (int w = 0; w < SEL_WAVES; ++w) z += w < nw ? sm.z[w][gl] : 0ull;
     if (S > 1) {
-      if (any_failed(1)) return false;
+      if (__ballot(z >> 56 != 0) != 0) return false;
       if (wave == 0 && lane < G) {
         st_tag(mine + MAX_G + lane, (uint32_t)z, tag);
         st_tag(mine + 2 * MAX_G + lane, (uint32_t)(z >> 32), tag);
@@ -688,8 +692,7 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
                                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)yb, gg));
     }
   } else {
-    lds_barrier();                                     // the histogram is clear
-    if (TAGGED && any_failed(0)) return false;
+    if (any_failed()) return false;                    // (and behind its barrier the histogram is clear)
   }
   FKV_STAMP(a, head, 4);
 
@@ -729,9 +732,9 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
       }
     }
   }
-  if (S > 1) tell(2);
+  if (failed) sm.alone = 1;
   lds_barrier();
-  return S == 1 || !any_failed(2);
+  return S == 1 || sm.alone == 0;
 }
 
 // The same by one group alone, which waits for nobody: page weights (TAGGED: made here once more), maxima, sums, keys, in
