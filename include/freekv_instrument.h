@@ -55,7 +55,9 @@ int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on);
 #define FKV_WAIT_MAXIMA   2  /* a slice's, for the other slices' maxima                                   */
 #define FKV_WAIT_SUMS     4  /*                ... softmax sums                                           */
 #define FKV_WAIT_KEYS     8  /* the last slice's, for the other slices' keys                              */
-#define FKV_WAIT_ALL     15
+#define FKV_WAIT_SPLITS  16  /* attention's, for the sums of a head's other blocks                        */
+#define FKV_WAIT_IDS     32  /* attention's of a corrected head, for the page ids picked in the launch    */
+#define FKV_WAIT_ALL     63
 int fkv_test_impatience(fkv_ctx* ctx, int32_t kinds);
 
 /* Test hook for the numbers that tell one launch's exchanged values from another's (31 bits, one per launch): the

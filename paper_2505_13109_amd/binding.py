@@ -16,7 +16,7 @@ FKV_PLACE_HBM, FKV_PLACE_HOST = 0, 1
 FKV_USE_ACTIVE, FKV_USE_PENDING, FKV_USE_BY_FLAG = 0, 1, 2
 FKV_HEADS_ALL, FKV_HEADS_FLAGGED, FKV_HEADS_UNFLAGGED = 0, 1, 2
 FKV_RECALL_GATHER, FKV_RECALL_MEMCPY = 0, 1
-FKV_WAIT_WEIGHTS, FKV_WAIT_MAXIMA, FKV_WAIT_SUMS, FKV_WAIT_KEYS = 1, 2, 4, 8
+FKV_WAIT_WEIGHTS, FKV_WAIT_MAXIMA, FKV_WAIT_SUMS, FKV_WAIT_KEYS, FKV_WAIT_SPLITS, FKV_WAIT_IDS = 1, 2, 4, 8, 16, 32
 DBG_SUMMARIES, DBG_WEIGHTS, DBG_SCORES, DBG_ACTIVE_IDS, DBG_PENDING_IDS, DBG_FLAGS, DBG_MISS, DBG_COSINE, DBG_TSTAMP = range(9)
 
 EXPORTED_SYMBOLS = (

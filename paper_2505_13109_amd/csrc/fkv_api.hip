@@ -331,6 +331,7 @@ static AttnIO make_attn_io(fkv_ctx* ctx, int layer, const void* q, float* out, i
   io.part_ml = ctx->words(ctx->lay.part_ml);
   io.max_splits = ctx->lay.max_splits;
   io.no = no;
+  io.impatient = ctx->impatient;
   io.status = ctx->status(layer);
   io.out = out;
   io.tstamp = ctx->tstamp();
@@ -974,7 +975,8 @@ int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on) {
   return FKV_OK;
 }
 
-static_assert(WAIT_WEIGHTS == FKV_WAIT_WEIGHTS && WAIT_MAXIMA == FKV_WAIT_MAXIMA && WAIT_SUMS == FKV_WAIT_SUMS && WAIT_KEYS == FKV_WAIT_KEYS, "");
+static_assert(WAIT_WEIGHTS == FKV_WAIT_WEIGHTS && WAIT_MAXIMA == FKV_WAIT_MAXIMA && WAIT_SUMS == FKV_WAIT_SUMS && WAIT_KEYS == FKV_WAIT_KEYS &&
+              WAIT_SPLITS == FKV_WAIT_SPLITS && WAIT_IDS == FKV_WAIT_IDS, "");
 int fkv_test_impatience(fkv_ctx* ctx, int32_t kinds) {
   if (!ctx) return FKV_EINVAL;
   if (kinds & ~FKV_WAIT_ALL) return ctx->fail(FKV_EINVAL, "unknown kind of wait");

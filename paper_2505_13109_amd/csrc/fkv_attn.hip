@@ -10,7 +10,9 @@ template <int DT, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void attn_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) float attn_lds[];
   touch_args<sizeof(AttnArgs)>();
-  attn_block<DT, NW, false, false>(a, blockIdx.x, blockIdx.y, attn_lds);
+  const AttnLeft left = attn_block<DT, NW, false, false>(a, blockIdx.x, blockIdx.y, attn_lds);
+  if (__builtin_expect(left.any(), 0))
+    attn_finish<DT, NW, false, false>(args_from_memory<AttnArgs>(), blockIdx.x, blockIdx.y, left);
 }
 
 // experiment builds only (see knob()): pages per block (0 = choose from the shape)
@@ -47,7 +49,7 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   AttnArgs a{};
   a.pd = pd; a.q = io.q; a.act_ids = io.act_ids; a.new_ids = io.new_ids; a.act_slots = io.act_slots; a.new_slots = io.new_slots;
   a.flags = io.flags; a.use = io.use; a.part = io.part; a.part_ml = io.part_ml; a.max_splits = io.max_splits;
-  a.no = io.no;
+  a.no = io.no; a.impatient = io.impatient;
   a.pps = attn_pages_per_block(n_att, heads, io.max_splits, 4);
   a.n_splits = (n_att + a.pps - 1) / a.pps;
   a.share = (d.G * D + a.n_splits - 1) / a.n_splits;

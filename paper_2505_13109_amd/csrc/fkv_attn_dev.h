@@ -16,6 +16,9 @@
 // So every step is entered as early as what it depends on allows: a wave looks up all its positions' ids with one load
 // and requests its first page before the correction test is made; the block combines its waves behind one barrier; and
 // the partial results are exchanged as tagged words (st_tag), one trip instead of store, counter and read.
+//
+// What a block waits for -- its head's picked ids, the sums of the head's other blocks -- comes from blocks that may not be
+// running yet, and another launch may keep them from it; so a block whose patience ends makes it itself (attn_finish).
 #pragma once
 #include "fkv_device.h"
 
@@ -118,6 +121,7 @@ struct AttnArgs {
   const unsigned long long* tagged;   // [heads][k]: this step's picked ids, tagged, written by the selection
   uint32_t tag;              // fused: tag of this launch
   uint32_t pick_tag;         // tag the picked ids are waited for with: the same (a test of the bounded wait asks for another)
+  uint32_t impatient;        // WAIT_* bits: waits that run out at once (tests)
   // fused, KV in a host pool: the tagged words are tagged_pick() values; a corrected head's wave copies a missing page
   // from the host pool into its slot while it attends over it
   const uint16_t* host_pool; // [heads][max_pages] units
@@ -149,26 +153,103 @@ __device__ __forceinline__ int attend_unit(const AttendList& al, const PoolDesc&
 // floats of LDS that a block of NW waves needs
 __host__ __device__ constexpr int attn_lds_floats(int NW, int G) { return NW * G * (D + 4) + NW * 32 + G * (D / 2 + 4); }
 
+// One output (query head gg, channel c) by one thread, over the whole attend list in fp32: for outputs whose block waited for
+// the others in vain.  Slow (about 10 ms for 65 pages), but it needs nobody.  corrected: the picked ids are this launch's;
+// should they not be there (a test sees to that; a block makes them before it comes here), the output is NaN.
+template <int DT, bool FUSED, bool HOSTFUSED>
+__device__ __forceinline__ float output_alone(const AttnArgs& a, int head, bool corrected, int gg, int c) {
+  const PoolDesc& pd = a.pd;
+  const Geom& g = a.g;
+  const float sl2 = 0.08838834764831845f * 1.4426950408889634f;
+  const int k = a.k, n_att = g.n_sink + k + g.n_win + (g.r > 0 ? 1 : 0);
+  const int new_page = FUSED ? (g.L - 1) / PG : -1, new_tok = (g.L - 1) % PG;
+  const uint16_t* const q = a.q + ((size_t)head * a.G + gg) * D;
+  const bool pending = !FUSED && (a.use == 1 || (a.use == 2 && a.flags[head] != 0));
+  float M = -__builtin_inff(), den = 0.0f, o = 0.0f;
+#pragma unroll 1
+  for (int p = 0; p < n_att; ++p) {
+    const int i = p - g.n_sink;                           // position in the picked list
+    int page, unit;
+    const uint16_t* up = pd.pool;
+    bool from_host = false;
+    if (i >= 0 && i < k) {
+      int slot = 0;
+      if (FUSED && corrected) {
+        unsigned long long w;
+        int it = 0;
+        while ((uint32_t)((w = ld_tag(a.tagged + (size_t)head * k + i)) >> 32) != a.pick_tag) {
+          if (++it > MAX_POLLS) { *a.status = 1; return __builtin_nanf(""); }
+          __builtin_amdgcn_s_sleep(2);
+        }
+        if constexpr (HOSTFUSED) tagged_unpick((uint32_t)w, page, slot, from_host);
+        else page = (int)(uint32_t)w;
+      } else {
+        page = (pending ? a.new_ids : a.act_ids)[(size_t)head * k + i];
+        if (pd.placement != 0) slot = (pending ? a.new_slots : a.act_slots)[(size_t)head * k + i];
+      }
+      if (page < 0) continue;
+      unit = pd.placement == 0 ? page : pd.sel_base + slot;
+    } else {
+      page = i < 0 ? p : g.n_full - g.n_win + (i - k);
+      unit = resident_unit(pd, page);
+    }
+    if (HOSTFUSED && from_host) up = a.host_pool + ((size_t)head * a.max_pages + page) * UNIT_ELEMS;
+    else up += ((size_t)head * pd.units_per_head + unit) * UNIT_ELEMS;
+    const bool has_new = FUSED && page == new_page;      // (its last token comes from the step's inputs)
+    const int n_tok = has_new ? new_tok + 1 : page == g.n_full ? g.r : PG;
+#pragma unroll 1
+    for (int t = 0; t < n_tok; ++t) {
+      const bool is_new = has_new && t == new_tok;
+      float dot = 0.0f;
+#pragma unroll 1
+      for (int c8 = 0; c8 < D; c8 += 8) {
+        const uint16_t* kp = is_new ? a.k_new + (size_t)head * D + c8 : up + k_elem_off(t, c8);
+        float kf[8], qf[8];
+        unpack8<DT>(*reinterpret_cast<const uint4*>(kp), kf);
+        unpack8<DT>(*reinterpret_cast<const uint4*>(q + c8), qf);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dot = __builtin_fmaf(kf[e], qf[e], dot);
+      }
+      const float s = dot * sl2, v = Unpack<DT>::one(is_new ? a.v_new[(size_t)head * D + c] : up[v_elem_off(t, c)]);
+      const float m_new = fmaxf(M, s), alpha = m_new == M ? 1.0f : fast_exp2(M - m_new), w = fast_exp2(s - m_new);
+      den = den * alpha + w;
+      o = o * alpha + w * v;
+      M = m_new;
+    }
+  }
+  if (HOSTFUSED && __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return __builtin_nanf("");
+  return o / den;
+}
+
 // One block of NW wavefronts: attend-list positions [split*pps, (split+1)*pps) of `head`,
 // wave w takes w, w+NW, ...  `lds`: attn_lds_floats(NW, G) floats, 16-byte aligned.
 // FUSED: in a launch with the step roles; HOSTFUSED: that, with the KV in a host pool (compile-time choices: what they
 // add to the page loop would cost the other launches registers).
+// Returns what it waited for in vain and left to attn_finish.
+struct AttnLeft {
+  bool ids;                  // the head's picked ids (the same in every thread of the block); before that, the block makes them
+  bool split;                // ... and so, of its own split, nothing is done
+  bool corrected;            // the head's picked ids are this launch's
+  uint32_t outputs;          // bit t: the thread's t-th output
+  __device__ __forceinline__ bool any() const { return ids || __ballot(outputs != 0) != 0; }
+};
 template <int DT, int NW, bool FUSED, bool HOSTFUSED>
-__device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int head, float* lds) {
+__device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int head, float* lds) {
   typedef typename Mma<DT>::vec vec;
   static_assert(!FUSED || NW >= MAX_G, "the correction test takes a wave per query head");
   const PoolDesc& pd = a.pd;
   const Geom& g = a.g;
   const int G = a.G, k = a.k;
-#define FKV_ASTAMP(i) do { if (a.tstamp && head == 0 && threadIdx.x == 0) a.tstamp[i] = wall_clock64(); } while (0)
-  if (split == 0) FKV_ASTAMP(16);
+#define FKV_ASTAMP(i) do { if (a.tstamp && head == 0 && thread_id(wave) == 0) a.tstamp[i] = wall_clock64(); } while (0)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (split == 0) FKV_ASTAMP(16);
   const int gq = lane & 15, rb = lane >> 4;
   float* sm_o = lds;                                    // [NW][G][D + 4]
   float* sm_ml = lds + NW * G * (D + 4);                // [NW][16][2]
   uint32_t* sm_q = reinterpret_cast<uint32_t*>(sm_ml + NW * 32);        // [G][D / 2 + 4] pairs
   __shared__ double s_cos[MAX_G];
   __shared__ float s_near[MAX_G];
+  __shared__ int s_no_ids;
 
   // the group's queries, for the correction test and (by way of LDS: registers are what this block is short of) as the
   // Q^T operand
@@ -309,13 +390,14 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
     if (next >= 0) load_v(up_next);
   };
 
-  bool lost = false;                                    // something waited for did not come: the outputs are poisoned
+  bool lost = false;
   bool two_phase = false;
   // the first page's loads, for the case that the head is not corrected
   const unsigned long long listed = __ballot(unit_l >= 0);
   const int i0 = listed ? (int)__builtin_ctzll(listed) : -1;
   const char* const up0 = source(i0 >= 0 ? i0 : 0);
   if (i0 >= 0) load_k(up0);
+  if (FUSED && wave == 0) s_no_ids = 0;
 #pragma unroll
   for (int u = 0; u * NW < MAX_G; ++u)
     if (wave + u * NW < G) sm_q[(wave + u * NW) * (D / 2 + 4) + lane] = cq[u];
@@ -381,19 +463,19 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
     loaded = false;
     if (todo == 0) break;
     // Wait for this step's ids of the positions: the selection writes every picked id as one tagged 64-bit word.
-    // The blocks that make it have lower block indices than any attention block and wait for nothing that has a
-    // higher one, so they are running or done; the wait is bounded all the same.
-    const unsigned long long* word = a.tagged + (size_t)head * k + (picked ? p - pk_lo : 0);
+    // The blocks that make it have lower block indices than any attention block, so that as a rule they are running or
+    // done.
+    const int at = split * a.pps + wave + (thread_id(wave) & 63) * NW - pk_lo;
+    const unsigned long long* word = a.tagged + (size_t)head * k + (picked ? at : 0);
     unsigned long long w = 0;
-    int it = 0;
-    for (;;) {
+    for (int it = 0;; ++it) {
       w = ld_tag(word);
-      if (__ballot(picked && (uint32_t)(w >> 32) != a.pick_tag) == 0 || ++it > MAX_POLLS) break;
+      if (__ballot(picked && (uint32_t)(w >> 32) != a.pick_tag) == 0) break;
+      if (it > PATIENCE) { lost = true; break; }
       __builtin_amdgcn_s_sleep(2);
     }
-    if (it > MAX_POLLS) {                             // the ids are not there: read nothing
-      lost = true;
-      if (lane == 0) *a.status = 1;
+    if (lost || a.impatient & WAIT_IDS) {
+      if (lane == 0) s_no_ids = 1;
       break;
     }
     if (picked) {
@@ -412,10 +494,6 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
     }
     todo = __ballot(picked && unit_l >= 0);
   }
-  // A wave whose wait ran out has not read its picked pages: make that visible on the data path.
-  // NaN in its sum poisons the block's partial and, through the merge, every output row of the
-  // KV head's query group.
-  if (lost) l_run = __builtin_nanf("");
   if constexpr (HOSTFUSED) {
     // With the KV in a host pool the wave that gives up also leaves the page-cache slot it was to fill unfilled, while
     // the recall plan lists the page as cached: the layer's state cannot be trusted from then on.  Every later step of
@@ -426,11 +504,12 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
 
   // ---- combine the waves: one barrier ----
   l_run = sum_over_rows(l_run);                         // per-wave totals of l over the 4 row blocks
-  if (gq < G) {
-    float* o = sm_o + ((size_t)wave * G + gq) * (D + 4);
+  const int tid = thread_id(wave);
+  if ((tid & 15) < G) {
+    float* o = sm_o + ((size_t)wave * G + (tid & 15)) * (D + 4) + (tid >> 4 & 3) * 4;
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) *reinterpret_cast<f32x4*>(o + cb * 16 + rb * 4) = acc[cb];
-    if (rb == 0) *reinterpret_cast<float2*>(sm_ml + (wave * 16 + gq) * 2) = make_float2(m_run, l_run);
+    for (int cb = 0; cb < 8; ++cb) *reinterpret_cast<f32x4*>(o + cb * 16) = acc[cb];
+    if ((tid & 63) < 16) *reinterpret_cast<float2*>(sm_ml + (wave * 16 + (tid & 15)) * 2) = make_float2(m_run, l_run);
   }
   const uint32_t tag = FUSED ? a.tag : a.no.dev ? device_tag((uint32_t)__builtin_amdgcn_readfirstlane(number)) : a.no.tag;
   lds_barrier();
@@ -445,92 +524,131 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int split, int hea
   unsigned long long* const pml = a.part_ml + (size_t)head * a.max_splits * G * 2;
   constexpr int IT = (MAX_G * D + NW * 64 - 1) / (NW * 64);
   float o[IT], den[IT], M[IT];
+  uint32_t left = 0;                                    // bit t: item t's output is left to be made alone
+  const bool no_ids = FUSED && __builtin_amdgcn_readfirstlane(s_no_ids) != 0;
+  if (!no_ids) {
 #pragma unroll
-  for (int t = 0; t < IT; ++t) {
-    const int idx = threadIdx.x + t * NW * 64;
-    if (idx >= items) continue;
-    const int gg = idx / D, c = idx % D;
-    float m[NW], l[NW], v[NW];
-    float Mt = -__builtin_inff();
+    for (int t = 0; t < IT; ++t) {
+      const int idx = tid + t * NW * 64;
+      if (idx >= items) continue;
+      const int gg = idx / D, c = idx % D;
+      float m[NW], l[NW], v[NW];
+      float Mt = -__builtin_inff();
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float2 ml = *reinterpret_cast<const float2*>(sm_ml + (w * 16 + gg) * 2);
-      m[w] = ml.x;
-      l[w] = ml.y;
-      v[w] = sm_o[((size_t)w * G + gg) * (D + 4) + c];
-      Mt = fmaxf(Mt, m[w]);
-    }
-    float ot = 0.0f, dt = 0.0f;
+      for (int w = 0; w < NW; ++w) {
+        const float2 ml = *reinterpret_cast<const float2*>(sm_ml + (w * 16 + gg) * 2);
+        m[w] = ml.x;
+        l[w] = ml.y;
+        v[w] = sm_o[((size_t)w * G + gg) * (D + 4) + c];
+        Mt = fmaxf(Mt, m[w]);
+      }
+      float ot = 0.0f, dt = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      // a wave that saw no page has m = -inf and zero sums (or a poisoned one)
-      const float wgt = m[w] == -__builtin_inff() ? 0.0f : fast_exp2(m[w] - Mt);
-      ot += v[w] * wgt;
-      dt += m[w] == -__builtin_inff() ? l[w] : l[w] * wgt;
-    }
-    o[t] = ot; den[t] = dt; M[t] = Mt;
-    if (n_splits > 1) {
-      if (idx < own_lo || idx >= own_hi) st_tag(po + (size_t)split * items + idx, __float_as_uint(ot), tag);
-      if (c == 0) {
-        st_tag(pml + (split * G + gg) * 2, __float_as_uint(Mt), tag);
-        st_tag(pml + (split * G + gg) * 2 + 1, __float_as_uint(dt), tag);
+      for (int w = 0; w < NW; ++w) {
+        // a wave that saw no page has m = -inf and zero sums (or a poisoned one)
+        const float wgt = m[w] == -__builtin_inff() ? 0.0f : fast_exp2(m[w] - Mt);
+        ot += v[w] * wgt;
+        dt += m[w] == -__builtin_inff() ? l[w] : l[w] * wgt;
+      }
+      o[t] = ot; den[t] = dt; M[t] = Mt;
+      if (n_splits > 1) {
+        if (idx < own_lo || idx >= own_hi) st_tag(po + (size_t)split * items + idx, __float_as_uint(ot), tag);
+        if (c == 0) {
+          st_tag(pml + (split * G + gg) * 2, __float_as_uint(Mt), tag);
+          st_tag(pml + (split * G + gg) * 2 + 1, __float_as_uint(dt), tag);
+        }
       }
     }
-  }
-  if (split == 0) FKV_ASTAMP(18);
+    if (split == 0) FKV_ASTAMP(18);
 #pragma unroll
-  for (int t = 0; t < IT; ++t) {
-    const int idx = threadIdx.x + t * NW * 64;
-    if (idx < own_lo || idx >= own_hi) continue;
-    const int gg = idx / D;
-    constexpr int CH = 8;
-    // (the others' splits, numbered from 0: the block's own is left out)
-    for (int s0 = 0; s0 < n_splits - 1; s0 += CH) {
-      unsigned long long wm[CH], wl[CH], wo[CH];
-      int it = 0;
-      for (;;) {
-        bool there = true;
+    for (int t = 0; t < IT; ++t) {
+      const int idx = tid + t * NW * 64;
+      if (idx < own_lo || idx >= own_hi) continue;
+      const int gg = idx / D;
+      constexpr int CH = 8;
+      // (the others' splits, numbered from 0: the block's own is left out)
+      for (int s0 = 0; s0 < n_splits - 1; s0 += CH) {
+        unsigned long long wm[CH], wl[CH], wo[CH];
+        bool late = (a.impatient & WAIT_SPLITS) != 0;
+        for (int it = 0; !late;) {
+          bool there = true;
+#pragma unroll
+          for (int u = 0; u < CH; ++u) {
+            int sp = min(s0 + u, n_splits - 2);
+            sp += sp >= split ? 1 : 0;
+            wo[u] = ld_tag(po + (size_t)sp * items + idx);
+            wm[u] = ld_tag(pml + (sp * G + gg) * 2);
+            wl[u] = ld_tag(pml + (sp * G + gg) * 2 + 1);
+          }
+#pragma unroll
+          for (int u = 0; u < CH; ++u)
+            there = there & ((uint32_t)(wo[u] >> 32) == tag) & ((uint32_t)(wm[u] >> 32) == tag) & ((uint32_t)(wl[u] >> 32) == tag);
+          if (there) break;
+          late = ++it > PATIENCE;
+          __builtin_amdgcn_s_sleep(1);
+        }
+        if (late) { left |= 1u << t; break; }
+        float Mc = M[t];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) Mc = fmaxf(Mc, __uint_as_float((uint32_t)wm[u]));
+        const bool none = M[t] == -__builtin_inff();
+        const float resc = none ? 0.0f : fast_exp2(M[t] - Mc);
+        den[t] = none ? den[t] : den[t] * resc;
+        o[t] *= resc;
+        M[t] = Mc;
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-          int sp = min(s0 + u, n_splits - 2);
-          sp += sp >= split ? 1 : 0;
-          wo[u] = ld_tag(po + (size_t)sp * items + idx);
-          wm[u] = ld_tag(pml + (sp * G + gg) * 2);
-          wl[u] = ld_tag(pml + (sp * G + gg) * 2 + 1);
-        }
-#pragma unroll
-        for (int u = 0; u < CH; ++u)
-          there = there & ((uint32_t)(wo[u] >> 32) == tag) & ((uint32_t)(wm[u] >> 32) == tag) & ((uint32_t)(wl[u] >> 32) == tag);
-        if (there) break;
-        if (++it > MAX_POLLS) {
-          *a.status = 1;
-          den[t] = __builtin_nanf("");
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-      float Mc = M[t];
-#pragma unroll
-      for (int u = 0; u < CH; ++u) Mc = fmaxf(Mc, __uint_as_float((uint32_t)wm[u]));
-      const bool none = M[t] == -__builtin_inff();
-      const float resc = none ? 0.0f : fast_exp2(M[t] - Mc);
-      den[t] = none ? den[t] : den[t] * resc;
-      o[t] *= resc;
-      M[t] = Mc;
-#pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        if (s0 + u < n_splits - 1) {
-          const float mu = __uint_as_float((uint32_t)wm[u]), lu = __uint_as_float((uint32_t)wl[u]);
-          const float w = mu == -__builtin_inff() ? 0.0f : fast_exp2(mu - Mc);
-          den[t] += mu == -__builtin_inff() ? lu : w * lu;
-          o[t] += w * __uint_as_float((uint32_t)wo[u]);
+          if (s0 + u < n_splits - 1) {
+            const float mu = __uint_as_float((uint32_t)wm[u]), lu = __uint_as_float((uint32_t)wl[u]);
+            const float w = mu == -__builtin_inff() ? 0.0f : fast_exp2(mu - Mc);
+            den[t] += mu == -__builtin_inff() ? lu : w * lu;
+            o[t] += w * __uint_as_float((uint32_t)wo[u]);
+          }
         }
       }
+      if (!(left >> t & 1u)) a.out[(size_t)head * items + idx] = o[t] / den[t];
     }
-    a.out[(size_t)head * items + idx] = o[t] / den[t];
   }
   if (split == 0) FKV_ASTAMP(21);
+  bool need_ids = no_ids;
+  if (FUSED && two_phase && n_splits > 1) {             // (outputs that were left need ids that may not be there)
+    if (left) s_no_ids = 1;
+    lds_barrier();
+    need_ids = __builtin_amdgcn_readfirstlane(s_no_ids) != 0;
+  }
+  return AttnLeft{need_ids, no_ids, two_phase, no_ids ? ~0u : left};
 #undef FKV_ASTAMP
+}
+
+// What a block left, without waiting for anyone.  If left.ids, the block has made the head's selection by now, into memory
+// and into the tagged words.
+template <int DT, int NW, bool FUSED, bool HOSTFUSED>
+__device__ __forceinline__ void attn_finish(const AttnArgs& a, int split, int head, AttnLeft left) {
+  if (FUSED && left.ids) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (each wave's words are where the others read them)
+    lds_barrier();
+  }
+  if (HOSTFUSED && left.split) {                        // the recall of the block's missing pages, as in attend_page
+    const int lo = a.g.n_sink, hi = min(lo + a.k, (split + 1) * a.pps);
+#pragma unroll 1
+    for (int p = max(split * a.pps, lo); p < hi; ++p) {
+      const unsigned long long w = ld_tag(a.tagged + (size_t)head * a.k + p - lo);
+      int page, slot;
+      bool miss;
+      tagged_unpick((uint32_t)w, page, slot, miss);
+      if ((uint32_t)(w >> 32) != a.pick_tag || page < 0 || !miss) continue;
+      const u32x4* from = reinterpret_cast<const u32x4*>(a.host_pool + ((size_t)head * a.max_pages + page) * UNIT_ELEMS);
+      u32x4* to = reinterpret_cast<u32x4*>(a.pd.pool + ((size_t)head * a.pd.units_per_head + a.pd.sel_base + slot) * UNIT_ELEMS);
+      for (int i = threadIdx.x; i < UNIT_BYTES / 16; i += NW * 64) to[i] = from[i];
+    }
+  }
+  constexpr int IT = (MAX_G * D + NW * 64 - 1) / (NW * 64);
+#pragma unroll 1
+  for (int t = 0; t < IT; ++t) {
+    const int idx = threadIdx.x + t * NW * 64;
+    if (idx < split * a.share || idx >= min(a.G * D, (split + 1) * a.share) || !(left.outputs >> t & 1u)) continue;
+    a.out[(size_t)head * a.G * D + idx] = output_alone<DT, FUSED, HOSTFUSED>(a, head, left.corrected, idx / D, idx % D);
+  }
 }
 
 }  // namespace fkv

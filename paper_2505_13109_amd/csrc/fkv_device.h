@@ -58,6 +58,20 @@ __device__ __forceinline__ void touch_args() {
   touch<BYTES>((const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
+// The same arguments (T: all of them, as one struct) once more from memory.  What this reads does not have to be kept in
+// registers up to here, and the compiler, which knows nothing about the pointer, cannot decide to.
+template <typename T>
+__device__ __forceinline__ T args_from_memory() {
+  typedef const __attribute__((address_space(4))) unsigned long long* WordPtr;
+  WordPtr p = (WordPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  static_assert(sizeof(T) % 8 == 0, "");
+  struct Words { unsigned long long w[sizeof(T) / 8]; } v;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 8); ++i) v.w[i] = p[i];
+  return __builtin_bit_cast(T, v);
+}
+
 // correction flag of a KV head from the similarities of its G query heads (Sec. 3.3): the
 // group-pooled similarity strictly below tau.  pool: 0 mean (sum in head order / G), 1 maximum,
 // 2 minimum (App. B.3).  fp64, one thread.
@@ -216,8 +230,17 @@ __device__ __forceinline__ uint32_t launch_tag(const LaunchNo& n) { return n.dev
 // whose patience ends makes what it waits for itself, from what was in memory before the launch, bit for bit what the other
 // block would have made, and goes on (and its compute unit is free again soon).
 constexpr int PATIENCE = 1 << 12;       // polls: a few milliseconds (a launch by itself: microseconds)
-// Polls before a wave gives up on values that are its own by then: never, unless a test sees to it.
+// Polls before a thread gives up on words that its block has written by then: that many only if a test sees to it.
 constexpr int MAX_POLLS = 1 << 16;
+
+// threadIdx.x once more, from the wave's number in a scalar register: what is worked out from this after a stretch of code that
+// needs every vector register does not have to be kept through it.
+__device__ __forceinline__ int thread_id(int wave) {
+  uint32_t t = (uint32_t)wave * 64 + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(t));
+  __builtin_assume(t < 1024);
+  return (int)t;
+}
 
 // A barrier that orders the block's LDS accesses and nothing else: global loads stay in flight across it, and no store's
 // acknowledgement is waited for.

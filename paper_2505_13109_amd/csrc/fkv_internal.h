@@ -91,7 +91,7 @@ __host__ __device__ inline uint32_t host_tag(uint32_t launch) { return (launch <
 __host__ __device__ inline uint32_t device_tag(uint32_t launch) { return launch << 1; }
 
 // what blocks of a launch wait for, as bits (a test makes waits of these kinds run out at once)
-constexpr uint32_t WAIT_WEIGHTS = 1, WAIT_MAXIMA = 2, WAIT_SUMS = 4, WAIT_KEYS = 8;
+constexpr uint32_t WAIT_WEIGHTS = 1, WAIT_MAXIMA = 2, WAIT_SUMS = 4, WAIT_KEYS = 8, WAIT_SPLITS = 16, WAIT_IDS = 32;
 
 // the fused step kernel: roles are OR-ed
 constexpr int ROLE_APPEND = 1, ROLE_CORR = 2, ROLE_SELECT = 4;
@@ -150,9 +150,10 @@ struct LayerIO {
 bool launch_floor(int grid, size_t lds, int reps, hipStream_t st);
 bool launch_layer(const Dims& d, const LayerIO& lio, Geom g, hipStream_t st);
 constexpr int kComputeUnits = 256;
-// Most blocks of a launch that may wait for each other (a head's selecting blocks, a head's attention blocks).  In block
-// order at most one head's are half there, so a launch by itself always gets on; with two launches on the machine at once
-// there is room for both as long as neither has more of them than half the blocks that fit (two to a compute unit).
+// Most blocks of a launch that wait for each other (a head's attention blocks, and its selecting blocks where it has several):
+// half of those that fit (two to a compute unit).  That keeps waits short: in block order at most one head's blocks are half
+// there, so a launch by itself gets on, and two at once mostly do.  It is not what makes them end: with more launches on the
+// machine, or another program's, a block may wait for one that cannot start, and goes on by itself (PATIENCE).
 constexpr int kMaxWaiting = kComputeUnits;
 int attn_pages_per_block(int n_att, int heads, int max_splits, int nw, int max_blocks = kMaxWaiting);
 void launch_load_prefix(const Dims& d, const PoolDesc& pd, uint16_t* summ, uint16_t* host_pool,
@@ -178,7 +179,7 @@ struct AttnIO {
   const uint16_t* q; const int32_t* act_ids; const int32_t* new_ids; const int32_t* act_slots; const int32_t* new_slots;
   const uint8_t* flags; int use;
   unsigned long long* part; unsigned long long* part_ml; int max_splits;
-  LaunchNo no;
+  LaunchNo no; uint32_t impatient;
   int* status; float* out; long long* tstamp;
 };
 void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end);

@@ -13,9 +13,12 @@ namespace fkv {
 // ---------------------------------------------------------------------------------
 template <int DT, int G>
 __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
-  extern __shared__ uint32_t dyn_lds[];              // selection: n_cand keys, then the recall plan
+  extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];              // selection: n_cand keys, then the recall plan
   touch_args<sizeof(StepArgs)>();
-  step_roles<DT, G>(a, blockIdx.x, blockIdx.y, dyn_lds);
+  int head, s, nw;
+  bool made;
+  if (step_roles<DT, G>(a, blockIdx.x, blockIdx.y, head, s) && select_begin<G, true>(a, head, s, dyn_lds, nw, made))
+    select_finish<DT, G, true>(a, head, dyn_lds, nw, made);
 }
 
 // The two halves of the bandwidth-bound regime.  The scan: append, correction test and page weights, in 256-thread
@@ -40,14 +43,18 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) void scan_kernel(StepArgs a) {
     if ((a.roles & ROLE_CORR) && i < a.heads) corr_role<DT, G, SCAN_WAVES>(a, i);
     return;
   }
-  score_role<DT, G, SCORE_PLAIN, SCAN_WAVES>(a, y - a.other_rows, blockIdx.x);
+  score_role<DT, G, false, SCAN_WAVES>(a, y - a.other_rows, blockIdx.x);
 }
 // The selection after it: one block per slice of a head's candidates, a head's slices adjacent.
 template <int G>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
-  extern __shared__ uint32_t dyn_lds[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
   touch_args<sizeof(StepArgs)>();
-  select_role<0, G, false, SEL_REGS_ALONE>(a, (int)blockIdx.x >> a.slices_log2, (int)blockIdx.x & (a.slices - 1), dyn_lds);
+  const int head = (int)blockIdx.x >> a.slices_log2;
+  int nw;
+  bool made;
+  if (select_begin<G, false, SEL_REGS_ALONE>(a, head, (int)blockIdx.x & (a.slices - 1), dyn_lds, nw, made))
+    select_finish<0, G, false>(a, head, dyn_lds, nw, made);
 }
 
 constexpr size_t kLdsPerUnit = 150 * 1024;   // of the 160 KiB of a compute unit
@@ -201,79 +208,133 @@ typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // 
 // packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), pages per
 // split (9), lose_selection, WAIT_* bits;   split_magic: 2^32 / splits rounded up, 0 for one split
 constexpr int kMaxLayersPacked = 1 << 13, kMaxCtxPacked = 1 << 19;
+struct LayerKernelArgs {                     // the kernel's arguments, in their order
+  const LayerConst* consts;
+  const uint16_t *q, *k_new, *v_new;
+  float* out;
+  uint32_t packed, host_numbered, plan, split_magic;
+};
+
+// what every block works out from the constants
+template <bool HOSTPOOL>
+struct LayerSetup {
+  LayerConstPtr c;
+  char* base;
+  uint16_t* qprev0;
+  int32_t *ids0, *slots0;
+  Geom g;
+  uint32_t tag;
+  PoolDesc pd;
+  int layer, now, before, chunks, passes_log2, slices_log2, slices, step_rows;      // now, before: halves (PENDING / staged, ACTIVE / previous)
+  __device__ __forceinline__ explicit LayerSetup(const LayerKernelArgs& ka) {
+    c = (LayerConstPtr)ka.consts;
+    layer = (int)(ka.packed >> 19);
+    now = (int)(ka.plan >> 1) & 1;
+    before = now ^ 1;
+    base = c->dev_base + c->layer_bytes * (unsigned long long)layer;
+    g = geom_of((int)(ka.packed & 0x7ffffu) + 1, c->n_sink, c->n_win, c->k);
+    tag = ka.host_numbered ? ka.host_numbered : device_tag((uint32_t)*(const __attribute__((address_space(4))) int*)c->launch_no);
+    qprev0 = reinterpret_cast<uint16_t*>(at(c->o_qprev));
+    ids0 = reinterpret_cast<int32_t*>(at(c->o_ids));
+    slots0 = reinterpret_cast<int32_t*>(at(c->o_slots));
+    pd.pool = reinterpret_cast<uint16_t*>(base);
+    pd.units_per_head = c->units_per_head;
+    pd.placement = HOSTPOOL ? 1 : 0;
+    pd.ring_base = c->ring_base; pd.n_ring = c->n_ring; pd.sel_base = c->sel_base;
+    passes_log2 = (int)(ka.plan >> 2) & 3;
+    const int chunk_log2 = 5 + passes_log2;
+    static_assert(PAGES_PER_PASS == 32, "chunks are a power of two of pages");
+    chunks = (g.n_cand + (1 << chunk_log2) - 1) >> chunk_log2;
+    slices_log2 = (int)(ka.plan >> 4) & 7;
+    slices = 1 << slices_log2;
+    step_rows = 2 + chunks + slices;
+  }
+  __device__ __forceinline__ char* at(uint32_t o) const { return base + (unsigned long long)o * 256; }
+  __device__ __forceinline__ uint16_t* qprev(int half) const { return qprev0 + (size_t)half * c->qprev_half; }
+  __device__ __forceinline__ int32_t* ids(int half) const { return ids0 + (size_t)half * c->ids_half; }
+  __device__ __forceinline__ int32_t* slots(int half) const { return slots0 + (size_t)half * c->ids_half; }
+
+  __device__ __forceinline__ StepArgs step_args(const LayerKernelArgs& ka) const {
+    StepArgs a;
+    a.roles = ROLE_APPEND | ROLE_CORR | ROLE_SELECT;
+    a.heads = c->heads; a.k = c->k; a.max_pages = c->max_pages; a.g = g; a.pd = pd;
+    a.summ = reinterpret_cast<uint16_t*>(at(c->o_summ));
+    a.k_new = ka.k_new; a.v_new = ka.v_new; a.q = ka.q;
+    a.q_prev = qprev(before); a.q_stage = qprev(now);
+    a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
+    a.flags = reinterpret_cast<uint8_t*>(at(c->o_flags)); a.flags_user = nullptr;
+    a.cosine = reinterpret_cast<double*>(at(c->o_cosine));
+    a.sel_pool = c->sel_pool; a.P = c->P; a.score = c->score;
+    a.ids = ids(now); a.ids_user = nullptr;
+    a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
+    a.slice = (g.n_cand + slices - 1) >> slices_log2;
+    a.exch = c->exch; a.keyx = c->keyx; a.no = LaunchNo{tag, nullptr}; a.impatient = ka.plan >> 23; a.tstamp = c->tstamp;
+    a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
+    a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
+    if (HOSTPOOL) {
+      a.plan_act_ids = ids(before);
+      a.plan_act_slots = slots(before);
+      a.plan_new_slots = slots(now);
+      a.plan_miss = reinterpret_cast<int32_t*>(at(c->o_miss));
+      a.plan_lds_off = select_key_words(g.n_cand);
+    }
+    return a;
+  }
+  __device__ __forceinline__ AttnArgs attn_args(const LayerKernelArgs& ka, int G) const {
+    AttnArgs a;
+    a.pd = pd; a.q = ka.q;
+    a.act_ids = ids(before); a.new_ids = nullptr;
+    a.act_slots = HOSTPOOL ? slots(before) : nullptr; a.new_slots = nullptr;
+    a.flags = nullptr; a.use = 2; a.part = c->part; a.part_ml = c->part_ml; a.max_splits = c->max_splits;
+    a.n_splits = (int)(ka.plan >> 7) & 63; a.pps = (int)(ka.plan >> 13) & 511;
+    a.share = ka.split_magic ? (int)__umulhi((uint32_t)(G * D + a.n_splits - 1), ka.split_magic) : G * D;
+    a.no = LaunchNo{}; a.out = ka.out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
+    a.status = reinterpret_cast<int*>(at(c->o_status)); a.tstamp = c->tstamp;
+    a.q_prev = qprev(before); a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
+    a.k_new = ka.k_new; a.v_new = ka.v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
+    a.tag = tag; a.pick_tag = tag + ((ka.plan >> 22) & 1u ? 2u : 0u);
+    a.impatient = ka.plan >> 23;
+    a.host_pool = HOSTPOOL ? reinterpret_cast<const uint16_t*>(c->host_base + c->host_layer_bytes * (unsigned long long)layer) : nullptr;
+    a.max_pages = c->max_pages;
+    return a;
+  }
+};
 
 template <int DT, int G, bool HOSTPOOL>
 __global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
                   uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
-  extern __shared__ uint32_t dyn_lds[];
-  LayerConstPtr c = (LayerConstPtr)consts;
-  touch<sizeof(LayerConst)>(c);
-  const int layer = (int)(packed >> 19), parity = (int)(plan >> 1) & 1;
-  char* const base = c->dev_base + c->layer_bytes * (unsigned long long)layer;
-  auto at = [&](uint32_t o) { return base + (unsigned long long)o * 256; };
-  const Geom g = geom_of((int)(packed & 0x7ffffu) + 1, c->n_sink, c->n_win, c->k);
-  const uint32_t tag = host_numbered ? host_numbered : device_tag((uint32_t)*(const __attribute__((address_space(4))) int*)c->launch_no);
-  PoolDesc pd;
-  pd.pool = reinterpret_cast<uint16_t*>(base);
-  pd.units_per_head = c->units_per_head;
-  pd.placement = HOSTPOOL ? 1 : 0;
-  pd.ring_base = c->ring_base; pd.n_ring = c->n_ring; pd.sel_base = c->sel_base;
-  uint16_t* const qprev0 = reinterpret_cast<uint16_t*>(at(c->o_qprev));
-  int32_t* const ids0 = reinterpret_cast<int32_t*>(at(c->o_ids));
-  int32_t* const slots0 = reinterpret_cast<int32_t*>(at(c->o_slots));
-  const int now = parity, before = parity ^ 1;             // halves: PENDING / staged, ACTIVE / previous
-  const int passes_log2 = (int)(plan >> 2) & 3, chunk_log2 = 5 + passes_log2;
-  static_assert(PAGES_PER_PASS == 32, "chunks are a power of two of pages");
-  const int chunks = (g.n_cand + (1 << chunk_log2) - 1) >> chunk_log2;
-  const int slices_log2 = (int)(plan >> 4) & 7, slices = 1 << slices_log2;
-  const int step_rows = 2 + chunks + slices;
-  int* const status = reinterpret_cast<int*>(at(c->o_status));
-  if ((int)blockIdx.y < step_rows) {
-    StepArgs a;
-    a.roles = ROLE_APPEND | ROLE_CORR | ROLE_SELECT;
-    a.heads = c->heads; a.k = c->k; a.max_pages = c->max_pages; a.g = g; a.pd = pd;
-    a.summ = reinterpret_cast<uint16_t*>(at(c->o_summ));
-    a.k_new = k_new; a.v_new = v_new; a.q = q;
-    a.q_prev = qprev0 + (size_t)before * c->qprev_half; a.q_stage = qprev0 + (size_t)now * c->qprev_half;
-    a.have_prev = (int)(plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
-    a.flags = reinterpret_cast<uint8_t*>(at(c->o_flags)); a.flags_user = nullptr;
-    a.cosine = reinterpret_cast<double*>(at(c->o_cosine));
-    a.sel_pool = c->sel_pool; a.P = c->P; a.score = c->score;
-    a.ids = ids0 + (size_t)now * c->ids_half; a.ids_user = nullptr;
-    a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
-    a.slice = (g.n_cand + slices - 1) >> slices_log2;
-    a.exch = c->exch; a.keyx = c->keyx; a.no = LaunchNo{tag, nullptr}; a.impatient = plan >> 23; a.tstamp = c->tstamp;
-    a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
-    a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
-    if (HOSTPOOL) {
-      a.plan_act_ids = ids0 + (size_t)before * c->ids_half;
-      a.plan_act_slots = slots0 + (size_t)before * c->ids_half;
-      a.plan_new_slots = slots0 + (size_t)now * c->ids_half;
-      a.plan_miss = reinterpret_cast<int32_t*>(at(c->o_miss));
-      a.plan_lds_off = select_key_words(g.n_cand);
-    }
-    step_roles<DT, G>(a, blockIdx.x, blockIdx.y, dyn_lds);
-    return;
+  extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
+  touch<sizeof(LayerConst)>((LayerConstPtr)consts);
+  const LayerKernelArgs ka{consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic};
+  const LayerSetup<HOSTPOOL> u(ka);
+  StepArgs s;
+  int head, nw = SEL_WAVES, own = 0;
+  bool made = false;
+  AttnLeft left{};
+  const bool step = (int)blockIdx.y < u.step_rows;
+  if (step) {
+    s = u.step_args(ka);
+    int slice;
+    if (!step_roles<DT, G>(s, blockIdx.x, blockIdx.y, head, slice) || !select_begin<G, true>(s, head, slice, dyn_lds, nw, made)) return;
+  } else {
+    const AttnArgs a = u.attn_args(ka, G);
+    // numbered through row by row, so that a head's blocks, which wait for each other, are adjacent
+    const uint32_t i = (blockIdx.y - (uint32_t)u.step_rows) * (uint32_t)u.c->heads + blockIdx.x;
+    head = (int)(split_magic ? __umulhi(i, split_magic) : i);
+    own = (int)i - head * a.n_splits;
+    left = attn_block<DT, STEP_WAVES, true, HOSTPOOL>(a, own, head, reinterpret_cast<float*>(dyn_lds));
+    if (__builtin_expect(!left.any(), 1)) return;
+    // What follows is hardly ever run.  Its arguments come from memory once more: kept up to here they would cost the page
+    // loop registers.
+    const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
+    s = LayerSetup<HOSTPOOL>(again).step_args(again);
+    if (left.ids) lds_barrier();                             // (the LDS is free)
   }
-  AttnArgs a;
-  a.pd = pd; a.q = q;
-  a.act_ids = ids0 + (size_t)before * c->ids_half; a.new_ids = nullptr;
-  a.act_slots = HOSTPOOL ? slots0 + (size_t)before * c->ids_half : nullptr; a.new_slots = nullptr;
-  a.flags = nullptr; a.use = 2; a.part = c->part; a.part_ml = c->part_ml; a.max_splits = c->max_splits;
-  a.n_splits = (int)(plan >> 7) & 63; a.pps = (int)(plan >> 13) & 511;
-  a.share = split_magic ? (int)__umulhi((uint32_t)(G * D + a.n_splits - 1), split_magic) : G * D;
-  a.no = LaunchNo{}; a.out = out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
-  a.status = status; a.tstamp = c->tstamp;
-  a.q_prev = qprev0 + (size_t)before * c->qprev_half; a.have_prev = (int)(plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
-  a.k_new = k_new; a.v_new = v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
-  a.tag = tag; a.pick_tag = tag + ((plan >> 22) & 1u ? 2u : 0u);
-  a.host_pool = HOSTPOOL ? reinterpret_cast<const uint16_t*>(c->host_base + c->host_layer_bytes * (unsigned long long)layer) : nullptr;
-  a.max_pages = c->max_pages;
-  // numbered through row by row, so that a head's blocks, which wait for each other, are adjacent
-  const uint32_t i = (blockIdx.y - (uint32_t)step_rows) * (uint32_t)c->heads + blockIdx.x;
-  const uint32_t head = split_magic ? __umulhi(i, split_magic) : i;
-  attn_block<DT, STEP_WAVES, true, HOSTPOOL>(a, (int)(i - head * (uint32_t)a.n_splits), (int)head, reinterpret_cast<float*>(dyn_lds));
+  if (step || left.ids) select_finish<DT, G, true>(s, head, dyn_lds, nw, made);
+  if (step) return;
+  const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
+  attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL>(again).attn_args(again, G), own, head, left);
 }
 
 struct LayerLaunch { dim3 grid; size_t lds; uint32_t packed, plan, split_magic; };
@@ -343,7 +404,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
 // The cost of a launch as such: a kernel of the same shape whose blocks return at once.
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(STEP_THREADS) void floor_kernel(uint32_t* sink) {
-  extern __shared__ uint32_t dyn_lds[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
   if (sink) *sink = dyn_lds[0];             // never taken: keeps the LDS allocation in the kernel
 }
 

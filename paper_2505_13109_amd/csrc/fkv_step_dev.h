@@ -163,28 +163,25 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // for a later launch each pass stores its own, which leaves the waves of a bandwidth-bound scan independent of each other
 // (28.2 us against 30.3 us through LDS for 256 heads x 992 pages).
 // ---------------------------------------------------------------------------------
-constexpr int SCORE_PLAIN = 0, SCORE_TAGGED = 1, SCORE_FOUR = 2;     // (SCORE_FOUR: a wave by itself, 4 pages from `at` on)
-template <int DT, int G, bool QMODE, int HOW, int WAVES>
-__device__ __forceinline__ void score_pages(const StepArgs& a, int head, int at) {
-  constexpr bool TAGGED = HOW == SCORE_TAGGED;
+template <int DT, int G, bool QMODE, bool TAGGED, int WAVES>
+__device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chunk) {
   constexpr int PASS = WAVES * 4;                         // pages per pass
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane >> 4, c8 = lane & 15;
-  constexpr int MOST = HOW == SCORE_FOUR ? 1 : SCORE_PASSES;
-  const int passes = TAGGED ? a.passes : MOST;            // (the scan always makes as many as there are)
-  const int n = a.g.n_cand, j0 = HOW == SCORE_FOUR ? at + grp : at * PASS * passes + wave * 4 + grp;
-  uint4 wmax[MOST], wmin[MOST];
+  const int passes = TAGGED ? a.passes : SCORE_PASSES;    // (the scan always makes as many as there are)
+  const int n = a.g.n_cand, j0 = chunk * PASS * passes + wave * 4 + grp;
+  uint4 wmax[SCORE_PASSES], wmin[SCORE_PASSES];
   const uint16_t* sm = a.summ + summ_idx(0, head, 0, 0, a.max_pages, a.g.cand_lo) + c8 * 8;
   const size_t to_min = (size_t)a.max_pages * D;
 #pragma unroll
-  for (int ps = 0; ps < MOST; ++ps) {
+  for (int ps = 0; ps < SCORE_PASSES; ++ps) {
     if (ps < passes) {
       const int j = min(j0 + ps * PASS, n - 1);
       wmax[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D);
       wmin[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D + to_min);
     }
   }
-  const uint32_t tag = HOW != SCORE_PLAIN ? launch_tag(a.no) : 0u;
+  const uint32_t tag = TAGGED ? launch_tag(a.no) : 0u;
   uint4 wq[G];
 #pragma unroll
   for (int gg = 0; gg < G; ++gg) wq[gg] = *reinterpret_cast<const uint4*>(a.q + ((size_t)head * G + gg) * D + c8 * 8);
@@ -270,30 +267,28 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int at)
       const int j = j0 + i * PASS;
       if (TAGGED) {
         if (c8 < NG) s_w[c8][i * PASS + wave * 4 + grp] = mine[i] * scale;
-      } else if (HOW == SCORE_FOUR) {
-        if (c8 < NG && j < n) st_tag(a.P + ((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j, __float_as_uint(mine[i] * scale), tag);
       } else if (c8 < NG && j < n) {
         reinterpret_cast<float*>(a.P)[((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j] = mine[i] * scale;
       }
     }
   };
   static_assert(SCORE_PASSES == 4, "");
-  if (HOW == SCORE_FOUR || passes == 1) score(UnrollBy<1>{});
-  else if (passes == 2) score(UnrollBy<(MOST >= 2 ? 2 : 1)>{});
-  else score(UnrollBy<MOST>{});
+  if (passes == 1) score(UnrollBy<1>{});
+  else if (passes == 2) score(UnrollBy<2>{});
+  else score(UnrollBy<4>{});
   if (!TAGGED) return;
   lds_barrier();
-  const int pages_log2 = __builtin_ctz(PASS * passes), pages = 1 << pages_log2, at0 = at * pages;     // (powers of two)
+  const int pages_log2 = __builtin_ctz(PASS * passes), pages = 1 << pages_log2, at0 = chunk * pages;     // (powers of two)
   for (int i = threadIdx.x; i < NG * pages; i += WAVES * 64) {
     const int gg = i >> pages_log2, jj = i & (pages - 1);
     if (at0 + jj < n) st_tag(a.P + ((size_t)head * G + gg) * a.max_pages + a.g.cand_lo + at0 + jj, __float_as_uint(s_w[gg][jj]), tag);
   }
 }
 
-template <int DT, int G, int HOW, int WAVES>
-__device__ __forceinline__ void score_role(const StepArgs& a, int head, int at) {
-  if (a.sel_pool >= 4) score_pages<DT, G, true, HOW, WAVES>(a, head, at);
-  else                 score_pages<DT, G, false, HOW, WAVES>(a, head, at);
+template <int DT, int G, bool TAGGED, int WAVES>
+__device__ __forceinline__ void score_role(const StepArgs& a, int head, int chunk) {
+  if (a.sel_pool >= 4) score_pages<DT, G, true, TAGGED, WAVES>(a, head, chunk);
+  else                 score_pages<DT, G, false, TAGGED, WAVES>(a, head, chunk);
 }
 
 // ---------------------------------------------------------------------------------
@@ -522,6 +517,11 @@ __device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, b
   }
 }
 
+__device__ __forceinline__ SelectLds& select_lds() {
+  __shared__ SelectLds sm;
+  return sm;
+}
+
 // The keys of one head's candidates into `key`, and the counts of their bins into sm.hist, by the groups that share the head.
 // A wave whose patience ends has nothing to say, and what it would have had to is never put into words under the tag: its
 // group learns of it at the next barrier, from a value no maximum or sum has, and leaves.  Of the groups only the last one has to end with all the keys, and it
@@ -737,92 +737,159 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
   return S == 1 || sm.alone == 0;
 }
 
-// The same by one group alone, which waits for nobody: page weights (TAGGED: made here once more), maxima, sums, keys, in
-// passes over the whole list.  The same numbers, bit for bit; the pooled scores are kept for inspection on the way.
+// The weight of one page for one query head of the group by one thread, bit for bit score_pages'.
+template <int DT, int G>
+__device__ __forceinline__ float weight_alone(const StepArgs& a, int head, int gg, int j) {
+  const uint16_t* const sm = a.summ + summ_idx(0, head, 0, 0, a.max_pages, a.g.cand_lo + j);
+  const size_t to_min = (size_t)a.max_pages * D;
+  const uint16_t* const q = a.q + (size_t)head * G * D;
+  const bool pooled = a.sel_pool >= 4;                   // MeanQ, MaxQ
+  float at1 = 0.0f, at2 = 0.0f, at4 = 0.0f, at8 = 0.0f, s = 0.0f;       // the tree over the 16 chunk sums: left halves in wait
+#pragma unroll 1
+  for (int c8 = 0; c8 < 16; ++c8) {
+    float qc[8], mx[8], mn[8];
+    unpack8<DT>(*reinterpret_cast<const uint4*>(q + (pooled ? 0 : gg) * D + c8 * 8), qc);
+    if (pooled) {
+#pragma unroll 1
+      for (int g = 1; g < G; ++g) {
+        float x[8];
+        unpack8<DT>(*reinterpret_cast<const uint4*>(q + g * D + c8 * 8), x);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) qc[c] = a.sel_pool == 4 ? qc[c] + x[c] : fmaxf(qc[c], x[c]);
+      }
+    }
+    unpack8<DT>(*reinterpret_cast<const uint4*>(sm + c8 * 8), mx);
+    unpack8<DT>(*reinterpret_cast<const uint4*>(sm + to_min + c8 * 8), mn);
+    s = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      if (pooled) {
+        if (a.sel_pool == 4) qc[c] = (float)((double)qc[c] / (double)G);
+        const float pr = qc[c] * (qc[c] >= 0.0f ? mx[c] : mn[c]);
+        s = c == 0 ? pr : s + pr;
+      } else {
+        s = __builtin_fmaf(qc[c], __float_as_uint(qc[c]) >> 31 ? mn[c] : mx[c], s);
+      }
+    }
+    if (!(c8 & 1)) at1 = s;
+    else if (!(c8 & 2)) at2 = at1 + s;
+    else if (!(c8 & 4)) at4 = at2 + (at1 + s);
+    else if (!(c8 & 8)) at8 = at4 + (at2 + (at1 + s));
+    else s = at8 + (at4 + (at2 + (at1 + s)));
+  }
+  return s * 0x1.6a09e6p-4f;                             // fl32(1/sqrt(128))
+}
+
+// All keys of a head by one group alone, which waits for nobody: page weights (TAGGED: made here, whoever else makes them),
+// maxima, sums, keys, in passes over the whole list.  The same numbers, bit for bit, by code that is short rather than fast:
+// it is hardly ever run, and a compute unit's instruction cache (64 KB for two units) has to hold the rest of the kernel.
 template <int DT, int G, bool TAGGED>
 __device__ __forceinline__ void alone_keys(const StepArgs& a, int head, int nw, uint32_t* key, SelectLds& sm) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
-  const int n = a.g.n_cand, lo = a.g.cand_lo;
+  const int n = a.g.n_cand;
   const int mode = a.sel_pool, ng = mode >= 4 ? 1 : G;
   const bool soft = mode <= 1;
-  lds_barrier();                                       // (every wave is done with the LDS of what it did before)
+  lds_barrier();                                         // (every wave is done with the LDS of what it did before)
   for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
   if (tid == 0) sm.n_list = 0;
+  const size_t base = (size_t)head * G * a.max_pages + a.g.cand_lo;
   if (TAGGED) {
-    for (int j = wave * 4; j < n; j += nw * 4) score_role<DT, G, SCORE_FOUR, SEL_WAVES>(a, head, j);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // they are where the group's waves read them
+    const uint32_t tag = launch_tag(a.no);
+#pragma unroll 1
+    for (int i = tid; i < n * ng; i += nt) {
+      const int gg = i / n, j = i - gg * n;
+      st_tag(a.P + base + (size_t)gg * a.max_pages + j, __float_as_uint(weight_alone<DT, G>(a, head, gg, j)), tag);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // they are where the group's waves read them
+    lds_barrier();
   }
-  lds_barrier();
-  auto weight = [&](int j, int gg) -> uint32_t {
-    const size_t at = ((size_t)head * G + min(gg, ng - 1)) * a.max_pages + lo + j;
+  auto weight = [&](int j, int gg) {
+    const size_t at = base + (size_t)(ng == 1 ? 0 : gg) * a.max_pages + j;
     return TAGGED ? (uint32_t)ld_tag(a.P + at) : reinterpret_cast<const uint32_t*>(a.P)[at];
   };
-  double zd[G], zr[G];
-  float mx[G];
-#pragma unroll
-  for (int gg = 0; gg < G; ++gg) { zd[gg] = zr[gg] = 1.0; mx[gg] = -__builtin_inff(); }
   if (soft) {
-    for (int j = tid; j < n; j += nt)
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) mx[gg] = fmaxf(mx[gg], __uint_as_float(weight(j, gg)));
-#pragma unroll
+#pragma unroll 1
     for (int gg = 0; gg < G; ++gg) {
-      const float v = wave_max_f32(mx[gg]);
+      float v = -__builtin_inff();
+#pragma unroll 1
+      for (int j = tid; j < n; j += nt) v = fmaxf(v, __uint_as_float(weight(j, gg)));
+      v = wave_max_f32(v);
       if (lane == 0) sm.mx[wave][gg] = v;
+      lds_barrier();
+      v = sm.mx[0][gg];
+#pragma unroll 1
+      for (int w = 1; w < nw; ++w) v = fmaxf(v, sm.mx[w][gg]);
+      unsigned long long z = 0;
+#pragma unroll 1
+      for (int j = tid; j < n; j += nt) z += softmax_fixed(__uint_as_float(weight(j, gg)), v);
+      z = wave_sum_u48(z);
+      if (lane == 0) sm.z[wave][gg] = z;
     }
     lds_barrier();
-    unsigned long long z[G];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      for (int w = 0; w < nw; ++w) mx[gg] = fmaxf(mx[gg], sm.mx[w][gg]);
-      z[gg] = 0;
-    }
-    for (int j = tid; j < n; j += nt)
-#pragma unroll
-      for (int gg = 0; gg < G; ++gg) z[gg] += softmax_fixed(__uint_as_float(weight(j, gg)), mx[gg]);
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      const unsigned long long v = wave_sum_u48(z[gg]);
-      if (lane == 0) sm.z[wave][gg] = v;
-    }
-    lds_barrier();
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      unsigned long long v = 0;
-      for (int w = 0; w < nw; ++w) v += sm.z[w][gg];
-      zd[gg] = (double)v;
-      zr[gg] = reciprocal_near(zd[gg]);
-    }
   }
+#pragma unroll 1
   for (int j = tid; j < n; j += nt) {
-    uint32_t x[G];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      x[gg] = weight(j, gg);
-      if (soft) x[gg] = softmax_fixed(__uint_as_float(x[gg]), mx[gg]);
+    double acc = 0.0;
+    float acc32 = 0.0f;
+#pragma unroll 1
+    for (int gg = 0; gg < ng; ++gg) {
+      const uint32_t x = weight(j, gg);
+      if (soft) {
+        float v = sm.mx[0][gg];
+        unsigned long long z = sm.z[0][gg];
+#pragma unroll 1
+        for (int w = 1; w < nw; ++w) {
+          v = fmaxf(v, sm.mx[w][gg]);
+          z += sm.z[w][gg];
+        }
+        const double zd = (double)z, sg = div_rn((double)softmax_fixed(__uint_as_float(x), v), zd, reciprocal_near(zd));
+        acc = gg == 0 ? sg : mode == 0 ? acc + sg : sg > acc ? sg : acc;
+      } else {
+        const float w = __uint_as_float(x);
+        acc32 = gg == 0 ? w : mode == 2 ? acc32 + w : fmaxf(acc32, w);
+      }
     }
-    const uint32_t kj = score_key(pooled_score<G>(x, zd, zr, mode));
+    const float sc = mode == 0 ? (float)(acc / (double)G) : mode == 1 ? (float)acc : mode == 2 ? (float)((double)acc32 / (double)G) : acc32;
+    const uint32_t kj = score_key(sc);
     key[j] = kj;
     atomicAdd(&sm.hist[topk_bin(kj, soft)], 1u);
-    a.score[(size_t)head * a.max_pages + lo + j] = key_score(kj);
   }
   lds_barrier();
 }
 
-template <int DT, int G, bool TAGGED, int REGS = SEL_REGS>
-__device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, uint32_t* key) {
-  __shared__ SelectLds sm;
+// Selecting block `s` of a head, up to the keys.  True for the waves that go on with select_finish -- the last block's, nw of
+// them -- and `made`: whether the keys are there.
+template <int G, bool TAGGED, int REGS = SEL_REGS>
+__device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s, uint32_t* key, int& nw, bool& made) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff, k = a.k;
-  const int S = a.slices;
+  const int S = a.slices, j0 = s * a.slice, j1 = min(a.g.n_cand, j0 + a.slice);
   const bool last = s == S - 1;
-  const uint32_t tag = launch_tag(a.no);
-  const int j0 = s * a.slice, j1 = min(n, j0 + a.slice);
   // The waves that take part: as many as there are candidates for; all of them where a plan has to be made or keys of
   // other slices have to be gathered.  The others of the block end here (a barrier counts the waves that are left).
-  const int nw = (last && S > 1) || a.plan_new_slots || kk == 0 ? SEL_WAVES : min(SEL_WAVES, (j1 - j0 + 63) / 64);
-  if (wave >= nw) return;
-  const int nt = nw * 64;
+  nw = (last && S > 1) || a.plan_new_slots || a.g.k_eff == 0 ? SEL_WAVES : min(SEL_WAVES, (j1 - j0 + 63) / 64);
+  made = true;
+  if (wave >= nw) return false;
+  if (a.g.k_eff == 0) return true;
+  uint32_t kreg[REGS];
+  made = shared_keys<G, TAGGED, REGS>(a, head, s, nw, key, select_lds(), kreg);
+  if (last) return true;
+  if (made) {                                            // the pooled scores, kept for inspection
+#pragma unroll
+    for (int u = 0; u < REGS; ++u) {
+      const int j = j0 + tid + u * nw * 64;
+      if (j < j1) a.score[(size_t)head * a.max_pages + a.g.cand_lo + j] = key_score(kreg[u]);
+    }
+  }
+  return false;
+}
+
+// ... and from the keys on, by nw waves: the top-k, the ids out, the recall plan.
+template <int DT, int G, bool TAGGED>
+__device__ __forceinline__ void select_finish(const StepArgs& a, int head, uint32_t* key, int nw, bool made) {
+  SelectLds& sm = select_lds();
+  const int tid = threadIdx.x, nt = nw * 64;
+  const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff, k = a.k;
+  const uint32_t tag = launch_tag(a.no);
   int32_t* out = a.ids + (size_t)head * k;
   int32_t* outu = a.ids_user ? a.ids_user + (size_t)head * k : nullptr;
   // a picked id goes out three ways: the layer's id list, the caller's copy, and (one-launch layer-step) as a tagged
@@ -837,9 +904,14 @@ __device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, 
     out[pos] = id;
     if (outu) outu[pos] = id;
   };
-  auto plan_and_publish = [&]() {
-    if (!plan_nid) return;
-    lds_barrier();                                     // the ids are all in LDS
+  if (kk > 0) {
+    if (__builtin_expect(!made, 0)) alone_keys<DT, G, TAGGED>(a, head, nw, key, sm);
+    FKV_STAMP(a, head, 5);
+    block_topk(key, n, kk, a.sel_pool <= 1, nw, sm, [&](int pos, int j) { put_id(pos, lo + j); });
+  }
+  for (int i = kk + tid; i < k; i += nt) put_id(i, -1);   // padding
+  if (plan_nid) {
+    lds_barrier();                                       // the ids are all in LDS
     plan_head<SEL_THREADS>(out, a.plan_act_ids + (size_t)head * k, a.plan_act_slots + (size_t)head * k,
                            a.plan_new_slots + (size_t)head * k, a.plan_miss + (size_t)head * (1 + 3 * k), k, a.g.n_full,
                            plan_sm, true);
@@ -850,32 +922,10 @@ __device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, 
       out[i] = id;
       if (outu) outu[i] = id;
     }
-  };
-  if (kk == 0) {
-    for (int i = tid; i < k; i += nt) put_id(i, -1);
-    plan_and_publish();
-    return;
   }
-  uint32_t kreg[REGS];
-  const bool made = shared_keys<G, TAGGED, REGS>(a, head, s, nw, key, sm, kreg);
-  auto keep_scores = [&]() {                           // the pooled scores, kept for inspection
-#pragma unroll
-    for (int u = 0; u < REGS; ++u) {
-      const int j = j0 + tid + u * nt;
-      if (j < j1) a.score[(size_t)head * a.max_pages + lo + j] = key_score(kreg[u]);
-    }
-  };
-  if (!last) {
-    if (made) keep_scores();
-    return;
-  }
-  if (__builtin_expect(!made, 0)) alone_keys<DT, G, TAGGED>(a, head, nw, key, sm);
-  FKV_STAMP(a, head, 5);
-  block_topk(key, n, kk, a.sel_pool <= 1, nw, sm, [&](int pos, int j) { put_id(pos, lo + j); });
-  for (int i = kk + tid; i < k; i += nt) put_id(i, -1);   // padding
-  plan_and_publish();
   FKV_STAMP(a, head, 8);
-  if (made) keep_scores();
+  // the pooled scores, kept for inspection: the group's own, or all of them if it was alone
+  for (int j = (made ? (a.slices - 1) * a.slice : 0) + tid; j < n; j += nt) a.score[(size_t)head * a.max_pages + lo + j] = key_score(key[j]);
 }
 
 // ---------------------------------------------------------------------------------
@@ -883,24 +933,27 @@ __device__ __forceinline__ void select_role(const StepArgs& a, int head, int s, 
 // present only if its role bit is set; x is the KV head, except that the selection's blocks are numbered through row by
 // row so that a head's are adjacent (they wait for each other: in block order, at most one head's are ever half there).
 // ---------------------------------------------------------------------------------
+// True for a selecting block: of `head`, slice `s`.
 template <int DT, int G>
-__device__ __forceinline__ void step_roles(const StepArgs& a, int head, int y, uint32_t* dyn_lds) {
+__device__ __forceinline__ bool step_roles(const StepArgs& a, int x, int y, int& head, int& s) {
   if (a.roles & ROLE_APPEND) {
-    if (y == 0) { append_role<DT>(a, head); return; }
+    if (y == 0) { append_role<DT>(a, x); return false; }
     y -= 1;
   }
   if (a.roles & ROLE_CORR) {
-    if (y == 0) { corr_role<DT, G>(a, head); return; }
+    if (y == 0) { corr_role<DT, G>(a, x); return false; }
     y -= 1;
   }
   if (y < a.chunks) {
-    if (y == 0) FKV_STAMP(a, head, 0);
-    score_role<DT, G, SCORE_TAGGED, STEP_WAVES>(a, head, y);
-    if (y == 0) FKV_STAMP(a, head, 1);
-    return;
+    if (y == 0) FKV_STAMP(a, x, 0);
+    score_role<DT, G, true, STEP_WAVES>(a, x, y);
+    if (y == 0) FKV_STAMP(a, x, 1);
+    return false;
   }
-  const int i = (y - a.chunks) * a.heads + head;
-  select_role<DT, G, true>(a, i >> a.slices_log2, i & (a.slices - 1), dyn_lds);
+  const int i = (y - a.chunks) * a.heads + x;
+  head = i >> a.slices_log2;
+  s = i & (a.slices - 1);
+  return true;
 }
 
 }  // namespace fkv
