@@ -49,7 +49,7 @@ int fkv_profile_launch_floor(fkv_ctx* ctx, int32_t layer, int32_t reps, void* st
 int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on);
 
 /* Test hook for what a block does when another block of its launch keeps it waiting too long: waits of these kinds
- * run out at the first look.  Nothing is lost by that -- the waiting block makes what it waits for itself -- so ids and
+ * run out.  Nothing is lost by that -- the waiting block makes what it waits for itself -- so ids and
  * outputs stay what they are, bit for bit.  Host-side switch, no GPU work. */
 #define FKV_WAIT_WEIGHTS  1  /* the selection's, for page weights from scoring blocks of the launch       */
 #define FKV_WAIT_MAXIMA   2  /* a slice's, for the other slices' maxima                                   */

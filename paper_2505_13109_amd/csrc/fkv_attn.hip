@@ -10,9 +10,10 @@ template <int DT, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void attn_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) float attn_lds[];
   touch_args<sizeof(AttnArgs)>();
-  const AttnLeft left = attn_block<DT, NW, false, false>(a, blockIdx.x, blockIdx.y, attn_lds);
+  const int head = (int)blockIdx.y;
+  const AttnLeft left = attn_block<DT, NW, false, false>(a, blockIdx.x, head, attn_lds);
   if (__builtin_expect(left.any(), 0))
-    attn_finish<DT, NW, false, false>(args_from_memory<AttnArgs>(), blockIdx.x, blockIdx.y, left);
+    attn_finish<DT, NW, false, false>(args_from_memory<AttnArgs>(), blockIdx.x, head, left);
 }
 
 // experiment builds only (see knob()): pages per block (0 = choose from the shape)

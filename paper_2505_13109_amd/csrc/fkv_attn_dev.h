@@ -522,6 +522,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   const int own_lo = split * a.share, own_hi = min(items, own_lo + a.share);
   unsigned long long* const po = a.part + (size_t)head * a.max_splits * items;
   unsigned long long* const pml = a.part_ml + (size_t)head * a.max_splits * G * 2;
+  const uint32_t want = tag + (a.impatient & WAIT_SPLITS ? 2u : 0u);      // (or a tag that no word has yet)
   constexpr int IT = (MAX_G * D + NW * 64 - 1) / (NW * 64);
   float o[IT], den[IT], M[IT];
   uint32_t left = 0;                                    // bit t: item t's output is left to be made alone
@@ -569,8 +570,8 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
       // (the others' splits, numbered from 0: the block's own is left out)
       for (int s0 = 0; s0 < n_splits - 1; s0 += CH) {
         unsigned long long wm[CH], wl[CH], wo[CH];
-        bool late = (a.impatient & WAIT_SPLITS) != 0;
-        for (int it = 0; !late;) {
+        int it = 0;
+        for (;;) {
           bool there = true;
 #pragma unroll
           for (int u = 0; u < CH; ++u) {
@@ -582,12 +583,12 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
           }
 #pragma unroll
           for (int u = 0; u < CH; ++u)
-            there = there & ((uint32_t)(wo[u] >> 32) == tag) & ((uint32_t)(wm[u] >> 32) == tag) & ((uint32_t)(wl[u] >> 32) == tag);
+            there = there & ((uint32_t)(wo[u] >> 32) == want) & ((uint32_t)(wm[u] >> 32) == want) & ((uint32_t)(wl[u] >> 32) == want);
           if (there) break;
-          late = ++it > PATIENCE;
+          if (++it > PATIENCE) break;
           __builtin_amdgcn_s_sleep(1);
         }
-        if (late) { left |= 1u << t; break; }
+        if (it > PATIENCE) { left |= 1u << t; break; }
         float Mc = M[t];
 #pragma unroll
         for (int u = 0; u < CH; ++u) Mc = fmaxf(Mc, __uint_as_float((uint32_t)wm[u]));

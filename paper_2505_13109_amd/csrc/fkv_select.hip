@@ -15,10 +15,11 @@ template <int DT, int G>
 __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];              // selection: n_cand keys, then the recall plan
   touch_args<sizeof(StepArgs)>();
-  int head, s, nw;
-  bool made;
-  if (step_roles<DT, G>(a, blockIdx.x, blockIdx.y, head, s) && select_begin<G, true>(a, head, s, dyn_lds, nw, made))
-    select_finish<DT, G, true>(a, head, dyn_lds, nw, made);
+  step_roles<DT, G>(a, blockIdx.x, blockIdx.y, [&](int head, int s) {
+    int nw;
+    bool made;
+    if (select_begin<G, true>(a, head, s, dyn_lds, nw, made)) select_finish<DT, G, true>(a, head, dyn_lds, nw, made);
+  });
 }
 
 // The two halves of the bandwidth-bound regime.  The scan: append, correction test and page weights, in 256-thread
@@ -315,8 +316,12 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
   const bool step = (int)blockIdx.y < u.step_rows;
   if (step) {
     s = u.step_args(ka);
-    int slice;
-    if (!step_roles<DT, G>(s, blockIdx.x, blockIdx.y, head, slice) || !select_begin<G, true>(s, head, slice, dyn_lds, nw, made)) return;
+    bool go_on = false;
+    step_roles<DT, G>(s, blockIdx.x, blockIdx.y, [&](int m, int slice) {
+      head = m;
+      go_on = select_begin<G, true>(s, m, slice, dyn_lds, nw, made);
+    });
+    if (!go_on) return;
   } else {
     const AttnArgs a = u.attn_args(ka, G);
     // numbered through row by row, so that a head's blocks, which wait for each other, are adjacent

@@ -870,9 +870,11 @@ __device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s,
   made = true;
   if (wave >= nw) return false;
   if (a.g.k_eff == 0) return true;
+  // What select_finish needs of the arguments is read now, while the weights are waited for, and not at the end of the chain
+  // (0.3 us of a layer-step of 8 to 20 us).
+  asm volatile("" ::"s"(a.ids), "s"(a.ids_user), "s"(a.tagged), "s"(a.k), "s"(launch_tag(a.no)), "s"(a.plan_new_slots));
   uint32_t kreg[REGS];
-  made = shared_keys<G, TAGGED, REGS>(a, head, s, nw, key, select_lds(), kreg);
-  if (last) return true;
+  made = __builtin_amdgcn_readfirstlane(shared_keys<G, TAGGED, REGS>(a, head, s, nw, key, select_lds(), kreg));
   if (made) {                                            // the pooled scores, kept for inspection
 #pragma unroll
     for (int u = 0; u < REGS; ++u) {
@@ -880,7 +882,7 @@ __device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s,
       if (j < j1) a.score[(size_t)head * a.max_pages + a.g.cand_lo + j] = key_score(kreg[u]);
     }
   }
-  return false;
+  return last;
 }
 
 // ... and from the keys on, by nw waves: the top-k, the ids out, the recall plan.
@@ -925,7 +927,7 @@ __device__ __forceinline__ void select_finish(const StepArgs& a, int head, uint3
   }
   FKV_STAMP(a, head, 8);
   // the pooled scores, kept for inspection: the group's own, or all of them if it was alone
-  for (int j = (made ? (a.slices - 1) * a.slice : 0) + tid; j < n; j += nt) a.score[(size_t)head * a.max_pages + lo + j] = key_score(key[j]);
+  if (!made) for (int j = tid; j < n; j += nt) a.score[(size_t)head * a.max_pages + lo + j] = key_score(key[j]);
 }
 
 // ---------------------------------------------------------------------------------
@@ -933,27 +935,25 @@ __device__ __forceinline__ void select_finish(const StepArgs& a, int head, uint3
 // present only if its role bit is set; x is the KV head, except that the selection's blocks are numbered through row by
 // row so that a head's are adjacent (they wait for each other: in block order, at most one head's are ever half there).
 // ---------------------------------------------------------------------------------
-// True for a selecting block: of `head`, slice `s`.
-template <int DT, int G>
-__device__ __forceinline__ bool step_roles(const StepArgs& a, int x, int y, int& head, int& s) {
+// select(head, slice): what a selecting block does.
+template <int DT, int G, typename Select>
+__device__ __forceinline__ void step_roles(const StepArgs& a, int x, int y, Select select) {
   if (a.roles & ROLE_APPEND) {
-    if (y == 0) { append_role<DT>(a, x); return false; }
+    if (y == 0) { append_role<DT>(a, x); return; }
     y -= 1;
   }
   if (a.roles & ROLE_CORR) {
-    if (y == 0) { corr_role<DT, G>(a, x); return false; }
+    if (y == 0) { corr_role<DT, G>(a, x); return; }
     y -= 1;
   }
   if (y < a.chunks) {
     if (y == 0) FKV_STAMP(a, x, 0);
     score_role<DT, G, true, STEP_WAVES>(a, x, y);
     if (y == 0) FKV_STAMP(a, x, 1);
-    return false;
+    return;
   }
   const int i = (y - a.chunks) * a.heads + x;
-  head = i >> a.slices_log2;
-  s = i & (a.slices - 1);
-  return true;
+  select(i >> a.slices_log2, i & (a.slices - 1));
 }
 
 }  // namespace fkv
