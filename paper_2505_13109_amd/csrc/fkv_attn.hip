@@ -5,12 +5,12 @@
 
 namespace fkv {
 
-// grid (n_splits, heads); NW wavefronts per block
+// grid (n_splits, n_kv, batch); NW wavefronts per block
 template <int DT, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void attn_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) float attn_lds[];
   touch_args<sizeof(AttnArgs)>();
-  const int head = (int)blockIdx.y;
+  const int head = (int)(blockIdx.z * a.n_kv + blockIdx.y);
   const AttnLeft left = attn_block<DT, NW, false, false>(a, blockIdx.x, head, attn_lds);
   if (__builtin_expect(left.any(), 0))
     attn_finish<DT, NW, false, false>(args_from_memory<AttnArgs>(), blockIdx.x, head, left);
@@ -55,7 +55,7 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   a.n_splits = (n_att + a.pps - 1) / a.pps;
   a.share = (d.G * D + a.n_splits - 1) / a.n_splits;
   a.out = io.out; a.g = g; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k; a.status = io.status; a.tstamp = io.tstamp;
-  dim3 grid(a.n_splits, heads);
+  dim3 grid(a.n_splits, d.n_kv, d.batch);
   constexpr int NW = 4;
   const size_t lds = attn_lds_floats(NW, d.G) * sizeof(float);
   if (ev_begin) (void)hipEventRecord(ev_begin, st);

@@ -28,13 +28,15 @@ __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
 // pages -- the smaller block leaves the unit's slots in finer pieces, so that more blocks are in different phases
 // (loading, computing, draining) at any time; blocks that take several chunks, pipelined or not, are slower than either.
 // A head's chunks are adjacent in block order (blocks that run together read one stretch of memory: 28.2 us with the KV
-// cache between two scans of that size, 30.0 us with the heads next to each other): grid (chunks, heads), below rows of
-// the same width for the other two roles.
+// cache between two scans of that size, 30.0 us with the heads next to each other): grid (chunks, rows), row by row first
+// the other two roles, then a head each; beyond kGridRows rows (a grid dimension ends at 65535) folded into a third dimension.
 constexpr int SCAN_WAVES = 4;
+constexpr int kGridRows = 1 << 15;
 template <int DT, int G>
 __global__ __launch_bounds__(SCAN_WAVES * 64) void scan_kernel(StepArgs a) {
   touch_args<sizeof(StepArgs)>();
-  const int y = blockIdx.y;
+  const int y = (int)(blockIdx.z * kGridRows + blockIdx.y);
+  if (y >= a.other_rows + a.heads) return;
   if (y < a.other_rows) {
     int i = y * a.chunks + blockIdx.x;
     if (a.roles & ROLE_APPEND) {
@@ -175,7 +177,8 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   a.P = reinterpret_cast<unsigned long long*>(io.P_plain);
   if (!grant_lds(&select_kernel<G>, lds, granted_select)) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
-  scan_kernel<DT, G><<<dim3(a.chunks, a.other_rows + heads), SCAN_WAVES * 64, 0, st>>>(a);
+  const int scan_rows = a.other_rows + heads;
+  scan_kernel<DT, G><<<dim3(a.chunks, scan_rows < kGridRows ? scan_rows : kGridRows, (scan_rows + kGridRows - 1) / kGridRows), SCAN_WAVES * 64, 0, st>>>(a);
   select_kernel<G><<<heads * a.slices, SEL_THREADS, lds, st>>>(a);
   *io.P_tagged = false;
   return 2;

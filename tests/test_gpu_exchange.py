@@ -273,3 +273,25 @@ def test_contexts_decoding_at_once_on_streams_of_their_own(n_ctx):
             assert all(_close(a, b) for a, b in zip(got[i], want[i])), (rounds, i)
     for g in gs:
         g.close()
+
+
+def test_more_heads_than_a_grid_dimension_holds():
+    """65600 (request, KV head) pairs, with scoring, selection and attention each a launch of its own: the requests on both
+    sides of the 32768th and 65536th pair against a context of those requests alone."""
+    batch, n_kv = 8200, 8
+    x = _Inputs(3, batch, n_kv, n_kv, 130, 2)
+    kw = dict(budget=96, sink=32, window=32, max_ctx=160)
+    pick = [0, 4095, 4096, 8191, 8192, 8199]
+    g, e = x.context(**kw), x.context(batch=len(pick), **kw)
+    out, ref = x.out(), torch.zeros((len(pick), n_kv, 128), dtype=torch.float32, device="cuda")
+    g.load_prefix(0, x.K, x.V)
+    e.load_prefix(0, x.K[pick].contiguous(), x.V[pick].contiguous())
+    for t in range(2):
+        _step(g, x.q[t], x.k[t], x.v[t], out)
+        _step(e, *(z[t][pick].contiguous() for z in (x.q, x.k, x.v)), ref)
+        assert g.step_launches(0) == 3
+        assert np.array_equal(g.debug_read(0, B.DBG_ACTIVE_IDS)[pick], e.debug_read(0, B.DBG_ACTIVE_IDS)), t
+        assert torch.isfinite(out).all() and _close(out[pick], ref), t
+    g.health(0)
+    g.close()
+    e.close()
