@@ -44,7 +44,7 @@ extern "C" {
 #define FKV_ERANGE  -3   /* layer / page / token count out of range               */
 #define FKV_ENOMEM  -4   /* arena too small                                       */
 #define FKV_EHIP    -5   /* a HIP call failed; see fkv_last_error                 */
-#define FKV_ETIMEOUT -6  /* a kernel gave up a bounded wait for another block     */
+#define FKV_ETIMEOUT -6  /* a kernel gave up a wait for values of its own launch   */
 
 #define FKV_DTYPE_FP16 0
 #define FKV_DTYPE_BF16 1
@@ -122,13 +122,18 @@ const char* fkv_last_error(const fkv_ctx* ctx);
 /* Tokens currently cached for `layer` (host-side counter), or a negative code. */
 int fkv_context_len(const fkv_ctx* ctx, int32_t layer);
 
-/* Did every kernel of `layer` so far finish its bounded waits?  In the one-launch layer-step the
- * attention blocks of a corrected head wait for that head's selection, made by other blocks of the
- * same launch; the wait is bounded (about 0.1 s).  A block that gives up makes the failure visible
- * on the data path -- every output row of that KV head's query group is NaN -- and sets a flag.
- * With the KV in a host pool the waves that gave up also left page-cache slots unfilled: the outputs of
- * every later step of the layer stay NaN while the flag is up, and after FKV_ETIMEOUT the layer has to
- * be loaded again (fkv_load_prefix) before its results mean anything.
+/* Did the blocks of every launch of `layer` so far end with what they needed?  Blocks of one launch hand each other
+ * values: page weights and, where several share a head's candidate list, maxima, sums and keys (fkv_decode_step,
+ * fkv_page_select); a corrected head's picked ids (fkv_decode_step); the sums of attention's splits (fkv_decode_step,
+ * fkv_sparse_decode_attn and its static form).  The block waited for may not be running: other launches -- further
+ * contexts on streams of their own, other programs -- may hold the compute units.  A block that has waited for a few
+ * milliseconds makes what it waits for itself, so no result depends on such a wait: page ids and flags are the same
+ * bit for bit, outputs to fp32 rounding; the launch takes some 10 ms longer.  Contexts may therefore decode at once,
+ * each with its own stream and calling thread, in any number.
+ * What is left to report is a picked id that a block has just made and cannot read back: every output row of that KV
+ * head's query group is NaN, and a flag is set.  With the KV in a host pool page-cache slots may then be unfilled: the
+ * outputs of every later step of the layer stay NaN while the flag is up, and after FKV_ETIMEOUT the layer has to be
+ * loaded again (fkv_load_prefix) before its results mean anything.
  * That is not expected to happen; this call synchronises the device, returns FKV_ETIMEOUT if it did
  * and clears the flag.  Blocking. */
 int fkv_health(fkv_ctx* ctx, int32_t layer);

@@ -42,10 +42,10 @@ int fkv_profile_select(fkv_ctx* ctx, const void* q_dev, size_t q_layer_stride, i
 int fkv_profile_launch_floor(fkv_ctx* ctx, int32_t layer, int32_t reps, void* stream, double* total_ms,
                              int32_t* grid, int32_t* lds_bytes);
 
-/* Test hook for the bounded wait of the one-launch layer-step: while on, the attention waves of a
- * corrected head wait for picked page ids tagged with an epoch that never comes (the host asks them to
- * wait for the wrong one).  Every kernel still ends; the wait runs out after about 0.1 s, the head's
- * output rows are NaN and fkv_health reports FKV_ETIMEOUT.  Host-side switch, no GPU work. */
+/* Test hook for what fkv_health reports: while on, the attention waves of a corrected head wait for picked page ids
+ * under a tag that no launch has had yet, and go on waiting for them after their block has made the selection itself.
+ * Every kernel still ends; the head's output rows are NaN and fkv_health returns FKV_ETIMEOUT.  Host-side switch, no
+ * GPU work. */
 int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on);
 
 /* Test hook for what a block does when another block of its launch keeps it waiting too long: waits of these kinds
