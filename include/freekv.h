@@ -126,9 +126,9 @@ int fkv_context_len(const fkv_ctx* ctx, int32_t layer);
  * values: page weights and, where several share a head's candidate list, maxima, sums and keys (fkv_decode_step,
  * fkv_page_select); a corrected head's picked ids (fkv_decode_step); the sums of attention's splits (fkv_decode_step,
  * fkv_sparse_decode_attn and its static form).  The block waited for may not be running: other launches -- further
- * contexts on streams of their own, other programs -- may hold the compute units.  A block that has waited for a few
+ * contexts on streams of their own, other programs -- may hold the compute units.  A block that has waited for some
  * milliseconds makes what it waits for itself, so no result depends on such a wait: page ids and flags are the same
- * bit for bit, outputs to fp32 rounding; the launch takes some 10 ms longer.  Contexts may therefore decode at once,
+ * bit for bit, outputs to fp32 rounding; the launch takes some milliseconds more.  Contexts may therefore decode at once,
  * each with its own stream and calling thread, in any number.
  * What is left to report is a picked id that a block has just made and cannot read back: every output row of that KV
  * head's query group is NaN, and a flag is set.  With the KV in a host pool page-cache slots may then be unfilled: the

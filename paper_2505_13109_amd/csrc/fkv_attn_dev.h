@@ -154,7 +154,7 @@ __device__ __forceinline__ int attend_unit(const AttendList& al, const PoolDesc&
 __host__ __device__ constexpr int attn_lds_floats(int NW, int G) { return NW * G * (D + 4) + NW * 32 + G * (D / 2 + 4); }
 
 // One output (query head gg, channel c) by one thread, over the whole attend list in fp32: for outputs whose block waited for
-// the others in vain.  Slow (about 10 ms for 65 pages), but it needs nobody.  corrected: the picked ids are this launch's;
+// the others in vain.  Slow (3 ms for 65 pages, 9 for 129), but it needs nobody.  corrected: the picked ids are this launch's;
 // should they not be there (a test sees to that; a block makes them before it comes here), the output is NaN.
 template <int DT, bool FUSED, bool HOSTFUSED>
 __device__ __forceinline__ float output_alone(const AttnArgs& a, int head, bool corrected, int gg, int c) {
@@ -522,6 +522,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   const int own_lo = split * a.share, own_hi = min(items, own_lo + a.share);
   unsigned long long* const po = a.part + (size_t)head * a.max_splits * items;
   unsigned long long* const pml = a.part_ml + (size_t)head * a.max_splits * G * 2;
+  constexpr int patience = HOSTFUSED ? PATIENCE_HOST : PATIENCE;
   const uint32_t want = tag + (a.impatient & WAIT_SPLITS ? 2u : 0u);      // (or a tag that no word has yet)
   constexpr int IT = (MAX_G * D + NW * 64 - 1) / (NW * 64);
   float o[IT], den[IT], M[IT];
@@ -585,10 +586,10 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
           for (int u = 0; u < CH; ++u)
             there = there & ((uint32_t)(wo[u] >> 32) == want) & ((uint32_t)(wm[u] >> 32) == want) & ((uint32_t)(wl[u] >> 32) == want);
           if (there) break;
-          if (++it > PATIENCE) break;
+          if (++it > patience) break;
           __builtin_amdgcn_s_sleep(1);
         }
-        if (it > PATIENCE) { left |= 1u << t; break; }
+        if (it > patience) { left |= 1u << t; break; }
         float Mc = M[t];
 #pragma unroll
         for (int u = 0; u < CH; ++u) Mc = fmaxf(Mc, __uint_as_float((uint32_t)wm[u]));

@@ -229,8 +229,11 @@ __device__ __forceinline__ uint32_t launch_tag(const LaunchNo& n) { return n.dev
 // launch's to decide: other launches may hold the compute units, with waits of their own.  So nothing depends on it: a block
 // whose patience ends makes what it waits for itself, from what was in memory before the launch, bit for bit what the other
 // block would have made, and goes on (and its compute unit is free again soon).
-constexpr int PATIENCE = 1 << 12;       // polls: a few milliseconds (a launch by itself: microseconds)
-// Polls before a thread gives up on words that its block has written by then: that many only if a test sees to it.
+// Polls: 0.7 ms where a wave waits for ids, 2 ms where a thread waits for sums (0.17 and 0.5 us a turn; in a launch by
+// itself a wait takes microseconds).  Blocks of a launch that fetches pages from a host pool wait for one another's transfers
+// too, and to do without them is expensive there: eight times as long.
+constexpr int PATIENCE = 1 << 12, PATIENCE_HOST = 8 * PATIENCE;
+// Polls before a thread gives up on words that its block has written by then (10 ms): that many only if a test sees to it.
 constexpr int MAX_POLLS = 1 << 16;
 
 // threadIdx.x once more, from the wave's number in a scalar register: what is worked out from this after a stretch of code that

@@ -230,8 +230,8 @@ def test_c4_every_layer_four_steps(oracle_pool):
 
 def test_bench_saturated_shape_batch_32(oracle_pool):
     """The shape bench.py reports as `saturated_shape`, at size: the config-2 shape with 32 requests of 32K
-    tokens, 2 layers, 4 steps, in the dispatch the bench times there (separate launches: scoring blocks that
-    take several chunks of 4 passes, the selection in a launch of its own, one attention block per head)."""
+    tokens, 2 layers, 4 steps, in the dispatch the bench times there (separate launches: the scan in blocks of 64
+    pages, the selection in a launch of its own, one attention block per head)."""
     from harness import PoolPair
     wl = W.get_workload("c2").scaled(batch=32)
     pr = PoolPair(wl, [0, 17], oracle_pool, steps=4)
@@ -577,7 +577,7 @@ def test_streamed_recall_into_an_nhd_pool():
 
 def test_a_wait_that_runs_out_is_reported():
     """The bounded wait of a corrected head's attention: with the library's test hook on, the waves that
-    attend picked pages wait for ids of an epoch that never comes.  Every kernel still ends; the failure
+    attend picked pages wait for ids under a tag that never comes.  Every kernel still ends; the failure
     shows on the data path (the outputs of the query groups are NaN) and fkv_health reports it once.
     With the hook off again the same context decodes normally."""
     import paper_2505_13109_amd as fkv
@@ -685,8 +685,7 @@ def test_many_requests_take_the_bandwidth_bound_dispatch():
 
 
 def test_big_scan_blocks_take_several_chunks():
-    """24 requests x 16 KV heads x 12K tokens: the scoring launch is past the size where a block takes
-    several chunks of its head in turn (and 4 passes per chunk)."""
+    """24 requests x 16 KV heads x 12K tokens: scoring in a launch of its own, several blocks of 64 pages per head."""
     wl = W.Workload("scan", 1, 24, 16, 16, "bf16", 12000, 1024, 64, 64, 0.8, 3, 0.8, 0.6, 71)
     pr = _pair(wl, [0])
     for t in range(wl.steps):
@@ -803,17 +802,16 @@ def test_a_seeded_sample_of_small_shapes():
 
 
 def test_selection_paths_of_the_separate_step_kernel():
-    """The host-pool placement always takes the separate step kernel.  Candidate counts on both sides of its
-    register / LDS-staging thresholds, for small and large groups, with the selection inside the scoring
-    launch (few blocks) and in a launch of its own (many blocks)."""
+    """Long candidate lists with the KV in the host pool, each with its recall plan, for small and large groups: one to
+    sixteen selecting blocks per head.  (The separate step kernel against the one-launch layer-step: test_gpu_exchange.py.)"""
     shapes = [  # (G, n_kv, batch, ctx): n_cand = ctx/32 - 4
-        (8, 1, 1, 30000),     # 933 candidates, G > 4: in registers, 2 per thread
-        (8, 1, 1, 50000),     # 1558 candidates, G > 4: staged in LDS
-        (3, 2, 1, 50000),     # 1558 candidates, G <= 4: in registers, 4 per thread
-        (4, 2, 2, 90000),     # 2808 candidates: staged in LDS, selection in its own launch
-        (6, 2, 3, 20000),     # 621 candidates: 2 per thread
-        (4, 2, 1, 200000),    # 6246 candidates: the selection of a head spread over 13 blocks (maxima, sums, short lists, merge)
-        (7, 1, 2, 170000),    # 5308 candidates, G = 7, two requests: 11 blocks per head
+        (8, 1, 1, 30000),     # 933 candidates, G > 4: two blocks
+        (8, 1, 1, 50000),     # 1558 candidates: four
+        (3, 2, 1, 50000),     # 1558 candidates, G <= 4: four
+        (4, 2, 2, 90000),     # 2808 candidates: eight
+        (6, 2, 3, 20000),     # 621 candidates: one
+        (4, 2, 1, 200000),    # 6246 candidates: sixteen
+        (7, 1, 2, 170000),    # 5308 candidates, two requests: sixteen
     ]
     for i, (G, n_kv, batch, ctx) in enumerate(shapes):
         wl = W.Workload(f"sel{i}", 1, batch, G * n_kv, n_kv, "bf16", ctx, 1024, 64, 64, 0.8, 5, 0.8, 0.6, 400 + i, placement=1)
