@@ -109,55 +109,71 @@ __global__ __launch_bounds__(256) void offload_kernel(PoolDesc pd, uint16_t* __r
 
 // ---- recall: copy missing pages host pool -> free page-cache slots ---------------
 // miss: [heads][1 + 3k] = count, then k page ids, k slots, k positions in the picked list.
-// A few 1024-thread blocks share the miss lists, four 16 KiB units in flight per block.  Loads
-// from host memory take microseconds to return and hold up the memory pipeline of the compute
-// unit they are issued from, so the blocks are kept few and each one claims a whole compute
+// What bounds it is the host link.  Loads from host memory take microseconds to return and hold up the memory pipeline of
+// the compute unit they are issued from, so the blocks are kept few and each one claims a whole compute
 // unit's LDS: no block of a kernel that uses LDS (attention, scoring) can share that unit.
 constexpr int GATHER_THREADS = 1024;
-constexpr int GATHER_BLOCKS = 16;            // measured: 8 and 16 blocks move 52-53 GB/s, 24 blocks 50, 32 blocks 47
-constexpr int GATHER_UNITS = 4;              // units in flight per block (8 is no faster)
+constexpr int GATHER_BLOCKS = 16;            // (8 and 24 are slower, see below)
+constexpr int GATHER_UNITS = 4;              // streamed recall: units in flight per block (8 is no faster)
+constexpr int GATHER_WAVES = GATHER_THREADS / 64;
+constexpr int GATHER_PIECES = 8;             // a wave has a piece of a unit (2 KiB) in flight
 // One launch serves the miss lists of up to GATHER_MAX_LAYERS layers (the deferred recall of several layers is
 // submitted together); a "head" below is a (layer, KV head) pair, numbered layer-major.
+// The missing units of all chosen heads are numbered through and dealt to the launch's waves one by one, parts of a unit where
+// there are fewer units than waves.  Waves do not wait for each other, so the link never sees a block turn from loading
+// to storing, and nothing is fetched but what is missing.  Eight layers of 8 heads at 32K tokens, two layers to a launch: 47.6 us a
+// launch, against 51.1 where a block fetches four units of one head at a time and rounds up a head's misses to them (a whole
+// step 242 us against 259); two layers of 32 heads at 124K tokens 331 us a step against 343.  Blocks and bytes in flight, the same
+// two: 8 blocks 255 and 337, 24 blocks 243 and 356, pieces of 4 KiB 243 and 335, of 8 KiB 252 and 339.
 __global__ __launch_bounds__(GATHER_THREADS) void gather_kernel(GatherLayers gl, int heads_mode,
                                                                 int k, int n_kv, int n_heads, int max_pages) {
-  extern __shared__ int32_t chunks_of[];     // [n_layers * n_heads]: 4-unit chunks this launch moves for each head
-  const int tid = threadIdx.x;
+  extern __shared__ int32_t first_of[];      // [n_layers * n_heads]: units of the heads up to and including this one
+  __shared__ uint32_t wave_total[GATHER_WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_all = gl.n * n_heads;
-  // The chunks (GATHER_UNITS units each) of all chosen heads, numbered through, are dealt to the blocks in turn, so that every
-  // block moves the same amount whatever the heads' miss counts are (a corrected-heads launch
-  // serves about every other head, with anything from 0 to k misses).
-  for (int h = tid; h < n_all; h += GATHER_THREADS) {
-    const int li = h / n_heads, head = h % n_heads;
-    const bool chosen = heads_mode == 0 || ((heads_mode == 1) == (gl.flags[li][head] != 0));
-    chunks_of[h] = chosen ? (gl.miss[li][(size_t)head * (1 + 3 * k)] + GATHER_UNITS - 1) / GATHER_UNITS : 0;
+  uint32_t total = 0;
+  for (int h0 = 0; h0 < n_all; h0 += GATHER_THREADS) {
+    const int h = h0 + tid, hc = min(h, n_all - 1), li = hc / n_heads, head = hc % n_heads;
+    const int missing = gl.miss[li][(size_t)head * (1 + 3 * k)];
+    const bool flagged = heads_mode != 0 && gl.flags[li][head] != 0;
+    const uint32_t n = h < n_all && (heads_mode == 0 || (heads_mode == 1) == flagged) ? (uint32_t)missing : 0u;
+    const uint32_t incl = wave_scan_u32(n);
+    if (lane == 63) wave_total[wave] = incl;
+    __syncthreads();
+    uint32_t before = total;
+    for (int w = 0; w < GATHER_WAVES; ++w) {
+      const uint32_t v = wave_total[w];
+      if (w < wave) before += v;
+      total += v;
+    }
+    if (h < n_all) first_of[h] = (int32_t)(before + incl);
+    __syncthreads();
   }
-  __syncthreads();
-  int first = 0;                                // number of the head's first chunk
-  for (int h = 0; h < n_all; ++h) {
-    const int n_chunks = chunks_of[h];
-    const int c_begin = first;
-    first += n_chunks;
-    // chunks of this head that are this block's: c_begin + j with (c_begin + j) % gridDim.x == blockIdx.x
-    int j = ((int)blockIdx.x - c_begin % (int)gridDim.x + (int)gridDim.x) % (int)gridDim.x;
-    if (j >= n_chunks) continue;
-    const int li = h / n_heads, head = h % n_heads;
+  const int units = (int)total, waves = (int)gridDim.x * GATHER_WAVES;
+  const int parts = units >= waves ? 1 : units * 2 >= waves ? 2 : GATHER_PIECES;      // of a unit, a wave each
+  for (int i = wave * (int)gridDim.x + (int)blockIdx.x; i < units * parts; i += waves) {
+    const int unit = i / parts, part = i % parts;
+    int lo = 0, hi = n_all - 1;              // the head whose unit it is: the first with first_of > unit
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (first_of[mid] > unit) hi = mid; else lo = mid + 1;
+    }
+    const int h = __builtin_amdgcn_readfirstlane(lo), li = h / n_heads, head = h % n_heads;
+    const int r = unit - (h > 0 ? __builtin_amdgcn_readfirstlane(first_of[h - 1]) : 0);
     const PoolDesc& pd = gl.pd[li];
     const int32_t* mh = gl.miss[li] + (size_t)head * (1 + 3 * k);
-    const int n = mh[0];
-    const uint16_t* src_head = gl.host_pool[li] + (size_t)head * max_pages * UNIT_ELEMS;
-    uint16_t* dst_head = pd.pool + ((size_t)head * pd.units_per_head + pd.sel_base) * UNIT_ELEMS;
-    for (; j < n_chunks; j += gridDim.x) {
-      const int i0 = j * GATHER_UNITS;
-      uint4 w[GATHER_UNITS];
+    const int page = __builtin_amdgcn_readfirstlane(mh[1 + r]), slot = __builtin_amdgcn_readfirstlane(mh[1 + k + r]);
+    const uint4* src = reinterpret_cast<const uint4*>(gl.host_pool[li] + ((size_t)head * max_pages + page) * UNIT_ELEMS) + lane;
+    uint4* dst = reinterpret_cast<uint4*>(pd.pool + ((size_t)head * pd.units_per_head + pd.sel_base + slot) * UNIT_ELEMS) + lane;
+    constexpr int PIECE = UNIT_BYTES / 16 / GATHER_PIECES;                            // 16-byte words
+    const int p0 = part * (GATHER_PIECES / parts);
+#pragma unroll 1
+    for (int p = p0; p < p0 + GATHER_PIECES / parts; ++p) {
+      uint4 w[PIECE / 64];
 #pragma unroll
-      for (int u = 0; u < GATHER_UNITS; ++u) {
-        const int i = min(i0 + u, n - 1);
-        w[u] = reinterpret_cast<const uint4*>(src_head + (size_t)mh[1 + i] * UNIT_ELEMS)[tid];
-      }
+      for (int j = 0; j < PIECE / 64; ++j) w[j] = src[p * PIECE + j * 64];
 #pragma unroll
-      for (int u = 0; u < GATHER_UNITS; ++u) {
-        if (i0 + u < n) reinterpret_cast<uint4*>(dst_head + (size_t)mh[1 + k + i0 + u] * UNIT_ELEMS)[tid] = w[u];
-      }
+      for (int j = 0; j < PIECE / 64; ++j) dst[p * PIECE + j * 64] = w[j];
     }
   }
 }

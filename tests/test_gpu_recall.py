@@ -1,0 +1,56 @@
+"""The recall kernel where its division of the work changes: from one missing unit to more than the launch has waves, heads
+without a miss among the others, more heads than a block has threads."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_13109_amd as fkv
+from paper_2505_13109_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch,n_kv,per_head", [
+    (1, 1, [1]),                                   # a single unit
+    (1, 8, [0, 3, 0, 0, 5, 1, 0, 8]),              # fewer units than waves: eight waves to a unit
+    (2, 8, [16, 0, 7, 16, 9, 0, 16, 1] * 2),       # ... two to a unit
+    (2, 8, [16] * 15 + [15]),                      # 255: one short of a unit a wave
+    (3, 8, [16, 13, 0, 16, 16, 16, 11, 16] * 3),   # more units than waves
+    (137, 8, [1, 0, 2, 0, 1, 1, 0, 1] * 137),      # more heads than a block has threads
+])
+def test_every_missing_unit_is_recalled_once(batch, n_kv, per_head):
+    ctx, k = 20 * 32 + 9, 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(len(per_head) + per_head[0])
+    K, V = (torch.randn((batch, ctx, n_kv, 128), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    g = fkv.FreeKV(n_layers=1, batch=batch, n_q_heads=n_kv, n_kv_heads=n_kv, max_ctx=704, budget=64 + k * 32, sink=32, window=32,
+                   tau=0.8, dtype="bf16", placement=fkv.FKV_PLACE_HOST)
+    g.load_prefix(0, K, V)
+    rng = np.random.default_rng(3)
+    ids = np.full((batch, n_kv, k), -1, dtype=np.int32)
+    for h, n in enumerate(per_head):
+        ids[h // n_kv, h % n_kv, :n] = np.sort(rng.choice(np.arange(1, 19), n, replace=False))
+    cached = g.dev_arena.clone()
+    g.recall_pages(0, torch.from_numpy(ids).cuda())
+    assert np.array_equal(g.debug_read(0, B.DBG_MISS)[..., 0].reshape(-1), per_head)
+    n_slots = k + 3
+    pool = torch.zeros((batch, n_slots, 2, 32, n_kv, 128), dtype=torch.bfloat16, device="cuda")
+    pages = torch.zeros((batch, n_kv, n_slots), dtype=torch.int32, device="cuda")
+    g.export_nhd(0, pool, pages, use=fkv.FKV_USE_PENDING)
+    torch.cuda.synchronize()
+    assert torch.equal(pages[:, :, 1:1 + k].cpu(), torch.from_numpy(ids))
+    for b in range(batch):
+        for m in range(n_kv):
+            n = per_head[b * n_kv + m]
+            if n == 0:
+                continue
+            at = torch.from_numpy(ids[b, m, :n].astype(np.int64)).cuda()
+            for x, which in ((K, 0), (V, 1)):
+                want = x[b, :, m][: 20 * 32].reshape(20, 32, 128)[at]
+                assert torch.equal(pool[b, 1:1 + n, which, :, m], want), (b, m, which)
+    # nothing else of the page pool is written: a head without a miss keeps its bytes
+    per = (1 + 3 + 2 * k) * 16384
+    before, after = (t[: batch * n_kv * per].view(batch * n_kv, per) for t in (cached, g.dev_arena))
+    same = (before == after).all(dim=1).cpu().numpy()
+    assert np.array_equal(same, np.array(per_head) == 0)
+    g.close()
