@@ -146,8 +146,9 @@ struct fkv_ctx {
   // Deferred recalls of one-launch layer-steps that are not submitted yet: a cross-stream dependency costs the host
   // three HIP calls and each stream a few microseconds, so several layers of a decode step share one.
   std::vector<int> deferred;
-  int defer_group = 1;                // layers per submission: a quarter of the layers, so that a recall submitted with the
-                                      // group's last layer still has three quarters of a decode step before it is needed;
+  int defer_group = 1;                // layers per submission: half of the layers, so that one half's recall is under way
+                                      // while the other half decodes, with the fewest hand-overs (8 layers at 32K tokens,
+                                      // 210 us a step; in quarters 230; all in one, which the next step then waits for, 350);
                                       // at most GATHER_MAX_LAYERS (4, 8 and 16 measure the same on a 32-layer stack)
   hipStream_t deferred_st = nullptr, deferred_cs = nullptr;
   std::vector<std::pair<hipEvent_t, hipStream_t>> waited;   // (recall event, stream that already waits for its latest record)
@@ -384,13 +385,24 @@ static void forget_waits(fkv_ctx* ctx, hipEvent_t ev) {     // `ev` has just bee
     if (w[i].first == ev) { w[i] = w.back(); w.pop_back(); } else ++i;
 }
 
+// Whether an event on `st` may be recorded by the launch it follows: that takes no packet of its own in the stream's queue
+// (a hand-over between two streams and back costs 7 us so and 10.5 us with hipEventRecord), but a capture does not see it.
+static bool launch_records(hipStream_t st) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+  return capture == hipStreamCaptureStatusNone;
+}
+
 // Submit the deferred recalls on the list: one dependency of the copy stream on the compute stream, one gather launch
 // for all listed layers' uncorrected heads, one event that every listed layer's next step looks at.
-static int flush_deferred(fkv_ctx* ctx) {
+// forked: the compute stream's last launch has recorded ev_fork.
+static int flush_deferred(fkv_ctx* ctx, bool forked = false) {
   if (ctx->deferred.empty()) return FKV_OK;
   hipStream_t st = ctx->deferred_st, cs = ctx->deferred_cs;
+  hipEvent_t done = ctx->layers[ctx->deferred.back()].ev_recall;
+  const bool by_launch = cs != st && launch_records(cs);
   if (cs != st) {
-    FKV_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
+    if (!forked) FKV_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
     FKV_HIP(ctx, hipStreamWaitEvent(cs, ctx->ev_fork, 0));
   }
   for (size_t i0 = 0; i0 < ctx->deferred.size(); i0 += GATHER_MAX_LAYERS) {
@@ -403,13 +415,12 @@ static int flush_deferred(fkv_ctx* ctx) {
       gl.flags[gl.n] = ctx->flags(l);
       gl.n += 1;
     }
-    launch_gather(ctx->dims, gl, FKV_HEADS_UNFLAGGED, cs);
+    launch_gather(ctx->dims, gl, FKV_HEADS_UNFLAGGED, cs, by_launch && i0 + GATHER_MAX_LAYERS >= ctx->deferred.size() ? done : nullptr);
   }
   int rc = after_launch(ctx, "gather kernel");
   if (rc) return rc;
-  hipEvent_t done = ctx->layers[ctx->deferred.back()].ev_recall;
   if (cs != st) {
-    FKV_HIP(ctx, hipEventRecord(done, cs));
+    if (!by_launch) FKV_HIP(ctx, hipEventRecord(done, cs));
     forget_waits(ctx, done);
   }
   for (int l : ctx->deferred) {
@@ -485,7 +496,7 @@ int fkv_create(const fkv_config* cfg, void* dev_arena, size_t dev_bytes, void* h
   ctx->dev = static_cast<char*>(dev_arena);
   ctx->host = cfg->placement == FKV_PLACE_HOST ? static_cast<char*>(host_arena) : nullptr;
   ctx->layers.resize(cfg->n_layers);
-  ctx->defer_group = cfg->n_layers / 4 < 1 ? 1 : cfg->n_layers / 4 > GATHER_MAX_LAYERS ? GATHER_MAX_LAYERS : cfg->n_layers / 4;
+  ctx->defer_group = cfg->n_layers / 2 < 1 ? 1 : cfg->n_layers / 2 > GATHER_MAX_LAYERS ? GATHER_MAX_LAYERS : cfg->n_layers / 2;
   hipError_t e = hipMemset(dev_arena, 0, l.total);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   const unsigned ev_flags = hipEventDisableTiming;
@@ -634,9 +645,16 @@ int fkv_page_select(fkv_ctx* ctx, int32_t layer, const void* q_dev, int32_t* pag
   return FKV_OK;
 }
 
-// copy the missing pages of the PENDING selection's chosen heads (by flag or by mask) into their slots
-static int recall_missing(fkv_ctx* ctx, int layer, int heads_mode, const uint8_t* select_by, hipStream_t cs) {
+// copy the missing pages of the PENDING selection's chosen heads (by flag or by mask) into their slots; `done`, if not null, is
+// recorded behind it
+static int recall_missing(fkv_ctx* ctx, int layer, int heads_mode, const uint8_t* select_by, hipStream_t cs, hipEvent_t done = nullptr) {
   LayerState& ls = ctx->layers[layer];
+  if (done && (ctx->cfg.recall_mode == FKV_RECALL_MEMCPY || ctx->nhd_pool || !launch_records(cs))) {
+    const int rc = recall_missing(ctx, layer, heads_mode, select_by, cs);
+    if (rc) return rc;
+    FKV_HIP(ctx, hipEventRecord(done, cs));
+    return FKV_OK;
+  }
   if (ls.offload_outstanding) {   // a page offloaded moments ago may be picked already
     FKV_HIP(ctx, hipStreamWaitEvent(cs, ls.ev_offload, 0));
   }
@@ -673,22 +691,26 @@ static int recall_missing(fkv_ctx* ctx, int layer, int heads_mode, const uint8_t
   GatherLayers gl{};
   gl.n = 1;
   gl.pd[0] = ctx->pool_desc(layer); gl.host_pool[0] = ctx->host_pool(layer); gl.miss[0] = ctx->miss(layer); gl.flags[0] = select_by;
-  launch_gather(ctx->dims, gl, heads_mode, cs);
+  launch_gather(ctx->dims, gl, heads_mode, cs, done);
   return after_launch(ctx, "gather kernel");
+}
+
+static int recall_pending(fkv_ctx* ctx, int layer, int heads, hipStream_t cs, hipEvent_t done) {
+  if (ctx->cfg.placement != FKV_PLACE_HOST) return FKV_OK;
+  LayerState& ls = ctx->layers[layer];
+  if (!ls.have_pending) return ctx->fail(FKV_ESTATE, "recall before page_select");
+  if (heads != FKV_HEADS_ALL && !ls.have_flags) return ctx->fail(FKV_ESTATE, "recall by flag before corr_check");
+  int rc = recall_missing(ctx, layer, heads, ctx->flags(layer), cs, done);
+  if (rc) return rc;
+  ls.recalled |= heads == FKV_HEADS_ALL ? 3 : heads == FKV_HEADS_FLAGGED ? 1 : 2;
+  return FKV_OK;
 }
 
 int fkv_recall_pending(fkv_ctx* ctx, int32_t layer, int32_t heads, void* copy_stream) {
   FKV_CHECK_LAYER(ctx, layer);
   FKV_FLUSH(ctx);
   if (heads < 0 || heads > 2) return ctx->fail(FKV_EINVAL, "bad heads selector");
-  if (ctx->cfg.placement != FKV_PLACE_HOST) return FKV_OK;
-  LayerState& ls = ctx->layers[layer];
-  if (!ls.have_pending) return ctx->fail(FKV_ESTATE, "recall before page_select");
-  if (heads != FKV_HEADS_ALL && !ls.have_flags) return ctx->fail(FKV_ESTATE, "recall by flag before corr_check");
-  int rc = recall_missing(ctx, layer, heads, ctx->flags(layer), static_cast<hipStream_t>(copy_stream));
-  if (rc) return rc;
-  ls.recalled |= heads == FKV_HEADS_ALL ? 3 : heads == FKV_HEADS_FLAGGED ? 1 : 2;
-  return FKV_OK;
+  return recall_pending(ctx, layer, heads, static_cast<hipStream_t>(copy_stream), nullptr);
 }
 
 int fkv_recall_pages(fkv_ctx* ctx, int32_t layer, const int32_t* page_ids_dev, const uint8_t* head_mask_dev, void* copy_stream) {
@@ -884,6 +906,9 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
     lio.max_splits = ctx->lay.max_splits;
     lio.impatient = ctx->impatient;
     lio.lose_selection = ctx->lose_selection;
+    // with the KV in a host pool: whether the deferred recalls are submitted behind this layer's launch
+    const bool last_of_group = host_pool && ((int)ctx->deferred.size() + 1 >= ctx->defer_group || layer == ctx->cfg.n_layers - 1);
+    lio.done = last_of_group && cs != st && launch_records(st) ? ctx->ev_fork : nullptr;
     lio.launch_grid = &ls.last_grid;
     lio.launch_lds = &ls.last_lds;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -914,8 +939,8 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
       ctx->deferred.push_back(layer);
       ctx->deferred_st = st;
       ctx->deferred_cs = cs;
-      if ((int)ctx->deferred.size() >= ctx->defer_group || layer == ctx->cfg.n_layers - 1) {
-        rc = flush_deferred(ctx);
+      if (last_of_group) {
+        rc = flush_deferred(ctx, lio.done != nullptr);
         if (rc) return rc;
       }
       return commit_layer(ctx, layer);
@@ -931,18 +956,16 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
   bool deferred = false;
   if (host_pool) {
     // corrected heads: recall before this step's attention (Sec. 3.3)
-    rc = fkv_recall_pending(ctx, layer, FKV_HEADS_FLAGGED, compute_stream);
+    rc = recall_pending(ctx, layer, FKV_HEADS_FLAGGED, st, cs != st ? ctx->ev_fork : nullptr);
     if (rc) return rc;
     // other heads: recall for the next step on the copy stream, off the critical path
     // (Sec. 3.2).  It writes only slots that this step's attention does not read, so it may run
     // beside it; it starts behind the corrected heads' recall so that it does not share the
     // host link with the transfer the attention is waiting for.
     if (cs != st) {
-      FKV_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
       FKV_HIP(ctx, hipStreamWaitEvent(cs, ctx->ev_fork, 0));
-      rc = fkv_recall_pending(ctx, layer, FKV_HEADS_UNFLAGGED, copy_stream);
+      rc = recall_pending(ctx, layer, FKV_HEADS_UNFLAGGED, cs, ls.ev_recall);
       if (rc) return rc;
-      FKV_HIP(ctx, hipEventRecord(ls.ev_recall, cs));
       forget_waits(ctx, ls.ev_recall);
       ls.recall_event = ls.ev_recall;
       deferred = true;     // the next step of this layer waits for it, not this step's attention
@@ -960,7 +983,7 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
     if (rc) return rc;
   }
   if (host_pool && cs == st) {
-    rc = fkv_recall_pending(ctx, layer, FKV_HEADS_UNFLAGGED, compute_stream);
+    rc = recall_pending(ctx, layer, FKV_HEADS_UNFLAGGED, st, nullptr);
     if (rc) return rc;
   }
   ls.recall_outstanding = deferred;

@@ -2,6 +2,8 @@
 #include "fkv_device.h"
 #include "fkv_plan_dev.h"
 
+#include <hip/hip_ext.h>
+
 namespace fkv {
 
 // ---- bulk load: grid (n_pages, n_kv, batch), 256 threads ------------------------
@@ -328,8 +330,11 @@ void launch_plan(const Dims& d, int32_t* new_ids, const int32_t* act_ids, const 
   plan_kernel<<<grid, 64, plan_lds_ints(d.k) * sizeof(int32_t), st>>>(new_ids, act_ids, act_slots, new_slots, miss, d.k, d.n_kv, n_full);
 }
 
-void launch_gather(const Dims& d, const GatherLayers& gl, int heads, hipStream_t st) {
-  if (d.k == 0 || gl.n <= 0) return;
+void launch_gather(const Dims& d, const GatherLayers& gl, int heads, hipStream_t st, hipEvent_t done) {
+  if (d.k == 0 || gl.n <= 0) {
+    if (done) (void)hipEventRecord(done, st);
+    return;
+  }
   static bool raised = false;
   const int hog = d.max_lds > 64 * 1024 ? d.max_lds - 1024 : 64 * 1024 - 1024;   // (nearly) all of a unit's LDS
   if (!raised) {
@@ -349,7 +354,10 @@ void launch_gather(const Dims& d, const GatherLayers& gl, int heads, hipStream_t
       part.miss[i] = gl.miss[l0 + i]; part.flags[i] = gl.flags[l0 + i];
     }
     const int blocks = n_heads * part.n < GATHER_BLOCKS ? n_heads * part.n : GATHER_BLOCKS;
-    gather_kernel<<<blocks, GATHER_THREADS, hog, st>>>(part, heads, d.k, d.n_kv, n_heads, d.max_pages);
+    if (done && l0 + part.n == gl.n)
+      hipExtLaunchKernelGGL(gather_kernel, dim3(blocks), dim3(GATHER_THREADS), hog, st, nullptr, done, 0, part, heads, d.k, d.n_kv, n_heads, d.max_pages);
+    else
+      gather_kernel<<<blocks, GATHER_THREADS, hog, st>>>(part, heads, d.k, d.n_kv, n_heads, d.max_pages);
   }
 }
 

@@ -144,6 +144,7 @@ struct LayerIO {
   int max_splits;
   uint32_t impatient;                        // WAIT_* bits
   bool lose_selection;                       // test of the bounded wait: attention waits for a tag that never comes
+  hipEvent_t done;                           // if not null: recorded by the launch itself
   int* launch_grid; size_t* launch_lds;      // out: shape of the launch that was made
 };
 // `reps` launches of a kernel that does nothing, with the given grid, 512 threads and dynamic LDS
@@ -174,7 +175,8 @@ struct GatherLayers {
   const int32_t* miss[GATHER_MAX_LAYERS];
   const uint8_t* flags[GATHER_MAX_LAYERS];
 };
-void launch_gather(const Dims& d, const GatherLayers& gl, int heads, hipStream_t st);
+// done: if not null, an event that the (last) launch records
+void launch_gather(const Dims& d, const GatherLayers& gl, int heads, hipStream_t st, hipEvent_t done = nullptr);
 struct AttnIO {
   const uint16_t* q; const int32_t* act_ids; const int32_t* new_ids; const int32_t* act_slots; const int32_t* new_slots;
   const uint8_t* flags; int use;

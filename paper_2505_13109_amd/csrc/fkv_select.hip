@@ -4,6 +4,8 @@
 #include "fkv_step_dev.h"
 #include "fkv_attn_dev.h"
 
+#include <hip/hip_ext.h>
+
 #pragma clang fp contract(off)
 
 namespace fkv {
@@ -351,7 +353,11 @@ template <int DT, int G, bool HOSTPOOL>
 static bool launch_layer_gh(const LayerIO& io, const LayerLaunch& l, hipStream_t st) {
   static size_t granted = 48 * 1024;
   if (!grant_lds(&layer_kernel<DT, G, HOSTPOOL>, l.lds, granted)) return false;
-  layer_kernel<DT, G, HOSTPOOL><<<l.grid, STEP_THREADS, l.lds, st>>>(io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
+  if (io.done)
+    hipExtLaunchKernelGGL((layer_kernel<DT, G, HOSTPOOL>), l.grid, dim3(STEP_THREADS), l.lds, st, nullptr, io.done, 0,
+                          io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
+  else
+    layer_kernel<DT, G, HOSTPOOL><<<l.grid, STEP_THREADS, l.lds, st>>>(io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
   return true;
 }
 template <int DT, int G>

@@ -54,3 +54,59 @@ def test_every_missing_unit_is_recalled_once(batch, n_kv, per_head):
     same = (before == after).all(dim=1).cpu().numpy()
     assert np.array_equal(same, np.array(per_head) == 0)
     g.close()
+
+
+@pytest.mark.parametrize("own_copy_stream", [False, True])
+@pytest.mark.parametrize("batch,ctx,launches", [(1, 4000, 1), (32, 4000, 3)])        # the layer-step in one launch, and in separate ones
+def test_a_captured_step_with_the_host_pool(batch, ctx, launches, own_copy_stream):
+    """Steps of two layers, captured right behind the prompts: the streams hand over to each other inside the capture, by
+    events that are recorded as calls of their own and not by a launch.  Every replay against eager steps."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(29)
+
+    def normal(*shape):
+        return torch.randn(shape, device="cuda", generator=gen)
+
+    layers, steps = 2, 2
+    kv = [[normal(batch, ctx, 8, 128).to(torch.bfloat16) for _ in range(2)] for _ in range(layers)]
+    q = [[normal(batch, 32, 128)] for _ in range(layers)]
+    for x in q:
+        x.append(0.8 * x[0] + 0.6 * normal(batch, 32, 128))
+    q = [[y.to(torch.bfloat16) for y in x] for x in q]
+    new = [[normal(2, batch, 8, 128).to(torch.bfloat16) for _ in range(steps)] for _ in range(layers)]
+    results = []
+    for captured in (False, True):
+        g = fkv.FreeKV(n_layers=layers, batch=batch, n_q_heads=32, n_kv_heads=8, max_ctx=4096, budget=1024, sink=64, window=64,
+                       tau=0.8, dtype="bf16", placement=fkv.FKV_PLACE_HOST)
+        out = torch.zeros((steps, layers, batch, 32, 128), device="cuda")
+        copy = torch.cuda.Stream()
+
+        def decode():
+            for t in range(steps):
+                for l in range(layers):
+                    g.decode_step(l, q[l][t], new[l][t][0], new[l][t][1], out[t, l], copy_stream=copy if own_copy_stream else None)
+            if own_copy_stream:
+                torch.cuda.current_stream().wait_stream(copy)
+
+        for l in range(layers):
+            g.load_prefix(l, *kv[l])
+        torch.cuda.synchronize()
+        if captured:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                decode()
+            for _ in range(3):
+                out.zero_()
+                graph.replay()
+                torch.cuda.synchronize()
+                results.append(out.clone())
+        else:
+            decode()
+            torch.cuda.synchronize()
+            results.append(out.clone())
+            assert g.step_launches(0) == launches
+        for l in range(layers):
+            g.health(l)
+        g.close()
+    for r in results[1:]:
+        assert torch.equal(r, results[0])
