@@ -54,7 +54,7 @@ struct Layout {
   // per layer
   size_t pool, summ, qprev, ids, slots, flags, miss, cosine, status, tagged, layer_bytes;
   // per context
-  size_t consts, P, part, part_ml, exch, keyx, words_end, P_plain, score, launch_no, dbg_page, tstamp, ctx_bytes;
+  size_t consts, P, part, part_ml, exch, keyx, keyid, cmax, words_end, P_plain, cmax_plain, score, launch_no, dbg_page, tstamp, ctx_bytes;
   size_t total;
   size_t host_layer_bytes, host_total;
   int units_per_head, ring_base, n_ring, sel_base, max_splits, k, max_pages;
@@ -91,9 +91,12 @@ Layout make_layout(const fkv_config& c) {
   l.part = p;    p += align_up((size_t)b * n_q * l.max_splits * D * 8);
   l.part_ml = p; p += align_up((size_t)b * n_q * l.max_splits * 2 * 8);
   l.exch = p;    p += align_up((size_t)b * n_kv * EXCH_WORDS * 8);   // what a head's selecting blocks exchange,
-  l.keyx = p;    p += align_up((size_t)b * n_kv * l.max_pages * 8);  // and the candidates' keys
+  l.keyx = p;    p += align_up((size_t)b * n_kv * l.max_pages * 8);  // and their candidates' keys
+  l.keyid = p;   p += align_up((size_t)b * n_kv * l.max_pages * 8);  // and page ids
+  l.cmax = p;    p += align_up((size_t)b * n_kv * cmax_stride(l.max_pages) * 8);
   l.words_end = p;
   l.P_plain = p; p += align_up((size_t)b * n_q * l.max_pages * 4);   // page weights between separate launches
+  l.cmax_plain = p; p += align_up((size_t)b * n_kv * cmax_plain_stride(l.max_pages) * 4);
   l.score = p;   p += align_up((size_t)b * n_kv * l.max_pages * 4);
   l.launch_no = p; p += align_up(4);                                 // number of the last captured launch
   l.dbg_page = p; p += align_up((size_t)UNIT_BYTES);
@@ -202,6 +205,7 @@ struct fkv_ctx {
     c.units_per_head = lay.units_per_head; c.ring_base = lay.ring_base; c.n_ring = lay.n_ring; c.sel_base = lay.sel_base;
     c.corr_pool = cfg.corr_pooling; c.sel_pool = cfg.select_pooling; c.tau = cfg.tau;
     c.P = words(lay.P); c.part = words(lay.part); c.part_ml = words(lay.part_ml); c.exch = words(lay.exch); c.keyx = words(lay.keyx);
+    c.keyid = words(lay.keyid); c.cmax = words(lay.cmax);
     c.score = score();
     c.launch_no = launch_no();
     c.host_base = host; c.host_layer_bytes = lay.host_layer_bytes;
@@ -305,6 +309,9 @@ static StepIO make_step_io(fkv_ctx* ctx, int layer, int roles, const void* q, co
   io.ids_user = ids_user;
   io.exch = ctx->words(ctx->lay.exch);
   io.keyx = ctx->words(ctx->lay.keyx);
+  io.keyid = ctx->words(ctx->lay.keyid);
+  io.cmax = ctx->words(ctx->lay.cmax);
+  io.cmax_plain = reinterpret_cast<float*>(ctx->ctx_base() + ctx->lay.cmax_plain);
   if (roles & ROLE_SELECT) io.no = next_launch(ctx, st);      // (the other roles exchange nothing)
   io.impatient = ctx->impatient;
   io.P_tagged = &ctx->P_tagged;

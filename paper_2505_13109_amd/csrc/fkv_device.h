@@ -115,10 +115,60 @@ __device__ __forceinline__ float wave_max_f32(float v) {
   return __uint_as_float(wave_reduce_u32(__float_as_uint(v), OpMaxF32()));
 }
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) { return wave_reduce_u32(v, OpAddU32()); }
-// sum of 64 values below 2^48 each, as two 24-bit-limb sums so that no 32-bit lane sum overflows
+// ---- reductions over the lanes that are equal modulo M (1, 2, 4, 8): every lane ends with its class's result ----------
+// (in a quad by permutation, in a row of 16 lanes by rotation, over the rows by the row-swapping moves)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false); }
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128, DPP_BCAST = 0x150;
+// lane LANE's value of each row of 16 lanes
+template <int LANE>
+__device__ __forceinline__ double row_bcast_f64(double v) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  return __builtin_bit_cast(double, (unsigned long long)dpp_u32<DPP_BCAST + LANE>((uint32_t)(u >> 32)) << 32 | dpp_u32<DPP_BCAST + LANE>((uint32_t)u));
+}
+template <int M, typename OP>
+__device__ __forceinline__ uint32_t class_reduce(uint32_t v, OP op) {
+  static_assert(M == 1 || M == 2 || M == 4 || M == 8, "");
+  if (M <= 1) v = op(v, dpp_u32<DPP_XOR1>(v));
+  if (M <= 2) v = op(v, dpp_u32<DPP_XOR2>(v));
+  if (M <= 4) v = op(v, dpp_u32<DPP_ROR4>(v));
+  v = op(v, dpp_u32<DPP_ROR8>(v));
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = op(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return op(b[0], b[1]);
+}
+// sum over the wave of values below 2^48, as two sums of 24-bit halves so that no 32-bit lane sum overflows
 __device__ __forceinline__ unsigned long long wave_sum_u48(unsigned long long v) {
-  const uint32_t l0 = (uint32_t)(v & 0xffffffu), l1 = (uint32_t)(v >> 24);
-  return (unsigned long long)wave_sum_u32(l0) + ((unsigned long long)wave_sum_u32(l1) << 24);
+  return (unsigned long long)class_reduce<1>((uint32_t)(v & 0xffffffu), OpAddU32()) + ((unsigned long long)class_reduce<1>((uint32_t)(v >> 24), OpAddU32()) << 24);
+}
+// the same over the lanes that are equal modulo 8
+__device__ __forceinline__ unsigned long long class8_sum_u48(unsigned long long v) {
+  return (unsigned long long)class_reduce<8>((uint32_t)(v & 0xffffffu), OpAddU32()) + ((unsigned long long)class_reduce<8>((uint32_t)(v >> 24), OpAddU32()) << 24);
+}
+// v[g]: a lane's value for class g.  Lane l ends with op over all lanes of v[l % M].  A step that joins two lanes also halves the
+// classes that each of them goes on with (M = 4: 15 instructions; four reductions one after the other take 24).
+template <int M, typename OP>
+__device__ __forceinline__ uint32_t class_fold(const uint32_t (&v)[M], OP op) {
+  const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  uint32_t x[M];
+#pragma unroll
+  for (int i = 0; i < M; ++i) x[i] = v[i];
+  if constexpr (M >= 2) {
+    const bool up = lane & 1u;
+#pragma unroll
+    for (int i = 0; i < M / 2; ++i) x[i] = op(up ? x[2 * i + 1] : x[2 * i], dpp_u32<DPP_XOR1>(up ? x[2 * i] : x[2 * i + 1]));
+  }
+  if constexpr (M >= 4) {
+    const bool up = lane & 2u;
+#pragma unroll
+    for (int i = 0; i < M / 4; ++i) x[i] = op(up ? x[2 * i + 1] : x[2 * i], dpp_u32<DPP_XOR2>(up ? x[2 * i] : x[2 * i + 1]));
+  }
+  if constexpr (M >= 8) {
+    const bool up = lane & 4u;                          // (a rotation by 4 flips this bit)
+    x[0] = op(up ? x[1] : x[0], dpp_u32<DPP_ROR4>(up ? x[0] : x[1]));
+  }
+  return class_reduce<M>(x[0], op);
 }
 
 // sum of an fp64 value over the wave, valid in lane 63 (a DPP step moves the two halves)

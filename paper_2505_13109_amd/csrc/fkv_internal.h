@@ -100,7 +100,8 @@ struct StepIO {
   const uint16_t* q; const uint16_t* q_prev; uint16_t* q_stage; int have_prev; float tau;
   uint8_t* flags; uint8_t* flags_user; double* cosine;                               // correction test
   unsigned long long* P; float* P_plain; float* score; int32_t* ids; int32_t* ids_user;              // selection
-  unsigned long long* exch; unsigned long long* keyx;                                // its exchange between blocks
+  unsigned long long* exch; unsigned long long* keyx; unsigned long long* keyid;     // its exchange between blocks
+  unsigned long long* cmax; float* cmax_plain;                                       // largest weights of the scored chunks
   LaunchNo no; uint32_t impatient;
   bool* P_tagged;                                                                    // out: whether the launch wrote P or P_plain
   long long* tstamp;                                                                 // debug timestamps or null
@@ -108,7 +109,12 @@ struct StepIO {
   // ACTIVE ids and slots in, PENDING slots and miss lists out
   const int32_t* plan_act_ids; const int32_t* plan_act_slots; int32_t* plan_new_slots; int32_t* plan_miss;
 };
-constexpr int EXCH_WORDS = 16 * 3 * MAX_G;   // per head: what the selecting blocks of a head tell each other
+constexpr int EXCH_WORDS = 16 * 2 * MAX_G;   // per head: what the selecting blocks of a head tell each other
+// Per head, the largest weight of every chunk of pages that was scored together, for each query head of the group (a power of
+// two of them): by scoring blocks of the same launch, 32 pages or more each; by waves of the scan, 16 pages each
+__host__ __device__ constexpr int group_pow2(int G) { return G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8; }
+__host__ __device__ constexpr size_t cmax_stride(int max_pages) { return (size_t)((max_pages + 31) / 32) * MAX_G; }
+__host__ __device__ constexpr size_t cmax_plain_stride(int max_pages) { return (size_t)((max_pages + 63) / 64) * 4 * MAX_G; }
 int launch_step(const Dims& d, int roles, const StepIO& io, Geom g, hipStream_t st);   // returns the launches made
 // What the one-launch layer-step needs and no step changes: kept in device memory, one per context, so that a launch hands
 // over 56 bytes -- which the hardware preloads into scalar registers -- and finds the rest in the L2 of every XCD.  (Fresh
@@ -125,7 +131,7 @@ struct LayerConst {
   int32_t units_per_head, ring_base, n_ring, sel_base;
   int32_t corr_pool, sel_pool;
   float tau;
-  unsigned long long *P, *part, *part_ml, *exch, *keyx;
+  unsigned long long *P, *part, *part_ml, *exch, *keyx, *keyid, *cmax;
   float* score;
   const int* launch_no;                      // number of the last captured launch
   const char* host_base;                     // KV in a host pool (else null)

@@ -6,6 +6,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #pragma clang fp contract(off)
 
 namespace fkv {
@@ -19,8 +21,9 @@ __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
   touch_args<sizeof(StepArgs)>();
   step_roles<DT, G>(a, blockIdx.x, blockIdx.y, [&](int head, int s) {
     int nw;
-    bool made;
-    if (select_begin<G, true>(a, head, s, dyn_lds, nw, made)) select_finish<DT, G, true>(a, head, dyn_lds, nw, made);
+    Selected got;
+    if (select_begin<G, true>(a, head, s, dyn_lds, nw, got)) 
+      select_finish<DT, G, true>(a, head, s, dyn_lds, nw, got, [] { return args_from_memory<StepArgs>(); });
   });
 }
 
@@ -32,7 +35,6 @@ __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
 // A head's chunks are adjacent in block order (blocks that run together read one stretch of memory: 28.2 us with the KV
 // cache between two scans of that size, 30.0 us with the heads next to each other): grid (chunks, rows), row by row first
 // the other two roles, then a head each; beyond kGridRows rows (a grid dimension ends at 65535) folded into a third dimension.
-constexpr int SCAN_WAVES = 4;
 constexpr int kGridRows = 1 << 15;
 template <int DT, int G>
 __global__ __launch_bounds__(SCAN_WAVES * 64) void scan_kernel(StepArgs a) {
@@ -55,11 +57,11 @@ template <int G>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
   touch_args<sizeof(StepArgs)>();
-  const int head = (int)blockIdx.x >> a.slices_log2;
+  const int head = (int)blockIdx.x >> a.slices_log2, s = (int)blockIdx.x & (a.slices - 1);
   int nw;
-  bool made;
-  if (select_begin<G, false, SEL_REGS_ALONE>(a, head, (int)blockIdx.x & (a.slices - 1), dyn_lds, nw, made))
-    select_finish<0, G, false>(a, head, dyn_lds, nw, made);
+  Selected got;
+  if (select_begin<G, false>(a, head, s, dyn_lds, nw, got)) 
+    select_finish<0, G, false>(a, head, s, dyn_lds, nw, got, [] { return args_from_memory<StepArgs>(); });
 }
 
 constexpr size_t kLdsPerUnit = 150 * 1024;   // of the 160 KiB of a compute unit
@@ -79,24 +81,23 @@ static bool grant_lds(F* fn, size_t lds, size_t& granted) {
 
 // experiment builds only (see knob())
 static const int g_min_passes = knob("FKV_LAYER_PASSES", 0);      // passes a scoring block makes
-static const int g_slice = knob("FKV_SLICE", 0);                  // candidates per selecting block
 static const int g_one_launch = knob("FKV_ONE_LAUNCH", -1);       // layer-step: 0 separate launches, 1 one launch whenever it can be
 
 static const int g_fuse = knob("FKV_FUSE", -1);
 
-// Selecting blocks of a head, a power of two: each takes at most `most` candidates (its registers).  One block for short
-// lists and as long as it has at most kSliceWork numerators to make: the exchanges of a shared list cost about 2 us in all
-// (8 heads x 992 candidates, G = 4: 10.1 us in one block, 12.4 in two; G = 5: 13.4 and 12.9; G = 8: 16.3 and 15.1, but
-// with 718 candidates 12.7 and 13.9).  A list that is shared anyway is cut down to
-// a candidate per thread while that leaves the launch small: 8 heads x 2016, G = 8 in two blocks 18.5 us, in four 17.2; but
-// 32 heads x 2016, G = 4, 19.8 and 25.8, the blocks being missed elsewhere.
-constexpr int kSliceAlways = 768, kSliceWork = 4096, kMaxFineSlices = 64;
-static int selection_slices(const Geom& g, int G, int heads, int most) {
+// Selecting blocks of a head, a power of two.  One as long as it has the registers and not too many softmax numerators to make:
+// the exchanges of a shared list (sums, then keys) cost about 3 us in all.  8 KV heads, layer-step in us, alone against the
+// best shared one: 1500 candidates, G = 4, 10.4 and 12.2; 3000, G = 3, 13.6 and 13.7; 1500, G = 6, 12.0 and 12.6; but 2016, G = 5,
+// 13.1 and 12.8; 1200, G = 8, 13.3 and 13.0; 3500, G = 3, 16.0 and 14.5.  A list that is shared is cut fine, since every phase
+// but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
+// in 2, 4, 8, 16 blocks: 2300 candidates 14.3, 13.4, 12.9, 13.5; 4000: 17.6, 17.0, 15.5, 15.0; 8160: -, 22.0, 19.8, 19.0; but 32 heads
+// x 4000 13.6, 13.4, 17.2, 19.7.
+constexpr int kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128;
+static int selection_slices(const Geom& g, int G, int heads) {
   const int n = g.n_cand;
-  if (g.k_eff == 0 || (n <= most && (n <= kSliceAlways || (long)n * G <= kSliceWork) && g_slice == 0)) return 1;
-  const int fine = g_slice > 0 ? g_slice : SEL_THREADS;
-  int s = 1;
-  while (s < MAX_SLICES && ((n + s - 1) / s > most || ((n + s - 1) / s > fine && heads * s * 2 <= kMaxFineSlices))) s *= 2;
+  if (g.k_eff == 0 || (n <= sel_regs_alone(G) * SEL_THREADS && (long)n * G <= kMaxAloneWork)) return 1;
+  int s = 2;
+  while (s < MAX_SLICES && ((n + s - 1) / s > SEL_REGS * SEL_THREADS || ((n + s - 1) / s > kFineSlice && heads * s * 2 <= kMaxFineBlocks))) s *= 2;
   return s;
 }
 
@@ -125,7 +126,7 @@ static void fill_step_args(const Dims& d, int roles, const StepIO& io, Geom g, i
   a.q = io.q; a.q_prev = io.q_prev; a.q_stage = io.q_stage; a.have_prev = io.have_prev; a.tau = io.tau;
   a.corr_pool = d.corr_pool; a.sel_pool = d.sel_pool;
   a.flags = io.flags; a.flags_user = io.flags_user; a.cosine = io.cosine;
-  a.P = io.P; a.score = io.score; a.ids = io.ids; a.ids_user = io.ids_user; a.exch = io.exch; a.keyx = io.keyx;
+  a.P = io.P; a.score = io.score; a.ids = io.ids; a.ids_user = io.ids_user; a.exch = io.exch; a.keyx = io.keyx; a.keyid = io.keyid; a.cmax = io.cmax;
   a.no = io.no; a.impatient = io.impatient; a.tstamp = io.tstamp;
   a.passes = passes;
   a.slices = slices;
@@ -168,15 +169,16 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   size_t lds;
   const int heads = d.batch * d.n_kv;
   if (!(roles & ROLE_SELECT) || (g_fuse >= 0 ? g_fuse == 1 : (long)heads * ((g.n_cand + PAGES_PER_PASS - 1) / PAGES_PER_PASS) <= kFuseMaxChunks)) {
-    const int slices = selection_slices(g, d.G, heads, SEL_REGS * SEL_THREADS);
+    const int slices = selection_slices(g, d.G, heads);
     fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
     if (!grant_lds(&step_kernel<DT, G>, lds, granted_step)) return -1;
     step_kernel<DT, G><<<dim3(heads, rows), STEP_THREADS, lds, st>>>(a);
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
   }
-  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, selection_slices(g, d.G, heads, SEL_REGS_ALONE * SEL_THREADS), a, rows, lds);
+  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, selection_slices(g, d.G, heads), a, rows, lds);
   a.P = reinterpret_cast<unsigned long long*>(io.P_plain);
+  a.cmax = reinterpret_cast<unsigned long long*>(io.cmax_plain);
   if (!grant_lds(&select_kernel<G>, lds, granted_select)) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
   const int scan_rows = a.other_rows + heads;
@@ -274,7 +276,7 @@ struct LayerSetup {
     a.ids = ids(now); a.ids_user = nullptr;
     a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
     a.slice = (g.n_cand + slices - 1) >> slices_log2;
-    a.exch = c->exch; a.keyx = c->keyx; a.no = LaunchNo{tag, nullptr}; a.impatient = ka.plan >> 23; a.tstamp = c->tstamp;
+    a.exch = c->exch; a.keyx = c->keyx; a.keyid = c->keyid; a.cmax = c->cmax; a.no = LaunchNo{tag, nullptr}; a.impatient = ka.plan >> 23; a.tstamp = c->tstamp;
     a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
     if (HOSTPOOL) {
@@ -315,8 +317,8 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
   const LayerKernelArgs ka{consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic};
   const LayerSetup<HOSTPOOL> u(ka);
   StepArgs s;
-  int head, nw = SEL_WAVES, own = 0;
-  bool made = false;
+  int head, nw = SEL_WAVES, own = 0;           // own: a selecting block's slice of the head's candidates, an attention block's split
+  Selected got = Selected::NOTHING;
   AttnLeft left{};
   const bool step = (int)blockIdx.y < u.step_rows;
   if (step) {
@@ -324,7 +326,8 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
     bool go_on = false;
     step_roles<DT, G>(s, blockIdx.x, blockIdx.y, [&](int m, int slice) {
       head = m;
-      go_on = select_begin<G, true>(s, m, slice, dyn_lds, nw, made);
+      own = slice;
+      go_on = select_begin<G, true>(s, m, slice, dyn_lds, nw, got);
     });
     if (!go_on) return;
   } else {
@@ -341,7 +344,12 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
     s = LayerSetup<HOSTPOOL>(again).step_args(again);
     if (left.ids) lds_barrier();                             // (the LDS is free)
   }
-  if (step || left.ids) select_finish<DT, G, true>(s, head, dyn_lds, nw, made);
+  if (step || left.ids) {
+    select_finish<DT, G, true>(s, head, own, dyn_lds, nw, got, [] {
+      const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
+      return LayerSetup<HOSTPOOL>(again).step_args(again);
+    });
+  }
   if (step) return;
   const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
   attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL>(again).attn_args(again, G), own, head, left);
@@ -383,7 +391,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   if (io.host_pool && (d.max_pages > TAGGED_MAX_PAGES || 2 * d.k > TAGGED_MAX_SLOTS)) return false;
   const int heads = d.batch * d.n_kv;
   const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
-  const int slices = selection_slices(g, d.G, heads, SEL_REGS * SEL_THREADS);
+  const int slices = selection_slices(g, d.G, heads);
   const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, kMaxWaiting - (slices > 1 ? heads * slices : 0));
   const int n_splits = (n_att + pps - 1) / pps;
   if (n_splits > 63 || pps > 511) return false;

@@ -42,6 +42,7 @@ constexpr int STEP_WAVES = STEP_THREADS / 64;
 constexpr int SCORE_PASSES = FKV_SCORE_PASSES;         // most passes a scoring block can make (StepArgs::passes <= this)
 constexpr int PAGES_PER_PASS = STEP_WAVES * 4;         // a wave scores 4 pages per pass
 constexpr int MAX_SLICES = 16;                         // most blocks that share one head's selection
+constexpr int SCAN_WAVES = 4;                          // of a block of the scan
 
 template <int U> struct UnrollBy { static constexpr int value = U; };
 
@@ -77,8 +78,10 @@ struct StepArgs {
   int passes;                // passes a scoring block makes (1 .. SCORE_PASSES)
   int slices, slices_log2;   // selecting blocks of a KV head (1 .. MAX_SLICES, a power of two)
   int slice;                 // candidates of each (the last may have fewer)
-  unsigned long long* exch;  // [heads][MAX_SLICES][3 * MAX_G] tagged: what a head's selecting blocks tell each other
-  unsigned long long* keyx;  // [heads][max_pages] tagged: the candidates' keys, for the head's last selecting block
+  unsigned long long* exch;  // [heads][MAX_SLICES][2 * MAX_G] tagged: what a head's selecting blocks tell each other
+  unsigned long long* keyx;  // [heads][max_pages] tagged: keys and page ids of each block's best candidates, for the head's
+  unsigned long long* keyid; // last selecting block
+  unsigned long long* cmax;  // the chunks' largest weights, [heads][cmax_stride] tagged, or (where P is plain) [heads][cmax_plain_stride]
   LaunchNo no;               // of this launch
   uint32_t impatient;        // WAIT_* bits: waits that run out at once (tests)
   long long* tstamp;         // debug: 100 MHz timestamps of head 0's phases (may be null)
@@ -211,6 +214,9 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
   }
   const float scale = 0x1.6a09e6p-4f;   // fl32(1/sqrt(128))
   __shared__ float s_w[NG][TAGGED ? PASS * SCORE_PASSES : 1];
+  __shared__ float s_max[TAGGED ? WAVES : 1][MAX_G];
+  float largest = -__builtin_inff();                      // of query head c8 among the pages of the row of lanes
+  constexpr int GP = group_pow2(G);
   // The weights of N passes' pages.  A channel contributes q_c * (q_c >= 0 ? kmax_c : kmin_c): the choice is made on the
   // packed 16-bit values, by the signs of a query's channel pair as a bit mask (one instruction for two channels, and the
   // mask serves N passes; as comparisons, 8 G lane masks would have to live in scalar registers, which from G = 5 on there
@@ -265,10 +271,12 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int j = j0 + i * PASS;
+      const float w = mine[i] * scale;
+      largest = j < n ? fmaxf(largest, w) : largest;
       if (TAGGED) {
-        if (c8 < NG) s_w[c8][i * PASS + wave * 4 + grp] = mine[i] * scale;
+        if (c8 < NG) s_w[c8][i * PASS + wave * 4 + grp] = w;
       } else if (c8 < NG && j < n) {
-        reinterpret_cast<float*>(a.P)[((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j] = mine[i] * scale;
+        reinterpret_cast<float*>(a.P)[((size_t)head * G + c8) * a.max_pages + a.g.cand_lo + j] = w;
       }
     }
   };
@@ -276,8 +284,21 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
   if (passes == 1) score(UnrollBy<1>{});
   else if (passes == 2) score(UnrollBy<2>{});
   else score(UnrollBy<4>{});
-  if (!TAGGED) return;
+  // The chunk's largest weight of each query head: where several blocks share a head's selection, each of them knows the head's
+  // maximum by these as soon as its own weights are there.
+  const bool soft = !QMODE && a.sel_pool <= 1 && a.slices > 1;
+  if (soft) largest = max_over_rows(largest);
+  if (!TAGGED) {
+    if (soft && lane < NG) reinterpret_cast<float*>(a.cmax)[head * cmax_plain_stride(a.max_pages) + (chunk * WAVES + wave) * GP + lane] = largest;
+    return;
+  }
+  if (soft && lane < MAX_G) s_max[wave][lane] = largest;  // (what lanes from NG on have is nobody's)
   lds_barrier();
+  static_assert(WAVES == 8 || !TAGGED, "");
+  if (soft && wave == WAVES - 1) {                        // lane 8w + g has wave w's of head g
+    const float v = __uint_as_float(class_reduce<8>(__float_as_uint(s_max[lane >> 3][lane & 7]), OpMaxF32()));
+    if (lane < NG) st_tag(a.cmax + head * cmax_stride(a.max_pages) + chunk * GP + lane, __float_as_uint(v), tag);
+  }
   const int pages_log2 = __builtin_ctz(PASS * passes), pages = 1 << pages_log2, at0 = chunk * pages;     // (powers of two)
   for (int i = threadIdx.x; i < NG * pages; i += WAVES * 64) {
     const int gg = i >> pages_log2, jj = i & (pages - 1);
@@ -294,21 +315,21 @@ __device__ __forceinline__ void score_role(const StepArgs& a, int head, int chun
 // ---------------------------------------------------------------------------------
 // softmax -> group mean -> top-k of one KV head: the arithmetic.
 // ---------------------------------------------------------------------------------
+// (As written, up to exact scalings: the coefficients times 2^31 give e * 2^31; t + 3 * 2^22 is rint(t) + 3 * 2^22, with n in its
+// last bits, from where it goes to the exponent by an integer addition; below t = -64 the result is below a half and so 0.)
 __device__ __forceinline__ uint32_t softmax_fixed(float p, float mx) {
   const float x = p - mx;
-  const float t = x * 0x1.715476p+0f;          // fl32(log2 e)
-  const float n = __builtin_rintf(t);
-  const float f = t - n;
-  float r = 0x1.430912p-13f;
-  r = r * f; r = r + 0x1.5d87fep-10f;
-  r = r * f; r = r + 0x1.3b2ab6p-7f;
-  r = r * f; r = r + 0x1.c6b08ep-5f;
-  r = r * f; r = r + 0x1.ebfbep-3f;
-  r = r * f; r = r + 0x1.62e43p-1f;
-  r = r * f; r = r + 1.0f;
-  // e = ldexp(r, n) is exact here (n >= -64), and so is e * 2^31: one ldexp gives the same number
-  float e31 = __builtin_ldexpf(r, (int)n + 31);
-  if (t < -64.0f) e31 = 0.0f;
+  const float t = fmaxf(x * 0x1.715476p+0f, -64.0f);      // fl32(log2 e)
+  const float shifted = t + 0x1.8p+23f;
+  const float f = t - (shifted - 0x1.8p+23f);
+  float r = 0x1.430912p+18f;
+  r = r * f; r = r + 0x1.5d87fep+21f;
+  r = r * f; r = r + 0x1.3b2ab6p+24f;
+  r = r * f; r = r + 0x1.c6b08ep+26f;
+  r = r * f; r = r + 0x1.ebfbep+28f;
+  r = r * f; r = r + 0x1.62e43p+30f;
+  r = r * f; r = r + 0x1p+31f;
+  const float e31 = __uint_as_float(__float_as_uint(r) + (__float_as_uint(shifted) << 23));
   return (uint32_t)__builtin_rintf(e31);
 }
 
@@ -325,16 +346,22 @@ __device__ __forceinline__ double reciprocal_near(double b) {
 }
 
 // The correctly rounded fp64 quotient a / b of integers 0 <= a <= b < 2^48 from such a y (one
-// reciprocal per head, not one division per candidate): q = a * y corrected twice with the exact
-// remainder r = a - b * q.  After the first correction q is within an ulp; the second leaves an
-// error of at most |r| * |y - 1/b| <= 2^-52 ulp, and a / b with b < 2^48 is either representable or at
-// least 2^-49 ulp away from the nearest rounding boundary, so the rounding cannot go wrong.
+// reciprocal per head, not one division per candidate): q = a * y is within 2^-51 of it, or four units in the last place; its
+// remainder r = a - b * q, a multiple of q's last place and below 2^51 of them, is exact; and r * y corrects q up to
+// |r| * |y - 1/b|, at most 4 * 2^-52 = 2^-50 of a unit in the last place.  a / b with b < 2^48 is either representable or at
+// least 2^-49 of a unit away from the nearest rounding boundary, so the last rounding cannot go wrong.
 __device__ __forceinline__ double div_rn(double a, double b, double y) {
-  double q = a * y;
-  double r = __builtin_fma(-b, q, a);
-  q = __builtin_fma(r, y, q);
-  r = __builtin_fma(-b, q, a);
-  return __builtin_fma(r, y, q);
+  const double q = a * y;
+  return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+
+// a / G, correctly rounded: one correction of a * RN(1 / G) by its exact remainder (Markstein); a power of two is exact anyway
+template <int G>
+__device__ __forceinline__ double div_by_group(double a) {
+  constexpr double y = 1.0 / G;
+  if constexpr ((G & (G - 1)) == 0) return a * y;
+  const double q = a * y;
+  return __builtin_fma(__builtin_fma(-(double)G, q, a), y, q);
 }
 
 // pooled score of one candidate from the G per-head values e[] (softmax numerators, or the bits of
@@ -350,7 +377,7 @@ __device__ __forceinline__ float pooled_score(const uint32_t* e, const double* z
       if (mode == 0) acc = acc + sg;
       else acc = sg > acc ? sg : acc;
     }
-    return mode == 0 ? (float)(acc / (double)G) : (float)acc;
+    return mode == 0 ? (float)div_by_group<G>(acc) : (float)acc;
   }
   // mean or maximum of the weights themselves in fp32, head order; or the pooled query's weight
   float acc = __uint_as_float(e[0]);
@@ -364,31 +391,42 @@ __device__ __forceinline__ float pooled_score(const uint32_t* e, const double* z
 
 // ---------------------------------------------------------------------------------
 // role: selection of one KV head by a.slices groups of SEL_THREADS threads with a.slice candidates each.  Each group keeps
-// its candidates' G values in registers from the weights to the key; what needs the whole head is exchanged as tagged
-// words: the per-head maxima, the integer softmax sums (exact, so their order does not matter), and the keys, which the
-// last group turns into the top-k.  A head's groups are adjacent in block order and wait for each other and for scoring
+// its candidates' G values in registers from the weights to the choice.  What needs the whole head comes as words of other
+// blocks: the maxima from the blocks that scored (the largest of every chunk of pages), the integer softmax sums from the
+// other groups (exact, so their order does not matter), and the keys and ids of each group's own best k, among which the
+// last group finds the head's.  A head's groups are adjacent in block order and wait for each other and for scoring
 // blocks (lower indices) only, and for neither of them for long (PATIENCE).
 //
-// What bounds it: a chain of short phases, each of them instructions of the waves that share a SIMD one after the other
-// (a wave-instruction takes the SIMD 4 cycles): about 26 per softmax numerator, 8 in fp64 per pooled term, and the
-// reductions, which every wave makes.  A group is 8 waves, two to a SIMD, which fill each other's gaps (4 waves with twice
+// What bounds it: a chain of short phases.  A wave issues an instruction that depends on the one before every 8 cycles, an LDS
+// round trip takes 62, a trip between blocks 0.4 us and more; so what counts is the number of dependent instructions and
+// of barriers.  A group is 8 waves, two to a SIMD, which fill each other's gaps (4 waves with twice
 // the candidates each: 1 us more of a 10 us layer-step), and waves without a candidate end at once.  A long list is shared
 // (selection_slices); each exchange costs a trip of about 1 us.
 // TAGGED: the weights come from scoring blocks of this launch; else from a launch that has ended.
 // ---------------------------------------------------------------------------------
 constexpr int SEL_WAVES = 8, SEL_THREADS = SEL_WAVES * 64;
-constexpr int SEL_REGS = 2, SEL_REGS_ALONE = 8;          // most candidates per thread, in the launches where scoring blocks
-                                                         // share the unit and in the one that only selects
+constexpr int SEL_REGS = 4;                              // most candidates per thread where a head's selection is shared
+__host__ __device__ constexpr int sel_regs_alone(int G) { return G <= 3 ? 8 : 4; }      // ... and where one group has it (registers)
+constexpr int SEL_OTHERS = 4;                            // most of the other groups' candidates per thread that are kept in registers
+// candidates that each group but the last hands on, group after group: all of them where the last group's registers hold
+// them, else its best k
+__host__ __device__ constexpr int handed_on(int slices, int slice, int kk) {
+  return (slices - 1) * slice <= SEL_OTHERS * SEL_THREADS || slice < kk ? slice : kk;
+}
 constexpr int TOPK_BINS = 512;
+// how far a group got: it has to make the keys alone; the keys of all that may be chosen are in LDS; the ids are out
+enum class Selected : int { NOTHING, KEYS, IDS };
 
 // 32-bit words of dynamic LDS that the keys of n candidates take (whole quads)
 __host__ __device__ constexpr int select_key_words(int n) { return n > 0 ? (n + 3) & ~3 : 4; }
 
 struct alignas(16) SelectLds {
   uint32_t hist[TOPK_BINS];
-  uint32_t list[64];
+  unsigned long long list[64];
   unsigned long long z[SEL_WAVES][MAX_G];
   float mx[SEL_WAVES][MAX_G];
+  uint32_t count[64];
+  uint32_t more[SEL_WAVES][64];
   uint32_t scan[SEL_WAVES];
   uint32_t n_list;
   int alone;
@@ -408,28 +446,113 @@ __device__ __forceinline__ uint32_t topk_floor(uint32_t bin, bool soft) {
 }
 
 // the bin of `hist` (ascending) that holds the `want`-th entry: bin, entries before it, entries in it.  Every wave
-// scans by itself (lane l owns bins 8l .. 8l+7).
+// scans by itself: lane l sums bins 8l .. 8l+7, then the eight bins of the lane where the entry is are read again, one a lane
+// (0.1 us less than picking it from a lane's eight registers).
 __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t want, uint32_t& bin, uint32_t& before, uint32_t& in_bin) {
   const int lane = threadIdx.x & 63;
   const uint4 c0 = *reinterpret_cast<const uint4*>(hist + 8 * lane), c1 = *reinterpret_cast<const uint4*>(hist + 8 * lane + 4);
-  const uint32_t c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-  const uint32_t tot = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+  const uint32_t tot = ((c0.x + c0.y) + (c0.z + c0.w)) + ((c1.x + c1.y) + (c1.z + c1.w));
   const uint32_t incl = wave_scan_u32(tot);
-  uint32_t at = incl - tot, f = 0, cnt = c[0];
-  const int src = __builtin_ctzll(__ballot(at < want && want <= incl));       // exactly one lane
-#pragma unroll
-  for (int i = 1; i < 8; ++i)
-    if (f == i - 1 && at + cnt < want) { at += cnt; cnt = c[i]; f = i; }
-  bin = (uint32_t)__builtin_amdgcn_readlane(8 * lane + (int)f, src);
-  before = (uint32_t)__builtin_amdgcn_readlane((int)at, src);
-  in_bin = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
+  const int src = __builtin_ctzll(__ballot(incl >= want));                    // (there are as many entries)
+  const uint32_t c = hist[8 * src + (lane & 7)];
+  uint32_t at = c;                                                            // inclusive, over eight lanes
+  at += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)at, 0x111, 0xf, 0xf, true);   // row_shr:1, 0 shifted in
+  at += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)at, 0x112, 0xf, 0xf, true);
+  at += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)at, 0x114, 0xf, 0xf, true);
+  at += (uint32_t)__builtin_amdgcn_readlane((int)(incl - tot), src);
+  const int f = __builtin_ctzll(__ballot(at >= want));                        // (one of the first eight lanes)
+  bin = (uint32_t)(8 * src + f);
+  in_bin = (uint32_t)__builtin_amdgcn_readlane((int)c, f);
+  before = (uint32_t)__builtin_amdgcn_readlane((int)at, f) - in_bin;
 }
 
-// Top-kk of n keys held in LDS, ties to the lower index, by nw waves: emit(pos, j) is called for the
-// chosen j in ascending order of j with pos = 0 .. kk-1 (whichever thread owns j calls it).
-// Before the call (and a barrier): sm.hist holds the counts of the keys' bins.  1 <= kk <= n.
-// The keys of the one bin that is only partly wanted are collected and ranked against each other; only if there are
-// more than 64 of them (ties, or scores that are not softmax values) the bytes are resolved one by one.
+// The best kk of a group's items, ties to the lower one in order: emit(pos, slot) is called by the thread that holds a chosen
+// one, pos = 0 .. kk - 1 in order.  A thread holds items key[u] in slots 0 .. first - 1 and A .. A + second - 1 (the same in the
+// whole group), where bit u of `have` is set; the order is by slot, then by thread; (first + second) * nw <= 64.  n: items of
+// the group.  Before the call (and a barrier): sm.hist holds the counts of the
+// keys' bins, sm.n_list and sm.more are 0.
+// The keys of the one bin that is only partly wanted are collected and ranked against each other, with their places in the
+// order, by every wave; the same barrier brings the counts per wave of what is chosen anyway.  False, and nothing done, if there
+// are more than 64 of them (ties, or scores that are not softmax values).
+template <int A, int R, typename Emit>
+__device__ __forceinline__ bool topk_items(const uint32_t (&key)[R], uint32_t have, int first, int second, int n, int kk, bool soft, int nw,
+                                           SelectLds& sm, Emit emit) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
+  // f(slot, row) for every slot in use (a branch over each unused one would cost more than the work of a used one)
+  auto rows = [&](auto f) {
+#pragma unroll
+    for (int u = 0; u < A; ++u) {
+      if (u >= first) break;
+      f(u, u);
+    }
+#pragma unroll
+    for (int u = A; u < R; ++u) {
+      if (u - A >= second) break;
+      f(u, first + u - A);
+    }
+  };
+  uint32_t pick = have, take = 0, in_bin = 0;        // bits of the chosen slots; how many of the listed keys are wanted
+  bool ranked = false;
+  if (kk < n) {
+    uint32_t bin, before;
+    find_bin(sm.hist, (uint32_t)kk, bin, before, in_bin);
+    take = (uint32_t)kk - before;
+    ranked = take != in_bin;
+    if (__builtin_expect(ranked && in_bin > 64, 0)) return false;
+    const uint32_t up_to = ranked ? bin : bin + 1;   // keys of lower bins are chosen
+    pick = 0;
+    uint32_t* n_list = &sm.n_list;
+    asm volatile("" : "+v"(n_list));                 // (an atomic of each lane: one for the wave would be a longer chain)
+    rows([&](int u, int row) {
+      const uint32_t b = (have >> u & 1u) ? topk_bin(key[u], soft) : TOPK_BINS;
+      pick |= b < up_to ? 1u << u : 0u;
+      if (ranked && b == bin) sm.list[atomicAdd(n_list, 1u)] = (unsigned long long)key[u] << 32 | ~(uint32_t)(row * nt + tid);
+    });
+  }
+  rows([&](int u, int row) {
+    const uint32_t c = (uint32_t)__popcll(__ballot(pick >> u & 1u));
+    if (lane == 0) sm.count[row * nw + wave] = c;
+  });
+  lds_barrier();
+  uint32_t cnt = lane < (first + second) * nw ? sm.count[lane] : 0u;
+  if (ranked) {
+    const unsigned long long mine = lane < (int)in_bin ? sm.list[lane] : 0ull;      // a list entry a lane
+    uint32_t above = 0;
+#pragma unroll 1
+    for (uint32_t i = 0; i < in_bin; i += 4) {
+#pragma unroll
+      for (uint32_t v = 0; v < 4; ++v) {             // (lanes without an entry have 0, which is above none)
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), (int)(i + v));
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, (int)(i + v));
+        above += ((unsigned long long)hi << 32 | lo) > mine ? 1u : 0u;
+      }
+    }
+    // the chosen ones, up to the least: counted in the rows and waves where they are (by each wave for itself)
+    const bool listed = lane < (int)in_bin;
+    if (listed && above < take) atomicAdd(&sm.more[wave][~(uint32_t)mine >> 6], 1u);
+    const int least = __builtin_ctzll(__ballot(listed && above == take - 1));
+    const unsigned long long floor = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), least) << 32 |
+                                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, least);
+    pick = 0;
+    rows([&](int u, int row) {
+      const unsigned long long at = (unsigned long long)key[u] << 32 | ~(uint32_t)(row * nt + tid);
+      pick |= (have >> u & 1u) && at >= floor ? 1u << u : 0u;
+    });
+    cnt += sm.more[wave][lane];
+  }
+  const uint32_t excl = wave_scan_u32(cnt) - cnt;
+  rows([&](int u, int row) {
+    const bool chosen = (pick >> u & 1u) != 0;
+    const unsigned long long b = __ballot(chosen);
+    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, (uint32_t)__builtin_amdgcn_readlane((int)excl, row * nw + wave)));
+    if (chosen) emit((int)pos, u);
+  });
+  return true;
+}
+
+// The same for n keys held in LDS: emit(pos, j) is called for the chosen j in ascending order of j with pos = 0 .. kk-1
+// (whichever thread owns j calls it).  1 <= kk <= n.  Longer chains: for lists that do not fit the registers, and for a group
+// that has made the keys alone.
 template <typename Emit>
 __device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, bool soft, int nw, SelectLds& sm, Emit emit) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = nw * 64;
@@ -446,7 +569,7 @@ __device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, b
         if (topk_bin(kj, soft) == bin) sm.list[atomicAdd(&sm.n_list, 1u)] = kj;
       }
       lds_barrier();
-      const uint32_t mine = lane < (int)in_bin ? sm.list[lane] : 0u;
+      const uint32_t mine = lane < (int)in_bin ? (uint32_t)sm.list[lane] : 0u;
       uint32_t above = 0, same = 0;
       for (uint32_t i = 0; i < in_bin; ++i) {
         const uint32_t ki = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)i);
@@ -522,24 +645,46 @@ __device__ __forceinline__ SelectLds& select_lds() {
   return sm;
 }
 
-// The keys of one head's candidates into `key`, and the counts of their bins into sm.hist, by the groups that share the head.
+// where a picked id goes: the layer's id list, the caller's copy, and (one-launch layer-step) as a tagged word, so that a
+// waiting attention wave sees "this launch's id" in one read.  With a recall plan to make, the ids are only collected in the
+// plan's LDS, and everything goes out after it.
+struct PutId {
+  int32_t *out, *outu, *plan_nid;
+  unsigned long long* tagw;
+  uint32_t tag;
+  __device__ __forceinline__ PutId(const StepArgs& a, int head, uint32_t* key) {
+    out = a.ids + (size_t)head * a.k;
+    outu = a.ids_user ? a.ids_user + (size_t)head * a.k : nullptr;
+    tagw = a.tagged ? a.tagged + (size_t)head * a.k : nullptr;
+    plan_nid = a.plan_new_slots ? reinterpret_cast<int32_t*>(key) + a.plan_lds_off + 4 * a.k : nullptr;
+    tag = launch_tag(a.no);
+  }
+  __device__ __forceinline__ void operator()(int pos, int id) const {
+    if (plan_nid) { plan_nid[pos] = id; return; }
+    if (tagw) st_tag(tagw + pos, (uint32_t)id, tag);
+    out[pos] = id;
+    if (outu) outu[pos] = id;
+  }
+};
+
+// One group's part of a head's selection, up to the ids (the last group) or to its own best candidates in words (the others).
 // A wave whose patience ends has nothing to say, and what it would have had to is never put into words under the tag: its
-// group learns of it at the next barrier, from a value no maximum or sum has, and leaves.  Of the groups only the last one has to end with all the keys, and it
-// can make them alone (alone_keys).  Returns whether this wave's keys (the last group: every key) are made.
-template <int G, bool TAGGED, int REGS>
-__device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, int nw, uint32_t* key, SelectLds& sm, uint32_t (&kreg)[REGS]) {
+// group learns of it at the next barrier, from a value no sum has or a flag, and leaves.  Of the groups only the last one has to
+// end with all the keys, and it can make them alone (alone_keys).  Returns how far the group got.
+template <int G, bool TAGGED>
+__device__ __forceinline__ Selected select_group(const StepArgs& a, int head, int s, int nw, uint32_t* key_lds, SelectLds& sm) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
-  const int n = a.g.n_cand, lo = a.g.cand_lo;
+  const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff;
   const int S = a.slices, j0 = s * a.slice, j1 = min(n, j0 + a.slice);
   const bool last = s == S - 1;
   const uint32_t tag = launch_tag(a.no);
   const int mode = a.sel_pool;                         // FKV_POOL_*
   const bool soft = mode <= 1;                         // the variants that pool softmax values
   const int ng = mode >= 4 ? 1 : G;                    // weights in use per page (pooled query: the group's first)
-  if (last) {
-    for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
-    if (tid == 0) { sm.n_list = 0; sm.alone = 0; }
-  }
+  constexpr int GP = group_pow2(G), REGS = sel_regs_alone(G);
+  for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
+  sm.more[wave][lane] = 0;
+  if (tid == 0) { sm.n_list = 0; sm.alone = 0; }
   // load_and_check() until every lane's words carry the tag; false: patience ended
   auto poll = [&](uint32_t kind, auto load_and_check) {
     int it = 0;
@@ -556,47 +701,77 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
     return __ballot(sm.failed[min(lane, nw - 1)] != 0) != 0;
   };
 
-  // ---- this group's weights: thread t has candidates j0 + t + u * nt ----
+  // ---- this group's weights: thread t has candidates j0 + t + u * nt; in a shared selection, wave w also reads its part of the
+  // largest weights of the head's chunks: 64w + l, 512 + 64w + l, ... in lane l, which is for head l % GP ----
   const int U = (j1 - j0 + nt - 1) / nt;               // 1 .. REGS
-  uint32_t e[REGS][G];                             // bits of the weights, then softmax numerators
+  uint32_t e[REGS][G];                                 // bits of the weights, then softmax numerators
+  float largest = -__builtin_inff();
+  const int n_max = soft && S > 1 ? a.chunks * (TAGGED ? 1 : SCAN_WAVES) * GP : 0;
+  const size_t max0 = head * (TAGGED ? cmax_stride(a.max_pages) : cmax_plain_stride(a.max_pages));
+  const int past = max(0, (lane & (GP - 1)) - (G - 1));        // (lanes of no head read the last one's)
+  auto max_at = [&](int i) { return max0 + (i + tid < n_max ? i + tid : lane & (GP - 1)) - past; };
   auto ours = [&](int u) { return j0 + tid + u * nt < j1; };
-  // (All of a poll's loads are issued before the first is looked at, and none sits behind a branch of its own: one trip.)
-  auto weights = [&](auto uc) {
-    constexpr int UC = decltype(uc)::value;
+  // UC rows of candidates from row u0 on.  (All of a poll's loads are issued before the first is looked at: one trip.  Not all
+  // rows at a time, because a word takes two registers.)
+  auto weights = [&](auto from, auto uc) {
+    constexpr int u0 = decltype(from)::value, UC = decltype(uc)::value;
+    uint32_t at[UC];                                   // (a head's weights are less than 1 MiB)
+#pragma unroll
+    for (int u = 0; u < UC; ++u) at[u] = (uint32_t)min(j0 + tid + (u0 + u) * nt, j1 - 1);
+    const uint32_t row = ng == 1 ? 0u : (uint32_t)a.max_pages;
     const size_t base = (size_t)head * G * a.max_pages + lo;
-    size_t at[UC];
-#pragma unroll
-    for (int u = 0; u < UC; ++u) at[u] = base + min(j0 + tid + u * nt, j1 - 1);
-    size_t row[G];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) row[gg] = (size_t)min(gg, ng - 1) * a.max_pages;
     if (TAGGED) {
-      failed = !poll(WAIT_WEIGHTS, [&]() {
+      const bool maxima = u0 == 0 && n_max > 0;
+      failed = !poll(WAIT_WEIGHTS | (maxima ? WAIT_MAXIMA : 0u), [&]() {
         bool ok = true;
-        unsigned long long w[UC][G];
+        unsigned long long w[UC][G], m = 0;
 #pragma unroll
         for (int u = 0; u < UC; ++u)
 #pragma unroll
-          for (int gg = 0; gg < G; ++gg) w[u][gg] = ld_tag(a.P + at[u] + row[gg]);
+          for (int gg = 0; gg < G; ++gg) w[u][gg] = ld_tag(a.P + base + (at[u] + gg * row));
+        if (maxima) m = ld_tag(a.cmax + max_at(0));
 #pragma unroll
         for (int u = 0; u < UC; ++u)
 #pragma unroll
           for (int gg = 0; gg < G; ++gg) {
-            e[u][gg] = (uint32_t)w[u][gg];
+            e[u0 + u][gg] = (uint32_t)w[u][gg];
             ok = ok & ((uint32_t)(w[u][gg] >> 32) == tag);
           }
+        if (maxima) {
+          ok = ok & ((uint32_t)(m >> 32) == tag);
+          largest = __uint_as_float((uint32_t)m);
+        }
         return ok;
-      });
+      }) || failed;
     } else {
 #pragma unroll
       for (int u = 0; u < UC; ++u)
 #pragma unroll
-        for (int gg = 0; gg < G; ++gg) e[u][gg] = __float_as_uint(reinterpret_cast<const float*>(a.P)[at[u] + row[gg]]);
+        for (int gg = 0; gg < G; ++gg) e[u0 + u][gg] = __float_as_uint((reinterpret_cast<const float*>(a.P) + base)[at[u] + gg * row]);
     }
   };
-  if (U == 1) weights(UnrollBy<1>{});
-  else if (REGS == 2 || U == 2) weights(UnrollBy<2>{});
-  else weights(UnrollBy<REGS>{});
+  if (U == 1) {
+    weights(UnrollBy<0>{}, UnrollBy<1>{});
+  } else if (U == 2) {
+    weights(UnrollBy<0>{}, UnrollBy<2>{});
+  } else if constexpr (REGS == 8) {
+    weights(UnrollBy<0>{}, UnrollBy<4>{});
+    if (U > 4) weights(UnrollBy<4>{}, UnrollBy<4>{});
+  } else {
+    weights(UnrollBy<0>{}, UnrollBy<2>{});
+    weights(UnrollBy<2>{}, UnrollBy<2>{});
+  }
+  if (TAGGED) {
+    for (int i = nt; i < n_max && !failed; i += nt) {
+      unsigned long long m = 0;
+      failed = !poll(WAIT_MAXIMA, [&]() { m = ld_tag(a.cmax + max_at(i)); return (uint32_t)(m >> 32) == tag; });
+      largest = fmaxf(largest, __uint_as_float((uint32_t)m));
+    }
+  } else {
+    for (int i = 0; i < n_max; i += 2 * nt)
+      largest = fmaxf(largest, fmaxf(reinterpret_cast<const float*>(a.cmax)[max_at(i)], reinterpret_cast<const float*>(a.cmax)[max_at(i + nt)]));
+  }
+  static_assert(REGS == (G <= 3 ? 8 : 4) && SEL_REGS == 4, "");
   FKV_STAMP(a, head, 2);
 
   // ---- fixed-point softmax: the head's maxima, numerators, integer denominators ----
@@ -604,137 +779,230 @@ __device__ __forceinline__ bool shared_keys(const StepArgs& a, int head, int s, 
 #pragma unroll
   for (int gg = 0; gg < G; ++gg) zd[gg] = zr[gg] = 1.0;
   if (soft) {
-    unsigned long long* const mine = a.exch + ((size_t)head * MAX_SLICES + s) * 3 * MAX_G;
-    const unsigned long long* const all = a.exch + (size_t)head * MAX_SLICES * 3 * MAX_G;
-    const int gl = min(lane & 7, G - 1);               // lane 8r + g works on head g
+    unsigned long long* const mine = a.exch + ((size_t)head * MAX_SLICES + s) * 2 * MAX_G;
+    const unsigned long long* const all = a.exch + (size_t)head * MAX_SLICES * 2 * MAX_G;
+    if (S > 1) {
+      largest = __uint_as_float(class_reduce<GP>(__float_as_uint(largest), OpMaxF32()));
+    } else {                                           // (a thread without a candidate repeats the last one)
+      uint32_t v[GP];
+#pragma unroll
+      for (int gg = 0; gg < GP; ++gg) v[gg] = gg < G ? e[0][gg < G ? gg : 0] : 0u;
+#pragma unroll
+      for (int u = 1; u < REGS; ++u) {
+        if (u >= U) break;
+#pragma unroll
+        for (int gg = 0; gg < G; ++gg) v[gg] = OpMaxF32()(v[gg], e[u][gg]);
+      }
+      largest = __uint_as_float(class_fold<GP>(v, OpMaxF32()));
+    }
+    if (lane < MAX_G) sm.mx[wave][lane] = largest;     // lane l: of head l % GP
+    lds_barrier();
+    largest = sm.mx[min(lane >> 3, nw - 1)][lane & 7];
+    largest = __uint_as_float(class_reduce<8>(__float_as_uint(largest), OpMaxF32()));
+    FKV_STAMP(a, head, 3);
+    uint32_t zl[GP], zh[GP];                           // a thread's sums, in 16-bit halves
+    typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
     float mx[G];
 #pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      float v = __uint_as_float(e[0][gg]);             // (a thread without a candidate repeats the slice's last one)
+    for (int gg = 0; gg < GP; ++gg) zl[gg] = zh[gg] = 0;
 #pragma unroll
-      for (int u = 1; u < REGS; ++u)
-        if (u < U) v = fmaxf(v, __uint_as_float(e[u][gg]));
-      v = wave_max_f32(v);
-      if (TAGGED && failed) v = __builtin_inff();
-      if (lane == 0) sm.mx[wave][gg] = v;
-    }
-    lds_barrier();
-    float v = -__builtin_inff();
+    for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(largest), gg));
 #pragma unroll
-    for (int w = 0; w < SEL_WAVES; ++w) v = fmaxf(v, sm.mx[min(w, nw - 1)][gl]);
-    if (TAGGED && __ballot(v == __builtin_inff()) != 0 && any_failed()) return false;    // (a weight may be infinite)
-    if (S > 1) {                                       // ... and over the slices: r is a slice
-      if (wave == 0 && lane < G) st_tag(mine + lane, __float_as_uint(v), tag);
-      const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
-      unsigned long long w0 = 0, w1 = 0;
-      failed = !poll(WAIT_MAXIMA, [&]() {
-        w0 = ld_tag(all + (size_t)r0 * 3 * MAX_G + gl);
-        w1 = ld_tag(all + (size_t)r1 * 3 * MAX_G + gl);
-        return ((uint32_t)(w0 >> 32) == tag) & ((uint32_t)(w1 >> 32) == tag);
-      });
-      v = fmaxf(__uint_as_float((uint32_t)w0), __uint_as_float((uint32_t)w1));
-      v = fmaxf(v, __shfl_xor(v, 8, 64));
-      v = fmaxf(v, __shfl_xor(v, 16, 64));
-      v = fmaxf(v, __shfl_xor(v, 32, 64));
-    }
+    for (int u = 0; u < REGS; ++u) {
+      if (u >= U) break;
+      if (ours(u)) {
 #pragma unroll
-    for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), gg));
-    FKV_STAMP(a, head, 3);
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      unsigned long long z = 0;
-#pragma unroll
-      for (int u = 0; u < REGS; ++u) {
-        if (u < U) {
+        for (int gg = 0; gg < G; ++gg) {
           e[u][gg] = softmax_fixed(__uint_as_float(e[u][gg]), mx[gg]);
-          if (ours(u)) z += e[u][gg];
+          const u16x2 c = __builtin_bit_cast(u16x2, e[u][gg]);
+          zl[gg] = __builtin_amdgcn_udot2(c, u16x2{1, 0}, zl[gg], false);
+          zh[gg] = __builtin_amdgcn_udot2(c, u16x2{0, 1}, zh[gg], false);
         }
       }
-      z = wave_sum_u48(z);
-      if (failed) z = 1ull << 56;                      // (sums are below 2^46)
-      if (lane == 0) sm.z[wave][gg] = z;
     }
+    // (sums of a head are below 2^46)
+    unsigned long long z = (unsigned long long)class_fold<GP>(zl, OpAddU32()) + ((unsigned long long)class_fold<GP>(zh, OpAddU32()) << 16);
+    if (failed) z = 1ull << 47;
+    if (lane < MAX_G) sm.z[wave][lane] = z;
     lds_barrier();
-    unsigned long long z = 0;
-#pragma unroll
-    for (int w = 0; w < SEL_WAVES; ++w) z += w < nw ? sm.z[w][gl] : 0ull;
-    if (S > 1) {
-      if (__ballot(z >> 56 != 0) != 0) return false;
+    z = class8_sum_u48((lane >> 3) < nw ? sm.z[min(lane >> 3, nw - 1)][lane & 7] : 0ull);
+    if (__ballot(z >> 47 != 0) != 0) return Selected::NOTHING;
+    if (S > 1) {                                       // ... and over the slices: lane 8r + g reads slice r's, r's and r + 8's
       if (wave == 0 && lane < G) {
-        st_tag(mine + MAX_G + lane, (uint32_t)z, tag);
-        st_tag(mine + 2 * MAX_G + lane, (uint32_t)(z >> 32), tag);
+        st_tag(mine + lane, (uint32_t)z, tag);
+        st_tag(mine + MAX_G + lane, (uint32_t)(z >> 32), tag);
       }
-      const int r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
+      const int gl = min(lane & 7, G - 1), r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
       unsigned long long w[4];
       failed = !poll(WAIT_SUMS, [&]() {
-        const unsigned long long* p0 = all + (size_t)r0 * 3 * MAX_G + MAX_G + gl;
-        const unsigned long long* p1 = all + (size_t)r1 * 3 * MAX_G + MAX_G + gl;
+        const unsigned long long* p0 = all + (size_t)r0 * 2 * MAX_G + gl;
+        const unsigned long long* p1 = all + (size_t)r1 * 2 * MAX_G + gl;
         w[0] = ld_tag(p0); w[1] = ld_tag(p0 + MAX_G); w[2] = ld_tag(p1); w[3] = ld_tag(p1 + MAX_G);
         return ((uint32_t)(w[0] >> 32) == tag) & ((uint32_t)(w[1] >> 32) == tag) & ((uint32_t)(w[2] >> 32) == tag) & ((uint32_t)(w[3] >> 32) == tag);
       });
       z = 0;
       if ((lane >> 3) < S) z += (w[0] & 0xffffffffull) | (w[1] << 32);
       if ((lane >> 3) + 8 < S) z += (w[2] & 0xffffffffull) | (w[3] << 32);
-#pragma unroll
-      for (int d = 8; d < 64; d <<= 1) {
-        const uint32_t zl = (uint32_t)__shfl_xor((int)(uint32_t)z, d, 64), zh = (uint32_t)__shfl_xor((int)(uint32_t)(z >> 32), d, 64);
-        z += ((unsigned long long)zh << 32) | zl;
-      }
+      z = class8_sum_u48(z);
     }
-    // one reciprocal per lane, handed to every lane as a scalar
+    // one reciprocal per lane, handed to the row's other lanes (as scalars they would need 32 registers that are not there)
     const double zv = (double)z, yv = reciprocal_near(zv);
-    const unsigned long long zb = __builtin_bit_cast(unsigned long long, zv), yb = __builtin_bit_cast(unsigned long long, yv);
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      zd[gg] = __builtin_bit_cast(double, ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(zb >> 32), gg) << 32) |
-                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)zb, gg));
-      zr[gg] = __builtin_bit_cast(double, ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(yb >> 32), gg) << 32) |
-                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)yb, gg));
-    }
+    auto hand = [&](auto gc) {
+      constexpr int gg = decltype(gc)::value;
+      if constexpr (gg < G) { zd[gg] = row_bcast_f64<gg>(zv); zr[gg] = row_bcast_f64<gg>(yv); }
+    };
+    hand(UnrollBy<0>{}); hand(UnrollBy<1>{}); hand(UnrollBy<2>{}); hand(UnrollBy<3>{});
+    hand(UnrollBy<4>{}); hand(UnrollBy<5>{}); hand(UnrollBy<6>{}); hand(UnrollBy<7>{});
   } else {
-    if (any_failed()) return false;                    // (and behind its barrier the histogram is clear)
+    if (any_failed()) return Selected::NOTHING;        // (and behind its barrier the histogram is clear)
   }
   FKV_STAMP(a, head, 4);
 
   // ---- pooled scores -> keys ----
+  uint32_t key[REGS];
+  int id[REGS];
+  uint32_t have = 0;
+#pragma unroll
+  for (int u = 0; u < REGS; ++u) { key[u] = 0; id[u] = lo + j0 + tid + u * nt; }
 #pragma unroll
   for (int u = 0; u < REGS; ++u) {
-    const int j = j0 + tid + u * nt;
-    if (u < U) {
-      kreg[u] = score_key(pooled_score<G>(e[u], zd, zr, mode));
-      if (ours(u)) {
-        if (last) {
-          key[j] = kreg[u];
-          atomicAdd(&sm.hist[topk_bin(kreg[u], soft)], 1u);
-        } else if (!failed) {
-          st_tag(a.keyx + (size_t)head * a.max_pages + j, kreg[u], tag);
+    if (u >= U) break;
+    key[u] = score_key(pooled_score<G>(e[u], zd, zr, mode));
+    if (ours(u)) have |= 1u << u;
+  }
+  auto store_scores = [&]() {                          // (kept for inspection)
+#pragma unroll
+    for (int u = 0; u < REGS; ++u) {
+      if (u >= U) break;
+      if (have >> u & 1u) a.score[(size_t)head * a.max_pages + id[u]] = key_score(key[u]);
+    }
+  };
+  unsigned long long* const keyx = a.keyx + (size_t)head * a.max_pages;
+  unsigned long long* const keyid = a.keyid + (size_t)head * a.max_pages;
+  const int m = handed_on(S, a.slice, kk);
+  const bool all = m == a.slice;                       // (then a key's place says whose it is)
+  if (!last && all) {
+#pragma unroll
+    for (int u = 0; u < REGS; ++u) {
+      if (u >= U) break;
+      if ((have >> u & 1u) && !failed) st_tag(keyx + id[u] - lo, key[u], tag);
+    }
+    store_scores();
+    return failed ? Selected::NOTHING : Selected::IDS;
+  }
+  const int others = last ? (S - 1) * m : 0, X = (others + nt - 1) / nt;       // what the other groups hand on, and its rows
+  const bool fits = X <= SEL_OTHERS;
+#pragma unroll
+  for (int u = 0; u < REGS; ++u) {
+    if (u >= U) break;
+    if (have >> u & 1u) {
+      if (!fits) key_lds[others + id[u] - lo - j0] = key[u];
+      atomicAdd(&sm.hist[topk_bin(key[u], soft)], 1u);
+    }
+  }
+  uint32_t key_of[SEL_OTHERS];                         // the other groups'
+  int id_of[SEL_OTHERS];
+  uint32_t have_of = 0;
+#pragma unroll
+  for (int x = 0; x < SEL_OTHERS; ++x) { key_of[x] = 0; id_of[x] = 0; }
+  if (S > 1) {
+    if (fits) {
+      if (X > 0) {
+        unsigned long long w[SEL_OTHERS][2];
+        const bool ok = poll(WAIT_KEYS, [&]() {
+          bool there = true;
+#pragma unroll
+          for (int x = 0; x < SEL_OTHERS; ++x) w[x][0] = ld_tag(keyx + min(tid + min(x, X - 1) * nt, others - 1));
+          if (!all) {
+#pragma unroll
+            for (int x = 0; x < SEL_OTHERS; ++x) w[x][1] = ld_tag(keyid + min(tid + min(x, X - 1) * nt, others - 1));
+          }
+#pragma unroll
+          for (int x = 0; x < SEL_OTHERS; ++x) there = there & ((uint32_t)(w[x][0] >> 32) == tag);
+          if (!all) {
+#pragma unroll
+            for (int x = 0; x < SEL_OTHERS; ++x) there = there & ((uint32_t)(w[x][1] >> 32) == tag);
+          }
+          return there;
+        });
+        failed = failed || !ok;
+#pragma unroll
+        for (int x = 0; x < SEL_OTHERS; ++x) {
+          if (x >= X) break;
+          if (tid + x * nt < others) {
+            key_of[x] = (uint32_t)w[x][0];
+            id_of[x] = all ? lo + tid + x * nt : (int)(uint32_t)w[x][1];
+            have_of |= 1u << x;
+            atomicAdd(&sm.hist[topk_bin(key_of[x], soft)], 1u);
+          }
+        }
+      }
+    } else {
+      for (int i0 = tid; i0 - lane < others && !failed; i0 += 4 * nt) {
+        unsigned long long w[4][2];
+        failed = !poll(WAIT_KEYS, [&]() {
+          bool there = true;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) w[x][0] = ld_tag(keyx + min(i0 + x * nt, others - 1));
+          if (!all) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) w[x][1] = ld_tag(keyid + min(i0 + x * nt, others - 1));
+          }
+#pragma unroll
+          for (int x = 0; x < 4; ++x) there = there & ((uint32_t)(w[x][0] >> 32) == tag);
+          if (!all) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) there = there & ((uint32_t)(w[x][1] >> 32) == tag);
+          }
+          return there;
+        });
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          if (i0 + x * nt < others) {
+            key_lds[i0 + x * nt] = (uint32_t)w[x][0];
+            atomicAdd(&sm.hist[topk_bin((uint32_t)w[x][0], soft)], 1u);
+          }
         }
       }
     }
+    if (failed) sm.alone = 1;
   }
-  if (!last) return !failed;
-  // the other slices' keys (lower block indices)
-  for (int jj = tid; jj - lane < j0 && !failed; jj += 4 * nt) {
-    unsigned long long w[4];
-    failed = !poll(WAIT_KEYS, [&]() {
-      bool ok = true;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) w[u] = ld_tag(a.keyx + (size_t)head * a.max_pages + min(jj + u * nt, j0 - 1));
-#pragma unroll
-      for (int u = 0; u < 4; ++u) ok = ok & ((uint32_t)(w[u] >> 32) == tag);
-      return ok;
-    });
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (jj + u * nt < j0) {
-        key[jj + u * nt] = (uint32_t)w[u];
-        atomicAdd(&sm.hist[topk_bin((uint32_t)w[u], soft)], 1u);
-      }
-    }
-  }
-  if (failed) sm.alone = 1;
   lds_barrier();
-  return S == 1 || sm.alone == 0;
+  if (S > 1 && sm.alone != 0) return Selected::NOTHING;
+  FKV_STAMP(a, head, 5);
+  store_scores();
+  if (!fits) return Selected::KEYS;
+  const PutId put(a, head, key_lds);
+  bool done;
+  if (S == 1) {
+    done = topk_items<REGS>(key, have, U, 0, n, kk, soft, nw, sm, [&](int pos, int u) { put(pos, id[u]); });
+  } else {                                             // (U <= SEL_REGS)
+    constexpr int R = SEL_OTHERS + SEL_REGS;
+    uint32_t item[R];
+    int item_id[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      item[u] = u < SEL_OTHERS ? key_of[u < SEL_OTHERS ? u : 0] : key[u < SEL_OTHERS ? 0 : u - SEL_OTHERS];
+      item_id[u] = u < SEL_OTHERS ? id_of[u < SEL_OTHERS ? u : 0] : id[u < SEL_OTHERS ? 0 : u - SEL_OTHERS];
+    }
+    done = topk_items<SEL_OTHERS>(item, have_of | have << SEL_OTHERS, X, U, others + j1 - j0, kk, soft, nw, sm, [&](int pos, int u) {
+      if (last) {
+        put(pos, item_id[u]);
+      } else {
+        st_tag(keyx + s * m + pos, item[u], tag);
+        st_tag(keyid + s * m + pos, (uint32_t)item_id[u], tag);
+      }
+    });
+  }
+  if (__builtin_expect(done, 1)) return Selected::IDS;
+#pragma unroll
+  for (int u = 0; u < REGS; ++u)
+    if (have >> u & 1u) key_lds[others + tid + u * nt] = key[u];
+#pragma unroll
+  for (int x = 0; x < SEL_OTHERS; ++x)
+    if (have_of >> x & 1u) key_lds[tid + x * nt] = key_of[x];
+  lds_barrier();
+  return Selected::KEYS;
 }
 
 // The weight of one page for one query head of the group by one thread, bit for bit score_pages'.
@@ -857,77 +1125,73 @@ __device__ __forceinline__ void alone_keys(const StepArgs& a, int head, int nw, 
   lds_barrier();
 }
 
-// Selecting block `s` of a head, up to the keys.  True for the waves that go on with select_finish -- the last block's, nw of
-// them -- and `made`: whether the keys are there.
-template <int G, bool TAGGED, int REGS = SEL_REGS>
-__device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s, uint32_t* key, int& nw, bool& made) {
+// Selecting block `s` of a head.  True for the waves that go on with select_finish -- the last block's, nw of them, and another's
+// that has its choice still to make -- and `got`: how far they are.
+template <int G, bool TAGGED>
+__device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s, uint32_t* key, int& nw, Selected& got) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = a.slices, j0 = s * a.slice, j1 = min(a.g.n_cand, j0 + a.slice);
   const bool last = s == S - 1;
-  // The waves that take part: as many as there are candidates for; all of them where a plan has to be made or keys of
+  // The waves that take part: as many as there are candidates for; all of them where a plan has to be made or the best of
   // other slices have to be gathered.  The others of the block end here (a barrier counts the waves that are left).
   nw = (last && S > 1) || a.plan_new_slots || a.g.k_eff == 0 ? SEL_WAVES : min(SEL_WAVES, (j1 - j0 + 63) / 64);
-  made = true;
+  got = Selected::IDS;
   if (wave >= nw) return false;
   if (a.g.k_eff == 0) return true;
-  // What select_finish needs of the arguments is read now, while the weights are waited for, and not at the end of the chain
+  // What the end of the chain needs of the arguments is read now, while the weights are waited for
   // (0.3 us of a layer-step of 8 to 20 us).
-  asm volatile("" ::"s"(a.ids), "s"(a.ids_user), "s"(a.tagged), "s"(a.k), "s"(launch_tag(a.no)), "s"(a.plan_new_slots));
-  uint32_t kreg[REGS];
-  made = __builtin_amdgcn_readfirstlane(shared_keys<G, TAGGED, REGS>(a, head, s, nw, key, select_lds(), kreg));
-  if (made) {                                            // the pooled scores, kept for inspection
-#pragma unroll
-    for (int u = 0; u < REGS; ++u) {
-      const int j = j0 + tid + u * nw * 64;
-      if (j < j1) a.score[(size_t)head * a.max_pages + a.g.cand_lo + j] = key_score(kreg[u]);
-    }
-  }
-  return last;
+  got = (Selected)__builtin_amdgcn_readfirstlane((int)select_group<G, TAGGED>(a, head, s, nw, key, select_lds()));
+  return last || got == Selected::KEYS;
 }
 
-// ... and from the keys on, by nw waves: the top-k, the ids out, the recall plan.
-template <int DT, int G, bool TAGGED>
-__device__ __forceinline__ void select_finish(const StepArgs& a, int head, uint32_t* key, int nw, bool made) {
+// ... and what is left after it, by nw waves: the ids where they are not out yet, the recall plan.  again(): the arguments once
+// more, from memory, for what is hardly ever run (kept up to here they would cost the rest its scalar registers).
+template <int DT, int G, bool TAGGED, typename Again>
+__device__ __forceinline__ void select_finish(const StepArgs& hot, int head, int s, uint32_t* key, int nw, Selected got, Again again) {
   SelectLds& sm = select_lds();
   const int tid = threadIdx.x, nt = nw * 64;
-  const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff, k = a.k;
-  const uint32_t tag = launch_tag(a.no);
-  int32_t* out = a.ids + (size_t)head * k;
-  int32_t* outu = a.ids_user ? a.ids_user + (size_t)head * k : nullptr;
-  // a picked id goes out three ways: the layer's id list, the caller's copy, and (one-launch layer-step) as a tagged
-  // word, so that a waiting attention wave sees "this launch's id" in one read
-  unsigned long long* tagw = a.tagged ? a.tagged + (size_t)head * k : nullptr;
-  // With a recall plan to make, the ids are only collected in the plan's LDS here and everything goes out after it.
-  int32_t* plan_sm = reinterpret_cast<int32_t*>(key) + a.plan_lds_off;
-  int32_t* plan_nid = a.plan_new_slots ? plan_sm + 4 * k : nullptr;
-  auto put_id = [&](int pos, int id) {
-    if (plan_nid) { plan_nid[pos] = id; return; }
-    if (tagw) st_tag(tagw + pos, (uint32_t)id, tag);
-    out[pos] = id;
-    if (outu) outu[pos] = id;
-  };
-  if (kk > 0) {
-    if (__builtin_expect(!made, 0)) alone_keys<DT, G, TAGGED>(a, head, nw, key, sm);
-    FKV_STAMP(a, head, 5);
-    block_topk(key, n, kk, a.sel_pool <= 1, nw, sm, [&](int pos, int j) { put_id(pos, lo + j); });
+  if (__builtin_expect(hot.g.k_eff > 0 && got != Selected::IDS, 0)) {
+    const StepArgs a = again();
+    const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff;
+    const uint32_t tag = launch_tag(a.no);
+    const PutId put(a, head, key);
+    const bool alone = got == Selected::NOTHING;
+    if (alone) {
+      alone_keys<DT, G, TAGGED>(a, head, nw, key, sm);
+      for (int j = tid; j < n; j += nt) a.score[(size_t)head * a.max_pages + lo + j] = key_score(key[j]);
+    }
+    // the keys in LDS: every candidate's, or what the other groups handed on and then this one's
+    const bool last = alone || s == a.slices - 1;
+    const int j0 = alone ? 0 : s * a.slice, m = handed_on(a.slices, a.slice, kk), others = last && !alone ? (a.slices - 1) * m : 0;
+    unsigned long long* const keyid = a.keyid + (size_t)head * a.max_pages;
+    block_topk(key, last ? others + n - j0 : a.slice, kk, a.sel_pool <= 1, nw, sm, [&](int pos, int j) {
+      const int id = j >= others ? lo + j0 + j - others : m == a.slice ? lo + j : (int)(uint32_t)ld_tag(keyid + j);
+      if (last) { put(pos, id); return; }
+      st_tag(a.keyx + (size_t)head * a.max_pages + s * m + pos, key[j], tag);
+      st_tag(keyid + s * m + pos, (uint32_t)id, tag);
+    });
+    if (!last) return;
   }
-  for (int i = kk + tid; i < k; i += nt) put_id(i, -1);   // padding
-  if (plan_nid) {
+  const StepArgs& a = hot;
+  const int kk = a.g.k_eff, k = a.k;
+  const uint32_t tag = launch_tag(a.no);
+  const PutId put(a, head, key);
+  for (int i = kk + tid; i < k; i += nt) put(i, -1);      // padding
+  if (put.plan_nid) {
+    int32_t* const plan_sm = reinterpret_cast<int32_t*>(key) + a.plan_lds_off;
     lds_barrier();                                       // the ids are all in LDS
-    plan_head<SEL_THREADS>(out, a.plan_act_ids + (size_t)head * k, a.plan_act_slots + (size_t)head * k,
+    plan_head<SEL_THREADS>(put.out, a.plan_act_ids + (size_t)head * k, a.plan_act_slots + (size_t)head * k,
                            a.plan_new_slots + (size_t)head * k, a.plan_miss + (size_t)head * (1 + 3 * k), k, a.g.n_full,
                            plan_sm, true);
     const int32_t* nslot = plan_sm + 5 * k;
     for (int i = tid; i < k; i += SEL_THREADS) {
-      const int id = plan_nid[i], sl = nslot[i];
-      if (tagw) st_tag(tagw + i, tagged_pick(id, sl & (TAGGED_MAX_SLOTS - 1), (sl & PLAN_MISS_BIT) != 0), tag);
-      out[i] = id;
-      if (outu) outu[i] = id;
+      const int id = put.plan_nid[i], sl = nslot[i];
+      if (put.tagw) st_tag(put.tagw + i, tagged_pick(id, sl & (TAGGED_MAX_SLOTS - 1), (sl & PLAN_MISS_BIT) != 0), tag);
+      put.out[i] = id;
+      if (put.outu) put.outu[i] = id;
     }
   }
   FKV_STAMP(a, head, 8);
-  // the pooled scores, kept for inspection: the group's own, or all of them if it was alone
-  if (!made) for (int j = tid; j < n; j += nt) a.score[(size_t)head * a.max_pages + lo + j] = key_score(key[j]);
 }
 
 // ---------------------------------------------------------------------------------

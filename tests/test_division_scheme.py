@@ -55,3 +55,29 @@ def test_refined_reciprocal_division_is_correctly_rounded():
         seed_error = (2.0 ** -rng.randrange(12, 40)) * (1 if i % 2 else -1)
         assert div_scheme(float(e), float(z), seed_error) == e / z, (e, z, seed_error)
         assert abs(reciprocal(float(z), seed_error) * z - 1.0) <= 2.0 ** -51
+
+
+def div_once(a: float, b: float, seed_error: float) -> float:
+    y = reciprocal(b, seed_error)
+    q = a * y
+    return fma(fma(-b, q, a), y, q)
+
+
+def test_one_correction_is_enough():
+    """What the kernel does: with y within 2^-52, q = E*y is off by at most four units in its last place, so that one
+    correction leaves 4 * 2^-52 of a unit, which is less than the 2^-49 above.  And the mean over a group: a sum of such
+    quotients divided by G, from RN(1/G) with one correction."""
+    rng = random.Random(6)
+    for i in range(60000):
+        z = rng.randrange(1, 1 << rng.randrange(1, 49)) if i % 3 else (1 << rng.randrange(2, 49)) + rng.randrange(-3, 4)
+        z = min(max(z, 1), (1 << 48) - 1)
+        e = rng.randrange(0, min(z, (1 << 32) - 1) + 1)
+        seed_error = (2.0 ** -rng.randrange(12, 40)) * (1 if i % 2 else -1)
+        assert abs(Fraction(reciprocal(float(z), seed_error)) * z - 1) <= Fraction(1, 1 << 52)
+        assert div_once(float(e), float(z), seed_error) == e / z, (e, z, seed_error)
+    for G in range(1, 9):
+        y = 1.0 / G
+        for _ in range(5000):
+            a = sum(rng.random() * 2.0 ** -rng.randrange(0, 30) for _ in range(G))
+            q = a * y
+            assert fma(fma(-float(G), q, a), y, q) == a / G, (a, G)
