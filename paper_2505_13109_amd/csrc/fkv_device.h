@@ -107,6 +107,10 @@ struct OpMaxF32 {   // on bit patterns of floats
     return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
   }
 };
+struct OpAddF32 {   // on bit patterns of floats
+  static __device__ __forceinline__ uint32_t identity() { return 0u; }
+  __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); }
+};
 struct OpAddU32 {
   static __device__ __forceinline__ uint32_t identity() { return 0u; }
   __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; }
@@ -119,7 +123,7 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) { return wave_reduc
 // (in a quad by permutation, in a row of 16 lanes by rotation, over the rows by the row-swapping moves)
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false); }
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128, DPP_BCAST = 0x150;
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128, DPP_HALF_MIRROR = 0x141, DPP_BCAST = 0x150;
 // lane LANE's value of each row of 16 lanes
 template <int LANE>
 __device__ __forceinline__ double row_bcast_f64(double v) {

@@ -324,6 +324,7 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
   if (step) {
     s = u.step_args(ka);
     bool go_on = false;
+    asm volatile(".p2align 6");       // (where the roles' code starts within 64 bytes is worth up to 2 %)
     step_roles<DT, G>(s, blockIdx.x, blockIdx.y, [&](int m, int slice) {
       head = m;
       own = slice;
