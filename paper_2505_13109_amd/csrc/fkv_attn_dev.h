@@ -265,15 +265,30 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   const int pk_lo = g.n_sink, pk_hi = g.n_sink + k;
   const int p = split * a.pps + wave + lane * NW;       // (a wave has at most 64 positions: attn_pages_per_block)
   const bool picked = p >= pk_lo && p < pk_hi && p < p_end;
-  const bool pending = !FUSED && (a.use == 1 || (a.use == 2 && a.flags[head] != 0));
-  const int32_t* ids = (pending ? a.new_ids : a.act_ids) + (size_t)head * k;
-  const int32_t* slots = pd.placement == 0 ? nullptr : (pending ? a.new_slots : a.act_slots) + (size_t)head * k;
   int page_l, unit_l;
   page_l = unit_l = -1;
   if (p < p_end) {
     if (picked) {
-      page_l = ids[p - pk_lo];
-      if (page_l >= 0) unit_l = pd.placement == 0 ? page_l : pd.sel_base + slots[p - pk_lo];
+      const size_t at = (size_t)head * k + (p - pk_lo);
+      int slot = 0;
+      if (FUSED) {
+        page_l = a.act_ids[at];
+        if (pd.placement != 0) slot = a.act_slots[at];
+      } else {
+        // by flag: both lists and the flag in one trip, not the list that the flag says after it
+        const int32_t* const ids0 = a.use == 1 ? a.new_ids : a.act_ids;
+        const int32_t* const ids1 = a.use == 0 ? a.act_ids : a.new_ids;
+        const int id0 = ids0[at], id1 = ids1[at];
+        int slot0 = 0, slot1 = 0;
+        if (pd.placement != 0) {
+          slot0 = (a.use == 1 ? a.new_slots : a.act_slots)[at];
+          slot1 = (a.use == 0 ? a.act_slots : a.new_slots)[at];
+        }
+        const bool second = a.use == 2 && a.flags[head] != 0;
+        page_l = second ? id1 : id0;
+        slot = second ? slot1 : slot0;
+      }
+      if (page_l >= 0) unit_l = pd.placement == 0 ? page_l : pd.sel_base + slot;
     } else {
       page_l = p < pk_lo ? p : g.n_full - g.n_win + (p - pk_hi);
       unit_l = resident_unit(pd, page_l);

@@ -27,6 +27,27 @@ __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
   });
 }
 
+// The append and the correction test as calls of their own (fkv_kv_append, fkv_corr_check).  Both are one trip to memory and
+// little else, so what counts is what a launch brings along: no more waves than there is work for, and arguments that fit the
+// registers the hardware preloads (8 heads, 2.7 us each as roles of the step kernel, whose arguments are fetched first; a kernel
+// that does nothing takes 1.6).
+template <int DT>
+__global__ __launch_bounds__(D) void append_kernel(uint16_t* pool, uint16_t* summ, const uint16_t* k_new, const uint16_t* v_new, int L, int max_pages,
+                                                   int units_per_head, int placement, int ring_base, int n_ring) {
+  StepArgs a{};
+  a.pd = PoolDesc{pool, units_per_head, placement, ring_base, n_ring, 0};
+  a.summ = summ; a.k_new = k_new; a.v_new = v_new; a.max_pages = max_pages; a.g.L = L;
+  append_role<DT>(a, blockIdx.x);
+}
+template <int DT, int G>
+__global__ __launch_bounds__(G * 64) void corr_kernel(const uint16_t* q, const uint16_t* q_prev, uint16_t* q_stage, uint8_t* flags, uint8_t* flags_user,
+                                                      double* cosine, float tau, int have_prev_and_pool) {
+  StepArgs a{};
+  a.q = q; a.q_prev = q_prev; a.q_stage = q_stage; a.flags = flags; a.flags_user = flags_user; a.cosine = cosine; a.tau = tau;
+  a.have_prev = have_prev_and_pool & 1; a.corr_pool = have_prev_and_pool >> 1;
+  corr_role<DT, G, G>(a, blockIdx.x);
+}
+
 // The two halves of the bandwidth-bound regime.  The scan: append, correction test and page weights, in 256-thread
 // blocks of one 64-page chunk each; measured on the scan alone (256 heads x 992 pages, 130 MB; a plain read of the same
 // bytes takes 22.1 us = 5.9 TB/s on this machine): 23.9 us in this shape against 25.7 us with 512-thread blocks of 128
@@ -168,6 +189,16 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   int rows;
   size_t lds;
   const int heads = d.batch * d.n_kv;
+  if (roles == ROLE_APPEND) {
+    append_kernel<DT><<<heads, D, 0, st>>>(io.pd.pool, io.summ, io.k_new, io.v_new, g.L, d.max_pages, io.pd.units_per_head, io.pd.placement, io.pd.ring_base,
+                                           io.pd.n_ring);
+    return 1;
+  }
+  if (roles == ROLE_CORR) {
+    corr_kernel<DT, G><<<heads, G * 64, 0, st>>>(io.q, io.q_prev, io.q_stage, io.flags, io.flags_user, io.cosine, io.tau,
+                                                 (io.have_prev ? 1 : 0) | d.corr_pool << 1);
+    return 1;
+  }
   if (!(roles & ROLE_SELECT) || (g_fuse >= 0 ? g_fuse == 1 : (long)heads * ((g.n_cand + PAGES_PER_PASS - 1) / PAGES_PER_PASS) <= kFuseMaxChunks)) {
     const int slices = selection_slices(g, d.G, heads);
     fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
