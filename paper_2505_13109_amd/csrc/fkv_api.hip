@@ -582,14 +582,15 @@ int fkv_load_prefix(fkv_ctx* ctx, int32_t layer, const void* K_dev, const void* 
   if (n_tokens > 0 && (!K_dev || !V_dev)) return ctx->fail(FKV_EINVAL, "null K or V");
   LayerState& ls = ctx->layers[layer];
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const Geom g = make_geom(ctx->cfg, n_tokens);
+  // a fresh context: no previous query, nothing picked
   launch_load_prefix(ctx->dims, ctx->pool_desc(layer), ctx->summ(layer), ctx->host_pool(layer),
-                     static_cast<const uint16_t*>(K_dev), static_cast<const uint16_t*>(V_dev), n_tokens, g, st);
+                     static_cast<const uint16_t*>(K_dev), static_cast<const uint16_t*>(V_dev), n_tokens, ctx->ids(layer, 0), st);
   int rc = after_launch(ctx, "load_prefix kernel");
   if (rc) return rc;
-  // a fresh context: no previous query, nothing picked
-  const size_t n = (size_t)2 * ctx->cfg.batch * ctx->cfg.n_kv_heads * (ctx->lay.k > 0 ? ctx->lay.k : 1) * 4;
-  FKV_HIP(ctx, hipMemsetAsync(ctx->ids(layer, 0), 0xff, n, st));
+  if (n_tokens == 0) {
+    const size_t n = (size_t)2 * ctx->cfg.batch * ctx->cfg.n_kv_heads * (ctx->lay.k > 0 ? ctx->lay.k : 1) * 4;
+    FKV_HIP(ctx, hipMemsetAsync(ctx->ids(layer, 0), 0xff, n, st));
+  }
   ls.L = n_tokens;
   ls.parity = 0;
   ls.have_prev_q = ls.have_active = ls.have_pending = ls.staged_q = ls.have_flags = false;

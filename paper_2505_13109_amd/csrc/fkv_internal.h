@@ -164,7 +164,7 @@ constexpr int kComputeUnits = 256;
 constexpr int kMaxWaiting = kComputeUnits;
 int attn_pages_per_block(int n_att, int heads, int max_splits, int nw, int max_blocks = kMaxWaiting);
 void launch_load_prefix(const Dims& d, const PoolDesc& pd, uint16_t* summ, uint16_t* host_pool,
-                        const uint16_t* K, const uint16_t* V, int n_tokens, Geom g, hipStream_t st);
+                        const uint16_t* K, const uint16_t* V, int n_tokens, int32_t* ids, hipStream_t st);   // ids: [2][heads][k], emptied
 void launch_summary_recompute(const Dims& d, const PoolDesc& pd, uint16_t* summ, int first_page,
                               int n_pages, Geom g, hipStream_t st);
 void launch_offload(const Dims& d, const PoolDesc& pd, uint16_t* host_pool, int page, hipStream_t st);
