@@ -499,7 +499,7 @@ int fkv_create(const fkv_config* cfg, void* dev_arena, size_t dev_bytes, void* h
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeSharedMemPerBlockOptin, dev_id) == hipSuccess && v > max_lds) max_lds = v;
   }
   ctx->dims = Dims{cfg->batch, cfg->n_q_heads, cfg->n_kv_heads, cfg->n_q_heads / cfg->n_kv_heads, l.k, l.max_pages, cfg->dtype, max_lds,
-                   cfg->select_pooling, cfg->corr_pooling};
+                   cfg->select_pooling, cfg->corr_pooling, cfg->n_layers};
   ctx->dev = static_cast<char*>(dev_arena);
   ctx->host = cfg->placement == FKV_PLACE_HOST ? static_cast<char*>(host_arena) : nullptr;
   ctx->layers.resize(cfg->n_layers);

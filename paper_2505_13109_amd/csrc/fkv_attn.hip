@@ -6,12 +6,12 @@
 namespace fkv {
 
 // grid (n_splits, n_kv, batch); NW wavefronts per block
-template <int DT, int NW>
+template <int DT, int NW, bool PAST>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void attn_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) float attn_lds[];
   touch_args<sizeof(AttnArgs)>();
   const int head = (int)(blockIdx.z * a.n_kv + blockIdx.y);
-  const AttnLeft left = attn_block<DT, NW, false, false>(a, blockIdx.x, head, attn_lds);
+  const AttnLeft left = attn_block<DT, NW, false, false, PAST>(a, blockIdx.x, head, attn_lds);
   if (__builtin_expect(left.any(), 0))
     attn_finish<DT, NW, false, false>(args_from_memory<AttnArgs>(), blockIdx.x, head, left);
 }
@@ -59,8 +59,11 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   constexpr int NW = 4;
   const size_t lds = attn_lds_floats(NW, d.G) * sizeof(float);
   if (ev_begin) (void)hipEventRecord(ev_begin, st);
-  if (d.dtype == 0) attn_kernel<0, NW><<<grid, NW * 64, lds, st>>>(a);
-  else              attn_kernel<1, NW><<<grid, NW * 64, lds, st>>>(a);
+  const bool past = (stream_of(d, g) & STREAM_PAGES) != 0;
+  if (d.dtype == 0 && past) attn_kernel<0, NW, true><<<grid, NW * 64, lds, st>>>(a);
+  else if (d.dtype == 0)    attn_kernel<0, NW, false><<<grid, NW * 64, lds, st>>>(a);
+  else if (past)            attn_kernel<1, NW, true><<<grid, NW * 64, lds, st>>>(a);
+  else                      attn_kernel<1, NW, false><<<grid, NW * 64, lds, st>>>(a);
   if (ev_end) (void)hipEventRecord(ev_end, st);
 }
 

@@ -224,7 +224,8 @@ __device__ __forceinline__ float output_alone(const AttnArgs& a, int head, bool 
 // One block of NW wavefronts: attend-list positions [split*pps, (split+1)*pps) of `head`,
 // wave w takes w, w+NW, ...  `lds`: attn_lds_floats(NW, G) floats, 16-byte aligned.
 // FUSED: in a launch with the step roles; HOSTFUSED: that, with the KV in a host pool (compile-time choices: what they
-// add to the page loop would cost the other launches registers).
+// add to the page loop would cost the other launches registers).  PAST: pages are read past the caches (STREAM_PAGES; as a branch
+// around the loads it costs short launches 2 to 3 %).
 // Returns what it waited for in vain and left to attn_finish.
 struct AttnLeft {
   bool ids;                  // the head's picked ids (the same in every thread of the block); before that, the block makes them
@@ -233,7 +234,7 @@ struct AttnLeft {
   uint32_t outputs;          // bit t: the thread's t-th output
   __device__ __forceinline__ bool any() const { return ids || __ballot(outputs != 0) != 0; }
 };
-template <int DT, int NW, bool FUSED, bool HOSTFUSED>
+template <int DT, int NW, bool FUSED, bool HOSTFUSED, bool PAST>
 __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int head, float* lds) {
   typedef typename Mma<DT>::vec vec;
   static_assert(!FUSED || NW >= MAX_G, "the correction test takes a wave per query head");
@@ -328,7 +329,10 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u));
     asm volatile("" : "+s"(base));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = *(const __attribute__((address_space(1))) u32x4*)(base + j * 1024 + lane16);
+    for (int j = 0; j < 4; ++j) {
+      const auto p = (const __attribute__((address_space(1))) u32x4*)(base + j * 1024 + lane16);
+      w[j] = PAST ? __builtin_nontemporal_load(p) : *p;
+    }
   };
   auto load_k = [&](const char* up) { load4(kw, up); load4(kw + 4, up + 4096); };
   auto load_v = [&](const char* up) { load4(vw, up + 8192); load4(vw + 4, up + 12288); };

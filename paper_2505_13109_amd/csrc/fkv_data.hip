@@ -6,7 +6,6 @@
 
 namespace fkv {
 
-typedef __attribute__((ext_vector_type(4))) uint32_t u4v;
 // ---- bulk load: grid (n_pages, n_kv, batch), 256 threads ------------------------
 // Bound by memory, half of it reads and half writes, neither touched again soon: both past the caches (two requests of 20K tokens,
 // 8 heads, 338 MB: 62 us a launch with plain accesses, 60 with only the reads past them, 54 so: 6.2 TB/s; stores to a host
@@ -34,8 +33,8 @@ __global__ __launch_bounds__(256) void load_prefix_kernel(PoolDesc pd, uint16_t*
     uint4 kv4 = make_uint4(0, 0, 0, 0), vv4 = make_uint4(0, 0, 0, 0);
     if (t < nv) {
       const size_t src = ((size_t)(b * (size_t)n_tokens + page * PG + t) * n_kv + m) * D + c8 * 8;
-      kv4 = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u4v*>(K + src)));
-      vv4 = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u4v*>(V + src)));
+      kv4 = load_past(K + src);
+      vv4 = load_past(V + src);
     }
     *reinterpret_cast<uint4*>(sk + t * D + c8 * 8) = kv4;
     *reinterpret_cast<uint4*>(sv + t * D + c8 * 8) = vv4;
@@ -68,7 +67,7 @@ __global__ __launch_bounds__(256) void load_prefix_kernel(PoolDesc pd, uint16_t*
       }
     }
     const uint4 w = *reinterpret_cast<const uint4*>(o);
-    if (dst_gpu) __builtin_nontemporal_store(__builtin_bit_cast(u4v, w), reinterpret_cast<u4v*>(dst_gpu + i * 8));
+    if (dst_gpu) __builtin_nontemporal_store(__builtin_bit_cast(word4, w), reinterpret_cast<word4*>(dst_gpu + i * 8));
     if (dst_host) *reinterpret_cast<uint4*>(dst_host + i * 8) = w;
   }
   if (tid < D) {

@@ -4,6 +4,12 @@
 
 namespace fkv {
 
+// 16 bytes, or the same past the caches
+typedef __attribute__((ext_vector_type(4))) uint32_t word4;
+__device__ __forceinline__ uint4 load_past(const uint16_t* p) {
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const word4*>(p)));
+}
+
 // one storage element / a packed pair of them -> fp32 (exact)
 template <int DT> struct Unpack;
 template <> struct Unpack<0> {   // fp16

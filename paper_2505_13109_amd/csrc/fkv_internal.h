@@ -78,7 +78,7 @@ __host__ __device__ inline int v_elem_off(int t, int ch) {
 }
 
 // ---- launch wrappers (defined in the kernel files) ----------------------
-struct Dims { int batch, n_q, n_kv, G, k, max_pages, dtype, max_lds, sel_pool, corr_pool; };
+struct Dims { int batch, n_q, n_kv, G, k, max_pages, dtype, max_lds, sel_pool, corr_pool, n_layers; };
 
 // Launches are numbered (31 bits, from 1), and the values that a launch's blocks exchange carry its number as a tag.  The
 // host counts.  A launch that is being captured runs again at every replay with the arguments it was captured with, so its
@@ -89,6 +89,19 @@ struct LaunchNo {
 };
 __host__ __device__ inline uint32_t host_tag(uint32_t launch) { return (launch << 1) | 1u; }
 __host__ __device__ inline uint32_t device_tag(uint32_t launch) { return launch << 1; }
+
+// What a decode step reads past the memory-side cache (256 MB), as bits.  All layers' summaries and attended pages are read again
+// at the next token, so as long as they fit they are better left there.  If they do not, a cyclic order of reads keeps
+// hardly any of them, and the summaries, of which more are read for every token served, go first: 8 layers of 32 heads x 992 candidates and 65
+// pages, 400 MB in all, 75 us a layer-step -> 63; but 268 MB in all 1 % slower, and with the pages past the cache as well 71.
+// Where the pages by themselves are too many, they go too: 8 layers of 128 heads x 65 pages, 1.1 GB, 40 us -> 37; 256 heads 65 -> 58;
+// 20 layers of 8 heads x 129 pages, 340 MB, no difference.
+constexpr int STREAM_SUMMARIES = 1, STREAM_PAGES = 2;      // (the second only with the first)
+inline int stream_of(const Dims& d, const Geom& g) {
+  const double heads = (double)d.n_layers * d.batch * d.n_kv;
+  const double pages = heads * (g.n_sink + d.k + g.n_win + 1) * UNIT_BYTES, summaries = heads * g.n_cand * 2 * D * 2;
+  return (pages + summaries > 270e6 ? STREAM_SUMMARIES : 0) | (pages > 400e6 ? STREAM_PAGES : 0);
+}
 
 // what blocks of a launch wait for, as bits (a test makes waits of these kinds run out at once)
 constexpr uint32_t WAIT_WEIGHTS = 1, WAIT_MAXIMA = 2, WAIT_SUMS = 4, WAIT_KEYS = 8, WAIT_SPLITS = 16, WAIT_IDS = 32;
@@ -156,6 +169,25 @@ struct LayerIO {
 // `reps` launches of a kernel that does nothing, with the given grid, 512 threads and dynamic LDS
 bool launch_floor(int grid, size_t lds, int reps, hipStream_t st);
 bool launch_layer(const Dims& d, const LayerIO& lio, Geom g, hipStream_t st);
+// how launch_layer has it launched, by the file that has the variant
+struct LayerLaunch { dim3 grid; size_t lds; uint32_t packed, plan, split_magic; };
+bool launch_layer_hbm(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+bool launch_layer_hbm_stream(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+bool launch_layer_hbm_past(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+bool launch_layer_host(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+bool launch_layer_host_stream(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+// Dynamic LDS above the default 64 KiB per block has to be granted per kernel function; false if the device refuses.
+template <typename F>
+static bool grant_lds(F* fn, size_t lds, size_t& granted) {
+  if (lds <= granted) return true;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  granted = lds;
+  return true;
+}
+
 constexpr int kComputeUnits = 256;
 // Most blocks of a launch that wait for each other (a head's attention blocks, and its selecting blocks where it has several):
 // half of those that fit (two to a compute unit).  That keeps waits short: in block order at most one head's blocks are half

@@ -1,0 +1,10 @@
+// The layer kernel's variants: KV in HBM, summaries and pages read past the caches.
+#include "fkv_layer_dev.h"
+
+namespace fkv {
+
+bool launch_layer_hbm_past(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st) {
+  return dtype == 0 ? launch_layer_variant<0, false, STREAM_SUMMARIES | STREAM_PAGES>(io, l, G, st) : launch_layer_variant<1, false, STREAM_SUMMARIES | STREAM_PAGES>(io, l, G, st);
+}
+
+}  // namespace fkv

@@ -1,0 +1,10 @@
+// The layer kernel's variants: KV in a host pool, summaries read past the caches.
+#include "fkv_layer_dev.h"
+
+namespace fkv {
+
+bool launch_layer_host_stream(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st) {
+  return dtype == 0 ? launch_layer_variant<0, true, STREAM_SUMMARIES>(io, l, G, st) : launch_layer_variant<1, true, STREAM_SUMMARIES>(io, l, G, st);
+}
+
+}  // namespace fkv

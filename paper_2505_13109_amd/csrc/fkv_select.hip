@@ -15,11 +15,11 @@ namespace fkv {
 // ---------------------------------------------------------------------------------
 // grid (heads, rows): rows as in step_roles
 // ---------------------------------------------------------------------------------
-template <int DT, int G>
+template <int DT, int G, bool PAST>
 __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];              // selection: n_cand keys, then the recall plan
   touch_args<sizeof(StepArgs)>();
-  step_roles<DT, G>(a, blockIdx.x, blockIdx.y, [&](int head, int s) {
+  step_roles<DT, G, PAST>(a, blockIdx.x, blockIdx.y, [&](int head, int s) {
     int nw;
     Selected got;
     if (select_begin<G, true>(a, head, s, dyn_lds, nw, got)) 
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(G * 64) void corr_kernel(const uint16_t* q, const u
 // the other two roles, then a head each; beyond kGridRows rows (a grid dimension ends at 65535) folded into a third dimension.
 constexpr int kGridRows = 1 << 15;
 template <int DT, int G>
-__global__ __launch_bounds__(SCAN_WAVES * 64) void scan_kernel(StepArgs a) {
+__global__ __launch_bounds__(SCAN_WAVES * 64) __attribute__((amdgpu_waves_per_eu(G <= 4 ? 7 : 5))) void scan_kernel(StepArgs a) {
   touch_args<sizeof(StepArgs)>();
   const int y = (int)(blockIdx.z * kGridRows + blockIdx.y);
   if (y >= a.other_rows + a.heads) return;
@@ -71,7 +71,8 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) void scan_kernel(StepArgs a) {
     if ((a.roles & ROLE_CORR) && i < a.heads) corr_role<DT, G, SCAN_WAVES>(a, i);
     return;
   }
-  score_role<DT, G, false, SCAN_WAVES>(a, y - a.other_rows, blockIdx.x);
+  score_role<DT, G, false, SCAN_WAVES, true>(a,     // (by itself it reads more than half of what the cache holds)
+                                              y - a.other_rows, blockIdx.x);
 }
 // The selection after it: one block per slice of a head's candidates, a head's slices adjacent.
 template <int G>
@@ -87,18 +88,6 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
 
 constexpr size_t kLdsPerUnit = 150 * 1024;   // of the 160 KiB of a compute unit
 constexpr int kLayerResident = 2 * kComputeUnits;   // blocks of the layer kernel that the GPU holds at once (by its registers)
-
-// Dynamic LDS above the default 64 KiB per block has to be granted per kernel function; false if the device refuses.
-template <typename F>
-static bool grant_lds(F* fn, size_t lds, size_t& granted) {
-  if (lds <= granted) return true;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  granted = lds;
-  return true;
-}
 
 // experiment builds only (see knob())
 static const int g_min_passes = knob("FKV_LAYER_PASSES", 0);      // passes a scoring block makes
@@ -184,7 +173,7 @@ constexpr long kFuseMaxChunks = 2560;
 
 template <int DT, int G>
 static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom& g, hipStream_t st) {
-  static size_t granted_step = 48 * 1024, granted_select = 48 * 1024;
+  static size_t granted_step = 48 * 1024, granted_past = 48 * 1024, granted_select = 48 * 1024;
   StepArgs a;
   int rows;
   size_t lds;
@@ -202,8 +191,10 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   if (!(roles & ROLE_SELECT) || (g_fuse >= 0 ? g_fuse == 1 : (long)heads * ((g.n_cand + PAGES_PER_PASS - 1) / PAGES_PER_PASS) <= kFuseMaxChunks)) {
     const int slices = selection_slices(g, d.G, heads);
     fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
-    if (!grant_lds(&step_kernel<DT, G>, lds, granted_step)) return -1;
-    step_kernel<DT, G><<<dim3(heads, rows), STEP_THREADS, lds, st>>>(a);
+    const bool past = (stream_of(d, g) & STREAM_SUMMARIES) != 0;
+    if (!(past ? grant_lds(&step_kernel<DT, G, true>, lds, granted_past) : grant_lds(&step_kernel<DT, G, false>, lds, granted_step))) return -1;
+    if (past) step_kernel<DT, G, true><<<dim3(heads, rows), STEP_THREADS, lds, st>>>(a);
+    else      step_kernel<DT, G, false><<<dim3(heads, rows), STEP_THREADS, lds, st>>>(a);
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
   }
@@ -235,176 +226,6 @@ int launch_step(const Dims& d, int roles, const StepIO& io, Geom g, hipStream_t 
   }
 }
 
-// ---------------------------------------------------------------------------------
-// The whole layer-step in ONE launch: the step roles followed by the attention blocks.  In a step without correction
-// the two chains do not depend on each other -- attention reads the previous step's page ids, takes the new token from
-// the step's inputs and redoes the (tiny) correction test itself -- so they overlap; the attention blocks
-// of a corrected head wait for that head's selection, made by blocks with lower indices.
-// grid (heads, step rows + splits)
-// ---------------------------------------------------------------------------------
-typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // (scalar loads)
-
-// packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), pages per
-// split (9), lose_selection, WAIT_* bits;   split_magic: 2^32 / splits rounded up, 0 for one split
-constexpr int kMaxLayersPacked = 1 << 13, kMaxCtxPacked = 1 << 19;
-struct LayerKernelArgs {                     // the kernel's arguments, in their order
-  const LayerConst* consts;
-  const uint16_t *q, *k_new, *v_new;
-  float* out;
-  uint32_t packed, host_numbered, plan, split_magic;
-};
-
-// what every block works out from the constants
-template <bool HOSTPOOL>
-struct LayerSetup {
-  LayerConstPtr c;
-  char* base;
-  uint16_t* qprev0;
-  int32_t *ids0, *slots0;
-  Geom g;
-  uint32_t tag;
-  PoolDesc pd;
-  int layer, now, before, chunks, passes_log2, slices_log2, slices, step_rows;      // now, before: halves (PENDING / staged, ACTIVE / previous)
-  __device__ __forceinline__ explicit LayerSetup(const LayerKernelArgs& ka) {
-    c = (LayerConstPtr)ka.consts;
-    layer = (int)(ka.packed >> 19);
-    now = (int)(ka.plan >> 1) & 1;
-    before = now ^ 1;
-    base = c->dev_base + c->layer_bytes * (unsigned long long)layer;
-    g = geom_of((int)(ka.packed & 0x7ffffu) + 1, c->n_sink, c->n_win, c->k);
-    tag = ka.host_numbered ? ka.host_numbered : device_tag((uint32_t)*(const __attribute__((address_space(4))) int*)c->launch_no);
-    qprev0 = reinterpret_cast<uint16_t*>(at(c->o_qprev));
-    ids0 = reinterpret_cast<int32_t*>(at(c->o_ids));
-    slots0 = reinterpret_cast<int32_t*>(at(c->o_slots));
-    pd.pool = reinterpret_cast<uint16_t*>(base);
-    pd.units_per_head = c->units_per_head;
-    pd.placement = HOSTPOOL ? 1 : 0;
-    pd.ring_base = c->ring_base; pd.n_ring = c->n_ring; pd.sel_base = c->sel_base;
-    passes_log2 = (int)(ka.plan >> 2) & 3;
-    const int chunk_log2 = 5 + passes_log2;
-    static_assert(PAGES_PER_PASS == 32, "chunks are a power of two of pages");
-    chunks = (g.n_cand + (1 << chunk_log2) - 1) >> chunk_log2;
-    slices_log2 = (int)(ka.plan >> 4) & 7;
-    slices = 1 << slices_log2;
-    step_rows = 2 + chunks + slices;
-  }
-  __device__ __forceinline__ char* at(uint32_t o) const { return base + (unsigned long long)o * 256; }
-  __device__ __forceinline__ uint16_t* qprev(int half) const { return qprev0 + (size_t)half * c->qprev_half; }
-  __device__ __forceinline__ int32_t* ids(int half) const { return ids0 + (size_t)half * c->ids_half; }
-  __device__ __forceinline__ int32_t* slots(int half) const { return slots0 + (size_t)half * c->ids_half; }
-
-  __device__ __forceinline__ StepArgs step_args(const LayerKernelArgs& ka) const {
-    StepArgs a;
-    a.roles = ROLE_APPEND | ROLE_CORR | ROLE_SELECT;
-    a.heads = c->heads; a.k = c->k; a.max_pages = c->max_pages; a.g = g; a.pd = pd;
-    a.summ = reinterpret_cast<uint16_t*>(at(c->o_summ));
-    a.k_new = ka.k_new; a.v_new = ka.v_new; a.q = ka.q;
-    a.q_prev = qprev(before); a.q_stage = qprev(now);
-    a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
-    a.flags = reinterpret_cast<uint8_t*>(at(c->o_flags)); a.flags_user = nullptr;
-    a.cosine = reinterpret_cast<double*>(at(c->o_cosine));
-    a.sel_pool = c->sel_pool; a.P = c->P; a.score = c->score;
-    a.ids = ids(now); a.ids_user = nullptr;
-    a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
-    a.slice = (g.n_cand + slices - 1) >> slices_log2;
-    a.exch = c->exch; a.keyx = c->keyx; a.keyid = c->keyid; a.cmax = c->cmax; a.no = LaunchNo{tag, nullptr}; a.impatient = ka.plan >> 23; a.tstamp = c->tstamp;
-    a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
-    a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
-    if (HOSTPOOL) {
-      a.plan_act_ids = ids(before);
-      a.plan_act_slots = slots(before);
-      a.plan_new_slots = slots(now);
-      a.plan_miss = reinterpret_cast<int32_t*>(at(c->o_miss));
-      a.plan_lds_off = select_key_words(g.n_cand);
-    }
-    return a;
-  }
-  __device__ __forceinline__ AttnArgs attn_args(const LayerKernelArgs& ka, int G) const {
-    AttnArgs a;
-    a.pd = pd; a.q = ka.q;
-    a.act_ids = ids(before); a.new_ids = nullptr;
-    a.act_slots = HOSTPOOL ? slots(before) : nullptr; a.new_slots = nullptr;
-    a.flags = nullptr; a.use = 2; a.part = c->part; a.part_ml = c->part_ml; a.max_splits = c->max_splits;
-    a.n_splits = (int)(ka.plan >> 7) & 63; a.pps = (int)(ka.plan >> 13) & 511;
-    a.share = ka.split_magic ? (int)__umulhi((uint32_t)(G * D + a.n_splits - 1), ka.split_magic) : G * D;
-    a.no = LaunchNo{}; a.out = ka.out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
-    a.status = reinterpret_cast<int*>(at(c->o_status)); a.tstamp = c->tstamp;
-    a.q_prev = qprev(before); a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
-    a.k_new = ka.k_new; a.v_new = ka.v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
-    a.tag = tag; a.pick_tag = tag + ((ka.plan >> 22) & 1u ? 2u : 0u);
-    a.impatient = ka.plan >> 23;
-    a.host_pool = HOSTPOOL ? reinterpret_cast<const uint16_t*>(c->host_base + c->host_layer_bytes * (unsigned long long)layer) : nullptr;
-    a.max_pages = c->max_pages;
-    return a;
-  }
-};
-
-template <int DT, int G, bool HOSTPOOL>
-__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
-void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
-                  uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
-  extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
-  touch<sizeof(LayerConst)>((LayerConstPtr)consts);
-  const LayerKernelArgs ka{consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic};
-  const LayerSetup<HOSTPOOL> u(ka);
-  StepArgs s;
-  int head, nw = SEL_WAVES, own = 0;           // own: a selecting block's slice of the head's candidates, an attention block's split
-  Selected got = Selected::NOTHING;
-  AttnLeft left{};
-  const bool step = (int)blockIdx.y < u.step_rows;
-  if (step) {
-    s = u.step_args(ka);
-    bool go_on = false;
-    asm volatile(".p2align 6");       // (where the roles' code starts within 64 bytes is worth up to 2 %)
-    step_roles<DT, G>(s, blockIdx.x, blockIdx.y, [&](int m, int slice) {
-      head = m;
-      own = slice;
-      go_on = select_begin<G, true>(s, m, slice, dyn_lds, nw, got);
-    });
-    if (!go_on) return;
-  } else {
-    const AttnArgs a = u.attn_args(ka, G);
-    // numbered through row by row, so that a head's blocks, which wait for each other, are adjacent
-    const uint32_t i = (blockIdx.y - (uint32_t)u.step_rows) * (uint32_t)u.c->heads + blockIdx.x;
-    head = (int)(split_magic ? __umulhi(i, split_magic) : i);
-    own = (int)i - head * a.n_splits;
-    left = attn_block<DT, STEP_WAVES, true, HOSTPOOL>(a, own, head, reinterpret_cast<float*>(dyn_lds));
-    if (__builtin_expect(!left.any(), 1)) return;
-    // What follows is hardly ever run.  Its arguments come from memory once more: kept up to here they would cost the page
-    // loop registers.
-    const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-    s = LayerSetup<HOSTPOOL>(again).step_args(again);
-    if (left.ids) lds_barrier();                             // (the LDS is free)
-  }
-  if (step || left.ids) {
-    select_finish<DT, G, true>(s, head, own, dyn_lds, nw, got, [] {
-      const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-      return LayerSetup<HOSTPOOL>(again).step_args(again);
-    });
-  }
-  if (step) return;
-  const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-  attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL>(again).attn_args(again, G), own, head, left);
-}
-
-struct LayerLaunch { dim3 grid; size_t lds; uint32_t packed, plan, split_magic; };
-
-template <int DT, int G, bool HOSTPOOL>
-static bool launch_layer_gh(const LayerIO& io, const LayerLaunch& l, hipStream_t st) {
-  static size_t granted = 48 * 1024;
-  if (!grant_lds(&layer_kernel<DT, G, HOSTPOOL>, l.lds, granted)) return false;
-  if (io.done)
-    hipExtLaunchKernelGGL((layer_kernel<DT, G, HOSTPOOL>), l.grid, dim3(STEP_THREADS), l.lds, st, nullptr, io.done, 0,
-                          io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
-  else
-    layer_kernel<DT, G, HOSTPOOL><<<l.grid, STEP_THREADS, l.lds, st>>>(io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
-  return true;
-}
-template <int DT, int G>
-static bool launch_layer_g(const LayerIO& io, const LayerLaunch& l, hipStream_t st) {
-  return io.host_pool ? launch_layer_gh<DT, G, true>(io, l, st) : launch_layer_gh<DT, G, false>(io, l, st);
-}
-
 // Which layer-steps take one launch: those that latency bounds.  Measured, one launch against separate ones: 32 KV heads of
 // 8K / 32K / 128K tokens 11 / 16 / 28 us against 19 / 26 / 37, 128 of 2K / 16K / 32K 18 / 27 / 53 against 25 / 31 / 55, and
 // 192 x 65 attended pages 62 against 65.  With 256 KV heads and more, attention by itself has a block for every compute
@@ -414,6 +235,7 @@ static bool launch_layer_g(const LayerIO& io, const LayerLaunch& l, hipStream_t 
 constexpr int kLayerMaxHeads = kComputeUnits - 1;
 constexpr long kLayerMaxAttended = 24576, kLayerMaxBlocks = 2560, kLayerMaxBlocksHost = 1024;
 
+constexpr int kMaxLayersPacked = 1 << 13, kMaxCtxPacked = 1 << 19;
 bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const int roles = ROLE_APPEND | ROLE_CORR | ROLE_SELECT;
   if (g_one_launch == 0 || d.k == 0 || append_races_selection(roles, g)) return false;
@@ -446,12 +268,10 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   l.split_magic = n_splits > 1 ? 0xffffffffu / (uint32_t)n_splits + 1u : 0u;      // exact for the block counts of a layer launch
   *io.launch_grid = (int)blocks;
   *io.launch_lds = l.lds;
-  switch (d.G) {
-#define FKV_CASE(GG) case GG: return d.dtype == 0 ? launch_layer_g<0, GG>(io, l, st) : launch_layer_g<1, GG>(io, l, st);
-    FKV_CASE(1) FKV_CASE(2) FKV_CASE(3) FKV_CASE(4) FKV_CASE(5) FKV_CASE(6) FKV_CASE(7) FKV_CASE(8)
-#undef FKV_CASE
-    default: return false;
-  }
+  const int stream = stream_of(d, g);
+  const auto launch = io.host_pool ? (stream & STREAM_SUMMARIES ? launch_layer_host_stream : launch_layer_host)
+                      : stream & STREAM_PAGES ? launch_layer_hbm_past : stream & STREAM_SUMMARIES ? launch_layer_hbm_stream : launch_layer_hbm;
+  return launch(io, l, d.dtype, d.G, st);
 }
 
 // ---------------------------------------------------------------------------------

@@ -166,7 +166,8 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // for a later launch each pass stores its own, which leaves the waves of a bandwidth-bound scan independent of each other
 // (28.2 us against 30.3 us through LDS for 256 heads x 992 pages).
 // ---------------------------------------------------------------------------------
-template <int DT, int G, bool QMODE, bool TAGGED, int WAVES>
+// PAST: the summaries are read past the caches (STREAM_SUMMARIES; as a branch around the loads it costs short launches 2 %).
+template <int DT, int G, bool QMODE, bool TAGGED, int WAVES, bool PAST>
 __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chunk) {
   constexpr int PASS = WAVES * 4;                         // pages per pass
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -179,9 +180,9 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
 #pragma unroll
   for (int ps = 0; ps < SCORE_PASSES; ++ps) {
     if (ps < passes) {
-      const int j = min(j0 + ps * PASS, n - 1);
-      wmax[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D);
-      wmin[ps] = *reinterpret_cast<const uint4*>(sm + (size_t)j * D + to_min);
+      const uint16_t* const p = sm + (size_t)min(j0 + ps * PASS, n - 1) * D;
+      wmax[ps] = PAST ? load_past(p) : *reinterpret_cast<const uint4*>(p);
+      wmin[ps] = PAST ? load_past(p + to_min) : *reinterpret_cast<const uint4*>(p + to_min);
     }
   }
   const uint32_t tag = TAGGED ? launch_tag(a.no) : 0u;
@@ -306,10 +307,10 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
   }
 }
 
-template <int DT, int G, bool TAGGED, int WAVES>
+template <int DT, int G, bool TAGGED, int WAVES, bool PAST>
 __device__ __forceinline__ void score_role(const StepArgs& a, int head, int chunk) {
-  if (a.sel_pool >= 4) score_pages<DT, G, true, TAGGED, WAVES>(a, head, chunk);
-  else                 score_pages<DT, G, false, TAGGED, WAVES>(a, head, chunk);
+  if (a.sel_pool >= 4) score_pages<DT, G, true, TAGGED, WAVES, PAST>(a, head, chunk);
+  else                 score_pages<DT, G, false, TAGGED, WAVES, PAST>(a, head, chunk);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1200,7 +1201,7 @@ __device__ __forceinline__ void select_finish(const StepArgs& hot, int head, int
 // row so that a head's are adjacent (they wait for each other: in block order, at most one head's are ever half there).
 // ---------------------------------------------------------------------------------
 // select(head, slice): what a selecting block does.
-template <int DT, int G, typename Select>
+template <int DT, int G, bool PAST, typename Select>
 __device__ __forceinline__ void step_roles(const StepArgs& a, int x, int y, Select select) {
   if (a.roles & ROLE_APPEND) {
     if (y == 0) { append_role<DT>(a, x); return; }
@@ -1212,7 +1213,7 @@ __device__ __forceinline__ void step_roles(const StepArgs& a, int x, int y, Sele
   }
   if (y < a.chunks) {
     if (y == 0) FKV_STAMP(a, x, 0);
-    score_role<DT, G, true, STEP_WAVES>(a, x, y);
+    score_role<DT, G, true, STEP_WAVES, PAST>(a, x, y);
     if (y == 0) FKV_STAMP(a, x, 1);
     return;
   }
