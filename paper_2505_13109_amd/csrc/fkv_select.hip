@@ -1,5 +1,5 @@
-// The "step" kernel (token append, correction test, page weights and the top-k selection), the one-launch layer kernel
-// (the step roles plus the attention blocks), and the host-side rules that size their launches.
+// The "step" kernel (token append, correction test, page weights and the top-k selection), the scan and the selection as launches
+// of their own, and the host-side rules that size their launches and the one-launch layer kernel's (fkv_layer_dev.h).
 // The roles themselves are in fkv_step_dev.h, attention in fkv_attn_dev.h.
 #include "fkv_step_dev.h"
 #include "fkv_attn_dev.h"
