@@ -407,11 +407,11 @@ static int flush_deferred(fkv_ctx* ctx, bool forked = false) {
   if (ctx->deferred.empty()) return FKV_OK;
   hipStream_t st = ctx->deferred_st, cs = ctx->deferred_cs;
   hipEvent_t done = ctx->layers[ctx->deferred.back()].ev_recall;
-  const bool by_launch = cs != st && launch_records(cs);
   if (cs != st) {
     if (!forked) FKV_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
     FKV_HIP(ctx, hipStreamWaitEvent(cs, ctx->ev_fork, 0));
   }
+  const bool by_launch = cs != st && launch_records(cs);      // (asked here: the wait is what brings the copy stream into a capture)
   for (size_t i0 = 0; i0 < ctx->deferred.size(); i0 += GATHER_MAX_LAYERS) {
     GatherLayers gl{};
     for (size_t i = i0; i < ctx->deferred.size() && gl.n < GATHER_MAX_LAYERS; ++i) {

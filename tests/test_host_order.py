@@ -1,0 +1,137 @@
+"""In which order the library hands work to streams, on the CPU: the HIP runtime's calls are taken by a recorder (hip_recorder.c),
+nothing runs, and what is recorded is read as a graph of what has to wait for what.  Here a missing wait between the compute
+stream and the copy stream shows whatever the timing; results on a GPU show it only when a recall happens to be late."""
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+COMPUTE, COPY = 0x100, 0x200
+
+
+def _play(recorder, library, config, calls):
+    """(In a process of its own: the recorder's symbols come before the HIP runtime's.)  For each call its return code and how many
+    lines the log had when it began."""
+    rec = C.CDLL(recorder, mode=C.RTLD_GLOBAL)
+    rec.rec_log.restype = C.c_char_p
+    lib = C.CDLL(library)
+    dims = ("n_layers", "batch", "n_q_heads", "n_kv_heads", "head_dim", "page_size", "max_ctx", "budget_tokens", "sink_tokens", "window_tokens", "dtype",
+            "placement")
+
+    class Config(C.Structure):
+        _fields_ = [(n, C.c_int32) for n in dims] + [("tau", C.c_float)] + [(n, C.c_int32) for n in ("recall_mode", "select_pooling", "corr_pooling")]
+
+    ctx, some = C.c_void_p(), C.c_void_p(0x10000000)                  # (no address is looked at)
+    st, cs, copy = C.c_void_p(COMPUTE), C.c_void_p(COPY), C.c_void_p(config.pop("copy", COPY))
+    rc = lib.fkv_create(C.byref(Config(**config)), some, C.c_size_t(1 << 50), some, C.c_size_t(1 << 50), C.byref(ctx))
+    assert rc == 0, rc
+    done = []
+    for call, *args in calls:
+        at = rec.rec_log().count(b"\n")
+        if call == "load":
+            rc = lib.fkv_load_prefix(ctx, args[0], some, some, args[1], st)
+        elif call == "step":
+            rc = lib.fkv_decode_step(ctx, args[0], some, some, some, some, st, copy)
+        elif call == "append":
+            rc = lib.fkv_kv_append(ctx, args[0], some, some, st, copy)
+        elif call == "capture":
+            rc = rec.rec_capture(st) and 0
+        elif call == "end_capture":
+            rc = rec.rec_end_capture() and 0
+        done.append((rc, at))
+    return rec.rec_log().decode().splitlines(), done
+
+
+@pytest.fixture(scope="module")
+def play(tmp_path_factory):
+    recorder = str(tmp_path_factory.mktemp("recorder") / "librecorder.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", recorder, os.path.join(ROOT, "tests", "hip_recorder.c")], check=True)
+    library = os.environ.get("FKV_LIB") or os.path.join(ROOT, "paper_2505_13109_amd", "libfreekv.so")
+
+    def run(calls, **config):
+        base = dict(n_layers=2, batch=1, n_q_heads=32, n_kv_heads=8, head_dim=128, page_size=32, max_ctx=8192, budget_tokens=1024, sink_tokens=64,
+                    window_tokens=64, dtype=1, placement=1, tau=0.8, recall_mode=0, select_pooling=0, corr_pooling=0)
+        base.update(config)
+        out = subprocess.run([sys.executable, os.path.abspath(__file__), json.dumps([recorder, library, base, calls])], check=True, capture_output=True, text=True)
+        lines, done = json.loads(out.stdout.splitlines()[-1])
+        return Order(lines, calls, done)
+
+    return run
+
+
+class Order:
+    def __init__(self, lines, calls, done):
+        self.ops = [line.split() for line in lines]
+        self.calls = calls
+        self.rc = [rc for rc, _ in done]
+        self.span = [(at, done[i + 1][1] if i + 1 < len(done) else len(lines)) for i, (_, at) in enumerate(done)]
+        last_of, recorded, sync, self.after = {}, {}, None, []        # after[i]: what op i directly waits for
+        for i, op in enumerate(self.ops):
+            if op[0] == "sync":
+                self.after.append(list(range(i)))
+                sync = i
+                continue
+            stream, captured = op[2], op[-1]
+            before = [last_of.get(stream), sync]
+            if op[0] == "wait" and recorded.get(op[1], (0, None))[1] == captured:      # (a record in a capture means nothing outside of it)
+                before.append(recorded[op[1]][0])
+            self.after.append([b for b in before if b is not None])
+            last_of[stream] = i
+            if op[0] == "record":
+                recorded[op[1]] = (i, captured)
+            if op[0] == "launch" and op[3] != "0" and op[3] != "(nil)":
+                recorded[op[3]] = (i, "0")                            # a stop event is never part of a capture
+
+    def before(self, a, b):
+        """op a is over before op b begins, whatever the timing"""
+        seen, todo = set(), [b]
+        while todo:
+            i = todo.pop()
+            if i == a:
+                return True
+            if i not in seen and i > a:
+                seen.add(i)
+                todo.extend(self.after[i])
+        return False
+
+    def launches(self, call, kernel, stream=None):
+        """ops of the call that launch the kernel"""
+        lo, hi = self.span[call]
+        return [i for i in range(lo, hi) if self.ops[i][0] == "launch" and kernel in self.ops[i][1] and (stream is None or int(self.ops[i][2], 16) == stream)]
+
+    def first_launch(self, call):
+        return self.launches(call, "")[0]
+
+    def recall_of(self, call):
+        """the deferred recall of a step's uncorrected heads: the first gather on the copy stream from there on"""
+        return next(i for i in range(self.span[call][0], len(self.ops)) if self.ops[i][0] == "launch" and "gather_kernel" in self.ops[i][1]
+                    and int(self.ops[i][2], 16) == COPY)
+
+
+def _index(calls, *wanted):
+    return [i for i, c in enumerate(calls) if tuple(c) == wanted]
+
+
+@pytest.mark.parametrize("captured", [False, True])
+@pytest.mark.parametrize("batch,layers", [(1, 1), (1, 2), (1, 5), (1, 18), (32, 2)])      # one launch a layer-step, and separate ones
+def test_a_deferred_recall_lies_between_its_step_and_the_next(play, batch, layers, captured):
+    loads = [("load", l, 4000) for l in range(layers)]
+    steps = [("step", l) for _ in range(4) for l in range(layers)]
+    calls = loads + ([("capture",)] if captured else []) + steps
+    o = play(calls, n_layers=layers, batch=batch)
+    assert set(o.rc) == {0}
+    for l in range(layers):
+        mine = _index(calls, "step", l)
+        for now, then in zip(mine, mine[1:]):
+            chosen = [i for k in ("layer_kernel", "step_kernel", "select_kernel") for i in o.launches(now, k)]
+            recall = o.recall_of(now)
+            assert chosen and o.before(chosen[-1], recall)
+            assert o.before(recall, o.first_launch(then)), f"layer {l}: nothing orders the next step behind the recall"
+
+
+if __name__ == "__main__":
+    print(json.dumps(_play(*json.loads(sys.argv[1]))))
