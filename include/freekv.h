@@ -149,7 +149,9 @@ int fkv_step_launches(const fkv_ctx* ctx, int32_t layer);
 /* Bulk-load a context of n_tokens (replaces the layer's state): stores K/V in
  * the paged layout, builds the min-max page summaries (Sec. 3.2) and, for
  * placement HOST, writes every page to the host pool in its contiguous
- * per-(page, KV head) unit (Sec. 4.2).  K, V: dev, [batch, n_tokens, n_kv, d]. */
+ * per-(page, KV head) unit (Sec. 4.2).  K, V: dev, [batch, n_tokens, n_kv, d].
+ * Placement HOST: `stream` is made to wait for what the layer's old context left on its copy stream (deferred
+ * recalls, an offloaded page). */
 int fkv_load_prefix(fkv_ctx* ctx, int32_t layer, const void* K_dev, const void* V_dev,
                     int32_t n_tokens, void* stream);
 

@@ -39,6 +39,7 @@ struct LayerState {
   bool recall_outstanding = false;
   bool recall_unsubmitted = false; // its deferred recall is still in the context's list, not on the copy stream yet
   hipEvent_t recall_event = nullptr;   // what "that recall finished" is recorded in (its own ev_recall, or a later layer's)
+  unsigned long long recall_capture = 0, offload_capture = 0;   // the captures in which recall_event and ev_offload were recorded (capture_of)
   int recalled = 0;          // placement HOST: which heads' pending pages have been recalled (bit 0 corrected, bit 1 the others)
   int last_launches = 0;     // kernel launches of the last fkv_decode_step (compute stream)
   int step_launches = 0;     // launches the last run_step made
@@ -357,6 +358,14 @@ static int run_step(fkv_ctx* ctx, int layer, int roles, const void* q, const voi
   return after_launch(ctx, "step kernel");
 }
 
+// The capture that `st` is in, 0: none.
+static unsigned long long capture_of(hipStream_t st) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(st, &capture, &id) != hipSuccess) (void)hipGetLastError();
+  return capture == hipStreamCaptureStatusNone ? 0 : id + 1;
+}
+
 // Host-side bookkeeping after an append has been enqueued; placement HOST offloads a page
 // the token filled (Sec. 4.2), behind the append, on the copy stream.
 static int after_append(fkv_ctx* ctx, int layer, hipStream_t st, hipStream_t cs) {
@@ -371,6 +380,7 @@ static int after_append(fkv_ctx* ctx, int layer, hipStream_t st, hipStream_t cs)
     int rc = after_launch(ctx, "offload kernel");
     if (rc) return rc;
     FKV_HIP(ctx, hipEventRecord(ls.ev_offload, cs));
+    ls.offload_capture = capture_of(cs);
     ls.offload_outstanding = true;
     ls.offload_unseen = cs != st;
   }
@@ -394,11 +404,7 @@ static void forget_waits(fkv_ctx* ctx, hipEvent_t ev) {     // `ev` has just bee
 
 // Whether an event on `st` may be recorded by the launch it follows: that takes no packet of its own in the stream's queue
 // (a hand-over between two streams and back costs 7 us so and 10.5 us with hipEventRecord), but a capture does not see it.
-static bool launch_records(hipStream_t st) {
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
-  return capture == hipStreamCaptureStatusNone;
-}
+static bool launch_records(hipStream_t st) { return capture_of(st) == 0; }
 
 // Submit the deferred recalls on the list: one dependency of the copy stream on the compute stream, one gather launch
 // for all listed layers' uncorrected heads, one event that every listed layer's next step looks at.
@@ -411,7 +417,8 @@ static int flush_deferred(fkv_ctx* ctx, bool forked = false) {
     if (!forked) FKV_HIP(ctx, hipEventRecord(ctx->ev_fork, st));
     FKV_HIP(ctx, hipStreamWaitEvent(cs, ctx->ev_fork, 0));
   }
-  const bool by_launch = cs != st && launch_records(cs);      // (asked here: the wait is what brings the copy stream into a capture)
+  const unsigned long long capture = capture_of(cs);          // (asked here: the wait is what brings the copy stream into a capture)
+  const bool by_launch = cs != st && capture == 0;
   for (size_t i0 = 0; i0 < ctx->deferred.size(); i0 += GATHER_MAX_LAYERS) {
     GatherLayers gl{};
     for (size_t i = i0; i < ctx->deferred.size() && gl.n < GATHER_MAX_LAYERS; ++i) {
@@ -434,6 +441,7 @@ static int flush_deferred(fkv_ctx* ctx, bool forked = false) {
     LayerState& ls = ctx->layers[l];
     ls.recall_unsubmitted = false;
     ls.recall_event = done;
+    ls.recall_capture = capture;
     ls.recall_outstanding = cs != st;
   }
   ctx->deferred.clear();
@@ -582,6 +590,18 @@ int fkv_load_prefix(fkv_ctx* ctx, int32_t layer, const void* K_dev, const void* 
   if (n_tokens > 0 && (!K_dev || !V_dev)) return ctx->fail(FKV_EINVAL, "null K or V");
   LayerState& ls = ctx->layers[layer];
   hipStream_t st = static_cast<hipStream_t>(stream);
+  // What the old context left on its copy stream would write into the new one: a recall into page-cache slots (and it reads
+  // the miss list, the flags and the host pool), an offload into the host pool.  (An event recorded in a capture has no meaning
+  // outside of it, nor one from outside in it: there the order is that of the graph's launches, which is the caller's.)
+  const unsigned long long capture = capture_of(st);
+  if (ls.recall_capture == capture) {
+    int rc = wait_recall(ctx, ls, st);
+    if (rc) return rc;
+  }
+  if (ls.offload_unseen && ls.offload_capture == capture) {
+    FKV_HIP(ctx, hipStreamWaitEvent(st, ls.ev_offload, 0));
+    ls.offload_unseen = false;
+  }
   // a fresh context: no previous query, nothing picked
   launch_load_prefix(ctx->dims, ctx->pool_desc(layer), ctx->summ(layer), ctx->host_pool(layer),
                      static_cast<const uint16_t*>(K_dev), static_cast<const uint16_t*>(V_dev), n_tokens, ctx->ids(layer, 0), st);
@@ -976,6 +996,7 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
       if (rc) return rc;
       forget_waits(ctx, ls.ev_recall);
       ls.recall_event = ls.ev_recall;
+      ls.recall_capture = capture_of(cs);
       deferred = true;     // the next step of this layer waits for it, not this step's attention
     }
   }

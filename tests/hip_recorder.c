@@ -20,6 +20,7 @@ static size_t log_len;
 static const void* stubs[MAX];
 static const char* names[MAX];
 static int n_stubs, n_captured;
+static unsigned long long n_captures;
 static void* captured[64];
 
 static int is_captured(void* s) {
@@ -30,7 +31,7 @@ static int is_captured(void* s) {
 #define LOG(...) (log_len += (size_t)snprintf(log_text + log_len, sizeof log_text - log_len, __VA_ARGS__))
 
 void rec_capture(void* s) { if (!is_captured(s)) captured[n_captured++] = s; }
-void rec_end_capture(void) { n_captured = 0; }
+void rec_end_capture(void) { n_captured = 0; n_captures += 1; }
 const char* rec_log(void) { return log_text; }
 
 static const char* name_of(const void* stub) {
@@ -88,6 +89,11 @@ int hipStreamWaitEvent(void* stream, void* e, unsigned flags) {
   return 0;
 }
 int hipStreamIsCapturing(void* stream, int* status) { *status = is_captured(stream); return 0; }
+int hipStreamGetCaptureInfo(void* stream, int* status, unsigned long long* id) {
+  *status = is_captured(stream);
+  *id = n_captures;
+  return 0;
+}
 int hipEventSynchronize(void* e) { (void)e; LOG("sync\n"); return 0; }
 int hipStreamSynchronize(void* s) { (void)s; LOG("sync\n"); return 0; }
 int hipDeviceSynchronize(void) { LOG("sync\n"); return 0; }

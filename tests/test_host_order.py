@@ -133,5 +133,35 @@ def test_a_deferred_recall_lies_between_its_step_and_the_next(play, batch, layer
             assert o.before(recall, o.first_launch(then)), f"layer {l}: nothing orders the next step behind the recall"
 
 
+@pytest.mark.parametrize("batch,layers", [(1, 1), (1, 2), (1, 5), (32, 2)])
+def test_a_new_prompt_lies_behind_what_the_old_context_left_on_the_copy_stream(play, batch, layers):
+    """A recall writes page-cache slots, an offload (here of the page that the first step fills) the host pool: both would land in
+    the new context."""
+    before = [("load", l, 4031) for l in range(layers)] + [("step", l) for _ in range(3) for l in range(layers)]
+    calls = before + [("load", l, 4000) for l in range(layers)]
+    o = play(calls, n_layers=layers, batch=batch)
+    assert set(o.rc) == {0}
+    for l in range(layers):
+        again = o.launches(_index(calls, "load", l, 4000)[0], "load_prefix_kernel")[0]
+        steps = _index(calls, "step", l)
+        offloads = o.launches(steps[0], "offload_kernel", COPY)
+        assert len(offloads) == 1
+        assert o.before(o.recall_of(steps[-1]), again), f"layer {l}: nothing orders the new prompt behind the recall"
+        assert o.before(offloads[0], again), f"layer {l}: nothing orders the new prompt behind the offload"
+
+
+@pytest.mark.parametrize("calls", [
+    [("step", 0), ("capture",), ("load", 0, 4000)],                        # a captured load behind eager steps
+    [("capture",), ("step", 0), ("end_capture",), ("load", 0, 4000)],      # ... the other way round
+    [("capture",), ("step", 0), ("end_capture",), ("capture",), ("load", 0, 4000)],      # ... in two captures
+])
+def test_a_new_prompt_does_not_wait_across_the_edge_of_a_capture(play, calls):
+    """(An event of the one side has no meaning on the other: the runtime refuses such a wait.)"""
+    o = play([("load", 0, 4031)] + calls, n_layers=1)
+    assert set(o.rc) == {0}
+    lo, hi = o.span[-1]
+    assert [op[0] for op in o.ops[lo:hi]] == ["launch"]
+
+
 if __name__ == "__main__":
     print(json.dumps(_play(*json.loads(sys.argv[1]))))
