@@ -366,6 +366,15 @@ static unsigned long long capture_of(hipStream_t st) {
   return capture == hipStreamCaptureStatusNone ? 0 : id + 1;
 }
 
+// `st` waits for the offload of the layer's last filled page, unless it has done so or the event is of another capture.
+static int wait_offload(fkv_ctx* ctx, LayerState& ls, hipStream_t st) {
+  if (ls.offload_unseen && ls.offload_capture == capture_of(st)) {
+    FKV_HIP(ctx, hipStreamWaitEvent(st, ls.ev_offload, 0));
+    ls.offload_unseen = false;
+  }
+  return FKV_OK;
+}
+
 // Host-side bookkeeping after an append has been enqueued; placement HOST offloads a page
 // the token filled (Sec. 4.2), behind the append, on the copy stream.
 static int after_append(fkv_ctx* ctx, int layer, hipStream_t st, hipStream_t cs) {
@@ -593,19 +602,13 @@ int fkv_load_prefix(fkv_ctx* ctx, int32_t layer, const void* K_dev, const void* 
   // What the old context left on its copy stream would write into the new one: a recall into page-cache slots (and it reads
   // the miss list, the flags and the host pool), an offload into the host pool.  (An event recorded in a capture has no meaning
   // outside of it, nor one from outside in it: there the order is that of the graph's launches, which is the caller's.)
-  const unsigned long long capture = capture_of(st);
-  if (ls.recall_capture == capture) {
-    int rc = wait_recall(ctx, ls, st);
-    if (rc) return rc;
-  }
-  if (ls.offload_unseen && ls.offload_capture == capture) {
-    FKV_HIP(ctx, hipStreamWaitEvent(st, ls.ev_offload, 0));
-    ls.offload_unseen = false;
-  }
+  int rc = ls.recall_capture == capture_of(st) ? wait_recall(ctx, ls, st) : FKV_OK;
+  if (!rc) rc = wait_offload(ctx, ls, st);
+  if (rc) return rc;
   // a fresh context: no previous query, nothing picked
   launch_load_prefix(ctx->dims, ctx->pool_desc(layer), ctx->summ(layer), ctx->host_pool(layer),
                      static_cast<const uint16_t*>(K_dev), static_cast<const uint16_t*>(V_dev), n_tokens, ctx->ids(layer, 0), st);
-  int rc = after_launch(ctx, "load_prefix kernel");
+  rc = after_launch(ctx, "load_prefix kernel");
   if (rc) return rc;
   if (n_tokens == 0) {
     const size_t n = (size_t)2 * ctx->cfg.batch * ctx->cfg.n_kv_heads * (ctx->lay.k > 0 ? ctx->lay.k : 1) * 4;
@@ -626,7 +629,11 @@ int fkv_kv_append(fkv_ctx* ctx, int32_t layer, const void* k_new_dev, const void
   LayerState& ls = ctx->layers[layer];
   if (ls.L >= ctx->cfg.max_ctx) return ctx->fail(FKV_ERANGE, "append beyond max_ctx");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  int rc = run_step(ctx, layer, ROLE_APPEND, nullptr, k_new_dev, v_new_dev, nullptr, nullptr, ls.L + 1, st);
+  // A page is offloaded before the next one is full: the ring has two units more than the window has pages, so its unit is not
+  // written again before that.
+  int rc = ls.L % PG == PG - 1 ? wait_offload(ctx, ls, st) : FKV_OK;
+  if (rc) return rc;
+  rc = run_step(ctx, layer, ROLE_APPEND, nullptr, k_new_dev, v_new_dev, nullptr, nullptr, ls.L + 1, st);
   if (rc) return rc;
   return after_append(ctx, layer, st, static_cast<hipStream_t>(copy_stream));
 }

@@ -163,5 +163,27 @@ def test_a_new_prompt_does_not_wait_across_the_edge_of_a_capture(play, calls):
     assert [op[0] for op in o.ops[lo:hi]] == ["launch"]
 
 
+@pytest.mark.parametrize("step", ["append", "step"])
+@pytest.mark.parametrize("window", [0, 64])
+def test_a_page_is_offloaded_before_a_later_one_takes_its_place(play, window, step):
+    """The window pages and the open one live in a ring of units: the token that opens page p goes where page p - n_ring was, which the copy
+    stream has to have read by then."""
+    n_ring, start = window // 32 + 2, 4000
+    calls = [("load", 0, start)] + [(step, 0)] * 300
+    o = play(calls, n_layers=1, window_tokens=window)
+    assert set(o.rc) == {0}
+    opens, fills = {}, {}
+    for i in range(1, len(calls)):
+        page, at = divmod(start + i - 1, 32)
+        if at == 0:
+            opens[page] = o.first_launch(i)
+        if at == 31:
+            fills[page] = o.launches(i, "offload_kernel", COPY)[0]
+    pairs = [(p, p + n_ring) for p in fills if p + n_ring in opens]
+    assert len(pairs) >= 5
+    for old, new in pairs:
+        assert o.before(fills[old], opens[new]), f"page {new} may be written over page {old} before that is offloaded"
+
+
 if __name__ == "__main__":
     print(json.dumps(_play(*json.loads(sys.argv[1]))))
