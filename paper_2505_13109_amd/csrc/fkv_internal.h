@@ -94,13 +94,16 @@ __host__ __device__ inline uint32_t device_tag(uint32_t launch) { return launch 
 // at the next token, so as long as they fit they are better left there.  If they do not, a cyclic order of reads keeps
 // hardly any of them, and the summaries, of which more are read for every token served, go first: 8 layers of 32 heads x 992 candidates and 65
 // pages, 400 MB in all, 75 us a layer-step -> 63; but 268 MB in all 1 % slower, and with the pages past the cache as well 71.
-// Where the pages by themselves are too many, they go too: 8 layers of 128 heads x 65 pages, 1.1 GB, 40 us -> 37; 256 heads 65 -> 58;
-// 20 layers of 8 heads x 129 pages, 340 MB, no difference.
+// Where the pages by themselves are too many, they go too.  A pass in the cache and past it, by the pages that there are to
+// attend (a short context has fewer than its budget): 32 layers of 8 heads x 55 pages, 230 MB, 821 and 857 us; x 65, 272 MB, 843 and 854;
+// x 82, 344 MB, 881 and 874; 3 layers of 320 heads x 17, 267 MB, 776 and 798; 2 x 33, 346 MB, 787 and 763; 2 layers of 384 heads
+// x 33, 415 MB, 899 and 826.  In the launches of a scan as well: one layer of 256 heads x 942 candidates and 17 pages, 195 MB, 398 us past the
+// cache and 381 in it.
 constexpr int STREAM_SUMMARIES = 1, STREAM_PAGES = 2;      // (the second only with the first)
 inline int stream_of(const Dims& d, const Geom& g) {
   const double heads = (double)d.n_layers * d.batch * d.n_kv;
-  const double pages = heads * (g.n_sink + d.k + g.n_win + 1) * UNIT_BYTES, summaries = heads * g.n_cand * 2 * D * 2;
-  return (pages + summaries > 270e6 ? STREAM_SUMMARIES : 0) | (pages > 400e6 ? STREAM_PAGES : 0);
+  const double pages = heads * (g.n_sink + g.k_eff + g.n_win + 1) * UNIT_BYTES, summaries = heads * g.n_cand * 2 * D * 2;
+  return (pages + summaries > 270e6 ? STREAM_SUMMARIES : 0) | (pages > 310e6 ? STREAM_PAGES : 0);
 }
 
 // what blocks of a launch wait for, as bits (a test makes waits of these kinds run out at once)

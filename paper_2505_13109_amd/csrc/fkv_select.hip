@@ -57,7 +57,7 @@ __global__ __launch_bounds__(G * 64) void corr_kernel(const uint16_t* q, const u
 // cache between two scans of that size, 30.0 us with the heads next to each other): grid (chunks, rows), row by row first
 // the other two roles, then a head each; beyond kGridRows rows (a grid dimension ends at 65535) folded into a third dimension.
 constexpr int kGridRows = 1 << 15;
-template <int DT, int G>
+template <int DT, int G, bool PAST>
 __global__ __launch_bounds__(SCAN_WAVES * 64) __attribute__((amdgpu_waves_per_eu(G <= 4 ? 7 : 5))) void scan_kernel(StepArgs a) {
   touch_args<sizeof(StepArgs)>();
   const int y = (int)(blockIdx.z * kGridRows + blockIdx.y);
@@ -71,8 +71,7 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) __attribute__((amdgpu_waves_per_eu
     if ((a.roles & ROLE_CORR) && i < a.heads) corr_role<DT, G, SCAN_WAVES>(a, i);
     return;
   }
-  score_role<DT, G, false, SCAN_WAVES, true>(a,     // (by itself it reads more than half of what the cache holds)
-                                              y - a.other_rows, blockIdx.x);
+  score_role<DT, G, false, SCAN_WAVES, PAST>(a, y - a.other_rows, blockIdx.x);
 }
 // The selection after it: one block per slice of a head's candidates, a head's slices adjacent.
 template <int G>
@@ -204,7 +203,9 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   if (!grant_lds(&select_kernel<G>, lds, granted_select)) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
   const int scan_rows = a.other_rows + heads;
-  scan_kernel<DT, G><<<dim3(a.chunks, scan_rows < kGridRows ? scan_rows : kGridRows, (scan_rows + kGridRows - 1) / kGridRows), SCAN_WAVES * 64, 0, st>>>(a);
+  const dim3 scan_grid(a.chunks, scan_rows < kGridRows ? scan_rows : kGridRows, (scan_rows + kGridRows - 1) / kGridRows);
+  if (stream_of(d, g) & STREAM_SUMMARIES) scan_kernel<DT, G, true><<<scan_grid, SCAN_WAVES * 64, 0, st>>>(a);
+  else                                    scan_kernel<DT, G, false><<<scan_grid, SCAN_WAVES * 64, 0, st>>>(a);
   select_kernel<G><<<heads * a.slices, SEL_THREADS, lds, st>>>(a);
   *io.P_tagged = false;
   return 2;

@@ -53,3 +53,25 @@ def test_a_layer_of_many_against_a_layer_by_itself(placement, layers, steps, dty
         g.close()
     for (w0, ids0, out0), (w1, ids1, out1) in zip(got[:len(q)], got[len(q):]):
         assert np.array_equal(w0, w1) and np.array_equal(ids0, ids1) and torch.equal(out0, out1)
+
+
+def test_a_scan_of_many_layers_against_a_layer_by_itself():
+    """256 heads of 346 candidates: 46 MB of summaries and 72 MB of pages a layer, which one layer leaves in the cache."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    batch, ctx = 32, 348 * 32 + 5
+    K, V = (torch.randn((batch, ctx, 8, 128), dtype=torch.bfloat16, device="cuda", generator=gen) for _ in range(2))
+    q = torch.randn((3, batch, 32, 128), device="cuda", generator=gen).to(torch.bfloat16)
+    got = []
+    for n in (1, 3):
+        g = fkv.FreeKV(n_layers=n, batch=batch, n_q_heads=32, n_kv_heads=8, max_ctx=350 * 32, budget=512, sink=32, window=32, tau=0.8, dtype="bf16")
+        g.load_prefix(n - 1, K, V)
+        out = torch.zeros((batch, 32, 128), device="cuda")
+        for t in range(3):
+            g.decode_step(n - 1, q[t], K[:, t].contiguous(), V[:, t].contiguous(), out)
+            assert g.step_launches(n - 1) == 3
+            got.append((g.debug_read(n - 1, B.DBG_WEIGHTS)[..., 1:347], g.debug_read(n - 1, B.DBG_ACTIVE_IDS), out.clone()))
+        g.health(n - 1)
+        g.close()
+    for (w0, ids0, out0), (w1, ids1, out1) in zip(got[:3], got[3:]):
+        assert np.array_equal(w0, w1) and np.array_equal(ids0, ids1) and torch.equal(out0, out1)

@@ -1,6 +1,7 @@
-"""In which order the library hands work to streams, on the CPU: the HIP runtime's calls are taken by a recorder (hip_recorder.c),
-nothing runs, and what is recorded is read as a graph of what has to wait for what.  Here a missing wait between the compute
-stream and the copy stream shows whatever the timing; results on a GPU show it only when a recall happens to be late."""
+"""Which kernels the library launches and in which order it hands work to streams, on the CPU: the HIP runtime's calls are taken by
+a recorder (hip_recorder.c), nothing runs, and what is recorded is read as a graph of what has to wait for what.  Here a missing
+wait between the compute stream and the copy stream shows whatever the timing; results on a GPU show it only when a recall
+happens to be late."""
 import ctypes as C
 import json
 import os
@@ -183,6 +184,24 @@ def test_a_page_is_offloaded_before_a_later_one_takes_its_place(play, window, st
     assert len(pairs) >= 5
     for old, new in pairs:
         assert o.before(fills[old], opens[new]), f"page {new} may be written over page {old} before that is offloaded"
+
+
+@pytest.mark.parametrize("kernel,past,layers,batch,ctx,budget", [
+    ("layer_kernelILi1ELi4ELb0E", "Li0E", 32, 1, 1500, 4096),        # 47 pages a head, 201 MB, though the budget is 129
+    ("layer_kernelILi1ELi4ELb0E", "Li3E", 32, 1, 2600, 4096),        # 82: 344 MB
+    ("layer_kernelILi1ELi4ELb0E", "Li3E", 40, 1, 32768, 2048),       # 341 MB
+    ("layer_kernelILi1ELi4ELb0E", "Li1E", 32, 1, 32768, 2048),       # 277 MB of pages, 130 MB of summaries
+    ("scan_kernelILi1ELi4E", "Lb0E", 1, 32, 16640, 1024),            # 138 MB of pages, 65 MB of summaries
+    ("scan_kernelILi1ELi4E", "Lb1E", 2, 32, 16640, 1024),
+    ("attn_kernelILi1ELi4E", "Lb0E", 2, 32, 16640, 1024),
+    ("attn_kernelILi1ELi4E", "Lb1E", 3, 32, 16640, 1024),            # 415 MB of pages
+])
+def test_reads_past_the_cache_are_for_what_does_not_fit_it(play, kernel, past, layers, batch, ctx, budget):
+    """By the bytes that a context's layers attend and score (template arguments of the kernel's name: past the caches or not)."""
+    o = play([("load", 0, ctx), ("step", 0)], n_layers=layers, batch=batch, max_ctx=33280, budget_tokens=budget, sink_tokens=256, window_tokens=256, placement=0)
+    assert o.rc == [0, 0]
+    (op,) = o.launches(1, kernel)
+    assert kernel + past + "E" in o.ops[op][1]
 
 
 if __name__ == "__main__":
