@@ -101,7 +101,7 @@ static const int g_fuse = knob("FKV_FUSE", -1);
 // but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
 // in 2, 4, 8, 16 blocks: 2300 candidates 14.3, 13.4, 12.9, 13.5; 4000: 17.6, 17.0, 15.5, 15.0; 8160: -, 22.0, 19.8, 19.0; but 32 heads
 // x 4000 13.6, 13.4, 17.2, 19.7.
-constexpr int kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128;
+constexpr int kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024;
 static int selection_slices(const Geom& g, int G, int heads) {
   const int n = g.n_cand;
   if (g.k_eff == 0 || (n <= sel_regs_alone(G) * SEL_THREADS && (long)n * G <= kMaxAloneWork)) return 1;
@@ -247,7 +247,12 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const int heads = d.batch * d.n_kv;
   const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
   const int slices = selection_slices(g, d.G, heads);
-  const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, kMaxWaiting - (slices > 1 ? heads * slices : 0));
+  // Attention's blocks, which come last, are fewer where a list is shared, since selecting blocks wait too; and as few where a list
+  // is as long as one that two blocks would share, because with that many scoring blocks the launch runs in rounds.  A pass of
+  // 8 layer-steps, two blocks to the list / one / one with a split of attention's more for each head: 128 heads x 1234
+  // candidates 372, 348 and 394 us; x 1515 419, 390 and 428; 64 x 1515 222, 215 and 233; 96 x 1234 294, 286 and 286.
+  const int selecting = slices > 1 ? slices : g.n_cand > kLongList ? 2 : 0;
+  const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, kMaxWaiting - heads * selecting);
   const int n_splits = (n_att + pps - 1) / pps;
   if (n_splits > 63 || pps > 511) return false;
   const int passes = scoring_passes(d, g, slices, n_splits, kLayerResident);

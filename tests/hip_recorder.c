@@ -1,6 +1,6 @@
 /* Stands in for the HIP runtime where a test looks at the order in which the library hands work to streams: nothing runs, and every
  * call that orders work is written down, one line each:
- *   launch <kernel> <stream> <stop event or 0> <captured>
+ *   launch <kernel> <stream> <stop event or nil> <grid> <captured>
  *   record <event> <stream> <captured>
  *   wait   <event> <stream> <captured>
  *   sync
@@ -39,8 +39,8 @@ static const char* name_of(const void* stub) {
     if (stubs[i] == stub) return names[i];
   return "?";
 }
-static void launched(const void* stub, void* stream, event_t* stop) {
-  LOG("launch %s %p %p %d\n", name_of(stub), stream, (void*)stop, is_captured(stream));
+static void launched(const void* stub, dim3_t grid, void* stream, event_t* stop) {
+  LOG("launch %s %p %p %ux%ux%u %d\n", name_of(stub), stream, (void*)stop, grid.x, grid.y, grid.z, is_captured(stream));
   if (stop) stop->captured = 0;
 }
 
@@ -64,13 +64,13 @@ int __hipPopCallConfiguration(dim3_t* grid, dim3_t* block, size_t* lds, void** s
   return 0;
 }
 int hipLaunchKernel(const void* stub, dim3_t grid, dim3_t block, void** args, size_t lds, void* stream) {
-  (void)grid; (void)block; (void)args; (void)lds;
-  launched(stub, stream, NULL);
+  (void)block; (void)args; (void)lds;
+  launched(stub, grid, stream, NULL);
   return 0;
 }
 int hipExtLaunchKernel(const void* stub, dim3_t grid, dim3_t block, void** args, size_t lds, void* stream, void* start, void* stop, int flags) {
-  (void)grid; (void)block; (void)args; (void)lds; (void)start; (void)flags;
-  launched(stub, stream, stop);
+  (void)block; (void)args; (void)lds; (void)start; (void)flags;
+  launched(stub, grid, stream, stop);
   return 0;
 }
 

@@ -84,7 +84,7 @@ class Order:
             last_of[stream] = i
             if op[0] == "record":
                 recorded[op[1]] = (i, captured)
-            if op[0] == "launch" and op[3] != "0" and op[3] != "(nil)":
+            if op[0] == "launch" and op[3] != "(nil)":
                 recorded[op[3]] = (i, "0")                            # a stop event is never part of a capture
 
     def before(self, a, b):
@@ -202,6 +202,19 @@ def test_reads_past_the_cache_are_for_what_does_not_fit_it(play, kernel, past, l
     assert o.rc == [0, 0]
     (op,) = o.launches(1, kernel)
     assert kernel + past + "E" in o.ops[op][1]
+
+
+@pytest.mark.parametrize("batch,ctx,scoring,selecting,splits", [
+    (16, 33300, 8, 1, 2),      # 1024 candidates
+    (16, 33312, 9, 1, 1),      # 1025
+    (8, 49000, 12, 1, 2),      # 1515
+    (8, 33300, 8, 1, 4),
+    (1, 49000, 48, 1, 9),      # (far fewer blocks than may wait)
+])
+def test_attention_beside_a_long_list_is_cut_no_finer_than_beside_a_shared_one(play, batch, ctx, scoring, selecting, splits):
+    o = play([("load", 0, ctx), ("step", 0)], n_layers=1, batch=batch, max_ctx=65536, budget_tokens=2048, sink_tokens=256, window_tokens=256, placement=0)
+    (op,) = o.launches(1, "layer_kernel")
+    assert o.ops[op][4] == f"{8 * batch}x{2 + scoring + selecting + splits}x1"
 
 
 if __name__ == "__main__":
