@@ -286,7 +286,10 @@ int fkv_commit(fkv_ctx* ctx, int32_t layer);
  * state once, and every replay repeats the captured step on what the buffers hold by then -- same position, same
  * ACTIVE selection, same previous query.  A replay's launches are numbered on the device, by a small kernel
  * ahead of each, so no replay can take another one's values for its own.  With placement HOST the recall's
- * events and deferred submissions are host-side state that a replay does not repeat: do not capture there. */
+ * events and deferred submissions are host-side state that a replay does not repeat.  Steps that are captured
+ * together hand over to each other inside the graph, but not to what is launched outside of it: capture there only
+ * right behind fkv_load_prefix of every layer, end with fkv_flush and with compute_stream waiting for copy_stream, and
+ * load the layers again before they step outside of the graph. */
 int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* k_new_dev,
                     const void* v_new_dev, float* out_dev, void* compute_stream, void* copy_stream);
 

@@ -617,7 +617,7 @@ int fkv_load_prefix(fkv_ctx* ctx, int32_t layer, const void* K_dev, const void* 
   ls.L = n_tokens;
   ls.parity = 0;
   ls.have_prev_q = ls.have_active = ls.have_pending = ls.staged_q = ls.have_flags = false;
-  ls.offload_outstanding = ls.recall_outstanding = false;
+  ls.offload_outstanding = ls.offload_unseen = ls.recall_outstanding = false;
   ls.recalled = 0;
   return FKV_OK;
 }

@@ -59,19 +59,21 @@ def test_every_missing_unit_is_recalled_once(batch, n_kv, per_head):
 @pytest.mark.parametrize("own_copy_stream", [False, True])
 @pytest.mark.parametrize("batch,ctx,launches", [(1, 4000, 1), (32, 4000, 3)])        # the layer-step in one launch, and in separate ones
 def test_a_captured_step_with_the_host_pool(batch, ctx, launches, own_copy_stream):
-    """Steps of two layers, captured right behind the prompts: the streams hand over to each other inside the capture, by
-    events that are recorded as calls of their own and not by a launch.  Every replay against eager steps."""
+    """Four steps of two layers, captured right behind the prompts, with heads that are not corrected and miss pages from the second
+    step on: what a captured recall moves is what the layer's next captured step attends.  (That the recall lies between the two
+    whatever the timing: test_host_order.py.)  Every replay against eager steps."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(29)
 
     def normal(*shape):
         return torch.randn(shape, device="cuda", generator=gen)
 
-    layers, steps = 2, 2
+    layers, steps = 2, 4
     kv = [[normal(batch, ctx, 8, 128).to(torch.bfloat16) for _ in range(2)] for _ in range(layers)]
     q = [[normal(batch, 32, 128)] for _ in range(layers)]
     for x in q:
-        x.append(0.8 * x[0] + 0.6 * normal(batch, 32, 128))
+        while len(x) < steps:
+            x.append(0.9 * x[-1] + 0.436 * normal(batch, 32, 128))
     q = [[y.to(torch.bfloat16) for y in x] for x in q]
     new = [[normal(2, batch, 8, 128).to(torch.bfloat16) for _ in range(steps)] for _ in range(layers)]
     results = []
@@ -81,10 +83,14 @@ def test_a_captured_step_with_the_host_pool(batch, ctx, launches, own_copy_strea
         out = torch.zeros((steps, layers, batch, 32, 128), device="cuda")
         copy = torch.cuda.Stream()
 
+        deferred = []                                      # units that a step's deferred recall moves, in the eager run
+
         def decode():
             for t in range(steps):
                 for l in range(layers):
                     g.decode_step(l, q[l][t], new[l][t][0], new[l][t][1], out[t, l], copy_stream=copy if own_copy_stream else None)
+                    if not captured:
+                        deferred.append(int(g.debug_read(l, B.DBG_MISS)[..., 0][g.debug_read(l, B.DBG_FLAGS) == 0].sum()))
             if own_copy_stream:
                 torch.cuda.current_stream().wait_stream(copy)
 
@@ -100,11 +106,18 @@ def test_a_captured_step_with_the_host_pool(batch, ctx, launches, own_copy_strea
                 graph.replay()
                 torch.cuda.synchronize()
                 results.append(out.clone())
+            out.zero_()
+            for l in range(layers):                        # outside of the graph once more: from the prompts on
+                g.load_prefix(l, *kv[l])
+            decode()
+            torch.cuda.synchronize()
+            results.append(out.clone())
         else:
             decode()
             torch.cuda.synchronize()
             results.append(out.clone())
             assert g.step_launches(0) == launches
+            assert min(deferred[layers:]) > 0, deferred
         for l in range(layers):
             g.health(l)
         g.close()

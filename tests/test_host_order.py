@@ -157,11 +157,14 @@ def test_a_new_prompt_lies_behind_what_the_old_context_left_on_the_copy_stream(p
     [("capture",), ("step", 0), ("end_capture",), ("capture",), ("load", 0, 4000)],      # ... in two captures
 ])
 def test_a_new_prompt_does_not_wait_across_the_edge_of_a_capture(play, calls):
-    """(An event of the one side has no meaning on the other: the runtime refuses such a wait.)"""
-    o = play([("load", 0, 4031)] + calls, n_layers=1)
+    """(An event of the one side has no meaning on the other.)  Nor does the first step after it."""
+    o = play([("load", 0, 4031)] + calls + [("step", 0)], n_layers=1)
     assert set(o.rc) == {0}
-    lo, hi = o.span[-1]
+    lo, hi = o.span[-2]
     assert [op[0] for op in o.ops[lo:hi]] == ["launch"]
+    lo, hi = o.span[-1]
+    first = o.first_launch(len(o.calls) - 1)
+    assert all(op[0] == "launch" for op in o.ops[lo:first])
 
 
 @pytest.mark.parametrize("step", ["append", "step"])
