@@ -421,6 +421,7 @@ enum class Selected : int { NOTHING, KEYS, IDS };
 // 32-bit words of dynamic LDS that the keys of n candidates take (whole quads)
 __host__ __device__ constexpr int select_key_words(int n) { return n > 0 ? (n + 3) & ~3 : 4; }
 
+struct TopkBins { uint32_t top, shift; };
 struct alignas(16) SelectLds {
   uint32_t hist[TOPK_BINS];
   unsigned long long list[64];
@@ -430,21 +431,23 @@ struct alignas(16) SelectLds {
   uint32_t more[SEL_WAVES][64];
   uint32_t scan[SEL_WAVES];
   uint32_t n_list;
+  TopkBins bins;                                         // of scores that are not softmax values
   int alone;
   int failed[SEL_WAVES];
 };
 
-// The first histogram of the top-k decides nearly everything: for softmax scores its bins are a sixteenth of an octave
-// wide below 1.0 (down to 2^-32), so the bin of the k-th score holds a handful of keys -- and few keys share a
-// counter, where bins by the top byte put a whole selection on two or three of them.  Other scores: by the top 9 bits.
-constexpr uint32_t kKeyOfOne = 0xBF800000u;               // score_key(1.0f)
-__device__ __forceinline__ uint32_t topk_bin(uint32_t key, bool soft) {     // ascending bins: descending keys
-  return soft ? min((uint32_t)TOPK_BINS - 1, (kKeyOfOne - min(key, kKeyOfOne)) >> 19) : (uint32_t)TOPK_BINS - 1 - (key >> 23);
+// The first histogram of the top-k decides nearly everything: its bins are so narrow that the bin of the k-th score holds a handful of
+// keys -- and few keys share a counter, where bins by the top byte put a whole selection on two or three of them.  Below `top`,
+// 2^(23 - shift) to an octave: for softmax scores 16 below 1.0 (down to 2^-32), for others 64 below the group's largest weight (8 heads
+// x 992 candidates, MeanQK, a layer-step: 9.4 us; with bins by the top 9 bits, of which page weights have a few, 12.7, since
+// hundreds of keys were left to block_topk).
+constexpr TopkBins kSoftBins = {0xBF800000u, 19};         // (score_key(1.0f))
+__device__ __forceinline__ TopkBins bins_below(uint32_t largest) { return TopkBins{min(largest, 0xff800000u) + (1u << 22), 17}; }
+__device__ __forceinline__ uint32_t topk_bin(uint32_t key, TopkBins b) {     // ascending bins: descending keys
+  return min((uint32_t)TOPK_BINS - 1, (b.top - min(key, b.top)) >> b.shift);
 }
-// all keys of the bins up to `bin` are above this value, no other key is; bin < TOPK_BINS - 1
-__device__ __forceinline__ uint32_t topk_floor(uint32_t bin, bool soft) {
-  return soft ? kKeyOfOne - ((bin + 1) << 19) : (((uint32_t)TOPK_BINS - 1 - bin) << 23) - 1u;
-}
+// all keys of the bins up to `bin` are above this value, no other key is; bin < TOPK_BINS - 1, and there are keys in later bins
+__device__ __forceinline__ uint32_t topk_floor(uint32_t bin, TopkBins b) { return b.top - ((bin + 1) << b.shift); }
 
 // the bin of `hist` (ascending) that holds the `want`-th entry: bin, entries before it, entries in it.  Every wave
 // scans by itself: lane l sums bins 8l .. 8l+7, then the eight bins of the lane where the entry is are read again, one a lane
@@ -474,9 +477,9 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t want, ui
 // keys' bins, sm.n_list and sm.more are 0.
 // The keys of the one bin that is only partly wanted are collected and ranked against each other, with their places in the
 // order, by every wave; the same barrier brings the counts per wave of what is chosen anyway.  False, and nothing done, if there
-// are more than 64 of them (ties, or scores that are not softmax values).
+// are more than 64 of them (ties, mostly).
 template <int A, int R, typename Emit>
-__device__ __forceinline__ bool topk_items(const uint32_t (&key)[R], uint32_t have, int first, int second, int n, int kk, bool soft, int nw,
+__device__ __forceinline__ bool topk_items(const uint32_t (&key)[R], uint32_t have, int first, int second, int n, int kk, TopkBins bins, int nw,
                                            SelectLds& sm, Emit emit) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
   // f(slot, row) for every slot in use (a branch over each unused one would cost more than the work of a used one)
@@ -505,7 +508,7 @@ __device__ __forceinline__ bool topk_items(const uint32_t (&key)[R], uint32_t ha
     uint32_t* n_list = &sm.n_list;
     asm volatile("" : "+v"(n_list));                 // (an atomic of each lane: one for the wave would be a longer chain)
     rows([&](int u, int row) {
-      const uint32_t b = (have >> u & 1u) ? topk_bin(key[u], soft) : TOPK_BINS;
+      const uint32_t b = (have >> u & 1u) ? topk_bin(key[u], bins) : TOPK_BINS;
       pick |= b < up_to ? 1u << u : 0u;
       if (ranked && b == bin) sm.list[atomicAdd(n_list, 1u)] = (unsigned long long)key[u] << 32 | ~(uint32_t)(row * nt + tid);
     });
@@ -555,7 +558,7 @@ __device__ __forceinline__ bool topk_items(const uint32_t (&key)[R], uint32_t ha
 // (whichever thread owns j calls it).  1 <= kk <= n.  Longer chains: for lists that do not fit the registers, and for a group
 // that has made the keys alone.
 template <typename Emit>
-__device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, bool soft, int nw, SelectLds& sm, Emit emit) {
+__device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, TopkBins bins, int nw, SelectLds& sm, Emit emit) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = nw * 64;
   uint32_t T = 0, take_eq = 0;                       // take keys > T, and the first take_eq keys == T
   if (kk < n) {
@@ -563,11 +566,11 @@ __device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, b
     find_bin(sm.hist, (uint32_t)kk, bin, before, in_bin);
     const uint32_t need = (uint32_t)kk - before;     // keys of the bin that are wanted
     if (need == in_bin && bin < TOPK_BINS - 1) {
-      T = topk_floor(bin, soft);
+      T = topk_floor(bin, bins);
     } else if (in_bin <= 64) {
       for (int j = tid; j < n; j += nt) {
         const uint32_t kj = key[j];
-        if (topk_bin(kj, soft) == bin) sm.list[atomicAdd(&sm.n_list, 1u)] = kj;
+        if (topk_bin(kj, bins) == bin) sm.list[atomicAdd(&sm.n_list, 1u)] = kj;
       }
       lds_barrier();
       const uint32_t mine = lane < (int)in_bin ? (uint32_t)sm.list[lane] : 0u;
@@ -776,6 +779,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
   FKV_STAMP(a, head, 2);
 
   // ---- fixed-point softmax: the head's maxima, numerators, integer denominators ----
+  TopkBins bins = kSoftBins;
   double zd[G], zr[G];
 #pragma unroll
   for (int gg = 0; gg < G; ++gg) zd[gg] = zr[gg] = 1.0;
@@ -855,7 +859,17 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     hand(UnrollBy<0>{}); hand(UnrollBy<1>{}); hand(UnrollBy<2>{}); hand(UnrollBy<3>{});
     hand(UnrollBy<4>{}); hand(UnrollBy<5>{}); hand(UnrollBy<6>{}); hand(UnrollBy<7>{});
   } else {
+    float most = -__builtin_inff();                    // weight: no score is above it (a thread without a candidate repeats the last one)
+#pragma unroll
+    for (int u = 0; u < REGS; ++u) {
+      if (u >= U) break;
+#pragma unroll
+      for (int gg = 0; gg < G; ++gg) most = fmaxf(most, __uint_as_float(e[u][gg]));
+    }
+    sm.mx[wave][0] = wave_max_f32(most);
     if (any_failed()) return Selected::NOTHING;        // (and behind its barrier the histogram is clear)
+    bins = bins_below(score_key(wave_max_f32(sm.mx[min(lane, nw - 1)][0])));
+    if (tid == 0) sm.bins = bins;
   }
   FKV_STAMP(a, head, 4);
 
@@ -898,7 +912,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     if (u >= U) break;
     if (have >> u & 1u) {
       if (!fits) key_lds[others + id[u] - lo - j0] = key[u];
-      atomicAdd(&sm.hist[topk_bin(key[u], soft)], 1u);
+      atomicAdd(&sm.hist[topk_bin(key[u], bins)], 1u);
     }
   }
   uint32_t key_of[SEL_OTHERS];                         // the other groups'
@@ -934,7 +948,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
             key_of[x] = (uint32_t)w[x][0];
             id_of[x] = all ? lo + tid + x * nt : (int)(uint32_t)w[x][1];
             have_of |= 1u << x;
-            atomicAdd(&sm.hist[topk_bin(key_of[x], soft)], 1u);
+            atomicAdd(&sm.hist[topk_bin(key_of[x], bins)], 1u);
           }
         }
       }
@@ -961,7 +975,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
         for (int x = 0; x < 4; ++x) {
           if (i0 + x * nt < others) {
             key_lds[i0 + x * nt] = (uint32_t)w[x][0];
-            atomicAdd(&sm.hist[topk_bin((uint32_t)w[x][0], soft)], 1u);
+            atomicAdd(&sm.hist[topk_bin((uint32_t)w[x][0], bins)], 1u);
           }
         }
       }
@@ -976,7 +990,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
   const PutId put(a, head, key_lds);
   bool done;
   if (S == 1) {
-    done = topk_items<REGS>(key, have, U, 0, n, kk, soft, nw, sm, [&](int pos, int u) { put(pos, id[u]); });
+    done = topk_items<REGS>(key, have, U, 0, n, kk, bins, nw, sm, [&](int pos, int u) { put(pos, id[u]); });
   } else {                                             // (U <= SEL_REGS)
     constexpr int R = SEL_OTHERS + SEL_REGS;
     uint32_t item[R];
@@ -986,7 +1000,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
       item[u] = u < SEL_OTHERS ? key_of[u < SEL_OTHERS ? u : 0] : key[u < SEL_OTHERS ? 0 : u - SEL_OTHERS];
       item_id[u] = u < SEL_OTHERS ? id_of[u < SEL_OTHERS ? u : 0] : id[u < SEL_OTHERS ? 0 : u - SEL_OTHERS];
     }
-    done = topk_items<SEL_OTHERS>(item, have_of | have << SEL_OTHERS, X, U, others + j1 - j0, kk, soft, nw, sm, [&](int pos, int u) {
+    done = topk_items<SEL_OTHERS>(item, have_of | have << SEL_OTHERS, X, U, others + j1 - j0, kk, bins, nw, sm, [&](int pos, int u) {
       if (last) {
         put(pos, item_id[u]);
       } else {
@@ -1121,7 +1135,7 @@ __device__ __forceinline__ void alone_keys(const StepArgs& a, int head, int nw, 
     const float sc = mode == 0 ? (float)(acc / (double)G) : mode == 1 ? (float)acc : mode == 2 ? (float)((double)acc32 / (double)G) : acc32;
     const uint32_t kj = score_key(sc);
     key[j] = kj;
-    atomicAdd(&sm.hist[topk_bin(kj, soft)], 1u);
+    atomicAdd(&sm.hist[topk_bin(kj, kSoftBins)], 1u);
   }
   lds_barrier();
 }
@@ -1165,7 +1179,7 @@ __device__ __forceinline__ void select_finish(const StepArgs& hot, int head, int
     const bool last = alone || s == a.slices - 1;
     const int j0 = alone ? 0 : s * a.slice, m = handed_on(a.slices, a.slice, kk), others = last && !alone ? (a.slices - 1) * m : 0;
     unsigned long long* const keyid = a.keyid + (size_t)head * a.max_pages;
-    block_topk(key, last ? others + n - j0 : a.slice, kk, a.sel_pool <= 1, nw, sm, [&](int pos, int j) {
+    block_topk(key, last ? others + n - j0 : a.slice, kk, alone || a.sel_pool <= 1 ? kSoftBins : sm.bins, nw, sm, [&](int pos, int j) {
       const int id = j >= others ? lo + j0 + j - others : m == a.slice ? lo + j : (int)(uint32_t)ld_tag(keyid + j);
       if (last) { put(pos, id); return; }
       st_tag(a.keyx + (size_t)head * a.max_pages + s * m + pos, key[j], tag);

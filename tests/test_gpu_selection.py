@@ -34,6 +34,26 @@ def _best(score, k):
     (4, 16, 8, 2600, 40),      # ... and two blocks per head
 ])
 def test_the_best_pages_of_a_list(G, n_kv, batch, n_cand, k, levels):
+    _check(G, n_kv, batch, n_cand, k, levels, "MeanS")
+
+
+@pytest.mark.parametrize("levels", [0, 1, 7])
+@pytest.mark.parametrize("pooling", ["MeanQK", "MaxQ"])  # scores of either sign, hundreds of them of one exponent
+@pytest.mark.parametrize("G,n_kv,batch,n_cand,k", [
+    (4, 2, 1, 64, 63),         # one wave
+    (4, 2, 1, 150, 20),        # three: fewer threads than counters
+    (4, 2, 1, 992, 32),
+    (5, 1, 2, 1880, 500),
+    (2, 3, 1, 4097, 33),       # sixteen blocks, each hands on its best
+    (8, 1, 1, 2400, 150),
+    (8, 1, 1, 5100, 200),      # more than the registers hold
+    (1, 16, 16, 600, 50),      # selection in a launch of its own
+])
+def test_the_best_pages_by_other_scores(G, n_kv, batch, n_cand, k, pooling, levels):
+    _check(G, n_kv, batch, n_cand, k, levels, pooling)
+
+
+def _check(G, n_kv, batch, n_cand, k, levels, pooling):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n_cand + levels)
     pages = n_cand + 4
@@ -45,7 +65,7 @@ def test_the_best_pages_of_a_list(G, n_kv, batch, n_cand, k, levels):
         K = torch.randn((batch, ctx, n_kv, 128), dtype=torch.bfloat16, device="cuda", generator=gen)
     q = torch.randn((batch, G * n_kv, 128), device="cuda", generator=gen).to(torch.bfloat16)
     g = fkv.FreeKV(n_layers=1, batch=batch, n_q_heads=G * n_kv, n_kv_heads=n_kv, max_ctx=ctx + 32, budget=128 + 32 * k, sink=64, window=64,
-                   tau=0.8, dtype="bf16")
+                   tau=0.8, dtype="bf16", select_pooling=pooling)
     g.load_prefix(0, K, K)
     new = torch.zeros((batch, n_kv, 128), dtype=torch.bfloat16, device="cuda")
     out = torch.empty((batch, G * n_kv, 128), device="cuda")
