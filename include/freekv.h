@@ -277,7 +277,7 @@ int fkv_commit(fkv_ctx* ctx, int32_t layer);
  * the cache does not hold reads it from the host pool and puts it into its page-cache slot -- which
  * leaves the same state: by the end of the step the page is cached and was attended over.
  * When the layer-step runs as one launch with the KV in a host pool, the deferred recall is not
- * put on copy_stream at once: the recalls of a quarter of the context's layers (at most 8) are
+ * put on copy_stream at once: the recalls of half of the context's layers (at least 1, at most 8) are
  * submitted together (one dependency between the two streams instead of one per layer) -- with
  * the last layer of such a group, with the last layer of the context, with the same layer's
  * next step, and by any other call on the context.

@@ -19,7 +19,7 @@ namespace fkv {
 typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // (scalar loads)
 
 // packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), pages per
-// split (9), lose_selection, WAIT_* bits (6), STREAM_* bits (2);   split_magic: 2^32 / splits rounded up, 0 for one split
+// split (9), lose_selection, WAIT_* bits (6);   split_magic: 2^32 / splits rounded up, 0 for one split
 struct LayerKernelArgs {                     // the kernel's arguments, in their order
   const LayerConst* consts;
   const uint16_t *q, *k_new, *v_new;

@@ -4,10 +4,6 @@
 #include "fkv_step_dev.h"
 #include "fkv_attn_dev.h"
 
-#include <hip/hip_ext.h>
-
-#include <algorithm>
-
 #pragma clang fp contract(off)
 
 namespace fkv {
