@@ -243,12 +243,13 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const int heads = d.batch * d.n_kv;
   const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
   const int slices = selection_slices(g, d.G, heads);
-  // Attention's blocks, which come last, are fewer where a list is shared, since selecting blocks wait too; and as few where a list
-  // is as long as one that two blocks would share, because with that many scoring blocks the launch runs in rounds.  A pass of
-  // 8 layer-steps, two blocks to the list / one / one with a split of attention's more for each head: 128 heads x 1234
-  // candidates 372, 348 and 394 us; x 1515 419, 390 and 428; 64 x 1515 222, 215 and 233; 96 x 1234 294, 286 and 286.
-  const int selecting = slices > 1 ? slices : g.n_cand > kLongList ? 2 : 0;
-  const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, kMaxWaiting - heads * selecting);
+  // Attention's blocks, which come last, are fewer where a list is shared, since selecting blocks wait too.  Beside a long list of one
+  // block, a head is cut half as fine as it could be: with that many scoring blocks the launch runs in rounds, and blocks of a later
+  // one queue.  A pass of 8 layer-steps, in full and half: 128 heads x 1234 candidates (2 splits and 1) 395 and 347 us, and 434 and 375
+  // where most heads are corrected; 64 x 1515 (4 and 2) 233 and 215, 288 and 255; 80 x 1234 (3 and 2) 254 and 239, 293 and 271 (in one 256,
+  // 292); 48 x 1515 (5 and 3) 190 and 180, 241 and 229; 96 x 1484 (2 and 1) 307 and 306, 343 and 342.
+  const int waiting = slices > 1 ? kMaxWaiting - heads * slices : g.n_cand > kLongList ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting;
+  const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, waiting);
   const int n_splits = (n_att + pps - 1) / pps;
   if (n_splits > 63 || pps > 511) return false;
   const int passes = scoring_passes(d, g, slices, n_splits, kLayerResident);
