@@ -97,7 +97,7 @@ static const int g_fuse = knob("FKV_FUSE", -1);
 // but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
 // in 2, 4, 8, 16 blocks: 2300 candidates 14.3, 13.4, 12.9, 13.5; 4000: 17.6, 17.0, 15.5, 15.0; 8160: -, 22.0, 19.8, 19.0; but 32 heads
 // x 4000 13.6, 13.4, 17.2, 19.7.
-constexpr int kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024;
+constexpr int kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024, kFewHeads = 40;
 static int selection_slices(const Geom& g, int G, int heads) {
   const int n = g.n_cand;
   if (g.k_eff == 0 || (n <= sel_regs_alone(G) * SEL_THREADS && (long)n * G <= kMaxAloneWork)) return 1;
@@ -243,12 +243,14 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const int heads = d.batch * d.n_kv;
   const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
   const int slices = selection_slices(g, d.G, heads);
-  // Attention's blocks, which come last, are fewer where a list is shared, since selecting blocks wait too.  Beside a long list of one
-  // block, a head is cut half as fine as it could be: with that many scoring blocks the launch runs in rounds, and blocks of a later
-  // one queue.  A pass of 8 layer-steps, in full and half: 128 heads x 1234 candidates (2 splits and 1) 395 and 347 us, and 434 and 375
-  // where most heads are corrected; 64 x 1515 (4 and 2) 233 and 215, 288 and 255; 80 x 1234 (3 and 2) 254 and 239, 293 and 271 (in one 256,
-  // 292); 48 x 1515 (5 and 3) 190 and 180, 241 and 229; 96 x 1484 (2 and 1) 307 and 306, 343 and 342.
-  const int waiting = slices > 1 ? kMaxWaiting - heads * slices : g.n_cand > kLongList ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting;
+  // Attention's blocks, which come last, are fewer where a list is shared, since selecting blocks wait too.  Beside long lists of
+  // many heads, a block each, a head is cut half as fine as it could be: with that many scoring blocks the launch runs in rounds, and
+  // blocks of a later one queue.  A pass of 8 layer-steps, in full and half: 128 heads x 1234 candidates (2 splits and 1) 395 and
+  // 347 us, and 434 and 375 where most heads are corrected; 64 x 1515 (4 and 2) 233 and 215, 288 and 255; 80 x 1234 (3 and 2) 254 and
+  // 239, 293 and 271 (in one 256, 292); 48 x 1515 (5 and 3) 190 and 180, 241 and 229; but 40 x 1389 (5 and 3) 201 and 205, 24 x 1389
+  // (9 and 5) 160 and 168.
+  const bool half = g.n_cand > kLongList && heads > kFewHeads;
+  const int waiting = slices > 1 ? kMaxWaiting - heads * slices : half ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting;
   const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, waiting);
   const int n_splits = (n_att + pps - 1) / pps;
   if (n_splits > 63 || pps > 511) return false;

@@ -213,9 +213,11 @@ def test_reads_past_the_cache_are_for_what_does_not_fit_it(play, kernel, past, l
     (8, 49000, 12, 1, 2),      # 1515
     (8, 33300, 8, 1, 4),
     (10, 40000, 10, 1, 2),     # three would fit
-    (1, 49000, 48, 1, 9),      # (far fewer blocks than may wait)
+    (6, 49000, 12, 1, 3),      # five would
+    (5, 49000, 12, 1, 5),
+    (1, 49000, 48, 1, 9),
 ])
-def test_attention_beside_a_long_list_is_cut_half_as_fine(play, batch, ctx, scoring, selecting, splits):
+def test_attention_beside_long_lists_of_many_heads_is_cut_half_as_fine(play, batch, ctx, scoring, selecting, splits):
     o = play([("load", 0, ctx), ("step", 0)], n_layers=1, batch=batch, max_ctx=65536, budget_tokens=2048, sink_tokens=256, window_tokens=256, placement=0)
     (op,) = o.launches(1, "layer_kernel")
     assert o.ops[op][4] == f"{8 * batch}x{2 + scoring + selecting + splits}x1"
