@@ -675,8 +675,8 @@ struct PutId {
 // A wave whose patience ends has nothing to say, and what it would have had to is never put into words under the tag: its
 // group learns of it at the next barrier, from a value no sum has or a flag, and leaves.  Of the groups only the last one has to
 // end with all the keys, and it can make them alone (alone_keys).  Returns how far the group got.
-// (Ways out that are hardly ever taken are marked as unlikely: without that the compiler keeps up to twice as many scalars in lanes of
-// vector registers, 1 to 2 % of a layer-step whose list is shared.)
+// (Ways out that are hardly ever taken, and the other scores, are marked as unlikely: without that the compiler keeps up to twice as
+// many scalars in lanes of vector registers, 0.5 to 2 % of a layer-step.)
 template <int G, bool TAGGED>
 __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, int s, int nw, uint32_t* key_lds, SelectLds& sm) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
@@ -785,7 +785,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
   double zd[G], zr[G];
 #pragma unroll
   for (int gg = 0; gg < G; ++gg) zd[gg] = zr[gg] = 1.0;
-  if (soft) {
+  if (__builtin_expect(soft, 1)) {
     unsigned long long* const mine = a.exch + ((size_t)head * MAX_SLICES + s) * 2 * MAX_G;
     const unsigned long long* const all = a.exch + (size_t)head * MAX_SLICES * 2 * MAX_G;
     if (S > 1) {
