@@ -516,11 +516,12 @@ int fkv_create(const fkv_config* cfg, void* dev_arena, size_t dev_bytes, void* h
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeSharedMemPerBlockOptin, dev_id) == hipSuccess && v > max_lds) max_lds = v;
   }
   ctx->dims = Dims{cfg->batch, cfg->n_q_heads, cfg->n_kv_heads, cfg->n_q_heads / cfg->n_kv_heads, l.k, l.max_pages, cfg->dtype, max_lds,
-                   cfg->select_pooling, cfg->corr_pooling, cfg->n_layers};
+                   cfg->select_pooling, cfg->corr_pooling, cfg->n_layers, false};
   ctx->dev = static_cast<char*>(dev_arena);
   ctx->host = cfg->placement == FKV_PLACE_HOST ? static_cast<char*>(host_arena) : nullptr;
   ctx->layers.resize(cfg->n_layers);
   ctx->defer_group = cfg->n_layers / 2 < 1 ? 1 : cfg->n_layers / 2 > GATHER_MAX_LAYERS ? GATHER_MAX_LAYERS : cfg->n_layers / 2;
+  if (l.total >= kWhereBlocks * sizeof(uint32_t)) ctx->dims.same_xcd = blocks_by_xcd(static_cast<uint32_t*>(dev_arena));
   hipError_t e = hipMemset(dev_arena, 0, l.total);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   const unsigned ev_flags = hipEventDisableTiming;

@@ -5,15 +5,17 @@
 
 namespace fkv {
 
-// grid (n_splits, n_kv, batch); NW wavefronts per block
+// grid: n_splits blocks a head, dealt to the heads (deal_block); NW wavefronts per block
 template <int DT, int NW, bool PAST>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void attn_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) float attn_lds[];
   touch_args<sizeof(AttnArgs)>();
-  const int head = (int)(blockIdx.z * a.n_kv + blockIdx.y);
-  const AttnLeft left = attn_block<DT, NW, false, false, PAST>(a, blockIdx.x, head, attn_lds);
+  int head, split;
+  deal_block(blockIdx.x, a.n_splits, a.home, [&](uint32_t j) { return a.split_magic ? __umulhi(j, a.split_magic) : j; }, head, split);
+  if (head >= a.heads) return;
+  const AttnLeft left = attn_block<DT, NW, false, false, PAST>(a, split, head, attn_lds);
   if (__builtin_expect(left.any(), 0))
-    attn_finish<DT, NW, false, false>(args_from_memory<AttnArgs>(), blockIdx.x, head, left);
+    attn_finish<DT, NW, false, false>(args_from_memory<AttnArgs>(), split, head, left);
 }
 
 // experiment builds only (see knob()): pages per block (0 = choose from the shape)
@@ -55,7 +57,10 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   a.n_splits = (n_att + a.pps - 1) / a.pps;
   a.share = (d.G * D + a.n_splits - 1) / a.n_splits;
   a.out = io.out; a.g = g; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k; a.status = io.status; a.tstamp = io.tstamp;
-  dim3 grid(a.n_splits, d.n_kv, d.batch);
+  a.heads = heads;
+  a.split_magic = a.n_splits > 1 ? 0xffffffffu / (uint32_t)a.n_splits + 1u : 0u;      // (exact for block numbers below 2^32 / n_splits)
+  a.home = a.n_splits > 1 && heads_at_home(d, heads, a.n_splits);
+  const dim3 grid((unsigned)(a.home ? by_xcd(heads) : heads) * a.n_splits);
   constexpr int NW = 4;
   const size_t lds = attn_lds_floats(NW, d.G) * sizeof(float);
   if (ev_begin) (void)hipEventRecord(ev_begin, st);

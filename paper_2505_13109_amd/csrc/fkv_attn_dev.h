@@ -104,10 +104,12 @@ struct AttnArgs {
   unsigned long long* part_ml;
   int max_splits, pps, n_splits;
   int share;                 // outputs of a head that each of its blocks finishes
+  bool home;                 // a head's blocks are on one XCD (deal_block)
+  uint32_t split_magic;      // stand-alone attention: 2^32 / n_splits rounded up, 0 for one split
   LaunchNo no;               // stand-alone attention: of this launch
   float* out;
   Geom g;
-  int n_kv, G, k;
+  int heads, n_kv, G, k;     // heads: stand-alone attention: (request, KV head) pairs
   int* status;               // set to 1 if a wait ran out
   long long* tstamp;
   // --- when attention shares its launch with the step roles ("fused") ---
@@ -577,10 +579,10 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
         ot += sm_o[((size_t)w * G + gg) * (D + 4) + c] * __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(wgt), w));
       o[t] = ot; den[t] = dt; M[t] = Mt;
       if (n_splits > 1) {
-        if (idx < own_lo || idx >= own_hi) st_tag(po + (size_t)split * items + idx, __float_as_uint(ot), tag);
+        if (idx < own_lo || idx >= own_hi) st_tag(po + (size_t)split * items + idx, __float_as_uint(ot), tag, a.home);
         if (c == 0) {
-          st_tag(pml + (split * G + gg) * 2, __float_as_uint(Mt), tag);
-          st_tag(pml + (split * G + gg) * 2 + 1, __float_as_uint(dt), tag);
+          st_tag(pml + (split * G + gg) * 2, __float_as_uint(Mt), tag, a.home);
+          st_tag(pml + (split * G + gg) * 2 + 1, __float_as_uint(dt), tag, a.home);
         }
       }
     }

@@ -274,12 +274,29 @@ __device__ __forceinline__ void tagged_unpick(uint32_t w, int& id, int& slot, bo
   miss = (w >> 31) != 0;
 }
 
+// Which head block i of a section of a launch's blocks works for, and which of the head's n it is.  Blocks go to the 8 XCDs in
+// turn, by their number in the launch.  At home: heads by 8, each on an XCD of its own, so that what a head's blocks tell each
+// other stays in that XCD's L2 (the section has to start at a multiple of 8; what is beyond the last head is nobody's).
+// Else a head's blocks are adjacent.  In both cases at most one head's blocks per XCD, or per launch, are ever half there.
+// div: i -> i / n.
+template <typename Div>
+__device__ __forceinline__ void deal_block(uint32_t i, int n, bool home, Div div, int& head, int& own) {
+  const uint32_t j = home ? i >> 3 : i, h = div(j);
+  own = (int)(j - h * (uint32_t)n);
+  head = (int)(home ? h * 8 + (i & 7u) : h);
+}
+
 // A value exchanged between blocks of one launch without a counter: one 64-bit word holding the value and a tag that no
 // earlier writer of that word used (a launch number), written and read in one piece at device scope.  A reader that sees
 // the tag has the value: no acknowledgement to wait for, no counter to bump, no second read.  Measured on this chip: one
 // way about 0.6 us, against 0.3 us (store acknowledged) + 0.4 us (atomic) + 0.6 us (read) for store / counter / read.
-__device__ __forceinline__ void st_tag(unsigned long long* p, uint32_t value, uint32_t tag) {
-  __hip_atomic_store(p, ((unsigned long long)tag << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// home: a head's blocks are all on one XCD (deal_block), so the word only has to be in that XCD's L2, where it stays till the
+// launch ends; else it is written through to memory.  Readers go past their L1 in either case, which is all there is between
+// them and the L2, so they need not know.  A word that could not be seen would be a wait that runs out (PATIENCE).
+__device__ __forceinline__ void st_tag(unsigned long long* p, uint32_t value, uint32_t tag, bool home) {
+  const unsigned long long w = ((unsigned long long)tag << 32) | value;
+  if (home) __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else      __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ unsigned long long ld_tag(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

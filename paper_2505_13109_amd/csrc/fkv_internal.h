@@ -78,7 +78,16 @@ __host__ __device__ inline int v_elem_off(int t, int ch) {
 }
 
 // ---- launch wrappers (defined in the kernel files) ----------------------
-struct Dims { int batch, n_q, n_kv, G, k, max_pages, dtype, max_lds, sel_pool, corr_pool, n_layers; };
+// same_xcd: blocks whose numbers in a launch are equal modulo 8 run on the same XCD (blocks_by_xcd)
+struct Dims { int batch, n_q, n_kv, G, k, max_pages, dtype, max_lds, sel_pool, corr_pool, n_layers; bool same_xcd; };
+constexpr int kXcds = 8;
+inline int by_xcd(int heads) { return (heads + kXcds - 1) / kXcds * kXcds; }
+// Whether the blocks of launches on this device are dealt to its XCDs in turn: by what a launch of kWhereBlocks blocks, which
+// each write where they are, leaves at `where` (device memory).
+constexpr int kWhereBlocks = 1024;
+bool blocks_by_xcd(uint32_t* where);
+// Whether a head's blocks, `rows` of them, are put on one XCD (deal_block).
+bool heads_at_home(const Dims& d, int heads, int rows);
 
 // Launches are numbered (31 bits, from 1), and the values that a launch's blocks exchange carry its number as a tag.  The
 // host counts.  A launch that is being captured runs again at every replay with the arguments it was captured with, so its

@@ -19,7 +19,7 @@ namespace fkv {
 typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // (scalar loads)
 
 // packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), pages per
-// split (9), lose_selection, WAIT_* bits (6);   split_magic: 2^32 / splits rounded up, 0 for one split
+// split (9), lose_selection, WAIT_* bits (6), at home;   split_magic: 2^32 / splits rounded up, 0 for one split
 struct LayerKernelArgs {                     // the kernel's arguments, in their order
   const LayerConst* consts;
   const uint16_t *q, *k_new, *v_new;
@@ -37,12 +37,14 @@ struct LayerSetup {
   Geom g;
   uint32_t tag;
   PoolDesc pd;
+  bool home;
   int layer, now, before, chunks, passes_log2, slices_log2, slices, step_rows;      // now, before: halves (PENDING / staged, ACTIVE / previous)
   __device__ __forceinline__ explicit LayerSetup(const LayerKernelArgs& ka) {
     c = (LayerConstPtr)ka.consts;
     layer = (int)(ka.packed >> 19);
     now = (int)(ka.plan >> 1) & 1;
     before = now ^ 1;
+    home = (ka.plan >> 29 & 1u) != 0;
     base = c->dev_base + c->layer_bytes * (unsigned long long)layer;
     g = geom_of((int)(ka.packed & 0x7ffffu) + 1, c->n_sink, c->n_win, c->k);
     tag = ka.host_numbered ? ka.host_numbered : device_tag((uint32_t)*(const __attribute__((address_space(4))) int*)c->launch_no);
@@ -80,7 +82,7 @@ struct LayerSetup {
     a.ids = ids(now); a.ids_user = nullptr;
     a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
     a.slice = (g.n_cand + slices - 1) >> slices_log2;
-    a.exch = c->exch; a.keyx = c->keyx; a.keyid = c->keyid; a.cmax = c->cmax; a.no = LaunchNo{tag, nullptr}; a.impatient = ka.plan >> 23; a.tstamp = c->tstamp;
+    a.exch = c->exch; a.keyx = c->keyx; a.keyid = c->keyid; a.cmax = c->cmax; a.no = LaunchNo{tag, nullptr}; a.home = home; a.impatient = ka.plan >> 23 & 63u; a.tstamp = c->tstamp;
     a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
     if (HOSTPOOL) {
@@ -105,7 +107,7 @@ struct LayerSetup {
     a.q_prev = qprev(before); a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
     a.k_new = ka.k_new; a.v_new = ka.v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.tag = tag; a.pick_tag = tag + ((ka.plan >> 22) & 1u ? 2u : 0u);
-    a.impatient = ka.plan >> 23;
+    a.impatient = ka.plan >> 23 & 63u; a.home = home; a.split_magic = ka.split_magic;
     a.host_pool = HOSTPOOL ? reinterpret_cast<const uint16_t*>(c->host_base + c->host_layer_bytes * (unsigned long long)layer) : nullptr;
     a.max_pages = c->max_pages;
     return a;
@@ -138,10 +140,11 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
     if (!go_on) return;
   } else {
     const AttnArgs a = u.attn_args(ka, G);
-    // numbered through row by row, so that a head's blocks, which wait for each other, are adjacent
-    const uint32_t i = (blockIdx.y - (uint32_t)u.step_rows) * (uint32_t)u.c->heads + blockIdx.x;
-    head = (int)(split_magic ? __umulhi(i, split_magic) : i);
-    own = (int)i - head * a.n_splits;
+    // numbered through row by row and dealt to the heads, whose blocks wait for each other
+    const uint32_t wide = (uint32_t)(u.home ? (u.c->heads + 7) & ~7 : u.c->heads);
+    deal_block((blockIdx.y - (uint32_t)u.step_rows) * wide + blockIdx.x, a.n_splits, u.home,
+               [&](uint32_t j) { return split_magic ? __umulhi(j, split_magic) : j; }, head, own);
+    if (head >= u.c->heads) return;
     left = attn_block<DT, STEP_WAVES, true, HOSTPOOL, (STREAM & STREAM_PAGES) != 0>(a, own, head, reinterpret_cast<float*>(dyn_lds));
     if (__builtin_expect(!left.any(), 1)) return;
     // What follows is hardly ever run.  Its arguments come from memory once more: kept up to here they would cost the page

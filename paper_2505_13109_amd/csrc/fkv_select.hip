@@ -69,12 +69,14 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) __attribute__((amdgpu_waves_per_eu
   }
   score_role<DT, G, false, SCAN_WAVES, PAST>(a, y - a.other_rows, blockIdx.x);
 }
-// The selection after it: one block per slice of a head's candidates, a head's slices adjacent.
+// The selection after it: one block per slice of a head's candidates, dealt to the heads (deal_block).
 template <int G>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
   touch_args<sizeof(StepArgs)>();
-  const int head = (int)blockIdx.x >> a.slices_log2, s = (int)blockIdx.x & (a.slices - 1);
+  int head, s;
+  deal_block(blockIdx.x, a.slices, a.home, [&](uint32_t j) { return j >> a.slices_log2; }, head, s);
+  if (head >= a.heads) return;
   int nw;
   Selected got;
   if (select_begin<G, false>(a, head, s, dyn_lds, nw, got)) 
@@ -104,6 +106,40 @@ static int selection_slices(const Geom& g, int G, int heads) {
   int s = 2;
   while (s < MAX_SLICES && ((n + s - 1) / s > SEL_REGS * SEL_THREADS || ((n + s - 1) / s > kFineSlice && heads * s * 2 <= kMaxFineBlocks))) s *= 2;
   return s;
+}
+
+static const int g_home = knob("FKV_HOME", -1);                   // 0 never, 1 always
+
+// A word that stays in the L2 it was written to is seen after 0.22 us, through memory after 0.3 to 0.5, and a block reads its
+// head's 30 KB of weights from the L2 at several times the rate; an exchange of a layer-step takes 0.3 to 0.8 us less.  Layer-steps
+// of G = 4, a head's blocks on one XCD against adjacent ones: 8 heads x 992 candidates 8.9 and 9.4 us, 2016 (G = 8) 13.8 and 16.1,
+// 16 heads x 992 9.5 and 10.3, 64 23.6 and 26.8 (27.0 and 31.9 where most are corrected), 248 heads of one block each the same.
+// Where the heads do not go round evenly some XCDs have more of them: still better while all of an XCD's blocks run at once
+// (4 heads x 32 candidates 6.7 and 7.3; 1 x 480 6.8 and 7.1; 20 x 480 9.7 and 9.9), not beyond (1 head x 8160 18.4 and 12.6; 20 x 2016
+// 16.7 and 15.9; 100 x 144 21.3 and 19.2).
+bool heads_at_home(const Dims& d, int heads, int rows) {
+  if (g_home >= 0) return g_home == 1;
+  return d.same_xcd && (heads % kXcds == 0 || by_xcd(heads) / kXcds * rows <= 2 * kComputeUnits / kXcds);
+}
+
+// Which XCD a block runs on is the dispatcher's choice, not the programming model's, so it is looked at once for every context
+// (here) and no result depends on it: where it is not so, words go through memory, and a word that a reader does not see is a
+// wait that runs out.
+__global__ void where_kernel(uint32_t* where) {
+  uint32_t xcd;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcd));
+  if (threadIdx.x == 0) where[blockIdx.x] = xcd;
+}
+bool blocks_by_xcd(uint32_t* where) {
+  uint32_t at[kWhereBlocks];
+  where_kernel<<<kWhereBlocks, 64>>>(where);
+  if (hipMemcpy(at, where, sizeof(at), hipMemcpyDeviceToHost) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  for (int i = kXcds; i < kWhereBlocks; ++i)
+    if (at[i] != at[i % kXcds]) return false;
+  return true;
 }
 
 // Passes of a scoring block: a launch runs in ceil(blocks / resident blocks) rounds, and blocks of a later round (the
@@ -187,9 +223,11 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
     const int slices = selection_slices(g, d.G, heads);
     fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
     const bool past = (stream_of(d, g) & STREAM_SUMMARIES) != 0;
+    a.home = (roles & ROLE_SELECT) != 0 && heads_at_home(d, heads, rows);
+    const dim3 grid(a.home ? by_xcd(heads) : heads, rows);
     if (!(past ? grant_lds(&step_kernel<DT, G, true>, lds, granted_past) : grant_lds(&step_kernel<DT, G, false>, lds, granted_step))) return -1;
-    if (past) step_kernel<DT, G, true><<<dim3(heads, rows), STEP_THREADS, lds, st>>>(a);
-    else      step_kernel<DT, G, false><<<dim3(heads, rows), STEP_THREADS, lds, st>>>(a);
+    if (past) step_kernel<DT, G, true><<<grid, STEP_THREADS, lds, st>>>(a);
+    else      step_kernel<DT, G, false><<<grid, STEP_THREADS, lds, st>>>(a);
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
   }
@@ -202,7 +240,8 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   const dim3 scan_grid(a.chunks, scan_rows < kGridRows ? scan_rows : kGridRows, (scan_rows + kGridRows - 1) / kGridRows);
   if (stream_of(d, g) & STREAM_SUMMARIES) scan_kernel<DT, G, true><<<scan_grid, SCAN_WAVES * 64, 0, st>>>(a);
   else                                    scan_kernel<DT, G, false><<<scan_grid, SCAN_WAVES * 64, 0, st>>>(a);
-  select_kernel<G><<<heads * a.slices, SEL_THREADS, lds, st>>>(a);
+  a.home = a.slices > 1 && heads_at_home(d, heads, a.slices);
+  select_kernel<G><<<(a.home ? by_xcd(heads) : heads) * a.slices, SEL_THREADS, lds, st>>>(a);
   *io.P_tagged = false;
   return 2;
 }
@@ -266,12 +305,13 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const long blocks = (long)heads * rows;
   if (g_one_launch < 0 && (heads > kLayerMaxHeads || (long)heads * n_att > kLayerMaxAttended ||
                            blocks > (io.host_pool ? kLayerMaxBlocksHost : kLayerMaxBlocks) || l.lds > kLdsPerUnit / 2)) return false;
-  l.grid = dim3(heads, rows);
+  const bool home = heads_at_home(d, heads, rows);
+  l.grid = dim3(home ? by_xcd(heads) : heads, rows);
   l.packed = (uint32_t)(g.L - 1) | (uint32_t)io.layer << 19;
   l.plan = (io.have_prev ? 1u : 0u) | (uint32_t)io.parity << 1 | (uint32_t)passes_log2 << 2 | (uint32_t)slices_log2 << 4 |
-           (uint32_t)n_splits << 7 | (uint32_t)pps << 13 | (io.lose_selection ? 1u << 22 : 0u) | io.impatient << 23;
+           (uint32_t)n_splits << 7 | (uint32_t)pps << 13 | (io.lose_selection ? 1u << 22 : 0u) | io.impatient << 23 | (home ? 1u << 29 : 0u);
   l.split_magic = n_splits > 1 ? 0xffffffffu / (uint32_t)n_splits + 1u : 0u;      // exact for the block counts of a layer launch
-  *io.launch_grid = (int)blocks;
+  *io.launch_grid = (int)(l.grid.x * l.grid.y);
   *io.launch_lds = l.lds;
   const int stream = stream_of(d, g);
   const auto launch = io.host_pool ? (stream & STREAM_SUMMARIES ? launch_layer_host_stream : launch_layer_host)

@@ -83,6 +83,7 @@ struct StepArgs {
   unsigned long long* keyid; // last selecting block
   unsigned long long* cmax;  // the chunks' largest weights, [heads][cmax_stride] tagged, or (where P is plain) [heads][cmax_plain_stride]
   LaunchNo no;               // of this launch
+  bool home;                 // a head's blocks are on one XCD (deal_block)
   uint32_t impatient;        // WAIT_* bits: waits that run out at once (tests)
   long long* tstamp;         // debug: 100 MHz timestamps of head 0's phases (may be null)
   unsigned long long* tagged; // if not null: [heads][k], every picked id once more as a tagged word: a block of
@@ -298,12 +299,12 @@ __device__ __forceinline__ void score_pages(const StepArgs& a, int head, int chu
   static_assert(WAVES == 8 || !TAGGED, "");
   if (soft && wave == WAVES - 1) {                        // lane 8w + g has wave w's of head g
     const float v = __uint_as_float(class_reduce<8>(__float_as_uint(s_max[lane >> 3][lane & 7]), OpMaxF32()));
-    if (lane < NG) st_tag(a.cmax + head * cmax_stride(a.max_pages) + chunk * GP + lane, __float_as_uint(v), tag);
+    if (lane < NG) st_tag(a.cmax + head * cmax_stride(a.max_pages) + chunk * GP + lane, __float_as_uint(v), tag, a.home);
   }
   const int pages_log2 = __builtin_ctz(PASS * passes), pages = 1 << pages_log2, at0 = chunk * pages;     // (powers of two)
   for (int i = threadIdx.x; i < NG * pages; i += WAVES * 64) {
     const int gg = i >> pages_log2, jj = i & (pages - 1);
-    if (at0 + jj < n) st_tag(a.P + ((size_t)head * G + gg) * a.max_pages + a.g.cand_lo + at0 + jj, __float_as_uint(s_w[gg][jj]), tag);
+    if (at0 + jj < n) st_tag(a.P + ((size_t)head * G + gg) * a.max_pages + a.g.cand_lo + at0 + jj, __float_as_uint(s_w[gg][jj]), tag, a.home);
   }
 }
 
@@ -656,16 +657,18 @@ struct PutId {
   int32_t *out, *outu, *plan_nid;
   unsigned long long* tagw;
   uint32_t tag;
+  bool home;
   __device__ __forceinline__ PutId(const StepArgs& a, int head, uint32_t* key) {
     out = a.ids + (size_t)head * a.k;
     outu = a.ids_user ? a.ids_user + (size_t)head * a.k : nullptr;
     tagw = a.tagged ? a.tagged + (size_t)head * a.k : nullptr;
     plan_nid = a.plan_new_slots ? reinterpret_cast<int32_t*>(key) + a.plan_lds_off + 4 * a.k : nullptr;
     tag = launch_tag(a.no);
+    home = a.home;
   }
   __device__ __forceinline__ void operator()(int pos, int id) const {
     if (plan_nid) { plan_nid[pos] = id; return; }
-    if (tagw) st_tag(tagw + pos, (uint32_t)id, tag);
+    if (tagw) st_tag(tagw + pos, (uint32_t)id, tag, home);
     out[pos] = id;
     if (outu) outu[pos] = id;
   }
@@ -836,8 +839,8 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     if (__builtin_expect(__ballot(z >> 47 != 0) != 0, 0)) return Selected::NOTHING;
     if (S > 1) {                                       // ... and over the slices: lane 8r + g reads slice r's, r's and r + 8's
       if (wave == 0 && lane < G) {
-        st_tag(mine + lane, (uint32_t)z, tag);
-        st_tag(mine + MAX_G + lane, (uint32_t)(z >> 32), tag);
+        st_tag(mine + lane, (uint32_t)z, tag, a.home);
+        st_tag(mine + MAX_G + lane, (uint32_t)(z >> 32), tag, a.home);
       }
       const int gl = min(lane & 7, G - 1), r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
       unsigned long long w[4];
@@ -902,7 +905,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
 #pragma unroll
     for (int u = 0; u < REGS; ++u) {
       if (u >= U) break;
-      if ((have >> u & 1u) && !failed) st_tag(keyx + id[u] - lo, key[u], tag);
+      if ((have >> u & 1u) && !failed) st_tag(keyx + id[u] - lo, key[u], tag, a.home);
     }
     store_scores();
     return failed ? Selected::NOTHING : Selected::IDS;
@@ -1006,8 +1009,8 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
       if (last) {
         put(pos, item_id[u]);
       } else {
-        st_tag(keyx + s * m + pos, item[u], tag);
-        st_tag(keyid + s * m + pos, (uint32_t)item_id[u], tag);
+        st_tag(keyx + s * m + pos, item[u], tag, a.home);
+        st_tag(keyid + s * m + pos, (uint32_t)item_id[u], tag, a.home);
       }
     });
   }
@@ -1083,7 +1086,7 @@ __device__ __forceinline__ void alone_keys(const StepArgs& a, int head, int nw, 
 #pragma unroll 1
     for (int i = tid; i < n * ng; i += nt) {
       const int gg = i / n, j = i - gg * n;
-      st_tag(a.P + base + (size_t)gg * a.max_pages + j, __float_as_uint(weight_alone<DT, G>(a, head, gg, j)), tag);
+      st_tag(a.P + base + (size_t)gg * a.max_pages + j, __float_as_uint(weight_alone<DT, G>(a, head, gg, j)), tag, a.home);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // they are where the group's waves read them
     lds_barrier();
@@ -1184,8 +1187,8 @@ __device__ __forceinline__ void select_finish(const StepArgs& hot, int head, int
     block_topk(key, last ? others + n - j0 : a.slice, kk, alone || a.sel_pool <= 1 ? kSoftBins : sm.bins, nw, sm, [&](int pos, int j) {
       const int id = j >= others ? lo + j0 + j - others : m == a.slice ? lo + j : (int)(uint32_t)ld_tag(keyid + j);
       if (last) { put(pos, id); return; }
-      st_tag(a.keyx + (size_t)head * a.max_pages + s * m + pos, key[j], tag);
-      st_tag(keyid + s * m + pos, (uint32_t)id, tag);
+      st_tag(a.keyx + (size_t)head * a.max_pages + s * m + pos, key[j], tag, a.home);
+      st_tag(keyid + s * m + pos, (uint32_t)id, tag, a.home);
     });
     if (!last) return;
   }
@@ -1203,7 +1206,7 @@ __device__ __forceinline__ void select_finish(const StepArgs& hot, int head, int
     const int32_t* nslot = plan_sm + 5 * k;
     for (int i = tid; i < k; i += SEL_THREADS) {
       const int id = put.plan_nid[i], sl = nslot[i];
-      if (put.tagw) st_tag(put.tagw + i, tagged_pick(id, sl & (TAGGED_MAX_SLOTS - 1), (sl & PLAN_MISS_BIT) != 0), tag);
+      if (put.tagw) st_tag(put.tagw + i, tagged_pick(id, sl & (TAGGED_MAX_SLOTS - 1), (sl & PLAN_MISS_BIT) != 0), tag, a.home);
       put.out[i] = id;
       if (put.outu) put.outu[i] = id;
     }
@@ -1213,12 +1216,21 @@ __device__ __forceinline__ void select_finish(const StepArgs& hot, int head, int
 
 // ---------------------------------------------------------------------------------
 // role dispatch of one block: row y of the grid counts [append][correction test][scoring ...][selection ...], each
-// present only if its role bit is set; x is the KV head, except that the selection's blocks are numbered through row by
-// row so that a head's are adjacent (they wait for each other: in block order, at most one head's are ever half there).
+// present only if its role bit is set; x is the KV head -- at home, the grid is a multiple of 8 wide -- except that the
+// selection's blocks are numbered through row by row and dealt to the heads (deal_block; they wait for each other).
 // ---------------------------------------------------------------------------------
 // select(head, slice): what a selecting block does.
 template <int DT, int G, bool PAST, typename Select>
 __device__ __forceinline__ void step_roles(const StepArgs& a, int x, int y, Select select) {
+  const int others = (a.roles & ROLE_APPEND ? 1 : 0) + (a.roles & ROLE_CORR ? 1 : 0);
+  if (y >= others + a.chunks) {
+    const int wide = a.home ? (a.heads + 7) & ~7 : a.heads;
+    int head, s;
+    deal_block((uint32_t)((y - others - a.chunks) * wide + x), a.slices, a.home, [&](uint32_t j) { return j >> a.slices_log2; }, head, s);
+    if (head < a.heads) select(head, s);
+    return;
+  }
+  if (x >= a.heads) return;
   if (a.roles & ROLE_APPEND) {
     if (y == 0) { append_role<DT>(a, x); return; }
     y -= 1;
@@ -1227,14 +1239,9 @@ __device__ __forceinline__ void step_roles(const StepArgs& a, int x, int y, Sele
     if (y == 0) { corr_role<DT, G>(a, x); return; }
     y -= 1;
   }
-  if (y < a.chunks) {
-    if (y == 0) FKV_STAMP(a, x, 0);
-    score_role<DT, G, true, STEP_WAVES, PAST>(a, x, y);
-    if (y == 0) FKV_STAMP(a, x, 1);
-    return;
-  }
-  const int i = (y - a.chunks) * a.heads + x;
-  select(i >> a.slices_log2, i & (a.slices - 1));
+  if (y == 0) FKV_STAMP(a, x, 0);
+  score_role<DT, G, true, STEP_WAVES, PAST>(a, x, y);
+  if (y == 0) FKV_STAMP(a, x, 1);
 }
 
 }  // namespace fkv

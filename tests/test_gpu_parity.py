@@ -684,6 +684,36 @@ def test_many_requests_take_the_bandwidth_bound_dispatch():
     pr.close()
 
 
+@pytest.mark.parametrize("batch,n_q,n_kv,ctx,placement", [
+    (1, 4, 1, 3000, 0),        # one head: one of the 8 XCDs has work
+    (3, 9, 3, 9000, 0),        # nine: the second round of heads has one
+    (3, 9, 3, 6000, 1),
+    (2, 16, 8, 40000, 0),      # two heads on each, every exchange of theirs at home
+    (1, 8, 2, 70000, 0),       # two heads, more blocks than one XCD runs at once: words through memory
+    (5, 20, 20, 3000, 0),      # a hundred: the same
+])
+def test_heads_dealt_to_the_xcds(batch, n_q, n_kv, ctx, placement):
+    """Every way the heads can be dealt to the XCDs, in the one-launch layer-step and in the primitives' launches."""
+    wl = W.Workload("xcds", 1, batch, n_q, n_kv, "bf16", ctx, 1024, 64, 64, 0.8, 4, 0.8, 0.6, 83, placement=placement)
+    pr = _pair(wl, [0])
+    for t in range(wl.steps - 1):
+        pr.step(0, t, deep=t == 0)
+    assert pr.g.step_launches(0) == 1
+    assert 0 < pr.stats["flagged"]
+    if placement == 0:
+        t = wl.steps - 1
+        q, k, v = pr.step_inputs(0, t)
+        pr.g.kv_append(0, k, v)
+        pr.g.corr_check(0, q)
+        pr.g.page_select(0, q)
+        pr.g.sparse_decode_attn(0, q, pr.out, use=2)
+        pr.g.commit(0)
+        res = [pr.oracles[(0, r)].step(pr.q[(0, r)][0][t], pr.kd[(0, r)][0][t], pr.vd[(0, r)][0][t]) for r in range(batch)]
+        pr.compare(0, t, res, pr.read_step(0, True), True)
+    pr.g.health(0)
+    pr.close()
+
+
 def test_big_scan_blocks_take_several_chunks():
     """24 requests x 16 KV heads x 12K tokens: scoring in a launch of its own, several blocks of 64 pages per head."""
     wl = W.Workload("scan", 1, 24, 16, 16, "bf16", 12000, 1024, 64, 64, 0.8, 3, 0.8, 0.6, 71)
