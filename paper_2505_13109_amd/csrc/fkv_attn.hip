@@ -53,8 +53,8 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   a.pd = pd; a.q = io.q; a.act_ids = io.act_ids; a.new_ids = io.new_ids; a.act_slots = io.act_slots; a.new_slots = io.new_slots;
   a.flags = io.flags; a.use = io.use; a.part = io.part; a.part_ml = io.part_ml; a.max_splits = io.max_splits;
   a.no = io.no; a.impatient = io.impatient;
-  a.pps = attn_pages_per_block(n_att, heads, io.max_splits, 4);
-  a.n_splits = (n_att + a.pps - 1) / a.pps;
+  const int pps = attn_pages_per_block(n_att, heads, io.max_splits, 4);
+  a.n_splits = (n_att + pps - 1) / pps;
   a.share = (d.G * D + a.n_splits - 1) / a.n_splits;
   a.out = io.out; a.g = g; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k; a.status = io.status; a.tstamp = io.tstamp;
   a.heads = heads;

@@ -18,8 +18,8 @@ namespace fkv {
 // ---------------------------------------------------------------------------------
 typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // (scalar loads)
 
-// packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), pages per
-// split (9), lose_selection, WAIT_* bits (6), at home;   split_magic: 2^32 / splits rounded up, 0 for one split
+// packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), 9 bits
+// of nothing, lose_selection, WAIT_* bits (6), at home;   split_magic: 2^32 / splits rounded up, 0 for one split
 struct LayerKernelArgs {                     // the kernel's arguments, in their order
   const LayerConst* consts;
   const uint16_t *q, *k_new, *v_new;
@@ -100,7 +100,7 @@ struct LayerSetup {
     a.act_ids = ids(before); a.new_ids = nullptr;
     a.act_slots = HOSTPOOL ? slots(before) : nullptr; a.new_slots = nullptr;
     a.flags = nullptr; a.use = 2; a.part = c->part; a.part_ml = c->part_ml; a.max_splits = c->max_splits;
-    a.n_splits = (int)(ka.plan >> 7) & 63; a.pps = (int)(ka.plan >> 13) & 511;
+    a.n_splits = (int)(ka.plan >> 7) & 63;
     a.share = ka.split_magic ? (int)__umulhi((uint32_t)(G * D + a.n_splits - 1), ka.split_magic) : G * D;
     a.no = LaunchNo{}; a.out = ka.out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
     a.status = reinterpret_cast<int*>(at(c->o_status)); a.tstamp = c->tstamp;

@@ -292,7 +292,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const int waiting = slices > 1 ? kMaxWaiting - heads * slices : half ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting;
   const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, waiting);
   const int n_splits = (n_att + pps - 1) / pps;
-  if (n_splits > 63 || pps > 511) return false;
+  if (n_splits > 63 || pps > 64 * STEP_WAVES) return false;
   const int passes = scoring_passes(d, g, slices, n_splits, kLayerResident);
   const int passes_log2 = passes == 4 ? 2 : passes == 2 ? 1 : 0;
   int slices_log2 = 0;
@@ -309,7 +309,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   l.grid = dim3(home ? by_xcd(heads) : heads, rows);
   l.packed = (uint32_t)(g.L - 1) | (uint32_t)io.layer << 19;
   l.plan = (io.have_prev ? 1u : 0u) | (uint32_t)io.parity << 1 | (uint32_t)passes_log2 << 2 | (uint32_t)slices_log2 << 4 |
-           (uint32_t)n_splits << 7 | (uint32_t)pps << 13 | (io.lose_selection ? 1u << 22 : 0u) | io.impatient << 23 | (home ? 1u << 29 : 0u);
+           (uint32_t)n_splits << 7 | (io.lose_selection ? 1u << 22 : 0u) | io.impatient << 23 | (home ? 1u << 29 : 0u);
   l.split_magic = n_splits > 1 ? 0xffffffffu / (uint32_t)n_splits + 1u : 0u;      // exact for the block counts of a layer launch
   *io.launch_grid = (int)(l.grid.x * l.grid.y);
   *io.launch_lds = l.lds;
