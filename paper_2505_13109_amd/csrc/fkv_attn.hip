@@ -33,8 +33,9 @@ int attn_pages_per_block(int n_att, int heads, int max_splits, int nw, int max_b
   while ((n_att + pps - 1) / pps > 32 && (long)heads * ((n_att + pps * 2 - 1) / (pps * 2)) >= 128 && pps < most) pps *= 2;
   // With many heads the launch is bandwidth-bound and what counts is the fixed cost of a block
   // (its partial, the exchange, the merge): measured best at about one block per compute unit,
-  // down to one block per head.
-  while (pps < n_att && pps < most && (long)heads * ((n_att + pps * 2 - 1) / (pps * 2)) >= 256) pps *= 2;
+  // down to one block per head; in the one-launch layer-step at two, where launch_layer lets it.
+  const int enough = std::max(kComputeUnits, max_blocks);
+  while (pps < n_att && pps < most && (long)heads * ((n_att + pps * 2 - 1) / (pps * 2)) >= enough) pps *= 2;
   // (4-wave blocks fit four to a unit; of long lists, one block to a unit streams better: 248 heads of 129 pages 117.7 us in one
   // split, 120.6 in two)
   if (nw == 4 && n_att <= 96) max_blocks *= 2;

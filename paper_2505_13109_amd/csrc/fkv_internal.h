@@ -202,7 +202,8 @@ static bool grant_lds(F* fn, size_t lds, size_t& granted) {
 
 constexpr int kComputeUnits = 256;
 // Most blocks of a launch that wait for each other (a head's attention blocks, and its selecting blocks where it has several):
-// half of those that fit (two to a compute unit).  That keeps waits short: in block order at most one head's blocks are half
+// half of those that fit (two to a compute unit), and all of them where there is something to be had by that (launch_layer).  That
+// keeps waits short: in block order at most one head's blocks are half
 // there, so a launch by itself gets on, and two at once mostly do.  It is not what makes them end: with more launches on the
 // machine, or another program's, a block may wait for one that cannot start, and goes on by itself (PATIENCE).
 constexpr int kMaxWaiting = kComputeUnits;

@@ -269,6 +269,7 @@ int launch_step(const Dims& d, int roles, const StepIO& io, Geom g, hipStream_t 
 // 64 against 70; 248 x 129: 133 against 117).  With the KV in a host pool the link decides early: 64 heads of 16K tokens
 // 241 against 243, 32 of 124K 183 against 183, so the bigger ones take the gather of its own.
 constexpr int kLayerMaxHeads = kComputeUnits - 1;
+constexpr int kShortStream = 96, kLooseBlocks = 192, kPagesEach = 16, kEnoughToCut = 40, kManyScored = 240, kFewAlone = 176;
 constexpr long kLayerMaxAttended = 24576, kLayerMaxBlocks = 2560, kLayerMaxBlocksHost = 1024;
 
 constexpr int kMaxLayersPacked = 1 << 13, kMaxCtxPacked = 1 << 19;
@@ -290,14 +291,36 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   // (9 and 5) 160 and 168.
   const bool half = g.n_cand > kLongList && heads > kFewHeads;
   const int waiting = slices > 1 ? kMaxWaiting - heads * slices : half ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting;
-  const int pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, waiting);
-  const int n_splits = (n_att + pps - 1) / pps;
+  int pps, n_splits, passes, rows;
+  auto cut = [&](int max_blocks) {
+    pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, max_blocks);
+    n_splits = (n_att + pps - 1) / pps;
+    passes = scoring_passes(d, g, slices, n_splits, kLayerResident);
+    rows = 2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + n_splits;
+  };
+  cut(waiting);
+  // As many blocks as fit, two to a compute unit, where the heads are many: with fewer, the dispatcher puts two on some units and
+  // none on others, according to which scoring blocks have just ended, and those of a launch that is bound by its bytes take
+  // that much longer.  G = 4, 65 pages, up to 256 blocks and up to 512: 64 heads 23.0 and 21.6 us, 96 33.3 and 30.0, 128 39.9 and
+  // 35.4, 160 50.7 and 39.4, 240 (G = 7) 82.7 and 69.7; where most heads are corrected 25.1 and 24.7, 33.7 and 34.6, 39.6 and 40.6,
+  // 50.8 and 42.8, 82.4 and 69.2.  Long streams of pages do better in few blocks as long as each has a unit of its own (129
+  // pages: 96 heads, 192 blocks and 480, 42.3 and 47.5, most corrected), but not where that is just missed (112 heads, 224 and 448:
+  // 59.7 and 48.0, 59.4 and 52.4; 80 heads, 240 and 480: 43.9 and 36.2, 46.2 and 41.9).  Over a host link nothing is gained.  And a
+  // block is to have pages enough for what it costs by itself (168 heads x 33 pages, one block and two, 23.1 and 24.4 us, 200 29.3
+  // and 31.3).  Heads of one block each that many scoring blocks come before find units to themselves as long as they are few
+  // (one block and three: 136 heads x 344 candidates 34.5 and 36.7, 168 42.0 and 43.7; but 160 x 218 47.5 and 39.8, 168 x 187 49.3
+  // and 40.9, and 224 x 468, one and two, 71.8 and 61.4).
+  const int blocks_now = heads * n_splits;
+  const bool loose = n_splits == 1 && g.n_cand > kManyScored && blocks_now <= kFewAlone;
+  const bool cut_finer = n_att <= kShortStream ? n_att >= kEnoughToCut && !loose : blocks_now > kLooseBlocks && blocks_now < kComputeUnits;
+  if (slices == 1 && !half && !io.host_pool && cut_finer) {
+    cut(std::min(kLayerResident, heads * std::max(n_splits, n_att / kPagesEach)));
+    if ((long)heads * rows > kLayerMaxBlocks) cut(waiting);
+  }
   if (n_splits > 63 || pps > 64 * STEP_WAVES) return false;
-  const int passes = scoring_passes(d, g, slices, n_splits, kLayerResident);
   const int passes_log2 = passes == 4 ? 2 : passes == 2 ? 1 : 0;
   int slices_log2 = 0;
   while ((1 << slices_log2) < slices) slices_log2 += 1;
-  const int rows = 2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + n_splits;
   LayerLaunch l;
   l.lds = (size_t)select_key_words(g.n_cand) * sizeof(uint32_t) + (io.host_pool ? plan_lds_ints(d.k) * sizeof(int32_t) : 0);
   const size_t lds_attn = (size_t)attn_lds_floats(STEP_WAVES, d.G) * sizeof(float);
