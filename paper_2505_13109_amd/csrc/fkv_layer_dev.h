@@ -107,16 +107,17 @@ struct LayerSetup {
     a.q_prev = qprev(before); a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
     a.k_new = ka.k_new; a.v_new = ka.v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.tag = tag; a.pick_tag = tag + ((ka.plan >> 22) & 1u ? 2u : 0u);
-    a.impatient = ka.plan >> 23 & 63u; a.home = home; a.split_magic = ka.split_magic;
+    a.impatient = ka.plan >> 23 & 63u; a.home = home; a.at_once = slices_log2 == 0; a.split_magic = ka.split_magic;
     a.host_pool = HOSTPOOL ? reinterpret_cast<const uint16_t*>(c->host_base + c->host_layer_bytes * (unsigned long long)layer) : nullptr;
     a.max_pages = c->max_pages;
     return a;
   }
 };
 
-// STREAM: STREAM_* bits
+// STREAM: STREAM_* bits.  Four waves to a SIMD, no more and no fewer: with only the lower limit the compiler schedules for more
+// and leaves a slot of scratch memory, that nobody reads or writes, to kernels of G = 7 and 8, which costs each launch 0.9 us.
 template <int DT, int G, bool HOSTPOOL, int STREAM>
-__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
                   uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];

@@ -714,6 +714,27 @@ def test_heads_dealt_to_the_xcds(batch, n_q, n_kv, ctx, placement):
     pr.close()
 
 
+@pytest.mark.parametrize("batch,n_q,n_kv,ctx,budget", [
+    (8, 16, 8, 2527, 1248),    # 64 heads: 39 pages and the open one (none after the first step), cut as for a block a unit
+    (8, 16, 8, 2527, 1280),    # one more: as many blocks as fit
+    (7, 56, 8, 1300, 3040),    # 56 heads, G = 7, fewer pages than the budget has room for
+    (31, 8, 8, 2527, 2048),    # 248 heads: two blocks each
+    (10, 8, 8, 4200, 3072),    # 80 heads of 97 pages: three blocks each would just miss a unit each
+    (12, 8, 8, 4200, 3072),    # 96: two blocks each
+    (17, 8, 8, 7900, 2048),    # 136 heads behind many scoring blocks: one block each
+])
+def test_heads_cut_into_blocks(batch, n_q, n_kv, ctx, budget):
+    """Every way attention of many heads is cut in the one-launch layer-step, with corrected heads among them."""
+    wl = W.Workload("cut", 1, batch, n_q, n_kv, "bf16", ctx, budget, 64, 96, 0.8, 3, 0.8, 0.6, 91)
+    pr = _pair(wl, [0])
+    for t in range(wl.steps):
+        pr.step(0, t)
+        assert pr.g.step_launches(0) == 1
+    assert 0 < pr.stats["flagged"] < pr.stats["heads"]
+    pr.g.health(0)
+    pr.close()
+
+
 def test_big_scan_blocks_take_several_chunks():
     """24 requests x 16 KV heads x 12K tokens: scoring in a launch of its own, several blocks of 64 pages per head."""
     wl = W.Workload("scan", 1, 24, 16, 16, "bf16", 12000, 1024, 64, 64, 0.8, 3, 0.8, 0.6, 71)
