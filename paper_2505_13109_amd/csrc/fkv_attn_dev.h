@@ -103,6 +103,7 @@ struct AttnArgs {
   unsigned long long* part;  // [heads][max_splits][G][D] tagged partial outputs, then [heads][max_splits][G][2] tagged (max, sum)
   unsigned long long* part_ml;
   int max_splits, n_splits;
+  int pps;                   // fused, KV in a host pool: positions of a block
   int share;                 // outputs of a head that each of its blocks finishes
   bool home;                 // a head's blocks are on one XCD (deal_block)
   uint32_t split_magic;      // stand-alone attention: 2^32 / n_splits rounded up, 0 for one split
@@ -231,7 +232,9 @@ __device__ __forceinline__ float output_alone(const AttnArgs& a, int head, bool 
 // what can be attended at once and of what has to wait for the ids; with runs those of the picked pages alone had nothing to do
 // until the ids came and all the work after that.  Layer-steps where most heads are corrected, runs against this: 8 heads of 65
 // pages 10.9 and 10.1 us, 4 heads (G = 7) 10.7 and 10.2, 48 22.7 and 21.1, 112 40.7 and 36.8, 96 of 129 pages 47.1 and 43.3;
-// where few are, the same to 1 % less.  `lds`: attn_lds_floats(NW, G) floats, 16-byte aligned.
+// where few are, the same to 1 % less.  With the KV in a host pool the link decides, and blocks have runs: the corrected heads' missing
+// pages are then fetched by as few waves at once as it takes to fill it (8 heads x 32 missing pages, 1286 us and, in turn, 1292 with
+// the load ahead of it).  `lds`: attn_lds_floats(NW, G) floats, 16-byte aligned.
 // FUSED: in a launch with the step roles; HOSTFUSED: that, with the KV in a host pool (compile-time choices: what they
 // add to the page loop would cost the other launches registers).  PAST: pages are read past the caches (STREAM_PAGES; as a branch
 // around the loads it costs short launches 2 to 3 %).
@@ -272,7 +275,8 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   // ---- what the wave attends: lane l looks up its (l)-th position, one load for all of them ----
   const int n_att = g.n_sink + k + g.n_win + (g.r > 0 ? 1 : 0);
   const int pk_lo = g.n_sink, pk_hi = g.n_sink + k;
-  const int p = split + (wave + lane * NW) * a.n_splits;        // (a wave has at most 64 positions: attn_pages_per_block)
+  const int nth = wave + lane * NW;                     // (a wave has at most 64 positions: attn_pages_per_block)
+  const int p = HOSTFUSED ? (nth < a.pps ? split * a.pps + nth : n_att) : split + nth * a.n_splits;
   const bool picked = p >= pk_lo && p < pk_hi;
   int page_l, unit_l;
   page_l = unit_l = -1;
@@ -502,7 +506,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
     // Wait for this step's ids of the positions: the selection writes every picked id as one tagged 64-bit word.
     // The blocks that make it have lower block indices than any attention block, so that as a rule they are running or
     // done.
-    const int at = split + (wave + (thread_id(wave) & 63) * NW) * a.n_splits - pk_lo;
+    const int its = wave + (thread_id(wave) & 63) * NW, at = (HOSTFUSED ? split * a.pps + its : split + its * a.n_splits) - pk_lo;
     const unsigned long long* word = a.tagged + (size_t)head * k + (picked ? at : 0);
     unsigned long long w = 0;
     for (int it = 0;; ++it) {
@@ -677,9 +681,9 @@ __device__ __forceinline__ void attn_finish(const AttnArgs& a, int split, int he
     lds_barrier();
   }
   if (HOSTFUSED && left.split) {                        // the recall of the block's missing pages, as in attend_page
-    const int lo = a.g.n_sink, hi = lo + a.k;
+    const int lo = a.g.n_sink, hi = min(lo + a.k, (split + 1) * a.pps);
 #pragma unroll 1
-    for (int p = lo + (split - lo % a.n_splits + a.n_splits) % a.n_splits; p < hi; p += a.n_splits) {
+    for (int p = max(split * a.pps, lo); p < hi; ++p) {
       const unsigned long long w = ld_tag(a.tagged + (size_t)head * a.k + p - lo);
       int page, slot;
       bool miss;

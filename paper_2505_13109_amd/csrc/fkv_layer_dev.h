@@ -18,8 +18,8 @@ namespace fkv {
 // ---------------------------------------------------------------------------------
 typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // (scalar loads)
 
-// packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), 9 bits
-// of nothing, lose_selection, WAIT_* bits (6), at home;   split_magic: 2^32 / splits rounded up, 0 for one split
+// packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), 9 unused
+// bits, lose_selection, WAIT_* bits (6), at home;   split_magic: 2^32 / splits rounded up, 0 for one split
 struct LayerKernelArgs {                     // the kernel's arguments, in their order
   const LayerConst* consts;
   const uint16_t *q, *k_new, *v_new;
@@ -102,6 +102,8 @@ struct LayerSetup {
     a.flags = nullptr; a.use = 2; a.part = c->part; a.part_ml = c->part_ml; a.max_splits = c->max_splits;
     a.n_splits = (int)(ka.plan >> 7) & 63;
     a.share = ka.split_magic ? (int)__umulhi((uint32_t)(G * D + a.n_splits - 1), ka.split_magic) : G * D;
+    const int n_att = g.n_sink + c->k + g.n_win + (g.r > 0 ? 1 : 0);
+    a.pps = ka.split_magic ? (int)__umulhi((uint32_t)(n_att + a.n_splits - 1), ka.split_magic) : n_att;
     a.no = LaunchNo{}; a.out = ka.out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
     a.status = reinterpret_cast<int*>(at(c->o_status)); a.tstamp = c->tstamp;
     a.q_prev = qprev(before); a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
