@@ -428,14 +428,14 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   // 11.4, most corrected 14.8 and 13.7; 8 heads of 65 8.8 and 8.6; 112 of 65, most corrected, 37.2 and 32.7.)
   const unsigned long long known = __ballot(unit_l >= 0);
   int i0 = known ? (int)__builtin_ctzll(known) : -1;
-  const bool at_once = !FUSED || a.at_once;
+  const bool at_once = FUSED && a.at_once;
   if (at_once && i0 >= 0) load_k(source(i0));
   if (FUSED && picked) {
     page_l = id_l;
     if (page_l >= 0) unit_l = pd.placement == 0 ? page_l : pd.sel_base + slot_l;
   }
   const unsigned long long listed = FUSED ? __ballot(unit_l >= 0) : known;
-  if (i0 < 0 && listed) i0 = (int)__builtin_ctzll(listed);
+  if (FUSED && i0 < 0 && listed) i0 = (int)__builtin_ctzll(listed);
   const char* const up0 = source(i0 >= 0 ? i0 : 0);
   if (!(at_once && known) && i0 >= 0) load_k(up0);
   if (FUSED && wave == 0) s_no_ids = 0;
