@@ -313,7 +313,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const int blocks_now = heads * n_splits;
   const bool loose = n_splits == 1 && g.n_cand > kManyScored && blocks_now <= kFewAlone;
   const bool cut_finer = n_att <= kShortStream ? n_att >= kEnoughToCut && !loose : blocks_now > kLooseBlocks && blocks_now < kComputeUnits;
-  if (slices == 1 && !half && !io.host_pool && cut_finer) {
+  if (slices == 1 && g.n_cand < kLongList && !io.host_pool && cut_finer) {
     cut(std::min(kLayerResident, heads * std::max(n_splits, n_att / kPagesEach)));
     if ((long)heads * rows > kLayerMaxBlocks) cut(waiting);
   }
