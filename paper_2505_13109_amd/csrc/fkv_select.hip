@@ -132,13 +132,18 @@ __global__ void where_kernel(uint32_t* where) {
 }
 bool blocks_by_xcd(uint32_t* where) {
   uint32_t at[kWhereBlocks];
-  where_kernel<<<kWhereBlocks, 64>>>(where);
-  if (hipMemcpy(at, where, sizeof(at), hipMemcpyDeviceToHost) != hipSuccess) {
+  hipError_t e = hipMemset(where, 0xff, sizeof(at));               // (no XCD's number: what stays so was not written)
+  if (e == hipSuccess) {
+    where_kernel<<<kWhereBlocks, 64>>>(where);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipMemcpy(at, where, sizeof(at), hipMemcpyDeviceToHost);
+  if (e != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  for (int i = kXcds; i < kWhereBlocks; ++i)
-    if (at[i] != at[i % kXcds]) return false;
+  for (int i = 0; i < kWhereBlocks; ++i)
+    if (at[i] == 0xffffffffu || at[i] != at[i % kXcds]) return false;
   return true;
 }
 

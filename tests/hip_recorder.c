@@ -4,6 +4,8 @@
  *   record <event> <stream> <captured>
  *   wait   <event> <stream> <captured>
  *   sync
+ * Device memory is not modelled, except for what the library asks its device about where blocks run: rec_where() says what a launch of
+ * where_kernel leaves there.
  * A stream is captured from rec_capture on, or from a wait for an event that was recorded in the capture (streams join a capture
  * that way); rec_end_capture ends it for all of them.  As in the runtime, the stop event of a launch that is captured is no
  * node of the capture. */
@@ -33,6 +35,10 @@ static int is_captured(void* s) {
 void rec_capture(void* s) { if (!is_captured(s)) captured[n_captured++] = s; }
 void rec_end_capture(void) { n_captured = 0; n_captures += 1; }
 const char* rec_log(void) { return log_text; }
+
+/* what where_kernel does: 0 writes block numbers modulo 8, 1 other numbers, 2 is refused, 3 writes nothing */
+static int where_mode, where_ran, where_fill, last_error;
+void rec_where(int mode) { where_mode = mode; }
 
 static const char* name_of(const void* stub) {
   for (int i = 0; i < n_stubs; ++i)
@@ -65,6 +71,10 @@ int __hipPopCallConfiguration(dim3_t* grid, dim3_t* block, size_t* lds, void** s
 }
 int hipLaunchKernel(const void* stub, dim3_t grid, dim3_t block, void** args, size_t lds, void* stream) {
   (void)block; (void)args; (void)lds;
+  if (strstr(name_of(stub), "where_kernel")) {
+    if (where_mode == 2) return last_error = 98;
+    where_ran = where_mode != 3;
+  }
   launched(stub, grid, stream, NULL);
   return 0;
 }
@@ -99,13 +109,19 @@ int hipStreamSynchronize(void* s) { (void)s; LOG("sync\n"); return 0; }
 int hipDeviceSynchronize(void) { LOG("sync\n"); return 0; }
 int hipEventElapsedTime(float* ms, void* a, void* b) { (void)a; (void)b; *ms = 0; return 0; }
 
-int hipMemcpy(void* d, const void* s, size_t n, int kind) { (void)d; (void)s; (void)n; (void)kind; return 0; }
+int hipMemcpy(void* d, const void* s, size_t n, int kind) {
+  (void)s;
+  if (kind != 2) return 0;
+  memset(d, where_fill, n);
+  for (size_t i = 0; where_ran && i < n / 4; ++i) ((unsigned*)d)[i] = (unsigned)(where_mode == 1 ? i / 2 % 8 : i % 8);
+  return 0;
+}
 int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void* st) { (void)d; (void)s; (void)n; (void)kind; (void)st; return 0; }
-int hipMemset(void* d, int v, size_t n) { (void)d; (void)v; (void)n; return 0; }
+int hipMemset(void* d, int v, size_t n) { (void)d; (void)n; where_fill = v; return 0; }
 int hipMemsetAsync(void* d, int v, size_t n, void* st) { (void)d; (void)v; (void)n; (void)st; return 0; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int* v, int attr, int dev) { (void)attr; (void)dev; *v = 160 * 1024; return 0; }
 int hipFuncSetAttribute(const void* f, int attr, int v) { (void)f; (void)attr; (void)v; return 0; }
 int hipGetSymbolAddress(void** p, const void* symbol) { (void)symbol; *p = (void*)0x1000; return 0; }
-int hipGetLastError(void) { return 0; }
+int hipGetLastError(void) { const int e = last_error; last_error = 0; return e; }
 const char* hipGetErrorString(int e) { (void)e; return "recorded"; }
