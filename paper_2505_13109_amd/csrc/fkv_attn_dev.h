@@ -227,8 +227,7 @@ __device__ __forceinline__ float output_alone(const AttnArgs& a, int head, bool 
   return o / den;
 }
 
-// One block of NW wavefronts: every n_splits-th attend-list position of `head` from `split` on, of which wave w takes the w-th,
-// (w+NW)-th, ...  Dealt like that, and not a run of positions to each block, every block of a corrected head has its share of
+// One block of NW wavefronts: every n_splits-th attend-list position of `head` from `split` on (nth_position, nth_of_wave).  Dealt like that, and not a run of positions to each block, every block of a corrected head has its share of
 // what can be attended at once and of what has to wait for the ids; with runs those of the picked pages alone had nothing to do
 // until the ids came and all the work after that.  Layer-steps where most heads are corrected, runs against this: 8 heads of 65
 // pages 10.9 and 10.1 us, 4 heads (G = 7) 10.7 and 10.2, 48 22.7 and 21.1, 112 40.7 and 36.8, 96 of 129 pages 47.1 and 43.3;
@@ -275,8 +274,14 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   // ---- what the wave attends: lane l looks up its (l)-th position, one load for all of them ----
   const int n_att = g.n_sink + k + g.n_win + (g.r > 0 ? 1 : 0);
   const int pk_lo = g.n_sink, pk_hi = g.n_sink + k;
-  const int nth = wave + lane * NW;                     // (a wave has at most 64 positions: attn_pages_per_block)
-  const int p = HOSTFUSED ? (nth < a.pps ? split * a.pps + nth : n_att) : split + nth * a.n_splits;
+  auto position = [&](int ln) {                         // lane ln's (a wave has at most 64: attn_pages_per_block)
+    if (HOSTFUSED) {
+      const int nth = wave + ln * NW;
+      return nth < a.pps ? split * a.pps + nth : n_att;
+    }
+    return nth_position(split + nth_of_wave(wave, ln, NW) * a.n_splits, n_att);
+  };
+  const int p = position(lane);
   const bool picked = p >= pk_lo && p < pk_hi;
   int page_l, unit_l;
   page_l = unit_l = -1;
@@ -506,7 +511,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
     // Wait for this step's ids of the positions: the selection writes every picked id as one tagged 64-bit word.
     // The blocks that make it have lower block indices than any attention block, so that as a rule they are running or
     // done.
-    const int its = wave + (thread_id(wave) & 63) * NW, at = (HOSTFUSED ? split * a.pps + its : split + its * a.n_splits) - pk_lo;
+    const int at = position(thread_id(wave) & 63) - pk_lo;
     const unsigned long long* word = a.tagged + (size_t)head * k + (picked ? at : 0);
     unsigned long long w = 0;
     for (int it = 0;; ++it) {

@@ -50,6 +50,16 @@ __host__ __device__ inline Geom geom_of(int L, int n_sink, int n_win, int k) {  
   return g;
 }
 
+// The attend-list positions that a head's blocks have where they are dealt to them in turn: block `split` of n_splits the split-th,
+// then every n_splits-th, in the order that nth_position counts; wave w of NW takes in lane 0 the one that nth_of_wave names, in lane 1
+// another, and so on.  The last position comes first: it is the open page, whose wave also takes in the step's new token, and lane 0 deals
+// from the last wave down, so that this wave is the one that gets a second page last.  (With the open page where its number puts
+// it, it was a wave's second page wherever a block has nine to eleven: 20 heads of 129 pages x 992 candidates 14.5 us a layer-step, so
+// 13.9; 32 of 65 13.3 and 12.6; 76 of 33 x 480 18.6 and 17.7; where most heads are corrected, 20.2 and 20.1, 18.5 and 18.5, 21.9 and
+// 21.5, but 64 of 33 x 992 20.6 and 21.1.)
+__host__ __device__ inline int nth_of_wave(int wave, int lane, int n_waves) { return lane == 0 ? n_waves - 1 - wave : wave + lane * n_waves; }
+__host__ __device__ inline int nth_position(int nth, int n_att) { return nth == 0 ? n_att - 1 : nth < n_att ? nth - 1 : n_att; }      // (n_att: none)
+
 // Where a KV head's pages live in HBM.  Unit u of head (b, m) starts at
 // pool + ((b * n_kv + m) * units_per_head + u) * UNIT_ELEMS.
 struct PoolDesc {
