@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfreekv.so")
-SOURCES = ["fkv_api.hip", "fkv_data.hip", "fkv_select.hip", "fkv_attn.hip",
+SOURCES = ["fkv_api.hip", "fkv_data.hip", "fkv_select.hip", "fkv_attn.hip", "fkv_step.hip", "fkv_step_home.hip",
            "fkv_layer_hbm.hip", "fkv_layer_hbm_stream.hip", "fkv_layer_hbm_past.hip", "fkv_layer_host.hip", "fkv_layer_host_stream.hip"]
 
 # -ffp-contract=off: the arithmetic that decides page ids is written operation by operation.

@@ -106,7 +106,6 @@ struct AttnArgs {
   int pps;                   // fused, KV in a host pool: positions of a block
   int share;                 // outputs of a head that each of its blocks finishes
   bool home;                 // a head's blocks are on one XCD (deal_block)
-  uint32_t split_magic;      // stand-alone attention: 2^32 / n_splits rounded up, 0 for one split
   LaunchNo no;               // stand-alone attention: of this launch
   float* out;
   Geom g;

@@ -192,7 +192,7 @@ struct LayerIO {
 bool launch_floor(int grid, size_t lds, int reps, hipStream_t st);
 bool launch_layer(const Dims& d, const LayerIO& lio, Geom g, hipStream_t st);
 // how launch_layer has it launched, by the file that has the variant
-struct LayerLaunch { dim3 grid; size_t lds; uint32_t packed, plan, split_magic; };
+struct LayerLaunch { dim3 grid; bool home; size_t lds; uint32_t packed, plan, split_magic; };
 bool launch_layer_hbm(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
 bool launch_layer_hbm_stream(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
 bool launch_layer_hbm_past(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);

@@ -19,7 +19,7 @@ namespace fkv {
 typedef const __attribute__((address_space(4))) LayerConst* LayerConstPtr;   // (scalar loads)
 
 // packed: L - 1 (19 bits) | layer (13);   plan: have_prev, parity, passes log2 (2), slices log2 (3), splits (6), 9 unused
-// bits, lose_selection, WAIT_* bits (6), at home;   split_magic: 2^32 / splits rounded up, 0 for one split
+// bits, lose_selection, WAIT_* bits (6);   split_magic: 2^32 / splits rounded up, 0 for one split
 struct LayerKernelArgs {                     // the kernel's arguments, in their order
   const LayerConst* consts;
   const uint16_t *q, *k_new, *v_new;
@@ -28,7 +28,7 @@ struct LayerKernelArgs {                     // the kernel's arguments, in their
 };
 
 // what every block works out from the constants
-template <bool HOSTPOOL>
+template <bool HOSTPOOL, bool HOME>
 struct LayerSetup {
   LayerConstPtr c;
   char* base;
@@ -37,14 +37,13 @@ struct LayerSetup {
   Geom g;
   uint32_t tag;
   PoolDesc pd;
-  bool home;
+  static constexpr bool home = HOME;
   int layer, now, before, chunks, passes_log2, slices_log2, slices, step_rows;      // now, before: halves (PENDING / staged, ACTIVE / previous)
   __device__ __forceinline__ explicit LayerSetup(const LayerKernelArgs& ka) {
     c = (LayerConstPtr)ka.consts;
     layer = (int)(ka.packed >> 19);
     now = (int)(ka.plan >> 1) & 1;
     before = now ^ 1;
-    home = (ka.plan >> 29 & 1u) != 0;
     base = c->dev_base + c->layer_bytes * (unsigned long long)layer;
     g = geom_of((int)(ka.packed & 0x7ffffu) + 1, c->n_sink, c->n_win, c->k);
     tag = ka.host_numbered ? ka.host_numbered : device_tag((uint32_t)*(const __attribute__((address_space(4))) int*)c->launch_no);
@@ -82,7 +81,7 @@ struct LayerSetup {
     a.ids = ids(now); a.ids_user = nullptr;
     a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
     a.slice = (g.n_cand + slices - 1) >> slices_log2;
-    a.exch = c->exch; a.keyx = c->keyx; a.keyid = c->keyid; a.cmax = c->cmax; a.no = LaunchNo{tag, nullptr}; a.home = home; a.impatient = ka.plan >> 23 & 63u; a.tstamp = c->tstamp;
+    a.exch = c->exch; a.keyx = c->keyx; a.keyid = c->keyid; a.cmax = c->cmax; a.no = LaunchNo{tag, nullptr}; a.home = home; a.impatient = ka.plan >> 23; a.tstamp = c->tstamp;
     a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
     if (HOSTPOOL) {
@@ -109,23 +108,20 @@ struct LayerSetup {
     a.q_prev = qprev(before); a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
     a.k_new = ka.k_new; a.v_new = ka.v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.tag = tag; a.pick_tag = tag + ((ka.plan >> 22) & 1u ? 2u : 0u);
-    a.impatient = ka.plan >> 23 & 63u; a.home = home; a.at_once = slices_log2 == 0; a.split_magic = ka.split_magic;
+    a.impatient = ka.plan >> 23; a.home = home; a.at_once = slices_log2 == 0;
     a.host_pool = HOSTPOOL ? reinterpret_cast<const uint16_t*>(c->host_base + c->host_layer_bytes * (unsigned long long)layer) : nullptr;
     a.max_pages = c->max_pages;
     return a;
   }
 };
 
-// STREAM: STREAM_* bits.  Four waves to a SIMD, no more and no fewer: with only the lower limit the compiler schedules for more
-// and leaves a slot of scratch memory, that nobody reads or writes, to kernels of G = 7 and 8, which costs each launch 0.9 us.
-template <int DT, int G, bool HOSTPOOL, int STREAM>
-__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
-                  uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
+template <int DT, int G, bool HOSTPOOL, int STREAM, bool HOME>
+__device__ __forceinline__ void layer_step(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
+                                           uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
   touch<sizeof(LayerConst)>((LayerConstPtr)consts);
   const LayerKernelArgs ka{consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic};
-  const LayerSetup<HOSTPOOL> u(ka);
+  const LayerSetup<HOSTPOOL, HOME> u(ka);
   StepArgs s;
   int head, nw = SEL_WAVES, own = 0;           // own: a selecting block's slice of the head's candidates, an attention block's split
   Selected got = Selected::NOTHING;
@@ -144,8 +140,8 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
   } else {
     const AttnArgs a = u.attn_args(ka, G);
     // numbered through row by row and dealt to the heads, whose blocks wait for each other
-    const uint32_t wide = (uint32_t)(u.home ? (u.c->heads + 7) & ~7 : u.c->heads);
-    deal_block((blockIdx.y - (uint32_t)u.step_rows) * wide + blockIdx.x, a.n_splits, u.home,
+    const uint32_t wide = (uint32_t)(HOME ? (u.c->heads + 7) & ~7 : u.c->heads);
+    deal_block((blockIdx.y - (uint32_t)u.step_rows) * wide + blockIdx.x, a.n_splits, HOME,
                [&](uint32_t j) { return split_magic ? __umulhi(j, split_magic) : j; }, head, own);
     if (head >= u.c->heads) return;
     left = attn_block<DT, STEP_WAVES, true, HOSTPOOL, (STREAM & STREAM_PAGES) != 0>(a, own, head, reinterpret_cast<float*>(dyn_lds));
@@ -153,29 +149,46 @@ void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k
     // What follows is hardly ever run.  Its arguments come from memory once more: kept up to here they would cost the page
     // loop registers.
     const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-    s = LayerSetup<HOSTPOOL>(again).step_args(again);
+    s = LayerSetup<HOSTPOOL, HOME>(again).step_args(again);
     if (left.ids) lds_barrier();                             // (the LDS is free)
   }
   if (step || left.ids) {
     select_finish<DT, G, true>(s, head, own, dyn_lds, nw, got, [] {
       const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-      return LayerSetup<HOSTPOOL>(again).step_args(again);
+      return LayerSetup<HOSTPOOL, HOME>(again).step_args(again);
     });
   }
   if (step) return;
   const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-  attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL>(again).attn_args(again, G), own, head, left);
+  attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL, HOME>(again).attn_args(again, G), own, head, left);
 }
 
+// STREAM: STREAM_* bits.  home_: a head's blocks on one XCD; two kernels, as in fkv_step_dev.h (8 heads x 992 candidates 8.5 us with a
+// test beside each store, 8.2 without).  Four waves to a SIMD, no more and no fewer: with only the lower limit the compiler schedules for
+// more and leaves a slot of scratch memory, that nobody reads or writes, to kernels of G = 7 and 8, which costs each launch 0.9 us.
 template <int DT, int G, bool HOSTPOOL, int STREAM>
+__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
+                  uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
+  layer_step<DT, G, HOSTPOOL, STREAM, false>(consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic);
+}
+template <int DT, int G, bool HOSTPOOL, int STREAM>
+__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void home_layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
+                       uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
+  layer_step<DT, G, HOSTPOOL, STREAM, true>(consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic);
+}
+
+template <int DT, int G, bool HOSTPOOL, int STREAM, bool HOME>
 static bool launch_layer_g(const LayerIO& io, const LayerLaunch& l, hipStream_t st) {
   static size_t granted = 48 * 1024;
-  if (!grant_lds(&layer_kernel<DT, G, HOSTPOOL, STREAM>, l.lds, granted)) return false;
+  constexpr auto kernel = HOME ? &home_layer_kernel<DT, G, HOSTPOOL, STREAM> : &layer_kernel<DT, G, HOSTPOOL, STREAM>;
+  if (!grant_lds(kernel, l.lds, granted)) return false;
   if (io.done)
-    hipExtLaunchKernelGGL((layer_kernel<DT, G, HOSTPOOL, STREAM>), l.grid, dim3(STEP_THREADS), l.lds, st, nullptr, io.done, 0,
+    hipExtLaunchKernelGGL(kernel, l.grid, dim3(STEP_THREADS), l.lds, st, nullptr, io.done, 0,
                           io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
   else
-    layer_kernel<DT, G, HOSTPOOL, STREAM><<<l.grid, STEP_THREADS, l.lds, st>>>(io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
+    kernel<<<l.grid, STEP_THREADS, l.lds, st>>>(io.consts, io.q, io.k_new, io.v_new, io.out, l.packed, io.tag, l.plan, l.split_magic);
   return true;
 }
 
@@ -183,7 +196,7 @@ static bool launch_layer_g(const LayerIO& io, const LayerLaunch& l, hipStream_t 
 template <int DT, bool HOSTPOOL, int STREAM>
 static bool launch_layer_variant(const LayerIO& io, const LayerLaunch& l, int G, hipStream_t st) {
   switch (G) {
-#define FKV_CASE(GG) case GG: return launch_layer_g<DT, GG, HOSTPOOL, STREAM>(io, l, st);
+#define FKV_CASE(GG) case GG: return l.home ? launch_layer_g<DT, GG, HOSTPOOL, STREAM, true>(io, l, st) : launch_layer_g<DT, GG, HOSTPOOL, STREAM, false>(io, l, st);
     FKV_CASE(1) FKV_CASE(2) FKV_CASE(3) FKV_CASE(4) FKV_CASE(5) FKV_CASE(6) FKV_CASE(7) FKV_CASE(8)
 #undef FKV_CASE
     default: return false;

@@ -1,5 +1,5 @@
-// The "step" kernel (token append, correction test, page weights and the top-k selection), the scan and the selection as launches
-// of their own, and the host-side rules that size their launches and the one-launch layer kernel's (fkv_layer_dev.h).
+// The append, the correction test, the scan and the selection as launches of their own, and the host-side rules that size these
+// launches, the step kernel's (fkv_step_dev.h) and the one-launch layer kernel's (fkv_layer_dev.h).
 // The roles themselves are in fkv_step_dev.h, attention in fkv_attn_dev.h.
 #include "fkv_step_dev.h"
 #include "fkv_attn_dev.h"
@@ -7,21 +7,6 @@
 #pragma clang fp contract(off)
 
 namespace fkv {
-
-// ---------------------------------------------------------------------------------
-// grid (heads, rows): rows as in step_roles
-// ---------------------------------------------------------------------------------
-template <int DT, int G, bool PAST>
-__global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];              // selection: n_cand keys, then the recall plan
-  touch_args<sizeof(StepArgs)>();
-  step_roles<DT, G, PAST>(a, blockIdx.x, blockIdx.y, [&](int head, int s) {
-    int nw;
-    Selected got;
-    if (select_begin<G, true>(a, head, s, dyn_lds, nw, got)) 
-      select_finish<DT, G, true>(a, head, s, dyn_lds, nw, got, [] { return args_from_memory<StepArgs>(); });
-  });
-}
 
 // The append and the correction test as calls of their own (fkv_kv_append, fkv_corr_check).  Both are one trip to memory and
 // little else, so what counts is what a launch brings along: no more waves than there is work for, and arguments that fit the
@@ -70,10 +55,11 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) __attribute__((amdgpu_waves_per_eu
   score_role<DT, G, false, SCAN_WAVES, PAST>(a, y - a.other_rows, blockIdx.x);
 }
 // The selection after it: one block per slice of a head's candidates, dealt to the heads (deal_block).
-template <int G>
+template <int G, bool HOME>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
   touch_args<sizeof(StepArgs)>();
+  a.home = HOME;
   int head, s;
   deal_block(blockIdx.x, a.slices, a.home, [&](uint32_t j) { return j >> a.slices_log2; }, head, s);
   if (head >= a.heads) return;
@@ -209,7 +195,7 @@ constexpr long kFuseMaxChunks = 2560;
 
 template <int DT, int G>
 static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom& g, hipStream_t st) {
-  static size_t granted_step = 48 * 1024, granted_past = 48 * 1024, granted_select = 48 * 1024;
+  static size_t granted_select = 48 * 1024, granted_home = 48 * 1024;
   StepArgs a;
   int rows;
   size_t lds;
@@ -229,24 +215,22 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
     fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
     const bool past = (stream_of(d, g) & STREAM_SUMMARIES) != 0;
     a.home = (roles & ROLE_SELECT) != 0 && heads_at_home(d, heads, rows);
-    const dim3 grid(a.home ? by_xcd(heads) : heads, rows);
-    if (!(past ? grant_lds(&step_kernel<DT, G, true>, lds, granted_past) : grant_lds(&step_kernel<DT, G, false>, lds, granted_step))) return -1;
-    if (past) step_kernel<DT, G, true><<<grid, STEP_THREADS, lds, st>>>(a);
-    else      step_kernel<DT, G, false><<<grid, STEP_THREADS, lds, st>>>(a);
+    if (!(a.home ? launch_step_kernel_home : launch_step_kernel)(a, DT, G, past, rows, lds, st)) return -1;
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
   }
   fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, selection_slices(g, d.G, heads), a, rows, lds);
   a.P = reinterpret_cast<unsigned long long*>(io.P_plain);
   a.cmax = reinterpret_cast<unsigned long long*>(io.cmax_plain);
-  if (!grant_lds(&select_kernel<G>, lds, granted_select)) return -1;
+  a.home = a.slices > 1 && heads_at_home(d, heads, a.slices);
+  if (!(a.home ? grant_lds(&select_kernel<G, true>, lds, granted_home) : grant_lds(&select_kernel<G, false>, lds, granted_select))) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
   const int scan_rows = a.other_rows + heads;
   const dim3 scan_grid(a.chunks, scan_rows < kGridRows ? scan_rows : kGridRows, (scan_rows + kGridRows - 1) / kGridRows);
   if (stream_of(d, g) & STREAM_SUMMARIES) scan_kernel<DT, G, true><<<scan_grid, SCAN_WAVES * 64, 0, st>>>(a);
   else                                    scan_kernel<DT, G, false><<<scan_grid, SCAN_WAVES * 64, 0, st>>>(a);
-  a.home = a.slices > 1 && heads_at_home(d, heads, a.slices);
-  select_kernel<G><<<(a.home ? by_xcd(heads) : heads) * a.slices, SEL_THREADS, lds, st>>>(a);
+  if (a.home) select_kernel<G, true><<<by_xcd(heads) * a.slices, SEL_THREADS, lds, st>>>(a);
+  else        select_kernel<G, false><<<heads * a.slices, SEL_THREADS, lds, st>>>(a);
   *io.P_tagged = false;
   return 2;
 }
@@ -333,11 +317,11 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const long blocks = (long)heads * rows;
   if (g_one_launch < 0 && (heads > kLayerMaxHeads || (long)heads * n_att > kLayerMaxAttended ||
                            blocks > (io.host_pool ? kLayerMaxBlocksHost : kLayerMaxBlocks) || l.lds > kLdsPerUnit / 2)) return false;
-  const bool home = heads_at_home(d, heads, rows);
-  l.grid = dim3(home ? by_xcd(heads) : heads, rows);
+  l.home = heads_at_home(d, heads, rows);
+  l.grid = dim3(l.home ? by_xcd(heads) : heads, rows);
   l.packed = (uint32_t)(g.L - 1) | (uint32_t)io.layer << 19;
   l.plan = (io.have_prev ? 1u : 0u) | (uint32_t)io.parity << 1 | (uint32_t)passes_log2 << 2 | (uint32_t)slices_log2 << 4 |
-           (uint32_t)n_splits << 7 | (io.lose_selection ? 1u << 22 : 0u) | io.impatient << 23 | (home ? 1u << 29 : 0u);
+           (uint32_t)n_splits << 7 | (io.lose_selection ? 1u << 22 : 0u) | io.impatient << 23;
   l.split_magic = n_splits > 1 ? 0xffffffffu / (uint32_t)n_splits + 1u : 0u;      // exact for the block counts of a layer launch
   *io.launch_grid = (int)(l.grid.x * l.grid.y);
   *io.launch_lds = l.lds;

@@ -1219,29 +1219,69 @@ __device__ __forceinline__ void select_finish(const StepArgs& hot, int head, int
 // present only if its role bit is set; x is the KV head -- at home, the grid is a multiple of 8 wide -- except that the
 // selection's blocks are numbered through row by row and dealt to the heads (deal_block; they wait for each other).
 // ---------------------------------------------------------------------------------
-// select(head, slice): what a selecting block does.
+// select(head, slice): what a selecting block does.  (Its code last: with it ahead of the scoring's a launch took 0.2 us longer.)
 template <int DT, int G, bool PAST, typename Select>
 __device__ __forceinline__ void step_roles(const StepArgs& a, int x, int y, Select select) {
-  const int others = (a.roles & ROLE_APPEND ? 1 : 0) + (a.roles & ROLE_CORR ? 1 : 0);
-  if (y >= others + a.chunks) {
-    const int wide = a.home ? (a.heads + 7) & ~7 : a.heads;
-    int head, s;
-    deal_block((uint32_t)((y - others - a.chunks) * wide + x), a.slices, a.home, [&](uint32_t j) { return j >> a.slices_log2; }, head, s);
-    if (head < a.heads) select(head, s);
-    return;
-  }
-  if (x >= a.heads) return;
+  const bool there = x < a.heads;
   if (a.roles & ROLE_APPEND) {
-    if (y == 0) { append_role<DT>(a, x); return; }
+    if (y == 0) { if (there) append_role<DT>(a, x); return; }
     y -= 1;
   }
   if (a.roles & ROLE_CORR) {
-    if (y == 0) { corr_role<DT, G>(a, x); return; }
+    if (y == 0) { if (there) corr_role<DT, G>(a, x); return; }
     y -= 1;
   }
-  if (y == 0) FKV_STAMP(a, x, 0);
-  score_role<DT, G, true, STEP_WAVES, PAST>(a, x, y);
-  if (y == 0) FKV_STAMP(a, x, 1);
+  if (y < a.chunks) {
+    if (!there) return;
+    if (y == 0) FKV_STAMP(a, x, 0);
+    score_role<DT, G, true, STEP_WAVES, PAST>(a, x, y);
+    if (y == 0) FKV_STAMP(a, x, 1);
+    return;
+  }
+  const int wide = a.home ? (a.heads + 7) & ~7 : a.heads;
+  int head, s;
+  deal_block((uint32_t)((y - a.chunks) * wide + x), a.slices, a.home, [&](uint32_t j) { return j >> a.slices_log2; }, head, s);
+  if (head < a.heads) select(head, s);
 }
+
+// ---------------------------------------------------------------------------------
+// grid (heads -- at home, the next multiple of 8 -- , rows): rows as in step_roles.  HOME is known when this is compiled because a
+// launch is a chain of a few microseconds and the test beside every store that other blocks wait for costs it 0.1 to 0.3 of them
+// (8 heads x 992 candidates 8.2 us with the test, 8.0 without; at home 7.6 and 7.5).
+// ---------------------------------------------------------------------------------
+template <int DT, int G, bool PAST, bool HOME>
+__global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];              // selection: n_cand keys, then the recall plan
+  touch_args<sizeof(StepArgs)>();
+  a.home = HOME;
+  step_roles<DT, G, PAST>(a, blockIdx.x, blockIdx.y, [&](int head, int s) {
+    int nw;
+    Selected got;
+    if (select_begin<G, true>(a, head, s, dyn_lds, nw, got)) 
+      select_finish<DT, G, true>(a, head, s, dyn_lds, nw, got, [] { return args_from_memory<StepArgs>(); });
+  });
+}
+
+template <int DT, int G, bool PAST, bool HOME>
+static bool launch_step_kernel_g(const StepArgs& a, int rows, size_t lds, hipStream_t st) {
+  static size_t granted = 48 * 1024;
+  if (!grant_lds(&step_kernel<DT, G, PAST, HOME>, lds, granted)) return false;
+  step_kernel<DT, G, PAST, HOME><<<dim3(HOME ? by_xcd(a.heads) : a.heads, rows), STEP_THREADS, lds, st>>>(a);
+  return true;
+}
+
+// one of these in each of the files that share the kernel's variants
+template <bool HOME>
+static bool launch_step_kernel_variant(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st) {
+  switch (G) {
+#define FKV_CASE(GG) case GG: return dtype == 0 ? (past ? launch_step_kernel_g<0, GG, true, HOME>(a, rows, lds, st) : launch_step_kernel_g<0, GG, false, HOME>(a, rows, lds, st)) \
+                                                : (past ? launch_step_kernel_g<1, GG, true, HOME>(a, rows, lds, st) : launch_step_kernel_g<1, GG, false, HOME>(a, rows, lds, st));
+    FKV_CASE(1) FKV_CASE(2) FKV_CASE(3) FKV_CASE(4) FKV_CASE(5) FKV_CASE(6) FKV_CASE(7) FKV_CASE(8)
+#undef FKV_CASE
+    default: return false;
+  }
+}
+bool launch_step_kernel(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st);        // a head's blocks adjacent
+bool launch_step_kernel_home(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st);   // ... on one XCD
 
 }  // namespace fkv

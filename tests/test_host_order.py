@@ -38,6 +38,10 @@ def _play(recorder, library, config, calls):
             rc = lib.fkv_load_prefix(ctx, args[0], some, some, args[1], st)
         elif call == "step":
             rc = lib.fkv_decode_step(ctx, args[0], some, some, some, some, st, copy)
+        elif call == "select":
+            rc = lib.fkv_page_select(ctx, args[0], some, None, st)
+        elif call == "attend":
+            rc = lib.fkv_sparse_decode_attn(ctx, args[0], some, some, 0, st)
         elif call == "append":
             rc = lib.fkv_kv_append(ctx, args[0], some, some, st, copy)
         elif call == "capture":
@@ -235,6 +239,20 @@ def test_heads_are_put_on_xcds_only_where_blocks_are_known_to_go(play, where, wi
     assert o.rc == [0, 0]
     (op,) = o.launches(1, "layer_kernel")
     assert o.ops[op][4].split("x")[0] == str(wide)
+    assert ("home_layer_kernel" in o.ops[op][1]) == (wide == 16)                     # (what the kernel was compiled for is what its grid says)
+
+
+@pytest.mark.parametrize("where,step,wide", [(0, "Lb1EE", 16), (1, "Lb0EE", 12)])
+def test_launches_of_the_primitives_at_home(play, where, step, wide):
+    """Twelve heads of 16 pages, at home if blocks are known to go there: the same of the step kernel, and of attention in its two grids."""
+    o = play([("load", 0, 2000), ("select", 0), ("attend", 0)], n_layers=1, batch=3, n_q_heads=16, n_kv_heads=4, max_ctx=4096, placement=0, where=where,
+             budget_tokens=512)
+    assert o.rc == [0, 0, 0]
+    (op,) = o.launches(1, "step_kernel")
+    assert step in o.ops[op][1] and o.ops[op][4].split("x")[0] == str(wide)
+    (op,) = o.launches(2, "attn_kernel")
+    n = 512 // 32 + 1                                                                # pages, four to a block
+    assert (("home_attn_kernel" in o.ops[op][1]), o.ops[op][4]) == ((True, f"8x{-(-n // 4)}x2") if where == 0 else (False, f"{-(-n // 4)}x12x1"))
 
 
 if __name__ == "__main__":
