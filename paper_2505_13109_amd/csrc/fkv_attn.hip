@@ -71,7 +71,8 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   a.share = (d.G * D + a.n_splits - 1) / a.n_splits;
   a.out = io.out; a.g = g; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k; a.status = io.status; a.tstamp = io.tstamp;
   a.heads = heads;
-  a.home = a.n_splits > 1 && heads_at_home(d, heads, a.n_splits);
+  const int n_there = n_att - d.k + g.k_eff;
+  a.home = a.n_splits > 1 && a.n_splits <= 2 * kMaxWaitingHome && heads_at_home(d, heads, (a.n_splits + 1) / 2, (double)n_there * UNIT_BYTES, true);
   const dim3 grid = a.home ? dim3(kXcds, a.n_splits, by_xcd(heads) / kXcds) : dim3(a.n_splits, std::min(heads, kHeadRows), (heads + kHeadRows - 1) / kHeadRows);
   constexpr int NW = 4;
   const size_t lds = attn_lds_floats(NW, d.G) * sizeof(float);

@@ -96,8 +96,9 @@ inline int by_xcd(int heads) { return (heads + kXcds - 1) / kXcds * kXcds; }
 // each write where they are, leaves at `where` (device memory).
 constexpr int kWhereBlocks = 1024;
 bool blocks_by_xcd(uint32_t* where);
-// Whether a head's blocks, `rows` of them, are put on one XCD (deal_block).
-bool heads_at_home(const Dims& d, int heads, int rows);
+// Whether a head's blocks, `rows` of them (as blocks of 512 threads) that read `bytes`, are put on one XCD (deal_block).
+bool heads_at_home(const Dims& d, int heads, int rows, double bytes, bool attn_only = false);
+constexpr double kSummaryBytes = 2 * D * 2;        // of a page
 
 // Launches are numbered (31 bits, from 1), and the values that a launch's blocks exchange carry its number as a tag.  The
 // host counts.  A launch that is being captured runs again at every replay with the arguments it was captured with, so its
@@ -216,7 +217,9 @@ constexpr int kComputeUnits = 256;
 // keeps waits short: in block order at most one head's blocks are half
 // there, so a launch by itself gets on, and two at once mostly do.  It is not what makes them end: with more launches on the
 // machine, or another program's, a block may wait for one that cannot start, and goes on by itself (PATIENCE).
-constexpr int kMaxWaiting = kComputeUnits;
+// At home it is one head per XCD and launch that may be half there, in 64 slots: no more blocks to a head than leave slots for others
+// when all four launches that a process has on the machine at once (its hardware queues) are there with one block missing.
+constexpr int kMaxWaiting = kComputeUnits, kMaxWaitingHome = 2 * kComputeUnits / kXcds / 4;
 int attn_pages_per_block(int n_att, int heads, int max_splits, int nw, int max_blocks = kMaxWaiting);
 void launch_load_prefix(const Dims& d, const PoolDesc& pd, uint16_t* summ, uint16_t* host_pool,
                         const uint16_t* K, const uint16_t* V, int n_tokens, int32_t* ids, hipStream_t st);   // ids: [2][heads][k], emptied

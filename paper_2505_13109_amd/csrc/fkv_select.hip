@@ -98,14 +98,27 @@ static const int g_home = knob("FKV_HOME", -1);                   // 0 never, 1 
 
 // A word that stays in the L2 it was written to is seen after 0.22 us, through memory after 0.3 to 0.5, and a block reads its
 // head's 30 KB of weights from the L2 at several times the rate; an exchange of a layer-step takes 0.3 to 0.8 us less.  Layer-steps
-// of G = 4, a head's blocks on one XCD against adjacent ones: 8 heads x 992 candidates 8.9 and 9.4 us, 2016 (G = 8) 13.8 and 16.1,
-// 16 heads x 992 9.5 and 10.3, 64 23.6 and 26.8 (27.0 and 31.9 where most are corrected), 248 heads of one block each the same.
-// Where the heads do not go round evenly some XCDs have more of them: still better while all of an XCD's blocks run at once
-// (4 heads x 32 candidates 6.7 and 7.3; 1 x 480 6.8 and 7.1; 20 x 480 9.7 and 9.9), not beyond (1 head x 8160 18.4 and 12.6; 20 x 2016
-// 16.7 and 15.9; 100 x 144 21.3 and 19.2).
-bool heads_at_home(const Dims& d, int heads, int rows) {
+// of G = 4, a head's blocks adjacent and on one XCD: 8 heads x 992 candidates 9.1 and 8.3 us, 2016 (G = 8) 15.4 and 12.7, 16 heads x 992
+// 10.7 and 9.5, 64 25.6 and 23.8 (31.0 and 28.5 where most are corrected).
+// Where the heads do not go round evenly some XCDs have more to read than if everything were spread, at about 1 MB a us, so what
+// decides is that excess over an even share.  Adjacent and at home (few corrected; most), MB too much: 28 heads x 992 candidates x 33 pages,
+// 0.5, 12.0 and 11.1, 17.1 and 15.4; 12 x 992 x 65, 0.8, 9.9 and 9.3, 15.1 and 13.7; 76 x 480 x 65, 0.7, 26.1 and 24.5, 30.7 and 28.9; but 12 x 100 x 129,
+// 0.92, 9.5 and 10.8, 12.1 and 12.7; 28 x 100 x 129, 0.92, 13.2 and 14.4, 16.3 and 16.9; 9 x 992 x 129, 2.3, 10.2 and 12.2, 16.5 and 16.1.  With fewer than
+// 8 heads, where an XCD has one and others none, there is more room: 4 x 992 x 65, 0.8, 8.7 and 8.3, 13.4 and 12.1; 1 x 992 x 65, 1.4, 8.3 and 7.9, 12.9 and
+// 11.7; 4 x 992 x 129, 1.3, 8.9 and 9.0, 14.3 and 13.4; but 1 x 992 x 193, 3.2, 9.0 and 9.8, 15.4 and 14.9; 1 x 992 x 257, 4.1, 9.5 and 11.7, 16.6 and 16.7.
+// Attention by itself has one exchange to gain by: 12 x 33 pages, 0.3, 5.8 and 5.4; 4 x 65, 0.5, 6.0 and 5.8; 1 x 65, 0.9, 5.9 and 5.6; but 12, 20 and 28 x 65,
+// 0.5, 7.2 and 7.3, 7.9 and 8.1, 9.2 and 9.4; 12 x 129, 1.1, 9.1 and 10.6; 4 x 129, 1.1, 8.2 and 8.5.
+// With up to two heads to an XCD the launch also has to be there all at once (14 heads x 480 x 129, 0.6 MB, 11.3 and 12.3); with more it
+// runs in rounds either way.
+constexpr double kHomeExcess = 0.9e6, kHomeExcessAttn = 0.45e6, kFewHeadsRoom = 2.2;
+constexpr int kSlotsOfXcd = 2 * kComputeUnits / kXcds;            // blocks of 512 threads that an XCD holds at once
+bool heads_at_home(const Dims& d, int heads, int rows, double bytes, bool attn_only) {
   if (g_home >= 0) return g_home == 1;
-  return d.same_xcd && (heads % kXcds == 0 || by_xcd(heads) / kXcds * rows <= 2 * kComputeUnits / kXcds);
+  if (!d.same_xcd) return false;
+  if (heads % kXcds == 0) return true;
+  const int most = by_xcd(heads) / kXcds;
+  if (most <= 2 && most * rows > kSlotsOfXcd) return false;
+  return (most - (double)heads / kXcds) * bytes <= (attn_only ? kHomeExcessAttn : kHomeExcess) * (heads < kXcds ? kFewHeadsRoom : 1.0);
 }
 
 // Which XCD a block runs on is the dispatcher's choice, not the programming model's, so it is looked at once for every context
@@ -214,7 +227,7 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
     const int slices = selection_slices(g, d.G, heads);
     fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
     const bool past = (stream_of(d, g) & STREAM_SUMMARIES) != 0;
-    a.home = (roles & ROLE_SELECT) != 0 && heads_at_home(d, heads, rows);
+    a.home = (roles & ROLE_SELECT) != 0 && heads_at_home(d, heads, rows, g.n_cand * kSummaryBytes);
     if (!(a.home ? launch_step_kernel_home : launch_step_kernel)(a, DT, G, past, rows, lds, st)) return -1;
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
@@ -222,7 +235,7 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, selection_slices(g, d.G, heads), a, rows, lds);
   a.P = reinterpret_cast<unsigned long long*>(io.P_plain);
   a.cmax = reinterpret_cast<unsigned long long*>(io.cmax_plain);
-  a.home = a.slices > 1 && heads_at_home(d, heads, a.slices);
+  a.home = a.slices > 1 && heads_at_home(d, heads, a.slices, (double)g.n_cand * d.G * sizeof(float));
   if (!(a.home ? grant_lds(&select_kernel<G, true>, lds, granted_home) : grant_lds(&select_kernel<G, false>, lds, granted_select))) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
   const int scan_rows = a.other_rows + heads;
@@ -270,7 +283,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   // missing pages themselves; the tagged words have to hold a page id and a slot
   if (io.host_pool && (d.max_pages > TAGGED_MAX_PAGES || 2 * d.k > TAGGED_MAX_SLOTS)) return false;
   const int heads = d.batch * d.n_kv;
-  const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0);
+  const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0), n_there = n_att - d.k + g.k_eff;
   const int slices = selection_slices(g, d.G, heads);
   // Attention's blocks, which come last, are fewer where a list is shared, since selecting blocks wait too.  Beside long lists of
   // many heads, a block each, a head is cut half as fine as it could be: with that many scoring blocks the launch runs in rounds, and
@@ -281,11 +294,14 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const bool half = g.n_cand > kLongList && heads > kFewHeads;
   const int waiting = slices > 1 ? kMaxWaiting - heads * slices : half ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting;
   int pps, n_splits, passes, rows;
+  auto size = [&]() {
+    passes = scoring_passes(d, g, slices, n_splits, kLayerResident);
+    rows = 2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + n_splits;
+  };
   auto cut = [&](int max_blocks) {
     pps = attn_pages_per_block(n_att, heads, io.max_splits, STEP_WAVES, max_blocks);
     n_splits = (n_att + pps - 1) / pps;
-    passes = scoring_passes(d, g, slices, n_splits, kLayerResident);
-    rows = 2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + n_splits;
+    size();
   };
   cut(waiting);
   // As many blocks as fit, two to a compute unit, where the heads are many: with fewer, the dispatcher puts two on some units and
@@ -306,18 +322,24 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
     cut(std::min(kLayerResident, heads * std::max(n_splits, n_att / kPagesEach)));
     if ((long)heads * rows > kLayerMaxBlocks) cut(waiting);
   }
+  LayerLaunch l;
+  l.home = heads_at_home(d, heads, rows, (double)n_there * UNIT_BYTES + g.n_cand * kSummaryBytes);
+  if (l.home && n_splits > kMaxWaitingHome) {
+    n_splits = kMaxWaitingHome;
+    pps = (n_att + n_splits - 1) / n_splits;
+    if (io.host_pool) n_splits = (n_att + pps - 1) / pps;
+    size();
+  }
   if (n_splits > 63 || pps > 64 * STEP_WAVES) return false;
   const int passes_log2 = passes == 4 ? 2 : passes == 2 ? 1 : 0;
   int slices_log2 = 0;
   while ((1 << slices_log2) < slices) slices_log2 += 1;
-  LayerLaunch l;
   l.lds = (size_t)select_key_words(g.n_cand) * sizeof(uint32_t) + (io.host_pool ? plan_lds_ints(d.k) * sizeof(int32_t) : 0);
   const size_t lds_attn = (size_t)attn_lds_floats(STEP_WAVES, d.G) * sizeof(float);
   if (lds_attn > l.lds) l.lds = lds_attn;
   const long blocks = (long)heads * rows;
   if (g_one_launch < 0 && (heads > kLayerMaxHeads || (long)heads * n_att > kLayerMaxAttended ||
                            blocks > (io.host_pool ? kLayerMaxBlocksHost : kLayerMaxBlocks) || l.lds > kLdsPerUnit / 2)) return false;
-  l.home = heads_at_home(d, heads, rows);
   l.grid = dim3(l.home ? by_xcd(heads) : heads, rows);
   l.packed = (uint32_t)(g.L - 1) | (uint32_t)io.layer << 19;
   l.plan = (io.have_prev ? 1u : 0u) | (uint32_t)io.parity << 1 | (uint32_t)passes_log2 << 2 | (uint32_t)slices_log2 << 4 |

@@ -255,5 +255,52 @@ def test_launches_of_the_primitives_at_home(play, where, step, wide):
     assert (("home_attn_kernel" in o.ops[op][1]), o.ops[op][4]) == ((True, f"8x{-(-n // 4)}x2") if where == 0 else (False, f"{-(-n // 4)}x12x1"))
 
 
+def _decode(play, heads, candidates, pages, call="step", **config):
+    """One call of `heads` KV heads with so many candidates and attended pages, the open one included: its launches"""
+    ctx = (candidates + 8) * 32 + 5
+    o = play([("load", 0, ctx), (call, 0)], **dict(dict(n_layers=1, batch=heads, n_q_heads=4, n_kv_heads=1, max_ctx=ctx + 59, budget_tokens=(pages - 1) * 32,
+                                                        sink_tokens=128, window_tokens=128, placement=0), **config))
+    assert o.rc == [0, 0]
+    lo, hi = o.span[1]
+    return [op for op in o.ops[lo:hi] if op[0] == "launch"]
+
+
+@pytest.mark.parametrize("heads,candidates,pages,home", [
+    (1, 100, 33, True), (1, 992, 65, True), (1, 992, 129, False),            # 0.5, 1.4 and 2.3 MB more than an even share for one XCD
+    (4, 992, 129, True), (4, 992, 257, False),               # 1.3, 2.4
+    (4, 90, 1000, True),                                     # a budget that the context has no pages for does not count: 0.8
+    (7, 992, 129, True),                                     # 0.3
+    (12, 992, 65, True), (12, 100, 129, False),              # 0.8, 0.9
+    (9, 992, 129, False),                                    # 2.3
+    (14, 480, 129, False), (14, 480, 65, True),              # two heads' 66 blocks do not fit an XCD at once; 50 do
+    (28, 992, 33, True), (100, 480, 65, True), (100, 992, 129, False),      # 0.5, 0.7, 1.3
+    (8, 992, 129, True), (120, 992, 129, True),              # they go round evenly
+])
+def test_heads_at_home_by_what_their_xcd_has_to_read(play, heads, candidates, pages, home):
+    (op,) = _decode(play, heads, candidates, pages)
+    assert ("home_layer_kernel" in op[1], int(op[4].split("x")[0])) == (home, -(-heads // 8) * 8 if home else heads)
+
+
+@pytest.mark.parametrize("heads,pages,home", [(1, 65, True), (1, 129, False), (4, 65, True), (4, 129, False), (12, 33, True), (12, 65, False), (28, 129, False),
+                                              (16, 257, True)])
+def test_attention_by_itself_at_home(play, heads, pages, home):
+    """(0.9, 1.8, 0.5, 1.1, 0.3, 0.5 and 1.1 MB; two heads to each)"""
+    (op,) = _decode(play, heads, 992, pages, call="attend")
+    assert ("home_attn_kernel" in op[1]) == home
+
+
+@pytest.mark.parametrize("heads,pages,placement,splits", [
+    (8, 65, 0, 9), (8, 129, 0, 16), (8, 257, 0, 16), (8, 1000, 0, 16),
+    (8, 129, 1, 15),                                         # runs of nine
+    (16, 129, 0, 9),
+    (1, 129, 0, 17),                                         # spread over the XCDs
+])
+def test_no_more_blocks_of_a_head_wait_on_an_xcd_than_four_launches_leave_room_for(play, heads, pages, placement, splits):
+    (op,) = [op for op in _decode(play, heads, 992, pages, placement=placement) if "layer_kernel" in op[1]]
+    rows = int(op[4].split("x")[1])
+    scoring = [-(-992 // (32 * passes)) for passes in (1, 2, 4)]
+    assert rows - 3 - splits in scoring, rows
+
+
 if __name__ == "__main__":
     print(json.dumps(_play(*json.loads(sys.argv[1]))))
