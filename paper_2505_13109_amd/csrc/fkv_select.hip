@@ -304,21 +304,25 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
     size();
   };
   cut(waiting);
-  // As many blocks as fit, two to a compute unit, where the heads are many: with fewer, the dispatcher puts two on some units and
-  // none on others, according to which scoring blocks have just ended, and those of a launch that is bound by its bytes take
-  // that much longer.  G = 4, 65 pages, up to 256 blocks and up to 512: 64 heads 23.0 and 21.6 us, 96 33.3 and 30.0, 128 39.9 and
-  // 35.4, 160 50.7 and 39.4, 240 (G = 7) 82.7 and 69.7; where most heads are corrected 25.1 and 24.7, 33.7 and 34.6, 39.6 and 40.6,
-  // 50.8 and 42.8, 82.4 and 69.2.  Long streams of pages do better in few blocks as long as each has a unit of its own (129
+  // As many blocks as fit, two to a compute unit, where the heads are many and the launch runs in rounds: with fewer, the dispatcher
+  // puts two on some units and none on others, according to which scoring blocks have just ended, and those of a launch that is
+  // bound by its bytes take that much longer.  G = 4, 65 pages, a block a unit and as many as fit (few corrected; most): 80 heads x 480 candidates
+  // 27.1 and 25.0 us, 32.1 and 29.5; 96 x 100 31.0 and 23.7, 36.1 and 28.6; 112 x 480 37.1 and 31.0, 42.1 and 37.9; 128 x 992 47.6 and 42.2, 54.0
+  // and 50.8; 240 x 480 (G = 7) 82.7 and 69.7, 82.4 and 69.2.  A launch that is there all at once has nothing to gain by it and gets a second round:
+  // 36 heads x 480 candidates x 129 pages, 504 blocks, 18.4 and, in 936, 23.2, 25.3 and 28.0; 68 x 100 x 65, 476, 17.9 and 21.9; 60 x 100 x 129, 480, 23.5
+  // and 26.4, 28.9 and 33.4.  (Which of it is faster is not a matter of rounds alone: 104 x 480 x 65 29.7 and 29.6, 33.2 and 35.8, between 96 heads, 32.0
+  // and 28.8, and 112.)  Long streams of pages do better in few blocks as long as each has a unit of its own (129
   // pages: 96 heads, 192 blocks and 480, 42.3 and 47.5, most corrected), but not where that is just missed (112 heads, 224 and 448:
   // 59.7 and 48.0, 59.4 and 52.4; 80 heads, 240 and 480: 43.9 and 36.2, 46.2 and 41.9).  Over a host link nothing is gained.  And a
   // block is to have pages enough for what it costs by itself (168 heads x 33 pages, one block and two, 23.1 and 24.4 us, 200 29.3
-  // and 31.3).  Heads of one block each that many scoring blocks come before find units to themselves as long as they are few
+  // and 31.3; a head of 65 pages keeps its four blocks where 256 fit, though six would be 10 % faster).  Heads of one block each that many scoring
+  // blocks come before find units to themselves as long as they are few
   // (one block and three: 136 heads x 344 candidates 34.5 and 36.7, 168 42.0 and 43.7; but 160 x 218 47.5 and 39.8, 168 x 187 49.3
   // and 40.9, and 224 x 468, one and two, 71.8 and 61.4).
   const int blocks_now = heads * n_splits;
   const bool loose = n_splits == 1 && g.n_cand > kManyScored && blocks_now <= kFewAlone;
   const bool cut_finer = n_att <= kShortStream ? n_att >= kEnoughToCut && !loose : blocks_now > kLooseBlocks && blocks_now < kComputeUnits;
-  if (slices == 1 && g.n_cand < kLongList && !io.host_pool && cut_finer) {
+  if (slices == 1 && g.n_cand < kLongList && !io.host_pool && cut_finer && (long)heads * rows > kLayerResident) {
     cut(std::min(kLayerResident, heads * std::max(n_splits, n_att / kPagesEach)));
     if ((long)heads * rows > kLayerMaxBlocks) cut(waiting);
   }

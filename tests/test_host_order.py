@@ -289,6 +289,23 @@ def test_attention_by_itself_at_home(play, heads, pages, home):
     assert ("home_attn_kernel" in op[1]) == home
 
 
+@pytest.mark.parametrize("heads,candidates,pages,scoring,splits", [
+    (36, 480, 129, 4, 7), (40, 480, 129, 8, 8),              # 504 blocks are there at once, 520 are not
+    (72, 100, 65, 1, 3), (76, 100, 65, 4, 4),                # 504, 532
+    (136, 100, 39, 2, 1), (136, 100, 40, 2, 2),              # a block has pages enough from 40 on
+    (136, 240, 65, 4, 3), (136, 241, 65, 2, 1),              # few heads of one block each behind many scoring blocks
+    (176, 344, 65, 3, 1), (184, 344, 65, 3, 2),              # no longer few
+    (96, 480, 96, 8, 5), (96, 480, 97, 4, 2),                # long streams: 192 blocks have a unit each
+    (104, 480, 97, 4, 4),                                    # 208 just miss that
+    (64, 480, 129, 8, 4), (68, 480, 129, 4, 7),              # 256 do not; 204 do
+    (196, 992, 80, 8, 2), (200, 992, 80, 8, 1),              # 2548 blocks; 2600 would be too many for one launch
+    (128, 1023, 65, 8, 4), (128, 1024, 65, 8, 2),            # beside long lists it is not cut finer
+])
+def test_attention_of_many_heads_is_cut_into_as_many_blocks_as_fit(play, heads, candidates, pages, scoring, splits):
+    (op,) = _decode(play, heads, candidates, pages)
+    assert "layer_kernel" in op[1] and int(op[4].split("x")[1]) == 2 + scoring + 1 + splits
+
+
 @pytest.mark.parametrize("heads,pages,placement,splits", [
     (8, 65, 0, 9), (8, 129, 0, 16), (8, 257, 0, 16), (8, 1000, 0, 16),
     (8, 129, 1, 15),                                         # runs of nine
