@@ -60,6 +60,12 @@ int fkv_test_lose_selection(fkv_ctx* ctx, int32_t on);
 #define FKV_WAIT_ALL     63
 int fkv_test_impatience(fkv_ctx* ctx, int32_t kinds);
 
+/* How often, since the last call, a block of the layer's launches made by itself what it else gets from other blocks of its launch:
+ * a wait ran out (or was made to: above), or the weights of a head were not finite.  Counted per selecting block and per wave of
+ * attention.  Results do not depend on it, but such a launch takes milliseconds; 0 in a program whose launches find room.
+ * at_home (may be NULL): whether the layer's last one-launch layer-step had each head's blocks on one XCD.  Blocking. */
+int fkv_test_by_itself(fkv_ctx* ctx, int32_t layer, int32_t* count, int32_t* at_home);
+
 /* Test hook for the numbers that tell one launch's exchanged values from another's (31 bits, one per launch): the
  * context's next launch gets the number after `last`.  Host-side, no GPU work. */
 int fkv_test_launch_number(fkv_ctx* ctx, int32_t last);

@@ -24,7 +24,7 @@ EXPORTED_SYMBOLS = (
     "fkv_load_prefix", "fkv_kv_append", "fkv_page_summary_update", "fkv_corr_check",
     "fkv_page_select", "fkv_recall_pages", "fkv_sparse_decode_attn", "fkv_commit",
     "fkv_decode_step", "fkv_flush", "fkv_debug_read", "fkv_debug_read_page", "fkv_profile_enable", "fkv_profile_read", "fkv_profile_attn", "fkv_profile_select", "fkv_profile_launch_floor", "fkv_step_launches", "fkv_export_nhd",
-    "fkv_sparse_decode_attn_static", "fkv_recall_pending", "fkv_attach_nhd_pool", "fkv_test_lose_selection", "fkv_test_launch_number", "fkv_test_impatience", "fkv_instrument_timestamps",
+    "fkv_sparse_decode_attn_static", "fkv_recall_pending", "fkv_attach_nhd_pool", "fkv_test_lose_selection", "fkv_test_launch_number", "fkv_test_impatience", "fkv_test_by_itself", "fkv_instrument_timestamps",
 )
 
 
@@ -86,6 +86,7 @@ def lib() -> C.CDLL:
         "fkv_test_lose_selection": (C.c_int, [vp, i32]),
         "fkv_test_launch_number": (C.c_int, [vp, i32]),
         "fkv_test_impatience": (C.c_int, [vp, i32]),
+        "fkv_test_by_itself": (C.c_int, [vp, i32, C.POINTER(i32), C.POINTER(i32)]),
         "fkv_instrument_timestamps": (C.c_int, [vp, i32]),
         "fkv_sparse_decode_attn": (C.c_int, [vp, i32, vp, vp, i32, vp]),
         "fkv_sparse_decode_attn_static": (C.c_int, [vp, i32, vp, vp, i32, vp]),
@@ -207,6 +208,12 @@ class FreeKV:
 
     def test_impatience(self, kinds):
         self._check(self.L.fkv_test_impatience(self._h, kinds), "fkv_test_impatience")
+
+    def test_by_itself(self, layer):
+        """(how often since the last call a block did without the others, whether the last layer-step's heads were at home)"""
+        n, home = C.c_int32(), C.c_int32()
+        self._check(self.L.fkv_test_by_itself(self._h, layer, C.byref(n), C.byref(home)), "fkv_test_by_itself")
+        return n.value, bool(home.value)
 
     def test_launch_number(self, last):
         self._check(self.L.fkv_test_launch_number(self._h, last), "fkv_test_launch_number")

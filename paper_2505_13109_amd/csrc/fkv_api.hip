@@ -43,7 +43,8 @@ struct LayerState {
   int recalled = 0;          // placement HOST: which heads' pending pages have been recalled (bit 0 corrected, bit 1 the others)
   int last_launches = 0;     // kernel launches of the last fkv_decode_step (compute stream)
   int step_launches = 0;     // launches the last run_step made
-  int last_grid = 0;         // grid and dynamic LDS of the last one-launch layer-step
+  int last_grid = 0;         // grid and dynamic LDS of the last one-launch layer-step, and whether its heads were at home
+  bool last_home = false;
   size_t last_lds = 0;
   hipEvent_t ev_offload = nullptr;   // last page offload finished
   hipEvent_t ev_recall = nullptr;    // deferred recall into ACTIVE's slots finished
@@ -82,7 +83,7 @@ Layout make_layout(const fkv_config& c) {
   l.flags = o;  o += align_up((size_t)b * n_kv);
   l.miss = o;   o += align_up((size_t)b * n_kv * (1 + 3 * l.k) * 4);   // per head: count, page ids, slots, positions in the picked list
   l.cosine = o; o += align_up((size_t)b * n_q * 8);
-  l.status = o; o += align_up(4);                                    // a kernel gave up a bounded wait
+  l.status = o; o += align_up(sizeof(LayerStatus));
   l.tagged = o; o += align_up((size_t)b * n_kv * (l.k > 0 ? l.k : 1) * 8);   // tagged copies of the picked ids (one-launch layer-step)
   l.layer_bytes = o;
   size_t p = 0;
@@ -187,7 +188,7 @@ struct fkv_ctx {
   int32_t* miss(int l) const { return reinterpret_cast<int32_t*>(layer_base(l) + lay.miss); }
   double* cosine(int l) const { return reinterpret_cast<double*>(layer_base(l) + lay.cosine); }
   unsigned long long* tagged(int l) const { return reinterpret_cast<unsigned long long*>(layer_base(l) + lay.tagged); }
-  int* status(int l) const { return reinterpret_cast<int*>(layer_base(l) + lay.status); }
+  LayerStatus* status(int l) const { return reinterpret_cast<LayerStatus*>(layer_base(l) + lay.status); }
   unsigned long long* words(size_t off) const { return reinterpret_cast<unsigned long long*>(ctx_base() + off); }
   float* P_plain() const { return reinterpret_cast<float*>(ctx_base() + lay.P_plain); }
   float* score() const { return reinterpret_cast<float*>(ctx_base() + lay.score); }
@@ -315,6 +316,7 @@ static StepIO make_step_io(fkv_ctx* ctx, int layer, int roles, const void* q, co
   io.cmax_plain = reinterpret_cast<float*>(ctx->ctx_base() + ctx->lay.cmax_plain);
   if (roles & ROLE_SELECT) io.no = next_launch(ctx, st);      // (the other roles exchange nothing)
   io.impatient = ctx->impatient;
+  io.status = ctx->status(layer);
   io.P_tagged = &ctx->P_tagged;
   io.tstamp = ctx->tstamp();
   if (ctx->cfg.placement == FKV_PLACE_HOST) {      // a selection comes with its recall plan
@@ -585,9 +587,9 @@ int fkv_health(fkv_ctx* ctx, int32_t layer) {
   FKV_FLUSH(ctx);
   int flag = 0;
   FKV_HIP(ctx, hipDeviceSynchronize());
-  FKV_HIP(ctx, hipMemcpy(&flag, ctx->status(layer), sizeof(int), hipMemcpyDeviceToHost));
+  FKV_HIP(ctx, hipMemcpy(&flag, &ctx->status(layer)->lost, sizeof(int), hipMemcpyDeviceToHost));
   if (flag != 0) {
-    FKV_HIP(ctx, hipMemset(ctx->status(layer), 0, sizeof(int)));
+    FKV_HIP(ctx, hipMemset(&ctx->status(layer)->lost, 0, sizeof(int)));
     return ctx->fail(FKV_ETIMEOUT, "an attention block gave up waiting for its head's selection");
   }
   return FKV_OK;
@@ -947,6 +949,7 @@ int fkv_decode_step(fkv_ctx* ctx, int32_t layer, const void* q_dev, const void* 
     lio.done = last_of_group && cs != st && launch_records(st) ? ctx->ev_fork : nullptr;
     lio.launch_grid = &ls.last_grid;
     lio.launch_lds = &ls.last_lds;
+    lio.launch_home = &ls.last_home;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ctx->prof_on && ctx->prof_used + 2 <= ctx->prof_ev.size()) {
       e0 = ctx->prof_ev[ctx->prof_used];
@@ -1041,6 +1044,16 @@ int fkv_test_impatience(fkv_ctx* ctx, int32_t kinds) {
   if (!ctx) return FKV_EINVAL;
   if (kinds & ~FKV_WAIT_ALL) return ctx->fail(FKV_EINVAL, "unknown kind of wait");
   ctx->impatient = (uint32_t)kinds;
+  return FKV_OK;
+}
+
+int fkv_test_by_itself(fkv_ctx* ctx, int32_t layer, int32_t* count, int32_t* at_home) {
+  FKV_CHECK_LAYER(ctx, layer);
+  if (!count) return ctx->fail(FKV_EINVAL, "null argument");
+  FKV_HIP(ctx, hipDeviceSynchronize());
+  FKV_HIP(ctx, hipMemcpy(count, &ctx->status(layer)->by_itself, sizeof(int), hipMemcpyDeviceToHost));
+  FKV_HIP(ctx, hipMemset(&ctx->status(layer)->by_itself, 0, sizeof(int)));
+  if (at_home) *at_home = ctx->layers[layer].last_home ? 1 : 0;
   return FKV_OK;
 }
 

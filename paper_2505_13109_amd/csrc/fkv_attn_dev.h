@@ -110,7 +110,7 @@ struct AttnArgs {
   float* out;
   Geom g;
   int heads, n_kv, G, k;     // heads: stand-alone attention: (request, KV head) pairs
-  int* status;               // set to 1 if a wait ran out
+  LayerStatus* status;
   long long* tstamp;
   // --- when attention shares its launch with the step roles ("fused") ---
   // flags are recomputed here, the new token is taken from k_new/v_new, a corrected head waits for its selection
@@ -183,7 +183,7 @@ __device__ __forceinline__ float output_alone(const AttnArgs& a, int head, bool 
         unsigned long long w;
         int it = 0;
         while ((uint32_t)((w = ld_tag(a.tagged + (size_t)head * k + i)) >> 32) != a.pick_tag) {
-          if (++it > MAX_POLLS) { *a.status = 1; return __builtin_nanf(""); }
+          if (++it > MAX_POLLS) { a.status->lost = 1; return __builtin_nanf(""); }
           __builtin_amdgcn_s_sleep(2);
         }
         if constexpr (HOSTFUSED) tagged_unpick((uint32_t)w, page, slot, from_host);
@@ -222,7 +222,7 @@ __device__ __forceinline__ float output_alone(const AttnArgs& a, int head, bool 
       M = m_new;
     }
   }
-  if (HOSTFUSED && __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return __builtin_nanf("");
+  if (HOSTFUSED && __hip_atomic_load(&a.status->lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return __builtin_nanf("");
   return o / den;
 }
 
@@ -543,7 +543,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
     // With the KV in a host pool the wave that gives up also leaves the page-cache slot it was to fill unfilled, while
     // the recall plan lists the page as cached: the layer's state cannot be trusted from then on.  Every later step of
     // the layer therefore stays marked -- NaN outputs -- for as long as the flag is up (fkv_health takes it down).
-    if (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) l_run = __builtin_nanf("");
+    if (__hip_atomic_load(&a.status->lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) l_run = __builtin_nanf("");
   }
   if (split == 0) FKV_ASTAMP(17);
 
@@ -680,6 +680,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
 // and into the tagged words.
 template <int DT, int NW, bool FUSED, bool HOSTFUSED>
 __device__ __forceinline__ void attn_finish(const AttnArgs& a, int split, int head, AttnLeft left) {
+  if ((threadIdx.x & 63) == 0) atomicAdd(&a.status->by_itself, 1);
   if (FUSED && left.ids) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (each wave's words are where the others read them)
     lds_barrier();

@@ -126,6 +126,10 @@ inline int stream_of(const Dims& d, const Geom& g) {
   return (pages + summaries > 270e6 ? STREAM_SUMMARIES : 0) | (pages > 310e6 ? STREAM_PAGES : 0);
 }
 
+// Per layer, in device memory.  lost: ids that a block had written by then were not there (fkv_health).  by_itself: how often a selecting
+// block or a wave of attention made alone what it else gets from other blocks of its launch (fkv_test_by_itself).
+struct LayerStatus { int lost, by_itself; };
+
 // what blocks of a launch wait for, as bits (a test makes waits of these kinds run out at once)
 constexpr uint32_t WAIT_WEIGHTS = 1, WAIT_MAXIMA = 2, WAIT_SUMS = 4, WAIT_KEYS = 8, WAIT_SPLITS = 16, WAIT_IDS = 32;
 
@@ -138,7 +142,7 @@ struct StepIO {
   unsigned long long* P; float* P_plain; float* score; int32_t* ids; int32_t* ids_user;              // selection
   unsigned long long* exch; unsigned long long* keyx; unsigned long long* keyid;     // its exchange between blocks
   unsigned long long* cmax; float* cmax_plain;                                       // largest weights of the scored chunks
-  LaunchNo no; uint32_t impatient;
+  LaunchNo no; uint32_t impatient; LayerStatus* status;
   bool* P_tagged;                                                                    // out: whether the launch wrote P or P_plain
   long long* tstamp;                                                                 // debug timestamps or null
   // KV in a host pool (else all null): a launch with ROLE_SELECT also makes the recall plan of the new selection --
@@ -187,7 +191,7 @@ struct LayerIO {
   uint32_t impatient;                        // WAIT_* bits
   bool lose_selection;                       // test of the bounded wait: attention waits for a tag that never comes
   hipEvent_t done;                           // if not null: recorded by the launch itself
-  int* launch_grid; size_t* launch_lds;      // out: shape of the launch that was made
+  int* launch_grid; size_t* launch_lds; bool* launch_home;      // out: shape of the launch that was made, whether heads are at home
 };
 // `reps` launches of a kernel that does nothing, with the given grid, 512 threads and dynamic LDS
 bool launch_floor(int grid, size_t lds, int reps, hipStream_t st);
@@ -246,7 +250,7 @@ struct AttnIO {
   const uint8_t* flags; int use;
   unsigned long long* part; unsigned long long* part_ml; int max_splits;
   LaunchNo no; uint32_t impatient;
-  int* status; float* out; long long* tstamp;
+  LayerStatus* status; float* out; long long* tstamp;
 };
 void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end);
 void launch_next_number(int* p, hipStream_t st);            // *p to the next launch number, by a kernel

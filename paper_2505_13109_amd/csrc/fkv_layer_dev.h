@@ -81,6 +81,7 @@ struct LayerSetup {
     a.ids = ids(now); a.ids_user = nullptr;
     a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
     a.slice = (g.n_cand + slices - 1) >> slices_log2;
+    a.by_itself = &reinterpret_cast<LayerStatus*>(at(c->o_status))->by_itself;
     a.exch = c->exch; a.keyx = c->keyx; a.keyid = c->keyid; a.cmax = c->cmax; a.no = LaunchNo{tag, nullptr}; a.home = home; a.impatient = ka.plan >> 23; a.tstamp = c->tstamp;
     a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.plan_act_ids = a.plan_act_slots = nullptr; a.plan_new_slots = a.plan_miss = nullptr; a.plan_lds_off = 0;
@@ -104,7 +105,7 @@ struct LayerSetup {
     const int n_att = g.n_sink + c->k + g.n_win + (g.r > 0 ? 1 : 0);
     a.pps = ka.split_magic ? (int)__umulhi((uint32_t)(n_att + a.n_splits - 1), ka.split_magic) : n_att;
     a.no = LaunchNo{}; a.out = ka.out; a.g = g; a.n_kv = c->n_kv; a.G = G; a.k = c->k;
-    a.status = reinterpret_cast<int*>(at(c->o_status)); a.tstamp = c->tstamp;
+    a.status = reinterpret_cast<LayerStatus*>(at(c->o_status)); a.tstamp = c->tstamp;
     a.q_prev = qprev(before); a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
     a.k_new = ka.k_new; a.v_new = ka.v_new; a.tagged = reinterpret_cast<unsigned long long*>(at(c->o_tagged));
     a.tag = tag; a.pick_tag = tag + ((ka.plan >> 22) & 1u ? 2u : 0u);

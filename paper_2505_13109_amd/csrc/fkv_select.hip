@@ -172,7 +172,7 @@ static void fill_step_args(const Dims& d, int roles, const StepIO& io, Geom g, i
   a.corr_pool = d.corr_pool; a.sel_pool = d.sel_pool;
   a.flags = io.flags; a.flags_user = io.flags_user; a.cosine = io.cosine;
   a.P = io.P; a.score = io.score; a.ids = io.ids; a.ids_user = io.ids_user; a.exch = io.exch; a.keyx = io.keyx; a.keyid = io.keyid; a.cmax = io.cmax;
-  a.no = io.no; a.impatient = io.impatient; a.tstamp = io.tstamp;
+  a.no = io.no; a.impatient = io.impatient; a.by_itself = &io.status->by_itself; a.tstamp = io.tstamp;
   a.passes = passes;
   a.slices = slices;
   rows = 0;
@@ -351,6 +351,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   l.split_magic = n_splits > 1 ? 0xffffffffu / (uint32_t)n_splits + 1u : 0u;      // exact for the block counts of a layer launch
   *io.launch_grid = (int)(l.grid.x * l.grid.y);
   *io.launch_lds = l.lds;
+  *io.launch_home = l.home;
   const int stream = stream_of(d, g);
   const auto launch = io.host_pool ? (stream & STREAM_SUMMARIES ? launch_layer_host_stream : launch_layer_host)
                       : stream & STREAM_PAGES ? launch_layer_hbm_past : stream & STREAM_SUMMARIES ? launch_layer_hbm_stream : launch_layer_hbm;

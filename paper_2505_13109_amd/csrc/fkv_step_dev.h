@@ -85,6 +85,7 @@ struct StepArgs {
   LaunchNo no;               // of this launch
   bool home;                 // a head's blocks are on one XCD (deal_block)
   uint32_t impatient;        // WAIT_* bits: waits that run out at once (tests)
+  int* by_itself;            // one more for every head's list that a block chose from without the others (LayerStatus)
   long long* tstamp;         // debug: 100 MHz timestamps of head 0's phases (may be null)
   unsigned long long* tagged; // if not null: [heads][k], every picked id once more as a tagged word: a block of
                               // this launch that waits for the selection polls the word it needs
@@ -1177,6 +1178,7 @@ __device__ __forceinline__ void select_finish(const StepArgs& hot, int head, int
     const PutId put(a, head, key);
     const bool alone = got == Selected::NOTHING;
     if (alone) {
+      if (tid == 0) atomicAdd(a.by_itself, 1);
       alone_keys<DT, G, TAGGED>(a, head, nw, key, sm);
       for (int j = tid; j < n; j += nt) a.score[(size_t)head * a.max_pages + lo + j] = key_score(key[j]);
     }

@@ -239,6 +239,21 @@ def test_an_attention_block_that_waits_in_vain(call, batch, n_q, n_kv, ctx, kw, 
     e.close()
 
 
+@pytest.mark.parametrize("call,kinds", [(_step, B.FKV_WAIT_KEYS), (_step, B.FKV_WAIT_SPLITS), (_step, B.FKV_WAIT_IDS), (_primitives, B.FKV_WAIT_WEIGHTS),
+                                        (_primitives, B.FKV_WAIT_SPLITS)])
+def test_what_blocks_make_by_themselves_is_counted(call, kinds):
+    """Four slices a head, every head corrected: none as long as waits end, and some for every kind that does not; once read, none again."""
+    x = _Inputs(3, 1, 16, 2, 40000, 4)
+    g, out = x.context(tau=1.5), x.out()
+    g.load_prefix(0, x.K, x.V)
+    for t, k in enumerate((0, kinds, 0)):
+        g.test_impatience(k)
+        call(g, x.q[t], x.k[t], x.v[t], out)
+        assert (g.test_by_itself(0)[0] > 0) == (k != 0), t
+    g.health(0)
+    g.close()
+
+
 @pytest.mark.parametrize("n_ctx", [2, 6])
 def test_contexts_decoding_at_once_on_streams_of_their_own(n_ctx):
     """Contexts of different shapes, each with a stream of its own and nothing waited for until all steps are enqueued, decode

@@ -684,20 +684,23 @@ def test_many_requests_take_the_bandwidth_bound_dispatch():
     pr.close()
 
 
-@pytest.mark.parametrize("batch,n_q,n_kv,ctx,placement", [
-    (1, 4, 1, 3000, 0),        # one head: one of the 8 XCDs has work
-    (3, 9, 3, 9000, 0),        # nine: the second round of heads has one
-    (3, 9, 3, 6000, 1),
-    (2, 16, 8, 40000, 0),      # two heads on each, every exchange of theirs at home
-    (1, 8, 2, 70000, 0),       # two heads, more blocks than one XCD runs at once: words through memory
-    (5, 20, 20, 3000, 0),      # a hundred: the same
+@pytest.mark.parametrize("batch,n_q,n_kv,ctx,placement,home", [
+    (1, 4, 1, 3000, 0, True),        # one head: one of the 8 XCDs has work
+    (3, 9, 3, 9000, 0, True),        # nine: the second round of heads has one
+    (3, 9, 3, 6000, 1, True),
+    (2, 16, 8, 40000, 0, True),      # two heads on each, every exchange of theirs at home
+    (1, 8, 2, 70000, 0, False),      # two heads, more blocks than one XCD runs at once: words through memory
+    (5, 20, 20, 3000, 0, True),      # a hundred: thirteen on some, twelve on the others
+    (3, 9, 3, 36000, 0, False),      # nine: the XCD that has two would read 1 MB more than its share
 ])
-def test_heads_dealt_to_the_xcds(batch, n_q, n_kv, ctx, placement):
-    """Every way the heads can be dealt to the XCDs, in the one-launch layer-step and in the primitives' launches."""
+def test_heads_dealt_to_the_xcds(batch, n_q, n_kv, ctx, placement, home):
+    """Every way the heads can be dealt to the XCDs, in the one-launch layer-step and in the primitives' launches.  A word that is not
+    where its reader looks would not show in results: the reader's wait runs out and it makes what it waits for.  So none may."""
     wl = W.Workload("xcds", 1, batch, n_q, n_kv, "bf16", ctx, 1024, 64, 64, 0.8, 4, 0.8, 0.6, 83, placement=placement)
     pr = _pair(wl, [0])
     for t in range(wl.steps - 1):
         pr.step(0, t, deep=t == 0)
+        assert pr.g.test_by_itself(0) == (0, home), t
     assert pr.g.step_launches(0) == 1
     assert 0 < pr.stats["flagged"]
     if placement == 0:
@@ -710,26 +713,30 @@ def test_heads_dealt_to_the_xcds(batch, n_q, n_kv, ctx, placement):
         pr.g.commit(0)
         res = [pr.oracles[(0, r)].step(pr.q[(0, r)][0][t], pr.kd[(0, r)][0][t], pr.vd[(0, r)][0][t]) for r in range(batch)]
         pr.compare(0, t, res, pr.read_step(0, True), True)
+        assert pr.g.test_by_itself(0)[0] == 0
     pr.g.health(0)
     pr.close()
 
 
-@pytest.mark.parametrize("batch,n_q,n_kv,ctx,budget", [
-    (8, 16, 8, 2527, 1248),    # 64 heads: 39 pages and the open one (none after the first step), cut as for a block a unit
-    (8, 16, 8, 2527, 1280),    # one more: as many blocks as fit
-    (7, 56, 8, 1300, 3040),    # 56 heads, G = 7, fewer pages than the budget has room for
-    (31, 8, 8, 2527, 2048),    # 248 heads: two blocks each
-    (10, 8, 8, 4200, 3072),    # 80 heads of 97 pages: three blocks each would just miss a unit each
-    (12, 8, 8, 4200, 3072),    # 96: two blocks each
-    (17, 8, 8, 7900, 2048),    # 136 heads behind many scoring blocks: one block each
+@pytest.mark.parametrize("batch,n_q,n_kv,ctx,budget,blocks", [
+    (17, 8, 8, 2015, 1248, (136 * 6, 136 * 7, 136 * 7)),      # 39 pages, one block a head; with the open page, from the second step on, two
+    (17, 8, 8, 2015, 1280, (136 * 7,) * 3),      # one more page: two from the first
+    (7, 56, 8, 1300, 3040, (56 * 9,) * 3),       # G = 7, fewer pages than the budget has room for: four
+    (31, 8, 8, 2527, 2048, (248 * 6,) * 3),      # two
+    (10, 8, 8, 4200, 3072, (80 * 11,) * 3),      # 97 pages: three would just miss a unit each, four
+    (12, 8, 8, 4200, 3072, (96 * 9,) * 3),       # two
+    (17, 8, 8, 7900, 2048, (136 * 6,) * 3),      # behind many scoring blocks: one
+    (18, 2, 2, 6000, 4096, (36 * 13,) * 3),      # there all at once: seven
 ])
-def test_heads_cut_into_blocks(batch, n_q, n_kv, ctx, budget):
+def test_heads_cut_into_blocks(batch, n_q, n_kv, ctx, budget, blocks):
     """Every way attention of many heads is cut in the one-launch layer-step, with corrected heads among them."""
     wl = W.Workload("cut", 1, batch, n_q, n_kv, "bf16", ctx, budget, 64, 96, 0.8, 3, 0.8, 0.6, 91)
     pr = _pair(wl, [0])
     for t in range(wl.steps):
         pr.step(0, t)
         assert pr.g.step_launches(0) == 1
+        assert pr.g.profile_launch_floor(0, 1)[1] == blocks[t], t         # heads times append, test, scoring, selecting, attending
+        assert pr.g.test_by_itself(0)[0] == 0, t
     assert 0 < pr.stats["flagged"] < pr.stats["heads"]
     pr.g.health(0)
     pr.close()
