@@ -291,6 +291,37 @@ def test_contexts_decoding_at_once_on_streams_of_their_own(n_ctx):
         g.close()
 
 
+def test_contexts_of_few_heads_at_once_find_room_on_the_xcds_they_share():
+    """Four contexts, as many as a process has launches on the machine at once, of one to seven heads each cut into as many blocks as may
+    wait for each other on one XCD, on streams of their own and with every head corrected: no wait runs out."""
+    shapes = [(1, 4, 1, 12000, 3072), (1, 8, 4, 30000, 6144), (1, 16, 2, 20000, 4096), (1, 28, 7, 20000, 4096)]
+    xs = [_Inputs(200 + i, b, n_q, n_kv, ctx, 12) for i, (b, n_q, n_kv, ctx, _) in enumerate(shapes)]
+    gs = [x.context(budget=s[4], tau=1.5) for x, s in zip(xs, shapes)]
+    streams = [torch.cuda.Stream() for _ in gs]
+    runs = []
+    for at_once in (False, True):
+        for x, g in zip(xs, gs):
+            g.load_prefix(0, x.K, x.V)
+        got = [[x.out() for _ in range(12)] for x in xs]
+        torch.cuda.synchronize()
+        for t in range(12):
+            for x, g, o, s in zip(xs, gs, got, streams):
+                g.decode_step(0, x.q[t], x.k[t], x.v[t], o[t], stream=s, copy_stream=s)
+                if not at_once:
+                    torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        for i, g in enumerate(gs):
+            assert g.step_launches(0) == 1
+            assert g.test_by_itself(0) == (0, True), (at_once, i)
+        runs.append((got, [g.debug_read(0, B.DBG_ACTIVE_IDS) for g in gs]))
+    (want, ids), (got, ids_then) = runs
+    for i, g in enumerate(gs):
+        assert np.array_equal(ids[i], ids_then[i]), i
+        assert all(_close(a, b) for a, b in zip(got[i], want[i])), i
+        g.health(0)
+        g.close()
+
+
 def test_more_heads_than_a_grid_dimension_holds():
     """65600 (request, KV head) pairs, with scoring, selection and attention each a launch of its own: the requests on both
     sides of the 32768th and 65536th pair against a context of those requests alone."""
