@@ -226,9 +226,10 @@ __device__ __forceinline__ float output_alone(const AttnArgs& a, int head, bool 
   return o / den;
 }
 
-// One block of NW wavefronts: every n_splits-th attend-list position of `head` from `split` on (nth_position, nth_of_wave).  Dealt like that, and not a run of positions to each block, every block of a corrected head has its share of
-// what can be attended at once and of what has to wait for the ids; with runs those of the picked pages alone had nothing to do
-// until the ids came and all the work after that.  Layer-steps where most heads are corrected, runs against this: 8 heads of 65
+// One block of NW wavefronts: every n_splits-th attend-list position of `head` from `split` on (nth_position, nth_of_wave).  Dealt
+// like that, and not a run of positions to each block, every block of a corrected head has its share of what can be attended at
+// once and of what has to wait for the ids; with runs those of the picked pages alone had nothing to do until the ids came and
+// all the work after that.  Layer-steps where most heads are corrected, runs against this: 8 heads of 65
 // pages 10.9 and 10.1 us, 4 heads (G = 7) 10.7 and 10.2, 48 22.7 and 21.1, 112 40.7 and 36.8, 96 of 129 pages 47.1 and 43.3;
 // where few are, the same to 1 % less.  With the KV in a host pool the link decides, and blocks have runs: the corrected heads' missing
 // pages are then fetched by as few waves at once as it takes to fill it (8 heads x 32 missing pages, 1286 us and, in turn, 1292 with
@@ -562,7 +563,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   // Block `split` finishes the split-th `share` of the head's G x D outputs: its threads keep their sums of that part, hand
   // the others to the blocks that finish them, and fold the other blocks' sums of their own part in as they arrive.  One
   // trip, and no block reads more than an n_splits-th of the partials (one block merging alone: 6 us of a 20 us launch at
-  // 16 splits of G = 8).  A head's blocks are adjacent in block order and wait for each other only.
+  // 16 splits of G = 8).  A head's blocks, dealt as deal_block says, wait for each other only.
   const int n_splits = a.n_splits, items = G * D;
   const int own_lo = split * a.share, own_hi = min(items, own_lo + a.share);
   unsigned long long* const po = a.part + (size_t)head * a.max_splits * items;

@@ -255,10 +255,9 @@ __device__ __forceinline__ int near_flag(const float* c, int G, float tau, int p
 }
 
 // ---- exchange between blocks of one launch ---------------------------------------
-// Each XCD has its own L2, so data one block writes for another block of the same launch must not sit in (or be read from)
-// a non-coherent L2 line.  A device-scope fence per block would write back and invalidate the whole L2 each time; instead
-// the few values that are exchanged are written and read with relaxed device-scope atomics, which the hardware serves at
-// the device coherence point.
+// Each XCD has its own L2, and one does not see what is in another's.  A device-scope fence per block would write back and
+// invalidate the whole L2 each time; instead each value that is exchanged goes by itself, as a relaxed atomic: into the L2
+// where its readers are on the writer's XCD, through to memory where they are not (st_tag).
 
 // A picked page as one 32-bit value, for the exchange between the selecting block and waiting attention waves when the
 // KV lives in a host pool: page id (< 2^16), page-cache slot (< 2^15), and whether the slot has yet to be filled from
@@ -277,7 +276,8 @@ __device__ __forceinline__ void tagged_unpick(uint32_t w, int& id, int& slot, bo
 // Which head block i of a section of a launch's blocks works for, and which of the head's n it is.  Blocks go to the 8 XCDs in
 // turn, by their number in the launch.  At home: heads by 8, each on an XCD of its own, so that what a head's blocks tell each
 // other stays in that XCD's L2 (the section has to start at a multiple of 8; what is beyond the last head is nobody's).
-// Else a head's blocks are adjacent.  In both cases at most one head's blocks per XCD, or per launch, are ever half there.
+// Else a head's blocks are adjacent, over all XCDs.  At home at most one head's blocks per XCD, else one's per launch, are ever half
+// there.
 // div: i -> i / n.
 template <typename Div>
 __device__ __forceinline__ void deal_block(uint32_t i, int n, bool home, Div div, int& head, int& own) {
@@ -287,12 +287,14 @@ __device__ __forceinline__ void deal_block(uint32_t i, int n, bool home, Div div
 }
 
 // A value exchanged between blocks of one launch without a counter: one 64-bit word holding the value and a tag that no
-// earlier writer of that word used (a launch number), written and read in one piece at device scope.  A reader that sees
-// the tag has the value: no acknowledgement to wait for, no counter to bump, no second read.  Measured on this chip: one
-// way about 0.6 us, against 0.3 us (store acknowledged) + 0.4 us (atomic) + 0.6 us (read) for store / counter / read.
+// earlier writer of that word used (a launch number), written and read in one piece.  A reader that sees the tag has the value:
+// no acknowledgement to wait for, no counter to bump, no second read.  Measured on this chip: one way 0.22 us in an L2 and
+// 0.3 to 0.5 through memory, where store / counter / read takes 0.3 us (store acknowledged) + 0.4 (atomic) + 0.6 (read).
 // home: a head's blocks are all on one XCD (deal_block), so the word only has to be in that XCD's L2, where it stays till the
 // launch ends; else it is written through to memory.  Readers go past their L1 in either case, which is all there is between
-// them and the L2, so they need not know.  A word that could not be seen would be a wait that runs out (PATIENCE).
+// them and the L2, so they need not know.  (A store at work-group scope that other work-groups read is more than the memory model
+// promises; it is what this machine does.  A word that could not be seen would be a wait that runs out, PATIENCE, and is counted,
+// LayerStatus.)
 __device__ __forceinline__ void st_tag(unsigned long long* p, uint32_t value, uint32_t tag, bool home) {
   const unsigned long long w = ((unsigned long long)tag << 32) | value;
   if (home) __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

@@ -218,10 +218,10 @@ static bool grant_lds(F* fn, size_t lds, size_t& granted) {
 constexpr int kComputeUnits = 256;
 // Most blocks of a launch that wait for each other (a head's attention blocks, and its selecting blocks where it has several):
 // half of those that fit (two to a compute unit), and all of them where there is something to be had by that (launch_layer).  That
-// keeps waits short: in block order at most one head's blocks are half
-// there, so a launch by itself gets on, and two at once mostly do.  It is not what makes them end: with more launches on the
-// machine, or another program's, a block may wait for one that cannot start, and goes on by itself (PATIENCE).
-// At home it is one head per XCD and launch that may be half there, in 64 slots: no more blocks to a head than leave slots for others
+// keeps waits short: in block order at most one head's blocks are half there, so a launch by itself gets on, and two at once mostly
+// do.  It is not what makes them end: with more launches on the machine, or another program's, a block may wait for one that cannot
+// start, and goes on by itself (PATIENCE).
+// At home one head per XCD and launch may be half there, in the XCD's 64 slots: no more blocks to a head than leave slots for others
 // when all four launches that a process has on the machine at once (its hardware queues) are there with one block missing.
 constexpr int kMaxWaiting = kComputeUnits, kMaxWaitingHome = 2 * kComputeUnits / kXcds / 4;
 int attn_pages_per_block(int n_att, int heads, int max_splits, int nw, int max_blocks = kMaxWaiting);

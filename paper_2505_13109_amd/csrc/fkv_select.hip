@@ -79,8 +79,8 @@ static const int g_one_launch = knob("FKV_ONE_LAUNCH", -1);       // layer-step:
 static const int g_fuse = knob("FKV_FUSE", -1);
 
 // Selecting blocks of a head, a power of two.  One as long as it has the registers and not too many softmax numerators to make:
-// the exchanges of a shared list (sums, then keys) cost about 3 us in all.  8 KV heads, layer-step in us, alone against the
-// best shared one: 1500 candidates, G = 4, 10.4 and 12.2; 3000, G = 3, 13.6 and 13.7; 1500, G = 6, 12.0 and 12.6; but 2016, G = 5,
+// the exchanges of a shared list (sums, then keys) are what it costs.  8 KV heads, layer-step in us with the words going through memory
+// (in the L2 the lines lie where they lay), alone against the best shared one: 1500 candidates, G = 4, 10.4 and 12.2; 3000, G = 3, 13.6 and 13.7; 1500, G = 6, 12.0 and 12.6; but 2016, G = 5,
 // 13.1 and 12.8; 1200, G = 8, 13.3 and 13.0; 3500, G = 3, 16.0 and 14.5.  A list that is shared is cut fine, since every phase
 // but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
 // in 2, 4, 8, 16 blocks: 2300 candidates 14.3, 13.4, 12.9, 13.5; 4000: 17.6, 17.0, 15.5, 15.0; 8160: -, 22.0, 19.8, 19.0; but 32 heads

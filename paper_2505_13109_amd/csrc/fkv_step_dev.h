@@ -397,14 +397,14 @@ __device__ __forceinline__ float pooled_score(const uint32_t* e, const double* z
 // its candidates' G values in registers from the weights to the choice.  What needs the whole head comes as words of other
 // blocks: the maxima from the blocks that scored (the largest of every chunk of pages), the integer softmax sums from the
 // other groups (exact, so their order does not matter), and the keys and ids of each group's own best k, among which the
-// last group finds the head's.  A head's groups are adjacent in block order and wait for each other and for scoring
-// blocks (lower indices) only, and for neither of them for long (PATIENCE).
+// last group finds the head's.  A head's groups, dealt as deal_block says, wait for each other and for scoring blocks (lower
+// indices) only, and for neither of them for long (PATIENCE).
 //
 // What bounds it: a chain of short phases.  A wave issues an instruction that depends on the one before every 8 cycles, an LDS
-// round trip takes 62, a trip between blocks 0.4 us and more; so what counts is the number of dependent instructions and
+// round trip takes 62, a trip between blocks 0.2 us and more (st_tag); so what counts is the number of dependent instructions and
 // of barriers.  A group is 8 waves, two to a SIMD, which fill each other's gaps (4 waves with twice
 // the candidates each: 1 us more of a 10 us layer-step), and waves without a candidate end at once.  A long list is shared
-// (selection_slices); each exchange costs a trip of about 1 us.
+// (selection_slices); each exchange costs its trip and the barriers around it.
 // TAGGED: the weights come from scoring blocks of this launch; else from a launch that has ended.
 // ---------------------------------------------------------------------------------
 constexpr int SEL_WAVES = 8, SEL_THREADS = SEL_WAVES * 64;
