@@ -132,10 +132,9 @@ __global__ void where_kernel(uint32_t* where) {
 bool blocks_by_xcd(uint32_t* where) {
   uint32_t at[kWhereBlocks];
   hipError_t e = hipMemset(where, 0xff, sizeof(at));               // (no XCD's number: what stays so was not written)
-  if (e == hipSuccess) {
-    where_kernel<<<kWhereBlocks, 64>>>(where);
-    e = hipGetLastError();
-  }
+  void* args[] = {&where};
+  // (the launch's own error: hipGetLastError would also say, and take away, what a call of the program's left behind)
+  if (e == hipSuccess) e = hipLaunchKernel(reinterpret_cast<const void*>(&where_kernel), dim3(kWhereBlocks), dim3(64), args, 0, nullptr);
   if (e == hipSuccess) e = hipMemcpy(at, where, sizeof(at), hipMemcpyDeviceToHost);
   if (e != hipSuccess) {
     (void)hipGetLastError();

@@ -36,9 +36,10 @@ void rec_capture(void* s) { if (!is_captured(s)) captured[n_captured++] = s; }
 void rec_end_capture(void) { n_captured = 0; n_captures += 1; }
 const char* rec_log(void) { return log_text; }
 
-/* what where_kernel does: 0 writes block numbers modulo 8, 1 other numbers, 2 is refused, 3 writes nothing */
+/* what where_kernel does: 0 writes block numbers modulo 8, 1 other numbers, 2 is refused, 3 writes nothing; 4 is 0, after a call of
+ * the program's own that failed */
 static int where_mode, where_ran, where_fill, last_error;
-void rec_where(int mode) { where_mode = mode; }
+void rec_where(int mode) { where_mode = mode; last_error = mode == 4 ? 98 : 0; }
 
 static const char* name_of(const void* stub) {
   for (int i = 0; i < n_stubs; ++i)

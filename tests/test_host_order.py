@@ -27,10 +27,13 @@ def _play(recorder, library, config, calls):
         _fields_ = [(n, C.c_int32) for n in dims] + [("tau", C.c_float)] + [(n, C.c_int32) for n in ("recall_mode", "select_pooling", "corr_pooling")]
 
     ctx, some = C.c_void_p(), C.c_void_p(0x10000000)                  # (no address is looked at)
-    rec.rec_where(config.pop("where", 0))
+    where = config.pop("where", 0)
+    rec.rec_where(where)
+    left = 98 if where == 4 else 0
     st, cs, copy = C.c_void_p(COMPUTE), C.c_void_p(COPY), C.c_void_p(config.pop("copy", COPY))
     rc = lib.fkv_create(C.byref(Config(**config)), some, C.c_size_t(1 << 50), some, C.c_size_t(1 << 50), C.byref(ctx))
     assert rc == 0, rc
+    assert rec.hipGetLastError() == left                              # (the program's own error is still there, and none of the library's)
     done = []
     for call, *args in calls:
         at = rec.rec_log().count(b"\n")
@@ -233,6 +236,7 @@ def test_attention_beside_long_lists_of_many_heads_is_cut_half_as_fine(play, bat
     (1, 12),      # they do not
     (2, 12),      # the kernel that looks was not launched, (3) or has written nothing: not known, whatever the memory held
     (3, 12),
+    (4, 16),      # they do, whatever the program called before
 ])
 def test_heads_are_put_on_xcds_only_where_blocks_are_known_to_go(play, where, wide):
     o = play([("load", 0, 2000), ("step", 0)], n_layers=1, batch=3, n_q_heads=16, n_kv_heads=4, max_ctx=4096, placement=0, where=where)
