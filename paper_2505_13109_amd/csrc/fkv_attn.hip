@@ -6,11 +6,12 @@
 namespace fkv {
 
 // NW wavefronts per block.  grid: a head's n_splits blocks adjacent (n_splits, heads), beyond kHeadRows heads (a grid dimension ends at
-// 65535) folded into a third dimension; at home (8, n_splits, heads / 8), so that a head's blocks are on one XCD (deal_block).  A block
+// 65535) folded into a third dimension; at home (8, n_splits, heads / 8), so that a head's blocks are on one XCD (deal_block), up to
+// kHomeHeads heads.  A block
 // finds its head without a word of its arguments, and whether it is at home is known when this is compiled: with a division by
 // n_splits and a test beside each store launches took 0.2 to 0.4 us longer (12 heads of 129 pages 9.2 and 9.0 us; at home, 8 of
 // 65 6.2 and 5.9, 8 of 33 5.6 and 5.1).
-constexpr int kHeadRows = 1 << 15;
+constexpr int kHeadRows = 1 << 15, kHomeHeads = 65535 * kXcds;
 template <int DT, int NW, bool PAST, bool HOME>
 __device__ __forceinline__ void attn_of(AttnArgs a, int head, int split) {
   extern __shared__ __attribute__((aligned(16))) float attn_lds[];
@@ -72,7 +73,8 @@ void launch_attn(const Dims& d, const PoolDesc& pd, const AttnIO& io, Geom g, hi
   a.out = io.out; a.g = g; a.n_kv = d.n_kv; a.G = d.G; a.k = d.k; a.status = io.status; a.tstamp = io.tstamp;
   a.heads = heads;
   const int n_there = n_att - d.k + g.k_eff;
-  a.home = a.n_splits > 1 && a.n_splits <= 2 * kMaxWaitingHome && heads_at_home(d, heads, (a.n_splits + 1) / 2, (double)n_there * UNIT_BYTES, true);
+  a.home = a.n_splits > 1 && a.n_splits <= 2 * kMaxWaitingHome && heads <= kHomeHeads &&
+           heads_at_home(d, heads, (a.n_splits + 1) / 2, (double)n_there * UNIT_BYTES, true);
   const dim3 grid = a.home ? dim3(kXcds, a.n_splits, by_xcd(heads) / kXcds) : dim3(a.n_splits, std::min(heads, kHeadRows), (heads + kHeadRows - 1) / kHeadRows);
   constexpr int NW = 4;
   const size_t lds = attn_lds_floats(NW, d.G) * sizeof(float);

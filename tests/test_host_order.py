@@ -293,6 +293,16 @@ def test_attention_by_itself_at_home(play, heads, pages, home):
     assert ("home_attn_kernel" in op[1]) == home
 
 
+@pytest.mark.parametrize("batch,home", [(65535, True), (65536, False)])
+def test_attention_by_itself_of_more_heads_than_its_grid_at_home_can_have(play, batch, home):
+    """Eight KV heads a request, a budget of two blocks a head: at home a grid dimension counts the heads by eight and ends at 65535."""
+    o = play([("load", 0, 40), ("attend", 0)], n_layers=1, batch=batch, n_q_heads=8, n_kv_heads=8, max_ctx=64, budget_tokens=300 * 32, placement=0)
+    assert o.rc == [0, 0]
+    (op,) = o.launches(1, "attn_kernel")
+    x, y, z = (int(v) for v in o.ops[op][4].split("x"))
+    assert ("home_attn_kernel" in o.ops[op][1]) == home and x * y * z >= batch * 8 * 2 and max(y, z) <= 65535
+
+
 @pytest.mark.parametrize("heads,candidates,pages,scoring,splits", [
     (36, 480, 129, 4, 7), (40, 480, 129, 8, 8),              # 504 blocks are there at once, 520 are not
     (72, 100, 65, 1, 3), (76, 100, 65, 4, 4),                # 504, 532
