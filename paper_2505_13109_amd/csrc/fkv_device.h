@@ -129,37 +129,45 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) { return wave_reduc
 // (in a quad by permutation, in a row of 16 lanes by rotation, over the rows by the row-swapping moves)
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false); }
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128, DPP_HALF_MIRROR = 0x141, DPP_BCAST = 0x150;
-// lane LANE's value of each row of 16 lanes
-template <int LANE>
-__device__ __forceinline__ double row_bcast_f64(double v) {
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128, DPP_HALF_MIRROR = 0x141;
+// a lane's value, for all of them
+__device__ __forceinline__ double lane_f64(double v, int lane) {
   const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-  return __builtin_bit_cast(double, (unsigned long long)dpp_u32<DPP_BCAST + LANE>((uint32_t)(u >> 32)) << 32 | dpp_u32<DPP_BCAST + LANE>((uint32_t)u));
+  return __builtin_bit_cast(double, (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane) << 32 |
+                                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane));
 }
+// ... of a row of 16 lanes, and of the wave
 template <int M, typename OP>
-__device__ __forceinline__ uint32_t class_reduce(uint32_t v, OP op) {
+__device__ __forceinline__ uint32_t class_reduce_row(uint32_t v, OP op) {
   static_assert(M == 1 || M == 2 || M == 4 || M == 8, "");
   if (M <= 1) v = op(v, dpp_u32<DPP_XOR1>(v));
   if (M <= 2) v = op(v, dpp_u32<DPP_XOR2>(v));
   if (M <= 4) v = op(v, dpp_u32<DPP_ROR4>(v));
-  v = op(v, dpp_u32<DPP_ROR8>(v));
+  return op(v, dpp_u32<DPP_ROR8>(v));
+}
+template <int M, typename OP>
+__device__ __forceinline__ uint32_t class_reduce(uint32_t v, OP op) {
+  v = class_reduce_row<M>(v, op);
   const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
   v = op(a[0], a[1]);
   const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
   return op(b[0], b[1]);
 }
+// over eight adjacent lanes: every lane ends with their result
+template <typename OP>
+__device__ __forceinline__ uint32_t reduce8(uint32_t v, OP op) {
+  v = op(v, dpp_u32<DPP_XOR1>(v));
+  v = op(v, dpp_u32<DPP_XOR2>(v));
+  return op(v, dpp_u32<DPP_HALF_MIRROR>(v));
+}
 // sum over the wave of values below 2^48, as two sums of 24-bit halves so that no 32-bit lane sum overflows
 __device__ __forceinline__ unsigned long long wave_sum_u48(unsigned long long v) {
   return (unsigned long long)class_reduce<1>((uint32_t)(v & 0xffffffu), OpAddU32()) + ((unsigned long long)class_reduce<1>((uint32_t)(v >> 24), OpAddU32()) << 24);
 }
-// the same over the lanes that are equal modulo 8
-__device__ __forceinline__ unsigned long long class8_sum_u48(unsigned long long v) {
-  return (unsigned long long)class_reduce<8>((uint32_t)(v & 0xffffffu), OpAddU32()) + ((unsigned long long)class_reduce<8>((uint32_t)(v >> 24), OpAddU32()) << 24);
-}
-// v[g]: a lane's value for class g.  Lane l ends with op over all lanes of v[l % M].  A step that joins two lanes also halves the
-// classes that each of them goes on with (M = 4: 15 instructions; four reductions one after the other take 24).
+// v[g]: a lane's value for class g.  Lane l ends with op over its row's lanes of v[l % M].  A step that joins two lanes also halves the
+// classes that each of them goes on with.
 template <int M, typename OP>
-__device__ __forceinline__ uint32_t class_fold(const uint32_t (&v)[M], OP op) {
+__device__ __forceinline__ uint32_t class_fold_row(const uint32_t (&v)[M], OP op) {
   const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   uint32_t x[M];
 #pragma unroll
@@ -178,7 +186,7 @@ __device__ __forceinline__ uint32_t class_fold(const uint32_t (&v)[M], OP op) {
     const bool up = lane & 4u;                          // (a rotation by 4 flips this bit)
     x[0] = op(up ? x[1] : x[0], dpp_u32<DPP_ROR4>(up ? x[0] : x[1]));
   }
-  return class_reduce<M>(x[0], op);
+  return class_reduce_row<M>(x[0], op);
 }
 
 // sum of an fp64 value over the wave, valid in lane 63 (a DPP step moves the two halves)

@@ -128,6 +128,10 @@ __device__ __forceinline__ void layer_step(const LayerConst* consts, const uint1
   Selected got = Selected::NOTHING;
   AttnLeft left{};
   const bool step = (int)blockIdx.y < u.step_rows;
+  const auto again = [] {
+    const LayerKernelArgs ka = args_from_memory<LayerKernelArgs>();
+    return LayerSetup<HOSTPOOL, HOME>(ka).step_args(ka);
+  };
   if (step) {
     s = u.step_args(ka);
     bool go_on = false;
@@ -135,7 +139,7 @@ __device__ __forceinline__ void layer_step(const LayerConst* consts, const uint1
     step_roles<DT, G, (STREAM & STREAM_SUMMARIES) != 0>(s, blockIdx.x, blockIdx.y, [&](int m, int slice) {
       head = m;
       own = slice;
-      go_on = select_begin<G, true>(s, m, slice, dyn_lds, nw, got);
+      go_on = select_begin<G, true>(s, m, slice, dyn_lds, nw, got, again);
     });
     if (!go_on) return;
   } else {
@@ -149,19 +153,15 @@ __device__ __forceinline__ void layer_step(const LayerConst* consts, const uint1
     if (__builtin_expect(!left.any(), 1)) return;
     // What follows is hardly ever run.  Its arguments come from memory once more: kept up to here they would cost the page
     // loop registers.
-    const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-    s = LayerSetup<HOSTPOOL, HOME>(again).step_args(again);
+    s = again();
     if (left.ids) lds_barrier();                             // (the LDS is free)
   }
   if (step || left.ids) {
-    select_finish<DT, G, true>(s, head, own, dyn_lds, nw, got, [] {
-      const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-      return LayerSetup<HOSTPOOL, HOME>(again).step_args(again);
-    });
+    select_finish<DT, G, true>(s, head, own, dyn_lds, nw, got, again);
   }
   if (step) return;
-  const LayerKernelArgs again = args_from_memory<LayerKernelArgs>();
-  attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL, HOME>(again).attn_args(again, G), own, head, left);
+  const LayerKernelArgs args = args_from_memory<LayerKernelArgs>();
+  attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL, HOME>(args).attn_args(args, G), own, head, left);
 }
 
 // STREAM: STREAM_* bits.  home_: a head's blocks on one XCD; two kernels, as in fkv_step_dev.h (8 heads x 992 candidates 8.5 us with a

@@ -65,8 +65,12 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
   if (head >= a.heads) return;
   int nw;
   Selected got;
-  if (select_begin<G, false>(a, head, s, dyn_lds, nw, got)) 
-    select_finish<0, G, false>(a, head, s, dyn_lds, nw, got, [] { return args_from_memory<StepArgs>(); });
+  const auto again = [] {
+    StepArgs b = args_from_memory<StepArgs>();
+    b.home = HOME;
+    return b;
+  };
+  if (select_begin<G, false>(a, head, s, dyn_lds, nw, got, again)) select_finish<0, G, false>(a, head, s, dyn_lds, nw, got, again);
 }
 
 constexpr size_t kLdsPerUnit = 150 * 1024;   // of the 160 KiB of a compute unit

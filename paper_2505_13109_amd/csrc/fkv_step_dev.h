@@ -29,17 +29,14 @@
 
 namespace fkv {
 
-#define FKV_STAMP(a, head, i) do { if ((a).tstamp && (head) == 0 && threadIdx.x == 0) (a).tstamp[i] = wall_clock64(); } while (0)
+#define FKV_STAMP(a, head, i) do { if (__builtin_expect((a).tstamp != nullptr, 0) && (head) == 0 && threadIdx.x == 0) (a).tstamp[i] = wall_clock64(); } while (0)
 
 #ifndef FKV_STEP_THREADS
 #define FKV_STEP_THREADS 512
 #endif
-#ifndef FKV_SCORE_PASSES
-#define FKV_SCORE_PASSES 4
-#endif
 constexpr int STEP_THREADS = FKV_STEP_THREADS;         // >= 256 (the radix histograms have 256 bins)
 constexpr int STEP_WAVES = STEP_THREADS / 64;
-constexpr int SCORE_PASSES = FKV_SCORE_PASSES;         // most passes a scoring block can make (StepArgs::passes <= this)
+constexpr int SCORE_PASSES = 4;                        // most passes a scoring block can make (StepArgs::passes <= this)
 constexpr int PAGES_PER_PASS = STEP_WAVES * 4;         // a wave scores 4 pages per pass
 constexpr int MAX_SLICES = 16;                         // most blocks that share one head's selection
 constexpr int SCAN_WAVES = 4;                          // of a block of the scan
@@ -78,7 +75,7 @@ struct StepArgs {
   int passes;                // passes a scoring block makes (1 .. SCORE_PASSES)
   int slices, slices_log2;   // selecting blocks of a KV head (1 .. MAX_SLICES, a power of two)
   int slice;                 // candidates of each (the last may have fewer)
-  unsigned long long* exch;  // [heads][MAX_SLICES][2 * MAX_G] tagged: what a head's selecting blocks tell each other
+  unsigned long long* exch;  // [heads][2 (halves)][MAX_G][MAX_SLICES] tagged: the softmax sums that a head's selecting blocks tell each other
   unsigned long long* keyx;  // [heads][max_pages] tagged: keys and page ids of each block's best candidates, for the head's
   unsigned long long* keyid; // last selecting block
   unsigned long long* cmax;  // the chunks' largest weights, [heads][cmax_stride] tagged, or (where P is plain) [heads][cmax_plain_stride]
@@ -367,22 +364,27 @@ __device__ __forceinline__ double div_by_group(double a) {
   return __builtin_fma(__builtin_fma(-(double)G, q, a), y, q);
 }
 
-// pooled score of one candidate from the G per-head values e[] (softmax numerators, or the bits of
-// the weights themselves), mode = FKV_POOL_*; zd = the heads' integer sums Z, zr = RN(1 / Z)
+// the method's score of a candidate: the mean of its G softmax values, from their numerators e, the heads' integer sums Z and RN(1 / Z)
+template <int G>
+__device__ __forceinline__ float mean_score(const uint32_t* e, const double* zd, const double* zr) {
+  double acc = div_rn((double)e[0], zd[0], zr[0]);
+#pragma unroll
+  for (int gg = 1; gg < G; ++gg) acc = acc + div_rn((double)e[gg], zd[gg], zr[gg]);
+  return (float)div_by_group<G>(acc);
+}
+// ... and by the other modes (FKV_POOL_*): the largest softmax value, in fp64; mean or maximum of the weights themselves (e: their bits) in
+// fp32, head order; the pooled query's weight
 template <int G>
 __device__ __forceinline__ float pooled_score(const uint32_t* e, const double* zd, const double* zr, int mode) {
-  if (mode <= 1) {
-    // mean (the method) or maximum over the group of the softmax values, in fp64
-    double acc = div_rn((double)e[0], zd[0], zr[0]);
+  if (mode == 1) {
+    double most = div_rn((double)e[0], zd[0], zr[0]);
 #pragma unroll
     for (int gg = 1; gg < G; ++gg) {
       const double sg = div_rn((double)e[gg], zd[gg], zr[gg]);
-      if (mode == 0) acc = acc + sg;
-      else acc = sg > acc ? sg : acc;
+      most = sg > most ? sg : most;
     }
-    return mode == 0 ? (float)div_by_group<G>(acc) : (float)acc;
+    return (float)most;
   }
-  // mean or maximum of the weights themselves in fp32, head order; or the pooled query's weight
   float acc = __uint_as_float(e[0]);
 #pragma unroll
   for (int gg = 1; gg < G; ++gg) {
@@ -400,9 +402,10 @@ __device__ __forceinline__ float pooled_score(const uint32_t* e, const double* z
 // last group finds the head's.  A head's groups, dealt as deal_block says, wait for each other and for scoring blocks (lower
 // indices) only, and for neither of them for long (PATIENCE).
 //
-// What bounds it: a chain of short phases.  A wave issues an instruction that depends on the one before every 8 cycles, an LDS
-// round trip takes 62, a trip between blocks 0.2 us and more (st_tag); so what counts is the number of dependent instructions and
-// of barriers.  A group is 8 waves, two to a SIMD, which fill each other's gaps (4 waves with twice
+// What bounds it: a chain of short phases.  A wave issues an instruction every 4 cycles, a value takes 28 from the vector unit through
+// a scalar and back, a branch 24 to 55, an LDS round trip 57, a trip between blocks 0.2 us and more (st_tag); so what counts is the
+// number of dependent instructions, of branches and of barriers (see topk_items, and select_rows for what is told apart once instead of
+// beside each row of candidates).  A group is 8 waves, two to a SIMD, which fill each other's gaps (4 waves with twice
 // the candidates each: 1 us more of a 10 us layer-step), and waves without a candidate end at once.  A long list is shared
 // (selection_slices); each exchange costs its trip and the barriers around it.
 // TAGGED: the weights come from scoring blocks of this launch; else from a launch that has ended.
@@ -417,6 +420,7 @@ __host__ __device__ constexpr int handed_on(int slices, int slice, int kk) {
   return (slices - 1) * slice <= SEL_OTHERS * SEL_THREADS || slice < kk ? slice : kk;
 }
 constexpr int TOPK_BINS = 512;
+constexpr uint32_t kNoSum = 1u << 28;                    // in place of a sum: a wave has not seen its weights
 // how far a group got: it has to make the keys alone; the keys of all that may be chosen are in LDS; the ids are out
 enum class Selected : int { NOTHING, KEYS, IDS };
 
@@ -424,13 +428,15 @@ enum class Selected : int { NOTHING, KEYS, IDS };
 __host__ __device__ constexpr int select_key_words(int n) { return n > 0 ? (n + 3) & ~3 : 4; }
 
 struct TopkBins { uint32_t top, shift; };
+constexpr int SEL_ROWS = SEL_WAVES * 4;                 // rows of 16 lanes
 struct alignas(16) SelectLds {
-  uint32_t hist[TOPK_BINS];
-  unsigned long long list[64];
+  uint32_t hist[TOPK_BINS + 64];                         // (and counters for threads without a candidate)
+  uint32_t list[128];                                    // (and a place for lanes that have nothing to put on it)
+  uint32_t count[64];
+  float mx_row[MAX_G][SEL_ROWS];                         // by query head and row of 16 lanes
+  uint2 z_row[MAX_G][SEL_ROWS];
   unsigned long long z[SEL_WAVES][MAX_G];
   float mx[SEL_WAVES][MAX_G];
-  uint32_t count[64];
-  uint32_t more[SEL_WAVES][64];
   uint32_t scan[SEL_WAVES];
   uint32_t n_list;
   TopkBins bins;                                         // of scores that are not softmax values
@@ -472,87 +478,95 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t want, ui
   before = (uint32_t)__builtin_amdgcn_readlane((int)at, f) - in_bin;
 }
 
-// The best kk of a group's items, ties to the lower one in order: emit(pos, slot) is called by the thread that holds a chosen
-// one, pos = 0 .. kk - 1 in order.  A thread holds items key[u] in slots 0 .. first - 1 and A .. A + second - 1 (the same in the
-// whole group), where bit u of `have` is set; the order is by slot, then by thread; (first + second) * nw <= 64.  n: items of
-// the group.  Before the call (and a barrier): sm.hist holds the counts of the
-// keys' bins, sm.n_list and sm.more are 0.
-// The keys of the one bin that is only partly wanted are collected and ranked against each other, with their places in the
-// order, by every wave; the same barrier brings the counts per wave of what is chosen anyway.  False, and nothing done, if there
-// are more than 64 of them (ties, mostly).
-template <int A, int R, typename Emit>
-__device__ __forceinline__ bool topk_items(const uint32_t (&key)[R], uint32_t have, int first, int second, int n, int kk, TopkBins bins, int nw,
-                                           SelectLds& sm, Emit emit) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
-  // f(slot, row) for every slot in use (a branch over each unused one would cost more than the work of a used one)
-  auto rows = [&](auto f) {
-#pragma unroll
-    for (int u = 0; u < A; ++u) {
-      if (u >= first) break;
-      f(u, u);
-    }
-#pragma unroll
-    for (int u = A; u < R; ++u) {
-      if (u - A >= second) break;
-      f(u, first + u - A);
-    }
-  };
-  uint32_t pick = have, take = 0, in_bin = 0;        // bits of the chosen slots; how many of the listed keys are wanted
+// The best kk of a group's items, ties to the lower one in order.  A thread holds items key[u] (0: none), u < T; the order is by u,
+// then by thread; T * nw <= 64.  emit(u, chosen, pos): the lanes of the mask `chosen` hold chosen items in slot u, in the order pos = 0 ..
+// kk - 1.  n: items of the group.  Before the call (and a barrier): sm.hist holds the counts of the keys' bins, sm.n_list is 0.
+// The keys of the one bin that is only partly wanted are collected with their places in the order -- what is left of a key in a bin, and
+// the place, fit 32 bits -- and ranked against each other by every wave; the same barrier brings the counts per wave of what is chosen
+// anyway, and which of the others are chosen is the same in every wave.  False, and nothing done, if there are more than 64 of them (ties,
+// mostly) or they are of the last bin, which is as wide as it takes.
+// The chain is what counts (a wave by itself: an instruction 4 cycles, a value that goes from the vector unit through a scalar and back 28,
+// a branch that is not taken 24 and one that is 38, one by a lane's condition 55, an LDS trip 57): so everything is done for all T slots at
+// once, by masks, and what a lane has no use for goes to a place that nobody reads -- a place of its own, since lanes queue up for one
+// word (512 atomics on one counter take 1090 cycles, on 32 of them 120).  From the weights to the ids, with the slots in loops over those
+// in use and the poolings told apart beside each, and so: 97 candidates, G = 4, 2.5 and 1.8 us; 992 3.8 and 3.0; 2015 in eight blocks, G = 8,
+// 6.0 and 4.9; layer-steps of 96 candidates, G = 7, all heads corrected 11.0 and 10.1.
+template <int T, typename Emit>
+__device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int kk, TopkBins bins, int nw, SelectLds& sm, Emit emit) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t above = 0, from = 0, base = 0;            // keys > above are chosen; those > from, up to there, if their turn comes
+  uint32_t take = 0, in_bin = 0;                     // how many of these are wanted
   bool ranked = false;
   if (kk < n) {
     uint32_t bin, before;
     find_bin(sm.hist, (uint32_t)kk, bin, before, in_bin);
     take = (uint32_t)kk - before;
     ranked = take != in_bin;
-    if (__builtin_expect(ranked && in_bin > 64, 0)) return false;
-    const uint32_t up_to = ranked ? bin : bin + 1;   // keys of lower bins are chosen
-    pick = 0;
-    uint32_t* n_list = &sm.n_list;
-    asm volatile("" : "+v"(n_list));                 // (an atomic of each lane: one for the wave would be a longer chain)
-    rows([&](int u, int row) {
-      const uint32_t b = (have >> u & 1u) ? topk_bin(key[u], bins) : TOPK_BINS;
-      pick |= b < up_to ? 1u << u : 0u;
-      if (ranked && b == bin) sm.list[atomicAdd(n_list, 1u)] = (unsigned long long)key[u] << 32 | ~(uint32_t)(row * nt + tid);
-    });
+    const int tail = bin == TOPK_BINS - 1;
+    if (__builtin_expect(((int)ranked & ((int)(in_bin > 64) | tail)) != 0, 0)) return false;
+    base = bins.top - (bin << bins.shift);           // (the bin of a key: at most that, since topk_bin takes what is above `top` as `top`)
+    const uint32_t end = (bin + 1) << bins.shift;
+    from = (tail | (int)(end > bins.top)) != 0 ? 0u : bins.top - end;
+    above = !ranked ? from : bin == 0 ? ~0u : base;
   }
-  rows([&](int u, int row) {
-    const uint32_t c = (uint32_t)__popcll(__ballot(pick >> u & 1u));
-    if (lane == 0) sm.count[row * nw + wave] = c;
-  });
-  lds_barrier();
-  uint32_t cnt = lane < (first + second) * nw ? sm.count[lane] : 0u;
-  if (ranked) {
-    const unsigned long long mine = lane < (int)in_bin ? sm.list[lane] : 0ull;      // a list entry a lane
-    uint32_t above = 0;
-#pragma unroll 1
-    for (uint32_t i = 0; i < in_bin; i += 4) {
+  static_assert(T * SEL_WAVES <= 64 && T * SEL_THREADS <= 4096 && 19 + 12 < 32, "");
+  unsigned long long sure[T], maybe[T];
+  uint32_t counts = 0;
 #pragma unroll
-      for (uint32_t v = 0; v < 4; ++v) {             // (lanes without an entry have 0, which is above none)
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), (int)(i + v));
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, (int)(i + v));
-        above += ((unsigned long long)hi << 32 | lo) > mine ? 1u : 0u;
+  for (int u = 0; u < T; ++u) {
+    sure[u] = __ballot(key[u] > above);
+    const uint32_t c = (uint32_t)__popcll(sure[u]);
+    counts = u == 0 || lane == u ? c : counts;       // (lane u: slot u's)
+  }
+  auto rank_of = [&](int u) { return ((base - min(key[u], base)) << 12) + (uint32_t)(u * nw * 64 + tid); };
+  if (ranked) {
+    uint32_t mine = 0;
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+      maybe[u] = __ballot(key[u] > from) & ~sure[u];
+      mine += key[u] > from && !(key[u] > above) ? 1u : 0u;
+    }
+    if (mine != 0) {
+      // (an atomic of each lane that has some: one for the wave would be a longer chain, and lanes queue up for one address)
+      auto* n_list = (__attribute__((address_space(3))) uint32_t*)&sm.n_list;
+      asm volatile("" : "+v"(n_list));
+      uint32_t at = __hip_atomic_fetch_add(n_list, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+      for (int u = 0; u < T; ++u) {
+        const bool in = key[u] > from && !(key[u] > above);
+        sm.list[in ? at : 64u + (uint32_t)lane] = rank_of(u);
+        at += in ? 1u : 0u;
       }
     }
-    // the chosen ones, up to the least: counted in the rows and waves where they are (by each wave for itself)
-    const bool listed = lane < (int)in_bin;
-    if (listed && above < take) atomicAdd(&sm.more[wave][~(uint32_t)mine >> 6], 1u);
-    const int least = __builtin_ctzll(__ballot(listed && above == take - 1));
-    const unsigned long long floor = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), least) << 32 |
-                                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, least);
-    pick = 0;
-    rows([&](int u, int row) {
-      const unsigned long long at = (unsigned long long)key[u] << 32 | ~(uint32_t)(row * nt + tid);
-      pick |= (have >> u & 1u) && at >= floor ? 1u << u : 0u;
-    });
-    cnt += sm.more[wave][lane];
   }
-  const uint32_t excl = wave_scan_u32(cnt) - cnt;
-  rows([&](int u, int row) {
-    const bool chosen = (pick >> u & 1u) != 0;
-    const unsigned long long b = __ballot(chosen);
-    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, (uint32_t)__builtin_amdgcn_readlane((int)excl, row * nw + wave)));
-    if (chosen) emit((int)pos, u);
-  });
+  sm.count[lane < T ? lane * nw + wave : wave] = counts;                      // (lanes from T on repeat slot 0's)
+  lds_barrier();
+  uint32_t cnt = sm.count[lane];
+  cnt = lane < T * nw ? cnt : 0u;
+  unsigned long long picked = 0;                     // of the list
+  uint32_t entry = ~0u, last = 0;
+  if (ranked) {
+    entry = sm.list[lane];                           // an entry a lane
+    entry = lane < (int)in_bin ? entry : ~0u;
+    uint32_t before = 0;
+#pragma unroll 1
+    for (uint32_t i = 0; i < in_bin; i += 8) {
+#pragma unroll
+      for (uint32_t v = 0; v < 8; ++v) before += (uint32_t)__builtin_amdgcn_readlane((int)entry, (int)(i + v)) < entry ? 1u : 0u;
+    }
+    last = (uint32_t)__builtin_amdgcn_readlane((int)entry, __builtin_ctzll(__ballot(before == take - 1 && lane < (int)in_bin)));
+    picked = __ballot(entry <= last);
+#pragma unroll
+    for (int u = 0; u < T; ++u) sure[u] |= maybe[u] & __ballot(rank_of(u) <= last);
+  }
+  const uint32_t excl = wave_scan_u32(cnt) - cnt, group = (entry & 4095u) >> 6;
+#pragma unroll
+  for (int u = 0; u < T; ++u) {
+    uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)excl, u * nw + wave);
+    if (ranked) first += (uint32_t)__popcll(picked & __ballot(group < (uint32_t)(u * nw + wave)));
+    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(sure[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)sure[u], first));
+    emit(u, sure[u], (int)pos);
+  }
   return true;
 }
 
@@ -575,7 +589,7 @@ __device__ __forceinline__ void block_topk(const uint32_t* key, int n, int kk, T
         if (topk_bin(kj, bins) == bin) sm.list[atomicAdd(&sm.n_list, 1u)] = kj;
       }
       lds_barrier();
-      const uint32_t mine = lane < (int)in_bin ? (uint32_t)sm.list[lane] : 0u;
+      const uint32_t mine = lane < (int)in_bin ? sm.list[lane] : 0u;
       uint32_t above = 0, same = 0;
       for (uint32_t i = 0; i < in_bin; ++i) {
         const uint32_t ki = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)i);
@@ -679,21 +693,20 @@ struct PutId {
 // A wave whose patience ends has nothing to say, and what it would have had to is never put into words under the tag: its
 // group learns of it at the next barrier, from a value no sum has or a flag, and leaves.  Of the groups only the last one has to
 // end with all the keys, and it can make them alone (alone_keys).  Returns how far the group got.
-// (Ways out that are hardly ever taken, and the other scores, are marked as unlikely: without that the compiler keeps up to twice as
-// many scalars in lanes of vector registers, 0.5 to 2 % of a layer-step.)
-template <int G, bool TAGGED>
+// MEAN: the method's own scores, straight through for U rows of candidates per thread; else any other pooling, U: most rows.  SHARED:
+// there may be several groups (MEAN: there are).
+template <int G, bool TAGGED, bool MEAN, bool SHARED, int U>
 __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, int s, int nw, uint32_t* key_lds, SelectLds& sm) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
   const int n = a.g.n_cand, lo = a.g.cand_lo, kk = a.g.k_eff;
-  const int S = a.slices, j0 = s * a.slice, j1 = min(n, j0 + a.slice);
-  const bool last = s == S - 1;
+  const int S = SHARED ? a.slices : 1, j0 = SHARED ? s * a.slice : 0, j1 = SHARED ? min(n, j0 + a.slice) : n;
+  const bool shared = SHARED && (MEAN || S > 1), last = !SHARED || s == S - 1;
   const uint32_t tag = launch_tag(a.no);
-  const int mode = a.sel_pool;                         // FKV_POOL_*
+  const int mode = MEAN ? 0 : a.sel_pool;              // FKV_POOL_*
   const bool soft = mode <= 1;                         // the variants that pool softmax values
   const int ng = mode >= 4 ? 1 : G;                    // weights in use per page (pooled query: the group's first)
-  constexpr int GP = group_pow2(G), REGS = sel_regs_alone(G);
-  for (int i = tid; i < TOPK_BINS; i += nt) sm.hist[i] = 0;
-  sm.more[wave][lane] = 0;
+  constexpr int GP = group_pow2(G);
+  for (int i = tid * 4; i < TOPK_BINS; i += nt * 4) *reinterpret_cast<uint4*>(&sm.hist[i]) = make_uint4(0, 0, 0, 0);
   if (tid == 0) { sm.n_list = 0; sm.alone = 0; }
   // load_and_check() until every lane's words carry the tag; false: patience ended
   auto poll = [&](uint32_t kind, auto load_and_check) {
@@ -705,22 +718,16 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     return (a.impatient & kind) == 0;
   };
   bool failed = false;                                 // this wave's patience ended
-  auto any_failed = [&]() {                            // (by way of a barrier)
-    if (lane == 0) sm.failed[wave] = failed ? 1 : 0;
-    lds_barrier();
-    return __ballot(sm.failed[min(lane, nw - 1)] != 0) != 0;
-  };
 
   // ---- this group's weights: thread t has candidates j0 + t + u * nt; in a shared selection, wave w also reads its part of the
   // largest weights of the head's chunks: 64w + l, 512 + 64w + l, ... in lane l, which is for head l % GP ----
-  const int U = (j1 - j0 + nt - 1) / nt;               // 1 .. REGS
-  uint32_t e[REGS][G];                                 // bits of the weights, then softmax numerators
+  uint32_t e[U][G];                                    // bits of the weights, then softmax numerators
+  auto ours = [&](int u) { return tid + u * nt < j1 - j0; };
   float largest = -__builtin_inff();
-  const int n_max = soft && S > 1 ? a.chunks * (TAGGED ? 1 : SCAN_WAVES) * GP : 0;
+  const int n_max = shared && soft ? a.chunks * (TAGGED ? 1 : SCAN_WAVES) * GP : 0;
   const size_t max0 = head * (TAGGED ? cmax_stride(a.max_pages) : cmax_plain_stride(a.max_pages));
   const int past = max(0, (lane & (GP - 1)) - (G - 1));        // (lanes of no head read the last one's)
   auto max_at = [&](int i) { return max0 + (i + tid < n_max ? i + tid : lane & (GP - 1)) - past; };
-  auto ours = [&](int u) { return j0 + tid + u * nt < j1; };
   // UC rows of candidates from row u0 on.  (All of a poll's loads are issued before the first is looked at: one trip.  Not all
   // rows at a time, because a word takes two registers.)
   auto weights = [&](auto from, auto uc) {
@@ -733,7 +740,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     if (TAGGED) {
       const bool maxima = u0 == 0 && n_max > 0;
       failed = !poll(WAIT_WEIGHTS | (maxima ? WAIT_MAXIMA : 0u), [&]() {
-        bool ok = true;
+        uint32_t off = 0;                              // (not 0: a tag is another)
         unsigned long long w[UC][G], m = 0;
 #pragma unroll
         for (int u = 0; u < UC; ++u)
@@ -745,13 +752,13 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
 #pragma unroll
           for (int gg = 0; gg < G; ++gg) {
             e[u0 + u][gg] = (uint32_t)w[u][gg];
-            ok = ok & ((uint32_t)(w[u][gg] >> 32) == tag);
+            off |= (uint32_t)(w[u][gg] >> 32) ^ tag;
           }
         if (maxima) {
-          ok = ok & ((uint32_t)(m >> 32) == tag);
+          off |= (uint32_t)(m >> 32) ^ tag;
           largest = __uint_as_float((uint32_t)m);
         }
-        return ok;
+        return off == 0;
       }) || failed;
     } else {
 #pragma unroll
@@ -760,16 +767,22 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
         for (int gg = 0; gg < G; ++gg) e[u0 + u][gg] = __float_as_uint((reinterpret_cast<const float*>(a.P) + base)[at[u] + gg * row]);
     }
   };
-  if (U == 1) {
+  static_assert(U == 1 || U == 2 || U == 4 || U == 8, "");
+  if constexpr (U == 1) {
     weights(UnrollBy<0>{}, UnrollBy<1>{});
-  } else if (U == 2) {
+  } else if constexpr (U == 2) {
     weights(UnrollBy<0>{}, UnrollBy<2>{});
-  } else if constexpr (REGS == 8) {
-    weights(UnrollBy<0>{}, UnrollBy<4>{});
-    if (U > 4) weights(UnrollBy<4>{}, UnrollBy<4>{});
-  } else {
+  } else if constexpr (U == 4) {
     weights(UnrollBy<0>{}, UnrollBy<2>{});
     weights(UnrollBy<2>{}, UnrollBy<2>{});
+  } else {
+    weights(UnrollBy<0>{}, UnrollBy<4>{});
+    if (4 * nt < j1 - j0) weights(UnrollBy<4>{}, UnrollBy<4>{});
+    else
+#pragma unroll
+      for (int u = 4; u < U; ++u)
+#pragma unroll
+        for (int gg = 0; gg < G; ++gg) e[u][gg] = e[0][gg];
   }
   if (TAGGED) {
     for (int i = nt; i < n_max && !failed; i += nt) {
@@ -781,181 +794,165 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     for (int i = 0; i < n_max; i += 2 * nt)
       largest = fmaxf(largest, fmaxf(reinterpret_cast<const float*>(a.cmax)[max_at(i)], reinterpret_cast<const float*>(a.cmax)[max_at(i + nt)]));
   }
-  static_assert(REGS == (G <= 3 ? 8 : 4) && SEL_REGS == 4, "");
   FKV_STAMP(a, head, 2);
 
-  // ---- fixed-point softmax: the head's maxima, numerators, integer denominators ----
+  // ---- fixed-point softmax: the head's maxima, numerators, integer denominators.  What the group's rows of 16 lanes have found goes
+  // through LDS; eight lanes then put a query head's together (the lanes of no head repeat the last one's). ----
   TopkBins bins = kSoftBins;
   double zd[G], zr[G];
 #pragma unroll
   for (int gg = 0; gg < G; ++gg) zd[gg] = zr[gg] = 1.0;
+  const int of_row = wave * 4 + (lane >> 4), gl = min(lane >> 3, G - 1), wl = lane & 7;
   if (__builtin_expect(soft, 1)) {
-    unsigned long long* const mine = a.exch + ((size_t)head * MAX_SLICES + s) * 2 * MAX_G;
-    const unsigned long long* const all = a.exch + (size_t)head * MAX_SLICES * 2 * MAX_G;
-    if (S > 1) {
-      largest = __uint_as_float(class_reduce<GP>(__float_as_uint(largest), OpMaxF32()));
+    if (shared) {
+      largest = __uint_as_float(class_reduce_row<GP>(__float_as_uint(largest), OpMaxF32()));
     } else {                                           // (a thread without a candidate repeats the last one)
       uint32_t v[GP];
 #pragma unroll
       for (int gg = 0; gg < GP; ++gg) v[gg] = gg < G ? e[0][gg < G ? gg : 0] : 0u;
 #pragma unroll
-      for (int u = 1; u < REGS; ++u) {
-        if (u >= U) break;
+      for (int u = 1; u < U; ++u)
 #pragma unroll
         for (int gg = 0; gg < G; ++gg) v[gg] = OpMaxF32()(v[gg], e[u][gg]);
-      }
-      largest = __uint_as_float(class_fold<GP>(v, OpMaxF32()));
+      largest = __uint_as_float(class_fold_row<GP>(v, OpMaxF32()));
     }
-    if (lane < MAX_G) sm.mx[wave][lane] = largest;     // lane l: of head l % GP
+    sm.mx_row[lane & (GP - 1)][of_row] = largest;
     lds_barrier();
-    largest = sm.mx[min(lane >> 3, nw - 1)][lane & 7];
-    largest = __uint_as_float(class_reduce<8>(__float_as_uint(largest), OpMaxF32()));
-    FKV_STAMP(a, head, 3);
-    uint32_t zl[GP], zh[GP];                           // a thread's sums, in 16-bit halves
+    const float4 m4 = *reinterpret_cast<const float4*>(&sm.mx_row[gl][min(wl, nw - 1) * 4]);
+    largest = __uint_as_float(reduce8(__float_as_uint(fmaxf(fmaxf(m4.x, m4.y), fmaxf(m4.z, m4.w))), OpMaxF32()));
+    uint32_t zl[GP], zh[GP];                           // a thread's sums, in 16-bit halves (sums of a head's halves are below 2^32)
     typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
     float mx[G];
 #pragma unroll
     for (int gg = 0; gg < GP; ++gg) zl[gg] = zh[gg] = 0;
 #pragma unroll
-    for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(largest), gg));
+    for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(largest), gg * 8));
 #pragma unroll
-    for (int u = 0; u < REGS; ++u) {
-      if (u >= U) break;
-      if (ours(u)) {
+    for (int u = 0; u < U; ++u) {
 #pragma unroll
-        for (int gg = 0; gg < G; ++gg) {
-          e[u][gg] = softmax_fixed(__uint_as_float(e[u][gg]), mx[gg]);
-          const u16x2 c = __builtin_bit_cast(u16x2, e[u][gg]);
-          zl[gg] = __builtin_amdgcn_udot2(c, u16x2{1, 0}, zl[gg], false);
-          zh[gg] = __builtin_amdgcn_udot2(c, u16x2{0, 1}, zh[gg], false);
-        }
+      for (int gg = 0; gg < G; ++gg) {
+        const uint32_t en = softmax_fixed(__uint_as_float(e[u][gg]), mx[gg]);
+        e[u][gg] = ours(u) ? en : 0u;
+        const u16x2 c = __builtin_bit_cast(u16x2, e[u][gg]);
+        zl[gg] = __builtin_amdgcn_udot2(c, u16x2{1, 0}, zl[gg], false);
+        zh[gg] = __builtin_amdgcn_udot2(c, u16x2{0, 1}, zh[gg], false);
       }
     }
-    // (sums of a head are below 2^46)
-    unsigned long long z = (unsigned long long)class_fold<GP>(zl, OpAddU32()) + ((unsigned long long)class_fold<GP>(zh, OpAddU32()) << 16);
-    if (failed) z = 1ull << 47;
-    if (lane < MAX_G) sm.z[wave][lane] = z;
+    // (a group's upper halves come to 2^28 at most if one of its waves has not seen its weights, else to 2^27)
+    uint2 z = make_uint2(class_fold_row<GP>(zl, OpAddU32()), class_fold_row<GP>(zh, OpAddU32()));
+    if (failed && lane < 16) z.y = kNoSum;
+    sm.z_row[lane & (GP - 1)][of_row] = z;
     lds_barrier();
-    z = class8_sum_u48((lane >> 3) < nw ? sm.z[min(lane >> 3, nw - 1)][lane & 7] : 0ull);
-    if (__builtin_expect(__ballot(z >> 47 != 0) != 0, 0)) return Selected::NOTHING;
-    if (S > 1) {                                       // ... and over the slices: lane 8r + g reads slice r's, r's and r + 8's
-      if (wave == 0 && lane < G) {
-        st_tag(mine + lane, (uint32_t)z, tag, a.home);
-        st_tag(mine + MAX_G + lane, (uint32_t)(z >> 32), tag, a.home);
+    const uint4* const z8 = reinterpret_cast<const uint4*>(&sm.z_row[gl][min(wl, nw - 1) * 4]);
+    const uint4 za = z8[0], zb = z8[1];
+    z = make_uint2((za.x + za.z) + (zb.x + zb.z), (za.y + za.w) + (zb.y + zb.w));
+    z = make_uint2(reduce8(wl < nw ? z.x : 0u, OpAddU32()), reduce8(wl < nw ? z.y : 0u, OpAddU32()));
+    if (__builtin_expect(__ballot(z.y >= kNoSum) != 0, 0)) return Selected::NOTHING;
+    if (shared) {                                      // ... and over the slices: lane 8g + r reads slice r's, r's and r + 8's
+      // (a sum of all slices side by side, as they are read)
+      unsigned long long* const every = a.exch + (size_t)head * EXCH_WORDS + gl * MAX_SLICES;
+      constexpr int UPPER = MAX_G * MAX_SLICES;
+      if (wave == 0 && wl == 0 && lane < 8 * G) {
+        st_tag(every + s, z.x, tag, a.home);
+        st_tag(every + UPPER + s, z.y, tag, a.home);
       }
-      const int gl = min(lane & 7, G - 1), r0 = min(lane >> 3, S - 1), r1 = min((lane >> 3) + 8, S - 1);
+      const unsigned long long* const p0 = every + min(wl, S - 1);
+      const unsigned long long* const p1 = every + min(wl + 8, S - 1);
       unsigned long long w[4];
       failed = !poll(WAIT_SUMS, [&]() {
-        const unsigned long long* p0 = all + (size_t)r0 * 2 * MAX_G + gl;
-        const unsigned long long* p1 = all + (size_t)r1 * 2 * MAX_G + gl;
-        w[0] = ld_tag(p0); w[1] = ld_tag(p0 + MAX_G); w[2] = ld_tag(p1); w[3] = ld_tag(p1 + MAX_G);
-        return ((uint32_t)(w[0] >> 32) == tag) & ((uint32_t)(w[1] >> 32) == tag) & ((uint32_t)(w[2] >> 32) == tag) & ((uint32_t)(w[3] >> 32) == tag);
+        w[0] = ld_tag(p0); w[1] = ld_tag(p0 + UPPER); w[2] = ld_tag(p1); w[3] = ld_tag(p1 + UPPER);
+        return ((((uint32_t)(w[0] >> 32) ^ tag) | ((uint32_t)(w[1] >> 32) ^ tag)) | (((uint32_t)(w[2] >> 32) ^ tag) | ((uint32_t)(w[3] >> 32) ^ tag))) == 0;
       });
-      z = 0;
-      if ((lane >> 3) < S) z += (w[0] & 0xffffffffull) | (w[1] << 32);
-      if ((lane >> 3) + 8 < S) z += (w[2] & 0xffffffffull) | (w[3] << 32);
-      z = class8_sum_u48(z);
+      const bool two = wl + 8 < S;
+      z = make_uint2((uint32_t)w[0] + (two ? (uint32_t)w[2] : 0u), (uint32_t)w[1] + (two ? (uint32_t)w[3] : 0u));
+      z = make_uint2(reduce8(wl < S ? z.x : 0u, OpAddU32()), reduce8(wl < S ? z.y : 0u, OpAddU32()));
     }
-    // one reciprocal per lane, handed to the row's other lanes (as scalars they would need 32 registers that are not there)
-    const double zv = (double)z, yv = reciprocal_near(zv);
-    auto hand = [&](auto gc) {
-      constexpr int gg = decltype(gc)::value;
-      if constexpr (gg < G) { zd[gg] = row_bcast_f64<gg>(zv); zr[gg] = row_bcast_f64<gg>(yv); }
-    };
-    hand(UnrollBy<0>{}); hand(UnrollBy<1>{}); hand(UnrollBy<2>{}); hand(UnrollBy<3>{});
-    hand(UnrollBy<4>{}); hand(UnrollBy<5>{}); hand(UnrollBy<6>{}); hand(UnrollBy<7>{});
+    // one reciprocal per query head
+    const double zv = (double)(((unsigned long long)z.y << 16) + z.x), yv = reciprocal_near(zv);
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      zd[gg] = lane_f64(zv, gg * 8);
+      zr[gg] = lane_f64(yv, gg * 8);
+    }
   } else {
     float most = -__builtin_inff();                    // weight: no score is above it (a thread without a candidate repeats the last one)
 #pragma unroll
-    for (int u = 0; u < REGS; ++u) {
-      if (u >= U) break;
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int gg = 0; gg < G; ++gg) most = fmaxf(most, __uint_as_float(e[u][gg]));
-    }
     sm.mx[wave][0] = wave_max_f32(most);
-    if (__builtin_expect(any_failed(), 0)) return Selected::NOTHING;        // (and behind its barrier the histogram is clear)
+    if (lane == 0) sm.failed[wave] = failed ? 1 : 0;
+    lds_barrier();
+    if (__builtin_expect(__ballot(sm.failed[min(lane, nw - 1)] != 0) != 0, 0)) return Selected::NOTHING;        // (and the histogram is clear)
     bins = bins_below(score_key(wave_max_f32(sm.mx[min(lane, nw - 1)][0])));
     if (tid == 0) sm.bins = bins;
   }
-  FKV_STAMP(a, head, 4);
 
-  // ---- pooled scores -> keys ----
-  uint32_t key[REGS];
-  int id[REGS];
-  uint32_t have = 0;
-#pragma unroll
-  for (int u = 0; u < REGS; ++u) { key[u] = 0; id[u] = lo + j0 + tid + u * nt; }
-#pragma unroll
-  for (int u = 0; u < REGS; ++u) {
-    if (u >= U) break;
-    key[u] = score_key(pooled_score<G>(e[u], zd, zr, mode));
-    if (ours(u)) have |= 1u << u;
-  }
-  auto store_scores = [&]() {                          // (kept for inspection)
-#pragma unroll
-    for (int u = 0; u < REGS; ++u) {
-      if (u >= U) break;
-      if (have >> u & 1u) a.score[(size_t)head * a.max_pages + id[u]] = key_score(key[u]);
-    }
-  };
+  // what the other groups hand on to the last one, and the rows that takes
   unsigned long long* const keyx = a.keyx + (size_t)head * a.max_pages;
   unsigned long long* const keyid = a.keyid + (size_t)head * a.max_pages;
   const int m = handed_on(S, a.slice, kk);
   const bool all = m == a.slice;                       // (then a key's place says whose it is)
-  if (!last && all) {
+  const int others = shared && last ? (S - 1) * m : 0, X = (others + SEL_THREADS - 1) / SEL_THREADS;      // (a group that has others is whole)
+  const bool fits = X <= SEL_OTHERS;
+
+  // ---- pooled scores -> keys (0: no candidate) ----
+  uint32_t key[U];
 #pragma unroll
-    for (int u = 0; u < REGS; ++u) {
-      if (u >= U) break;
-      if ((have >> u & 1u) && !failed) st_tag(keyx + id[u] - lo, key[u], tag, a.home);
-    }
+  for (int u = 0; u < U; ++u) {
+    const uint32_t ku = score_key(MEAN ? mean_score<G>(e[u], zd, zr) : pooled_score<G>(e[u], zd, zr, mode));
+    key[u] = ours(u) ? ku : 0u;
+  }
+  auto id = [&](int u) { return lo + j0 + tid + u * nt; };
+  auto store_scores = [&]() {                          // (kept for inspection: nobody waits for them)
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (ours(u)) a.score[(size_t)head * a.max_pages + id(u)] = key_score(key[u]);
+  };
+  if (shared && !last && all) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (ours(u) && !failed) st_tag(keyx + id(u) - lo, key[u], tag, a.home);
     store_scores();
     return failed ? Selected::NOTHING : Selected::IDS;
   }
-  const int others = last ? (S - 1) * m : 0, X = (others + nt - 1) / nt;       // what the other groups hand on, and its rows
-  const bool fits = X <= SEL_OTHERS;
+  auto count = [&](uint32_t k, bool there) { atomicAdd(&sm.hist[there ? topk_bin(k, bins) : (uint32_t)(TOPK_BINS + lane)], 1u); };
 #pragma unroll
-  for (int u = 0; u < REGS; ++u) {
-    if (u >= U) break;
-    if (have >> u & 1u) {
-      if (!fits) key_lds[others + id[u] - lo - j0] = key[u];
-      atomicAdd(&sm.hist[topk_bin(key[u], bins)], 1u);
-    }
+  for (int u = 0; u < U; ++u) {
+    count(key[u], ours(u));
+    if (shared && !fits && ours(u)) key_lds[others + tid + u * nt] = key[u];
   }
   uint32_t key_of[SEL_OTHERS];                         // the other groups'
   int id_of[SEL_OTHERS];
-  uint32_t have_of = 0;
 #pragma unroll
   for (int x = 0; x < SEL_OTHERS; ++x) { key_of[x] = 0; id_of[x] = 0; }
-  if (S > 1) {
+  if (shared) {
     if (fits) {
       if (X > 0) {
         unsigned long long w[SEL_OTHERS][2];
         const bool ok = poll(WAIT_KEYS, [&]() {
-          bool there = true;
+          uint32_t off = 0;
 #pragma unroll
-          for (int x = 0; x < SEL_OTHERS; ++x) w[x][0] = ld_tag(keyx + min(tid + min(x, X - 1) * nt, others - 1));
+          for (int x = 0; x < SEL_OTHERS; ++x) w[x][0] = ld_tag(keyx + min(tid + min(x, X - 1) * SEL_THREADS, others - 1));
           if (!all) {
 #pragma unroll
-            for (int x = 0; x < SEL_OTHERS; ++x) w[x][1] = ld_tag(keyid + min(tid + min(x, X - 1) * nt, others - 1));
+            for (int x = 0; x < SEL_OTHERS; ++x) w[x][1] = ld_tag(keyid + min(tid + min(x, X - 1) * SEL_THREADS, others - 1));
           }
 #pragma unroll
-          for (int x = 0; x < SEL_OTHERS; ++x) there = there & ((uint32_t)(w[x][0] >> 32) == tag);
+          for (int x = 0; x < SEL_OTHERS; ++x) off |= (uint32_t)(w[x][0] >> 32) ^ tag;
           if (!all) {
 #pragma unroll
-            for (int x = 0; x < SEL_OTHERS; ++x) there = there & ((uint32_t)(w[x][1] >> 32) == tag);
+            for (int x = 0; x < SEL_OTHERS; ++x) off |= (uint32_t)(w[x][1] >> 32) ^ tag;
           }
-          return there;
+          return off == 0;
         });
         failed = failed || !ok;
 #pragma unroll
         for (int x = 0; x < SEL_OTHERS; ++x) {
-          if (x >= X) break;
-          if (tid + x * nt < others) {
-            key_of[x] = (uint32_t)w[x][0];
-            id_of[x] = all ? lo + tid + x * nt : (int)(uint32_t)w[x][1];
-            have_of |= 1u << x;
-            atomicAdd(&sm.hist[topk_bin(key_of[x], bins)], 1u);
-          }
+          const bool there = tid + x * SEL_THREADS < others;
+          key_of[x] = there ? (uint32_t)w[x][0] : 0u;
+          id_of[x] = all ? lo + tid + x * SEL_THREADS : (int)(uint32_t)w[x][1];
+          if (x < X) count(key_of[x], there);
         }
       }
     } else {
@@ -989,41 +986,66 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     if (failed) sm.alone = 1;
   }
   lds_barrier();
-  if (__builtin_expect(S > 1 && sm.alone != 0, 0)) return Selected::NOTHING;
+  if (shared && __builtin_expect(__builtin_amdgcn_readfirstlane(sm.alone) != 0, 0)) return Selected::NOTHING;
   FKV_STAMP(a, head, 5);
-  store_scores();
-  if (__builtin_expect(!fits, 0)) return Selected::KEYS;
+  if (SHARED && __builtin_expect(!fits, 0)) {
+    store_scores();
+    return Selected::KEYS;
+  }
   const PutId put(a, head, key_lds);
   bool done;
-  if (S == 1) {
-    done = topk_items<REGS>(key, have, U, 0, n, kk, bins, nw, sm, [&](int pos, int u) { put(pos, id[u]); });
-  } else {                                             // (U <= SEL_REGS)
-    constexpr int R = SEL_OTHERS + SEL_REGS;
-    uint32_t item[R];
-    int item_id[R];
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-      item[u] = u < SEL_OTHERS ? key_of[u < SEL_OTHERS ? u : 0] : key[u < SEL_OTHERS ? 0 : u - SEL_OTHERS];
-      item_id[u] = u < SEL_OTHERS ? id_of[u < SEL_OTHERS ? u : 0] : id[u < SEL_OTHERS ? 0 : u - SEL_OTHERS];
-    }
-    done = topk_items<SEL_OTHERS>(item, have_of | have << SEL_OTHERS, X, U, others + j1 - j0, kk, bins, nw, sm, [&](int pos, int u) {
-      if (last) {
-        put(pos, item_id[u]);
-      } else {
-        st_tag(keyx + s * m + pos, item[u], tag, a.home);
-        st_tag(keyid + s * m + pos, (uint32_t)item_id[u], tag, a.home);
+  if (!shared) {
+    done = topk_items<U>(key, n, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+      if (__builtin_amdgcn_inverse_ballot_w64(chosen)) put(pos, id(u));
+    });
+  } else if (!last) {
+    done = topk_items<U>(key, j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+      if (__builtin_amdgcn_inverse_ballot_w64(chosen)) {
+        st_tag(keyx + s * m + pos, key[u], tag, a.home);
+        st_tag(keyid + s * m + pos, (uint32_t)id(u), tag, a.home);
       }
     });
+  } else {                                             // the others' rows, then the group's own
+    auto choose = [&](auto xc) {
+      constexpr int XR = decltype(xc)::value, T = XR + (U < SEL_REGS ? U : SEL_REGS);     // (a slice's rows)
+      uint32_t item[T];
+#pragma unroll
+      for (int u = 0; u < T; ++u) item[u] = u < XR ? key_of[u < XR ? u : 0] : key[u < XR ? 0 : u - XR];
+      return topk_items<T>(item, others + j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+        if (__builtin_amdgcn_inverse_ballot_w64(chosen)) put(pos, u < XR ? id_of[u < XR ? u : 0] : id(u < XR ? 0 : u - XR));
+      });
+    };
+    done = X <= 1 ? choose(UnrollBy<1>{}) : choose(UnrollBy<SEL_OTHERS>{});
   }
+  store_scores();
   if (__builtin_expect(done, 1)) return Selected::IDS;
 #pragma unroll
-  for (int u = 0; u < REGS; ++u)
-    if (have >> u & 1u) key_lds[others + tid + u * nt] = key[u];
+  for (int u = 0; u < U; ++u)
+    if (ours(u)) key_lds[others + tid + u * nt] = key[u];
 #pragma unroll
   for (int x = 0; x < SEL_OTHERS; ++x)
-    if (have_of >> x & 1u) key_lds[tid + x * nt] = key_of[x];
+    if (tid + x * SEL_THREADS < others) key_lds[tid + x * SEL_THREADS] = key_of[x];
   lds_barrier();
   return Selected::KEYS;
+}
+// By the rows of candidates that a thread has, and the method's own scores apart from the other poolings: each is straight code then (a
+// test of the pooling beside every row and of the rows in use beside every phase cost 0.6 to 1 us of what topk_items says).
+// again(): the arguments once more, from memory: what several ways have in common would be worked out ahead of them all and kept in lanes of
+// vector registers, of which a host pool's kernels have none to spare.
+template <int G, bool TAGGED, typename Again>
+__device__ __forceinline__ Selected select_rows(const StepArgs& a, int head, int s, int nw, int mine, uint32_t* key, SelectLds& sm, Again again) {
+  constexpr int REGS = sel_regs_alone(G);
+  const int nt = nw * 64;
+  if (__builtin_expect(a.sel_pool != 0, 0)) return select_group<G, TAGGED, false, true, REGS>(again(), head, s, nw, key, sm);
+  if (a.slices > 1) {
+    if (mine <= nt) return select_group<G, TAGGED, true, true, 1>(again(), head, s, nw, key, sm);
+    if (mine <= 2 * nt) return select_group<G, TAGGED, true, true, 2>(again(), head, s, nw, key, sm);
+    return select_group<G, TAGGED, true, true, SEL_REGS>(again(), head, s, nw, key, sm);
+  }
+  if (mine <= nt) return select_group<G, TAGGED, true, false, 1>(a, head, s, nw, key, sm);
+  if (mine <= 2 * nt) return select_group<G, TAGGED, true, false, 2>(a, head, s, nw, key, sm);
+  if (REGS == 4 || mine <= 4 * nt) return select_group<G, TAGGED, true, false, 4>(a, head, s, nw, key, sm);
+  return select_group<G, TAGGED, true, false, REGS>(a, head, s, nw, key, sm);
 }
 
 // The weight of one page for one query head of the group by one thread, bit for bit score_pages'.
@@ -1148,8 +1170,8 @@ __device__ __forceinline__ void alone_keys(const StepArgs& a, int head, int nw, 
 
 // Selecting block `s` of a head.  True for the waves that go on with select_finish -- the last block's, nw of them, and another's
 // that has its choice still to make -- and `got`: how far they are.
-template <int G, bool TAGGED>
-__device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s, uint32_t* key, int& nw, Selected& got) {
+template <int G, bool TAGGED, typename Again>
+__device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s, uint32_t* key, int& nw, Selected& got, Again again) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = a.slices, j0 = s * a.slice, j1 = min(a.g.n_cand, j0 + a.slice);
   const bool last = s == S - 1;
@@ -1161,7 +1183,7 @@ __device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s,
   if (a.g.k_eff == 0) return true;
   // What the end of the chain needs of the arguments is read now, while the weights are waited for
   // (0.3 us of a layer-step of 8 to 20 us).
-  got = (Selected)__builtin_amdgcn_readfirstlane((int)select_group<G, TAGGED>(a, head, s, nw, key, select_lds()));
+  got = (Selected)__builtin_amdgcn_readfirstlane((int)select_rows<G, TAGGED>(a, head, s, nw, j1 - j0, key, select_lds(), again));
   return last || got == Selected::KEYS;
 }
 
@@ -1259,8 +1281,12 @@ __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
   step_roles<DT, G, PAST>(a, blockIdx.x, blockIdx.y, [&](int head, int s) {
     int nw;
     Selected got;
-    if (select_begin<G, true>(a, head, s, dyn_lds, nw, got)) 
-      select_finish<DT, G, true>(a, head, s, dyn_lds, nw, got, [] { return args_from_memory<StepArgs>(); });
+    const auto again = [] {
+      StepArgs b = args_from_memory<StepArgs>();
+      b.home = HOME;
+      return b;
+    };
+    if (select_begin<G, true>(a, head, s, dyn_lds, nw, got, again)) select_finish<DT, G, true>(a, head, s, dyn_lds, nw, got, again);
   });
 }
 

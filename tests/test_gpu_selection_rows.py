@@ -1,0 +1,50 @@
+"""The choice of the k best pages where its code differs: rows of candidates per thread, waves that are not full, keys that are ranked
+against each other or not, scores below the last counter's reach, and what several blocks hand on.  Against the numbers' definition:
+the ids by the scores that the library reports, the scores by those of the same list in a launch of another shape."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_13109_amd as fkv
+from paper_2505_13109_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _best(score, k):
+    """ids (from 0) of the k largest, ties to the lower id, ascending"""
+    order = np.lexsort((np.arange(len(score)), -score.astype(np.float64)))
+    return np.sort(order[:k])
+
+
+def _select(G, n_cand, k, K, q, batch=1):
+    g = fkv.FreeKV(n_layers=1, batch=batch, n_q_heads=G, n_kv_heads=1, max_ctx=K.shape[1] + 32, budget=128 + 32 * k, sink=64, window=64, tau=0.8)
+    g.load_prefix(0, K.expand(batch, -1, -1, -1).contiguous(), K.expand(batch, -1, -1, -1).contiguous())
+    ids = torch.full((batch, 1, k), -1, dtype=torch.int32, device="cuda")
+    g.page_select(0, q.expand(batch, -1, -1).contiguous(), ids)
+    score = g.debug_read(0, B.DBG_SCORES)[:, 0, 2:2 + n_cand]
+    g.health(0)
+    g.close()
+    return ids.cpu().numpy()[:, 0], score
+
+
+@pytest.mark.parametrize("scale", [0.0, 1.0, 12.0])      # all alike; a softmax over many pages; one whose k-th best is next to nothing
+@pytest.mark.parametrize("G,n_cand,k", [
+    (4, 1, 1), (4, 63, 7), (4, 65, 64),                   # one wave, two
+    (4, 511, 32), (4, 512, 32), (4, 513, 512),            # one row; a second of one candidate
+    (7, 1024, 96), (7, 1025, 3), (7, 1342, 100),          # two rows, three of four, the most that one block has
+    (3, 2048, 500), (3, 2049, 64), (3, 3133, 40),         # four rows, eight
+    (8, 1300, 65), (5, 2100, 33), (4, 4096, 300),         # in several blocks: every key handed on
+    (4, 5000, 32), (4, 8160, 1), (6, 9000, 129),          # ... each block's best
+])
+def test_rows_waves_and_ranks(G, n_cand, k, scale):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_cand + k)
+    K = torch.randn((1, (n_cand + 4) * 32, 1, 128), dtype=torch.bfloat16, device="cuda", generator=gen)
+    q = (scale * torch.randn((1, G, 128), device="cuda", generator=gen)).to(torch.bfloat16)
+    ids, score = _select(G, n_cand, k, K, q)
+    assert np.array_equal(ids[0], 2 + _best(score[0], k))
+    # 320 requests with the same list, in a scan and a selection of their own where that is what so many take: the same bits
+    if n_cand in (63, 513, 1025):
+        many, scores = _select(G, n_cand, k, K, q, batch=320)
+        assert np.array_equal(scores, np.broadcast_to(score[0], scores.shape)) and np.array_equal(many, np.broadcast_to(ids[0], many.shape))
