@@ -37,17 +37,22 @@ template <> struct Mma<0> {
   static __device__ __forceinline__ f32x4 mma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
-  // p >= 0 split into two storage-type values whose sum carries ~22 bits of p
+  // p >= 0 split into two storage-type values whose sum carries ~22 bits of p; pairs, so that the conversions are the packed ones (round
+  // to nearest even), which take fewer registers too
+  typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+  static __device__ __forceinline__ f16x2 pack(float a, float b) { return __builtin_convertvector((f32x2{a, b}), f16x2); }
   static __device__ __forceinline__ void split(const float* p, vec& hi, vec& lo) {
+    u32x4 h, l;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const _Float16 h = (_Float16)p[e];
-      hi[e] = h;
-      lo[e] = (_Float16)(p[e] - (float)h);
+    for (int e = 0; e < 4; ++e) {
+      const f16x2 he = pack(p[2 * e], p[2 * e + 1]);
+      h[e] = __builtin_bit_cast(uint32_t, he);
+      l[e] = __builtin_bit_cast(uint32_t, pack(p[2 * e] - (float)he[0], p[2 * e + 1] - (float)he[1]));
     }
+    hi = __builtin_bit_cast(vec, h);
+    lo = __builtin_bit_cast(vec, l);
   }
   static __device__ __forceinline__ float add_pair(uint32_t w, float c) {
-    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
     return __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, w), f16x2{(_Float16)1.0f, (_Float16)1.0f}, c, false);
   }
 };
@@ -315,6 +320,18 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   // takes it from the step's inputs -- it starts from that token instead of from nothing -- and attends the page without it.
   const int new_page = FUSED ? (g.L - 1) / PG : -1, new_tok = (g.L - 1) % PG;
   const bool owns_new = FUSED && __ballot(page_l == new_page && !picked) != 0;
+  u32x4 kn[4];
+  uint2 vn[8];
+  auto k_part = [&](int s) { return *reinterpret_cast<const u32x4*>(a.k_new + (size_t)head * D + (s * 4 + rb) * 8); };
+  auto v_part = [&](int cb) { return *reinterpret_cast<const uint2*>(a.v_new + (size_t)head * D + cb * 16 + rb * 4); };
+  // requested as early as the queries: after the test, they were what the whole head waited for (8 heads of 65 pages, the open page's wave
+  // done 4.7 us after its block began, the others 3.9; so, 3.9).  A host pool's kernels have no registers for that.
+  if (FUSED && !HOSTFUSED && owns_new) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) kn[s] = k_part(s);
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) vn[cb] = v_part(cb);
+  }
   if (FUSED && new_tok == 0 && page_l == new_page) unit_l = -1;
 
   int number = 0;                                       // (waited for where the tag is needed)
@@ -323,6 +340,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   const uint16_t* head_pool = pd.pool + (size_t)head * pd.units_per_head * UNIT_ELEMS;
   const float sl2 = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(d) * log2(e)
   float m_run = -__builtin_inff(), l_run = 0.0f;
+  bool fresh = true;                                    // nothing is summed up yet
   f32x4 acc[8];
   u32x4 kw[8], vw[8];
   uint32_t miss_l = 0;                                  // HOSTFUSED: the lane's page has to come from the host pool
@@ -373,12 +391,22 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
       }
     }
     f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const vec qs = q_of(s);
+    auto products = [&](int s, vec qs) {
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb) st[mb] = Mma<DT>::mma(__builtin_bit_cast(vec, kw[s * 2 + mb]), qs, st[mb]);
       if (s < 3) __builtin_amdgcn_sched_barrier(0);     // (not all of the operand at once: registers)
+    };
+    if constexpr (HOSTFUSED) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) products(s, q_of(s));
+    } else {                                            // (the operand a step ahead, for which a host pool's kernels have no registers)
+      vec qs = q_of(0);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const vec q1 = s < 3 ? q_of(s + 1) : qs;
+        products(s, qs);
+        qs = q1;
+      }
     }
     if (next >= 0) load_k(up_next);
     // logits (base 2) of head gq for tokens mb*16 + rb*4 + i
@@ -400,9 +428,12 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
       const float alpha = m_new == m_run ? 1.0f : fast_exp2(m_run - m_new);
       l_run *= alpha;
       m_run = m_new;
+      if (HOSTFUSED || !fresh) {                        // (the test takes a register that a host pool's kernels have not)
 #pragma unroll
-      for (int cb = 0; cb < 8; ++cb) acc[cb] *= alpha;
+        for (int cb = 0; cb < 8; ++cb) acc[cb] *= alpha;
+      }
     }
+    fresh = false;
     float p[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = fast_exp2(sc[e] - m_run);
@@ -453,6 +484,11 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
     const float c = near_cosine_of<DT>(cq[0], cp);
     if (lane == 63) s_near[wave] = c;
   }
+#pragma unroll
+  for (int cb = 0; cb < 8; ++cb) {
+    acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (!HOSTFUSED) asm volatile("" : "+v"(acc[cb]));      // (here, while loads are under way)
+  }
   lds_barrier();
   if (FUSED) {
     int flag = a.have_prev ? __builtin_amdgcn_readfirstlane(near_flag(s_near, G, a.tau, a.corr_pool)) : 1;
@@ -466,23 +502,24 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
     }
     two_phase = flag != 0;
   }
-  if (i0 >= 0) load_v(up0);
-#pragma unroll
-  for (int cb = 0; cb < 8; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (HOSTFUSED && i0 >= 0) load_v(up0);
   if (FUSED && owns_new) {
-    uint2 vn[8];
+    if (HOSTFUSED) {
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) vn[cb] = *reinterpret_cast<const uint2*>(a.v_new + (size_t)head * D + cb * 16 + rb * 4);
+      for (int cb = 0; cb < 8; ++cb) vn[cb] = v_part(cb);
+    }
     f32x4 st = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < 4; ++s)                         // (the key in every row of the tile)
-      st = Mma<DT>::mma(*reinterpret_cast<const vec*>(a.k_new + (size_t)head * D + (s * 4 + rb) * 8), q_of(s), st);
+      st = Mma<DT>::mma(__builtin_bit_cast(vec, HOSTFUSED ? k_part(s) : kn[s]), q_of(s), st);
     m_run = st[0] * sl2;
     l_run = rb == 0 ? 1.0f : 0.0f;
+    fresh = false;
 #pragma unroll
     for (int cb = 0; cb < 8; ++cb)
       acc[cb] = f32x4{Unpack<DT>::lo(vn[cb].x), Unpack<DT>::hi(vn[cb].x), Unpack<DT>::lo(vn[cb].y), Unpack<DT>::hi(vn[cb].y)};
   }
+  if (!HOSTFUSED && i0 >= 0) load_v(up0);
   // A corrected head of a fused launch attends with this step's selection, which other blocks of
   // the same launch are still making.  Only the k picked positions of the attend list depend on it:
   // the wave first attends its sink, window and open-page positions (phase 0), then waits for the selection and
@@ -573,7 +610,7 @@ __device__ __forceinline__ AttnLeft attn_block(const AttnArgs& a, int split, int
   constexpr int IT = (MAX_G * D + NW * 64 - 1) / (NW * 64);
   float o[IT], den[IT], M[IT];
   uint32_t left = 0;                                    // bit t: item t's output is left to be made alone
-  const bool no_ids = FUSED && __builtin_amdgcn_readfirstlane(s_no_ids) != 0;
+  const bool no_ids = FUSED && two_phase && __builtin_amdgcn_readfirstlane(s_no_ids) != 0;
   if (!no_ids) {
     // A wave's 64 outputs are of one query head, so what is the same for all of them -- the weights of the block's waves, and
     // then of the head's splits -- is worked out by a lane each and handed round as scalars.  (With every thread working them out

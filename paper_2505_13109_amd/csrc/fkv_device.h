@@ -251,13 +251,16 @@ __device__ __forceinline__ float near_cosine_of(uint32_t qw, uint32_t pw) {
 // The correction flag from such values: 0 or 1 where they decide it, -1 where the pooled one is too close to tau.
 __device__ __forceinline__ int near_flag(const float* c, int G, float tau, int pool) {
   float acc = c[0];
-  for (int gg = 1; gg < G; ++gg) {
-    const float v = c[gg];
-    if (pool == 0) acc = acc + v;
-    else if (pool == 1) acc = v > acc || v != v ? v : acc;
-    else acc = v < acc || v != v ? v : acc;
+  if (pool == 0) {
+#pragma unroll
+    for (int gg = 1; gg < MAX_G; ++gg) acc = acc + (gg < G ? c[gg] : 0.0f);
+    acc = acc * __builtin_amdgcn_rcpf((float)G);
+  } else {
+    for (int gg = 1; gg < G; ++gg) {
+      const float v = c[gg];
+      acc = v != v || (pool == 1 ? v > acc : v < acc) ? v : acc;
+    }
   }
-  if (pool == 0) acc = acc * __builtin_amdgcn_rcpf((float)G);
   const float d = acc - tau;
   return d < -1e-4f ? 1 : d > 1e-4f ? 0 : -1;
 }
