@@ -82,17 +82,29 @@ static const int g_one_launch = knob("FKV_ONE_LAUNCH", -1);       // layer-step:
 
 static const int g_fuse = knob("FKV_FUSE", -1);
 
-// Selecting blocks of a head, a power of two.  One as long as it has the registers and not too many softmax numerators to make:
-// the exchanges of a shared list (sums, then keys) are what it costs.  8 KV heads, layer-step in us with the words going through memory
-// (in the L2 the lines lie where they lay), alone against the best shared one: 1500 candidates, G = 4, 10.4 and 12.2; 3000, G = 3, 13.6 and 13.7; 1500, G = 6, 12.0 and 12.6; but 2016, G = 5,
-// 13.1 and 12.8; 1200, G = 8, 13.3 and 13.0; 3500, G = 3, 16.0 and 14.5.  A list that is shared is cut fine, since every phase
+// Selecting blocks of a head, a power of two.  One as long as it has the registers and not too much work: the exchanges of a shared
+// list (sums, then keys) are what sharing costs, about 1.5 us.  The work of a block that has the list alone is that of its rows of candidates
+// (one, two, four or eight per thread, by the code that there is) times the query heads, and what sharing saves grows with it.  Layer-steps in us,
+// alone and shared as below.  8 heads, two rows: 992 candidates, G = 8, 9.5 and 9.9, G = 4 7.1 and 8.1; four: 2000, G = 3, 8.8 and 8.9; 1040, G = 4, 8.4 and
+// 8.3; 1700, 9.2 and 8.7; 1200, G = 5, 9.5 and 9.0; 1200, G = 6, 10.2 and 9.4; 1040, G = 7, 11.2 and 9.8 (most corrected, 14.9 and 13.5); 1040,
+// G = 8, 11.8 and 10.2; eight: 4000, G = 1, 10.8 and 10.7; 2300, G = 2, 10.0 and 8.7; 2200, G = 3, 11.5 and 9.1.  Fewer: 1 x 1100, G = 8, 11.4 and 9.9; 4 x
+// 1700, G = 4, 9.0 and 8.6; 6 x 1800, G = 5, 10.0 and 9.2; but 1 x 1700, G = 4, which then is not
+// at home (scoring_passes), 8.5 and 8.9, and 2 x 1700 8.7 and 9.3.  With more heads it depends on what else the launch has to do -- 16 x 1100, G = 5, most
+// corrected, 15.8 and 16.1, 1200, G = 6, 12.0 and 11.9; 32 x 2100, G = 3, 18.8 and 20.2, x 2500 20.1 and 18.8 -- and two blocks a head are no better than one
+// (48 x 1300, G = 6, 20.1 and 20.2): there the list stays with one block a little longer, and so it does under the other poolings, whose
+// code takes all its rows however few are in use, and with the KV in a host pool, where the link decides (8 x 1100, G = 8, 23.7 and 23.4; 4 x 2500, G = 3, 27.6
+// and, at home as well, 28.8).
+// A list that is shared is cut fine, since every phase
 // but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
-// in 2, 4, 8, 16 blocks: 2300 candidates 14.3, 13.4, 12.9, 13.5; 4000: 17.6, 17.0, 15.5, 15.0; 8160: -, 22.0, 19.8, 19.0; but 32 heads
-// x 4000 13.6, 13.4, 17.2, 19.7.
-constexpr int kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024, kFewHeads = 40;
-static int selection_slices(const Geom& g, int G, int heads) {
-  const int n = g.n_cand;
-  if (g.k_eff == 0 || (n <= sel_regs_alone(G) * SEL_THREADS && (long)n * G <= kMaxAloneWork)) return 1;
+// in 4, 8, 16 blocks: 2300 candidates 10.6, 9.6, 10.1; 4000: 13.1, 12.0, 11.7; 8160: 17.8, 15.9, 15.2; 2016, G = 8, 12.5, 12.0, 13.3; but 16 heads
+// x 1200, G = 6, 11.9, 12.0, 12.0.
+constexpr int kRowsAlone = 2, kLightWork = 12, kLightWorkAway = 16, kFewShared = 8, kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024, kFewHeads = 40;
+static int selection_slices(const Dims& d, const Geom& g, bool host_pool) {
+  const int n = g.n_cand, G = d.G, heads = d.batch * d.n_kv, regs = sel_regs_alone(G);
+  int rows = 1;
+  while (rows * SEL_THREADS < n) rows *= 2;
+  const bool light = d.sel_pool == 0 && !host_pool && heads <= kFewShared ? rows <= kRowsAlone || rows * G <= (heads < kXcds / 2 ? kLightWorkAway : kLightWork) : (long)n * G <= kMaxAloneWork;
+  if (g.k_eff == 0 || (rows <= regs && light)) return 1;
   int s = 2;
   while (s < MAX_SLICES && ((n + s - 1) / s > SEL_REGS * SEL_THREADS || ((n + s - 1) / s > kFineSlice && heads * s * 2 <= kMaxFineBlocks))) s *= 2;
   return s;
@@ -116,13 +128,15 @@ static const int g_home = knob("FKV_HOME", -1);                   // 0 never, 1 
 // runs in rounds either way.
 constexpr double kHomeExcess = 0.9e6, kHomeExcessAttn = 0.45e6, kFewHeadsRoom = 2.2;
 constexpr int kSlotsOfXcd = 2 * kComputeUnits / kXcds;            // blocks of 512 threads that an XCD holds at once
+static bool little_excess(const Dims& d, int heads, double bytes, bool attn_only) {
+  const double excess = (by_xcd(heads) - heads) / (double)kXcds * bytes;
+  return d.same_xcd && excess <= (attn_only ? kHomeExcessAttn : kHomeExcess) * (heads < kXcds ? kFewHeadsRoom : 1.0);
+}
 bool heads_at_home(const Dims& d, int heads, int rows, double bytes, bool attn_only) {
   if (g_home >= 0) return g_home == 1;
-  if (!d.same_xcd) return false;
-  if (heads % kXcds == 0) return true;
   const int most = by_xcd(heads) / kXcds;
-  if (most <= 2 && most * rows > kSlotsOfXcd) return false;
-  return (most - (double)heads / kXcds) * bytes <= (attn_only ? kHomeExcessAttn : kHomeExcess) * (heads < kXcds ? kFewHeadsRoom : 1.0);
+  if (heads % kXcds != 0 && most <= 2 && most * rows > kSlotsOfXcd) return false;
+  return little_excess(d, heads, bytes, attn_only);
 }
 
 // Which XCD a block runs on is the dispatcher's choice, not the programming model's, so it is looked at once for every context
@@ -151,15 +165,24 @@ bool blocks_by_xcd(uint32_t* where) {
 
 // Passes of a scoring block: a launch runs in ceil(blocks / resident blocks) rounds, and blocks of a later round (the
 // selection and attention come last) queue behind the scoring blocks.  The passes that give the fewest rounds -- one, the
-// whole launch resident at once, where the shape allows -- and among those the fewest (most blocks).
-static int scoring_passes(const Dims& d, const Geom& g, int slices, int other_rows, int resident) {
+// whole launch resident at once, where the shape allows -- and among those the fewest (most blocks).  Where the heads do not go round the
+// XCDs evenly but are few enough to be at home, it is an XCD's slots that count: at home the launch has to be there all at once
+// (heads_at_home), and that gains more than a pass more costs.  Layer-steps in us, one pass a block and away, two or four and at home: 4 heads x
+// 1700 candidates, G = 4, 9.7 and 8.6; x 2000, G = 7, 11.2 and 10.7; 6 x 1800, G = 5, 10.9 and 9.2; 6 x 3000, G = 4, 12.8 and 10.8; 4 x 4000 12.5 and 11.4; but 2 x 4000, which have too much to read for one XCD each, 11.3 and 12.5 (heads on
+// less than half of the XCDs are left as they were: 2 x 1700 8.7 and 8.3).
+// home: they would be, and the link to a host pool does not decide.
+static int scoring_passes(const Dims& d, const Geom& g, int slices, int other_rows, int resident, bool home) {
   if (g_min_passes > 0) return g_min_passes;
   const long heads = (long)d.batch * d.n_kv;
+  auto blocks_of = [&](long wide, int passes) { return wide * (2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + other_rows); };
+  if (home && heads % kXcds != 0 && heads >= kXcds / 2 && heads < 2 * kXcds) {
+    for (int passes = 1; passes <= SCORE_PASSES; passes *= 2)
+      if (blocks_of(by_xcd((int)heads), passes) <= resident) return passes;
+  }
   int best = 1;
   long best_rounds = 0;
   for (int passes = 1; passes <= SCORE_PASSES; passes *= 2) {
-    const long blocks = heads * (2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + other_rows);
-    const long rounds = (blocks + resident - 1) / resident;
+    const long rounds = (blocks_of(heads, passes) + resident - 1) / resident;
     if (passes == 1 || rounds < best_rounds) { best = passes; best_rounds = rounds; }
   }
   return best;
@@ -227,15 +250,15 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
     return 1;
   }
   if (!(roles & ROLE_SELECT) || (g_fuse >= 0 ? g_fuse == 1 : (long)heads * ((g.n_cand + PAGES_PER_PASS - 1) / PAGES_PER_PASS) <= kFuseMaxChunks)) {
-    const int slices = selection_slices(g, d.G, heads);
-    fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident), slices, a, rows, lds);
+    const int slices = selection_slices(d, g, io.pd.placement != 0);
+    fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident, io.pd.placement == 0 && little_excess(d, heads, g.n_cand * kSummaryBytes, false)), slices, a, rows, lds);
     const bool past = (stream_of(d, g) & STREAM_SUMMARIES) != 0;
     a.home = (roles & ROLE_SELECT) != 0 && heads_at_home(d, heads, rows, g.n_cand * kSummaryBytes);
     if (!(a.home ? launch_step_kernel_home : launch_step_kernel)(a, DT, G, past, rows, lds, st)) return -1;
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
   }
-  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, selection_slices(g, d.G, heads), a, rows, lds);
+  fill_step_args(d, roles, io, g, SCAN_WAVES * 4, SCORE_PASSES, selection_slices(d, g, io.pd.placement != 0), a, rows, lds);
   a.P = reinterpret_cast<unsigned long long*>(io.P_plain);
   a.cmax = reinterpret_cast<unsigned long long*>(io.cmax_plain);
   a.home = a.slices > 1 && heads_at_home(d, heads, a.slices, (double)g.n_cand * d.G * sizeof(float));
@@ -287,7 +310,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   if (io.host_pool && (d.max_pages > TAGGED_MAX_PAGES || 2 * d.k > TAGGED_MAX_SLOTS)) return false;
   const int heads = d.batch * d.n_kv;
   const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0), n_there = n_att - d.k + g.k_eff;
-  const int slices = selection_slices(g, d.G, heads);
+  const int slices = selection_slices(d, g, io.host_pool);
   // Attention's blocks, which come last, are fewer where a list is shared, since selecting blocks wait too.  Beside long lists of
   // many heads, a block each, a head is cut half as fine as it could be: with that many scoring blocks the launch runs in rounds, and
   // blocks of a later one queue.  A pass of 8 layer-steps, in full and half: 128 heads x 1234 candidates (2 splits and 1) 395 and
@@ -296,9 +319,11 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   // (9 and 5) 160 and 168.
   const bool half = g.n_cand > kLongList && heads > kFewHeads;
   const int waiting = slices > 1 ? kMaxWaiting - heads * slices : half ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting;
+  const double bytes = (double)n_there * UNIT_BYTES + g.n_cand * kSummaryBytes;
+  const bool home = !io.host_pool && little_excess(d, heads, bytes, false);
   int pps, n_splits, passes, rows;
   auto size = [&]() {
-    passes = scoring_passes(d, g, slices, n_splits, kLayerResident);
+    passes = scoring_passes(d, g, slices, n_splits, kLayerResident, home);
     rows = 2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + n_splits;
   };
   auto cut = [&](int max_blocks) {
@@ -330,7 +355,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
     if ((long)heads * rows > kLayerMaxBlocks) cut(waiting);
   }
   LayerLaunch l;
-  l.home = heads_at_home(d, heads, rows, (double)n_there * UNIT_BYTES + g.n_cand * kSummaryBytes);
+  l.home = heads_at_home(d, heads, rows, bytes);
   if (l.home && n_splits > kMaxWaitingHome) {
     n_splits = kMaxWaitingHome;
     pps = (n_att + n_splits - 1) / n_splits;

@@ -48,3 +48,22 @@ def test_rows_waves_and_ranks(G, n_cand, k, scale):
     if n_cand in (63, 513, 1025):
         many, scores = _select(G, n_cand, k, K, q, batch=320)
         assert np.array_equal(scores, np.broadcast_to(score[0], scores.shape)) and np.array_equal(many, np.broadcast_to(ids[0], many.shape))
+
+
+@pytest.mark.parametrize("G,n_cand,heads", [
+    (3, 2048, 2), (3, 2049, 2), (3, 2300, 9),             # the longest list that one block has, the shortest that several share, heads too many for it
+    (2, 2049, 4), (4, 1025, 5), (5, 1024, 1), (5, 1025, 1), (5, 1100, 8), (5, 1100, 9),
+    (8, 1025, 3), (8, 1150, 40), (7, 1342, 8),
+])
+def test_alone_and_shared(G, n_cand, heads):
+    """One list per head, cut by the number of heads and candidates: the same scores, bit for bit, as in 96 heads, which have a block each."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_cand * 64 + heads)
+    k = 37
+    K = torch.randn((1, (n_cand + 4) * 32, 1, 128), dtype=torch.bfloat16, device="cuda", generator=gen)
+    q = torch.randn((1, G, 128), device="cuda", generator=gen).to(torch.bfloat16)
+    ids, score = _select(G, n_cand, k, K, q, batch=heads)
+    many, scores = _select(G, n_cand, k, K, q, batch=96)
+    want = 2 + _best(score[0], k)
+    assert np.array_equal(ids, np.broadcast_to(want, ids.shape)) and np.array_equal(many, np.broadcast_to(want, many.shape))
+    assert np.array_equal(score, np.broadcast_to(score[0], score.shape)) and np.array_equal(scores, np.broadcast_to(score[0], scores.shape))
