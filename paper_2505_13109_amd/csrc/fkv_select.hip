@@ -85,25 +85,24 @@ static const int g_fuse = knob("FKV_FUSE", -1);
 // Selecting blocks of a head, a power of two.  One as long as it has the registers and not too much work: the exchanges of a shared
 // list (sums, then keys) are what sharing costs, about 1.5 us.  The work of a block that has the list alone is that of its rows of candidates
 // (one, two, four or eight per thread, by the code that there is) times the query heads, and what sharing saves grows with it.  Layer-steps in us,
-// alone and shared as below.  8 heads, two rows: 992 candidates, G = 8, 9.5 and 9.9, G = 4 7.1 and 8.1; four: 2000, G = 3, 8.8 and 8.9; 1040, G = 4, 8.4 and
-// 8.3; 1700, 9.2 and 8.7; 1200, G = 5, 9.5 and 9.0; 1200, G = 6, 10.2 and 9.4; 1040, G = 7, 11.2 and 9.8 (most corrected, 14.9 and 13.5); 1040,
-// G = 8, 11.8 and 10.2; eight: 4000, G = 1, 10.8 and 10.7; 2300, G = 2, 10.0 and 8.7; 2200, G = 3, 11.5 and 9.1.  Fewer: 1 x 1100, G = 8, 11.4 and 9.9; 4 x
-// 1700, G = 4, 9.0 and 8.6; 6 x 1800, G = 5, 10.0 and 9.2; but 1 x 1700, G = 4, which then is not
-// at home (scoring_passes), 8.5 and 8.9, and 2 x 1700 8.7 and 9.3.  With more heads it depends on what else the launch has to do -- 16 x 1100, G = 5, most
+// alone and shared as below.  8 heads, work of 8: 4000 candidates, G = 1, 10.8 and 10.7; 12: 2000, G = 3, 8.8 and 8.9; 16: 992, G = 8, 9.5 and 9.9, 1200, G = 4,
+// 8.5 and 8.4, 1700 9.2 and 8.7, but 1 x 1700 8.5 and 8.9; 20: 1200, G = 5, 9.5 and 9.0; 24: 1200, G = 6, 10.2 and 9.4, 2200, G = 3, 11.5 and 9.1; 28: 1040, G = 7, 11.2 and
+// 9.8 (most corrected, 14.9 and 13.5); 32: 1040, G = 8, 11.8 and 10.2.  Fewer heads: 1 x 1100, G = 8, 11.4 and 9.9; 3 x 1400, G = 6, 10.2 and 9.4; 6 x
+// 1800, G = 5, 10.0 and 9.2.  With more heads it depends on what else the launch has to do -- 16 x 1100, G = 5, most
 // corrected, 15.8 and 16.1, 1200, G = 6, 12.0 and 11.9; 32 x 2100, G = 3, 18.8 and 20.2, x 2500 20.1 and 18.8 -- and two blocks a head are no better than one
 // (48 x 1300, G = 6, 20.1 and 20.2): there the list stays with one block a little longer, and so it does under the other poolings, whose
-// code takes all its rows however few are in use, and with the KV in a host pool, where the link decides (8 x 1100, G = 8, 23.7 and 23.4; 4 x 2500, G = 3, 27.6
-// and, at home as well, 28.8).
+// code takes all its rows however few are in use, and with the KV in a host pool, where the link decides
+// (8 x 1100, G = 8, 23.7 and 23.4; the same launch takes between 27 and 31 from one process to the next, 4 x 2500, G = 3).
 // A list that is shared is cut fine, since every phase
 // but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
 // in 4, 8, 16 blocks: 2300 candidates 10.6, 9.6, 10.1; 4000: 13.1, 12.0, 11.7; 8160: 17.8, 15.9, 15.2; 2016, G = 8, 12.5, 12.0, 13.3; but 16 heads
 // x 1200, G = 6, 11.9, 12.0, 12.0.
-constexpr int kRowsAlone = 2, kLightWork = 12, kLightWorkAway = 16, kFewShared = 8, kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024, kFewHeads = 40;
+constexpr int kLightWork = 16, kFewShared = 8, kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024, kFewHeads = 40;
 static int selection_slices(const Dims& d, const Geom& g, bool host_pool) {
   const int n = g.n_cand, G = d.G, heads = d.batch * d.n_kv, regs = sel_regs_alone(G);
   int rows = 1;
   while (rows * SEL_THREADS < n) rows *= 2;
-  const bool light = d.sel_pool == 0 && !host_pool && heads <= kFewShared ? rows <= kRowsAlone || rows * G <= (heads < kXcds / 2 ? kLightWorkAway : kLightWork) : (long)n * G <= kMaxAloneWork;
+  const bool light = d.sel_pool == 0 && !host_pool && heads <= kFewShared ? rows * G <= kLightWork : (long)n * G <= kMaxAloneWork;
   if (g.k_eff == 0 || (rows <= regs && light)) return 1;
   int s = 2;
   while (s < MAX_SLICES && ((n + s - 1) / s > SEL_REGS * SEL_THREADS || ((n + s - 1) / s > kFineSlice && heads * s * 2 <= kMaxFineBlocks))) s *= 2;
@@ -165,17 +164,18 @@ bool blocks_by_xcd(uint32_t* where) {
 
 // Passes of a scoring block: a launch runs in ceil(blocks / resident blocks) rounds, and blocks of a later round (the
 // selection and attention come last) queue behind the scoring blocks.  The passes that give the fewest rounds -- one, the
-// whole launch resident at once, where the shape allows -- and among those the fewest (most blocks).  Where the heads do not go round the
-// XCDs evenly but are few enough to be at home, it is an XCD's slots that count: at home the launch has to be there all at once
-// (heads_at_home), and that gains more than a pass more costs.  Layer-steps in us, one pass a block and away, two or four and at home: 4 heads x
-// 1700 candidates, G = 4, 9.7 and 8.6; x 2000, G = 7, 11.2 and 10.7; 6 x 1800, G = 5, 10.9 and 9.2; 6 x 3000, G = 4, 12.8 and 10.8; 4 x 4000 12.5 and 11.4; but 2 x 4000, which have too much to read for one XCD each, 11.3 and 12.5 (heads on
-// less than half of the XCDs are left as they were: 2 x 1700 8.7 and 8.3).
+// whole launch resident at once, where the shape allows -- and among those the fewest (most blocks).  Where fewer than eight heads
+// are to be at home, it is an XCD's slots that count: there the launch has to be resident all at once (heads_at_home), and where a
+// list is shared, with the exchanges that this takes, that gains more than a pass more costs.  Layer-steps in us, one pass a block and away, two or four and at home: 4 heads x
+// 2000 candidates, G = 7, 11.2 and 10.7; 6 x 1800, G = 5, 10.9 and 9.2; 6 x 3000, G = 4, 12.8 and 10.8; 4 x 4000 12.5 and 11.4; but 4 x 2000, G = 4, not shared, 9.2 and
+// 9.3; 2 x 4000, which have too much to read for one XCD each, 11.3 and 12.5 (heads on less than half of the XCDs are left as they were: 2 x 1700,
+// G = 8, 10.7 and 10.4).
 // home: they would be, and the link to a host pool does not decide.
 static int scoring_passes(const Dims& d, const Geom& g, int slices, int other_rows, int resident, bool home) {
   if (g_min_passes > 0) return g_min_passes;
   const long heads = (long)d.batch * d.n_kv;
   auto blocks_of = [&](long wide, int passes) { return wide * (2 + (g.n_cand + PAGES_PER_PASS * passes - 1) / (PAGES_PER_PASS * passes) + slices + other_rows); };
-  if (home && heads % kXcds != 0 && heads >= kXcds / 2 && heads < 2 * kXcds) {
+  if (home && slices > 1 && heads >= kXcds / 2 && heads < kXcds) {
     for (int passes = 1; passes <= SCORE_PASSES; passes *= 2)
       if (blocks_of(by_xcd((int)heads), passes) <= resident) return passes;
   }
