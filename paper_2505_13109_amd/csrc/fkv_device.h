@@ -131,10 +131,11 @@ template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false); }
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128, DPP_HALF_MIRROR = 0x141;
 // a lane's value, for all of them
+__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int lane) {
+  return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+}
 __device__ __forceinline__ double lane_f64(double v, int lane) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-  return __builtin_bit_cast(double, (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane) << 32 |
-                                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane));
+  return __builtin_bit_cast(double, lane_u64(__builtin_bit_cast(unsigned long long, v), lane));
 }
 // ... of a row of 16 lanes, and of the wave
 template <int M, typename OP>

@@ -433,7 +433,10 @@ struct alignas(16) SelectLds {
   uint32_t hist[TOPK_BINS + 64];                         // (and counters for threads without a candidate)
   uint32_t list[128];                                    // (and a place for lanes that have nothing to put on it)
   uint32_t count[64];
-  float mx_row[MAX_G][SEL_ROWS];                         // by query head and row of 16 lanes
+  union {
+    float mx_row[MAX_G][SEL_ROWS];                       // by query head and row of 16 lanes
+    unsigned long long whole[128];                       // the list with whole keys (the maxima are not read any more then)
+  };
   uint2 z_row[MAX_G][SEL_ROWS];
   unsigned long long z[SEL_WAVES][MAX_G];
   float mx[SEL_WAVES][MAX_G];
@@ -481,19 +484,24 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t want, ui
 // The best kk of a group's items, ties to the lower one in order.  A thread holds items key[u] (0: none), u < T; the order is by u,
 // then by thread; T * nw <= 64.  emit(u, chosen, pos): the lanes of the mask `chosen` hold chosen items in slot u, in the order pos = 0 ..
 // kk - 1.  n: items of the group.  Before the call (and a barrier): sm.hist holds the counts of the keys' bins, sm.n_list is 0.
-// The keys of the one bin that is only partly wanted are collected with their places in the order -- what is left of a key in a bin, and
-// the place, fit 32 bits -- and ranked against each other by every wave; the same barrier brings the counts per wave of what is chosen
-// anyway, and which of the others are chosen is the same in every wave.  False, and nothing done, if there are more than 64 of them (ties,
-// mostly) or they are of the last bin, which is as wide as it takes.
+// The keys of the one bin that is only partly wanted are collected with their places in the order and ranked against each other by every
+// wave; the same barrier brings the counts per wave of what is chosen anyway, and which of the others are chosen is the same in every
+// wave.  False, and nothing done, if there are more than 64 of them (ties, mostly).
+// ANY: of any keys.  Else of keys up to bins.top: what is left of a key in a bin, and the place, fit 32 bits -- except in the last bin,
+// which is as wide as it takes: false there too.
 // The chain is what counts (a wave by itself: an instruction 4 cycles, a value that goes from the vector unit through a scalar and back 28,
 // a branch that is not taken 24 and one that is 38, one by a lane's condition 55, an LDS trip 57): so everything is done for all T slots at
 // once, by masks, and what a lane has no use for goes to a place that nobody reads -- a place of its own, since lanes queue up for one
 // word (512 atomics on one counter take 1090 cycles, on 32 of them 120).  From the weights to the ids, with the slots in loops over those
 // in use and the poolings told apart beside each, and so: 97 candidates, G = 4, 2.5 and 1.8 us; 992 3.8 and 3.0; 2015 in eight blocks, G = 8,
 // 6.0 and 4.9; layer-steps of 96 candidates, G = 7, all heads corrected 11.0 and 10.1.
-template <int T, typename Emit>
+template <bool ANY, int T, typename Emit>
 __device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int kk, TopkBins bins, int nw, SelectLds& sm, Emit emit) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto slots = [&](auto f) {
+#pragma unroll
+    for (int u = 0; u < T; ++u) f(u);
+  };
   uint32_t above = 0, from = 0, base = 0;            // keys > above are chosen; those > from, up to there, if their turn comes
   uint32_t take = 0, in_bin = 0;                     // how many of these are wanted
   bool ranked = false;
@@ -503,40 +511,40 @@ __device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int 
     take = (uint32_t)kk - before;
     ranked = take != in_bin;
     const int tail = bin == TOPK_BINS - 1;
-    if (__builtin_expect(((int)ranked & ((int)(in_bin > 64) | tail)) != 0, 0)) return false;
-    base = bins.top - (bin << bins.shift);           // (the bin of a key: at most that, since topk_bin takes what is above `top` as `top`)
+    if (__builtin_expect(((int)ranked & ((int)(in_bin > 64) | (ANY ? 0 : tail))) != 0, 0)) return false;
+    base = bins.top - (bin << bins.shift);           // (the bin of a key: at most that, or the first)
     const uint32_t end = (bin + 1) << bins.shift;
     from = (tail | (int)(end > bins.top)) != 0 ? 0u : bins.top - end;
     above = !ranked ? from : bin == 0 ? ~0u : base;
   }
   static_assert(T * SEL_WAVES <= 64 && T * SEL_THREADS <= 4096 && 19 + 12 < 32, "");
   unsigned long long sure[T], maybe[T];
-  uint32_t counts = 0;
-#pragma unroll
-  for (int u = 0; u < T; ++u) {
+  uint32_t counts = 0;                               // lane u: slot u's
+  slots([&](int u) {
     sure[u] = __ballot(key[u] > above);
     const uint32_t c = (uint32_t)__popcll(sure[u]);
-    counts = u == 0 || lane == u ? c : counts;       // (lane u: slot u's)
-  }
-  auto rank_of = [&](int u) { return ((base - min(key[u], base)) << 12) + (uint32_t)(u * nw * 64 + tid); };
+    counts = u == 0 || lane == u ? c : counts;
+  });
+  auto place = [&](int u) { return (uint32_t)(u * nw * 64 + tid); };
+  auto rank_of = [&](int u) { return ((base - min(key[u], base)) << 12) + place(u); };
+  auto whole_rank_of = [&](int u) { return (unsigned long long)~key[u] << 32 | place(u); };
   if (ranked) {
     uint32_t mine = 0;
-#pragma unroll
-    for (int u = 0; u < T; ++u) {
+    slots([&](int u) {
       maybe[u] = __ballot(key[u] > from) & ~sure[u];
       mine += key[u] > from && !(key[u] > above) ? 1u : 0u;
-    }
+    });
     if (mine != 0) {
       // (an atomic of each lane that has some: one for the wave would be a longer chain, and lanes queue up for one address)
       auto* n_list = (__attribute__((address_space(3))) uint32_t*)&sm.n_list;
       asm volatile("" : "+v"(n_list));
       uint32_t at = __hip_atomic_fetch_add(n_list, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-#pragma unroll
-      for (int u = 0; u < T; ++u) {
+      slots([&](int u) {
         const bool in = key[u] > from && !(key[u] > above);
-        sm.list[in ? at : 64u + (uint32_t)lane] = rank_of(u);
+        if (ANY) sm.whole[in ? at : 64u + (uint32_t)lane] = whole_rank_of(u);
+        else     sm.list[in ? at : 64u + (uint32_t)lane] = rank_of(u);
         at += in ? 1u : 0u;
-      }
+      });
     }
   }
   sm.count[lane < T ? lane * nw + wave : wave] = counts;                      // (lanes from T on repeat slot 0's)
@@ -544,29 +552,44 @@ __device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int 
   uint32_t cnt = sm.count[lane];
   cnt = lane < T * nw ? cnt : 0u;
   unsigned long long picked = 0;                     // of the list
-  uint32_t entry = ~0u, last = 0;
+  uint32_t at = ~0u;                                 // the place of this lane's entry
   if (ranked) {
-    entry = sm.list[lane];                           // an entry a lane
-    entry = lane < (int)in_bin ? entry : ~0u;
-    uint32_t before = 0;
+    // an entry a lane; up to `last` they are chosen
+    if constexpr (ANY) {
+      unsigned long long entry = sm.whole[lane];
+      entry = lane < (int)in_bin ? entry : ~0ull;
+      uint32_t before = 0;
 #pragma unroll 1
-    for (uint32_t i = 0; i < in_bin; i += 8) {
+      for (uint32_t i = 0; i < in_bin; i += 4) {
 #pragma unroll
-      for (uint32_t v = 0; v < 8; ++v) before += (uint32_t)__builtin_amdgcn_readlane((int)entry, (int)(i + v)) < entry ? 1u : 0u;
+        for (uint32_t v = 0; v < 4; ++v) before += lane_u64(entry, (int)(i + v)) < entry ? 1u : 0u;
+      }
+      const unsigned long long last = lane_u64(entry, __builtin_ctzll(__ballot(before == take - 1 && lane < (int)in_bin)));
+      picked = __ballot(entry <= last);
+      at = (uint32_t)entry;
+      slots([&](int u) { sure[u] |= maybe[u] & __ballot(whole_rank_of(u) <= last); });
+    } else {
+      uint32_t entry = sm.list[lane];
+      entry = lane < (int)in_bin ? entry : ~0u;
+      uint32_t before = 0;
+#pragma unroll 1
+      for (uint32_t i = 0; i < in_bin; i += 8) {
+#pragma unroll
+        for (uint32_t v = 0; v < 8; ++v) before += (uint32_t)__builtin_amdgcn_readlane((int)entry, (int)(i + v)) < entry ? 1u : 0u;
+      }
+      const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)entry, __builtin_ctzll(__ballot(before == take - 1 && lane < (int)in_bin)));
+      picked = __ballot(entry <= last);
+      at = entry;
+      slots([&](int u) { sure[u] |= maybe[u] & __ballot(rank_of(u) <= last); });
     }
-    last = (uint32_t)__builtin_amdgcn_readlane((int)entry, __builtin_ctzll(__ballot(before == take - 1 && lane < (int)in_bin)));
-    picked = __ballot(entry <= last);
-#pragma unroll
-    for (int u = 0; u < T; ++u) sure[u] |= maybe[u] & __ballot(rank_of(u) <= last);
   }
-  const uint32_t excl = wave_scan_u32(cnt) - cnt, group = (entry & 4095u) >> 6;
-#pragma unroll
-  for (int u = 0; u < T; ++u) {
-    uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)excl, u * nw + wave);
-    if (ranked) first += (uint32_t)__popcll(picked & __ballot(group < (uint32_t)(u * nw + wave)));
-    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(sure[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)sure[u], first));
+  const uint32_t excl = wave_scan_u32(cnt) - cnt, group = (at & 4095u) >> 6;
+  slots([&](int u) {
+    uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)excl, u * nw + wave);
+    if (ranked) before += (uint32_t)__popcll(picked & __ballot(group < (uint32_t)(u * nw + wave)));
+    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(sure[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)sure[u], before));
     emit(u, sure[u], (int)pos);
-  }
+  });
   return true;
 }
 
@@ -995,11 +1018,11 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
   const PutId put(a, head, key_lds);
   bool done;
   if (!shared) {
-    done = topk_items<U>(key, n, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+    done = topk_items<!MEAN>(key, n, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
       if (__builtin_amdgcn_inverse_ballot_w64(chosen)) put(pos, id(u));
     });
   } else if (!last) {
-    done = topk_items<U>(key, j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+    done = topk_items<!MEAN>(key, j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
       if (__builtin_amdgcn_inverse_ballot_w64(chosen)) {
         st_tag(keyx + s * m + pos, key[u], tag, a.home);
         st_tag(keyid + s * m + pos, (uint32_t)id(u), tag, a.home);
@@ -1011,7 +1034,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
       uint32_t item[T];
 #pragma unroll
       for (int u = 0; u < T; ++u) item[u] = u < XR ? key_of[u < XR ? u : 0] : key[u < XR ? 0 : u - XR];
-      return topk_items<T>(item, others + j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+      return topk_items<!MEAN>(item, others + j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
         if (__builtin_amdgcn_inverse_ballot_w64(chosen)) put(pos, u < XR ? id_of[u < XR ? u : 0] : id(u < XR ? 0 : u - XR));
       });
     };

@@ -1,0 +1,79 @@
+"""The choice of the k best pages by the poolings without a softmax, whose scores have no largest value that is known beforehand: lists
+shared by several blocks, with the best pages in other blocks than the one that puts them in order."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_13109_amd as fkv
+from paper_2505_13109_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+EDGE = 2                                                 # sink and window pages
+
+
+def _best(score, k):
+    """ids (from 0) of the k largest, ties to the lower id, ascending"""
+    order = np.lexsort((np.arange(len(score)), -score.astype(np.float64)))
+    return np.sort(order[:k])
+
+
+def _context(G, n_cand, k, pooling, n_kv=1, batch=1):
+    """One channel of the keys decides: a page's weight is its value there, times 7 / sqrt(128) or so."""
+    return fkv.FreeKV(n_layers=1, batch=batch, n_q_heads=G * n_kv, n_kv_heads=n_kv, max_ctx=(n_cand + 2 * EDGE + 1) * 32, budget=(2 * EDGE + k) * 32,
+                      sink=EDGE * 32, window=EDGE * 32, tau=0.8, select_pooling=pooling)
+
+
+def _select(G, values, k, pooling, batch=1):
+    """ids and scores of a list of pages with these values"""
+    n = len(values)
+    K = torch.zeros((batch, (n + 2 * EDGE) * 32, 1, 128), dtype=torch.bfloat16, device="cuda")
+    K[:, EDGE * 32:(EDGE + n) * 32, 0, 3] = torch.tensor(values, device="cuda").to(torch.bfloat16).repeat_interleave(32)
+    q = torch.zeros((batch, G, 128), dtype=torch.bfloat16, device="cuda")
+    q[..., 3] = 7.0
+    g = _context(G, n, k, pooling, batch=batch)
+    g.load_prefix(0, K, K)
+    ids = torch.full((batch, 1, k), -1, dtype=torch.int32, device="cuda")
+    out = torch.empty((batch, G, 128), device="cuda")
+    new = torch.zeros((batch, 1, 128), dtype=torch.bfloat16, device="cuda")
+    g.page_select(0, q, ids)
+    score = g.debug_read(0, B.DBG_SCORES)[:, 0, EDGE:EDGE + n]
+    g.decode_step(0, q, new, new, out)
+    stepped = g.debug_read(0, B.DBG_ACTIVE_IDS)[:, 0]
+    g.health(0)
+    g.close()
+    ids = ids.cpu().numpy()[:, 0]
+    assert np.array_equal(ids, stepped)
+    return ids - EDGE, score
+
+
+# in several blocks, of which each hands on its best (5000 candidates) or all it has, and in one
+@pytest.mark.parametrize("pooling", ["MeanQK", "MaxQK", "MeanQ", "MaxQ", "MaxS", "MeanS"])
+@pytest.mark.parametrize("end", [-1.0, 1.0])             # the list's last quarter below zero, or above the rest of it
+@pytest.mark.parametrize("G,n_cand,k,high", [
+    (4, 5000, 32, 40), (4, 5000, 32, 33), (1, 5000, 32, 64), (4, 5000, 3, 63),
+    (8, 2400, 150, 190), (8, 1300, 20, 60), (4, 992, 32, 40), (4, 97, 20, 30),
+])
+def test_high_pages_far_from_the_last_block(G, n_cand, k, high, end, pooling):
+    """The best pages are in the first half of the list, the later the better, and far above all of its end."""
+    gen = np.random.default_rng(n_cand + high)
+    values = gen.integers(-64, 64, n_cand) / 64.0                                      # (bf16 holds these)
+    values[3 * n_cand // 4:] += end
+    at = np.sort(gen.permutation(n_cand // 2)[:high])
+    values[at] = 4.0 + np.arange(high) / 32.0
+    ids, score = _select(G, values, k, pooling)
+    assert np.array_equal(ids[0], _best(score[0], k))
+    assert set(ids[0]) <= set(at)
+
+
+@pytest.mark.parametrize("pooling", ["MeanQK", "MaxQK", "MeanQ", "MaxQ"])
+@pytest.mark.parametrize("G,n_cand,k", [(4, 5000, 32), (8, 1300, 20), (4, 992, 32), (1, 97, 40)])
+def test_scores_far_below_the_largest(G, n_cand, k, pooling):
+    """One page high, no more than k - 1 within eight octaves of it: the last of the chosen are among those of the last counter."""
+    values = np.full(n_cand, -3.0)
+    few = np.arange(5, n_cand, n_cand // (k + 12))[:k + 10]
+    values[few] = 2.0 ** -9 * (1.0 + (np.arange(len(few)) * 37 % 64) / 64.0)
+    values[few[: k // 2]] = 1.0
+    values[7] = 3.0
+    ids, score = _select(G, values, k, pooling)
+    assert np.array_equal(ids[0], _best(score[0], k))
