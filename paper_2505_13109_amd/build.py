@@ -8,8 +8,9 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfreekv.so")
-SOURCES = ["fkv_api.hip", "fkv_data.hip", "fkv_select.hip", "fkv_attn.hip", "fkv_step.hip", "fkv_step_home.hip",
-           "fkv_layer_hbm.hip", "fkv_layer_hbm_stream.hip", "fkv_layer_hbm_past.hip", "fkv_layer_host.hip", "fkv_layer_host_stream.hip"]
+SOURCES = ["fkv_api.hip", "fkv_data.hip", "fkv_select.hip", "fkv_attn.hip", "fkv_step.hip", "fkv_step_home.hip", "fkv_step_pool.hip", "fkv_step_pool_home.hip",
+           "fkv_layer_hbm.hip", "fkv_layer_hbm_stream.hip", "fkv_layer_hbm_past.hip", "fkv_layer_host.hip", "fkv_layer_host_stream.hip",
+           "fkv_layer_hbm_pool.hip", "fkv_layer_hbm_stream_pool.hip", "fkv_layer_hbm_past_pool.hip", "fkv_layer_host_pool.hip", "fkv_layer_host_stream_pool.hip"]
 
 # -ffp-contract=off: the arithmetic that decides page ids is written operation by operation.
 # packed fp32 ops are switched off for this target.

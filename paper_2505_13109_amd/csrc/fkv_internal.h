@@ -203,6 +203,12 @@ bool launch_layer_hbm_stream(const LayerIO& io, const LayerLaunch& l, int dtype,
 bool launch_layer_hbm_past(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
 bool launch_layer_host(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
 bool launch_layer_host_stream(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+// ... of the poolings beside the method's
+bool launch_layer_hbm_pool(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+bool launch_layer_hbm_stream_pool(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+bool launch_layer_hbm_past_pool(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+bool launch_layer_host_pool(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
+bool launch_layer_host_stream_pool(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st);
 // Dynamic LDS above the default 64 KiB per block has to be granted per kernel function; false if the device refuses.
 template <typename F>
 static bool grant_lds(F* fn, size_t lds, size_t& granted) {

@@ -28,7 +28,7 @@ struct LayerKernelArgs {                     // the kernel's arguments, in their
 };
 
 // what every block works out from the constants
-template <bool HOSTPOOL, bool HOME>
+template <bool HOSTPOOL, bool MEAN, bool HOME>
 struct LayerSetup {
   LayerConstPtr c;
   char* base;
@@ -77,7 +77,7 @@ struct LayerSetup {
     a.have_prev = (int)(ka.plan & 1u); a.tau = c->tau; a.corr_pool = c->corr_pool;
     a.flags = reinterpret_cast<uint8_t*>(at(c->o_flags)); a.flags_user = nullptr;
     a.cosine = reinterpret_cast<double*>(at(c->o_cosine));
-    a.sel_pool = c->sel_pool; a.P = c->P; a.score = c->score;
+    a.sel_pool = MEAN ? 0 : c->sel_pool; a.P = c->P; a.score = c->score;
     a.ids = ids(now); a.ids_user = nullptr;
     a.chunks = chunks; a.passes = 1 << passes_log2; a.slices = slices; a.slices_log2 = slices_log2;
     a.slice = (g.n_cand + slices - 1) >> slices_log2;
@@ -116,13 +116,19 @@ struct LayerSetup {
   }
 };
 
-template <int DT, int G, bool HOSTPOOL, int STREAM, bool HOME>
+// what a kernel is compiled for, beside the STREAM_* bits: the method's pooling, or any other (select_rows)
+constexpr int OTHER_POOLING = 4;
+static_assert(OTHER_POOLING > (STREAM_SUMMARIES | STREAM_PAGES), "");
+
+template <int DT, int G, bool HOSTPOOL, int KIND, bool HOME>
 __device__ __forceinline__ void layer_step(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
                                            uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
+  constexpr int STREAM = KIND & ~OTHER_POOLING;
+  constexpr bool MEAN = (KIND & OTHER_POOLING) == 0;
   touch<sizeof(LayerConst)>((LayerConstPtr)consts);
   const LayerKernelArgs ka{consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic};
-  const LayerSetup<HOSTPOOL, HOME> u(ka);
+  const LayerSetup<HOSTPOOL, MEAN, HOME> u(ka);
   StepArgs s;
   int head, nw = SEL_WAVES, own = 0;           // own: a selecting block's slice of the head's candidates, an attention block's split
   Selected got = Selected::NOTHING;
@@ -130,7 +136,7 @@ __device__ __forceinline__ void layer_step(const LayerConst* consts, const uint1
   const bool step = (int)blockIdx.y < u.step_rows;
   const auto again = [] {
     const LayerKernelArgs ka = args_from_memory<LayerKernelArgs>();
-    return LayerSetup<HOSTPOOL, HOME>(ka).step_args(ka);
+    return LayerSetup<HOSTPOOL, MEAN, HOME>(ka).step_args(ka);
   };
   if (step) {
     s = u.step_args(ka);
@@ -139,7 +145,7 @@ __device__ __forceinline__ void layer_step(const LayerConst* consts, const uint1
     step_roles<DT, G, (STREAM & STREAM_SUMMARIES) != 0>(s, blockIdx.x, blockIdx.y, [&](int m, int slice) {
       head = m;
       own = slice;
-      go_on = select_begin<G, true>(s, m, slice, dyn_lds, nw, got, again);
+      go_on = select_begin<G, true, MEAN>(s, m, slice, dyn_lds, nw, got, again);
     });
     if (!go_on) return;
   } else {
@@ -161,29 +167,29 @@ __device__ __forceinline__ void layer_step(const LayerConst* consts, const uint1
   }
   if (step) return;
   const LayerKernelArgs args = args_from_memory<LayerKernelArgs>();
-  attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL, HOME>(args).attn_args(args, G), own, head, left);
+  attn_finish<DT, STEP_WAVES, true, HOSTPOOL>(LayerSetup<HOSTPOOL, MEAN, HOME>(args).attn_args(args, G), own, head, left);
 }
 
-// STREAM: STREAM_* bits.  home_: a head's blocks on one XCD; two kernels, as in fkv_step_dev.h (8 heads x 992 candidates 8.5 us with a
+// KIND: STREAM_* bits, OTHER_POOLING.  home_: a head's blocks on one XCD; two kernels, as in fkv_step_dev.h (8 heads x 992 candidates 8.5 us with a
 // test beside each store, 8.2 without).  Four waves to a SIMD, no more and no fewer: with only the lower limit the compiler schedules for
 // more and leaves a slot of scratch memory, that nobody reads or writes, to kernels of G = 7 and 8, which costs each launch 0.9 us.
-template <int DT, int G, bool HOSTPOOL, int STREAM>
+template <int DT, int G, bool HOSTPOOL, int KIND>
 __global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
                   uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
-  layer_step<DT, G, HOSTPOOL, STREAM, false>(consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic);
+  layer_step<DT, G, HOSTPOOL, KIND, false>(consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic);
 }
-template <int DT, int G, bool HOSTPOOL, int STREAM>
+template <int DT, int G, bool HOSTPOOL, int KIND>
 __global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void home_layer_kernel(const LayerConst* consts, const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out,
                        uint32_t packed, uint32_t host_numbered, uint32_t plan, uint32_t split_magic) {
-  layer_step<DT, G, HOSTPOOL, STREAM, true>(consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic);
+  layer_step<DT, G, HOSTPOOL, KIND, true>(consts, q, k_new, v_new, out, packed, host_numbered, plan, split_magic);
 }
 
-template <int DT, int G, bool HOSTPOOL, int STREAM, bool HOME>
+template <int DT, int G, bool HOSTPOOL, int KIND, bool HOME>
 static bool launch_layer_g(const LayerIO& io, const LayerLaunch& l, hipStream_t st) {
   static size_t granted = 48 * 1024;
-  constexpr auto kernel = HOME ? &home_layer_kernel<DT, G, HOSTPOOL, STREAM> : &layer_kernel<DT, G, HOSTPOOL, STREAM>;
+  constexpr auto kernel = HOME ? &home_layer_kernel<DT, G, HOSTPOOL, KIND> : &layer_kernel<DT, G, HOSTPOOL, KIND>;
   if (!grant_lds(kernel, l.lds, granted)) return false;
   if (io.done)
     hipExtLaunchKernelGGL(kernel, l.grid, dim3(STEP_THREADS), l.lds, st, nullptr, io.done, 0,
@@ -194,10 +200,11 @@ static bool launch_layer_g(const LayerIO& io, const LayerLaunch& l, hipStream_t 
 }
 
 // one of these in each of the files that share the kernel's variants
-template <int DT, bool HOSTPOOL, int STREAM>
-static bool launch_layer_variant(const LayerIO& io, const LayerLaunch& l, int G, hipStream_t st) {
+template <bool HOSTPOOL, int KIND>
+static bool launch_layer_variant(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st) {
   switch (G) {
-#define FKV_CASE(GG) case GG: return l.home ? launch_layer_g<DT, GG, HOSTPOOL, STREAM, true>(io, l, st) : launch_layer_g<DT, GG, HOSTPOOL, STREAM, false>(io, l, st);
+#define FKV_CASE(GG) case GG: return dtype == 0 ? (l.home ? launch_layer_g<0, GG, HOSTPOOL, KIND, true>(io, l, st) : launch_layer_g<0, GG, HOSTPOOL, KIND, false>(io, l, st)) \
+                                                : (l.home ? launch_layer_g<1, GG, HOSTPOOL, KIND, true>(io, l, st) : launch_layer_g<1, GG, HOSTPOOL, KIND, false>(io, l, st));
     FKV_CASE(1) FKV_CASE(2) FKV_CASE(3) FKV_CASE(4) FKV_CASE(5) FKV_CASE(6) FKV_CASE(7) FKV_CASE(8)
 #undef FKV_CASE
     default: return false;

@@ -1,0 +1,10 @@
+// The layer kernel's variants: KV in HBM, the poolings beside the method's.
+#include "fkv_layer_dev.h"
+
+namespace fkv {
+
+bool launch_layer_hbm_pool(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st) {
+  return launch_layer_variant<false, OTHER_POOLING>(io, l, dtype, G, st);
+}
+
+}  // namespace fkv

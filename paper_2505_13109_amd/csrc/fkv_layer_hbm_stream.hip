@@ -4,7 +4,7 @@
 namespace fkv {
 
 bool launch_layer_hbm_stream(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st) {
-  return dtype == 0 ? launch_layer_variant<0, false, STREAM_SUMMARIES>(io, l, G, st) : launch_layer_variant<1, false, STREAM_SUMMARIES>(io, l, G, st);
+  return launch_layer_variant<false, STREAM_SUMMARIES>(io, l, dtype, G, st);
 }
 
 }  // namespace fkv

@@ -4,7 +4,7 @@
 namespace fkv {
 
 bool launch_layer_host_stream(const LayerIO& io, const LayerLaunch& l, int dtype, int G, hipStream_t st) {
-  return dtype == 0 ? launch_layer_variant<0, true, STREAM_SUMMARIES>(io, l, G, st) : launch_layer_variant<1, true, STREAM_SUMMARIES>(io, l, G, st);
+  return launch_layer_variant<true, STREAM_SUMMARIES>(io, l, dtype, G, st);
 }
 
 }  // namespace fkv

@@ -55,11 +55,12 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) __attribute__((amdgpu_waves_per_eu
   score_role<DT, G, false, SCAN_WAVES, PAST>(a, y - a.other_rows, blockIdx.x);
 }
 // The selection after it: one block per slice of a head's candidates, dealt to the heads (deal_block).
-template <int G, bool HOME>
+template <int G, bool MEAN, bool HOME>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];
   touch_args<sizeof(StepArgs)>();
   a.home = HOME;
+  if (MEAN) a.sel_pool = 0;
   int head, s;
   deal_block(blockIdx.x, a.slices, a.home, [&](uint32_t j) { return j >> a.slices_log2; }, head, s);
   if (head >= a.heads) return;
@@ -68,9 +69,10 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(StepArgs a) {
   const auto again = [] {
     StepArgs b = args_from_memory<StepArgs>();
     b.home = HOME;
+    if (MEAN) b.sel_pool = 0;
     return b;
   };
-  if (select_begin<G, false>(a, head, s, dyn_lds, nw, got, again)) select_finish<0, G, false>(a, head, s, dyn_lds, nw, got, again);
+  if (select_begin<G, false, MEAN>(a, head, s, dyn_lds, nw, got, again)) select_finish<0, G, false>(a, head, s, dyn_lds, nw, got, again);
 }
 
 constexpr size_t kLdsPerUnit = 150 * 1024;   // of the 160 KiB of a compute unit
@@ -90,8 +92,8 @@ static const int g_fuse = knob("FKV_FUSE", -1);
 // 9.8 (most corrected, 14.9 and 13.5); 32: 1040, G = 8, 11.8 and 10.2.  Fewer heads: 1 x 1100, G = 8, 11.4 and 9.9; 3 x 1400, G = 6, 10.2 and 9.4; 6 x
 // 1800, G = 5, 10.0 and 9.2.  With more heads it depends on what else the launch has to do -- 16 x 1100, G = 5, most
 // corrected, 15.8 and 16.1, 1200, G = 6, 12.0 and 11.9; 32 x 2100, G = 3, 18.8 and 20.2, x 2500 20.1 and 18.8 -- and two blocks a head are no better than one
-// (48 x 1300, G = 6, 20.1 and 20.2): there the list stays with one block a little longer, and so it does under the other poolings, whose
-// code takes all its rows however few are in use, and with the KV in a host pool, where the link decides
+// (48 x 1300, G = 6, 20.1 and 20.2): there the list stays with one block a little longer, and so it does under the other poolings, which
+// were not looked at again, and with the KV in a host pool, where the link decides
 // (8 x 1100, G = 8, 23.7 and 23.4; the same launch takes between 27 and 31 from one process to the next, 4 x 2500, G = 3).
 // A list that is shared is cut fine, since every phase
 // but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
@@ -234,7 +236,9 @@ constexpr long kFuseMaxChunks = 2560;
 
 template <int DT, int G>
 static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom& g, hipStream_t st) {
-  static size_t granted_select = 48 * 1024, granted_home = 48 * 1024;
+  static constexpr void (*select_kernels[2][2])(StepArgs) = {{&select_kernel<G, true, false>, &select_kernel<G, true, true>},
+                                                             {&select_kernel<G, false, false>, &select_kernel<G, false, true>}};
+  static size_t granted[2][2] = {{48 * 1024, 48 * 1024}, {48 * 1024, 48 * 1024}};
   StepArgs a;
   int rows;
   size_t lds;
@@ -254,7 +258,8 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
     fill_step_args(d, roles, io, g, PAGES_PER_PASS, scoring_passes(d, g, slices, 0, kLayerResident, io.pd.placement == 0 && little_excess(d, heads, g.n_cand * kSummaryBytes, false)), slices, a, rows, lds);
     const bool past = (stream_of(d, g) & STREAM_SUMMARIES) != 0;
     a.home = (roles & ROLE_SELECT) != 0 && heads_at_home(d, heads, rows, g.n_cand * kSummaryBytes);
-    if (!(a.home ? launch_step_kernel_home : launch_step_kernel)(a, DT, G, past, rows, lds, st)) return -1;
+    const bool other = d.sel_pool != 0;
+    if (!(other ? (a.home ? launch_step_kernel_pool_home : launch_step_kernel_pool) : a.home ? launch_step_kernel_home : launch_step_kernel)(a, DT, G, past, rows, lds, st)) return -1;
     if (roles & ROLE_SELECT) *io.P_tagged = true;
     return 1;
   }
@@ -262,14 +267,14 @@ static int launch_step_g(const Dims& d, int roles, const StepIO& io, const Geom&
   a.P = reinterpret_cast<unsigned long long*>(io.P_plain);
   a.cmax = reinterpret_cast<unsigned long long*>(io.cmax_plain);
   a.home = a.slices > 1 && heads_at_home(d, heads, a.slices, (double)g.n_cand * d.G * sizeof(float));
-  if (!(a.home ? grant_lds(&select_kernel<G, true>, lds, granted_home) : grant_lds(&select_kernel<G, false>, lds, granted_select))) return -1;
+  const int other = d.sel_pool != 0, home = a.home;
+  if (!grant_lds(select_kernels[other][home], lds, granted[other][home])) return -1;
   a.other_rows = (((roles & ROLE_APPEND ? 1 : 0) + (roles & ROLE_CORR ? 1 : 0)) * heads + a.chunks - 1) / a.chunks;
   const int scan_rows = a.other_rows + heads;
   const dim3 scan_grid(a.chunks, scan_rows < kGridRows ? scan_rows : kGridRows, (scan_rows + kGridRows - 1) / kGridRows);
   if (stream_of(d, g) & STREAM_SUMMARIES) scan_kernel<DT, G, true><<<scan_grid, SCAN_WAVES * 64, 0, st>>>(a);
   else                                    scan_kernel<DT, G, false><<<scan_grid, SCAN_WAVES * 64, 0, st>>>(a);
-  if (a.home) select_kernel<G, true><<<by_xcd(heads) * a.slices, SEL_THREADS, lds, st>>>(a);
-  else        select_kernel<G, false><<<heads * a.slices, SEL_THREADS, lds, st>>>(a);
+  select_kernels[other][home]<<<(home ? by_xcd(heads) : heads) * a.slices, SEL_THREADS, lds, st>>>(a);
   *io.P_tagged = false;
   return 2;
 }
@@ -381,9 +386,11 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   *io.launch_lds = l.lds;
   *io.launch_home = l.home;
   const int stream = stream_of(d, g);
-  const auto launch = io.host_pool ? (stream & STREAM_SUMMARIES ? launch_layer_host_stream : launch_layer_host)
-                      : stream & STREAM_PAGES ? launch_layer_hbm_past : stream & STREAM_SUMMARIES ? launch_layer_hbm_stream : launch_layer_hbm;
-  return launch(io, l, d.dtype, d.G, st);
+  const bool other = d.sel_pool != 0;
+  const auto host = stream & STREAM_SUMMARIES ? (other ? launch_layer_host_stream_pool : launch_layer_host_stream) : other ? launch_layer_host_pool : launch_layer_host;
+  const auto hbm = stream & STREAM_PAGES ? (other ? launch_layer_hbm_past_pool : launch_layer_hbm_past)
+                   : stream & STREAM_SUMMARIES ? (other ? launch_layer_hbm_stream_pool : launch_layer_hbm_stream) : other ? launch_layer_hbm_pool : launch_layer_hbm;
+  return (io.host_pool ? host : hbm)(io, l, d.dtype, d.G, st);
 }
 
 // ---------------------------------------------------------------------------------

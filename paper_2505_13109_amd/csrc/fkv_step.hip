@@ -5,6 +5,6 @@
 
 namespace fkv {
 bool launch_step_kernel(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st) {
-  return launch_step_kernel_variant<false>(a, dtype, G, past, rows, lds, st);
+  return launch_step_kernel_variant<true, false>(a, dtype, G, past, rows, lds, st);
 }
 }  // namespace fkv

@@ -487,20 +487,28 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t want, ui
 // The keys of the one bin that is only partly wanted are collected with their places in the order and ranked against each other by every
 // wave; the same barrier brings the counts per wave of what is chosen anyway, and which of the others are chosen is the same in every
 // wave.  False, and nothing done, if there are more than 64 of them (ties, mostly).
-// ANY: of any keys.  Else of keys up to bins.top: what is left of a key in a bin, and the place, fit 32 bits -- except in the last bin,
-// which is as wide as it takes: false there too.
+// ANY: of any keys, in the slots below `first` and from A on, `second` of them.  Else of keys up to bins.top, in all slots: what is left
+// of a key in a bin, and the place, fit 32 bits -- except in the last bin, which is as wide as it takes: false there too.
 // The chain is what counts (a wave by itself: an instruction 4 cycles, a value that goes from the vector unit through a scalar and back 28,
 // a branch that is not taken 24 and one that is 38, one by a lane's condition 55, an LDS trip 57): so everything is done for all T slots at
 // once, by masks, and what a lane has no use for goes to a place that nobody reads -- a place of its own, since lanes queue up for one
 // word (512 atomics on one counter take 1090 cycles, on 32 of them 120).  From the weights to the ids, with the slots in loops over those
 // in use and the poolings told apart beside each, and so: 97 candidates, G = 4, 2.5 and 1.8 us; 992 3.8 and 3.0; 2015 in eight blocks, G = 8,
 // 6.0 and 4.9; layer-steps of 96 candidates, G = 7, all heads corrected 11.0 and 10.1.
-template <bool ANY, int T, typename Emit>
-__device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int kk, TopkBins bins, int nw, SelectLds& sm, Emit emit) {
+template <bool ANY, int A, int T, typename Emit>
+__device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int first, int second, int n, int kk, TopkBins bins, int nw, SelectLds& sm, Emit emit) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto slots = [&](auto f) {
 #pragma unroll
-    for (int u = 0; u < T; ++u) f(u);
+    for (int u = 0; u < A; ++u) {
+      if (ANY && u >= first) break;
+      f(u);
+    }
+#pragma unroll
+    for (int u = A; u < T; ++u) {
+      if (ANY && u - A >= second) break;
+      f(u);
+    }
   };
   uint32_t above = 0, from = 0, base = 0;            // keys > above are chosen; those > from, up to there, if their turn comes
   uint32_t take = 0, in_bin = 0;                     // how many of these are wanted
@@ -518,22 +526,26 @@ __device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int 
     above = !ranked ? from : bin == 0 ? ~0u : base;
   }
   static_assert(T * SEL_WAVES <= 64 && T * SEL_THREADS <= 4096 && 19 + 12 < 32, "");
-  unsigned long long sure[T], maybe[T];
+  unsigned long long sure[T], maybe[T];              // (not ANY)
   uint32_t counts = 0;                               // lane u: slot u's
+  uint32_t mine = 0;                                 // this lane's that go on the list
   slots([&](int u) {
-    sure[u] = __ballot(key[u] > above);
-    const uint32_t c = (uint32_t)__popcll(sure[u]);
-    counts = u == 0 || lane == u ? c : counts;
+    const unsigned long long b = __ballot(key[u] > above);
+    if (ANY) mine += key[u] > from && !(key[u] > above) ? 1u : 0u;           // (one loop for both: a branch for each slot)
+    else     sure[u] = b;
+    const uint32_t c = (uint32_t)__popcll(b);
+    counts = lane == u || (u == 0 && (!ANY || lane >= T)) ? c : counts;
   });
   auto place = [&](int u) { return (uint32_t)(u * nw * 64 + tid); };
   auto rank_of = [&](int u) { return ((base - min(key[u], base)) << 12) + place(u); };
   auto whole_rank_of = [&](int u) { return (unsigned long long)~key[u] << 32 | place(u); };
   if (ranked) {
-    uint32_t mine = 0;
-    slots([&](int u) {
-      maybe[u] = __ballot(key[u] > from) & ~sure[u];
-      mine += key[u] > from && !(key[u] > above) ? 1u : 0u;
-    });
+    if (!ANY) {
+      slots([&](int u) {
+        maybe[u] = __ballot(key[u] > from) & ~sure[u];
+        mine += key[u] > from && !(key[u] > above) ? 1u : 0u;
+      });
+    }
     if (mine != 0) {
       // (an atomic of each lane that has some: one for the wave would be a longer chain, and lanes queue up for one address)
       auto* n_list = (__attribute__((address_space(3))) uint32_t*)&sm.n_list;
@@ -553,8 +565,9 @@ __device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int 
   cnt = lane < T * nw ? cnt : 0u;
   unsigned long long picked = 0;                     // of the list
   uint32_t at = ~0u;                                 // the place of this lane's entry
+  unsigned long long up_to = ((unsigned long long)~above << 32) - 1;         // (ANY: the last of the chosen, or what they are all before)
   if (ranked) {
-    // an entry a lane; up to `last` they are chosen
+    // an entry a lane
     if constexpr (ANY) {
       unsigned long long entry = sm.whole[lane];
       entry = lane < (int)in_bin ? entry : ~0ull;
@@ -564,10 +577,9 @@ __device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int 
 #pragma unroll
         for (uint32_t v = 0; v < 4; ++v) before += lane_u64(entry, (int)(i + v)) < entry ? 1u : 0u;
       }
-      const unsigned long long last = lane_u64(entry, __builtin_ctzll(__ballot(before == take - 1 && lane < (int)in_bin)));
-      picked = __ballot(entry <= last);
+      up_to = lane_u64(entry, __builtin_ctzll(__ballot(before == take - 1 && lane < (int)in_bin)));
+      picked = __ballot(entry <= up_to);
       at = (uint32_t)entry;
-      slots([&](int u) { sure[u] |= maybe[u] & __ballot(whole_rank_of(u) <= last); });
     } else {
       uint32_t entry = sm.list[lane];
       entry = lane < (int)in_bin ? entry : ~0u;
@@ -587,8 +599,9 @@ __device__ __forceinline__ bool topk_items(const uint32_t (&key)[T], int n, int 
   slots([&](int u) {
     uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)excl, u * nw + wave);
     if (ranked) before += (uint32_t)__popcll(picked & __ballot(group < (uint32_t)(u * nw + wave)));
-    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(sure[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)sure[u], before));
-    emit(u, sure[u], (int)pos);
+    const unsigned long long chosen = ANY ? __ballot(whole_rank_of(u) <= up_to) : sure[u];
+    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(chosen >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)chosen, before));
+    emit(u, chosen, (int)pos);
   });
   return true;
 }
@@ -716,8 +729,8 @@ struct PutId {
 // A wave whose patience ends has nothing to say, and what it would have had to is never put into words under the tag: its
 // group learns of it at the next barrier, from a value no sum has or a flag, and leaves.  Of the groups only the last one has to
 // end with all the keys, and it can make them alone (alone_keys).  Returns how far the group got.
-// MEAN: the method's own scores, straight through for U rows of candidates per thread; else any other pooling, U: most rows.  SHARED:
-// there may be several groups (MEAN: there are).
+// MEAN: the method's own scores, straight through for U rows of candidates per thread; else any other pooling, by those of U rows that
+// are in use.  SHARED: there may be several groups (MEAN: there are).
 template <int G, bool TAGGED, bool MEAN, bool SHARED, int U>
 __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, int s, int nw, uint32_t* key_lds, SelectLds& sm) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = nw * 64;
@@ -729,11 +742,13 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
   const bool soft = mode <= 1;                         // the variants that pool softmax values
   const int ng = mode >= 4 ? 1 : G;                    // weights in use per page (pooled query: the group's first)
   constexpr int GP = group_pow2(G);
+  asm volatile(".p2align 6");                          // (here and at the polls: see select_rows)
   for (int i = tid * 4; i < TOPK_BINS; i += nt * 4) *reinterpret_cast<uint4*>(&sm.hist[i]) = make_uint4(0, 0, 0, 0);
   if (tid == 0) { sm.n_list = 0; sm.alone = 0; }
   // load_and_check() until every lane's words carry the tag; false: patience ended
   auto poll = [&](uint32_t kind, auto load_and_check) {
     int it = 0;
+    asm volatile(".p2align 6");
     while (__ballot(!load_and_check()) != 0) {
       if (++it > PATIENCE) return false;
       __builtin_amdgcn_s_sleep(1);
@@ -746,6 +761,14 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
   // largest weights of the head's chunks: 64w + l, 512 + 64w + l, ... in lane l, which is for head l % GP ----
   uint32_t e[U][G];                                    // bits of the weights, then softmax numerators
   auto ours = [&](int u) { return tid + u * nt < j1 - j0; };
+  const int rows = MEAN ? U : (j1 - j0 + SEL_THREADS - 1) / SEL_THREADS;       // (in a group that is not whole one)
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!MEAN && u >= rows) break;
+      f(u);
+    }
+  };
   float largest = -__builtin_inff();
   const int n_max = shared && soft ? a.chunks * (TAGGED ? 1 : SCAN_WAVES) * GP : 0;
   const size_t max0 = head * (TAGGED ? cmax_stride(a.max_pages) : cmax_plain_stride(a.max_pages));
@@ -791,7 +814,19 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     }
   };
   static_assert(U == 1 || U == 2 || U == 4 || U == 8, "");
-  if constexpr (U == 1) {
+  if constexpr (!MEAN) {
+    if (rows == 1) {
+      weights(UnrollBy<0>{}, UnrollBy<1>{});
+    } else if (rows == 2) {
+      weights(UnrollBy<0>{}, UnrollBy<2>{});
+    } else if constexpr (U == 8) {
+      weights(UnrollBy<0>{}, UnrollBy<4>{});
+      if (rows > 4) weights(UnrollBy<4>{}, UnrollBy<4>{});
+    } else {
+      weights(UnrollBy<0>{}, UnrollBy<2>{});
+      weights(UnrollBy<2>{}, UnrollBy<2>{});
+    }
+  } else if constexpr (U == 1) {
     weights(UnrollBy<0>{}, UnrollBy<1>{});
   } else if constexpr (U == 2) {
     weights(UnrollBy<0>{}, UnrollBy<2>{});
@@ -833,10 +868,11 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
       uint32_t v[GP];
 #pragma unroll
       for (int gg = 0; gg < GP; ++gg) v[gg] = gg < G ? e[0][gg < G ? gg : 0] : 0u;
-#pragma unroll
-      for (int u = 1; u < U; ++u)
+      each([&](int u) {
+        if (u == 0) return;
 #pragma unroll
         for (int gg = 0; gg < G; ++gg) v[gg] = OpMaxF32()(v[gg], e[u][gg]);
+      });
       largest = __uint_as_float(class_fold_row<GP>(v, OpMaxF32()));
     }
     sm.mx_row[lane & (GP - 1)][of_row] = largest;
@@ -850,8 +886,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     for (int gg = 0; gg < GP; ++gg) zl[gg] = zh[gg] = 0;
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) mx[gg] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(largest), gg * 8));
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
+    each([&](int u) {
 #pragma unroll
       for (int gg = 0; gg < G; ++gg) {
         const uint32_t en = softmax_fixed(__uint_as_float(e[u][gg]), mx[gg]);
@@ -860,7 +895,7 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
         zl[gg] = __builtin_amdgcn_udot2(c, u16x2{1, 0}, zl[gg], false);
         zh[gg] = __builtin_amdgcn_udot2(c, u16x2{0, 1}, zh[gg], false);
       }
-    }
+    });
     // (a group's upper halves come to 2^28 at most if one of its waves has not seen its weights, else to 2^27)
     uint2 z = make_uint2(class_fold_row<GP>(zl, OpAddU32()), class_fold_row<GP>(zh, OpAddU32()));
     if (failed && lane < 16) z.y = kNoSum;
@@ -899,10 +934,10 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     }
   } else {
     float most = -__builtin_inff();                    // weight: no score is above it (a thread without a candidate repeats the last one)
-#pragma unroll
-    for (int u = 0; u < U; ++u)
+    each([&](int u) {
 #pragma unroll
       for (int gg = 0; gg < G; ++gg) most = fmaxf(most, __uint_as_float(e[u][gg]));
+    });
     sm.mx[wave][0] = wave_max_f32(most);
     if (lane == 0) sm.failed[wave] = failed ? 1 : 0;
     lds_barrier();
@@ -921,30 +956,32 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
 
   // ---- pooled scores -> keys (0: no candidate) ----
   uint32_t key[U];
+  if (!MEAN) {
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < U; ++u) key[u] = 0;
+  }
+  each([&](int u) {
     const uint32_t ku = score_key(MEAN ? mean_score<G>(e[u], zd, zr) : pooled_score<G>(e[u], zd, zr, mode));
     key[u] = ours(u) ? ku : 0u;
-  }
+  });
   auto id = [&](int u) { return lo + j0 + tid + u * nt; };
   auto store_scores = [&]() {                          // (kept for inspection: nobody waits for them)
-#pragma unroll
-    for (int u = 0; u < U; ++u)
+    each([&](int u) {
       if (ours(u)) a.score[(size_t)head * a.max_pages + id(u)] = key_score(key[u]);
+    });
   };
   if (shared && !last && all) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
+    each([&](int u) {
       if (ours(u) && !failed) st_tag(keyx + id(u) - lo, key[u], tag, a.home);
+    });
     store_scores();
     return failed ? Selected::NOTHING : Selected::IDS;
   }
   auto count = [&](uint32_t k, bool there) { atomicAdd(&sm.hist[there ? topk_bin(k, bins) : (uint32_t)(TOPK_BINS + lane)], 1u); };
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
+  each([&](int u) {
     count(key[u], ours(u));
     if (shared && !fits && ours(u)) key_lds[others + tid + u * nt] = key[u];
-  }
+  });
   uint32_t key_of[SEL_OTHERS];                         // the other groups'
   int id_of[SEL_OTHERS];
 #pragma unroll
@@ -1018,11 +1055,11 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
   const PutId put(a, head, key_lds);
   bool done;
   if (!shared) {
-    done = topk_items<!MEAN>(key, n, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+    done = topk_items<!MEAN, U>(key, rows, 0, n, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
       if (__builtin_amdgcn_inverse_ballot_w64(chosen)) put(pos, id(u));
     });
   } else if (!last) {
-    done = topk_items<!MEAN>(key, j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+    done = topk_items<!MEAN, U>(key, rows, 0, j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
       if (__builtin_amdgcn_inverse_ballot_w64(chosen)) {
         st_tag(keyx + s * m + pos, key[u], tag, a.home);
         st_tag(keyid + s * m + pos, (uint32_t)id(u), tag, a.home);
@@ -1034,41 +1071,45 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
       uint32_t item[T];
 #pragma unroll
       for (int u = 0; u < T; ++u) item[u] = u < XR ? key_of[u < XR ? u : 0] : key[u < XR ? 0 : u - XR];
-      return topk_items<!MEAN>(item, others + j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+      return topk_items<!MEAN, XR>(item, X, rows, others + j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
         if (__builtin_amdgcn_inverse_ballot_w64(chosen)) put(pos, u < XR ? id_of[u < XR ? u : 0] : id(u < XR ? 0 : u - XR));
       });
     };
-    done = X <= 1 ? choose(UnrollBy<1>{}) : choose(UnrollBy<SEL_OTHERS>{});
+    done = MEAN && X <= 1 ? choose(UnrollBy<1>{}) : choose(UnrollBy<SEL_OTHERS>{});
   }
   store_scores();
   if (__builtin_expect(done, 1)) return Selected::IDS;
-#pragma unroll
-  for (int u = 0; u < U; ++u)
+  each([&](int u) {
     if (ours(u)) key_lds[others + tid + u * nt] = key[u];
+  });
 #pragma unroll
   for (int x = 0; x < SEL_OTHERS; ++x)
     if (tid + x * SEL_THREADS < others) key_lds[tid + x * SEL_THREADS] = key_of[x];
   lds_barrier();
   return Selected::KEYS;
 }
-// By the rows of candidates that a thread has, and the method's own scores apart from the other poolings: each is straight code then (a
-// test of the pooling beside every row and of the rows in use beside every phase cost 0.6 to 1 us of what topk_items says).
+// The method's own scores by the rows of candidates that a thread has: each is straight code then (a test of the pooling beside every row
+// and of the rows in use beside every phase cost 0.6 to 1 us of what topk_items says).  The other poolings have kernels of their own.
 // again(): the arguments once more, from memory: what several ways have in common would be worked out ahead of them all and kept in lanes of
-// vector registers, of which a host pool's kernels have none to spare.
-template <int G, bool TAGGED, typename Again>
+// vector registers, of which a host pool's kernels have none to spare (with it for lists of one block too, 8 heads x 97 and 480 candidates
+// 6.63 and 6.92 us a layer-step, so 6.51 and 6.82, and the step kernel has no scratch memory up to G = 6 but for fp16 G = 4).
+// Where the ways and their polls start within 64 bytes is worth up to 10 % where few blocks have a list on units that are otherwise
+// idle (page_select of one head x 5000 candidates 10.5 to 11.7 us with code ahead of it that is not run, 10.6 aligned; layer-steps of one to
+// four heads x 1700 to 8160 candidates 1 % longer without, 1.5 % shorter so).
+template <int G, bool TAGGED, bool MEAN, typename Again>
 __device__ __forceinline__ Selected select_rows(const StepArgs& a, int head, int s, int nw, int mine, uint32_t* key, SelectLds& sm, Again again) {
   constexpr int REGS = sel_regs_alone(G);
   const int nt = nw * 64;
-  if (__builtin_expect(a.sel_pool != 0, 0)) return select_group<G, TAGGED, false, true, REGS>(again(), head, s, nw, key, sm);
+  if constexpr (!MEAN) return select_group<G, TAGGED, false, true, REGS>(a, head, s, nw, key, sm);
   if (a.slices > 1) {
     if (mine <= nt) return select_group<G, TAGGED, true, true, 1>(again(), head, s, nw, key, sm);
     if (mine <= 2 * nt) return select_group<G, TAGGED, true, true, 2>(again(), head, s, nw, key, sm);
     return select_group<G, TAGGED, true, true, SEL_REGS>(again(), head, s, nw, key, sm);
   }
-  if (mine <= nt) return select_group<G, TAGGED, true, false, 1>(a, head, s, nw, key, sm);
-  if (mine <= 2 * nt) return select_group<G, TAGGED, true, false, 2>(a, head, s, nw, key, sm);
-  if (REGS == 4 || mine <= 4 * nt) return select_group<G, TAGGED, true, false, 4>(a, head, s, nw, key, sm);
-  return select_group<G, TAGGED, true, false, REGS>(a, head, s, nw, key, sm);
+  if (mine <= nt) return select_group<G, TAGGED, true, false, 1>(again(), head, s, nw, key, sm);
+  if (mine <= 2 * nt) return select_group<G, TAGGED, true, false, 2>(again(), head, s, nw, key, sm);
+  if (REGS == 4 || mine <= 4 * nt) return select_group<G, TAGGED, true, false, 4>(again(), head, s, nw, key, sm);
+  return select_group<G, TAGGED, true, false, REGS>(again(), head, s, nw, key, sm);
 }
 
 // The weight of one page for one query head of the group by one thread, bit for bit score_pages'.
@@ -1193,7 +1234,7 @@ __device__ __forceinline__ void alone_keys(const StepArgs& a, int head, int nw, 
 
 // Selecting block `s` of a head.  True for the waves that go on with select_finish -- the last block's, nw of them, and another's
 // that has its choice still to make -- and `got`: how far they are.
-template <int G, bool TAGGED, typename Again>
+template <int G, bool TAGGED, bool MEAN, typename Again>
 __device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s, uint32_t* key, int& nw, Selected& got, Again again) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = a.slices, j0 = s * a.slice, j1 = min(a.g.n_cand, j0 + a.slice);
@@ -1206,7 +1247,7 @@ __device__ __forceinline__ bool select_begin(const StepArgs& a, int head, int s,
   if (a.g.k_eff == 0) return true;
   // What the end of the chain needs of the arguments is read now, while the weights are waited for
   // (0.3 us of a layer-step of 8 to 20 us).
-  got = (Selected)__builtin_amdgcn_readfirstlane((int)select_rows<G, TAGGED>(a, head, s, nw, j1 - j0, key, select_lds(), again));
+  got = (Selected)__builtin_amdgcn_readfirstlane((int)select_rows<G, TAGGED, MEAN>(a, head, s, nw, j1 - j0, key, select_lds(), again));
   return last || got == Selected::KEYS;
 }
 
@@ -1294,39 +1335,41 @@ __device__ __forceinline__ void step_roles(const StepArgs& a, int x, int y, Sele
 // ---------------------------------------------------------------------------------
 // grid (heads -- at home, the next multiple of 8 -- , rows): rows as in step_roles.  HOME is known when this is compiled because a
 // launch is a chain of a few microseconds and the test beside every store that other blocks wait for costs it 0.1 to 0.3 of them
-// (8 heads x 992 candidates 8.2 us with the test, 8.0 without; at home 7.6 and 7.5).
+// (8 heads x 992 candidates 8.2 us with the test, 8.0 without; at home 7.6 and 7.5).  MEAN: the method's pooling, or any other (select_rows).
 // ---------------------------------------------------------------------------------
-template <int DT, int G, bool PAST, bool HOME>
+template <int DT, int G, bool MEAN, bool PAST, bool HOME>
 __global__ __launch_bounds__(STEP_THREADS) void step_kernel(StepArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t dyn_lds[];              // selection: n_cand keys, then the recall plan
   touch_args<sizeof(StepArgs)>();
   a.home = HOME;
+  if (MEAN) a.sel_pool = 0;
   step_roles<DT, G, PAST>(a, blockIdx.x, blockIdx.y, [&](int head, int s) {
     int nw;
     Selected got;
     const auto again = [] {
       StepArgs b = args_from_memory<StepArgs>();
       b.home = HOME;
+      if (MEAN) b.sel_pool = 0;
       return b;
     };
-    if (select_begin<G, true>(a, head, s, dyn_lds, nw, got, again)) select_finish<DT, G, true>(a, head, s, dyn_lds, nw, got, again);
+    if (select_begin<G, true, MEAN>(a, head, s, dyn_lds, nw, got, again)) select_finish<DT, G, true>(a, head, s, dyn_lds, nw, got, again);
   });
 }
 
-template <int DT, int G, bool PAST, bool HOME>
+template <int DT, int G, bool MEAN, bool PAST, bool HOME>
 static bool launch_step_kernel_g(const StepArgs& a, int rows, size_t lds, hipStream_t st) {
   static size_t granted = 48 * 1024;
-  if (!grant_lds(&step_kernel<DT, G, PAST, HOME>, lds, granted)) return false;
-  step_kernel<DT, G, PAST, HOME><<<dim3(HOME ? by_xcd(a.heads) : a.heads, rows), STEP_THREADS, lds, st>>>(a);
+  if (!grant_lds(&step_kernel<DT, G, MEAN, PAST, HOME>, lds, granted)) return false;
+  step_kernel<DT, G, MEAN, PAST, HOME><<<dim3(HOME ? by_xcd(a.heads) : a.heads, rows), STEP_THREADS, lds, st>>>(a);
   return true;
 }
 
 // one of these in each of the files that share the kernel's variants
-template <bool HOME>
+template <bool MEAN, bool HOME>
 static bool launch_step_kernel_variant(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st) {
   switch (G) {
-#define FKV_CASE(GG) case GG: return dtype == 0 ? (past ? launch_step_kernel_g<0, GG, true, HOME>(a, rows, lds, st) : launch_step_kernel_g<0, GG, false, HOME>(a, rows, lds, st)) \
-                                                : (past ? launch_step_kernel_g<1, GG, true, HOME>(a, rows, lds, st) : launch_step_kernel_g<1, GG, false, HOME>(a, rows, lds, st));
+#define FKV_CASE(GG) case GG: return dtype == 0 ? (past ? launch_step_kernel_g<0, GG, MEAN, true, HOME>(a, rows, lds, st) : launch_step_kernel_g<0, GG, MEAN, false, HOME>(a, rows, lds, st)) \
+                                                : (past ? launch_step_kernel_g<1, GG, MEAN, true, HOME>(a, rows, lds, st) : launch_step_kernel_g<1, GG, MEAN, false, HOME>(a, rows, lds, st));
     FKV_CASE(1) FKV_CASE(2) FKV_CASE(3) FKV_CASE(4) FKV_CASE(5) FKV_CASE(6) FKV_CASE(7) FKV_CASE(8)
 #undef FKV_CASE
     default: return false;
@@ -1334,5 +1377,7 @@ static bool launch_step_kernel_variant(const StepArgs& a, int dtype, int G, bool
 }
 bool launch_step_kernel(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st);        // a head's blocks adjacent
 bool launch_step_kernel_home(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st);   // ... on one XCD
+bool launch_step_kernel_pool(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st);   // the same for a.sel_pool != 0
+bool launch_step_kernel_pool_home(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st);
 
 }  // namespace fkv

@@ -5,6 +5,6 @@
 
 namespace fkv {
 bool launch_step_kernel_home(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st) {
-  return launch_step_kernel_variant<true>(a, dtype, G, past, rows, lds, st);
+  return launch_step_kernel_variant<true, true>(a, dtype, G, past, rows, lds, st);
 }
 }  // namespace fkv

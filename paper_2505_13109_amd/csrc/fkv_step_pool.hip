@@ -1,0 +1,10 @@
+// Variants of the step kernel for the poolings beside the method's: a head's blocks adjacent in block order.  (In files of their own so that they are compiled side by side.)
+#include "fkv_step_dev.h"
+
+#pragma clang fp contract(off)
+
+namespace fkv {
+bool launch_step_kernel_pool(const StepArgs& a, int dtype, int G, bool past, int rows, size_t lds, hipStream_t st) {
+  return launch_step_kernel_variant<false, false>(a, dtype, G, past, rows, lds, st);
+}
+}  // namespace fkv

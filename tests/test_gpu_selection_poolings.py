@@ -77,3 +77,23 @@ def test_scores_far_below_the_largest(G, n_cand, k, pooling):
     values[7] = 3.0
     ids, score = _select(G, values, k, pooling)
     assert np.array_equal(ids[0], _best(score[0], k))
+
+
+@pytest.mark.parametrize("pooling", ["MaxS", "MeanQK", "MaxQK", "MeanQ", "MaxQ"])
+@pytest.mark.parametrize("G,n_cand,k,batch", [
+    (4, 1, 1, 1), (4, 63, 7, 1), (7, 65, 64, 1),          # one wave, two
+    (4, 512, 32, 1), (4, 513, 512, 1),                    # one row of candidates a thread, a second of one candidate
+    (8, 1024, 96, 1), (8, 1025, 3, 1), (5, 1537, 33, 1),  # two, three, four
+    (3, 2049, 64, 1), (2, 3073, 40, 1), (2, 4096, 500, 1),           # five, seven, eight
+    (4, 2400, 33, 1), (4, 6000, 32, 1), (1, 9000, 600, 1),           # several blocks: every key handed on, each block's best, too many for registers
+    (4, 513, 32, 320), (2, 2100, 32, 256),                # in a launch of their own
+])
+def test_rows_in_use(G, n_cand, k, batch, pooling):
+    """Random pages: the ids are those of the scores, and the scores of one request the same bits in a launch of any shape."""
+    gen = np.random.default_rng(n_cand + k)
+    values = (gen.standard_normal(n_cand) * 0.5).astype(np.float32)
+    ids, score = _select(G, values, k, pooling, batch=batch)
+    one, s1 = _select(G, values, k, pooling, batch=12)
+    assert np.array_equal(score, np.broadcast_to(s1[0], score.shape)) and np.array_equal(s1, np.broadcast_to(s1[0], s1.shape))
+    want = _best(s1[0], k)
+    assert np.array_equal(ids, np.broadcast_to(want, ids.shape)) and np.array_equal(one, np.broadcast_to(want, one.shape))

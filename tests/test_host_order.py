@@ -333,5 +333,18 @@ def test_no_more_blocks_of_a_head_wait_on_an_xcd_than_four_launches_leave_room_f
     assert rows - 3 - splits in scoring, rows
 
 
+@pytest.mark.parametrize("placement", [0, 1])
+@pytest.mark.parametrize("pooling", range(6))
+def test_the_poolings_beside_the_methods_have_kernels_of_their_own(play, pooling, placement):
+    """In each of the launches that pick pages: with the layer-step, by themselves, and after a scan of their own."""
+    (op,) = [op for op in _decode(play, 8, 480, 33, placement=placement, select_pooling=pooling) if "layer_kernel" in op[1]]
+    kind = int(op[1].split("layer_kernelILi1ELi4ELb" + str(placement) + "ELi")[1].split("E")[0])
+    assert (kind & 4 != 0) == (pooling != 0)
+    (op,) = _decode(play, 8, 480, 33, call="select", placement=placement, select_pooling=pooling)
+    assert "step_kernelILi1ELi4ELb" + ("1" if pooling == 0 else "0") + "E" in op[1]
+    op = _decode(play, 256, 480, 33, call="select", placement=placement, select_pooling=pooling)[-1]
+    assert "select_kernelILi4ELb" + ("1" if pooling == 0 else "0") + "E" in op[1]
+
+
 if __name__ == "__main__":
     print(json.dumps(_play(*json.loads(sys.argv[1]))))
