@@ -99,7 +99,7 @@ static const int g_fuse = knob("FKV_FUSE", -1);
 // but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
 // in 4, 8, 16 blocks: 2300 candidates 10.6, 9.6, 10.1; 4000: 13.1, 12.0, 11.7; 8160: 17.8, 15.9, 15.2; 2016, G = 8, 12.5, 12.0, 13.3; but 16 heads
 // x 1200, G = 6, 11.9, 12.0, 12.0.
-constexpr int kLightWork = 16, kFewShared = 8, kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024, kFewHeads = 40;
+constexpr int kLightWork = 16, kFewShared = 8, kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024, kFewHeads = 40, kFewSlices = 4;
 static int selection_slices(const Dims& d, const Geom& g, bool host_pool) {
   const int n = g.n_cand, G = d.G, heads = d.batch * d.n_kv, regs = sel_regs_alone(G);
   int rows = 1;
@@ -315,7 +315,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   if (io.host_pool && (d.max_pages > TAGGED_MAX_PAGES || 2 * d.k > TAGGED_MAX_SLOTS)) return false;
   const int heads = d.batch * d.n_kv;
   const int n_att = g.n_sink + d.k + g.n_win + (g.r > 0 ? 1 : 0), n_there = n_att - d.k + g.k_eff;
-  const int slices = selection_slices(d, g, io.host_pool);
+  int slices = selection_slices(d, g, io.host_pool);
   // Attention's blocks, which come last, are fewer where a list is shared, since selecting blocks wait too.  Beside long lists of
   // many heads, a block each, a head is cut half as fine as it could be: with that many scoring blocks the launch runs in rounds, and
   // blocks of a later one queue.  A pass of 8 layer-steps, in full and half: 128 heads x 1234 candidates (2 splits and 1) 395 and
@@ -323,7 +323,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   // 239, 293 and 271 (in one 256, 292); 48 x 1515 (5 and 3) 190 and 180, 241 and 229; but 40 x 1389 (5 and 3) 201 and 205, 24 x 1389
   // (9 and 5) 160 and 168.
   const bool half = g.n_cand > kLongList && heads > kFewHeads;
-  const int waiting = slices > 1 ? kMaxWaiting - heads * slices : half ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting;
+  auto most_waiting = [&]() { return slices > 1 ? kMaxWaiting - heads * slices : half ? (kMaxWaiting / heads + 1) / 2 * heads : kMaxWaiting; };
   const double bytes = (double)n_there * UNIT_BYTES + g.n_cand * kSummaryBytes;
   const bool home = !io.host_pool && little_excess(d, heads, bytes, false);
   int pps, n_splits, passes, rows;
@@ -336,7 +336,14 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
     n_splits = (n_att + pps - 1) / pps;
     size();
   };
-  cut(waiting);
+  cut(most_waiting());
+  // One to three heads whose blocks just miss being on their XCD all at once share the list among half as many: 3 heads x 1500
+  // candidates, G = 5, away in eight and at home in four, 10.6 and 9.3 us, 15.0 and 12.4 where most are corrected (one block a head,
+  // at home, 10.4 and 13.9); 2 x 1500, G = 8, 11.3 and 10.8, 15.7 and 14.0.
+  if (home && heads < kXcds / 2 && slices > kFewSlices && rows > kSlotsOfXcd && rows - slices / 2 <= kSlotsOfXcd) {
+    slices /= 2;
+    cut(most_waiting());
+  }
   // As many blocks as fit, two to a compute unit, where the heads are many and the launch runs in rounds: with fewer, the dispatcher
   // puts two on some units and none on others, according to which scoring blocks have just ended, and those of a launch that is
   // bound by its bytes take that much longer.  G = 4, 65 pages, a block a unit and as many as fit (few corrected; most): 80 heads x 480 candidates
@@ -357,7 +364,7 @@ bool launch_layer(const Dims& d, const LayerIO& io, Geom g, hipStream_t st) {
   const bool cut_finer = n_att <= kShortStream ? n_att >= kEnoughToCut && !loose : blocks_now > kLooseBlocks && blocks_now < kComputeUnits;
   if (slices == 1 && g.n_cand < kLongList && !io.host_pool && cut_finer && (long)heads * rows > kLayerResident) {
     cut(std::min(kLayerResident, heads * std::max(n_splits, n_att / kPagesEach)));
-    if ((long)heads * rows > kLayerMaxBlocks) cut(waiting);
+    if ((long)heads * rows > kLayerMaxBlocks) cut(most_waiting());
   }
   LayerLaunch l;
   l.home = heads_at_home(d, heads, rows, bytes);

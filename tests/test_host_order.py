@@ -346,5 +346,17 @@ def test_the_poolings_beside_the_methods_have_kernels_of_their_own(play, pooling
     assert "select_kernelILi4ELb" + ("1" if pooling == 0 else "0") + "E" in op[1]
 
 
+@pytest.mark.parametrize("heads", [1, 2, 3])
+@pytest.mark.parametrize("candidates,selecting,home", [
+    (1440, 8, True),                                         # 2 + 45 + 8 + 9 blocks are an XCD's slots
+    (1441, 4, True), (1568, 4, True),                        # 46 to 49 scoring blocks: half as many select
+    (1569, 8, False),                                        # nor would those fit
+])
+def test_few_heads_share_a_list_among_as_many_blocks_as_fit_their_xcd(play, heads, candidates, selecting, home):
+    (op,) = _decode(play, heads, candidates, 65, n_q_heads=5)
+    assert ("home_layer_kernel" in op[1]) == home
+    assert int(op[4].split("x")[1]) == 2 + -(-candidates // 32) + selecting + 9
+
+
 if __name__ == "__main__":
     print(json.dumps(_play(*json.loads(sys.argv[1]))))
