@@ -1058,6 +1058,12 @@ __device__ __forceinline__ Selected select_group(const StepArgs& a, int head, in
     done = topk_items<!MEAN, U>(key, rows, 0, n, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
       if (__builtin_amdgcn_inverse_ballot_w64(chosen)) put(pos, id(u));
     });
+    // (few keys of the last bin in a short list: still shorter than by way of block_topk -- 70 candidates, 48 wanted, most of them with
+    // next to no weight, 8.6 and 7.1 us a layer-step)
+    if (MEAN && U == 1 && __builtin_expect(!done, 0))
+      done = topk_items<true, U>(key, 1, 0, n, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
+        if (__builtin_amdgcn_inverse_ballot_w64(chosen)) put(pos, id(u));
+      });
   } else if (!last) {
     done = topk_items<!MEAN, U>(key, rows, 0, j1 - j0, kk, bins, nw, sm, [&](int u, unsigned long long chosen, int pos) {
       if (__builtin_amdgcn_inverse_ballot_w64(chosen)) {

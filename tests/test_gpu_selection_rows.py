@@ -67,3 +67,20 @@ def test_alone_and_shared(G, n_cand, heads):
     want = 2 + _best(score[0], k)
     assert np.array_equal(ids, np.broadcast_to(want, ids.shape)) and np.array_equal(many, np.broadcast_to(want, many.shape))
     assert np.array_equal(score, np.broadcast_to(score[0], score.shape)) and np.array_equal(scores, np.broadcast_to(score[0], scores.shape))
+
+
+@pytest.mark.parametrize("n_cand,k", [(61, 48), (70, 48), (100, 48), (130, 70)])
+def test_weights_next_to_nothing(n_cand, k):
+    """A few pages have it all, and fewer than are chosen: the others' scores, of which there are 64 and fewer or more, are below the last
+    counter's reach."""
+    values = 0.15 + 0.4 * (np.arange(n_cand) * 29 % 64) / 64.0
+    high = np.arange(0, n_cand, 2)[:k - 8]
+    values[high] = 8.0
+    K = torch.zeros((1, (n_cand + 4) * 32, 1, 128), dtype=torch.bfloat16, device="cuda")
+    K[0, 64:(n_cand + 2) * 32, 0, 0] = torch.tensor(values, device="cuda").to(torch.bfloat16).repeat_interleave(32)
+    q = torch.zeros((1, 4, 128), dtype=torch.bfloat16, device="cuda")
+    q[..., 0] = torch.tensor([32.0, 31.0, 31.5, 32.5], device="cuda")
+    ids, score = _select(4, n_cand, k, K, q)
+    low = np.delete(score[0], high)
+    assert (low < 2.0 ** -32).all() and len(np.unique(low)) > 2
+    assert np.array_equal(ids[0], 2 + _best(score[0], k))
