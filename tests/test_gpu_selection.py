@@ -22,6 +22,7 @@ def _best(score, k):
     (4, 2, 1, 64, 63),         # one wave
     (1, 1, 1, 513, 40),        # one block: two rows, the second with one candidate
     (4, 2, 1, 1537, 97),       # four rows
+    # (of more than eight heads; with two, both of these are shared, and test_gpu_selection_rows.py has them with nine)
     (5, 1, 2, 1880, 31),       # 9400 numerators: the most that one block takes
     (5, 1, 2, 1881, 31),       # shared by eight blocks, every key handed on
     (2, 3, 1, 4096, 33),       # eight rows

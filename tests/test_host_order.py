@@ -358,5 +358,29 @@ def test_few_heads_share_a_list_among_as_many_blocks_as_fit_their_xcd(play, head
     assert int(op[4].split("x")[1]) == 2 + -(-candidates // 32) + selecting + 9
 
 
+@pytest.mark.parametrize("heads,G,candidates,selecting,config", [
+    (8, 8, 1024, 1, {}), (8, 8, 1025, 4, {}), (8, 3, 2048, 1, {}), (8, 3, 2049, 8, {}), (8, 5, 1024, 1, {}), (8, 5, 1025, 4, {}),   # rows times G of 16
+    (8, 4, 2048, 1, {}), (8, 4, 2049, 8, {}), (8, 2, 4096, 1, {}), (8, 2, 4097, 16, {}),                                            # the registers
+    (9, 5, 1880, 1, {}), (9, 5, 1881, 8, {}), (9, 8, 1175, 1, {}), (9, 8, 1176, 4, {}),                                             # more than eight heads
+    (8, 8, 1175, 1, dict(select_pooling=2)), (8, 8, 1176, 4, dict(select_pooling=2)),                                               # other poolings
+    (8, 8, 1175, 1, dict(placement=1)), (8, 8, 1176, 4, dict(placement=1)),                                                         # a host pool
+])
+def test_how_many_blocks_have_a_list(play, heads, G, candidates, selecting, config):
+    (op,) = _decode(play, heads, candidates, 33, call="select", n_q_heads=G, **config)
+    rows = int(op[4].split("x")[1])
+    assert "step_kernel" in op[1] and rows - selecting in [-(-candidates // (32 * passes)) for passes in (1, 2, 4)]
+
+
+@pytest.mark.parametrize("heads,G,candidates,home,rows", [
+    (7, 5, 1100, True, 2 + 35 + 4 + 9),                                                                              # one pass a scoring block fits
+    (6, 5, 1800, True, 2 + 29 + 8 + 9), (4, 7, 2000, True, 2 + 32 + 8 + 9), (7, 5, 1700, True, 2 + 27 + 8 + 9),      # two
+    (4, 4, 4000, True, 2 + 32 + 16 + 9),                                                                             # four
+    (4, 4, 2000, False, 2 + 63 + 1 + 9), (3, 5, 1800, False, 2 + 57 + 8 + 9),        # a block each; fewer than four heads: one pass, and away
+])
+def test_few_heads_with_shared_lists_come_home_by_more_passes(play, heads, G, candidates, home, rows):
+    (op,) = _decode(play, heads, candidates, 65, n_q_heads=G)
+    assert ("home_layer_kernel" in op[1], int(op[4].split("x")[1])) == (home, rows)
+
+
 if __name__ == "__main__":
     print(json.dumps(_play(*json.loads(sys.argv[1]))))
