@@ -70,7 +70,13 @@ int fkv_test_by_itself(fkv_ctx* ctx, int32_t layer, int32_t* count, int32_t* at_
  * context's next launch gets the number after `last`.  Host-side, no GPU work. */
 int fkv_test_launch_number(fkv_ctx* ctx, int32_t last);
 
-/* While on, kernels record 100 MHz phase timestamps of head 0 (read with FKV_DBG_TSTAMP). */
+/* While on, kernels record 100 MHz phase timestamps of head 0 (read with FKV_DBG_TSTAMP).  Of the 64 words these are
+ * written, by a block of the head each (by the last one to come there, where several do); the others keep what they held:
+ *    0  the first scoring block begins               1  its weights are out
+ *    2  a selecting block has its weights             5  the keys of all that may be chosen are there
+ *    8  the page ids are out
+ *   16  attention's first block begins               17  its first wave's pages are done
+ *   18  its waves are combined                       21  the head's output is out, or left to be made alone */
 int fkv_instrument_timestamps(fkv_ctx* ctx, int32_t on);
 
 #ifdef __cplusplus
