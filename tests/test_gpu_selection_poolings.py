@@ -97,3 +97,38 @@ def test_rows_in_use(G, n_cand, k, batch, pooling):
     assert np.array_equal(score, np.broadcast_to(s1[0], score.shape)) and np.array_equal(s1, np.broadcast_to(s1[0], s1.shape))
     want = _best(s1[0], k)
     assert np.array_equal(ids, np.broadcast_to(want, ids.shape)) and np.array_equal(one, np.broadcast_to(want, one.shape))
+
+
+@pytest.mark.parametrize("pooling", ["MaxS", "MeanQK", "MaxQ"])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("placement,layers", [
+    (0, 64), (0, 80),                                     # 277 MB of pages that the layers attend, 346: summaries, and pages too, read past the caches
+    (1, 1), (1, 64),                                      # the KV in a host pool
+])
+def test_the_layer_step_in_larger_contexts_and_with_a_host_pool(placement, layers, dtype, pooling):
+    """Three steps of one layer against a context of that layer alone in HBM: page ids and scores are the same, outputs up to how they are split."""
+    n_kv, G, ctx, k, tokens = 8, 2, 5000, 16, 3
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(layers + placement)
+    K, V = (torch.randn((1, ctx, n_kv, 128), dtype=dt, device="cuda", generator=gen) for _ in range(2))
+    q = [torch.randn((1, n_kv * G, 128), device="cuda", generator=gen).to(dt) for _ in range(tokens)]
+    new = [torch.randn((2, 1, n_kv, 128), device="cuda", generator=gen).to(dt) for _ in range(tokens)]
+    seen = []
+    for where, n_layers in ((placement, layers), (0, 1)):
+        g = fkv.FreeKV(n_layers=n_layers, batch=1, n_q_heads=n_kv * G, n_kv_heads=n_kv, max_ctx=ctx + 120, budget=1024, sink=256, window=256, tau=0.8,
+                       dtype=dtype, placement=where, select_pooling=pooling)
+        g.load_prefix(0, K, V)
+        out = torch.empty((tokens, 1, n_kv * G, 128), device="cuda")
+        steps = []
+        for t in range(tokens):
+            g.decode_step(0, q[t], new[t][0], new[t][1], out[t])
+            steps.append((g.debug_read(0, B.DBG_ACTIVE_IDS), g.debug_read(0, B.DBG_SCORES)[..., 8:156], g.debug_read(0, B.DBG_FLAGS)))
+        assert g.step_launches(0) == 1
+        g.flush()
+        g.health(0)
+        g.close()
+        seen.append((steps, out.cpu()))
+    for one, other in zip(seen[0][0], seen[1][0]):
+        assert all(np.array_equal(a, b) for a, b in zip(one, other))
+    assert (seen[0][1] - seen[1][1]).abs().max() <= 1e-4 * seen[1][1].abs().max()

@@ -382,5 +382,11 @@ def test_few_heads_with_shared_lists_come_home_by_more_passes(play, heads, G, ca
     assert ("home_layer_kernel" in op[1], int(op[4].split("x")[1])) == (home, rows)
 
 
+@pytest.mark.parametrize("placement,layers,kind", [(0, 1, 4), (0, 64, 5), (0, 80, 7), (1, 1, 4), (1, 64, 5)])
+def test_other_poolings_read_past_the_cache_by_the_same_rule(play, placement, layers, kind):
+    (op,) = [op for op in _decode(play, 1, 140, 33, n_layers=layers, n_q_heads=16, n_kv_heads=8, placement=placement, select_pooling=2) if "layer_kernel" in op[1]]
+    assert f"layer_kernelILi1ELi2ELb{placement}ELi{kind}EE" in op[1]
+
+
 if __name__ == "__main__":
     print(json.dumps(_play(*json.loads(sys.argv[1]))))
