@@ -84,21 +84,20 @@ static const int g_one_launch = knob("FKV_ONE_LAUNCH", -1);       // layer-step:
 
 static const int g_fuse = knob("FKV_FUSE", -1);
 
-// Selecting blocks of a head, a power of two.  One as long as it has the registers and not too much work: the exchanges of a shared
-// list (sums, then keys) are what sharing costs, about 1.5 us.  The work of a block that has the list alone is that of its rows of candidates
-// (one, two, four or eight per thread, by the code that there is) times the query heads, and what sharing saves grows with it.  Layer-steps in us,
-// alone and shared as below.  8 heads, work of 8: 4000 candidates, G = 1, 10.8 and 10.7; 12: 2000, G = 3, 8.8 and 8.9; 16: 992, G = 8, 9.5 and 9.9, 1200, G = 4,
-// 8.5 and 8.4, 1700 9.2 and 8.7, but 1 x 1700 8.5 and 8.9; 20: 1200, G = 5, 9.5 and 9.0; 24: 1200, G = 6, 10.2 and 9.4, 2200, G = 3, 11.5 and 9.1; 28: 1040, G = 7, 11.2 and
-// 9.8 (most corrected, 14.9 and 13.5); 32: 1040, G = 8, 11.8 and 10.2.  Fewer heads: 1 x 1100, G = 8, 11.4 and 9.9; 3 x 1400, G = 6, 10.2 and 9.4; 6 x
-// 1800, G = 5, 10.0 and 9.2.  With more heads it depends on what else the launch has to do -- 16 x 1100, G = 5, most
-// corrected, 15.8 and 16.1, 1200, G = 6, 12.0 and 11.9; 32 x 2100, G = 3, 18.8 and 20.2, x 2500 20.1 and 18.8 -- and two blocks a head are no better than one
-// (48 x 1300, G = 6, 20.1 and 20.2): there the list stays with one block a little longer, and so it does under the other poolings, which
-// were not looked at again, and with the KV in a host pool, where the link decides
-// (8 x 1100, G = 8, 23.7 and 23.4; the same launch takes between 27 and 31 from one process to the next, 4 x 2500, G = 3).
-// A list that is shared is cut fine, since every phase
-// but the exchanges gets shorter, as long as the blocks that wait for each other stay a small part of the launch: 8 heads, G = 4,
-// in 4, 8, 16 blocks: 2300 candidates 10.6, 9.6, 10.1; 4000: 13.1, 12.0, 11.7; 8160: 17.8, 15.9, 15.2; 2016, G = 8, 12.5, 12.0, 13.3; but 16 heads
-// x 1200, G = 6, 11.9, 12.0, 12.0.
+// Selecting blocks of a head, a power of two.  One as long as it has the registers and not too much work: a shared list costs about
+// 1.5 us for its exchanges (sums, then keys).  The work of a block that has the list alone is its rows of candidates per thread (one, two,
+// four or eight, by the code that there is) times the query heads, and what sharing saves grows with it.  Layer-steps in us, alone and shared:
+// - up to kFewShared heads, the method's pooling, KV in HBM: alone up to kLightWork rows times G.  At 12 and 16: 8 heads x 2000 candidates,
+//   G = 3, 8.8 and 8.9; 8 x 992, G = 8, 9.5 and 9.9; 8 x 1515, G = 4, 8.6 and 8.6.  At 20, 24 and 32: 8 x 1200, G = 5, 9.5 and 9.0; 8 x 1200,
+//   G = 6, 10.2 and 9.4; 6 x 1800, G = 5, 10.0 and 9.2; 8 x 1040, G = 8, 11.8 and 10.2; 1 x 1100, G = 8, 11.4 and 9.9.  The line is on the safe
+//   side: 8 x 1700, G = 4, 9.2 and 8.7, and 8 x 2300, G = 2, 10.0 and 8.7, would gain, 1 x 1700, G = 4, 8.5 and 8.9, would not.
+// - otherwise alone up to kMaxAloneWork weights.  With more heads it depends on what else the launch has to do: 16 x 2500, G = 3, 14.8
+//   and 13.4, 24 x 1500, G = 5, 15.8 and 14.7, but 16 x 1100, G = 5, most corrected, 15.8 and 16.1, 32 x 2100, G = 3, 18.8 and 20.2, and in two
+//   blocks a head 48 x 1300, G = 6, 20.1 and 20.2.  With the KV in a host pool the link decides (8 x 1100, G = 8, 23.7 and 23.4).  The other
+//   poolings were not looked at again.
+// A list that is shared is cut fine, since every phase but the exchanges gets shorter, as long as the blocks that wait for each other stay a
+// small part of the launch: 8 heads, G = 4, in 4, 8, 16 blocks: 2300 candidates 10.6, 9.6, 10.1; 4000: 13.1, 12.0, 11.7; 8160: 17.8, 15.9,
+// 15.2; 2016, G = 8, 12.5, 12.0, 13.3; but 16 heads x 1200, G = 6, 11.9, 12.0, 12.0, and 2 x 4000, G = 4, in 8 and 16, 10.6 and 11.4.
 constexpr int kLightWork = 16, kFewShared = 8, kMaxAloneWork = 9400, kFineSlice = 320, kMaxFineBlocks = 128, kLongList = 1024, kFewHeads = 40, kFewSlices = 4;
 static int selection_slices(const Dims& d, const Geom& g, bool host_pool) {
   const int n = g.n_cand, G = d.G, heads = d.batch * d.n_kv, regs = sel_regs_alone(G);
@@ -114,17 +113,18 @@ static int selection_slices(const Dims& d, const Geom& g, bool host_pool) {
 static const int g_home = knob("FKV_HOME", -1);                   // 0 never, 1 always
 
 // A word that stays in the L2 it was written to is seen after 0.22 us, through memory after 0.3 to 0.5, and a block reads its
-// head's 30 KB of weights from the L2 at several times the rate; an exchange of a layer-step takes 0.3 to 0.8 us less.  Layer-steps
-// of G = 4, a head's blocks adjacent and on one XCD: 8 heads x 992 candidates 9.1 and 8.3 us, 2016 (G = 8) 15.4 and 12.7, 16 heads x 992
-// 10.7 and 9.5, 64 25.6 and 23.8 (31.0 and 28.5 where most are corrected).
-// Where the heads do not go round evenly some XCDs have more to read than if everything were spread, at about 1 MB a us, so what
-// decides is that excess over an even share.  Adjacent and at home (few corrected; most), MB too much: 28 heads x 992 candidates x 33 pages,
-// 0.5, 12.0 and 11.1, 17.1 and 15.4; 12 x 992 x 65, 0.8, 9.9 and 9.3, 15.1 and 13.7; 76 x 480 x 65, 0.7, 26.1 and 24.5, 30.7 and 28.9; but 12 x 100 x 129,
-// 0.92, 9.5 and 10.8, 12.1 and 12.7; 28 x 100 x 129, 0.92, 13.2 and 14.4, 16.3 and 16.9; 9 x 992 x 129, 2.3, 10.2 and 12.2, 16.5 and 16.1.  With fewer than
-// 8 heads, where an XCD has one and others none, there is more room: 4 x 992 x 65, 0.8, 8.7 and 8.3, 13.4 and 12.1; 1 x 992 x 65, 1.4, 8.3 and 7.9, 12.9 and
-// 11.7; 4 x 992 x 129, 1.3, 8.9 and 9.0, 14.3 and 13.4; but 1 x 992 x 193, 3.2, 9.0 and 9.8, 15.4 and 14.9; 1 x 992 x 257, 4.1, 9.5 and 11.7, 16.6 and 16.7.
-// Attention by itself has one exchange to gain by: 12 x 33 pages, 0.3, 5.8 and 5.4; 4 x 65, 0.5, 6.0 and 5.8; 1 x 65, 0.9, 5.9 and 5.6; but 12, 20 and 28 x 65,
-// 0.5, 7.2 and 7.3, 7.9 and 8.1, 9.2 and 9.4; 12 x 129, 1.1, 9.1 and 10.6; 4 x 129, 1.1, 8.2 and 8.5.
+// head's 30 KB of weights from the L2 at several times the rate; an exchange of a layer-step takes 0.3 to 0.8 us less.  Where the heads do not
+// go round evenly some XCDs have more to read than if everything were spread, at about 1 MB a us.  So what decides is that excess over an
+// even share: kHomeExcess bytes, with fewer than 8 heads, where an XCD has one and others none, kFewHeadsRoom times that; for attention by
+// itself, which has one exchange to gain by, kHomeExcessAttn.  Layer-steps in us (G = 4; few heads corrected; most), a head's blocks adjacent
+// and on one XCD, with the excess in MB:
+// - none: 8 heads x 992 candidates 9.1 and 8.3; 16 x 992 10.7 and 9.5; 64 x 992 25.6 and 23.8, 31.0 and 28.5; 8 x 2016, G = 8, 15.4 and 12.7;
+// - up to 0.9: 28 x 992 x 33 pages, 0.5, 12.0 and 11.1, 17.1 and 15.4; 12 x 992 x 65, 0.8, 9.9 and 9.3, 15.1 and 13.7; 76 x 480 x 65, 0.7, 26.1
+//   and 24.5, 30.7 and 28.9; but 12 x 100 x 129, 0.92, 9.5 and 10.8, 12.1 and 12.7; 9 x 992 x 129, 2.3, 10.2 and 12.2, 16.5 and 16.1;
+// - few heads, up to 2.0: 1 x 992 x 65, 1.4, 8.3 and 7.9, 12.9 and 11.7; 4 x 992 x 129, 1.3, 8.9 and 9.0, 14.3 and 13.4; but 1 x 992 x 193, 3.2,
+//   9.0 and 9.8, 15.4 and 14.9;
+// - attention by itself, up to 0.45 (few heads 1.0): 12 x 33 pages, 0.3, 5.8 and 5.4; 1 x 65, 0.9, 5.9 and 5.6; but 12 x 65, 0.5, 7.2 and 7.3;
+//   12 x 129, 1.1, 9.1 and 10.6; 4 x 129, 1.1, 8.2 and 8.5.
 // With up to two heads to an XCD the launch also has to be there all at once (14 heads x 480 x 129, 0.6 MB, 11.3 and 12.3); with more it
 // runs in rounds either way.
 constexpr double kHomeExcess = 0.9e6, kHomeExcessAttn = 0.45e6, kFewHeadsRoom = 2.2;
@@ -166,13 +166,12 @@ bool blocks_by_xcd(uint32_t* where) {
 
 // Passes of a scoring block: a launch runs in ceil(blocks / resident blocks) rounds, and blocks of a later round (the
 // selection and attention come last) queue behind the scoring blocks.  The passes that give the fewest rounds -- one, the
-// whole launch resident at once, where the shape allows -- and among those the fewest (most blocks).  Where fewer than eight heads
-// are to be at home, it is an XCD's slots that count: there the launch has to be resident all at once (heads_at_home), and where a
-// list is shared, with the exchanges that this takes, that gains more than a pass more costs.  Layer-steps in us, one pass a block and away, two or four and at home: 4 heads x
-// 2000 candidates, G = 7, 11.2 and 10.7; 6 x 1800, G = 5, 10.9 and 9.2; 6 x 3000, G = 4, 12.8 and 10.8; 4 x 4000 12.5 and 11.4; but 4 x 2000, G = 4, not shared, 9.2 and
-// 9.3; 2 x 4000, which have too much to read for one XCD each, 11.3 and 12.5 (heads on less than half of the XCDs are left as they were: 2 x 1700,
-// G = 8, 10.7 and 10.4).
-// home: they would be, and the link to a host pool does not decide.
+// whole launch resident at once, where the shape allows -- and among those the fewest (most blocks).  Where four to seven heads are to be at
+// home and share their lists, it is an XCD's slots that count: there the launch has to be resident all at once (heads_at_home), and with a
+// shared list's exchanges that gains more than a pass more costs.  Layer-steps in us, one pass a block and away, two or four and at home: 4 heads
+// x 2000 candidates, G = 7, 11.2 and 10.7; 6 x 1800, G = 5, 10.9 and 9.2; 6 x 3000, G = 4, 12.8 and 10.8; 4 x 4000 12.5 and 11.4; but 4 x 2000,
+// G = 4, not shared, 9.2 and 9.3; 2 x 4000, which have too much to read for one XCD each, 11.3 and 12.5.
+// home: the heads would be, and the link to a host pool does not decide.
 static int scoring_passes(const Dims& d, const Geom& g, int slices, int other_rows, int resident, bool home) {
   if (g_min_passes > 0) return g_min_passes;
   const long heads = (long)d.batch * d.n_kv;
